@@ -331,23 +331,6 @@ size_t gptq_prepare_workspace_bytes(int64_t K)
     return 2 * align256((size_t)K * K * 4) + align256((size_t)K * K * 2) + align256((size_t)NB * NB * 4) + align256((size_t)K * 4) + 256;
 }
 
-// H = (accumulate ? H : 0) + Xr^T Xr for rotated calibration rows Xr [T, K] (fp32, row-major)
-hipError_t launch_gptq_hessian_product(const float* Xr, int64_t T, int64_t K, float* H, bool accumulate, hipStream_t st)
-{
-    GemmF32 g{};
-    g.C = H;
-    g.A = Xr;
-    g.B = Xr;
-    g.ldc = g.lda = g.ldb = K;
-    g.m = (int)K;
-    g.n = (int)K;
-    g.k = (int)T;
-    g.alpha = 1.0f;
-    g.beta = accumulate ? 1.0f : 0.0f;
-    g.transA = 1;
-    return gemm_f32(g, 1, st);
-}
-
 hipError_t launch_gptq_prepare(const float* H, int64_t K64, float damp, bool use_order, int* perm, float* U, void* workspace,
                                hipStream_t st)
 {

@@ -268,6 +268,25 @@ def test_hessian_accumulation_matches_the_fp64_product(fp4, oracle, b):
         assert np.array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("T,K,b", [(1, 2, 1), (63, 130, 1), (65, 140, 1), (64, 128, 128), (200, 144, 16), (129, 448, 64), (1100, 384, 128), (2300, 640, 32)])
+def test_hessian_tiles_and_split_rows(fp4, oracle, T, K, b):
+    """Tile edges (K below, at and beyond a tile of 128; K not a multiple of eight, where rows are not 16-byte aligned), row
+    counts around a stage of 64, and enough rows for the tiles' sums to be split into parts; fresh and accumulated.
+    Bound: fp32 rounding of T terms, 2e-5 of the Cauchy-Schwarz scale at 700 of them as above, growing with their root."""
+    import torch
+    xb = inputs.RECIPES[6].x(T, K, salt=300 + T)
+    X = oracle.rotate(xb, b).astype(np.float64)
+    want = X.T @ X
+    say(f"gptq hessian T={T} K={K} b={b}")
+    H = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(xb), b)
+    H2 = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(xb), b, H.clone())
+    torch.cuda.synchronize()
+    scale = np.sqrt(np.outer(np.diag(want), np.diag(want)))
+    for got, times in ((np_(H).astype(np.float64), 1), (np_(H2).astype(np.float64), 2)):
+        assert np.all(np.abs(got - times * want) <= 2e-5 * times * max(1.0, (T / 700) ** 0.5) * scale)
+        assert np.array_equal(got, got.T)
+
+
 def test_calibration_rows_to_codes_entirely_on_the_gpu(fp4, oracle, gptq):
     import torch
     N, K, T, b = 64, 512, 1536, 32
