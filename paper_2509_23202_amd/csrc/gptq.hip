@@ -241,7 +241,7 @@ __global__ __launch_bounds__(64) void gptq_outer_kernel(GptqArgs a, int o, int o
         // push the block's errors onto the rest of the outer block
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            *reinterpret_cast<float4*>(&Es[row][part * 16 + 4 * v]) = make_float4(-ek[4 * v], -ek[4 * v + 1], -ek[4 * v + 2], -ek[4 * v + 3]);
+            *reinterpret_cast<float4*>(&Es[row][part * 16 + 4 * v]) = make_float4(ek[4 * v], ek[4 * v + 1], ek[4 * v + 2], ek[4 * v + 3]);
         __syncthreads();
         float ea[16];  // A operand of the 16 MFMAs of a column tile: row l16, terms 4 ks + q
 #pragma unroll
@@ -273,26 +273,31 @@ __global__ __launch_bounds__(64) void gptq_outer_kernel(GptqArgs a, int o, int o
         for (int c0 = b0 + kB; c0 < oe; c0 += 2 * kB) {  // two trips per iteration so that the buffers swap statically
             const bool second = c0 + kB < oe;
             if (second) fetch(c0 + kB, accn, un);
+            v4f sum[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) sum[t] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < 16; ++ks)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[ks], u[t][ks], acc[t], 0, 0, 0);
+                for (int t = 0; t < 4; ++t) sum[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[ks], u[t][ks], sum[t], 0, 0, 0);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (wlive[v]) a.wp[wrow[v] + c0 + 16 * t + l16] = acc[t][v];
+                    if (wlive[v]) a.wp[wrow[v] + c0 + 16 * t + l16] = acc[t][v] - sum[t][v];
             if (!second) break;
             if (c0 + 2 * kB < oe) fetch(c0 + 2 * kB, acc, u);
 #pragma unroll
+            for (int t = 0; t < 4; ++t) sum[t] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
             for (int ks = 0; ks < 16; ++ks)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) accn[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[ks], un[t][ks], accn[t], 0, 0, 0);
+                for (int t = 0; t < 4; ++t) sum[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[ks], un[t][ks], sum[t], 0, 0, 0);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (wlive[v]) a.wp[wrow[v] + c0 + kB + 16 * t + l16] = accn[t][v];
+                    if (wlive[v]) a.wp[wrow[v] + c0 + kB + 16 * t + l16] = accn[t][v] - sum[t][v];
         }
         stash_block(cur ^ 1);
         __threadfence_block();  // the next block's working weights were written by other lanes of this wave
@@ -318,7 +323,7 @@ __global__ __launch_bounds__(256) void gptq_update_kernel(GptqArgs a, int u0, in
     // a lane holds rows 4q .. 4q+3 of column l16 of every 16 x 16 tile; c_end and the tile start are multiples of 64, so
     // a wave's 64 columns are in or out together
     const bool in = c0 + wc < c_end;
-    v4f acc[NT][NT];
+    v4f acc[NT][NT], old[NT][NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -326,7 +331,10 @@ __global__ __launch_bounds__(256) void gptq_update_kernel(GptqArgs a, int u0, in
             const int n = min(n0 + wr + i * 16 + 4 * q + v, a.N - 1);
             const float* src = a.wp + (int64_t)n * a.K + c0 + wc + l16;
 #pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j][v] = in ? src[j * 16] : 0.0f;
+            for (int j = 0; j < NT; ++j) {
+                old[i][j][v] = in ? src[j * 16] : 0.0f;
+                acc[i][j][v] = 0.0f;
+            }
         }
     float re[NL], ru[NL];
     auto fetch = [&](int r0) {
@@ -337,7 +345,7 @@ __global__ __launch_bounds__(256) void gptq_update_kernel(GptqArgs a, int u0, in
             // the columns
             const int te = idx % KC, xe = idx / KC;
             const int n = min(n0 + xe, a.N - 1);
-            re[it] = -a.err[(int64_t)n * kOuter + e0 + r0 + te];
+            re[it] = a.err[(int64_t)n * kOuter + e0 + r0 + te];
             const int x = idx % T, t = idx / T;
             ru[it] = (c0 + x < c_end) ? a.U[(int64_t)(u0 + r0 + t) * a.K + c0 + x] : 0.0f;
         }
@@ -375,7 +383,7 @@ __global__ __launch_bounds__(256) void gptq_update_kernel(GptqArgs a, int u0, in
             if (n >= a.N) continue;
             float* dst = a.wp + (int64_t)n * a.K + c0 + wc + l16;
 #pragma unroll
-            for (int j = 0; j < NT; ++j) dst[j * 16] = acc[i][j][v];
+            for (int j = 0; j < NT; ++j) dst[j * 16] = old[i][j][v] - acc[i][j][v];
         }
 }
 

@@ -4,13 +4,22 @@
 // triangular U with U^T U = A^-1 whose row j drives the update after column j.
 //
 // U is obtained without forming A^-1: factor A = R R^T with R UPPER triangular; then A^-1 = R^-T R^-1 and U = R^-1.
-// With J the index reversal, J A J = L L^T is an ordinary (lower) Cholesky factorization and R = J L J, so the work is
-//   1. gather  At[i][j] = A[K-1-i][K-1-j]                       (one pass, applies order and dampening)
-//   2. blocked Cholesky of At in place, 64 columns at a time:   diagonal block factored (and inverted) by one wave,
-//      panel  L21 = A21 L11^-T  as a product with that inverse, trailing update  A22 -= L21 L21^T
-//   3. V = L^-1 by recursive doubling over the diagonal blocks: [L11 0; L21 L22]^-1 = [V11 0; -V22 L21 V11, V22]
-//   4. U[i][j] = V[K-1-i][K-1-j]
-// All in fp32; the products run on one tiled kernel on the fp32 MFMA.
+// With J the index reversal, J A J = L L^T is an ordinary (lower) Cholesky factorization, R = J L J and U = J L^-1 J.
+//
+// L^-1 comes out of the factorization itself: the row operations that turn J A J into L^T turn the identity beside it into
+// L^-1 (Gauss elimination of [A | I]).  Block column k of A is finished when that of I begins to fill, so ONE square
+// matrix M holds both: after step k its block columns 0 .. k are those of the right-hand side, the others those of A.
+// Step k of K / 128, with D = the inverse of the diagonal block's Cholesky factor:
+//   panel    L_ik = M_ik D^T  (i > k, into a scratch panel),  M_kj <- D M_kj  (j < k),  M_kk <- D
+//   update   M_ij <- M_ij - L_ik X_j  for all i > k, j <= i, where X_j = M_kj (j <= k; M_ik counts as zero) or L_jk^T (j > k)
+// and the first workgroup of the update takes the next diagonal block: it updates it, factors it and inverts the factor
+// while the others work, so the only serial chain of the method -- K columns, one behind the other -- runs beside the
+// products instead of between them.  Two launches per 128 columns.  The diagonal block is treated by the same elimination,
+// 16 columns at a time.  All in fp32, products on the fp32 MFMA (v_mfma_f32_16x16x4_f32).
+//
+// Bound by that chain: [4096, 4096] takes 1.5 ms, per 128 columns 8.7 us of panel and 31 - 40 us of update, of which the
+// diagonal block is 4 us of loads, 4 us of product and 19 us of elimination.  (6.3 ms with 64-column blocks, one wave per
+// diagonal block between the products (47 us each) and an inversion by recursive doubling behind the factorization.)
 #include "device_util.hpp"
 #include "internal.hpp"
 
@@ -20,413 +29,534 @@
 namespace fp4mr {
 namespace {
 
-constexpr int NB = 64;  // block size of the factorization
+constexpr int NB = 128;        // block size of the elimination
+constexpr int SB = 16;         // columns per step inside a diagonal block
+constexpr int NS = NB / SB;    // such steps
+constexpr int LD = NB + 16;    // LDS row of 128 values: 16 mod 64 banks, so the four k-rows of an MFMA operand do not meet
+constexpr int PW = 32;         // columns per workgroup of the panel kernel
+
+struct PrepArgs {
+    float* M;        // [Kp, Kp], lower block triangle used
+    float* LT;       // [NB, Kp]: the panel L_ik, contraction index first
+    float* DT;       // [NB, NB]: D transposed
+    int Kp;          // K rounded up to whole blocks; the padding is the identity
+    int nt;          // Kp / NB
+    int k;
+};
 
 // ---------------------------------------------------------------- ordering and gather
 
-// rank of column i in the order "descending diagonal, ties by ascending index"; perm[rank] = i.  (A diagonal with
-// NaNs does not rank into a permutation; perm is pre-filled with the identity so that every entry is at least valid.)
-__global__ __launch_bounds__(256) void order_kernel(const float* diag, int K, int use_order, int* perm)
+// the diagonal as a contiguous array; perm = identity (a diagonal with NaNs does not rank into a permutation below: every
+// entry is at least valid)
+__global__ __launch_bounds__(256) void diag_kernel(const float* H, int K, float* diag, int* perm)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= K) return;
+    diag[i] = H[(int64_t)i * K + i];
+    perm[i] = i;
+}
+
+// rank of column i in the order "descending diagonal, ties by ascending index", counted by one wave; perm[rank] = i.
+// The last workgroup sums the diagonal (in double, in a fixed order) for its mean instead.
+__global__ __launch_bounds__(256) void order_kernel(const float* diag, int K, int use_order, int* perm, float* mean)
+{
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ double part[256];
+        double s = 0.0;
+        for (int i = threadIdx.x; i < K; i += 256) s += (double)diag[i];
+        part[threadIdx.x] = s;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *mean = (float)(part[0] / (double)K);
+        return;
+    }
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (i >= K || !use_order) return;
     const float di = diag[i];
-    int rank = i;
-    if (use_order) {
-        rank = 0;
-        for (int j = 0; j < K; ++j) {
-            const float dj = diag[j];
-            rank += (dj > di) || (dj == di && j < i);
+    int rank = 0;
+    for (int j = lane; j < K; j += 64) {
+        const float dj = diag[j];
+        rank += (dj > di) || (dj == di && j < i);
+    }
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) rank += __shfl_xor(rank, s);
+    if (lane == 0) perm[min(rank, K - 1)] = i;
+}
+
+// M[i][j] = H[perm[K-1-i]][perm[K-1-j]] + (i == j) damp * mean up to the end of row i's diagonal block.  One workgroup per row:
+// the row of H goes through LDS, so that memory is read and written in order.
+__global__ __launch_bounds__(256) void gather_kernel(const float* H, const int* perm, const float* mean, float damp, int K, int Kp, float* M)
+{
+    extern __shared__ float row[];
+    const int i = blockIdx.x;
+    const int end = (i / NB + 1) * NB;
+    if (i < K) {
+        const float* src = H + (int64_t)min(max(perm[K - 1 - i], 0), K - 1) * K;
+        for (int j = threadIdx.x; j < K; j += 256) row[j] = src[j];
+        __syncthreads();
+        const float add = damp * (*mean);
+        for (int j = threadIdx.x; j < end; j += 256) {
+            float v = 0.0f;
+            if (j < K) v = row[min(max(perm[K - 1 - j], 0), K - 1)];
+            if (i == j) v += add;
+            M[(int64_t)i * Kp + j] = v;
+        }
+    } else {
+        for (int j = threadIdx.x; j < end; j += 256) M[(int64_t)i * Kp + j] = (i == j) ? 1.0f : 0.0f;
+    }
+}
+
+// U[i][j] = V[K-1-i][K-1-j] on and above the diagonal, 0 below
+__global__ __launch_bounds__(256) void reverse_kernel(const float* V, int K, int Kp, float* U)
+{
+    const int i = blockIdx.x;
+    for (int j = threadIdx.x; j < K; j += 256)
+        U[(int64_t)i * K + j] = (j >= i) ? V[(int64_t)(K - 1 - i) * Kp + (K - 1 - j)] : 0.0f;
+}
+
+// ---------------------------------------------------------------- panel
+
+// A workgroup takes 32 columns of either half: rows k of M to the left of the diagonal block (B = M_kj as it lies), or rows of
+// M below it (B = M_ik^T, transposed on its way into LDS); out = D B, 128 x 32, one 32 x 32 piece per wave.
+__global__ __launch_bounds__(256) void panel_kernel(PrepArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float As[NB][LD];       // [contraction][row of D]
+    __shared__ float Bs[NB][PW + 16];                               // [contraction][column]
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int blk = blockIdx.x / (NB / PW), sub = (blockIdx.x % (NB / PW)) * PW;
+    const bool left = blk < a.k;
+    const int k0 = a.k * NB;
+    const int c0 = (left ? blk : blk + 1) * NB + sub;  // first column of M_kj, or first row of M_ik
+    float4 d[16];
+#pragma unroll
+    for (int it = 0; it < 16; ++it) d[it] = reinterpret_cast<const float4*>(a.DT)[it * 256 + tid];
+    float4 m[4];
+    if (left) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int idx = it * 256 + tid;  // 8 float4 per row of 32
+            m[it] = *reinterpret_cast<const float4*>(a.M + (int64_t)(k0 + idx / 8) * a.Kp + c0 + (idx % 8) * 4);
+        }
+    } else {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int idx = it * 256 + tid;  // 32 float4 per row of 128
+            m[it] = *reinterpret_cast<const float4*>(a.M + (int64_t)(c0 + idx / 32) * a.Kp + k0 + (idx % 32) * 4);
         }
     }
-    perm[min(rank, K - 1)] = i;
-}
-
-__global__ __launch_bounds__(256) void identity_kernel(int K, int* perm)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < K) perm[i] = i;
-}
-
-// the diagonal as a contiguous array, and its mean (summed in double, one workgroup)
-__global__ __launch_bounds__(256) void mean_diag_kernel(const float* H, int K, float* diag, float* out)
-{
-    __shared__ double part[256];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < K; i += 256) {
-        const float d = H[(int64_t)i * K + i];
-        diag[i] = d;
-        s += (double)d;
+#pragma unroll
+    for (int it = 0; it < 16; ++it) {
+        const int idx = it * 256 + tid;
+        *reinterpret_cast<float4*>(&As[idx / 32][(idx % 32) * 4]) = d[it];
     }
-    part[threadIdx.x] = s;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const int idx = it * 256 + tid;
+        const float v[4] = {m[it].x, m[it].y, m[it].z, m[it].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (left) Bs[idx / 8][(idx % 8) * 4 + e] = v[e];
+            else Bs[(idx % 32) * 4 + e][idx / 32] = v[e];
+        }
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
+    v4f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    const int wr = wave * 32;
+    // D is lower triangular: rows wr .. wr + 31 have nothing beyond contraction index wr + 31
+#pragma unroll 4
+    for (int ks = 0; ks < (wr + 32) / 4; ++ks) {
+        float x[2], y[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[i] = As[ks * 4 + q][wr + 16 * i + l16];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) y[j] = Bs[ks * 4 + q][16 * j + l16];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[j], acc[i][j], 0, 0, 0);
     }
-    if (threadIdx.x == 0) *out = (float)(part[0] / (double)K);
+    float* out = left ? a.M + (int64_t)k0 * a.Kp + c0 : a.LT + c0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) out[(int64_t)(wr + 16 * i + 4 * q + v) * a.Kp + 16 * j + l16] = acc[i][j][v];
 }
 
-// At[i][j] = H[perm[K-1-i]][perm[K-1-j]] + (i == j) damp * mean;  V = 0
-__global__ __launch_bounds__(256) void gather_kernel(const float* H, const int* perm, const float* mean, float damp, int K,
-                                                     float* At, float* V)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    const int i = blockIdx.y;
-    if (j >= K) return;
-    const int pi = min(max(perm[K - 1 - i], 0), K - 1), pj = min(max(perm[K - 1 - j], 0), K - 1);
-    float v = H[(int64_t)pi * K + pj];
-    if (i == j) v += damp * (*mean);
-    At[(int64_t)i * K + j] = v;
-    V[(int64_t)i * K + j] = 0.0f;
-}
+// ---------------------------------------------------------------- diagonal block
 
-// ---------------------------------------------------------------- diagonal block: Cholesky and inverse, one wave
+// The lower block triangle of a diagonal block in LDS: strip s (rows 16 s ..) holds its 16 (s + 1) columns at a row pitch
+// that puts the four row groups of an MFMA result into different banks.
+__device__ __forceinline__ int strip_pitch(int s) { return SB * (s + 1) + 4; }
+__device__ __forceinline__ int strip_base(int s) { return SB * (8 * s * (s + 1) + 4 * s); }
+constexpr int kStripFloats = SB * (8 * NS * (NS + 1) + 4 * NS);
 
-// A[k0:k0+nb, k0:k0+nb] (nb <= 64) -> L11 in place (lower), its inverse into V's diagonal block (lower) and into
-// Linv (dense 64 x 64 scratch, row-major, zero above the diagonal and beyond nb).  One wave; lane r keeps row r of the
-// block in registers, and what a step needs from another lane's row comes through v_readlane with a constant lane
-// index (both loops are fully unrolled), so the factorization itself touches no memory.  Rows beyond nb are rows of
-// the identity.  Entries right of the diagonal in a lane's registers are scratch: updated, never used.
+struct DiagLds {
+    float S[kStripFloats];
+    float X[2][SB][LD];  // per step p: [contraction][column]: columns of blocks j <= p hold X_j = D S_pj (j == p: D), the others L_jp^T
+};
+
 __device__ __forceinline__ float lane_value(float v, int lane)
 {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-__global__ __launch_bounds__(64) void diag_block_kernel(float* A, float* V, float* Linv, int K, int k0, int nb)
+// x (a finished 16 x 16 diagonal block of step p, as an MFMA leaves it: column l16, rows 4 q + v) -> D, its Cholesky factor's
+// inverse, into S and X; one wave.  Column j is row j as well (the block is symmetric), so the sixteen lanes of group j / 4
+// hold it with the row along the lanes; scaled by 1 / L_jj, without its upper part and with zeros in the other groups, it is
+// an operand whose only non-zero contraction index is j / 4, and one MFMA forms the outer product L_j L_j^T that the rest
+// of the block loses -- another one L_j V_j for the inverse in the making, whose row j the same lanes hold.  No value
+// travels between lanes but the pivot.
+__device__ __forceinline__ void factor_block(DiagLds& t, int p, v4f x)
 {
-    __shared__ float t[NB][NB + 1];
-    __shared__ float xs[NB][NB + 1];
-    const int r = threadIdx.x;
-    // memory is walked a row per step with the lane as the column (coalesced); LDS transposes to a row per lane
-#pragma unroll 16
-    for (int rr = 0; rr < NB; ++rr)
-        t[rr][r] = (rr < nb && r < nb && r <= rr) ? A[(int64_t)(k0 + rr) * K + k0 + r] : (rr == r ? 1.0f : 0.0f);
-    __syncthreads();
-    float row[NB];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    v4f w;
 #pragma unroll
-    for (int c = 0; c < NB; ++c) row[c] = t[r][c];
-    // right-looking Cholesky: after step j, row[j] holds L[r][j] for the lanes r >= j
+    for (int v = 0; v < 4; ++v) w[v] = (4 * q + v == l16) ? 1.0f : 0.0f;
+    const v4f zero = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const float d = sqrtf(lane_value(row[j], j));
-        row[j] = (r == j) ? d : row[j] / d;
-#pragma unroll
-        for (int c = j + 1; c < NB; ++c) row[c] = fmaf(-row[j], lane_value(row[j], c), row[c]);
-        __builtin_amdgcn_sched_barrier(0);  // (keeps the scheduler's regions, and the compile time, small)
-    }
-    // L goes to LDS (row per lane -> row-major) for the coalesced store and for the inversion
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < NB; ++c) t[r][c] = row[c];
-    __syncthreads();
-#pragma unroll 16
-    for (int rr = 0; rr < NB; ++rr)
-        if (rr < nb && r < nb && r <= rr) A[(int64_t)(k0 + rr) * K + k0 + r] = t[rr][r];
-    // inverse, column by column: lane c solves L x = e_c by forward substitution, its x in LDS column c.  Eight rows at a
-    // time: their sums over the rows already solved are eight independent chains fed by one read of x and two 16-byte
-    // broadcast reads of a transposed copy of L; then the 8 x 8 triangle in registers.  The loops over row groups and
-    // solved rows stay rolled: unrolled like the factorization they cost minutes of compile time.
-    __shared__ __attribute__((aligned(16))) float tT[NB][NB + 4];  // tT[u][i] = L[i][u]
-#pragma unroll
-    for (int c = 0; c < NB; ++c) tT[c][r] = row[c];
-    __syncthreads();
-    {
-        const int c = r;
-        for (int i0 = 0; i0 < NB; i0 += 8) {
-            float sum[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) sum[k] = (i0 + k == c) ? 1.0f : 0.0f;
-#pragma unroll 4
-            for (int u = 0; u < i0; ++u) {
-                const float xv = xs[u][c];
-                const float4 la = *reinterpret_cast<const float4*>(&tT[u][i0]);
-                const float4 lb = *reinterpret_cast<const float4*>(&tT[u][i0 + 4]);
-                sum[0] = fmaf(-la.x, xv, sum[0]);
-                sum[1] = fmaf(-la.y, xv, sum[1]);
-                sum[2] = fmaf(-la.z, xv, sum[2]);
-                sum[3] = fmaf(-la.w, xv, sum[3]);
-                sum[4] = fmaf(-lb.x, xv, sum[4]);
-                sum[5] = fmaf(-lb.y, xv, sum[5]);
-                sum[6] = fmaf(-lb.z, xv, sum[6]);
-                sum[7] = fmaf(-lb.w, xv, sum[7]);
-            }
-            float x[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-#pragma unroll
-                for (int k2 = 0; k2 < k; ++k2) sum[k] = fmaf(-tT[i0 + k2][i0 + k], x[k2], sum[k]);
-                x[k] = (i0 + k >= c) ? sum[k] / tT[i0 + k][i0 + k] : 0.0f;
-                xs[i0 + k][c] = x[k];
-            }
+    for (int j = 0; j < SB; ++j) {
+        constexpr int R = SB;
+        const int first = R * (j / 4);  // lane of row 0 of column j
+        const float d = lane_value(x[j % 4], first + j);
+        float y = __builtin_amdgcn_rsqf(d);
+        y = fmaf(0.5f * y, fmaf(-d * y, y, 1.0f), y);  // (one Newton step: 1 / sqrt(d) to an ulp)
+        const float r = w[j % 4] * y;
+        if (j + 1 < SB) {
+            const bool below = (unsigned)(lane - (first + j + 1)) < (unsigned)(R - 1 - j);
+            const float l = below ? x[j % 4] * y : 0.0f;
+            const float rj = (lane >> 4) == j / 4 ? r : 0.0f;
+            const v4f dx = __builtin_amdgcn_mfma_f32_16x16x4f32(l, l, zero, 0, 0, 0);
+            const v4f dw = __builtin_amdgcn_mfma_f32_16x16x4f32(l, rj, zero, 0, 0, 0);
+            x = x - dx;
+            w[j % 4] = (lane >> 4) == j / 4 ? r : w[j % 4];
+            w = w - dw;
+        } else {
+            w[j % 4] = (lane >> 4) == j / 4 ? r : w[j % 4];
         }
     }
-    __syncthreads();
-#pragma unroll 16
-    for (int rr = 0; rr < NB; ++rr) {
-        const float v = (rr < nb && r < nb && r <= rr) ? xs[rr][r] : 0.0f;
-        if (rr < nb && r < nb) V[(int64_t)(k0 + rr) * K + k0 + r] = v;
-        Linv[rr * NB + r] = v;
+    float* s = t.S + strip_base(p) + 4 * q * strip_pitch(p) + SB * p + l16;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const float d = (4 * q + v >= l16) ? w[v] : 0.0f;
+        s[v * strip_pitch(p)] = d;
+        t.X[p & 1][4 * q + v][SB * p + l16] = d;
     }
 }
 
-// ---------------------------------------------------------------- plain fp32 product
-// C[m x n] = beta C + alpha op(A) op(B),  op(A) = A[m x k] or A^T with A stored [k x m], op(B) = B[k x n] or B^T with
-// B stored [n x k]; row-major with leading dimensions.  A dense fp32 contraction, so it runs on the fp32 MFMA
-// (v_mfma_f32_16x16x4_f32: true fp32 products and sums): T x T tile per workgroup (T = 64, or 128 for big products),
-// one quarter of it per wave as (T/32)^2 MFMA tiles, k in chunks of 16 (32 for the wide tile) through LDS with the next chunk prefetched into registers; results are written after all
-// inputs of the tile have been read (a tile may overwrite its own A rows when n fits one tile).
-// Batches along blockIdx.z: pointers advance by the given strides.  ragged > 0 (the pairs of the triangular
-// inversion): batch z covers rows [z 2s + s, z 2s + 2s) of a matrix with `total` rows, s = ragged; its row count is
-// clipped to what exists, and so is k when k_is_rows is set.  lower_only skips tiles strictly above the diagonal.
-struct GemmF32 {
-    float* C;
-    const float* A;
-    const float* B;
-    int64_t ldc, lda, ldb;
-    int64_t sC, sA, sB;
-    int m, n, k;
-    float alpha, beta;
-    int transB, ragged, total, k_is_rows, lower_only;
-    int transA;  // A stored [k x m] (the product is A^T op(B))
-};
-
-template <int T>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g)
+// D (a row block of 16 with the contraction along the registers) times what `b` points to, 16 x 16: b[k] is the lane's column
+// at contraction index 4 q + k, so an MFMA takes the contraction in the order q, q + 4, ... on both sides
+__device__ __forceinline__ v4f times_d(const DiagLds& t, int p, const float (&b)[4])
 {
-    constexpr int KC = (T == 128) ? 32 : 16;  // k per chunk
-    // row pitch = 20 mod 64 banks: the fills along k (16 k-rows x 4 rows per wave store) hit 64 different banks, and the
-    // four k-rows of an MFMA operand read (16 consecutive floats each) overlap in 12 banks only
-    constexpr int LD = T + 20;
-    constexpr int WT = T / 2, NT = WT / 16;  // wave tile and its MFMA tiles per side
-    __shared__ float As[KC][LD];  // [k][row]
-    __shared__ float Bs[KC][LD];  // [k][col]
-    const int z = blockIdx.z;
-    int m = g.m, k = g.k;
-    if (g.ragged > 0) {
-        const int rows = min(g.ragged, g.total - (z * 2 * g.ragged + g.ragged));
-        if (rows <= 0) return;
-        m = rows;
-        if (g.k_is_rows) k = rows;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    const float4 d = *reinterpret_cast<const float4*>(t.S + strip_base(p) + l16 * strip_pitch(p) + SB * p + 4 * q);
+    v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x, b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d.y, b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d.z, b[2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d.w, b[3], acc, 0, 0, 0);
+    return acc;
+}
+
+// L_ip^T = D S_ip^T: contraction index 4 q + v, row l16 of block row i
+__device__ __forceinline__ v4f factor_rows(const DiagLds& t, int p, int i)
+{
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    const float4 s = *reinterpret_cast<const float4*>(t.S + strip_base(i) + l16 * strip_pitch(i) + SB * p + 4 * q);
+    const float b[4] = {s.x, s.y, s.z, s.w};
+    return times_d(t, p, b);
+}
+
+// The block in t.S (its Cholesky factor's inverse replaces it), eight waves.  Wave 0 walks the serial chain: the diagonal
+// block of 16 columns, its factor and inverse D, then only what the next diagonal block waits for.  The other seven take
+// the rest of step p meanwhile: the seven products with D (rows of the inverse to the left, columns of the factor
+// below), then the elimination of all later rows.
+__device__ __forceinline__ void invert_factor(DiagLds& t)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    auto block = [&](int i, int j) { return t.S + strip_base(i) + 4 * q * strip_pitch(i) + SB * j + l16; };
+    if (wave == 0) {
+        v4f x;
+        const float* s = block(0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = s[v * strip_pitch(0)];
+        factor_block(t, 0, x);
     }
-    const int r0 = blockIdx.y * T, c0 = blockIdx.x * T;
-    if (r0 >= m || c0 >= g.n) return;
-    if (g.lower_only && c0 > r0 + T - 1) return;
-    const float* A = g.A + (int64_t)z * g.sA;
-    const float* B = g.B + (int64_t)z * g.sB;
-    float* C = g.C + (int64_t)z * g.sC;
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
-    const int wr = (wave >> 1) * WT, wc = (wave & 1) * WT;  // this wave's corner inside the tile
-    v4f acc[NT][NT];
+    for (int p = 0; p < NS; ++p) {
+        float(*X)[LD] = t.X[p & 1];
+        __syncthreads();  // D of step p is there, step p - 1 has been eliminated everywhere
+        if (wave == 0) {
+            v4f x = v4f{0.f, 0.f, 0.f, 0.f};
+            if (p + 1 < NS) {
+                const v4f l = factor_rows(t, p, p + 1);
+                v4f acc = x;
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+                for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(l[v], l[v], acc, 0, 0, 0);
+                const float* s = block(p + 1, p + 1);
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    // the next chunk's elements travel from global memory into registers while the MFMAs of the current chunk run
-    constexpr int NL = KC * T / 256;
-    float ra[NL], rb[NL];
-    auto fetch = [&](int kk) {
-#pragma unroll
-        for (int it = 0; it < NL; ++it) {
-            const int idx = it * 256 + tid;
-            if (g.transA) {  // A stored [k x m]: consecutive threads along the row index (contiguous in memory)
-                const int rr = idx % T, kx = idx / T;
-                const int row = r0 + rr, kc = kk + kx;
-                ra[it] = (row < m && kc < k) ? A[(int64_t)kc * g.lda + row] : 0.0f;
-            } else {         // A stored [m x k]: consecutive threads along k
-                const int kx = idx % KC, rr = idx / KC;
-                const int row = r0 + rr, kc = kk + kx;
-                ra[it] = (row < m && kc < k) ? A[(int64_t)row * g.lda + kc] : 0.0f;
+                for (int v = 0; v < 4; ++v) x[v] = s[v * strip_pitch(p + 1)] - acc[v];
             }
-            if (g.transB) {  // B stored [n x k]
-                const int kx = idx % KC, cc = idx / KC;
-                const int col = c0 + cc, kc = kk + kx;
-                rb[it] = (col < g.n && kc < k) ? B[(int64_t)col * g.ldb + kc] : 0.0f;
-            } else {         // B stored [k x n]
-                const int cc = idx % T, kx = idx / T;
-                const int col = c0 + cc, kc = kk + kx;
-                rb[it] = (col < g.n && kc < k) ? B[(int64_t)kc * g.ldb + col] : 0.0f;
+            __syncthreads();
+            if (p + 1 < NS) factor_block(t, p + 1, x);
+        } else {
+            const int u = wave - 1;
+            if (u < p) {
+                float* s = block(p, u);
+                float b[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) b[v] = s[v * strip_pitch(p)];
+                const v4f r = times_d(t, p, b);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    s[v * strip_pitch(p)] = r[v];
+                    X[4 * q + v][SB * u + l16] = r[v];
+                }
+            } else {
+                const v4f r = factor_rows(t, p, u + 1);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) X[4 * q + v][SB * (u + 1) + l16] = r[v];
+            }
+            __syncthreads();
+            // one block column per wave (the last two, of two tiles and one, share a wave), two tiles at a time
+            for (int j = u; j < (u == NS - 2 ? NS : u + 1); ++j) {
+                float xj[4];
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) xj[ks] = X[ks * 4 + q][SB * j + l16];
+                // (the diagonal tile of row p + 1 is wave 0's)
+                for (int i = max(p + 1, j) + (j == p + 1 ? 1 : 0); i < NS; i += 2) {
+                    const int i2 = min(i + 1, NS - 1);
+                    float* s[2] = {block(i, j), block(i2, j)};
+                    const int pitch[2] = {strip_pitch(i), strip_pitch(i2)};
+                    v4f old[2], acc[2];
+                    float xi[2][4];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) old[e][v] = s[e][v * pitch[e]];
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks) xi[e][ks] = X[ks * 4 + q][SB * (e ? i2 : i) + l16];
+                        acc[e] = v4f{0.f, 0.f, 0.f, 0.f};
+                        // (block column p was the factor's and becomes the inverse's: it starts from zero)
+                        if (j == p) old[e] = acc[e];
+                    }
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(xi[e][ks], xj[ks], acc[e], 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) s[e][v * pitch[e]] = old[e][v] - acc[e][v];
+                }
             }
         }
+    }
+    __syncthreads();
+}
+
+// ---------------------------------------------------------------- update
+
+// Workgroup 0: the next diagonal block (lower 16 x 16 tiles of its product only, one strip of rows per wave), then
+// invert_factor; k == -1 starts the method with block 0 as it is.  The others: one 128 x 128 block each, a 64 x 32 piece per
+// wave, contraction 32 at a time through LDS with the next 32 in flight.  Every product is summed from zero and subtracted
+// once: with the accumulators started as M (one pass over registers less) each of the 32 MFMAs rounds at the size of M,
+// towards zero, and the factor came out eight times less accurate (2.7e-4 against 3.5e-5 at K = 4096, condition 1.7e4).
+__global__ __launch_bounds__(512, 4) void update_kernel(PrepArgs a)
+{
+    constexpr int KC = 32;
+    union Lds {
+        struct { float A[KC][LD]; float B[KC][LD]; } u;
+        float L[NB][LD];
+        DiagLds d;
     };
-    auto stash = [&]() {
+    __shared__ __attribute__((aligned(16))) Lds lds;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int k0 = a.k * NB, next = a.k + 1;
+    if (blockIdx.x == 0) {
+        __builtin_amdgcn_s_setprio(3);  // (the chain of the whole method: ahead of a neighbour's products on this compute unit)
+        float* const Md = a.M + (int64_t)next * NB * (a.Kp + 1);
+        // strips 0 .. 7 have 1 .. 8 tiles: a SIMD's two waves (w, w + 4) share nine
+        const int strip = wave < 4 ? wave : 11 - wave;
+        v4f old[NS];
 #pragma unroll
-        for (int it = 0; it < NL; ++it) {
-            const int idx = it * 256 + tid;
-            if (g.transA) As[idx / T][idx % T] = ra[it]; else As[idx % KC][idx / KC] = ra[it];
-            if (g.transB) Bs[idx % KC][idx / KC] = rb[it]; else Bs[idx / T][idx % T] = rb[it];
+        for (int j = 0; j < NS; ++j) {
+            old[j] = v4f{0.f, 0.f, 0.f, 0.f};
+            if (j <= strip) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) old[j][v] = Md[(int64_t)(SB * strip + 4 * q + v) * a.Kp + SB * j + l16];
+            }
+        }
+        if (a.k >= 0) {
+            v4f l[8];
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                const int idx = it * 512 + tid;
+                l[it] = *reinterpret_cast<const v4f*>(a.LT + (int64_t)(idx / 32) * a.Kp + next * NB + (idx % 32) * 4);
+            }
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                const int idx = it * 512 + tid;
+                *reinterpret_cast<v4f*>(&lds.L[idx / 32][(idx % 32) * 4]) = l[it];
+            }
+            __syncthreads();
+            v4f acc[NS];
+#pragma unroll
+            for (int j = 0; j < NS; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+            for (int ks = 0; ks < NB / 4; ++ks) {
+                const float* Lk = lds.L[ks * 4 + q] + l16;
+                const float x = Lk[SB * strip];
+#pragma unroll
+                for (int j = 0; j < NS; ++j)
+                    if (j <= strip) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, Lk[SB * j], acc[j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < NS; ++j) old[j] = old[j] - acc[j];
+            __syncthreads();
+        }
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+            if (j <= strip) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) lds.d.S[strip_base(strip) + (4 * q + v) * strip_pitch(strip) + SB * j + l16] = old[j][v];
+            }
+        __syncthreads();
+        invert_factor(lds.d);
+#pragma unroll 4
+        for (int idx = tid; idx < NB * NB; idx += 512) {
+            const int r = idx / NB, c = idx % NB;
+            Md[(int64_t)r * a.Kp + c] = (c <= r) ? lds.d.S[strip_base(r / SB) + (r % SB) * strip_pitch(r / SB) + c] : 0.0f;
+            a.DT[idx] = (c >= r) ? lds.d.S[strip_base(c / SB) + (c % SB) * strip_pitch(c / SB) + r] : 0.0f;  // [contraction r][row c]
+        }
+        return;
+    }
+    // block (i, j): rows next, next + 1, ... with i + 1 blocks each, the diagonal block of the first of them left out
+    const int p = (int)blockIdx.x - 1 < next ? blockIdx.x - 1 : blockIdx.x;
+    const int64_t n = p + (int64_t)next * (next + 1) / 2;
+    int i = (int)((sqrtf(8.0f * (float)n + 1.0f) - 1.0f) * 0.5f);
+    while ((int64_t)i * (i + 1) / 2 > n) --i;
+    while ((int64_t)(i + 1) * (i + 2) / 2 <= n) ++i;
+    const int j = (int)(n - (int64_t)i * (i + 1) / 2);
+    const float* A = a.LT + i * NB;
+    const float* B = (j > a.k) ? a.LT + j * NB : a.M + (int64_t)k0 * a.Kp + j * NB;
+    const int wr = (wave >> 2) * 64, wc = (wave & 3) * 32;
+    float* const C = a.M + (int64_t)(i * NB + wr + 4 * q) * a.Kp + j * NB + wc + l16;
+    v4f acc[4][2], old[4][2];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = old[x][y] = v4f{0.f, 0.f, 0.f, 0.f};
+    if (j != a.k) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) old[x][y][v] = C[(int64_t)(16 * x + v) * a.Kp + 16 * y];
+    }
+    v4f ra[2], rb[2];
+    auto fetch = [&](int kc) {
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const int idx = it * 512 + tid;
+            const int64_t off = (int64_t)(kc + idx / 32) * a.Kp + (idx % 32) * 4;
+            ra[it] = *reinterpret_cast<const v4f*>(A + off);
+            rb[it] = *reinterpret_cast<const v4f*>(B + off);
         }
     };
     fetch(0);
-    for (int kk = 0; kk < k; kk += KC) {
-        __syncthreads();  // the previous chunk's MFMA operands have been read
-        stash();
+    for (int kc = 0; kc < NB; kc += KC) {
         __syncthreads();
-        if (kk + KC < k) fetch(kk + KC);
-        // one MFMA = 16 x 16 outputs over 4 k: lane (l16, q) supplies op(A)[row l16][k q] and op(B)[k q][col l16]
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const int idx = it * 512 + tid;
+            *reinterpret_cast<v4f*>(&lds.u.A[idx / 32][(idx % 32) * 4]) = ra[it];
+            *reinterpret_cast<v4f*>(&lds.u.B[idx / 32][(idx % 32) * 4]) = rb[it];
+        }
+        __syncthreads();
+        if (kc + KC < NB) fetch(kc + KC);
 #pragma unroll
         for (int ks = 0; ks < KC / 4; ++ks) {
-            float a[NT], b[NT];
+            float x[4], y[2];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) a[i] = As[ks * 4 + q][wr + i * 16 + l16];
+            for (int e = 0; e < 4; ++e) x[e] = lds.u.A[ks * 4 + q][wr + 16 * e + l16];
 #pragma unroll
-            for (int j = 0; j < NT; ++j) b[j] = Bs[ks * 4 + q][wc + j * 16 + l16];
+            for (int e = 0; e < 2; ++e) y[e] = lds.u.B[ks * 4 + q][wc + 16 * e + l16];
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+                for (int f = 0; f < 2; ++f) acc[e][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[f], acc[e][f], 0, 0, 0);
         }
     }
-    __syncthreads();  // every thread of the tile has read its inputs
-    // a lane holds rows 4q .. 4q+3 of column l16 of every MFMA tile
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = r0 + wr + i * 16 + 4 * q + v;
-            if (row >= m) continue;
+        for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const int col = c0 + wc + j * 16 + l16;
-                if (col >= g.n) continue;
-                float* p = C + (int64_t)row * g.ldc + col;
-                *p = (g.beta == 0.0f) ? g.alpha * acc[i][j][v] : g.beta * (*p) + g.alpha * acc[i][j][v];
-            }
-        }
-    }
-}
-
-hipError_t gemm_f32(const GemmF32& g, int batches, hipStream_t st)
-{
-    if (g.m <= 0 || g.n <= 0 || batches <= 0) return hipSuccess;
-    // the wide tile for products with enough tiles of it to fill the chip and enough k to pay for its larger fills (never
-    // the in-place panel, whose n is one narrow tile, nor the rank-64 trailing updates, which want many small tiles)
-    if (g.m >= 1024 && g.n >= 1024 && g.k >= 256) {
-        const dim3 grid((unsigned)((g.n + 127) / 128), (unsigned)((g.m + 127) / 128), (unsigned)batches);
-        hipLaunchKernelGGL(gemm_f32_kernel<128>, grid, dim3(256), 0, st, g);
-    } else {
-        const dim3 grid((unsigned)((g.n + 63) / 64), (unsigned)((g.m + 63) / 64), (unsigned)batches);
-        hipLaunchKernelGGL(gemm_f32_kernel<64>, grid, dim3(256), 0, st, g);
-    }
-    return hipGetLastError();
-}
-
-// U[i][j] = V[K-1-i][K-1-j] on and above the diagonal, 0 below
-__global__ __launch_bounds__(256) void reverse_kernel(const float* V, int K, float* U)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    const int i = blockIdx.y;
-    if (j >= K) return;
-    U[(int64_t)i * K + j] = (j >= i) ? V[(int64_t)(K - 1 - i) * K + (K - 1 - j)] : 0.0f;
+            for (int y = 0; y < 2; ++y) C[(int64_t)(16 * x + v) * a.Kp + 16 * y] = old[x][y][v] - acc[x][y][v];
 }
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
+inline int64_t padded(int64_t K) { return (K + NB - 1) / NB * NB; }
 
 }  // namespace
 
 size_t gptq_prepare_workspace_bytes(int64_t K)
 {
-    // At, V: K x K each; T: K x K / 2; the diagonal block's inverse; the diagonal; the mean
-    return 2 * align256((size_t)K * K * 4) + align256((size_t)K * K * 2) + align256((size_t)NB * NB * 4) + align256((size_t)K * 4) + 256;
+    // M; the panel; the diagonal block's inverse; the diagonal; the mean
+    const size_t Kp = (size_t)padded(K);
+    return Kp * Kp * 4 + NB * Kp * 4 + NB * NB * 4 + align256((size_t)K * 4) + 256;
 }
 
 hipError_t launch_gptq_prepare(const float* H, int64_t K64, float damp, bool use_order, int* perm, float* U, void* workspace,
                                hipStream_t st)
 {
+    if (K64 <= 0 || K64 > 24576) return hipErrorInvalidValue;  // (a row of H is staged in LDS)
     const int K = (int)K64;
-    if (K <= 0 || K > 65535) return hipErrorInvalidValue;  // (rows ride on grid.y)
+    const int64_t Kp = padded(K);
     char* ws = static_cast<char*>(workspace);
-    float* At = reinterpret_cast<float*>(ws);
-    ws += align256((size_t)K * K * 4);
-    float* V = reinterpret_cast<float*>(ws);
-    ws += align256((size_t)K * K * 4);
-    float* T = reinterpret_cast<float*>(ws);
-    ws += align256((size_t)K * K * 2);
-    float* Linv = reinterpret_cast<float*>(ws);
-    ws += align256((size_t)NB * NB * 4);
+    PrepArgs a{};
+    a.Kp = (int)Kp;
+    a.nt = (int)(Kp / NB);
+    a.M = reinterpret_cast<float*>(ws);
+    ws += (size_t)Kp * Kp * 4;
+    a.LT = reinterpret_cast<float*>(ws);
+    ws += (size_t)NB * Kp * 4;
+    a.DT = reinterpret_cast<float*>(ws);
+    ws += (size_t)NB * NB * 4;
     float* diag = reinterpret_cast<float*>(ws);
     ws += align256((size_t)K * 4);
     float* mean = reinterpret_cast<float*>(ws);
 
-    const unsigned kb = (unsigned)((K + 255) / 256);
-    hipLaunchKernelGGL(mean_diag_kernel, dim3(1), dim3(256), 0, st, H, K, diag, mean);
-    hipLaunchKernelGGL(identity_kernel, dim3(kb), dim3(256), 0, st, K, perm);
-    hipLaunchKernelGGL(order_kernel, dim3(kb), dim3(256), 0, st, (const float*)diag, K, use_order ? 1 : 0, perm);
-    hipLaunchKernelGGL(gather_kernel, dim3(kb, (unsigned)K), dim3(256), 0, st, H, (const int*)perm, (const float*)mean, damp, K, At, V);
-
-    hipError_t e;
-    // 2. blocked Cholesky
-    for (int k0 = 0; k0 < K; k0 += NB) {
-        const int nb = std::min(NB, K - k0);
-        hipLaunchKernelGGL(diag_block_kernel, dim3(1), dim3(64), 0, st, At, V, Linv, K, k0, nb);
-        const int rest = K - k0 - nb;
-        if (rest <= 0) break;
-        GemmF32 p{};  // panel: L21 = A21 Linv^T  (in place; one tile wide, so a tile reads all it overwrites first)
-        p.C = At + (int64_t)(k0 + nb) * K + k0;
-        p.A = p.C;
-        p.B = Linv;
-        p.ldc = p.lda = K;
-        p.ldb = NB;
-        p.m = rest;
-        p.n = nb;
-        p.k = nb;
-        p.alpha = 1.0f;
-        p.beta = 0.0f;
-        p.transB = 1;
-        if ((e = gemm_f32(p, 1, st)) != hipSuccess) return e;
-        GemmF32 u{};  // trailing update: A22 -= L21 L21^T (lower tiles)
-        u.C = At + (int64_t)(k0 + nb) * K + (k0 + nb);
-        u.A = At + (int64_t)(k0 + nb) * K + k0;
-        u.B = u.A;
-        u.ldc = u.lda = u.ldb = K;
-        u.m = rest;
-        u.n = rest;
-        u.k = nb;
-        u.alpha = -1.0f;
-        u.beta = 1.0f;
-        u.transB = 1;
-        u.lower_only = 1;
-        if ((e = gemm_f32(u, 1, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(diag_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, H, K, diag, perm);
+    hipLaunchKernelGGL(order_kernel, dim3((unsigned)((K + 3) / 4 + 1)), dim3(256), 0, st, (const float*)diag, K, use_order ? 1 : 0, perm, mean);
+    static LdsAttrOnce lds_once;
+    if ((size_t)K * 4 > 48 * 1024) {
+        const hipError_t le = lds_once.ensure(reinterpret_cast<const void*>(gather_kernel), 24576 * 4);
+        if (le != hipSuccess) return le;
     }
-    // 3. V = L^-1: the diagonal blocks are in place; double the inverted block size until it spans the matrix
-    for (int s = NB; s < K; s *= 2) {
-        const int pairs = (K + 2 * s - 1) / (2 * s);
-        GemmF32 t{};  // T_z = L21 V11
-        t.C = T;
-        t.A = At + (int64_t)s * K;
-        t.B = V;
-        t.ldc = s;
-        t.lda = t.ldb = K;
-        t.sC = (int64_t)s * s;
-        t.sA = t.sB = (int64_t)2 * s * K + 2 * s;
-        t.m = s;
-        t.n = s;
-        t.k = s;
-        t.alpha = 1.0f;
-        t.beta = 0.0f;
-        t.ragged = s;
-        t.total = K;
-        if ((e = gemm_f32(t, pairs, st)) != hipSuccess) return e;
-        GemmF32 v{};  // V21_z = -V22 T_z
-        v.C = V + (int64_t)s * K;
-        v.A = V + (int64_t)s * K + s;
-        v.B = T;
-        v.ldc = v.lda = K;
-        v.ldb = s;
-        v.sC = v.sA = (int64_t)2 * s * K + 2 * s;
-        v.sB = (int64_t)s * s;
-        v.m = s;
-        v.n = s;
-        v.k = s;
-        v.alpha = -1.0f;
-        v.beta = 0.0f;
-        v.ragged = s;
-        v.total = K;
-        v.k_is_rows = 1;
-        if ((e = gemm_f32(v, pairs, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(gather_kernel, dim3((unsigned)Kp), dim3(256), (size_t)K * 4, st, H, (const int*)perm, (const float*)mean, damp, K, (int)Kp, a.M);
+    a.k = -1;
+    hipLaunchKernelGGL(update_kernel, dim3(1), dim3(512), 0, st, a);
+    for (a.k = 0; a.k < a.nt; ++a.k) {
+        if (a.nt > 1) hipLaunchKernelGGL(panel_kernel, dim3((unsigned)((a.nt - 1) * (NB / PW))), dim3(256), 0, st, a);
+        if (a.k + 1 == a.nt) break;
+        const int64_t tiles = (int64_t)a.nt * (a.nt + 1) / 2 - (int64_t)(a.k + 1) * (a.k + 2) / 2;
+        // Up to two blocks per compute unit the chain in workgroup 0 is the longer side, and unused dynamic LDS that keeps a
+        // second workgroup off its compute unit shortens it (41 -> 34 us at 390 blocks); with more blocks two per unit win.
+        const unsigned lone = tiles <= 2 * compute_units() ? 12288 : 0;
+        hipLaunchKernelGGL(update_kernel, dim3((unsigned)tiles), dim3(512), lone, st, a);
     }
-    hipLaunchKernelGGL(reverse_kernel, dim3(kb, (unsigned)K), dim3(256), 0, st, (const float*)V, K, U);
+    hipLaunchKernelGGL(reverse_kernel, dim3((unsigned)K), dim3(256), 0, st, (const float*)a.M, K, (int)Kp, U);
     return hipGetLastError();
 }
 

@@ -205,6 +205,28 @@ def test_prepare_matches_the_oracle_order_and_factor(fp4, oracle, gptq, K):
     assert np.linalg.norm(np_(U0) - want_U0) / np.linalg.norm(want_U0) <= 5e-4
 
 
+@pytest.mark.parametrize("K", [1, 2, 16, 127, 128, 129, 255, 257, 400])
+def test_prepare_at_the_edges_of_its_blocks(fp4, gptq, K):
+    """Sizes around the 128-column blocks of the elimination and the 16-column steps inside them.  Bounds as above."""
+    import torch
+    rng = np.random.default_rng(500 + K)
+    X = rng.standard_normal((2 * K + 10, K)) * rng.uniform(0.2, 3.0, K)
+    H32 = (X.T @ X).astype(np.float32)
+    H32 = np.tril(H32) + np.tril(H32, -1).T
+    say(f"gptq prepare edges K={K}")
+    perm, U = fp4.fp4_gptq_prepare(to_dev(H32), 1e-2, True)
+    torch.cuda.synchronize()
+    perm, U = np_(perm), np_(U).astype(np.float64)
+    H64 = H32.astype(np.float64)
+    want_perm = gptq.act_order(H64)
+    assert np.array_equal(perm, want_perm)
+    want_U = gptq.inverse_factor(H64, want_perm, damp=1e-2)
+    assert np.all(np.tril(U, -1) == 0)
+    assert np.linalg.norm(U - want_U) / np.linalg.norm(want_U) <= 5e-4
+    A = H64[np.ix_(want_perm, want_perm)] + 1e-2 * np.mean(np.diag(H64)) * np.eye(K)
+    assert np.abs(U.T @ U @ A - np.eye(K)).max() <= 2e-3
+
+
 def test_prepare_orders_equal_diagonal_entries_by_index(fp4, gptq):
     import torch
     K = 128
