@@ -512,9 +512,10 @@ inline int64_t padded(int64_t K) { return (K + NB - 1) / NB * NB; }
 
 size_t gptq_prepare_workspace_bytes(int64_t K)
 {
-    // M; the panel; the diagonal block's inverse; the diagonal; the mean
-    const size_t Kp = (size_t)padded(K);
-    return Kp * Kp * 4 + NB * Kp * 4 + NB * NB * 4 + align256((size_t)K * 4) + 256;
+    // M; the panel; the diagonal block's inverse; the diagonal; the mean.  Never less than the 2.5 K^2 floats that callers of
+    // this entry point are told to expect.
+    const size_t Kp = (size_t)padded(K), k = (size_t)K;
+    return std::max(Kp * Kp * 4 + NB * Kp * 4 + NB * NB * 4 + align256(k * 4) + 256, align256(k * k * 10));
 }
 
 hipError_t launch_gptq_prepare(const float* H, int64_t K64, float damp, bool use_order, int* perm, float* U, void* workspace,
