@@ -13,9 +13,11 @@
 //     re-converting them);
 //   * only W is converted inside the product, and a wave's tile is 128 rows of X by 64 (or 32) rows of W: four (two)
 //     half-fragment conversions per 64 (32) MFMAs.
-// Block tile 128 x 256 (or 128 x 128 for a remainder of the tile grid), four waves side by side along N, K-step 64,
-// three-stage LDS ring fed by direct-to-LDS loads, one barrier per K-step.  75 KB of LDS and 256 registers per wave: two
-// workgroups share a compute unit, and one's barrier and fragment loads hide under the other's MFMAs.
+// Block tile 128 x 256 (or 128 x 128 for a remainder of the tile grid, or 128 x 512), four (eight) waves side by side along
+// N, K-step 64, three-stage LDS ring fed by direct-to-LDS loads, one barrier per K-step.  75 KB of LDS and 256 registers per
+// wave: two workgroups share a compute unit (or one of eight waves fills it).
+// What bounds it (timing builds of N = 57344, K = 8192, M = 2048): the MFMAs alone, on real operands, take 1054 us of 1350; the
+// copies into LDS cost 200, the conversions of W 65, the reads of X 55, the barrier nothing measurable.
 //
 // Operand order of one K-step of 64 (16 rows): the MFMA takes 8 halves per lane and call (lane = row r + 16 q); lane (r, q)
 // owns the 16 elements k = 16 q .. 16 q + 15 -- exactly one NVFP4 group, one E4M3 scale -- and two MFMAs (s = 0, 1) consume
@@ -88,19 +90,19 @@ __global__ __launch_bounds__(256) void nv_x16_kernel(const uint8_t* __restrict__
 // ---------------------------------------------------------------------------------------------------------------
 // SPLITK: the workgroup multiplies K-steps blockIdx.y * split_steps .. only and writes its fp32 partial tile, without the
 // tensor scales, to slice blockIdx.y of the output; nv16_reduce_kernel adds the slices in split order.
-template <int BN, bool OUT_F32, int STAGES = 3, bool SPLITK = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_nv16_kernel(Nv16Args g)
+template <int NW, int TN, bool OUT_F32, int STAGES, bool SPLITK = false>
+__global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
 {
     static_assert(!SPLITK || OUT_F32, "split-K workgroups write fp32 partials");
-    constexpr int BM = 128, NW = 4;
-    constexpr int WN = BN / NW;            // 64 or 32 columns per wave
-    constexpr int TM = BM / 16, TN = WN / 16;
+    constexpr int BM = 128, WN = 16 * TN, BN = NW * WN;   // 64 or 32 columns per wave
+    constexpr int TM = BM / 16;
     constexpr int FX = BM / 16, FW = BN / 16;
     constexpr int WS_SLOT = 256;           // scale bytes one full-wave copy writes: four row-blocks' worth per wave
     constexpr int X_BYTES = FX * 2048, WC_BYTES = FW * 512, WS_BYTES = NW * WS_SLOT;
     constexpr int STAGE_BYTES = X_BYTES + WC_BYTES + WS_BYTES;
     constexpr int XPW = FX * 2 / NW, WPW = FW / NW;      // 1 KB X chunks and W half-fragments a wave copies per stage
-    constexpr int OPS = XPW + WPW / 2 + 1;                // vector-memory operations per wave and stage
+    constexpr int WCI = WPW / 2;                          // W code instructions per wave and stage
+    constexpr int OPS = XPW + WCI + 1;                    // vector-memory operations per wave and stage
     static_assert(FX * 2 % NW == 0 && FW % NW == 0, "the copies are dealt evenly to the waves");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -136,7 +138,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
     //     data at 16 l behind the base whatever address the lane reads from);
     //   W scales: 64 bytes per row-block and K-step -- one instruction copies those of FOUR row-blocks, 16 lanes each.
     static_assert(WPW % 2 == 0 && (WPW == 4 || WPW == 2), "W halves are copied in pairs, scales in fours (or twos)");
-    constexpr int WCI = WPW / 2;          // W code instructions per wave and stage
     const uint32_t wc_voff0 = (uint32_t)((lane & 31) * 16 + min(wave * WPW + (lane >> 5), w_rb_last) * wc_rb_bytes);
     const uint32_t wc_voff1 = (uint32_t)((lane & 31) * 16 + min(wave * WPW + 2 + (lane >> 5), w_rb_last) * wc_rb_bytes);   // (WCI = 2 only)
     // (a wave that owns two row-blocks only fills the rest of its 256-byte slot with the scales of the two behind them)
@@ -222,49 +223,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
         return v;
     };
 
+    // The K-step's operands are read one step ahead: behind the barrier that says stage kh + 1 has landed, the MFMAs of step
+    // kh's LAST column-tile alternate with the reads of stage kh + 1 -- every X fragment is replaced right after its last use --
+    // and with the conversion of its first W half-fragment, so that no MFMA waits for LDS at the head of a step.
+    v8h xf[TM][2];
+    WRaw wraw[TN];
+    WHalf wcur, wnext;
+    auto read_x = [&](const char* base, int j, int s) { xf[j][s] = *(reinterpret_cast<const v8h*>(base + (j * 2 + s) * 1024) + lane); };
+    wait_vmcnt<(STAGES - 2) * OPS>();
+    block_barrier();
+#pragma unroll
+    for (int i = 0; i < TN; ++i) wraw[i] = read_w(smem, i);
+#pragma unroll
+    for (int t = 0; t < 2 * TM; ++t) read_x(smem, t % TM, t / TM);
+    {
+        const v2h s2 = scale2(wraw[0]);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) micro(wraw[0], s2, wcur, u);
+    }
+    // lgkmcnt(0): nothing is pending where the loop is entered, so that the waits inside count its own reads only (with an
+    // order of its own on the way in, the compiler waits for everything at the head of every step)
+    __builtin_amdgcn_s_waitcnt(0xc07f);
     for (int kh = 0; kh < KH; ++kh) {
-        // stage kh has landed (this wave's copies: vmcnt; everybody's: barrier); the barrier also says that every wave is
-        // done with stage kh - 1, whose slot stage kh + STAGES - 1 is about to refill
-        wait_vmcnt<(STAGES - 2) * OPS>();
-        block_barrier();
         const int kn = kh + STAGES - 1, kl = min(kn, KH - 1);
         char* const fill = smem + (kn % STAGES) * STAGE_BYTES;
-
-        const char* base = smem + (kh % STAGES) * STAGE_BYTES;
-        v8h xf[TM][2];
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int s = 0; s < 2; ++s) xf[j][s] = *(reinterpret_cast<const v8h*>(base + (j * 2 + s) * 1024) + lane);
-        WRaw wraw[TN];
-#pragma unroll
-        for (int i = 0; i < TN; ++i) wraw[i] = read_w(base, i);
-        WHalf wcur, wnext;
-        {
-            const v2h s2 = scale2(wraw[0]);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) micro(wraw[0], s2, wcur, u);
-        }
+        const char* const next = smem + ((kh + 1) % STAGES) * STAGE_BYTES;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < TN; ++i) {
+            const bool last = i + 1 == TN;
+            if (last) {
+                // stage kh + 1 has landed (this wave's copies: vmcnt; everybody's: barrier); the barrier also says that every
+                // wave holds stage kh in registers, so that its slot may be refilled
+                wait_vmcnt<(STAGES - 2) * OPS>();
+                block_barrier();
+#pragma unroll
+                for (int v = 0; v < TN; ++v) wraw[v] = read_w(next, v);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             v2h s2 = {0, 0};
-            if (i + 1 < TN) s2 = scale2(wraw[i + 1]);
+            if (!last) s2 = scale2(wraw[i + 1]);
             const v8h a0 = operand(wcur, 0), a1 = operand(wcur, 1);
 #pragma unroll
             for (int t = 0; t < 2 * TM; ++t) {
                 const int j = t % TM, s = t / TM;
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(s == 0 ? a0 : a1, xf[j][s], acc[i][j], 0, 0, 0);
-                if (i + 1 < TN && t < 8) micro(wraw[i + 1], s2, wnext, t);
+                if (!last) {
+                    if (t < 8) micro(wraw[i + 1], s2, wnext, t);
+                } else {
+                    read_x(next, j, s);
+                    if (t == 2 * TM - 9) s2 = scale2(wraw[0]);
+                    if (t >= 2 * TM - 8) micro(wraw[0], s2, wnext, t - (2 * TM - 8));
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // the refill of the slot everybody left at this step's barrier, a third of it behind each of the first three
-            // column-tiles (TN = 2: X behind the first, both W pieces behind the second)
+            // the refill of the slot everybody left at the barrier of the step before, in pieces behind the first column-tiles
             if (i == 0) issue_x(kl, fill);
-            if (i == 1) issue_wc(kl, fill);
-            if (i == (TN == 2 ? 1 : 2)) issue_ws(kl, fill);
+            if (i == (TN == 2 ? 0 : 1)) issue_wc(kl, fill);
+            if (i == (TN == 2 ? 0 : 2)) issue_ws(kl, fill);
             __builtin_amdgcn_sched_barrier(0);
-            if (i + 1 < TN) wcur = wnext;
+            wcur = wnext;
         }
     }
     wait_vmcnt<0>();   // (the repeated copies of the last steps: nothing may be in flight into LDS when the workgroup ends)
@@ -379,43 +397,50 @@ int device_cus()
     return compute_units();
 }
 
-template <int BN, int STAGES>
-hipError_t launch_tiles_ring(const Nv16Args& g, bool out_f32, hipStream_t st, int splits)
+template <int NW, int TN, int STAGES>
+hipError_t launch_tiles(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1)
 {
-    constexpr size_t lds = STAGES * (size_t)(8 * 2048 + (BN / 16) * 512 + 4 * 256);
+    constexpr int BN = NW * TN * 16;
+    constexpr size_t lds = STAGES * (size_t)(8 * 2048 + (BN / 16) * 512 + NW * 256);
+    if (g.n_cols <= 0) return hipSuccess;
     const int tiles_n = (g.n_cols + BN - 1) / BN;
     if (splits > 1) {
         static LdsAttrOnce raised_s;
-        auto k = gemm_nv16_kernel<BN, true, STAGES, true>;
+        auto k = gemm_nv16_kernel<NW, TN, true, STAGES, true>;
         hipError_t es;
         if ((es = raised_s.ensure(reinterpret_cast<const void*>(k), (int)lds)) != hipSuccess) return es;
-        hipLaunchKernelGGL(k, dim3((unsigned)(g.tiles_m * tiles_n), (unsigned)splits), dim3(256), lds, st, g);
+        hipLaunchKernelGGL(k, dim3((unsigned)(g.tiles_m * tiles_n), (unsigned)splits), dim3(NW * 64), lds, st, g);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(g.tiles_m * tiles_n));
     hipError_t e;
     static LdsAttrOnce raised[2];
     if (out_f32) {
-        auto k = gemm_nv16_kernel<BN, true, STAGES>;
+        auto k = gemm_nv16_kernel<NW, TN, true, STAGES>;
         if ((e = raised[1].ensure(reinterpret_cast<const void*>(k), (int)lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k, grid, dim3(256), lds, st, g);
+        hipLaunchKernelGGL(k, grid, dim3(NW * 64), lds, st, g);
     } else {
-        auto k = gemm_nv16_kernel<BN, false, STAGES>;
+        auto k = gemm_nv16_kernel<NW, TN, false, STAGES>;
         if ((e = raised[0].ensure(reinterpret_cast<const void*>(k), (int)lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k, grid, dim3(256), lds, st, g);
+        hipLaunchKernelGGL(k, grid, dim3(NW * 64), lds, st, g);
     }
     return hipGetLastError();
 }
 
-// Three stages (75 KB of LDS with 256 columns, two workgroups per compute unit).  (A ring of six or seven stages for launches
-// with at most one workgroup per compute unit measured the same: N = K = 4096, M = 80: 43.1 against 43.5 us -- a K-step of
-// such a launch is bound by the tile's own 64 MFMAs per wave, not by its loads.)
-template <int BN>
-hipError_t launch_tiles(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1)
+// Tile columns of 256 (or wider).  Two workgroups of 128 x 256 share a compute unit, and one's epilogue runs under the other's
+// products; but each copies the same rows of X into LDS for itself.  Where a single round of the chip has more such
+// workgroups than compute units and no more than one of twice the width, eight waves share a 128 x 512 tile instead (34 KB
+// copied per K-step, not 50; there is no second round for an epilogue to run under): N = 8192, M = 2048: K = 28672 669 ->
+// 641 us, K = 8192 205 -> 201.  Over several rounds the pairs stay ahead (N = 57344, K = 8192: 1324 against 1342 us).
+// Three stages either way: a fourth for the 512 columns measured 1 % slower.
+hipError_t launch_wide(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1)
 {
-    if (g.n_cols <= 0) return hipSuccess;
-    return launch_tiles_ring<BN, 3>(g, out_f32, st, splits);
+    const int64_t rows = (int64_t)g.tiles_m * splits, cus = device_cus();
+    if (rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st, splits);
+    return launch_tiles<4, 4, 3>(g, out_f32, st, splits);
 }
+
+hipError_t launch_narrow(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1) { return launch_tiles<4, 2, 3>(g, out_f32, st, splits); }
 
 }  // namespace
 
@@ -470,7 +495,7 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
             g.n_first = 0;
             g.n_cols = (int)N;
             g.split_steps = steps;
-            if ((e = narrow ? launch_tiles<128>(g, true, st, splits) : launch_tiles<256>(g, true, st, splits)) != hipSuccess) return e;
+            if ((e = narrow ? launch_narrow(g, true, st, splits) : launch_wide(g, true, st, splits)) != hipSuccess) return e;
             const int64_t mn = M * N;
             const unsigned rblocks = (unsigned)std::min<int64_t>((mn + 255) / 256, 256 * 16);
             if (out_f32) hipLaunchKernelGGL(nv16_reduce_kernel<true>, dim3(rblocks), dim3(256), 0, st, static_cast<const float*>(partial), splits, mn, a_ts, w_ts, out);
@@ -491,10 +516,10 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
         if (t_split < t_wide) {
             g.n_first = 0;
             g.n_cols = (int)(full_cols * 256);
-            if ((e = launch_tiles<256>(g, out_f32, st)) != hipSuccess) return e;
+            if ((e = launch_wide(g, out_f32, st)) != hipSuccess) return e;
             g.n_first = (int)(full_cols * 256);
             g.n_cols = (int)rest_cols;
-            return launch_tiles<128>(g, out_f32, st);
+            return launch_narrow(g, out_f32, st);
         }
     }
     g.n_first = 0;
@@ -502,8 +527,8 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     // less than a round and a quarter of wide tiles (one per compute unit and a few doubled up, or compute units left
     // idle): 128 x 128 tiles spread the same work twice as finely (N = 10240, K = 8192 at M = 512: 136 -> 119 us;
     // N = 8192, K = 28672 at M = 512 without the split-K workspace: 412 -> 280 us)
-    if (nv16_narrow_tiles(tiles_w, cus)) return launch_tiles<128>(g, out_f32, st);
-    return launch_tiles<256>(g, out_f32, st);
+    if (nv16_narrow_tiles(tiles_w, cus)) return launch_narrow(g, out_f32, st);
+    return launch_wide(g, out_f32, st);
 }
 
 }  // namespace fp4mr
