@@ -305,86 +305,121 @@ __global__ __launch_bounds__(64) void gptq_outer_kernel(GptqArgs a, int o, int o
     }
 }
 
-// wp[n, c] -= sum_{j < rank} err[n, e0 + j] * U[u0 + j, c] for the columns c_begin <= c < c_end (visiting order): a dense
-// fp32 contraction, on the fp32 MFMA (v_mfma_f32_16x16x4_f32; the terms enter four at a time in ascending order, where the
-// column-by-column definition applies them singly -- the same sum up to fp32 rounding order).  128 x 128 output tile per
-// workgroup, a 64 x 64 quarter per wave (16 MFMA tiles whose accumulators start as the working weights), the negated
-// errors and the rows of U staged through LDS 32 terms at a time, the next 32 fetched while the current ones multiply.
-__global__ __launch_bounds__(256) void gptq_update_kernel(GptqArgs a, int u0, int e0, int rank, int c_begin, int c_end)
+// A value as the sum of three bf16: 8 + 8 + 8 significant bits are a binary32's 24, and what a rounding leaves over is exact
+// in the subtraction, so hi + mid + lo is the value itself (down to 2^-110, below which the last part may underflow).
+struct Split3 {
+    v8bf part[3];
+};
+__device__ __forceinline__ Split3 split3(const float (&x)[8])
 {
-    constexpr int T = 128, KC = 32, LD = T + 20, NT = 4, NL = KC * T / 256;
-    __shared__ float Et[KC][LD];  // [term][row], negated
-    __shared__ float Ut[KC][LD];  // [term][column]
+    Split3 s;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        float rest = x[i];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const __bf16 h = (__bf16)rest;
+            s.part[p][i] = h;
+            rest -= (float)h;
+        }
+    }
+    return s;
+}
+
+// wp[n, c] -= sum_{j < kOuter} err[n, j] * U[u0 + j, c] for the columns c_begin <= c < c_end (visiting order): a dense fp32
+// contraction, [N x 512] . [512 x columns].  The fp32 MFMA (157 TFLOP/s) bounded it, 82 of them; here both factors are split
+// into three bf16 and the six products above 2^-24 of the whole run on the bf16 MFMA, 6 / 16 of the time.  They are exact in
+// binary32; per 32 terms they are summed smallest first from zero and added to the accumulator once, 16 roundings at its
+// size where the fp32 MFMA had 128: codes that differ from a sweep in 64 bits 7e-4 -> 6e-5 (MXFP4, K = 4096; NVFP4 level),
+// [6144, 4096] behind its first outer block 308 -> 157 us.
+// 128 x 128 output tile per workgroup, a 64 x 64 quarter per wave; 32 terms at a time are split and written to LDS in the
+// MFMA's operand order (lane (r, q) of a 16-wide block: element r, terms 8 q .. 8 q + 7), the next 32 fetched meanwhile.  U is
+// the MFMA's A operand, so that a lane owns four neighbouring columns of a row.
+__global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int u0, int c_begin, int c_end)
+{
+    constexpr int T = 128, KC = 32, NT = 4;
+    __shared__ v8bf Et[3][T / 16][64], Ut[3][T / 16][64];   // [part][block of 16 rows / columns][lane]
     const int c0 = c_begin + blockIdx.x * T;
     const int n0 = blockIdx.y * T;
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
-    const int wr = (wave >> 1) * 64, wc = (wave & 1) * 64;
-    // a lane holds rows 4q .. 4q+3 of column l16 of every 16 x 16 tile; c_end and the tile start are multiples of 64, so
-    // a wave's 64 columns are in or out together
-    const bool in = c0 + wc < c_end;
-    v4f acc[NT][NT], old[NT][NT];
+    const int wr = (wave >> 1) * 4, wc = (wave & 1) * 4;   // first block of rows / columns of the wave's quarter
+    // this thread stages lane `lane` of the blocks wave and wave + 4 of either operand (past the edges: the last row and
+    // column again, which only feed outputs that are not stored)
+    const float* er[2];
+    const float* uc[2];
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int n = min(n0 + wr + i * 16 + 4 * q + v, a.N - 1);
-            const float* src = a.wp + (int64_t)n * a.K + c0 + wc + l16;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                old[i][j][v] = in ? src[j * 16] : 0.0f;
-                acc[i][j][v] = 0.0f;
-            }
-        }
-    float re[NL], ru[NL];
+    for (int h = 0; h < 2; ++h) {
+        er[h] = a.err + (int64_t)min(n0 + (wave + 4 * h) * 16 + l16, a.N - 1) * kOuter + 8 * q;
+        uc[h] = a.U + (int64_t)(u0 + 8 * q) * a.K + min(c0 + (wave + 4 * h) * 16 + l16, a.K - 1);
+    }
+    float re[2][8], ru[2][8];
     auto fetch = [&](int r0) {
 #pragma unroll
-        for (int it = 0; it < NL; ++it) {
-            const int idx = it * 256 + tid;
-            // both reads run along the contiguous index: the errors of a row are consecutive over the terms, a row of U over
-            // the columns
-            const int te = idx % KC, xe = idx / KC;
-            const int n = min(n0 + xe, a.N - 1);
-            re[it] = a.err[(int64_t)n * kOuter + e0 + r0 + te];
-            const int x = idx % T, t = idx / T;
-            ru[it] = (c0 + x < c_end) ? a.U[(int64_t)(u0 + r0 + t) * a.K + c0 + x] : 0.0f;
+        for (int h = 0; h < 2; ++h) {
+            const float4 lo = *reinterpret_cast<const float4*>(er[h] + r0), hi = *reinterpret_cast<const float4*>(er[h] + r0 + 4);
+            re[h][0] = lo.x, re[h][1] = lo.y, re[h][2] = lo.z, re[h][3] = lo.w;
+            re[h][4] = hi.x, re[h][5] = hi.y, re[h][6] = hi.z, re[h][7] = hi.w;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ru[h][i] = uc[h][(int64_t)(r0 + i) * a.K];
         }
     };
-    fetch(0);
-    for (int r0 = 0; r0 < rank; r0 += KC) {
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < NL; ++it) {
-            const int idx = it * 256 + tid;
-            Et[idx % KC][idx / KC] = re[it];
-            Ut[idx / T][idx % T] = ru[it];
-        }
-        __syncthreads();
-        if (r0 + KC < rank) fetch(r0 + KC);
-#pragma unroll
-        for (int ks = 0; ks < KC / 4; ++ks) {
-            float e[NT], u[NT];
-#pragma unroll
-            for (int i = 0; i < NT; ++i) e[i] = Et[ks * 4 + q][wr + i * 16 + l16];
-#pragma unroll
-            for (int j = 0; j < NT; ++j) u[j] = Ut[ks * 4 + q][wc + j * 16 + l16];
-#pragma unroll
-            for (int i = 0; i < NT; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(e[i], u[j], acc[i][j], 0, 0, 0);
-        }
-    }
-    if (!in) return;
+    v4f acc[NT][NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int n = n0 + wr + i * 16 + 4 * q + v;
-            if (n >= a.N) continue;
-            float* dst = a.wp + (int64_t)n * a.K + c0 + wc + l16;
+        for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    for (int r0 = 0; r0 < kOuter; r0 += KC) {
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < NT; ++j) dst[j * 16] = old[i][j][v] - acc[i][j][v];
+        for (int h = 0; h < 2; ++h) {
+            const Split3 e = split3(re[h]), u = split3(ru[h]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                Et[p][wave + 4 * h][lane] = e.part[p];
+                Ut[p][wave + 4 * h][lane] = u.part[p];
+            }
         }
+        __syncthreads();
+        if (r0 + KC < kOuter) fetch(r0 + KC);
+        v8bf u[3][NT];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) u[p][j] = Ut[p][wc + j][lane];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            v8bf e[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) e[p] = Et[p][wr + i][lane];
+            v4f sum[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) sum[j] = v4f{0.f, 0.f, 0.f, 0.f};
+            // (part of U, part of the error): 2^-16, 2^-8, 1 of the product
+            constexpr int order[6][2] = {{2, 0}, {1, 1}, {0, 2}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    sum[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u[order[t][0]][j], e[order[t][1]], sum[j], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] += sum[j];
+        }
+    }
+    // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 tile (c_end is a multiple of 64)
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        const int n = n0 + (wr + i) * 16 + l16;
+        if (n >= a.N) continue;
+        float* row = a.wp + (int64_t)n * a.K + c0 + wc * 16 + 4 * q;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            if (c0 + (wc + j) * 16 >= c_end) continue;
+            v4f* dst = reinterpret_cast<v4f*>(row + 16 * j);
+            *dst = *dst - acc[i][j];
+        }
+    }
 }
 
 // codes[n, kb] = code of column 2 kb | code of column 2 kb + 1 << 4, fetched from their visiting positions
@@ -447,9 +482,9 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     }
     hipLaunchKernelGGL(gptq_rotate_gather_kernel, dim3((unsigned)N), dim3(256), row_lds, st, a);
     const unsigned row128 = (unsigned)((N + 127) / 128), row16 = (unsigned)((N + 15) / 16);
-    auto update = [&](int u0, int e0, int rank, int c_begin, int c_end) {
+    auto update = [&](int u0, int c_begin, int c_end) {
         const unsigned tiles = (unsigned)((c_end - c_begin + 127) / 128);
-        hipLaunchKernelGGL(gptq_update_kernel, dim3(tiles, row128), dim3(256), 0, st, a, u0, e0, rank, c_begin, c_end);
+        hipLaunchKernelGGL(gptq_update_kernel, dim3(tiles, row128), dim3(256), 0, st, a, u0, c_begin, c_end);
     };
     for (int o = 0; o < (int)K; o += kOuter) {
         const int oe = std::min(o + kOuter, (int)K);
@@ -458,7 +493,7 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
         if (fmt == 0) hipLaunchKernelGGL(gptq_outer_kernel<0>, dim3(row16), dim3(64), 0, st, a, o, oe);
         else hipLaunchKernelGGL(gptq_outer_kernel<1>, dim3(row16), dim3(64), 0, st, a, o, oe);
         // ... everything behind the outer block sees all of its errors in one pass
-        if (oe < (int)K) update(o, 0, oe - o, oe, (int)K);
+        if (oe < (int)K) update(o, oe, (int)K);
     }
     hipLaunchKernelGGL(gptq_pack_kernel, dim3((unsigned)N), dim3(256), 0, st, a);
     return hipGetLastError();

@@ -334,6 +334,30 @@ def test_calibration_rows_to_codes_entirely_on_the_gpu(fp4, oracle, gptq):
     assert abs(e_got - e_ref) <= 1e-2 * e_ref and e_got < 0.8 * e_rtn
 
 
+@pytest.mark.parametrize("N,K", [(1, 576), (128, 640), (129, 704), (127, 1600)])
+def test_update_behind_an_outer_block_at_the_edges_of_its_tiles(fp4, oracle, gptq, N, K):
+    """A dense factor with full 24-bit entries, so that everything behind column 512 has its values from the 128 x 128 tiles
+    of the update: one row, whole and ragged tiles, a last tile of 64 columns.  The update is as exact as a binary32 sum, so
+    codes differ only where the running value is within binary32 noise of a midpoint: the bound of the tests above."""
+    import torch
+    rng = np.random.default_rng(N + K)
+    w = rng.standard_normal((N, K)).astype(np.float32)
+    wb = inputs.f32_to_bf16_bits(w)
+    U = np.triu(rng.standard_normal((K, K)) * 0.02, 1).astype(np.float32)
+    U[np.diag_indices(K)] = rng.uniform(0.5, 2.0, K).astype(np.float32)
+    perm = rng.permutation(K).astype(np.int32)
+    y = oracle.rotate(wb, 1)
+    _, scales, _ = oracle.quantize(y, MX)
+    want, _ = gptq.sweep(y, scales, MX, None, U, perm)
+    say(f"gptq dense factor N={N} K={K}")
+    c, s, _ = fp4.fp4_gptq_quantize_weights(to_dev_bf16(wb), 1, MX, to_dev(U), to_dev(perm))
+    torch.cuda.synchronize()
+    assert np.array_equal(np_(s).reshape(N, -1), scales)
+    diff = unpack(np_(c).reshape(N, -1)) != unpack(want)
+    say(f"   codes differing from the oracle: {diff.mean():.2e}")
+    assert diff.mean() <= 1e-3
+
+
 def test_sweep_at_layer_size_on_sampled_rows(fp4, oracle, gptq):
     """A whole [4096, 4096] layer through the library (the benchmark's shape: 64 blocks, 8 outer blocks), checked against the
     oracle on 32 sampled rows -- rows never interact, so the oracle sweeps just those rows with the same factor."""
