@@ -16,10 +16,13 @@
 #include "layout.hpp"
 #include "rq_core.hpp"
 
+#include <algorithm>
+
 namespace fp4mr {
 namespace {
 
 constexpr int kFusedWaves = 8;
+constexpr int kLdsBytes = 160 * 1024;   // of a compute unit
 
 struct FusedArgs {
     const uint16_t* x;       // [M, K] bf16
@@ -274,6 +277,204 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_w4a16_decode_kernel(Fus
     }
 }
 
+// ------------------------------------------------------------------------------------------------------
+// The same product with PERSISTENT workgroups, one per compute unit, each walking the row-blocks of W with a stride of the
+// grid.  The kernel above rotates the activations again in every workgroup (M = 4, N = 28672, K = 4096: 1792 times, 18.5 us),
+// and its W loads wait for that; here they are rotated once per workgroup into LDS (M K bf16, in the order in which a
+// fragment's MFMAs read them: [fragment][MFMA j][K-block][token], neighbouring lanes 16 bytes apart), under the first W
+// loads, and from then on two batches of four W fragments per wave are in flight while a third is multiplied.  A batch that
+// does not exist is requested with zero size, so that every request is unconditional (the compiler's waits count on it).
+// Same K split, same order of additions: bit-identical.
+// QUANT: the quantizing product; a fragment in LDS is then 4 M entries [K-block][token] of sixteen code bytes and behind them
+// 4 M dwords with the scale byte.
+template <bool QUANT, bool OUT_F32>
+__global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(FusedArgs a)
+{
+    using GQ = GroupQuant<32, 8, 16, true>;
+    constexpr int U = 4, TOK = 4;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    float (*const partial)[kFusedWaves][256] = reinterpret_cast<float (*)[kFusedWaves][256]>(smem);   // [2]: alternating
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int g = lane & 15, q = lane >> 4;
+    const int KC = a.K >> 7, KS = (a.K + 511) >> 9, n_rb = (a.N + 15) >> 4, G = (int)gridDim.x;
+    const int per = (KC + kFusedWaves - 1) / kFusedWaves;
+    const int k_begin = min(wave * per, KC), k_end = min(k_begin + per, KC);
+    const int nb = (per + U - 1) / U;   // batches per row-block, the same for every wave
+    const int frag_bytes = a.M * (QUANT ? 80 : 256);
+    char* const xs = smem + 2 * sizeof(partial[0]) + wave * per * frag_bytes;
+
+    auto make_rsrc = [](const void* base, int64_t bytes) {
+        const uint32_t n = bytes > 0xffffffffll ? 0xffffffffu : (uint32_t)bytes;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)n, 0x00020000);
+    };
+    struct Batch {
+        v4i wf[U];
+        uint32_t sw[U];
+    };
+    int rb_ahead = (int)blockIdx.x, batch_ahead = 0;   // the next batch to be requested
+    auto request = [&](Batch& b) {
+        const int kc0 = k_begin + batch_ahead * U;
+        const bool valid = rb_ahead < n_rb && kc0 < k_end;
+        const int rb = valid ? rb_ahead : 0;
+        const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(a.w_codes + (int64_t)rb * KC * 1024, valid ? (int64_t)KC * 1024 : 0);
+        const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(a.w_scales + (int64_t)rb * KS * 256, valid ? (int64_t)KS * 256 : 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int kc = max(min(kc0 + u, k_end - 1), 0);   // (the tail repeats the last fragment; its products are skipped)
+            b.wf[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs_w, lane * 16, kc * 1024, 2));   // streamed once
+            b.sw[u] = __builtin_amdgcn_raw_buffer_load_b32(rs_s, lane * 4, (kc >> 2) * 256, 0);
+        }
+        if (++batch_ahead == nb) {
+            batch_ahead = 0;
+            rb_ahead += G;
+        }
+    };
+    // the wave's share of the activations, rotated, into LDS: four tokens of sixteen 32-element vectors (a batch of fragments)
+    // at a time, the next loads under the current rotation (tokens past M read the last one again and are not written).
+    v8bf hop[2][1];
+    build_hadamard_operand<32>(hop, g, q, a.b < 32 ? a.b : 32);
+    const int kron = a.b > 32 ? (a.b == 64 ? 1 : 2) : 0;
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(a.x, (int64_t)a.M * a.K * 2);
+    const int groups = (a.M + TOK - 1) / TOK;
+    auto load_x = [&](v4i (&x)[TOK], int item) {
+        const int c = item / groups, m0 = (item - c * groups) * TOK;
+        const int k_lane = (k_begin + c * U) * 256 + g * 64 + q * 16;
+#pragma unroll
+        for (int t = 0; t < TOK; ++t) x[t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs_x, k_lane, min(m0 + t, a.M - 1) * a.K * 2, 0));
+    };
+    auto rotate = [&](v4i (&x)[TOK], int item) {
+        const int c = item / groups, m0 = (item - c * groups) * TOK;
+        const int f = c * U + (g >> 2);   // fragment of the wave's share; its K-block g % 4 is vector g
+#pragma unroll 1
+        for (int m = m0; m < min(m0 + TOK, a.M); ++m) {   // (not unrolled, the tokens move up instead: less code to fetch)
+            v4f h[2];
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) {
+                h[tt] = v4f{0.f, 0.f, 0.f, 0.f};
+                h[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hop[tt][0], __builtin_bit_cast(v8bf, x[0]), h[tt], 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t + 1 < TOK; ++t) x[t] = x[t + 1];
+            kronecker_levels<2>(h, g, kron);
+            float y[8];
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) y[4 * tt + v] = __fmaf_rn(h[tt][v], a.c_hi, h[tt][v] * a.c_lo);
+            if constexpr (QUANT) {
+                uint32_t codes[1], sc[1];
+                GQ::mx(y, codes, sc);
+                char* const dst = xs + f * frag_bytes;
+                const int pos = (g & 3) * a.M + m;
+                if (k_begin + f < k_end) {
+                    *reinterpret_cast<uint32_t*>(dst + pos * 16 + q * 4) = codes[0];
+                    if (q == 0) *reinterpret_cast<uint32_t*>(dst + a.M * 64 + pos * 4) = sc[0];
+                }
+            } else {
+                v8bf yb;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) yb[i] = (__bf16)y[i];
+                if (k_begin + f < k_end) *reinterpret_cast<v8bf*>(xs + f * frag_bytes + ((q * 4 + (g & 3)) * a.M + m) * 16) = yb;
+            }
+        }
+    };
+    const int items = (k_end - k_begin + U - 1) / U * groups;
+    // (the first activations are asked for before W: loads return in order)
+    v4i x0[TOK], x1[TOK];
+    load_x(x0, 0);
+    if (items > 1) load_x(x1, 1);
+    Batch buf[3];
+    request(buf[0]);
+    request(buf[1]);
+    if (items > 0) rotate(x0, 0);
+    for (int item = 1; item < items; item += 2) {
+        if (item + 1 < items) load_x(x0, item + 1);
+        rotate(x1, item);
+        if (item + 1 < items) {
+            if (item + 2 < items) load_x(x1, item + 2);
+            rotate(x0, item + 1);
+        }
+    }
+
+    // (columns of the product past M read the last token again and are not stored)
+    const int x_pos = q * a.M + min(g, a.M - 1);
+    v4f acc = {0.f, 0.f, 0.f, 0.f};
+    int rb = (int)blockIdx.x, batch = 0, it = 0;
+    // one batch: request the batch two ahead, multiply the current one, and behind a row-block's last batch add the eight
+    // waves' partial sums in wave order and store; true = that was the last row-block
+    auto step = [&](const Batch& cur, Batch& nxt) -> bool {
+        request(nxt);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int kc = k_begin + batch * U + u;
+            if (kc < k_end) {
+                const char* const xf = xs + (kc - k_begin) * frag_bytes;
+                if constexpr (QUANT) {
+                    const v4i x = *reinterpret_cast<const v4i*>(xf + x_pos * 16);
+                    const uint32_t sx = *reinterpret_cast<const uint32_t*>(xf + a.M * 64 + x_pos * 4);
+                    const v8i a8 = {cur.wf[u][0], cur.wf[u][1], cur.wf[u][2], cur.wf[u][3], 0, 0, 0, 0};
+                    const v8i b8 = {x[0], x[1], x[2], x[3], 0, 0, 0, 0};
+                    acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, b8, acc, 4, 4, 0, (int)(cur.sw[u] >> (8 * (kc & 3))), 0, (int)sx);
+                    continue;
+                }
+                const float wscale = __uint_as_float(((cur.sw[u] >> (8 * (kc & 3))) & 0xffu) << 23);   // E8M0 byte as a binary32's exponent
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const v8bf w8 = decode8_bf16((uint32_t)cur.wf[u][j], wscale);
+                    const v8bf x8 = *reinterpret_cast<const v8bf*>(xf + (x_pos + j * 4 * a.M) * 16);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w8, x8, acc, 0, 0, 0);
+                }
+            }
+        }
+        if (++batch < nb) return false;
+        batch = 0;
+        *reinterpret_cast<v4f*>(&partial[it][wave][lane * 4]) = acc;
+        acc = v4f{0.f, 0.f, 0.f, 0.f};
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the LDS writes have landed
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int e = wave * 32 + (lane & 31), l = e >> 2;
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kFusedWaves; ++w) s += partial[it][w][e];
+        s *= a.alpha;
+        const int m = l & 15, n = rb * 16 + (l >> 4) * 4 + (e & 3);
+        if (lane < 32 && m < a.M && n < a.N) {
+            if constexpr (OUT_F32) static_cast<float*>(a.out)[(int64_t)m * a.N + n] = s;
+            else static_cast<__bf16*>(a.out)[(int64_t)m * a.N + n] = (__bf16)s;
+        }
+        it ^= 1;
+        rb += G;
+        return rb >= n_rb;
+    };
+    for (;;) {
+        if (step(buf[0], buf[2])) break;
+        if (step(buf[1], buf[0])) break;
+        if (step(buf[2], buf[1])) break;
+    }
+}
+
+// LDS of the persistent kernel: two sets of partial sums and the rotated activations
+size_t few_stream_lds(int64_t M, int64_t K, bool quant)
+{
+    const int64_t per = ((K >> 7) + kFusedWaves - 1) / kFusedWaves;
+    return 2 * kFusedWaves * 256 * sizeof(float) + (size_t)(kFusedWaves * per * M * (quant ? 80 : 256));
+}
+
+template <bool QUANT, bool OUT_F32>
+hipError_t launch_few_stream(const FusedArgs& a, hipStream_t st)
+{
+    static LdsAttrOnce raised;
+    const hipError_t e = raised.ensure(reinterpret_cast<const void*>(gemm_few_stream_kernel<QUANT, OUT_F32>), kLdsBytes);
+    if (e != hipSuccess) return e;
+    const unsigned grid = (unsigned)std::min((a.N + 15) / 16, compute_units());
+    hipLaunchKernelGGL((gemm_few_stream_kernel<QUANT, OUT_F32>), dim3(grid), dim3(kFusedWaves * 64), few_stream_lds(a.M, a.K, QUANT), st, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_fused_decode(const void* x, int64_t M, int64_t K, int b, const void* w_codes, const void* w_scales,
@@ -293,6 +494,17 @@ hipError_t launch_fused_decode(const void* x, int64_t M, int64_t K, int b, const
     a.c_lo = (float)(c - (double)a.c_hi);
     a.alpha = alpha;
     const dim3 grid((unsigned)((N + 15) / 16)), block(kFusedWaves * 64);
+    // Persistent workgroups wherever their LDS holds the activations (weight-only: M K <= 73728).  Cold weights, one-shot ->
+    // persistent, us, M = 1 / 4 / 16: N = 6144, K = 4096 6.3 / 6.3 / 18.0 -> 6.1 / 6.4 / 9.6; N = 28672 16.2 / 18.2 / 60.5 ->
+    // 13.2 / 13.1 / 16.7; N = 4096, K = 14336 10.9 / 13.9 -> 9.4 / 11.3; N = K = 1024 level, 8.0 -> 6.7.
+    // The quantizing product, M = 1 / 4: N = 28672, K = 4096 13.0 / 16.2 -> 12.0 / 12.1; N = K = 8192 8.7 / 9.6 -> 8.4 / 9.1;
+    // N = 4096, K = 14336 9.3 / 12.2 -> 9.0 / 11.8; with less than two row-blocks per workgroup and a short K there is nothing
+    // to stream ahead and the one-shot kernel starts faster (N = 6144, K = 4096 5.3 / 5.7 against 5.5 / 6.2; N = K = 1024 2.7 / 3.5
+    // against 3.2 / 4.1).
+    const bool fits = few_stream_lds(M, K, !weight_only) <= (size_t)kLdsBytes;
+    if (weight_only && fits) return out_f32 ? launch_few_stream<false, true>(a, st) : launch_few_stream<false, false>(a, st);
+    if (!weight_only && fits && ((N + 15) / 16 >= 2 * (int64_t)compute_units() || K > 8192))
+        return out_f32 ? launch_few_stream<true, true>(a, st) : launch_few_stream<true, false>(a, st);
     if (weight_only) {
         if (M <= 4) {
             if (out_f32) hipLaunchKernelGGL((gemm_w4a16_decode_kernel<true, 4>), grid, block, 0, st, a);
@@ -301,12 +513,9 @@ hipError_t launch_fused_decode(const void* x, int64_t M, int64_t K, int b, const
             if (out_f32) hipLaunchKernelGGL((gemm_w4a16_decode_kernel<true, 16>), grid, block, 0, st, a);
             else hipLaunchKernelGGL((gemm_w4a16_decode_kernel<false, 16>), grid, block, 0, st, a);
         }
-    } else if (M <= 4) {
-        if (out_f32) hipLaunchKernelGGL((gemm_fused_decode_kernel<true, 4>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((gemm_fused_decode_kernel<false, 4>), grid, block, 0, st, a);
     } else {
-        if (out_f32) hipLaunchKernelGGL((gemm_fused_decode_kernel<true, 16>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((gemm_fused_decode_kernel<false, 16>), grid, block, 0, st, a);
+        if (out_f32) hipLaunchKernelGGL((gemm_fused_decode_kernel<true, 4>), grid, block, 0, st, a);   // (the entry point takes M <= 4)
+        else hipLaunchKernelGGL((gemm_fused_decode_kernel<false, 4>), grid, block, 0, st, a);
     }
     return hipGetLastError();
 }

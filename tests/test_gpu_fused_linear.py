@@ -171,3 +171,17 @@ def test_w4a16_full_size_decode_layers(fp4, oracle):
     for i, L in enumerate(inputs.LLAMA3_8B_LAYERS[:2] + inputs.LLAMA3_8B_LAYERS[3:]):
         N = min(L.N, 4096)
         _w4a16_case(fp4, oracle, 1, N, L.K, 32, False, salt=300 + i)
+
+
+@pytest.mark.parametrize("M,N,K,b", [(1, 8200, 512, 32), (3, 8216, 128 * 9, 64), (4, 12296, 4096, 128), (2, 40, 128 * 67, 16), (4, 8600, 128, 32)])
+def test_fused_persistent_equals_two_launch_path(fp4, M, N, K, b):
+    """Sizes that take the persistent workgroups (two or more row-blocks each, or K > 8192): a ragged last row-block, a share of
+    K that ends inside a batch of fragments, waves with no share, one batch and several per row-block."""
+    test_fused_equals_two_launch_path(fp4, M, N, K, b, False)
+
+
+@pytest.mark.parametrize("M,N,K,b", [(1, 8200, 128, 32), (5, 8216, 128 * 9, 64), (16, 4360, 640, 16), (6, 24, 12288, 32), (7, 24, 12288, 128)])
+def test_w4a16_persistent_against_oracle(fp4, oracle, M, N, K, b):
+    """Several row-blocks per workgroup; M K = 73728, which fills the LDS of a compute unit, and one token more, which takes the
+    one-shot kernel."""
+    _w4a16_case(fp4, oracle, M, N, K, b, False, salt=M + N + b + 1)
