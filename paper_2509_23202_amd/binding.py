@@ -7,6 +7,7 @@ library has not been built (``python -m paper_2509_23202_amd.build``).
 from __future__ import annotations
 
 import ctypes
+import functools
 from pathlib import Path
 
 import torch
@@ -84,14 +85,24 @@ def _check(status: int) -> None:
         raise Fp4mrError(status)
 
 
+# The current stream's handle without a Stream object around it: 0.2 us of host time per call, not 2.8, where a whole
+# one-launch linear of a small layer takes 3 us on the GPU.  (Outputs come from Tensor.new_empty for the same reason: it has no
+# device argument to parse, 1.3 against 1.8 us.)
+try:
+    _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+except AttributeError:   # a build of torch without these two
+    _raw_stream, _current_device = (lambda device: torch.cuda.current_stream(device).cuda_stream), torch.cuda.current_device
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+@functools.lru_cache(maxsize=1024, typed=True)   # (a function of its arguments alone)
 def packed_bytes(rows: int, K: int, fmt: int, flags: int = 0):
     c, s = _sz(), _sz()
     _check(lib.fp4_packed_bytes(rows, K, fmt, flags, ctypes.byref(c), ctypes.byref(s)))
@@ -111,8 +122,8 @@ def _quantize(fn, op, x, had_block, fmt, flags, tensor_scale, codes, scales, wor
         raise TypeError("x must be bfloat16 (or float32 with had_block=1)")
     if codes is None or scales is None:
         cb, sb = packed_bytes(rows, K, fmt, flags & LAYOUT_GEMM)
-        codes = torch.empty(cb, dtype=torch.uint8, device=x.device)
-        scales = torch.empty(sb, dtype=torch.uint8, device=x.device)
+        codes = x.new_empty(cb, dtype=torch.uint8)
+        scales = x.new_empty(sb, dtype=torch.uint8)
     ts = None
     if flags & SCALE_FIT_RANGE:
         # [alpha, beta, 256 scale values]; a caller-supplied tensor (its first two floats set) means: use that alpha, beta
@@ -127,10 +138,10 @@ def _quantize(fn, op, x, had_block, fmt, flags, tensor_scale, codes, scales, wor
             flags |= STATIC_TENSOR_SCALE
             ts = tensor_scale
         else:
-            ts = torch.empty(1, dtype=torch.float32, device=x.device)
+            ts = x.new_empty(1, dtype=torch.float32)
     need = workspace_bytes(op, rows, 0, K, fmt, flags)
     if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+        workspace = x.new_empty(need, dtype=torch.uint8)
     wsz = 0 if workspace is None else workspace.numel()
     if rot is None:
         _check(fn(x.data_ptr(), rows, K, had_block, fmt, codes.data_ptr(), scales.data_ptr(), _ptr(ts), _ptr(workspace), wsz,
@@ -231,10 +242,10 @@ def fp4_gemm(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scal
              flags: int = 0, out=None, workspace=None):
     """out[M,N] = Ahat @ What^T (bf16, or fp32 with OUT_F32).  Operand layouts per A_LAYOUT_GEMM / W_LAYOUT_GEMM."""
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16, device=a_codes.device)
+        out = a_codes.new_empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
     need = workspace_bytes(OP_GEMM_SPLIT_K, M, N, K, fmt, flags)   # (what the call needs plus optional split-K room)
     if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=a_codes.device)
+        workspace = a_codes.new_empty(need, dtype=torch.uint8)
     wsz = 0 if workspace is None else workspace.numel()
     _check(lib.fp4_gemm(a_codes.data_ptr(), a_scales.data_ptr(), _ptr(a_tensor_scale), w_codes.data_ptr(), w_scales.data_ptr(),
                         _ptr(w_tensor_scale), M, N, K, fmt, out.data_ptr(), _ptr(workspace), wsz, flags, _stream()))
@@ -246,7 +257,7 @@ def fp4_fused_linear(x, had_block: int, w_codes, w_scales, N: int, fmt: int = MX
     assert x.is_cuda and x.dim() == 2 and x.is_contiguous() and x.dtype == torch.bfloat16
     M, K = x.shape
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16, device=x.device)
+        out = x.new_empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
     _check(lib.fp4_fused_linear(x.data_ptr(), M, K, had_block, w_codes.data_ptr(), w_scales.data_ptr(), N, fmt, out.data_ptr(),
                                 flags | W_LAYOUT_GEMM, _stream()))
     return out
@@ -257,7 +268,7 @@ def fp4_w4a16_linear(x, had_block: int, w_codes, w_scales, N: int, fmt: int = MX
     assert x.is_cuda and x.dim() == 2 and x.is_contiguous() and x.dtype == torch.bfloat16
     M, K = x.shape
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16, device=x.device)
+        out = x.new_empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
     _check(lib.fp4_w4a16_linear(x.data_ptr(), M, K, had_block, w_codes.data_ptr(), w_scales.data_ptr(), N, fmt, out.data_ptr(),
                                 flags | W_LAYOUT_GEMM, _stream()))
     return out
