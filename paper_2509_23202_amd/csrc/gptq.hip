@@ -97,210 +97,207 @@ __device__ __forceinline__ float decode_scale(uint32_t byte, float s_T, float fa
     }
 }
 
-// 64 columns b0 .. b0+63 (visiting order) of 16 rows per wave: four neighbouring lanes share a row, lane part p keeping
-// the working weights of the block's columns 16p .. 16p+15 in registers.  At column j the lane that owns it rounds it
-// and computes the error, the error is broadcast inside the quad, and every lane updates its 16 registers with row j
-// of the block's triangle of U, read from LDS (zero below the diagonal, so columns already visited need no masking: they
-// are touched but never read again).
-template <int OWNER>
-__device__ __forceinline__ float quad_owner_value(float v)
-{
-    constexpr int ctrl = OWNER * 0x55;  // quad_perm: every lane of the quad reads lane OWNER
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
-}
-
+// One outer block (columns o .. oe-1 in visiting order) of 16 rows in one workgroup, its working weights in LDS for as long
+// as it lasts.  Columns are strictly sequential, so what bounds this is the chain from column to column; everything else is
+// taken out of it.  Four waves sweep: sixteen lanes share a row, lane `part` holding the working weights of the columns
+// 4 part .. 4 part + 3 of the current 64-column block, so that a column costs a lane four updates; the column's weight is
+// broadcast along the sixteen lanes and all of them round it and form its error.  Four waves push: while block b is swept
+// they move the errors of block b - 1 onto the blocks behind b (whose turn is not yet) and fetch block b + 1's triangle of U
+// and scales; between two sweeps they only move block b's errors onto block b + 1, whose factor is in registers by then.  A push
+// is a [16 x 64] x [64 x 16] product per 16 columns on the fp32 MFMA (v_mfma_f32_16x16x4_f32), summed from zero and
+// subtracted once.  Blocks receive the pushes in ascending order.
+// [6144, 4096]: 149 us per outer block with one wave per 16 rows doing all of this in turn, its weights in global memory.
+// The rounding uses the converting instructions (round-to-nearest-even onto E2M1, saturating; decode back to fp32); the two
+// divisions of the definition are multiplications by reciprocals formed once (exact for power-of-two scales and a unit
+// diagonal).
 typedef float v2f_t __attribute__((ext_vector_type(2)));
 
-// Columns 16 P .. 16 P + 15 of the block.  The rounding uses the converting instructions (round-to-nearest-even onto
-// E2M1, saturating; decode back to fp32); the two divisions of the definition are multiplications by reciprocals
-// formed once per block (exact for power-of-two scales and a unit diagonal).  The owner lanes keep their errors and
-// codes in registers (ek, ck) and store them once at the end.
-template <int P>
-__device__ __forceinline__ void sweep_part(float (&w)[16], float (&ek)[16], uint32_t (&ck)[4], const float* Us, const float* Ru,
-                                           const v2f_t* Sc, int row, int part)
+constexpr int kWStride = kOuter + 4;   // floats per row of working weights in LDS: rows start four banks apart
+constexpr int kEStride = kB + 4;
+
+struct SweepState {
+    float w[4], ek[4];
+    uint32_t ck;
+};
+
+// what four columns of the sweep read from LDS: scale and reciprocal (0 for a zero scale), 1 / U[j,j], the lane's part of row j
+// of the triangle (zero below the diagonal: columns already visited need no mask, and are not read again)
+struct SweepOperands {
+    v2f_t sc[4];
+    float4 ru, u[4];
+};
+
+__device__ __forceinline__ SweepOperands sweep_operands(const float* Us, const float* Ru, const v2f_t* Sc, int p, int row, int part)
 {
-    const bool mine = part == P;
+    SweepOperands x;
+    x.ru = *reinterpret_cast<const float4*>(Ru + p * 4);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int j = P * 16 + i;
-        const v2f_t sc = Sc[j * 16 + row];  // scale, 1 / scale (0 for a zero scale)
-        const float wj = w[i];              // meaningful in the lanes with part == P
-        const float t = wj * sc[1];
-        const uint32_t pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, t, t, 1.0f, 0);
-        const uint32_t code = (sc[0] > 0.0f) ? (pk & 15u) : 0u;
-        const v2f_t qv = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(code, 1.0f, 0);
-        const float dq = qv[0] * sc[0];
-        const float e_own = (wj - dq) * Ru[j];
-        ek[i] = mine ? e_own : ek[i];
-        ck[i / 4] = mine ? (ck[i / 4] | (code << (8 * (i & 3)))) : ck[i / 4];
-        const float e = quad_owner_value<P>(e_own);
-        const float4* u4 = reinterpret_cast<const float4*>(Us + j * kB + part * 16);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float4 u = u4[v];
-            w[4 * v] = __fmaf_rn(-e, u.x, w[4 * v]);
-            w[4 * v + 1] = __fmaf_rn(-e, u.y, w[4 * v + 1]);
-            w[4 * v + 2] = __fmaf_rn(-e, u.z, w[4 * v + 2]);
-            w[4 * v + 3] = __fmaf_rn(-e, u.w, w[4 * v + 3]);
-        }
+    for (int i = 0; i < 4; ++i) {
+        x.sc[i] = Sc[(p * 4 + i) * 16 + row];
+        x.u[i] = *reinterpret_cast<const float4*>(Us + (p * 4 + i) * kB + part * 4);
     }
+    return x;
 }
 
-// One outer block (columns o .. oe-1 in visiting order) of 16 rows, one wave, no other wave involved: rows never
-// interact, so the wave walks the outer block's 64-column blocks by itself -- sweep a block, then push that block's 64
-// errors onto the rest of the outer block for its own rows -- and the whole outer block is a single launch.
-//   * sweep: sweep_part above (four lanes per row);
-//   * push: wp[rows, c] -= sum_j e[rows, j] U[b0 + j, c] for b0 + 64 <= c < oe, a [16 x 64] x [64 x 16] product per 16
-//     columns on the fp32 MFMA (v_mfma_f32_16x16x4_f32): the negated errors go through LDS into the A operand once per
-//     block, the rows of U come straight from global memory as the B operand (64 bytes per row per load), and the
-//     accumulator starts as the working weights;
-//   * the next block's columns were just written by other lanes of this wave: a workgroup-scope fence orders the stores
-//     before the loads (one compute unit, one vector cache).
-// The errors also go to err[N, kOuter] for the rank-512 update of everything behind the outer block.
-template <int FMT>
-__global__ __launch_bounds__(64) void gptq_outer_kernel(GptqArgs a, int o, int oe)
+// the four columns 4 P .. 4 P + 3 of the block, the next four's operands on their way meanwhile
+template <int P>
+__device__ __forceinline__ void sweep_part(SweepState& s, const SweepOperands& x, const float* Us, const float* Ru, const v2f_t* Sc, int row, int part)
 {
-    // the block's triangle of U, 1 / U[j,j] and the columns' original positions: two buffers, the next block's set is
-    // fetched into registers before the push and stored after it (its latency hides behind the push)
-    __shared__ __attribute__((aligned(16))) float Us2[2][kB * kB];
-    __shared__ float Ru2[2][kB];
-    __shared__ int cols2[2][kB];
-    __shared__ __attribute__((aligned(8))) v2f_t Sc[kB * 16];   // [column][row of the wave]: scale and its reciprocal
-    __shared__ __attribute__((aligned(16))) float Es[16][kB + 4];  // negated errors of the block: [row][term]
-    const int lane = threadIdx.x;
-    const int row = lane >> 2, part = lane & 3;  // sweep: four lanes per row
-    const int l16 = lane & 15, q = lane >> 4;    // push: MFMA operand coordinates
-    const int n_raw = blockIdx.x * 16 + row;
-    const bool live = n_raw < a.N;
-    const int n = live ? n_raw : a.N - 1;  // idle lanes shadow the last row and store nothing
-    const float s_T = (FMT == 1) ? *a.s_T : 1.0f;
-    const uint8_t* srow = a.scales + (int64_t)n * (a.K / a.G);
-    const int gshift = (a.G == 32) ? 5 : 4;
+    SweepOperands next = x;
+    if constexpr (P + 1 < 16) next = sweep_operands(Us, Ru, Sc, P + 1, row, part);
+    __builtin_amdgcn_sched_barrier(0);
+    const bool mine = part == P;
+    const float ru[4] = {x.ru.x, x.ru.y, x.ru.z, x.ru.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        constexpr int ctrl = 0x150 + P;     // row_newbcast: the sixteen lanes of a row read lane P
+        const float wj = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s.w[i]), ctrl, 0xf, 0xf, true));
+        const float t = wj * x.sc[i][1];
+        const uint32_t pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, t, t, 1.0f, 0);
+        const v2f_t qv = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(pk, 1.0f, 0);
+        const float e = __fmaf_rn(-qv[0], x.sc[i][0], wj) * ru[i];
+        const uint32_t code = (x.sc[i][0] > 0.0f) ? (pk & 15u) : 0u;
+        s.ek[i] = mine ? e : s.ek[i];
+        s.ck = mine ? (s.ck | (code << (8 * i))) : s.ck;
+        s.w[0] = __fmaf_rn(-e, x.u[i].x, s.w[0]);
+        s.w[1] = __fmaf_rn(-e, x.u[i].y, s.w[1]);
+        s.w[2] = __fmaf_rn(-e, x.u[i].z, s.w[2]);
+        s.w[3] = __fmaf_rn(-e, x.u[i].w, s.w[3]);
+    }
+    asm volatile("" : "+v"(s.ck));   // (the codes are put together here: left for the end of the block, they are 64 registers)
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (P + 1 < 16) sweep_part<P + 1>(s, next, Us, Ru, Sc, row, part);
+}
+
+// The errors also go to err[N, kOuter] for the update of everything behind the outer block.
+template <int FMT>
+__global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, int oe)
+{
+    __shared__ __attribute__((aligned(16))) float W[16 * kWStride];      // working weights of the outer block
+    __shared__ __attribute__((aligned(16))) float Us[kB * kB];           // the block's triangle of U, zero below the diagonal
+    __shared__ __attribute__((aligned(16))) v2f_t Sc[kB * 16];           // [column][row]: the block's scales and their reciprocals
+    __shared__ __attribute__((aligned(16))) float Es[16 * kEStride];     // the block's errors
+    __shared__ __attribute__((aligned(16))) uint8_t Sb[kOuter * 16];     // [column][row]: scale bytes of the outer block
+    __shared__ __attribute__((aligned(16))) float Rd[kOuter];            // 1 / U[j,j]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4;
+    const int n0 = blockIdx.x * 16, width = oe - o, blocks = width / kB;
     const float* __restrict__ Ug = a.U;
-    float up[kB * kB / 64];  // a block's triangle on its way to LDS: element (it, lane) = row it, column lane
-    float rup;
-    int cup;
-    auto fetch_block = [&](int bb) {  // (unrolled: all 64 loads in flight together)
-#pragma unroll
-        for (int it = 0; it < kB * kB / 64; ++it) up[it] = (lane >= it) ? Ug[(int64_t)(bb + it) * a.K + bb + lane] : 0.0f;
-        rup = Ug[(int64_t)(bb + lane) * a.K + bb + lane];
-        cup = visit_col(a, bb + lane);
-    };
-    auto stash_block = [&](int buf) {
-#pragma unroll
-        for (int it = 0; it < kB * kB / 64; ++it) Us2[buf][it * 64 + lane] = up[it];
-        Ru2[buf][lane] = 1.0f / rup;
-        cols2[buf][lane] = cup;
-    };
-    fetch_block(o);
-    stash_block(0);
-    __syncthreads();
-    for (int b0 = o; b0 < oe; b0 += kB) {
-        const int cur = ((b0 - o) / kB) & 1;
-        const float* Us = Us2[cur];
-        const float* Ru = Ru2[cur];
-        const int* cols = cols2[cur];
+    const float s_T = (FMT == 1) ? *a.s_T : 1.0f;
 
-        float w[16];
-        const float4* src = reinterpret_cast<const float4*>(a.wp + (int64_t)n * a.K + b0 + part * 16);
+    // rows past the end shadow the last one and store nothing
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float4 t = src[v];
-            w[4 * v] = t.x;
-            w[4 * v + 1] = t.y;
-            w[4 * v + 2] = t.z;
-            w[4 * v + 3] = t.w;
-        }
-        uint32_t sbyte[16];
+    for (int h = 0; h < 2; ++h) {
+        const int row = wave * 2 + h;
+        const float* src = a.wp + (int64_t)min(n0 + row, a.N - 1) * a.K + o;
+        for (int c = lane * 4; c < width; c += 256) *reinterpret_cast<float4*>(&W[row * kWStride + c]) = *reinterpret_cast<const float4*>(src + c);
+    }
+    if (tid < width) {
+        const int gshift = (a.G == 32) ? 5 : 4;
+        const int group = visit_col(a, o + tid) >> gshift, groups = a.K >> gshift;
+        uint32_t bytes[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sbyte[i] = srow[cols[part * 16 + i] >> gshift];  // sixteen independent loads in flight
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int j = part * 16 + i;
-            const float sv = a.table ? a.table[sbyte[i]] : decode_scale<FMT>(sbyte[i], s_T, a.factor);
-            Sc[j * 16 + row] = v2f_t{sv, sv > 0.0f ? 1.0f / sv : 0.0f};
-        }
-        __syncthreads();  // the scale of a column is read by every lane of its row's quad
-        float ek[16];
-        uint32_t ck[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 16; ++i) ek[i] = 0.0f;
-        sweep_part<0>(w, ek, ck, Us, Ru, Sc, row, part);
-        sweep_part<1>(w, ek, ck, Us, Ru, Sc, row, part);
-        sweep_part<2>(w, ek, ck, Us, Ru, Sc, row, part);
-        sweep_part<3>(w, ek, ck, Us, Ru, Sc, row, part);
-        if (live) {
-            float4* ed = reinterpret_cast<float4*>(a.err + (int64_t)n * kOuter + (b0 - o) + part * 16);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) ed[v] = make_float4(ek[4 * v], ek[4 * v + 1], ek[4 * v + 2], ek[4 * v + 3]);
-            *reinterpret_cast<uint4*>(a.q + (int64_t)n * a.K + b0 + part * 16) = make_uint4(ck[0], ck[1], ck[2], ck[3]);
-        }
-        if (b0 + kB >= oe) break;
+        for (int r = 0; r < 16; ++r) bytes[r >> 2] |= (uint32_t)a.scales[(int64_t)min(n0 + r, a.N - 1) * groups + group] << (8 * (r & 3));
+        *reinterpret_cast<uint4*>(&Sb[tid * 16]) = make_uint4(bytes[0], bytes[1], bytes[2], bytes[3]);
+        Rd[tid] = 1.0f / Ug[(int64_t)(o + tid) * a.K + o + tid];
+    }
 
-        fetch_block(b0 + kB);  // lands while the push below runs
-        // push the block's errors onto the rest of the outer block
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            *reinterpret_cast<float4*>(&Es[row][part * 16 + 4 * v]) = make_float4(ek[4 * v], ek[4 * v + 1], ek[4 * v + 2], ek[4 * v + 3]);
+    // Two barriers per block, the same for the sweeping and the pushing waves: behind the sweep (its errors are in LDS), and
+    // behind the push onto the next block (its weights, triangle and scales are).
+    if (wave < 4) {
         __syncthreads();
-        float ea[16];  // A operand of the 16 MFMAs of a column tile: row l16, terms 4 ks + q
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) ea[ks] = Es[l16][ks * 4 + q];
-        // a lane holds rows 4q .. 4q+3 of column l16 of the output tile
-        int64_t wrow[4];
-        bool wlive[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int nn = blockIdx.x * 16 + 4 * q + v;
-            wlive[v] = nn < a.N;
-            wrow[v] = (int64_t)min(nn, a.N - 1) * a.K;
-        }
-        const float* __restrict__ ub = Ug + (int64_t)(b0 + q) * a.K + l16;  // + 4 ks K + c0
-        // 64 columns (four tiles) per trip, the next trip's operands loaded before this trip's MFMAs: a single wave has
-        // nothing else to cover the loads' latency with
-        v4f acc[4], accn[4];
-        float u[4][16], un[4][16];
-        auto fetch = [&](int c0, v4f (&ac)[4], float (&uu)[4][16]) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) ac[t][v] = a.wp[wrow[v] + c0 + 16 * t + l16];
-#pragma unroll
-                for (int ks = 0; ks < 16; ++ks) uu[t][ks] = ub[(int64_t)ks * 4 * a.K + c0 + 16 * t];
+        __syncthreads();
+        const int row = wave * 4 + q, part = l16, n = n0 + row;
+        for (int b = 0; b < blocks; ++b) {
+            SweepState s{};
+            const float4 w4 = *reinterpret_cast<const float4*>(&W[row * kWStride + b * kB + part * 4]);
+            s.w[0] = w4.x, s.w[1] = w4.y, s.w[2] = w4.z, s.w[3] = w4.w;
+            sweep_part<0>(s, sweep_operands(Us, Rd + b * kB, Sc, 0, row, part), Us, Rd + b * kB, Sc, row, part);
+            const float4 e4 = make_float4(s.ek[0], s.ek[1], s.ek[2], s.ek[3]);
+            *reinterpret_cast<float4*>(&Es[row * kEStride + part * 4]) = e4;
+            if (n < a.N) {
+                *reinterpret_cast<float4*>(a.err + (int64_t)n * kOuter + b * kB + part * 4) = e4;
+                *reinterpret_cast<uint32_t*>(a.q + (int64_t)n * a.K + o + b * kB + part * 4) = s.ck;
             }
-        };
-        fetch(b0 + kB, acc, u);
-        for (int c0 = b0 + kB; c0 < oe; c0 += 2 * kB) {  // two trips per iteration so that the buffers swap statically
-            const bool second = c0 + kB < oe;
-            if (second) fetch(c0 + kB, accn, un);
-            v4f sum[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) sum[t] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < 16; ++ks)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) sum[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[ks], u[t][ks], sum[t], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (wlive[v]) a.wp[wrow[v] + c0 + 16 * t + l16] = acc[t][v] - sum[t][v];
-            if (!second) break;
-            if (c0 + 2 * kB < oe) fetch(c0 + 2 * kB, acc, u);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) sum[t] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < 16; ++ks)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) sum[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[ks], un[t][ks], sum[t], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (wlive[v]) a.wp[wrow[v] + c0 + kB + 16 * t + l16] = accn[t][v] - sum[t][v];
+            __syncthreads();
+            __syncthreads();
         }
-        stash_block(cur ^ 1);
-        __threadfence_block();  // the next block's working weights were written by other lanes of this wave
+        return;
+    }
+
+    const int pt = tid - 256, pw = wave - 4;
+    float4 tri[4];   // on its way to LDS for the next block
+    float ea[16];    // errors of the last block (B operand: row l16, terms 4 ks + q)
+    auto fetch_tri = [&](int b) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int row = it * 16 + (pt >> 4), c = (pt & 15) * 4;
+            const float4 u = *reinterpret_cast<const float4*>(Ug + (int64_t)(o + b * kB + row) * a.K + o + b * kB + c);
+            tri[it] = make_float4(c >= row ? u.x : 0.0f, c + 1 >= row ? u.y : 0.0f, c + 2 >= row ? u.z : 0.0f, c + 3 >= row ? u.w : 0.0f);
+        }
+    };
+    v2f_t scn[4];
+    auto decode_scales = [&](int b) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const uint32_t byte = Sb[b * kB * 16 + it * 256 + pt];
+            const float sv = a.table ? a.table[byte] : decode_scale<FMT>(byte, s_T, a.factor);
+            scn[it] = v2f_t{sv, sv > 0.0f ? 1.0f / sv : 0.0f};
+        }
+    };
+    auto stash = [&] {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            *reinterpret_cast<float4*>(&Us[(it * 16 + (pt >> 4)) * kB + (pt & 15) * 4]) = tri[it];
+            Sc[it * 256 + pt] = scn[it];
+        }
+    };
+    auto fetch_u = [&](float (&u)[16], int b, int c) {   // A operand: rows of block b, columns c .. c + 15 of the outer block
+        const float* src = Ug + (int64_t)(o + b * kB + q) * a.K + o + c + l16;
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) u[ks] = src[(int64_t)ks * 4 * a.K];
+    };
+    auto push = [&](const float (&u)[16], int c) {   // (a lane owns four neighbouring columns of row l16)
+        v4f sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(u[ks], ea[ks], sum, 0, 0, 0);
+        v4f* dst = reinterpret_cast<v4f*>(&W[l16 * kWStride + c + 4 * q]);
+        *dst = *dst - sum;
+    };
+    fetch_tri(0);
+    __syncthreads();
+    decode_scales(0);
+    stash();
+    __syncthreads();
+    for (int b = 0; b < blocks; ++b) {
+        float un[16];
+        if (b + 1 < blocks) {
+            fetch_tri(b + 1);
+            fetch_u(un, b, (b + 1) * kB + pw * 16);
+            // the columns behind the next block, 16 at a time, the next factor on its way under the current product
+            int c = (b + 1) * kB + pw * 16;
+            if (b > 0) {
+                float u0[16], u1[16];
+                fetch_u(u0, b - 1, c);
+                for (; c < width; c += 2 * kB) {
+                    const bool second = c + kB < width;
+                    if (second) fetch_u(u1, b - 1, c + kB);
+                    push(u0, c);
+                    if (!second) break;
+                    if (c + 2 * kB < width) fetch_u(u0, b - 1, c + 2 * kB);
+                    push(u1, c + kB);
+                }
+            }
+            decode_scales(b + 1);
+        }
+        __syncthreads();
+        if (b + 1 < blocks) {
+            stash();
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) ea[ks] = Es[l16 * kEStride + ks * 4 + q];
+            push(un, (b + 1) * kB + pw * 16);
+        }
         __syncthreads();
     }
 }
@@ -490,8 +487,8 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
         const int oe = std::min(o + kOuter, (int)K);
         // the outer block itself: every wave sweeps its 16 rows through the block's columns, pushing each 64-column
         // block's errors onto the rest of the outer block as it goes ...
-        if (fmt == 0) hipLaunchKernelGGL(gptq_outer_kernel<0>, dim3(row16), dim3(64), 0, st, a, o, oe);
-        else hipLaunchKernelGGL(gptq_outer_kernel<1>, dim3(row16), dim3(64), 0, st, a, o, oe);
+        if (fmt == 0) hipLaunchKernelGGL(gptq_outer_kernel<0>, dim3(row16), dim3(512), 0, st, a, o, oe);
+        else hipLaunchKernelGGL(gptq_outer_kernel<1>, dim3(row16), dim3(512), 0, st, a, o, oe);
         // ... everything behind the outer block sees all of its errors in one pass
         if (oe < (int)K) update(o, oe, (int)K);
     }
