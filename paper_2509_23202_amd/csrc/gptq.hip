@@ -115,13 +115,17 @@ typedef float v2f_t __attribute__((ext_vector_type(2)));
 constexpr int kWStride = kOuter + 4;   // floats per row of working weights in LDS: rows start four banks apart
 constexpr int kEStride = kB + 4;
 
-struct SweepState {
-    float w[4], ek[4];
-    uint32_t ck;
-};
+// a weight rounded onto the grid of its scale: the code and the grid value (e2m1), before the scale
+__device__ __forceinline__ float round_e2m1(float wj, float inv_scale, uint32_t& packed)
+{
+    const float t = wj * inv_scale;
+    packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, t, t, 1.0f, 0);   // (writes the low byte; the rest is not looked at)
+    return __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(packed, 1.0f, 0)[0];
+}
 
 // what four columns of the sweep read from LDS: scale and reciprocal (0 for a zero scale), 1 / U[j,j], the lane's part of row j
-// of the triangle (zero below the diagonal: columns already visited need no mask, and are not read again)
+// of the triangle.  The triangle is zero on and below the diagonal: a column that has been visited keeps the weight that was rounded,
+// from which its lane makes code and error once more when the block is done -- two selects per column less in the chain.
 struct SweepOperands {
     v2f_t sc[4];
     float4 ru, u[4];
@@ -141,32 +145,24 @@ __device__ __forceinline__ SweepOperands sweep_operands(const float* Us, const f
 
 // the four columns 4 P .. 4 P + 3 of the block, the next four's operands on their way meanwhile
 template <int P>
-__device__ __forceinline__ void sweep_part(SweepState& s, const SweepOperands& x, const float* Us, const float* Ru, const v2f_t* Sc, int row, int part)
+__device__ __forceinline__ void sweep_part(float (&w)[4], uint32_t packed, const SweepOperands& x, const float* Us, const float* Ru, const v2f_t* Sc, int row, int part)
 {
     SweepOperands next = x;
     if constexpr (P + 1 < 16) next = sweep_operands(Us, Ru, Sc, P + 1, row, part);
     __builtin_amdgcn_sched_barrier(0);
-    const bool mine = part == P;
     const float ru[4] = {x.ru.x, x.ru.y, x.ru.z, x.ru.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         constexpr int ctrl = 0x150 + P;     // row_newbcast: the sixteen lanes of a row read lane P
-        const float wj = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s.w[i]), ctrl, 0xf, 0xf, true));
-        const float t = wj * x.sc[i][1];
-        const uint32_t pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, t, t, 1.0f, 0);
-        const v2f_t qv = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(pk, 1.0f, 0);
-        const float e = __fmaf_rn(-qv[0], x.sc[i][0], wj) * ru[i];
-        const uint32_t code = (x.sc[i][0] > 0.0f) ? (pk & 15u) : 0u;
-        s.ek[i] = mine ? e : s.ek[i];
-        s.ck = mine ? (s.ck | (code << (8 * i))) : s.ck;
-        s.w[0] = __fmaf_rn(-e, x.u[i].x, s.w[0]);
-        s.w[1] = __fmaf_rn(-e, x.u[i].y, s.w[1]);
-        s.w[2] = __fmaf_rn(-e, x.u[i].z, s.w[2]);
-        s.w[3] = __fmaf_rn(-e, x.u[i].w, s.w[3]);
+        const float wj = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(w[i]), ctrl, 0xf, 0xf, true));
+        const float e = __fmaf_rn(-round_e2m1(wj, x.sc[i][1], packed), x.sc[i][0], wj) * ru[i];
+        w[0] = __fmaf_rn(-e, x.u[i].x, w[0]);
+        w[1] = __fmaf_rn(-e, x.u[i].y, w[1]);
+        w[2] = __fmaf_rn(-e, x.u[i].z, w[2]);
+        w[3] = __fmaf_rn(-e, x.u[i].w, w[3]);
     }
-    asm volatile("" : "+v"(s.ck));   // (the codes are put together here: left for the end of the block, they are 64 registers)
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (P + 1 < 16) sweep_part<P + 1>(s, next, Us, Ru, Sc, row, part);
+    if constexpr (P + 1 < 16) sweep_part<P + 1>(w, packed, next, Us, Ru, Sc, row, part);
 }
 
 // The errors also go to err[N, kOuter] for the update of everything behind the outer block.
@@ -174,7 +170,7 @@ template <int FMT>
 __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, int oe)
 {
     __shared__ __attribute__((aligned(16))) float W[16 * kWStride];      // working weights of the outer block
-    __shared__ __attribute__((aligned(16))) float Us[kB * kB];           // the block's triangle of U, zero below the diagonal
+    __shared__ __attribute__((aligned(16))) float Us[kB * kB];           // the block's triangle of U, zero on and below the diagonal
     __shared__ __attribute__((aligned(16))) v2f_t Sc[kB * 16];           // [column][row]: the block's scales and their reciprocals
     __shared__ __attribute__((aligned(16))) float Es[16 * kEStride];     // the block's errors
     __shared__ __attribute__((aligned(16))) uint8_t Sb[kOuter * 16];     // [column][row]: scale bytes of the outer block
@@ -210,15 +206,25 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
         __syncthreads();
         const int row = wave * 4 + q, part = l16, n = n0 + row;
         for (int b = 0; b < blocks; ++b) {
-            SweepState s{};
             const float4 w4 = *reinterpret_cast<const float4*>(&W[row * kWStride + b * kB + part * 4]);
-            s.w[0] = w4.x, s.w[1] = w4.y, s.w[2] = w4.z, s.w[3] = w4.w;
-            sweep_part<0>(s, sweep_operands(Us, Rd + b * kB, Sc, 0, row, part), Us, Rd + b * kB, Sc, row, part);
-            const float4 e4 = make_float4(s.ek[0], s.ek[1], s.ek[2], s.ek[3]);
+            float w[4] = {w4.x, w4.y, w4.z, w4.w};
+            const float* const Ru = Rd + b * kB;
+            sweep_part<0>(w, 0u, sweep_operands(Us, Ru, Sc, 0, row, part), Us, Ru, Sc, row, part);
+            // the lane's own four columns: w is what was rounded
+            float e[4];
+            uint32_t codes = 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const v2f_t sc = Sc[(part * 4 + i) * 16 + row];
+                uint32_t packed = 0u;
+                e[i] = __fmaf_rn(-round_e2m1(w[i], sc[1], packed), sc[0], w[i]) * Ru[part * 4 + i];
+                if (sc[0] > 0.0f) codes |= (packed & 15u) << (8 * i);
+            }
+            const float4 e4 = make_float4(e[0], e[1], e[2], e[3]);
             *reinterpret_cast<float4*>(&Es[row * kEStride + part * 4]) = e4;
             if (n < a.N) {
                 *reinterpret_cast<float4*>(a.err + (int64_t)n * kOuter + b * kB + part * 4) = e4;
-                *reinterpret_cast<uint32_t*>(a.q + (int64_t)n * a.K + o + b * kB + part * 4) = s.ck;
+                *reinterpret_cast<uint32_t*>(a.q + (int64_t)n * a.K + o + b * kB + part * 4) = codes;
             }
             __syncthreads();
             __syncthreads();
@@ -234,7 +240,7 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
         for (int it = 0; it < 4; ++it) {
             const int row = it * 16 + (pt >> 4), c = (pt & 15) * 4;
             const float4 u = *reinterpret_cast<const float4*>(Ug + (int64_t)(o + b * kB + row) * a.K + o + b * kB + c);
-            tri[it] = make_float4(c >= row ? u.x : 0.0f, c + 1 >= row ? u.y : 0.0f, c + 2 >= row ? u.z : 0.0f, c + 3 >= row ? u.w : 0.0f);
+            tri[it] = make_float4(c > row ? u.x : 0.0f, c + 1 > row ? u.y : 0.0f, c + 2 > row ? u.z : 0.0f, c + 3 > row ? u.w : 0.0f);
         }
     };
     v2f_t scn[4];
@@ -253,10 +259,14 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
             Sc[it * 256 + pt] = scn[it];
         }
     };
-    auto fetch_u = [&](float (&u)[16], int b, int c) {   // A operand: rows of block b, columns c .. c + 15 of the outer block
-        const float* src = Ug + (int64_t)(o + b * kB + q) * a.K + o + c + l16;
+    // A operand of a push onto 16 columns: rows 4 ks + q of block b.  (Through a buffer resource: one lane offset for all
+    // loads, the rest scalar; sixteen 64-bit addresses would not leave the registers for two factors in flight.)
+    const int u_lane = (q * a.K + l16) * 4;
+    auto fetch_u = [&](float (&u)[16], int b, int c) {
+        const int64_t first = (int64_t)(o + b * kB) * a.K + o, bytes = ((int64_t)a.K * a.K - first) * 4;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ug + first), 0, (int)(uint32_t)min(bytes, (int64_t)0xffffffff), 0x00020000);
 #pragma unroll
-        for (int ks = 0; ks < 16; ++ks) u[ks] = src[(int64_t)ks * 4 * a.K];
+        for (int ks = 0; ks < 16; ++ks) u[ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, u_lane, (ks * 4 * a.K + c) * 4, 0));
     };
     auto push = [&](const float (&u)[16], int c) {   // (a lane owns four neighbouring columns of row l16)
         v4f sum = {0.f, 0.f, 0.f, 0.f};
@@ -275,10 +285,10 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
         if (b + 1 < blocks) {
             fetch_tri(b + 1);
             fetch_u(un, b, (b + 1) * kB + pw * 16);
-            // the columns behind the next block, 16 at a time, the next factor on its way under the current product
-            int c = (b + 1) * kB + pw * 16;
             if (b > 0) {
+                // from the next block on, 16 columns at a time, the next factor on its way under the current product
                 float u0[16], u1[16];
+                int c = (b + 1) * kB + pw * 16;
                 fetch_u(u0, b - 1, c);
                 for (; c < width; c += 2 * kB) {
                     const bool second = c + kB < width;
