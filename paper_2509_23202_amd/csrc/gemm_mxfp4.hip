@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 
 // the tile shapes that have a split-K instantiation (the ones the cost model picks for shapes with few tiles)
 template <int BM, int BN, int WM, int RD, bool PERSIST, int STAGES>
-constexpr bool kHasSplitK = !PERSIST && STAGES == 4 && ((BM == 128 && BN == 128) || (BM == 256 && BN == 128 && WM == 128 && RD == 2) ||
+constexpr bool kHasSplitK = !PERSIST && STAGES == 4 && ((BM == 128 && BN == 128) || (BM == 256 && BN == 128 && WM == 64) ||
                                          (BM == 256 && BN == 256 && WM == 64 && RD == 3));
 
 // splits > 1: every tile is computed by `splits` workgroups, split y taking K-steps y * split_steps .. and writing its
@@ -557,94 +557,93 @@ hipError_t launch_variant(const GemmArgs& g0, bool out_f32, hipStream_t st, int 
     return hipGetLastError();
 }
 
-// tile configuration by shape (the numbers of launch_gemm_mxfp4's switch)
-int pick_variant_mx(int64_t M, int64_t N, int64_t K)
+// What a launch of one of the tile shapes takes: rounds of workgroups over the chip times (a tile's fixed cost + K-steps times a
+// step, which grows with the share of the chip that is busy), in microseconds, fitted to launches of every shape on 154
+// products (M = 80 ... 4096, N = 2048 ... 57344, K = 1536 ... 28672; rms error 2 - 4 %).
+struct TileCost {
+    int variant, bm, bn, per_cu;       // per_cu: workgroups a compute unit holds
+    double fixed, step, step_busy, once;
+};
+// The shapes differ in how they round off.  128 rows or columns less than a square tile's mean more tiles of less arithmetic per
+// byte; 192 and 160 rows fill in between (M = 1111: 192 x 128 tiles on 192 compute units where 256 x 128 had 160, N = 4096,
+// K = 14336: 45.5 -> 38.0 us, K = 4096: 17.0 -> 12.9; 192 x 256, N = 28672, K = 4096: 72 -> 68; M = 600, N = K = 8192, 160 x 128:
+// 28.9 -> 23.4; M = 300, N = 57344, K = 8192, 192 x 256: 102 -> 82).  256 x 128 has eight waves of 64 x 64: two to a SIMD, one's LDS
+// reads under the other's products, against four of 128 x 64 M = 1111, N = 4096, K = 14336: 45.5 -> 41.0 us.
+constexpr TileCost kTileCosts[] = {
+    {2, 128, 128, 2, 2.3, 0.230, 0.233, 1.6},
+    {18, 128, 128, 1, 2.6, 0.163, 0.075, 1.3},   // one workgroup per compute unit, eight-stage ring: up to three quarters of them
+    {17, 128, 128, 1, 2.9, 0.179, 0.063, 1.4},   // (with more of them busy four waves measured level or faster)
+    {5, 256, 128, 1, 3.8, 0.265, 0.150, 0.5},
+    {6, 192, 128, 1, 3.0, 0.229, 0.114, 0.9},
+    {7, 160, 128, 1, 2.7, 0.236, 0.072, 1.6},
+    {8, 192, 256, 1, 5.0, 0.384, 0.202, 0.0},
+    {13, 256, 192, 1, 5.4, 0.373, 0.210, 0.0},
+    {10, 256, 256, 1, 5.7, 0.465, 0.293, 0.0},
+    {11, 256, 256, 1, 4.9, 0.450, 0.324, 0.0},   // persistent: the next tile's first stages and the stores overlap
+};
+
+double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, int cus)
 {
-    int variant;
-    if (M <= 16) variant = 4;
-    else if (M <= 64) variant = 3;
-    else {
-        // Pick the tile by a small cost model: rounds of workgroups over the chip times (fixed cost per tile + K-steps
-        // times the measured step time of that tile).  256x256 and 256x128 hold one workgroup per compute unit,
-        // 128x128 two (and runs faster still when a compute unit has a single one).
-        const int cus = compute_units();
-        const double kt = (double)(K >> 7);
-        auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * (double)((N + bn - 1) / bn); };
-        auto rounds = [](double t, double slots) { return t <= slots ? 1.0 : ceil(t / slots); };
-        const double t10 = rounds(tiles(256, 256), cus) * (9.5 + kt * 0.74);
-        const double t5 = rounds(tiles(256, 128), cus) * (9.0 + kt * 0.37);
-        const double n2 = tiles(128, 128);
-        // (0.47 us per K-step with two workgroups on a compute unit: N = 57344, K = 8192, M = 320, three rounds of 128x128 tiles
-        // measured 131 us against 121 for two rounds of persistent 256x256 tiles)
-        const double t2 = rounds(n2, 2.0 * cus) * (8.0 + kt * (n2 <= cus ? 0.15 : 0.47));
-        variant = 10;
-        double best = t10;
-        if (t5 < best * 0.97) { variant = 5; best = t5; }
-        if (t2 < best * 0.97) { variant = 2; best = t2; }
-        // 256x192: for widths where it tiles into fewer rounds than the square tile (N = 6144 on 256 compute units:
-        // 512 tiles, two full rounds of three quarters the work each, against 384 tiles = one and a half rounds)
-        const double t13 = rounds(tiles(256, 192), cus) * (10.0 + kt * 0.56);
-        if (t13 < best * 0.97) { variant = 13; best = t13; }
-        // more 256x256 tiles than compute units: persistent workgroups, which prefetch the next tile's first stages
-        // and let the output stores drain under its first K-steps (1.5-6% on such shapes, never slower)
-        // -- where the tiles fill whole rounds or many of them; a ragged few rounds (N = 28672, M = 1024 / 2048: 1.75 / 3.5
-        // rounds) measured 5-6 % faster with one workgroup per tile, which the hardware hands to whichever unit is free
-        if (variant == 10 && tiles(256, 256) > cus) {
-            const int64_t t = (int64_t)tiles(256, 256);
-            if (t % cus == 0 || t >= 5 * (int64_t)cus) variant = 11;
-        }
-        // K around 1024: a tile is 8 K-steps, about as long as its own start-up and stores.  128x256 tiles with two
-        // workgroups per compute unit overlap one workgroup's epilogue with the other's main loop: 10-13 % faster
-        // there, level at K = 1536-2048, slower beyond (three stages, one and a half times the operand traffic) and
-        // below (K = 512: the persistent 256x256 workgroups win).
-        if ((variant == 10 || variant == 11) && K >= 768 && K <= 1280) variant = tiles(128, 256) > 2.0 * cus ? 16 : 15;
-        // 128x128 tiles that leave compute units without a tile: one workgroup per unit at most, bound by what a single
-        // unit can pull in -- the eight-stage ring keeps twice the bytes in flight (N = 4096, M = 128: K = 4096 14.3 ->
-        // 12.5 us, K = 14336 43 -> 35 us), and eight waves of 32 x 64 (two per SIMD, one's LDS reads under the other's
-        // MFMAs) are another 3-6 % faster than four of 64 x 64 (variant 17) when the unit has nothing else to run
-        // (up to three quarters of the compute units busy; with more, four waves measured level or faster: N = 28672, M = 96,
-        // 224 tiles: 17.4 us against 20.3)
-        if (variant == 2 && n2 <= cus) variant = 4 * n2 <= 3 * cus ? 18 : 17;
-    }
-    return variant;
+    const int64_t slots = (int64_t)cus * c.per_cu, full = tiles / slots, rest = tiles % slots;
+    double t = c.once + (double)full * (c.fixed + (double)kt * (c.step + c.step_busy));
+    const double busy = (double)rest / (double)slots;
+    // (a 128 x 128 workgroup that has its compute unit to itself)
+    if (rest > 0 && c.per_cu == 2 && rest <= cus) t += 1.8 + (double)kt * 0.211 * (1.0 + 0.387 * busy);
+    else if (rest > 0) t += c.fixed + (double)kt * (c.step + c.step_busy * busy);
+    return t;
 }
 
-// Split-K plan for a product the cost model gives to 128x128, 256x128 or 256x256 tiles (more than 64 tokens).  With few
-// tiles and a long K -- 65 to a few hundred tokens against a narrow layer, the batched-decoding regime -- a handful of
-// compute units each stream a long K range alone and the launch is bound by the latency of their few loads in flight
-// (M = 128, N = 4096, K = 14336: 32 tiles, 42 us, 0.7 TB/s).  Every tile's K range can then be cut into up to eight
-// parts of at least 16 K-steps (whole scale batches of eight), each part one workgroup (17 us on that shape, reduction
-// included).  The number of parts minimises an estimate in microseconds, measured on such shapes:
-//     fixed cost of a tile + K-steps per part x step time + (split only) 3 for the reduction's launch
-//                                                          + splits x M x N x 8 bytes of partials written and read at 4 TB/s
-// and the product is split only for an estimated gain of at least 10 % (a tile of 32 K-steps is mostly fixed cost:
-// N = 4096, K = 4096, M = 128 measured 14.1 us split against 13.8).  splits == 1: leave the product alone.
-void plan_split_k_mx(int64_t M, int64_t N, int64_t K, int variant, int* splits, int* steps)
+// Tile configuration by shape (the numbers of launch_gemm_mxfp4's switch): the cheapest by the table above, with more than 64
+// tokens and a partials buffer also as a split-K run.  With few tiles and a long K -- 65 to a few hundred tokens against
+// a narrow layer, the batched-decoding regime -- a handful of compute units each stream a long K range alone and the launch is
+// bound by the latency of their few loads in flight (M = 128, N = 4096, K = 14336: 32 tiles, 42 us, 0.7 TB/s).  Every tile's
+// K range can then be cut into up to eight parts of at least 16 K-steps (whole scale batches of eight), each part one
+// workgroup of as many tiles (17 us on that shape).  The reduction of the partials costs another launch and their way to
+// memory and back, 5.5 us + bytes at 12 TB/s (they are read back from the last-level cache), and a split has to win 3 %.
+void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int* splits, int* steps)
 {
     *splits = 1;
     *steps = 0;
-    int bm, bn, per_cu;
-    double fixed, step_alone, step_shared;  // step time with at most one workgroup per compute unit / with more
-    if (variant == 2 || variant == 17 || variant == 18) { bm = 128; bn = 128; per_cu = 2; fixed = 8.0; step_alone = variant == 2 ? 0.30 : 0.25; step_shared = 0.40; }
-    else if (variant == 5) { bm = 256; bn = 128; per_cu = 1; fixed = 9.0; step_alone = step_shared = 0.45; }
-    else if (variant == 10) { bm = 256; bn = 256; per_cu = 1; fixed = 9.5; step_alone = step_shared = 0.74; }
-    else return;
+    if (M <= 64) {
+        *variant = M <= 16 ? 4 : 3;
+        return;
+    }
     const int cus = compute_units();
-    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    const int64_t slots = (int64_t)cus * per_cu;
-    const int kt = (int)(K >> 7);
-    const int64_t s_max = std::min<int64_t>(std::min<int64_t>(slots / tiles, kt / 16), 8);
-    const double t1 = fixed + kt * (tiles <= cus ? step_alone : step_shared);
-    double best = 0.9 * t1;
-    for (int64_t s = 2; s <= s_max; ++s) {
-        const int st = (int)(((kt + s - 1) / s + 7) / 8 * 8);
-        const int64_t n = (kt + st - 1) / st;  // parts of st steps that cover K (the last may be shorter)
-        if (n < 2) continue;
-        const double t = fixed + st * (tiles * n <= cus ? step_alone : step_shared) + 3.0 + (double)n * (double)M * (double)N * 8.0 / 4.0e6;
-        if (t < best) {
-            best = t;
-            *splits = (int)n;
-            *steps = st;
+    const int64_t kt = K >> 7;
+    auto tiles = [&](const TileCost& c) { return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
+    double best = 1e30;
+    for (const TileCost& c : kTileCosts) {
+        const int64_t t = tiles(c);
+        if (c.variant == 18 && 4 * t > 3 * (int64_t)cus) continue;
+        if (c.variant == 17 && (4 * t <= 3 * (int64_t)cus || t > cus)) continue;
+        if ((c.variant == 11) != (t > cus) && (c.variant == 10 || c.variant == 11)) continue;
+        const double us = tile_cost(c, t, kt, cus);
+        if (us < best) {
+            best = us;
+            *variant = c.variant;
+        }
+    }
+    // K around 1024: a tile is 8 K-steps, about as long as its own start-up and stores.  128x256 tiles with two
+    // workgroups per compute unit overlap one workgroup's epilogue with the other's main loop: 10-13 % faster than the square
+    // tiles there, level at K = 1536-2048, slower beyond (three stages, one and a half times the operand traffic) and
+    // below (K = 512: the persistent 256x256 workgroups win).
+    if ((*variant == 10 || *variant == 11) && K >= 768 && K <= 1280) *variant = ((M + 127) / 128) * ((N + 255) / 256) > 2 * (int64_t)cus ? 16 : 15;
+    if (!may_split) return;
+    best *= 0.97;
+    for (const TileCost& c : kTileCosts) {
+        if (c.variant != 2 && c.variant != 5 && c.variant != 10) continue;
+        const int64_t t = tiles(c), s_max = std::min<int64_t>(std::min<int64_t>((int64_t)cus * c.per_cu / t, kt / 16), 8);
+        for (int64_t s = 2; s <= s_max; ++s) {
+            const int64_t st = ((kt + s - 1) / s + 7) / 8 * 8;
+            const int64_t n = (kt + st - 1) / st;  // parts of st steps that cover K (the last may be shorter)
+            if (n < 2) continue;
+            const double us = tile_cost(c, t * n, st, cus) + 5.5 + (double)n * (double)M * (double)N * 8.0 / 12.0e6;
+            if (us < best) {
+                best = us;
+                *variant = c.variant;
+                *splits = (int)n;
+                *steps = (int)st;
+            }
         }
     }
 }
@@ -654,9 +653,8 @@ void plan_split_k_mx(int64_t M, int64_t N, int64_t K, int variant, int* splits, 
 // bytes of fp32 partials a split-K run of this product needs (0: the product is not split)
 size_t gemm_mx_split_k_bytes(int64_t M, int64_t N, int64_t K)
 {
-    if (M <= 64) return 0;
-    int splits, steps;
-    plan_split_k_mx(M, N, K, pick_variant_mx(M, N, K), &splits, &steps);
+    int variant, splits, steps;
+    plan_mx(M, N, K, true, &variant, &splits, &steps);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * 4 : 0;
 }
 
@@ -677,21 +675,17 @@ hipError_t launch_gemm_mxfp4(const void* a_codes, const void* a_scales, const vo
     g.N = N;
     g.K = K;
     int splits = 1, split_steps = 0;
-    if (variant == 0) {
-        variant = pick_variant_mx(M, N, K);
-        if (partial && M > 64) plan_split_k_mx(M, N, K, variant, &splits, &split_steps);
-        if ((variant == 17 || variant == 18) && splits > 1) variant = 2;  // the parts run as four-stage workgroups, two per compute unit where needed
-    }
+    if (variant == 0) plan_mx(M, N, K, partial != nullptr, &variant, &splits, &split_steps);
     float* const pp = static_cast<float*>(partial);
     switch (variant) {
         case 1: return launch_variant<256, 256, 128, 128, 4>(g, out_f32, st);
         case 2: return launch_variant<128, 128, 64, 64, 4>(g, out_f32, st, splits, split_steps, pp);
         case 3: return launch_variant<64, 256, 64, 64, 4>(g, out_f32, st);
         case 4: return launch_variant<16, 256, 16, 64, 4>(g, out_f32, st);
-        case 5: return launch_variant<256, 128, 128, 64, 4>(g, out_f32, st, splits, split_steps, pp);
-        case 6: return launch_variant<256, 256, 128, 64, 4>(g, out_f32, st);
-        case 7: return launch_variant<256, 256, 64, 128, 4>(g, out_f32, st);
-        case 8: return launch_variant<256, 256, 128, 128, 4, 4>(g, out_f32, st);
+        case 5: return launch_variant<256, 128, 64, 64, 4>(g, out_f32, st, splits, split_steps, pp);
+        case 6: return launch_variant<192, 128, 48, 64, 4>(g, out_f32, st);
+        case 7: return launch_variant<160, 128, 80, 64, 4>(g, out_f32, st);
+        case 8: return launch_variant<192, 256, 96, 64, 4>(g, out_f32, st);
         case 9: return launch_variant<256, 256, 128, 128, 4, 6>(g, out_f32, st);
         case 10: return launch_variant<256, 256, 64, 128, 4, 3>(g, out_f32, st, splits, split_steps, pp);
         case 11: return launch_variant<256, 256, 64, 128, 4, 3, true>(g, out_f32, st);

@@ -264,7 +264,7 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
     const int u_lane = (q * a.K + l16) * 4;
     auto fetch_u = [&](float (&u)[16], int b, int c) {
         const int64_t first = (int64_t)(o + b * kB) * a.K + o, bytes = ((int64_t)a.K * a.K - first) * 4;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ug + first), 0, (int)(uint32_t)min(bytes, (int64_t)0xffffffff), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ug + first), 0, (int)(uint32_t)(bytes > 0xffffffffll ? 0xffffffffll : bytes), 0x00020000);
 #pragma unroll
         for (int ks = 0; ks < 16; ++ks) u[ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, u_lane, (ks * 4 * a.K + c) * 4, 0));
     };

@@ -256,6 +256,22 @@ def test_gemm_mxfp4_tile_variants_bf16_output_through_the_staged_epilogue(fp4, o
     _gemm_case(fp4, oracle, MX, 272, 528, 1280, seed=80 + variant, out_f32=False, layout_gemm=True)
 
 
+@pytest.mark.parametrize("variant", [5, 6, 7, 8])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (161, 136, 384), (193, 264, 640), (383, 520, 1152), (257, 257, 2176)])
+def test_gemm_mxfp4_tiles_of_160_and_192_rows_and_of_eight_waves(fp4, oracle, variant, M, N, K, knobs):
+    """Tiles whose rows or waves do not divide each other evenly (10 or 12 row-blocks of X dealt to four or eight waves, the last
+    copies of a stage and of a scale batch repeated): one row, one row more than a tile, ragged last tile row and column, fewer
+    K-steps than the ring has stages, an N that keeps the output out of the staged epilogue."""
+    knobs(variant=variant)
+    _gemm_case(fp4, oracle, MX, M, N, K, seed=60 + variant + M, out_f32=False, layout_gemm=True)
+
+
+@pytest.mark.parametrize("variant", [5, 6, 7, 8])
+@pytest.mark.parametrize("K", [640, 2176])
+def test_gemm_mxfp4_scale_batches_of_uneven_tiles(fp4, oracle, variant, K, knobs):
+    test_gemm_mxfp4_scales_that_differ_per_row_block_and_k_block(fp4, oracle, variant, K, knobs)
+
+
 @pytest.mark.parametrize("variant", [17, 18])
 @pytest.mark.parametrize("K", [128, 512, 896, 1024, 1152, 2048, 2176, 4224])
 def test_gemm_mxfp4_eight_stage_ring_with_two_scale_buffers(fp4, oracle, K, variant, knobs):
