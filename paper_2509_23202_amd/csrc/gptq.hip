@@ -59,30 +59,54 @@ __global__ void gptq_iperm_kernel(GptqArgs a)
     if (j < a.K) a.iperm[visit_col(a, j)] = j;
 }
 
-// wp[n, j] = (W H_b)[n, perm[j]]: the rotated weight of the column visited j-th.  One workgroup per row: the row is
-// copied to LDS and rotated there in natural column order (sums of up to 128 bf16 values in fp32 -- exact unless their exponents spread
-// over more than 16 bits -- then one multiplication by 1/sqrt(b) carried in two floats; neighbouring threads read the
-// same block, so the loads are broadcasts), and read back from LDS in visiting order for coalesced stores.
+// wp[n, j] = (W H_b)[n, perm[j]]: the rotated weight of the column visited j-th.  One workgroup per row.  A thread rotates sixteen
+// neighbouring columns in registers -- butterflies, the levels above sixteen across lanes (sums of up to 128 bf16 values in fp32:
+// exact unless their exponents spread over more than 16 bits), then one multiplication by 1/sqrt(b) carried in two floats -- and the
+// row is read back from LDS in visiting order for whole-line stores.  With a sum over the block per column, from LDS, [6144, 4096]
+// took 91 us at b = 16 and 486 at b = 128; now 39 at either.
 __global__ __launch_bounds__(256) void gptq_rotate_gather_kernel(GptqArgs a)
 {
-    extern __shared__ float rowbuf[];  // K floats (the rotated row), then K bf16 (the row as read)
-    uint16_t* const xs = reinterpret_cast<uint16_t*>(rowbuf + a.K);
-    const int n = blockIdx.x;
-    const uint32_t* x2 = reinterpret_cast<const uint32_t*>(a.w + (int64_t)n * a.K);
-    for (int i = threadIdx.x; i < a.K / 2; i += 256) reinterpret_cast<uint32_t*>(xs)[i] = x2[i];
-    __syncthreads();
-    for (int col = threadIdx.x; col < a.K; col += 256) {
-        const int j0 = col & ~(a.b - 1), c = col - j0;
-        float sum = 0.0f;
-#pragma unroll 8
-        for (int r = 0; r < a.b; ++r) {
-            const float v = __uint_as_float((uint32_t)xs[j0 + r] << 16);
-            sum += (__popc((unsigned)(r & c)) & 1) ? -v : v;
+    extern __shared__ __attribute__((aligned(16))) float rowbuf[];  // K floats
+    const int n = blockIdx.x, levels = a.b <= 16 ? 0 : (a.b == 32 ? 1 : a.b == 64 ? 2 : 3);
+    const uint4* src = reinterpret_cast<const uint4*>(a.w + (int64_t)n * a.K);
+    // (K is a multiple of 64 and of b, so the lanes that exchange values are in or out of the row together)
+    for (int c = threadIdx.x; c < a.K / 16; c += 256) {
+        const uint4 lo = src[2 * c], hi = src[2 * c + 1];
+        const uint32_t raw[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            v[2 * i] = __uint_as_float(raw[i] << 16);
+            v[2 * i + 1] = __uint_as_float(raw[i] & 0xffff0000u);
         }
-        rowbuf[col] = (a.b == 1) ? sum : __fmaf_rn(sum, a.c_hi, sum * a.c_lo);
+        if (a.b > 1) {
+#pragma unroll
+            for (int d = 1; d < 16; d <<= 1)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (!(i & d)) {
+                        const float x = v[i], y = v[i + d];
+                        v[i] = x + y;
+                        v[i + d] = x - y;
+                    }
+            for (int l = 0; l < levels; ++l) {
+                const bool upper = (threadIdx.x >> l) & 1;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float o = __shfl_xor(v[i], 1 << l);
+                    v[i] = upper ? o - v[i] : v[i] + o;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = __fmaf_rn(v[i], a.c_hi, v[i] * a.c_lo);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) reinterpret_cast<float4*>(rowbuf)[4 * c + i] = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < a.K; j += 256) a.wp[(int64_t)n * a.K + j] = rowbuf[visit_col(a, j)];
+    float4* dst = reinterpret_cast<float4*>(a.wp + (int64_t)n * a.K);
+    for (int j = threadIdx.x; j < a.K / 4; j += 256)
+        dst[j] = make_float4(rowbuf[visit_col(a, 4 * j)], rowbuf[visit_col(a, 4 * j + 1)], rowbuf[visit_col(a, 4 * j + 2)], rowbuf[visit_col(a, 4 * j + 3)]);
 }
 
 template <int FMT>
@@ -429,14 +453,24 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int u0,
     }
 }
 
-// codes[n, kb] = code of column 2 kb | code of column 2 kb + 1 << 4, fetched from their visiting positions
+// codes[n, kb] = code of column 2 kb | code of column 2 kb + 1 << 4, fetched from their visiting positions: the row goes through LDS,
+// a thread packs eight columns (byte reads from memory: 30 us for [6144, 4096], now 10)
 __global__ __launch_bounds__(256) void gptq_pack_kernel(GptqArgs a)
 {
+    extern __shared__ __attribute__((aligned(16))) uint8_t qrow[];  // K codes
     const int n = blockIdx.x;
-    const uint8_t* qr = a.q + (int64_t)n * a.K;
-    for (int kb = threadIdx.x; kb < a.K / 2; kb += 256) {
-        const uint32_t lo = qr[a.iperm[2 * kb]] & 15u, hi = qr[a.iperm[2 * kb + 1]] & 15u;
-        a.codes[(int64_t)n * (a.K / 2) + kb] = (uint8_t)(lo | (hi << 4));
+    const uint4* src = reinterpret_cast<const uint4*>(a.q + (int64_t)n * a.K);
+    for (int i = threadIdx.x; i < a.K / 16; i += 256) reinterpret_cast<uint4*>(qrow)[i] = src[i];
+    __syncthreads();
+    uint32_t* dst = reinterpret_cast<uint32_t*>(a.codes + (int64_t)n * (a.K / 2));
+    for (int i = threadIdx.x; i < a.K / 8; i += 256) {
+        uint32_t packed = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int4 at = reinterpret_cast<const int4*>(a.iperm)[2 * i + h];
+            packed |= ((qrow[at.x] & 15u) | (qrow[at.y] & 15u) << 4 | (qrow[at.z] & 15u) << 8 | (qrow[at.w] & 15u) << 12) << (16 * h);
+        }
+        dst[i] = packed;
     }
 }
 
@@ -476,15 +510,15 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     a.c_hi = (float)c;
     a.c_lo = (float)(c - (double)a.c_hi);
     a.factor = factor;
-    if (K % kB != 0 || N <= 0 || K > 24576) return hipErrorInvalidValue;  // (a row is staged in LDS twice, as read and rotated: 6 K bytes)
+    if (K % kB != 0 || N <= 0 || K > 24576) return hipErrorInvalidValue;  // (a row is staged in LDS)
 
     const unsigned kblocks = (unsigned)((K + 255) / 256);
     hipLaunchKernelGGL(gptq_iperm_fill_kernel, dim3(kblocks), dim3(256), 0, st, a);
     hipLaunchKernelGGL(gptq_iperm_kernel, dim3(kblocks), dim3(256), 0, st, a);
-    const size_t row_lds = (size_t)K * 6;
+    const size_t row_lds = (size_t)K * 4;
+    static LdsAttrOnce raised;
     if (row_lds > 48 * 1024) {
-        const hipError_t le = hipFuncSetAttribute(reinterpret_cast<const void*>(gptq_rotate_gather_kernel),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds);
+        const hipError_t le = raised.ensure(reinterpret_cast<const void*>(gptq_rotate_gather_kernel), 24576 * 4);
         if (le != hipSuccess) return le;
     }
     hipLaunchKernelGGL(gptq_rotate_gather_kernel, dim3((unsigned)N), dim3(256), row_lds, st, a);
@@ -502,7 +536,7 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
         // ... everything behind the outer block sees all of its errors in one pass
         if (oe < (int)K) update(o, oe, (int)K);
     }
-    hipLaunchKernelGGL(gptq_pack_kernel, dim3((unsigned)N), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(gptq_pack_kernel, dim3((unsigned)N), dim3(256), (size_t)K, st, a);
     return hipGetLastError();
 }
 
