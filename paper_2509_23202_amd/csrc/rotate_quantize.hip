@@ -35,6 +35,10 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWavesPerBlock = kThreads / kWave;
 constexpr int kAmaxPassBlocks = 1024;  // grid cap of the NVFP4 abs-max pass and of the tensor-scale fit pass (4096 partials)
+// Abs-max partials that every wave of the quantize pass reduces for itself, one launch less.  K = 8192, separate launch -> folded, us:
+// M = 100 (400 partials) 8.2 -> 6.9, M = 200 8.4 -> 7.4, M = 320 (1280) 9.4 -> 8.6; at 4000 partials the sixty loads per lane cost
+// more than the launch (M = 1000 12.4 -> 12.9, M = 2048 17 -> 21).
+constexpr int kFoldedPartials = 1536;
 constexpr int kFitRounds = 3;          // alternations of the tensor-scale fit
 constexpr int kRangePassBlocks = 512;  // grid cap of the range pre-pass (two partials per wave: the same 4096 slots)
 
@@ -139,7 +143,13 @@ __device__ __forceinline__ float load_tensor_scale(const RqArgs& a, int lane)
     uint32_t m;
     if (a.n_partials > 0) {
         m = 0;
-        for (int i = lane; i < a.n_partials; i += 64) m = max(m, a.amax_partial[i]);
+        for (int i0 = lane; i0 < a.n_partials; i0 += 8 * 64) {   // (eight loads in flight; the last ones repeat the last partial)
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = a.amax_partial[min(i0 + u * 64, a.n_partials - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m = max(m, v[u]);
+        }
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d));
     } else {
@@ -858,7 +868,7 @@ hipError_t launch_rotate_quantize(const void* x, int64_t rows, int64_t K, int b,
         if (e != hipSuccess) return e;
         // blocks that had no item still wrote their (zero) partial: every wave of the grid stores one
         const int n_partials = pass_blocks * kWavesPerBlock;
-        if (n_partials <= 256 && policy != 3) {
+        if (n_partials <= kFoldedPartials && policy != 3) {
             a.n_partials = n_partials;  // few-token calls: one launch less, the quantize pass reduces the partials itself
         } else {
             hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, st, a.amax_partial, n_partials, a.amax_bits);

@@ -654,3 +654,17 @@ def test_gemm_few_token_dispatch_on_seeded_random_shapes(fp4, oracle, case, knob
     i, fmt, M, N, K, out_f32, grid = case
     knobs(grid=grid)
     _gemm_case(fp4, oracle, fmt, M, N, K, seed=6000 + i, out_f32=out_f32, layout_gemm=True)
+
+
+@pytest.mark.parametrize("rows", [256, 257, 1536, 1537])
+@pytest.mark.parametrize("layout_gemm", [False, True])
+def test_nvfp4_tensor_scale_on_either_side_of_the_folded_reduction(fp4, rows, layout_gemm):
+    """K = 2048: one abs-max partial per row (rounded up to four), reduced by the quantize pass itself up to 1536 of them and by a
+    launch of its own beyond.  The only non-zero block is the last one, one element of value 1: rotated it is 1/4 everywhere,
+    so the tensor scale is 0.25 / 2688 rounded once, whichever way the maximum travelled."""
+    import torch
+    x = torch.zeros(rows, 2048, device="cuda", dtype=torch.bfloat16)
+    x[-1, -16] = 1.0
+    _, _, ts = fp4.fp4_rotate_quantize(x, 16, NV, flags=fp4.LAYOUT_GEMM if layout_gemm else 0)
+    torch.cuda.synchronize()
+    assert float(np_(ts)[0]) == float(np.float32(0.25) / np.float32(2688.0))
