@@ -272,7 +272,10 @@ fp4mr_status_t fp4_gptq_quantize_weights(const void* w, int64_t N, int64_t K, in
  *   x          [T,K] bf16 row-major, device (T calibration rows; rows = M in fp4_workspace_bytes), K <= 24576
  *   hessian    [K,K] fp32 row-major, device; overwritten, or added to when accumulate != 0 (batches of rows)
  *   workspace  fp4_workspace_bytes(FP4MR_OP_GPTQ_HESSIAN, T, 0, K, fmt ignored, 0) = 4 T K bytes
- * The result is symmetric bit for bit (added to a symmetric matrix).
+ * The rows are rotated first and products and sums are as accurate as fp32's: the error of H[i][j] is relative to
+ * sqrt(H[i][i] H[j][j]), also where channels of a block share a large component that the rotation takes out of most of them.
+ * The result is symmetric bit for bit (added to a symmetric matrix).  Rows with non-finite values leave NaNs or infinities in
+ * the rows and columns of H that belong to their blocks.
  */
 fp4mr_status_t fp4_gptq_accumulate_hessian(const void* x, int64_t T, int64_t K, int had_block, float* hessian, int accumulate,
                                            void* workspace, size_t workspace_bytes, void* stream);

@@ -285,7 +285,7 @@ fp4mr_status_t fp4_gptq_accumulate_hessian(const void* x, int64_t T, int64_t K, 
     const size_t need = align256((size_t)T * K * 4);
     if (!workspace || workspace_bytes < need || !aligned16(workspace)) return FP4MR_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return launch_gptq_hessian(x, T, K, had_block, hessian, accumulate != 0, workspace, workspace_bytes, st) == hipSuccess ? FP4MR_OK : FP4MR_ERR_DEVICE;
+    return launch_gptq_hessian(x, T, K, had_block, hessian, accumulate != 0, workspace, st) == hipSuccess ? FP4MR_OK : FP4MR_ERR_DEVICE;
 }
 
 fp4mr_status_t fp4_gptq_prepare(const float* hessian, int64_t K, float damp, int act_order, int32_t* perm_out, float* hinv_u_out,

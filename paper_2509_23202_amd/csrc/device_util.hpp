@@ -127,6 +127,28 @@ __device__ __forceinline__ float e4m3_decode(uint32_t c)
     }
 }
 
+// ---------------------------------------------------------------- 24 bits on the bf16 MFMA
+// A value as the sum of three bf16: 8 + 8 + 8 significant bits are a binary32's 24, and what a rounding leaves over is exact
+// in the subtraction, so hi + mid + lo is the value itself (down to 2^-110, below which the last part may underflow).
+struct Split3 {
+    v8bf part[3];
+};
+__device__ __forceinline__ Split3 split3(const float (&x)[8])
+{
+    Split3 s;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        float rest = x[i];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const __bf16 h = (__bf16)rest;
+            s.part[p][i] = h;
+            rest -= (float)h;
+        }
+    }
+    return s;
+}
+
 // ---------------------------------------------------------------- misc
 __device__ __forceinline__ float fabs_max(float a, float b) { return fmaxf(a, fabsf(b)); }
 

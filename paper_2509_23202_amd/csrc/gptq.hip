@@ -336,27 +336,6 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
     }
 }
 
-// A value as the sum of three bf16: 8 + 8 + 8 significant bits are a binary32's 24, and what a rounding leaves over is exact
-// in the subtraction, so hi + mid + lo is the value itself (down to 2^-110, below which the last part may underflow).
-struct Split3 {
-    v8bf part[3];
-};
-__device__ __forceinline__ Split3 split3(const float (&x)[8])
-{
-    Split3 s;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float rest = x[i];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const __bf16 h = (__bf16)rest;
-            s.part[p][i] = h;
-            rest -= (float)h;
-        }
-    }
-    return s;
-}
-
 // wp[n, c] -= sum_{j < kOuter} err[n, j] * U[u0 + j, c] for the columns c_begin <= c < c_end (visiting order): a dense fp32
 // contraction, [N x 512] . [512 x columns].  The fp32 MFMA (157 TFLOP/s) bounded it, 82 of them; here both factors are split
 // into three bf16 and the six products above 2^-24 of the whole run on the bf16 MFMA, 6 / 16 of the time.  They are exact in

@@ -1,19 +1,19 @@
 // Hessian of a layer from calibration rows (arXiv 2509.23202, Section 4 "Standard GPTQ": the second-order information of
 // ||X What - X W||^2 is X^T X; Section 4.1 "Ingredient 3": of the ROTATED inputs X H_b).
 //
-// The rotation is linear and the same for every row, so it is taken out of the sum:
-//     (X H_b)^T (X H_b) = H_b^T (X^T X) H_b ,
-// and X^T X is a product of bf16 values: its terms are exact in fp32, so the bf16 MFMA (16x the fp32 MFMA's rate) forms
-// them without loss, with the fp32 accumulation the rotated product had.  The rotation then costs two butterflies on a
-// finished 128 x 128 tile -- K^2 values instead of T K, none of them through memory -- and no rotated copy of X exists.
+// The rows are rotated FIRST and every rotated value is kept to 24 bits, so that an entry's error is relative to
+// sqrt(h_ii h_jj) of its own two channels.  (Rotating the finished X^T X is three times as fast, but where channels of a
+// block have something in common most rotated channels are small differences of large sums: with an offset of 100 under
+// unit noise the entries were off by 1 % of that scale, and diagonal entries could come out negative.)  Two launches:
+//   hessian_rotate_kernel   X -> the rotated rows in fp32, in the workspace, eight rows of a column side by side
+//   hessian_split_kernel    X'^T X' on the bf16 MFMA, both factors split into three bf16 parts: the six products above
+//                           2^-24 of the whole
+// 8192 rows at K = 4096: 0.87 ms (4.15 on the fp32 MFMA over both triangles; 0.27 for rotating X^T X).  Largest error over
+// sqrt(h_ii h_jj), T = 8192, b = 128, fp32 MFMA -> now: normal rows with loud channels 5.4e-6 -> 1.1e-6, offset 30
+// 3.5e-5 -> 7e-7, offset 100 3.3e-6 -> 5e-7, one factor per block and 0.2 % of noise 4.8e-6 -> 7e-7; a single row
+// 6e-8 -> 1e-7 (mean 2.5e-8 -> 2.6e-8).
+// Without rotation (b == 1) the values are bf16 and their products exact in fp32: hessian_kernel, straight from X.
 // The matrix is symmetric: only tiles on and below the diagonal are computed, each is stored twice.
-//
-// Bound: LDS bandwidth (a 64 x 64 wave tile reads 16 KB per 32 MFMAs), then the L2.  Tile 128 x 128 over 64 rows of X at a
-// time, four waves, two workgroups per compute unit (64.5 KB of LDS) so that one's staging runs under the other's MFMAs.
-// 8192 rows at K = 4096 (137 GFLOP in one triangle): 206 us; 4.12 ms before, when the rows were rotated into an fp32 copy
-// (0.6 ms at b = 128) and multiplied, both triangles, on the fp32 MFMA (3.5 ms).  Against 64 bits: 3.9e-7 (1.4e-6 before).
-// X is staged as it lies in memory, rows along the contraction; the MFMA operands want the contraction along a lane's
-// registers, which the transposing LDS read (ds_read_b64_tr_b16) provides: no transposed copy in memory, no packing.
 #include "device_util.hpp"
 #include "internal.hpp"
 
@@ -33,14 +33,15 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 struct HessArgs {
     const uint16_t* x;  // [T, K] bf16
     float* H;           // [K, K]
-    float* part;        // partial tiles of the split tail
+    float* xr;          // b > 1: the rotated rows, packed (packed_at)
+    float* part;        // b == 1: partial tiles of the split tail
     int64_t T;
     int K, b, accumulate;
     int nt;             // tiles per side
     int full;           // tiles 0 .. full - 1 take all of T in one workgroup ...
     int parts;          // ... each of the others is shared by this many
     int chunk;          // rows of X per part (multiple of kRows)
-    float inv_b;
+    float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b
 };
 
 // p-th tile of the lower triangle (row >= col), counted super-row by super-row
@@ -72,30 +73,7 @@ __device__ __forceinline__ void tile_of(int p, int nt, int& row, int& col)
 // transposing read takes, and those of its neighbour group eight rows on, fall into different banks
 __device__ __forceinline__ int swz(int t) { return (t & 7) ^ ((t >> 1) & 4); }
 
-__device__ __forceinline__ void butterfly(float (&v)[64], int b, bool upper)
-{
-#pragma unroll
-    for (int s = 1; s < 64; s *= 2) {
-        if (s < b) {
-#pragma unroll
-            for (int e = 0; e < 64; ++e) {
-                if (e & s) continue;
-                const float lo = v[e], hi = v[e + s];
-                v[e] = lo + hi;
-                v[e + s] = lo - hi;
-            }
-        }
-    }
-    if (b == 128) {
-#pragma unroll
-        for (int e = 0; e < 64; ++e) {
-            const float other = __shfl_xor(v[e], 1);
-            v[e] = upper ? other - v[e] : v[e] + other;
-        }
-    }
-}
-
-// the finished sums of tile (ti, tj), in the MFMA's output order, rotated from both sides and stored with their mirror image
+// the finished sums of tile (ti, tj), in the MFMA's output order, stored with their mirror image
 __device__ __forceinline__ void finish_tile(const HessArgs& a, int ti, int tj, const v4f (&acc)[4][4], float* S)
 {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
@@ -108,24 +86,6 @@ __device__ __forceinline__ void finish_tile(const HessArgs& a, int ti, int tj, c
 #pragma unroll
             for (int v = 0; v < 4; ++v) S[(wr + i * 16 + 4 * q + v) * kPitch + wc + j * 16 + l16] = acc[i][j][v];
     __syncthreads();
-    if (a.b > 1) {
-        float v[64];
-        const int line = tid >> 1, half = tid & 1;
-        float* p = S + line * kPitch + half * 64;
-#pragma unroll
-        for (int e = 0; e < 64; ++e) v[e] = p[e];
-        butterfly(v, a.b, half);
-#pragma unroll
-        for (int e = 0; e < 64; ++e) p[e] = v[e];
-        __syncthreads();
-        p = S + half * 64 * kPitch + line;
-#pragma unroll
-        for (int e = 0; e < 64; ++e) v[e] = p[e * kPitch];
-        butterfly(v, a.b, half);
-#pragma unroll
-        for (int e = 0; e < 64; ++e) p[e * kPitch] = v[e] * a.inv_b;  // (1/sqrt(b) from each side: a power of two, exact)
-        __syncthreads();
-    }
     const int r0 = ti * kT, c0 = tj * kT;
     const int c = tid & (kT - 1), r1 = tid >> 7;  // a wave stores 64 consecutive floats
     const bool diag = ti == tj;
@@ -135,8 +95,7 @@ __device__ __forceinline__ void finish_tile(const HessArgs& a, int ti, int tj, c
 #pragma unroll 4
         for (int r = r1; r < kT; r += 2) {
             if (row0 + r >= a.K) break;
-            // (on the diagonal both halves take the lower one's values: the two butterflies do not round symmetrically)
-            const bool swap = side || (diag && c > r);
+            const bool swap = side || (diag && c > r);  // (on the diagonal both halves take the lower one's values)
             const float s = swap ? S[c * kPitch + r] : S[r * kPitch + c];
             float* p = a.H + (int64_t)(row0 + r) * a.K + col0 + c;
             *p = a.accumulate ? *p + s : s;
@@ -144,6 +103,11 @@ __device__ __forceinline__ void finish_tile(const HessArgs& a, int ti, int tj, c
     }
 }
 
+// ---------------------------------------------------------------- b == 1: bf16 values, exact products
+// Bound: LDS bandwidth (a 64 x 64 wave tile reads 16 KB per 32 MFMAs), then the L2.  Tile 128 x 128 over 64 rows of X at a
+// time, four waves, two workgroups per compute unit (64.5 KB of LDS) so that one's staging runs under the other's MFMAs.
+// X is staged as it lies in memory, rows along the contraction; the MFMA operands want the contraction along a lane's
+// registers, which the transposing LDS read (ds_read_b64_tr_b16) provides: no transposed copy in memory, no packing.
 template <bool WHOLE>  // WHOLE: K % 8 == 0, every 16-byte piece of a row is inside it or outside
 __global__ __launch_bounds__(256, 2) void hessian_kernel(HessArgs a)
 {
@@ -287,28 +251,282 @@ __global__ __launch_bounds__(256, 2) void hessian_tail_kernel(HessArgs a)
     finish_tile(a, ti, tj, acc, S);
 }
 
+// ---------------------------------------------------------------- b > 1: rotated rows
+
+// Where element (t, column) of the rotated rows lies: eight rows of a column side by side (what a lane of the bf16 MFMA takes
+// of the contraction), columns behind each other; a last group of fewer rows is packed, so that T K floats hold it all.
+__device__ __forceinline__ int64_t packed_at(const HessArgs& a, int64_t group, int col, int rows) { return group * 8 * a.K + (int64_t)col * rows; }
+
+// Eight rows by 512 columns per workgroup.  A thread rotates sixteen neighbouring columns of a row in registers -- butterflies, the
+// levels above sixteen across lanes, fp32 sums of up to 128 bf16 values -- and the power of two nearest below sqrt(b) is
+// divided out, exactly; what is left of 1 / b (a half at b = 32 and 128) is multiplied onto the finished sums.
+constexpr int kRotCols = 512;
+__global__ __launch_bounds__(256) void hessian_rotate_kernel(HessArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float S[kRotCols * 8 + kRotCols / 16 * 8];  // [column][row]; eight floats more every sixteen columns (banks)
+    const int tid = threadIdx.x, r = tid >> 5, piece = tid & 31;
+    const int c0 = blockIdx.y * kRotCols, cols = min(kRotCols, a.K - c0);
+    const int64_t group = blockIdx.x;
+    const int rows = (int)min((int64_t)8, a.T - group * 8);
+    const int levels = a.b == 16 ? 0 : (a.b == 32 ? 1 : a.b == 64 ? 2 : 3);
+    uint4 lo = make_uint4(0u, 0u, 0u, 0u), hi = lo;
+    if (r < rows && piece * 16 < cols) {  // (K is a multiple of b: lanes that exchange values are in or out of the row together)
+        const uint4* src = reinterpret_cast<const uint4*>(a.x + (group * 8 + r) * a.K + c0 + piece * 16);
+        lo = src[0];
+        hi = src[1];
+    }
+    const uint32_t raw[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        v[2 * i] = __uint_as_float(raw[i] << 16);
+        v[2 * i + 1] = __uint_as_float(raw[i] & 0xffff0000u);
+    }
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (!(i & d)) {
+                const float x = v[i], y = v[i + d];
+                v[i] = x + y;
+                v[i + d] = x - y;
+            }
+    for (int l = 0; l < levels; ++l) {
+        const bool upper = (tid >> l) & 1;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float o = __shfl_xor(v[i], 1 << l);
+            v[i] = upper ? o - v[i] : v[i] + o;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S[(piece * 16 + i) * 8 + piece * 8 + r] = v[i] * a.in_scale;
+    __syncthreads();
+    float* const dst = a.xr + packed_at(a, group, c0, rows);
+    if (rows == 8) {
+        for (int i = tid; i < cols * 2; i += 256)
+            reinterpret_cast<float4*>(dst)[i] = *reinterpret_cast<const float4*>(&S[i * 4 + (i >> 5) * 8]);
+    } else {
+        for (int i = tid; i < cols * rows; i += 256) {
+            const int c = i / rows;
+            dst[i] = S[c * 8 + (c >> 4) * 8 + i - c * rows];
+        }
+    }
+}
+
+// A tile of 2 W x 2 W, a W x W quarter per wave, 32 rows of X' at a time: split and written to LDS in the MFMA's operand order
+// (lane (r, q) of a 16-wide block: column r, rows 8 q .. 8 q + 7), the next 32 rows fetched meanwhile.  The products of 32 rows
+// are summed from zero, the largest apart from the five others (the MFMA cuts off what an addition leaves over, the vector
+// adder rounds), and added to the accumulator once.  The column operand is the MFMA's A, so that a lane
+// owns four neighbouring columns of a row of H.
+// Bound at W = 64: a wave issues 96 MFMAs (1536 cycles) and 370 vector instructions (1480, half of them the split) per stage, and
+// two workgroups per compute unit overlap the two in part: 512 tiles over 8192 rows 0.70 ms, 1.2 PFLOP/s.
+template <int W>
+__global__ __launch_bounds__(256, 2) void hessian_split_kernel(HessArgs a)
+{
+    constexpr int NT = W / 16, BL = 2 * NT, PER = BL / 2;   // 16-wide blocks per wave side, per operand, and staged per wave
+    constexpr int AHEAD = W == 64 ? 1 : 4;                  // stages on their way (a small tile's is shorter than a load takes)
+    constexpr int BUFS = W == 64 ? 1 : 2;                   // stages in LDS
+    constexpr int SUB = 64 / W;
+    __shared__ v8bf St[BUFS][3][2 * BL][64];                 // [part][block of 16 rows, then columns, of the tile][lane]
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of the tiles
+    const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
+    const int p = xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3);
+    int ti, tj;
+    tile_of((SUB > 1 ? a.full : 0) + p / (SUB * SUB), a.nt, ti, tj);
+    if constexpr (SUB > 1) {   // a part of one of the tiles that are left
+        ti = SUB * ti + p / SUB % SUB;
+        tj = SUB * tj + p % SUB;
+        if (tj > ti || ti * 2 * W >= a.K) return;
+    }
+    const bool diag = ti == tj;
+    const int r0 = ti * 2 * W, c0 = tj * 2 * W;
+    const int wr = (wave >> 1) * NT, wc = (wave & 1) * NT;   // first block of rows / columns of the wave's quarter
+    const bool idle = diag && wr < wc;                       // (above the diagonal)
+
+    // This wave stages the blocks wave, wave + 4, ... of the 2 BL.  Every request is unconditional (the compiler's waits count on
+    // it): what does not exist is requested with zero size and reads as zero.  (Columns past the end: the last one again,
+    // it only feeds outputs that are not stored.  A diagonal tile takes its rows for both.)
+    float ahead[AHEAD][PER][8];
+    const int64_t stages = a.T / 32;
+    int col[PER];
+#pragma unroll
+    for (int h = 0; h < PER; ++h) {
+        const int block = wave + 4 * h;
+        col[h] = min((block < BL ? r0 + block * 16 : c0 + (block - BL) * 16) + l16, a.K - 1);
+    }
+    auto fetch = [&](int64_t s, float (&v)[PER][8]) {
+        const bool valid = s < stages;
+        float* const base = a.xr + (valid ? s : 0) * 32 * a.K;
+#pragma unroll
+        for (int h = 0; h < PER; ++h) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, valid && !(diag && wave + 4 * h >= BL) ? 128 * a.K : 0, 0x00020000);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const v4f x = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs, (q * a.K + col[h]) * 32, half * 16, 0));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[h][half * 4 + i] = x[i];
+            }
+        }
+    };
+    // the last T % 32 rows, the rest of the stage zero
+    auto fetch_rest = [&](float (&v)[PER][8]) {
+        const int64_t last = (a.T - 1) / 8, group = stages * 4 + q, g = min(group, last);
+        const int rows = (int)min((int64_t)8, a.T - g * 8);
+#pragma unroll
+        for (int h = 0; h < PER; ++h) {
+            const float* src = a.xr + packed_at(a, g, col[h], rows);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float x = src[min(i, rows - 1)];
+                v[h][i] = group == g && i < rows ? x : 0.0f;
+            }
+        }
+    };
+    v4f acc[NT][NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    const int wcol = diag ? wc : BL + wc;
+    auto put = [&](const float (&v)[PER][8], int buf) {
+#pragma unroll
+        for (int h = 0; h < PER; ++h) {
+            const Split3 x = split3(v[h]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) St[buf][k][wave + 4 * h][lane] = x.part[k];
+        }
+    };
+    auto multiply = [&](int buf) {
+        v8bf u[3][NT];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) u[k][j] = St[buf][k][wcol + j][lane];
+        v8bf next[3];   // row operands, one block ahead
+#pragma unroll
+        for (int k = 0; k < 3; ++k) next[k] = St[buf][k][wr][lane];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            v8bf e[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) e[k] = next[k];
+            if (i + 1 < NT) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) next[k] = St[buf][k][wr + i + 1][lane];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // (part of the column, part of the row): 2^-16, 2^-8 of the product, then 1
+            constexpr int order[6][2] = {{2, 0}, {1, 1}, {0, 2}, {1, 0}, {0, 1}, {0, 0}};
+            v4f low[NT], high[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) low[j] = high[j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 6; ++s)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    v4f& d = s < 5 ? low[j] : high[j];
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u[order[s][0]][j], e[order[s][1]], d, 0, 0, 0);
+                }
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] += high[j] + low[j];
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < AHEAD; ++d) fetch(d, ahead[d]);
+    if constexpr (BUFS == 1) {
+        for (int64_t s = 0; s < stages; ++s) {
+            __syncthreads();
+            put(ahead[0], 0);
+            __syncthreads();
+            fetch(s + 1, ahead[0]);
+            multiply(0);
+        }
+    } else {
+        // the next stage is split under the products of this one; one barrier each: a stage overwrites what was read before the last
+        put(ahead[0], 0);
+        fetch(AHEAD, ahead[0]);
+        for (int64_t s = 0; s < stages; s += AHEAD) {   // (up to AHEAD - 1 stages of zeros behind the last)
+#pragma unroll
+            for (int d = 0; d < AHEAD; ++d) {
+                __syncthreads();
+                put(ahead[(d + 1) % AHEAD], (d + 1) % 2);
+                fetch(s + d + 1 + AHEAD, ahead[(d + 1) % AHEAD]);
+                multiply(d % 2);
+            }
+        }
+    }
+    if (a.T % 32) {
+        fetch_rest(ahead[0]);
+        __syncthreads();
+        put(ahead[0], 0);
+        __syncthreads();
+        multiply(0);
+    }
+    if (idle) return;
+    // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 block; of the diagonal blocks the lower half counts, and is
+    // mirrored like all the rest (K is a multiple of 16)
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        const int row = r0 + (wr + i) * 16 + l16;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int col = c0 + (wc + j) * 16 + 4 * q;
+            if (row >= a.K || col >= a.K || (diag && wr + i < wc + j)) continue;
+            const bool cut = diag && wr + i == wc + j;
+            const v4f s = acc[i][j] * a.out_scale;
+            float* const own = a.H + (int64_t)row * a.K + col;
+            float* const mirror = a.H + (int64_t)col * a.K + row;
+            if (!cut) {
+                v4f* const d = reinterpret_cast<v4f*>(own);
+                *d = a.accumulate ? *d + s : s;
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (cut && col + v <= row) own[v] = a.accumulate ? own[v] + s[v] : s[v];
+                float* const m = mirror + (int64_t)v * a.K;
+                if (!cut || col + v < row) *m = a.accumulate ? *m + s[v] : s[v];
+            }
+        }
+    }
+}
+
 }  // namespace
 
-hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float* H, bool accumulate, void* workspace, size_t workspace_bytes, hipStream_t st)
+hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float* H, bool accumulate, void* workspace, hipStream_t st)
 {
     if (T <= 0 || K <= 0 || K > 24576) return hipErrorInvalidValue;
     HessArgs a{};
     a.x = static_cast<const uint16_t*>(x);
     a.H = H;
-    a.part = static_cast<float*>(workspace);
+    a.xr = a.part = static_cast<float*>(workspace);   // 4 T K bytes either way
     a.T = T;
     a.K = (int)K;
     a.b = b;
     a.accumulate = accumulate ? 1 : 0;
-    a.inv_b = 1.0f / (float)b;
     a.nt = (int)((K + kT - 1) / kT);
-    const int tiles = a.nt * (a.nt + 1) / 2, slots = 2 * compute_units();
-    // Two workgroups per compute unit work at a time.  The tiles beyond whole rounds of those would run on a mostly idle
-    // chip for a whole tile's time (K = 4096: 528 tiles for 512 slots), so T is cut into parts for them, of at least 512
-    // rows (less does not repay the second launch), as many as fit the round and the caller's workspace.
-    const int rem = tiles % slots;
+    // two workgroups per compute unit work at a time; the tiles beyond whole rounds of those would run on a mostly idle chip for a
+    // whole tile's time (K = 4096: 528 tiles for 512 slots)
+    const int tiles = a.nt * (a.nt + 1) / 2, slots = 2 * compute_units(), rem = tiles % slots;
+    if (b > 1) {
+        a.in_scale = b >= 64 ? 0.125f : 0.25f;
+        a.out_scale = 1.0f / ((float)b * a.in_scale * a.in_scale);
+        hipLaunchKernelGGL(hessian_rotate_kernel, dim3((unsigned)((T + 7) / 8), (unsigned)((K + kRotCols - 1) / kRotCols)), dim3(256), 0, st, a);
+        // in parts of 64 x 64, or of 32 x 32 where they are so few that those have compute units to themselves.  8192 rows, the tiles
+        // left whole / in 64 / in 32, us: K = 4096 (16 left) 1150 / 962 / 862, 1024 (36) 515 / 207 / 160, 1408 (66) 522 / 289 / 239,
+        // 1664 (91) 525 / 295 / 300, 2048 (136) 519 / 360 / 401, 2944 (276) 714 / 622 / 764, 3328 (351) 725 / 737 / 961
+        const int parts = rem > slots * 5 / 8 ? 0 : rem > slots / 6 ? 32 : 16, small = parts ? rem : 0;
+        a.full = tiles - small;
+        if (a.full) hipLaunchKernelGGL(hessian_split_kernel<64>, dim3((unsigned)a.full), dim3(256), 0, st, a);
+        if (small && parts == 16) hipLaunchKernelGGL(hessian_split_kernel<16>, dim3((unsigned)(16 * small)), dim3(256), 0, st, a);
+        else if (small) hipLaunchKernelGGL(hessian_split_kernel<32>, dim3((unsigned)(4 * small)), dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
+    // So T is cut into parts for them, of at least 512 rows (less does not repay the second launch), as many as fit the round
+    // and the workspace that every caller has (not the one at hand: the last bits do not depend on its size).
     int parts = rem ? std::min({slots / rem, 8, (int)std::min<int64_t>(T / 512, 8)}) : 1;
-    if (rem) parts = std::min(parts, (int)std::min<int64_t>(8, (int64_t)(workspace_bytes / ((size_t)rem * kT * kT * 4))));
+    if (rem) parts = std::min(parts, (int)std::min<int64_t>(8, T * K / (int64_t)(rem * kT * kT)));
     a.full = tiles;
     a.parts = 1;
     a.chunk = 0;

@@ -96,9 +96,8 @@ size_t gptq_prepare_workspace_bytes(int64_t K);
 hipError_t launch_gptq_prepare(const float* H, int64_t K, float damp, bool use_order, int* perm, float* U, void* workspace,
                                hipStream_t st);
 
-// H (+)= (x H_b)^T (x H_b); workspace: room for the partial sums of the last round of tiles (used as far as it reaches)
-hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float* H, bool accumulate, void* workspace,
-                               size_t workspace_bytes, hipStream_t st);
+// H (+)= (x H_b)^T (x H_b); workspace of 4 T K bytes: the rotated rows, or without rotation the partial sums of the last tiles
+hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float* H, bool accumulate, void* workspace, hipStream_t st);
 
 // measurement aids (fp4_probe): which = 0 scaled-FP4 MFMA issue loop, 1 fp16 MFMA issue loop (buf: one 24-byte record per
 // compute unit), 2 streaming copy of the first half of buf to the second, 3 streaming read of the first half

@@ -309,6 +309,48 @@ def test_hessian_tiles_and_split_rows(fp4, oracle, T, K, b):
         assert np.array_equal(got, got.T)
 
 
+def common_mode_rows(kind, T, K, b, salt):
+    """Calibration rows whose channels have something in common inside a rotation block, as bf16 bits: the rotation moves it
+    into a few channels and the others keep what little is left."""
+    rng = np.random.default_rng(700 + salt)
+    if kind == "offset":          # one constant under unit noise
+        x = 100.0 + rng.standard_normal((T, K))
+    elif kind == "factor":        # one zero-mean value per row and block, 0.2 % of noise per channel
+        f = rng.standard_normal((T, K // b))
+        x = np.repeat(f, b, axis=1) * (1.0 + 0.002 * rng.standard_normal((T, K)))
+    elif kind == "walsh":         # the same, with the signs of a rotated channel
+        f = rng.standard_normal((T, K // b))
+        signs = np.where(np.array([bin(i & 5).count("1") & 1 for i in range(b)]), -1.0, 1.0)
+        x = np.repeat(f, b, axis=1) * np.tile(signs, K // b) * (1.0 + 0.01 * rng.standard_normal((T, K)))
+    else:                         # "constant": every row constant within a block but for its last element
+        x = np.repeat(rng.uniform(1.0, 2.0, (T, K // b)), b, axis=1)
+        x[:, b - 1::b] *= 1.0 + 2.0 ** -7
+    return inputs.f32_to_bf16_bits(x.astype(np.float32))
+
+
+@pytest.mark.parametrize("kind", ["offset", "factor", "walsh", "constant"])
+@pytest.mark.parametrize("T,K,b", [(1, 128, 128), (700, 256, 16), (1500, 320, 32), (1500, 320, 64), (4100, 384, 128),
+                                   (70, 1808, 16), (97, 3344, 16), (41, 4112, 16)])
+def test_hessian_of_rows_with_a_common_component_in_a_block(fp4, oracle, kind, T, K, b):
+    """Rotated channels of very different size beside each other: every entry is accurate on the scale of ITS two rotated
+    channels, not of the largest one in the block, and no diagonal entry is negative; fresh and accumulated.  The last three
+    sizes have tiles of 64 x 64, of 128 x 128, and of 128 x 128 with some of 32 x 32 left over.  Bound as above."""
+    import torch
+    xb = common_mode_rows(kind, T, K, b, salt=T + b)
+    X = oracle.rotate(xb, b).astype(np.float64)
+    want = X.T @ X
+    say(f"gptq hessian {kind} T={T} K={K} b={b}")
+    H = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(xb), b)
+    H2 = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(xb), b, H.clone())
+    torch.cuda.synchronize()
+    scale = np.sqrt(np.outer(np.diag(want), np.diag(want)))
+    for got, times in ((np_(H).astype(np.float64), 1), (np_(H2).astype(np.float64), 2)):
+        say(f"   largest error over sqrt(h_ii h_jj): {(np.abs(got - times * want) / np.where(scale > 0, scale, np.inf)).max():.2e}")
+        assert np.all(np.diag(got) >= 0.0)
+        assert np.all(np.abs(got - times * want) <= 2e-5 * times * max(1.0, (T / 700) ** 0.5) * scale)
+        assert np.array_equal(got, got.T)
+
+
 def test_calibration_rows_to_codes_entirely_on_the_gpu(fp4, oracle, gptq):
     import torch
     N, K, T, b = 64, 512, 1536, 32
