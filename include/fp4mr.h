@@ -260,6 +260,8 @@ fp4mr_status_t fp4_w4a16_linear(const void* x, int64_t M, int64_t K, int had_blo
  *                anything else: FP4MR_ERR_FMT
  * Per column j (visiting order), for every row:  q = E2M1(w_j / s),  e = (w_j - q s) / U[j,j],  w_k -= e U[j,k] (k > j),
  * in fp32; s is the fixed scale of the group the column belongs to in the ORIGINAL order.
+ * A non-finite rotated weight spoils what it scales (its group; NVFP4: the tensor scale) and the codes of the columns of its row
+ * that are visited after it, not of those visited before.
  */
 fp4mr_status_t fp4_gptq_quantize_weights(const void* w, int64_t N, int64_t K, int had_block, fp4mr_fmt_t fmt,
                                          const float* hinv_u, const int32_t* perm, void* codes_out, void* scales_out,

@@ -150,6 +150,9 @@ __device__ __forceinline__ float round_e2m1(float wj, float inv_scale, uint32_t&
 // what four columns of the sweep read from LDS: scale and reciprocal (0 for a zero scale), 1 / U[j,j], the lane's part of row j
 // of the triangle.  The triangle is zero on and below the diagonal: a column that has been visited keeps the weight that was rounded,
 // from which its lane makes code and error once more when the block is done -- two selects per column less in the chain.
+// (As long as errors are finite: an infinite or NaN one times zero takes the visited columns of its row with it.  A block that
+// comes out with a weight that is not finite is swept once more with KEEP, which puts every weight aside as it is rounded: to do so
+// always costs 4 us per 512 columns of [6144, 4096].)
 struct SweepOperands {
     v2f_t sc[4];
     float4 ru, u[4];
@@ -168,8 +171,8 @@ __device__ __forceinline__ SweepOperands sweep_operands(const float* Us, const f
 }
 
 // the four columns 4 P .. 4 P + 3 of the block, the next four's operands on their way meanwhile
-template <int P>
-__device__ __forceinline__ void sweep_part(float (&w)[4], uint32_t packed, const SweepOperands& x, const float* Us, const float* Ru, const v2f_t* Sc, int row, int part)
+template <int P, bool KEEP>
+__device__ __forceinline__ void sweep_part(float (&w)[4], float (&kept)[4], uint32_t packed, const SweepOperands& x, const float* Us, const float* Ru, const v2f_t* Sc, int row, int part)
 {
     SweepOperands next = x;
     if constexpr (P + 1 < 16) next = sweep_operands(Us, Ru, Sc, P + 1, row, part);
@@ -180,13 +183,14 @@ __device__ __forceinline__ void sweep_part(float (&w)[4], uint32_t packed, const
         constexpr int ctrl = 0x150 + P;     // row_newbcast: the sixteen lanes of a row read lane P
         const float wj = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(w[i]), ctrl, 0xf, 0xf, true));
         const float e = __fmaf_rn(-round_e2m1(wj, x.sc[i][1], packed), x.sc[i][0], wj) * ru[i];
+        if (KEEP && part == P) kept[i] = wj;
         w[0] = __fmaf_rn(-e, x.u[i].x, w[0]);
         w[1] = __fmaf_rn(-e, x.u[i].y, w[1]);
         w[2] = __fmaf_rn(-e, x.u[i].z, w[2]);
         w[3] = __fmaf_rn(-e, x.u[i].w, w[3]);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (P + 1 < 16) sweep_part<P + 1>(w, packed, next, Us, Ru, Sc, row, part);
+    if constexpr (P + 1 < 16) sweep_part<P + 1, KEEP>(w, kept, packed, next, Us, Ru, Sc, row, part);
 }
 
 // The errors also go to err[N, kOuter] for the update of everything behind the outer block.
@@ -231,11 +235,14 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
         const int row = wave * 4 + q, part = l16, n = n0 + row;
         for (int b = 0; b < blocks; ++b) {
             const float4 w4 = *reinterpret_cast<const float4*>(&W[row * kWStride + b * kB + part * 4]);
-            float w[4] = {w4.x, w4.y, w4.z, w4.w};
+            float w[4] = {w4.x, w4.y, w4.z, w4.w}, e[4];
             const float* const Ru = Rd + b * kB;
-            sweep_part<0>(w, 0u, sweep_operands(Us, Ru, Sc, 0, row, part), Us, Ru, Sc, row, part);
+            sweep_part<0, false>(w, w, 0u, sweep_operands(Us, Ru, Sc, 0, row, part), Us, Ru, Sc, row, part);
+            if (__builtin_expect(__any(!(fabsf(w[0]) + fabsf(w[1]) + fabsf(w[2]) + fabsf(w[3]) < INFINITY)), 0)) {
+                float again[4] = {w4.x, w4.y, w4.z, w4.w};
+                sweep_part<0, true>(again, w, 0u, sweep_operands(Us, Ru, Sc, 0, row, part), Us, Ru, Sc, row, part);
+            }
             // the lane's own four columns: w is what was rounded
-            float e[4];
             uint32_t codes = 0u;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {

@@ -400,6 +400,30 @@ def test_update_behind_an_outer_block_at_the_edges_of_its_tiles(fp4, oracle, gpt
     assert diff.mean() <= 1e-3
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("at", [40, 616, 1130])
+def test_sweep_keeps_the_codes_of_columns_visited_before_a_non_finite_weight(fp4, oracle, value, at):
+    """A non-finite weight spoils the columns of its row that are visited after it (their running values carry its error),
+    not those visited before it, in the same 64-column block either; other rows see nothing of it."""
+    import torch
+    N, K, row = 35, 1152, 17
+    rng = np.random.default_rng(at)
+    w = rng.standard_normal((N, K)).astype(np.float32)
+    U = np.triu(rng.standard_normal((K, K)) * 0.02, 1).astype(np.float32)
+    U[np.diag_indices(K)] = rng.uniform(0.5, 2.0, K).astype(np.float32)
+    say(f"gptq non-finite weight {value} at {at}")
+    codes = []
+    for v in (w[row, at], value):
+        w[row, at] = v
+        c, s, _ = fp4.fp4_gptq_quantize_weights(to_dev_bf16(inputs.f32_to_bf16_bits(w)), 1, MX, to_dev(U), None)
+        torch.cuda.synchronize()
+        codes.append(unpack(np_(c).reshape(N, -1)))
+    group = at // 32 * 32      # (the columns of its own group may have another scale)
+    assert np.array_equal(codes[0][row, :group], codes[1][row, :group])
+    others = np.arange(N) != row
+    assert np.array_equal(codes[0][others], codes[1][others])
+
+
 def test_sweep_at_layer_size_on_sampled_rows(fp4, oracle, gptq):
     """A whole [4096, 4096] layer through the library (the benchmark's shape: 64 blocks, 8 outer blocks), checked against the
     oracle on 32 sampled rows -- rows never interact, so the oracle sweeps just those rows with the same factor."""
