@@ -558,38 +558,44 @@ hipError_t launch_variant(const GemmArgs& g0, bool out_f32, hipStream_t st, int 
 }
 
 // What a launch of one of the tile shapes takes: rounds of workgroups over the chip times (a tile's fixed cost + K-steps times a
-// step, which grows with the share of the chip that is busy), in microseconds, fitted to launches of every shape on 154
-// products (M = 80 ... 4096, N = 2048 ... 57344, K = 1536 ... 28672; rms error 2 - 4 %).
+// step, which grows with the share of the chip that is busy), in microseconds; more where the output's rows are not whole
+// 64-byte pieces (their stores share lines with the next row: a quarter of the launch at M = 4085, N = 9224, K = 1024).  Fitted to
+// launches of every shape on 818 products (M = 65 ... 4096, N = 1024 ... 57344, K = 512 ... 28672, weights in the cache where
+// they fit), for the choice to lose least.  On 138 others the tile taken is 0.3 % slower than the best of all on average, 11 % at most.
 struct TileCost {
     int variant, bm, bn, per_cu;       // per_cu: workgroups a compute unit holds
-    double fixed, step, step_busy, once;
+    double fixed, step, step_busy, once, ragged;
+    double alone, alone_step, alone_busy;   // (two to a compute unit:) fixed cost and step of one that has it to itself
 };
 // The shapes differ in how they round off.  128 rows or columns less than a square tile's mean more tiles of less arithmetic per
 // byte; 192 and 160 rows fill in between (M = 1111: 192 x 128 tiles on 192 compute units where 256 x 128 had 160, N = 4096,
 // K = 14336: 45.5 -> 38.0 us, K = 4096: 17.0 -> 12.9; 192 x 256, N = 28672, K = 4096: 72 -> 68; M = 600, N = K = 8192, 160 x 128:
 // 28.9 -> 23.4; M = 300, N = 57344, K = 8192, 192 x 256: 102 -> 82).  256 x 128 has eight waves of 64 x 64: two to a SIMD, one's LDS
-// reads under the other's products, against four of 128 x 64 M = 1111, N = 4096, K = 14336: 45.5 -> 41.0 us.
+// reads under the other's products, against four of 128 x 64 M = 1111, N = 4096, K = 14336: 45.5 -> 41.0 us.  128 x 256 with two
+// workgroups per compute unit overlaps one's start-up and stores with the other's main loop: where a tile is not much longer
+// than those (M = 2166, N = 10968, K = 1024: 26.5 us, the best of the others 30.0; M = 1104, N = 26544, K = 1536: 38.4 against 42.5).
 constexpr TileCost kTileCosts[] = {
-    {2, 128, 128, 2, 2.3, 0.230, 0.233, 1.6},
-    {18, 128, 128, 1, 2.6, 0.163, 0.075, 1.3},   // one workgroup per compute unit, eight-stage ring: up to three quarters of them
-    {17, 128, 128, 1, 2.9, 0.179, 0.063, 1.4},   // (with more of them busy four waves measured level or faster)
-    {5, 256, 128, 1, 3.8, 0.265, 0.150, 0.5},
-    {6, 192, 128, 1, 3.0, 0.229, 0.114, 0.9},
-    {7, 160, 128, 1, 2.7, 0.236, 0.072, 1.6},
-    {8, 192, 256, 1, 5.0, 0.384, 0.202, 0.0},
-    {13, 256, 192, 1, 5.4, 0.373, 0.210, 0.0},
-    {10, 256, 256, 1, 5.7, 0.465, 0.293, 0.0},
-    {11, 256, 256, 1, 4.9, 0.450, 0.324, 0.0},   // persistent: the next tile's first stages and the stores overlap
+    {2, 128, 128, 2, 2.885, 0.281, 0.186, 1.120, 1.651, 2.652, 0.211, 0.211},
+    {18, 128, 128, 1, 2.701, 0.170, 0.044, 1.420, 1.750},   // one workgroup per compute unit, eight-stage ring: up to three quarters of them
+    {17, 128, 128, 1, 3.466, 0.193, 0.045, 1.608, 1.108},   // (with more of them busy four waves measured level or faster)
+    {5, 256, 128, 1, 3.778, 0.230, 0.182, 1.092, 3.494},
+    {6, 192, 128, 1, 2.593, 0.229, 0.111, 1.579, 2.698},
+    {7, 160, 128, 1, 2.929, 0.233, 0.070, 1.806, 0.788},
+    {8, 192, 256, 1, 4.722, 0.255, 0.340, 0.831, 4.297},
+    {13, 256, 192, 1, 6.085, 0.236, 0.348, 0.625, 3.638},
+    {10, 256, 256, 1, 6.520, 0.330, 0.420, 0.361, 4.510},
+    {11, 256, 256, 1, 5.436, 0.418, 0.297, 1.245, 5.429},   // persistent: the next tile's first stages and the stores overlap
+    {15, 128, 256, 2, 4.910, 0.491, 0.429, 0.114, 2.003, 4.595, 0.436, 0.247},
+    {16, 128, 256, 2, 4.598, 0.548, 0.372, 1.127, 1.970, 2.754, 0.362, 0.370},   // persistent
 };
 
-double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, int cus)
+double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int cus)
 {
     const int64_t slots = (int64_t)cus * c.per_cu, full = tiles / slots, rest = tiles % slots;
     double t = c.once + (double)full * (c.fixed + (double)kt * (c.step + c.step_busy));
-    const double busy = (double)rest / (double)slots;
-    // (a 128 x 128 workgroup that has its compute unit to itself)
-    if (rest > 0 && c.per_cu == 2 && rest <= cus) t += 1.8 + (double)kt * 0.211 * (1.0 + 0.387 * busy);
-    else if (rest > 0) t += c.fixed + (double)kt * (c.step + c.step_busy * busy);
+    if (ragged) t += c.ragged * (double)tiles / (double)slots;
+    if (rest > 0 && c.per_cu == 2 && rest <= cus) t += c.alone + (double)kt * c.alone_step * (1.0 + c.alone_busy * (double)rest / (double)cus);
+    else if (rest > 0) t += c.fixed + (double)kt * (c.step + c.step_busy * (double)rest / (double)slots);
     return t;
 }
 
@@ -616,18 +622,14 @@ void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int*
         const int64_t t = tiles(c);
         if (c.variant == 18 && 4 * t > 3 * (int64_t)cus) continue;
         if (c.variant == 17 && (4 * t <= 3 * (int64_t)cus || t > cus)) continue;
-        if ((c.variant == 11) != (t > cus) && (c.variant == 10 || c.variant == 11)) continue;
-        const double us = tile_cost(c, t, kt, cus);
+        if ((c.variant == 10 && t > cus) || (c.variant == 11 && t <= cus)) continue;
+        if ((c.variant == 15 && t > 2 * (int64_t)cus) || (c.variant == 16 && t <= 2 * (int64_t)cus)) continue;
+        const double us = tile_cost(c, t, kt, N % 32 != 0, cus);
         if (us < best) {
             best = us;
             *variant = c.variant;
         }
     }
-    // K around 1024: a tile is 8 K-steps, about as long as its own start-up and stores.  128x256 tiles with two
-    // workgroups per compute unit overlap one workgroup's epilogue with the other's main loop: 10-13 % faster than the square
-    // tiles there, level at K = 1536-2048, slower beyond (three stages, one and a half times the operand traffic) and
-    // below (K = 512: the persistent 256x256 workgroups win).
-    if ((*variant == 10 || *variant == 11) && K >= 768 && K <= 1280) *variant = ((M + 127) / 128) * ((N + 255) / 256) > 2 * (int64_t)cus ? 16 : 15;
     if (!may_split) return;
     best *= 0.97;
     for (const TileCost& c : kTileCosts) {
@@ -637,7 +639,7 @@ void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int*
             const int64_t st = ((kt + s - 1) / s + 7) / 8 * 8;
             const int64_t n = (kt + st - 1) / st;  // parts of st steps that cover K (the last may be shorter)
             if (n < 2) continue;
-            const double us = tile_cost(c, t * n, st, cus) + 5.5 + (double)n * (double)M * (double)N * 8.0 / 12.0e6;
+            const double us = tile_cost(c, t * n, st, N % 16 != 0, cus) + 5.5 + (double)n * (double)M * (double)N * 8.0 / 12.0e6;
             if (us < best) {
                 best = us;
                 *variant = c.variant;

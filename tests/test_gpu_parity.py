@@ -272,6 +272,15 @@ def test_gemm_mxfp4_scale_batches_of_uneven_tiles(fp4, oracle, variant, K, knobs
     test_gemm_mxfp4_scales_that_differ_per_row_block_and_k_block(fp4, oracle, variant, K, knobs)
 
 
+@pytest.mark.parametrize("variant", [15, 16])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (129, 264, 256), (193, 520, 384), (257, 257, 640)])
+def test_gemm_mxfp4_128x256_tiles_on_short_k(fp4, oracle, variant, M, N, K, knobs):
+    """The two-to-a-compute-unit tiles are taken for the shortest K as well: fewer K-steps than the ring has stages, a single scale
+    batch, ragged last tiles, an N that keeps the output out of the staged epilogue."""
+    knobs(variant=variant)
+    _gemm_case(fp4, oracle, MX, M, N, K, seed=160 + variant + M, out_f32=False, layout_gemm=True)
+
+
 @pytest.mark.parametrize("variant", [17, 18])
 @pytest.mark.parametrize("K", [128, 512, 896, 1024, 1152, 2048, 2176, 4224])
 def test_gemm_mxfp4_eight_stage_ring_with_two_scale_buffers(fp4, oracle, K, variant, knobs):
