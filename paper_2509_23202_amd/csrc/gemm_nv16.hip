@@ -431,12 +431,15 @@ hipError_t launch_tiles(const Nv16Args& g, bool out_f32, hipStream_t st, int spl
 // products; but each copies the same rows of X into LDS for itself.  Where a single round of the chip has more such
 // workgroups than compute units and no more than one of twice the width, eight waves share a 128 x 512 tile instead (34 KB
 // copied per K-step, not 50; there is no second round for an epilogue to run under): N = 8192, M = 2048: K = 28672 669 ->
-// 641 us, K = 8192 205 -> 201.  Over several rounds the pairs stay ahead (N = 57344, K = 8192: 1324 against 1342 us).
+// 641 us, K = 8192 205 -> 201.  Over several rounds the pairs stay ahead (N = 57344, K = 8192: 1324 against 1342 us), and below
+// K = 6656, where a tile is short for its start-up and epilogue, which the pair overlaps: on 23 shapes from there to K = 15000
+// 512 columns took 0.95 - 1.02 of the pairs' time (M = 419, N = 24064, K = 8576: 180 -> 171 us), on 47 below it 0.98 - 1.11
+// (M = 451, N = 25992, K = 1536: 54 against 60).
 // Three stages either way: a fourth for the 512 columns measured 1 % slower.
 hipError_t launch_wide(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1)
 {
     const int64_t rows = (int64_t)g.tiles_m * splits, cus = device_cus();
-    if (rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st, splits);
+    if (g.K >= 6656 && rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st, splits);
     return launch_tiles<4, 4, 3>(g, out_f32, st, splits);
 }
 

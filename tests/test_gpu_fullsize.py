@@ -240,8 +240,15 @@ def test_nvfp4_narrow_tiles_when_wide_ones_are_about_one_round(fp4, oracle, M, N
 
 @pytest.mark.parametrize("M,N,K", [(2048, 8192, 128), (2041, 7945, 256), (300, 28680, 384), (320, 8200, 8192)])
 def test_nvfp4_eight_wave_tiles_in_a_single_round(fp4, oracle, M, N, K):
-    """More 128 x 256 tiles than compute units in no more than one round: 128 x 512 tiles of eight waves, with two K-steps
-    (fewer than the ring has stages), a ragged last tile row and column, and (the last case) shared out along K.  Columns
-    either side of the multiples of 512 near the start, the middle and the end of N are sampled on purpose."""
+    """More 128 x 256 tiles than compute units in no more than one round: short K (pairs of 128 x 256 tiles), with two K-steps
+    (fewer than the ring has stages) and a ragged last tile row and column, and (the last case) 128 x 512 tiles of eight waves
+    shared out along K.  Columns either side of the multiples of 512 near the start, the middle and the end of N are sampled on
+    purpose."""
     seams = [c * 512 + d for c in (1, N // 1024, N // 512) for d in (-1, 0)] + [N - 1]
     check_layer(fp4, oracle, inputs.RECIPES[4], M, K, N, NV, 16, n_m=48, n_n=96, salt=M + N, extra_n=seams)
+
+
+@pytest.mark.parametrize("M,N,K", [(2048, 8192, 6656), (2041, 7945, 6784), (300, 28680, 6656)])
+def test_nvfp4_eight_wave_tiles_unsplit(fp4, oracle, M, N, K):
+    """The same grids from the K on at which 128 x 512 tiles are taken, each workgroup over the whole of K."""
+    test_nvfp4_eight_wave_tiles_in_a_single_round(fp4, oracle, M, N, K)
