@@ -86,8 +86,7 @@ def _check(status: int) -> None:
 
 
 # The current stream's handle without a Stream object around it: 0.2 us of host time per call, not 2.8, where a whole
-# one-launch linear of a small layer takes 3 us on the GPU.  (Outputs come from Tensor.new_empty for the same reason: it has no
-# device argument to parse, 1.3 against 1.8 us.)
+# one-launch linear of a small layer takes 3 us on the GPU.
 try:
     _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 except AttributeError:   # a build of torch without these two
@@ -96,6 +95,15 @@ except AttributeError:   # a build of torch without these two
 
 def _stream() -> int:
     return _raw_stream(_current_device())
+
+
+# Outputs come from Tensor.new_empty, which has no device argument to parse (1.3 us against torch.empty's 1.8) -- but not for a
+# subclass of Tensor (a Parameter, ...), which it would hand back to the subclass: every call returns plain tensors.
+_Tensor = torch.Tensor
+
+
+def _plain_empty(like):
+    return functools.partial(torch.empty, device=like.device)
 
 
 def _ptr(t):
@@ -120,10 +128,11 @@ def _quantize(fn, op, x, had_block, fmt, flags, tensor_scale, codes, scales, wor
         flags |= INPUT_F32
     elif x.dtype != torch.bfloat16:
         raise TypeError("x must be bfloat16 (or float32 with had_block=1)")
+    empty = x.new_empty if type(x) is _Tensor else _plain_empty(x)
     if codes is None or scales is None:
         cb, sb = packed_bytes(rows, K, fmt, flags & LAYOUT_GEMM)
-        codes = x.new_empty(cb, dtype=torch.uint8)
-        scales = x.new_empty(sb, dtype=torch.uint8)
+        codes = empty(cb, dtype=torch.uint8)
+        scales = empty(sb, dtype=torch.uint8)
     ts = None
     if flags & SCALE_FIT_RANGE:
         # [alpha, beta, 256 scale values]; a caller-supplied tensor (its first two floats set) means: use that alpha, beta
@@ -138,10 +147,10 @@ def _quantize(fn, op, x, had_block, fmt, flags, tensor_scale, codes, scales, wor
             flags |= STATIC_TENSOR_SCALE
             ts = tensor_scale
         else:
-            ts = x.new_empty(1, dtype=torch.float32)
+            ts = empty(1, dtype=torch.float32)
     need = workspace_bytes(op, rows, 0, K, fmt, flags)
     if need and workspace is None:
-        workspace = x.new_empty(need, dtype=torch.uint8)
+        workspace = empty(need, dtype=torch.uint8)
     wsz = 0 if workspace is None else workspace.numel()
     if rot is None:
         _check(fn(x.data_ptr(), rows, K, had_block, fmt, codes.data_ptr(), scales.data_ptr(), _ptr(ts), _ptr(workspace), wsz,
@@ -241,11 +250,12 @@ def fp4_gptq_quantize_weights(w, had_block: int, fmt: int, hinv_u, perm=None, *,
 def fp4_gemm(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M: int, N: int, K: int, fmt: int, *,
              flags: int = 0, out=None, workspace=None):
     """out[M,N] = Ahat @ What^T (bf16, or fp32 with OUT_F32).  Operand layouts per A_LAYOUT_GEMM / W_LAYOUT_GEMM."""
+    empty = a_codes.new_empty if type(a_codes) is _Tensor else _plain_empty(a_codes)
     if out is None:
-        out = a_codes.new_empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
+        out = empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
     need = workspace_bytes(OP_GEMM_SPLIT_K, M, N, K, fmt, flags)   # (what the call needs plus optional split-K room)
     if need and workspace is None:
-        workspace = a_codes.new_empty(need, dtype=torch.uint8)
+        workspace = empty(need, dtype=torch.uint8)
     wsz = 0 if workspace is None else workspace.numel()
     _check(lib.fp4_gemm(a_codes.data_ptr(), a_scales.data_ptr(), _ptr(a_tensor_scale), w_codes.data_ptr(), w_scales.data_ptr(),
                         _ptr(w_tensor_scale), M, N, K, fmt, out.data_ptr(), _ptr(workspace), wsz, flags, _stream()))
@@ -257,7 +267,8 @@ def fp4_fused_linear(x, had_block: int, w_codes, w_scales, N: int, fmt: int = MX
     assert x.is_cuda and x.dim() == 2 and x.is_contiguous() and x.dtype == torch.bfloat16
     M, K = x.shape
     if out is None:
-        out = x.new_empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
+        empty = x.new_empty if type(x) is _Tensor else _plain_empty(x)
+        out = empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
     _check(lib.fp4_fused_linear(x.data_ptr(), M, K, had_block, w_codes.data_ptr(), w_scales.data_ptr(), N, fmt, out.data_ptr(),
                                 flags | W_LAYOUT_GEMM, _stream()))
     return out
@@ -268,7 +279,8 @@ def fp4_w4a16_linear(x, had_block: int, w_codes, w_scales, N: int, fmt: int = MX
     assert x.is_cuda and x.dim() == 2 and x.is_contiguous() and x.dtype == torch.bfloat16
     M, K = x.shape
     if out is None:
-        out = x.new_empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
+        empty = x.new_empty if type(x) is _Tensor else _plain_empty(x)
+        out = empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
     _check(lib.fp4_w4a16_linear(x.data_ptr(), M, K, had_block, w_codes.data_ptr(), w_scales.data_ptr(), N, fmt, out.data_ptr(),
                                 flags | W_LAYOUT_GEMM, _stream()))
     return out

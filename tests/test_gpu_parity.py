@@ -677,3 +677,25 @@ def test_nvfp4_tensor_scale_on_either_side_of_the_folded_reduction(fp4, rows, la
     _, _, ts = fp4.fp4_rotate_quantize(x, 16, NV, flags=fp4.LAYOUT_GEMM if layout_gemm else 0)
     torch.cuda.synchronize()
     assert float(np_(ts)[0]) == float(np.float32(0.25) / np.float32(2688.0))
+
+
+def test_outputs_for_tensor_subclasses_are_plain_tensors(fp4):
+    """What is handed in as a Parameter, or as another subclass of Tensor, gives plain tensors of the same values."""
+    import torch
+
+    class Tagged(torch.Tensor):
+        pass
+
+    x, w = torch.randn(4, 128, device="cuda").bfloat16(), torch.randn(32, 128, device="cuda").bfloat16()
+    for wrap in (lambda t: t.as_subclass(Tagged), lambda t: torch.nn.Parameter(t, requires_grad=False)):
+        results = []
+        for f in (lambda t: t, wrap):
+            q = fp4.fp4_quantize_weights(f(w), 32, MX, flags=fp4.LAYOUT_GEMM)
+            a = fp4.fp4_rotate_quantize(f(x), 32, MX, flags=fp4.LAYOUT_GEMM)
+            nv = fp4.fp4_rotate_quantize(f(x), 16, NV)
+            y = fp4.fp4_gemm(f(a[0]), f(a[1]), None, f(q[0]), f(q[1]), None, 4, 32, 128, MX, flags=fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM)
+            assert all(type(t) is torch.Tensor for t in q[:2] + a[:2])
+            results.append([*nv, y, fp4.fp4_fused_linear(f(x), 32, q[0], q[1], 32), fp4.fp4_w4a16_linear(f(x), 32, q[0], q[1], 32)])
+        torch.cuda.synchronize()
+        for plain, wrapped in zip(*results):
+            assert type(wrapped) is torch.Tensor and torch.equal(plain, wrapped)
