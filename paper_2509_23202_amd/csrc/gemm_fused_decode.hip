@@ -1,4 +1,4 @@
-// One launch for a handful of tokens (M <= 16), MXFP4:  out = Q(X H_b) Q(W H_b)^T  with the activations rotated and
+// One launch for a handful of tokens (M <= 4; the weight-only form below M <= 16), MXFP4:  out = Q(X H_b) Q(W H_b)^T  with the activations rotated and
 // quantized inside the GEMM (arXiv 2509.23202, Section 4.2 items 1 and 2 in one kernel; the appendix on inference regimes
 // notes that at small batch the separate kernels give little: here the activation side costs no launch of its own).
 //
@@ -34,11 +34,12 @@ struct FusedArgs {
     float alpha;             // factor on the result (4/3 when the weights' scales carry the tensor-level 4/3), else 1
 };
 
-// MP = token rows kept in the staging area (4 or 16): rows of the activation fragments beyond MP are zero by construction
-// and never touch LDS, which keeps the workgroup small enough for four of them per compute unit when M <= 4.
-template <bool OUT_F32, int MP>
+// MP = token rows kept in the staging area: rows of the activation fragments beyond them are zero by construction and never
+// touch LDS, which keeps the workgroup small enough for four of them per compute unit.
+template <bool OUT_F32>
 __global__ __launch_bounds__(kFusedWaves * 64) void gemm_fused_decode_kernel(FusedArgs a)
 {
+    constexpr int MP = 4;   // (the entry point takes M <= 4)
     constexpr int U = 4;    // fragments per chunk = 16 vectors of 32
     constexpr int TOK = 4;  // tokens whose loads are in flight together
     using GQ = GroupQuant<32, 8, 16, true>;
@@ -514,8 +515,8 @@ hipError_t launch_fused_decode(const void* x, int64_t M, int64_t K, int b, const
             else hipLaunchKernelGGL((gemm_w4a16_decode_kernel<false, 16>), grid, block, 0, st, a);
         }
     } else {
-        if (out_f32) hipLaunchKernelGGL((gemm_fused_decode_kernel<true, 4>), grid, block, 0, st, a);   // (the entry point takes M <= 4)
-        else hipLaunchKernelGGL((gemm_fused_decode_kernel<false, 4>), grid, block, 0, st, a);
+        if (out_f32) hipLaunchKernelGGL(gemm_fused_decode_kernel<true>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(gemm_fused_decode_kernel<false>, grid, block, 0, st, a);
     }
     return hipGetLastError();
 }
