@@ -233,7 +233,8 @@ fp4mr_status_t fp4_fused_linear(const void* x, int64_t M, int64_t K, int had_blo
  * (round-to-nearest-even) instead of quantized; the weights' E2M1 codes are decoded with their E8M0 scales and the
  * product accumulates in fp32 (appendix on inference regimes: where the layer is memory-bound, weight-only
  * quantization loses no speed and keeps the activations' accuracy).  Arguments as fp4_fused_linear, except
- * 1 <= M <= 16 (the library has no other weight-only path; above four tokens it falls behind a bf16 GEMM on wide layers).
+ * 1 <= M <= 16 (the library has no other weight-only path; beyond M K = 73728 the activations are rotated again for every 16
+ * rows of W, and at M = 16 it is no faster than a bf16 GEMM there).
  */
 fp4mr_status_t fp4_w4a16_linear(const void* x, int64_t M, int64_t K, int had_block, const void* w_codes, const void* w_scales,
                                 int64_t N, fp4mr_fmt_t fmt, void* out, uint32_t flags, void* stream);

@@ -60,8 +60,9 @@ __global__ void gptq_iperm_kernel(GptqArgs a)
 }
 
 // wp[n, j] = (W H_b)[n, perm[j]]: the rotated weight of the column visited j-th.  One workgroup per row.  A thread rotates sixteen
-// neighbouring columns in registers -- butterflies, the levels above sixteen across lanes (sums of up to 128 bf16 values in fp32:
-// exact unless their exponents spread over more than 16 bits), then one multiplication by 1/sqrt(b) carried in two floats -- and the
+// neighbouring columns in registers -- butterflies, the levels above sixteen across lanes (fp32 sums of b bf16 values, exact while
+// the values' exponents spread over no more than 16 - log2(b) bits: 9 at b = 128, 12 at 16; beyond, every level rounds, log2(b)
+// roundings where a sequential sum has b), then one multiplication by 1/sqrt(b) carried in two floats -- and the
 // row is read back from LDS in visiting order for whole-line stores.  With a sum over the block per column, from LDS, [6144, 4096]
 // took 91 us at b = 16 and 486 at b = 128; now 39 at either.
 __global__ __launch_bounds__(256) void gptq_rotate_gather_kernel(GptqArgs a)
@@ -515,8 +516,8 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     };
     for (int o = 0; o < (int)K; o += kOuter) {
         const int oe = std::min(o + kOuter, (int)K);
-        // the outer block itself: every wave sweeps its 16 rows through the block's columns, pushing each 64-column
-        // block's errors onto the rest of the outer block as it goes ...
+        // the outer block itself: every workgroup takes 16 rows through the block's columns, four waves sweeping 64 of them at a
+        // time, four pushing their errors onto the rest of the outer block ...
         if (fmt == 0) hipLaunchKernelGGL(gptq_outer_kernel<0>, dim3(row16), dim3(512), 0, st, a, o, oe);
         else hipLaunchKernelGGL(gptq_outer_kernel<1>, dim3(row16), dim3(512), 0, st, a, o, oe);
         // ... everything behind the outer block sees all of its errors in one pass

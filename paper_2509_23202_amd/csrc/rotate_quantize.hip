@@ -36,8 +36,9 @@ constexpr int kThreads = 256;
 constexpr int kWavesPerBlock = kThreads / kWave;
 constexpr int kAmaxPassBlocks = 1024;  // grid cap of the NVFP4 abs-max pass and of the tensor-scale fit pass (4096 partials)
 // Abs-max partials that every wave of the quantize pass reduces for itself, one launch less.  K = 8192, separate launch -> folded, us:
-// M = 100 (400 partials) 8.2 -> 6.9, M = 200 8.4 -> 7.4, M = 320 (1280) 9.4 -> 8.6; at 4000 partials the sixty loads per lane cost
-// more than the launch (M = 1000 12.4 -> 12.9, M = 2048 17 -> 21).
+// M = 100 (400 partials) 8.2 -> 6.9, M = 200 8.4 -> 7.4, M = 320 (1280) 9.4 -> 8.6, M = 375 (1500) 9.7 -> 9.1 (K = 1024 ... 28672 at
+// 1500: 0.4 - 0.9 us); at 4000 partials the sixty loads per lane cost more than the launch (M = 1000 12.4 -> 12.9, M = 2048
+// 17 -> 21).  Nothing between was timed.
 constexpr int kFoldedPartials = 1536;
 constexpr int kFitRounds = 3;          // alternations of the tensor-scale fit
 constexpr int kRangePassBlocks = 512;  // grid cap of the range pre-pass (two partials per wave: the same 4096 slots)
