@@ -215,7 +215,9 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 // an operand whose only non-zero contraction index is j / 4, and one MFMA forms the outer product L_j L_j^T that the rest
 // of the block loses -- another one L_j V_j for the inverse in the making, whose row j the same lanes hold.  No value
 // travels between lanes but the pivot.
-__device__ __forceinline__ void factor_block(DiagLds& t, int p, v4f x)
+// SUBNORMAL: for pivots that are subnormal, which v_rsq_f32 takes for zero: they are moved up by 2^48 on the way.
+template <bool SUBNORMAL>
+__device__ __forceinline__ v4f factor_columns(v4f x)
 {
     const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
     v4f w;
@@ -227,7 +229,7 @@ __device__ __forceinline__ void factor_block(DiagLds& t, int p, v4f x)
         constexpr int R = SB;
         const int first = R * (j / 4);  // lane of row 0 of column j
         const float d = lane_value(x[j % 4], first + j);
-        float y = __builtin_amdgcn_rsqf(d);
+        float y = SUBNORMAL && d < 0x1p-126f ? __builtin_amdgcn_rsqf(d * 0x1p48f) * 0x1p24f : __builtin_amdgcn_rsqf(d);
         y = fmaf(0.5f * y, fmaf(-d * y, y, 1.0f), y);  // (one Newton step: 1 / sqrt(d) to an ulp)
         const float r = w[j % 4] * y;
         if (j + 1 < SB) {
@@ -243,6 +245,16 @@ __device__ __forceinline__ void factor_block(DiagLds& t, int p, v4f x)
             w[j % 4] = (lane >> 4) == j / 4 ? r : w[j % 4];
         }
     }
+    return w;
+}
+
+__device__ __forceinline__ void factor_block(DiagLds& t, int p, v4f x)
+{
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    v4f w = factor_columns<false>(x);
+    // (a subnormal pivot, or one that is not positive, leaves infinities or NaNs; two selects per column in the chain instead cost
+    // 45 us at K = 4096)
+    if (__builtin_expect(__any(!(fabsf(w[0]) + fabsf(w[1]) + fabsf(w[2]) + fabsf(w[3]) < INFINITY)), 0)) w = factor_columns<true>(x);
     float* s = t.S + strip_base(p) + 4 * q * strip_pitch(p) + SB * p + l16;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {

@@ -227,6 +227,28 @@ def test_prepare_at_the_edges_of_its_blocks(fp4, gptq, K):
     assert np.abs(U.T @ U @ A - np.eye(K)).max() <= 2e-3
 
 
+@pytest.mark.parametrize("log2_scale", [-124, -60, 110])
+def test_prepare_of_very_small_and_large_hessians(fp4, gptq, log2_scale):
+    """The factor scales with the Hessian, also where pivots are subnormal in binary32 (mean of the diagonal 2^-124; they still
+    hold 17 bits).  Bound as above."""
+    import torch
+    K = 300
+    rng = np.random.default_rng(900)
+    X = rng.standard_normal((2 * K, K)) * rng.uniform(0.1, 2.0, K)
+    H = X.T @ X
+    H32 = (H / np.mean(np.diag(H)) * 2.0 ** log2_scale).astype(np.float32)
+    H32 = np.tril(H32) + np.tril(H32, -1).T
+    say(f"gptq prepare at 2^{log2_scale}")
+    perm, U = fp4.fp4_gptq_prepare(to_dev(H32), 1e-2, True)
+    torch.cuda.synchronize()
+    perm, U = np_(perm), np_(U).astype(np.float64)
+    H64 = H32.astype(np.float64)
+    want_perm = gptq.act_order(H64)
+    assert np.array_equal(perm, want_perm)
+    want_U = gptq.inverse_factor(H64, want_perm, damp=1e-2)
+    assert np.linalg.norm(U - want_U) / np.linalg.norm(want_U) <= 5e-4
+
+
 def test_prepare_orders_equal_diagonal_entries_by_index(fp4, gptq):
     import torch
     K = 128
