@@ -560,8 +560,11 @@ hipError_t launch_variant(const GemmArgs& g0, bool out_f32, hipStream_t st, int 
 // What a launch of one of the tile shapes takes: rounds of workgroups over the chip times (a tile's fixed cost + K-steps times a
 // step, which grows with the share of the chip that is busy), in microseconds; more where the output's rows are not whole
 // 64-byte pieces (their stores share lines with the next row: a quarter of the launch at M = 4085, N = 9224, K = 1024).  Fitted to
-// launches of every shape on 818 products (M = 65 ... 4096, N = 1024 ... 57344, K = 512 ... 28672, weights in the cache where
-// they fit), for the choice to lose least.  On 138 others the tile taken is 0.3 % slower than the best of all on average, 11 % at most.
+// launches of every shape on 806 products with cold weights (as many copies in turn as fill 400 MB: what a model's layers see)
+// and, at a fifth of the weight, 873 with the same weights again and again (M = 65 ... 4096, N = 1024 ... 57344, K = 512 ... 28672), for
+// the choice to lose least.  On products left out of the fit the tile taken is slower than the best of all by 0.3 % on average (97
+// cold ones; 7 % at most) and 0.8 % (139 warm ones; 9 %).  (A fit to warm weights alone took 128 x 128 and 160 x 128 tiles with four stages where the
+// eight-stage ring keeps twice the bytes in flight: N = K = 8192, M = 394, cold: 22.3 -> 26.4 us.)
 struct TileCost {
     int variant, bm, bn, per_cu;       // per_cu: workgroups a compute unit holds
     double fixed, step, step_busy, once, ragged;
@@ -575,18 +578,26 @@ struct TileCost {
 // workgroups per compute unit overlaps one's start-up and stores with the other's main loop: where a tile is not much longer
 // than those (M = 2166, N = 10968, K = 1024: 26.5 us, the best of the others 30.0; M = 1104, N = 26544, K = 1536: 38.4 against 42.5).
 constexpr TileCost kTileCosts[] = {
-    {2, 128, 128, 2, 2.885, 0.281, 0.186, 1.120, 1.651, 2.652, 0.211, 0.211},
-    {18, 128, 128, 1, 2.701, 0.170, 0.044, 1.420, 1.750},   // one workgroup per compute unit, eight-stage ring: up to three quarters of them
-    {17, 128, 128, 1, 3.466, 0.193, 0.045, 1.608, 1.108},   // (with more of them busy four waves measured level or faster)
-    {5, 256, 128, 1, 3.778, 0.230, 0.182, 1.092, 3.494},
-    {6, 192, 128, 1, 2.593, 0.229, 0.111, 1.579, 2.698},
-    {7, 160, 128, 1, 2.929, 0.233, 0.070, 1.806, 0.788},
-    {8, 192, 256, 1, 4.722, 0.255, 0.340, 0.831, 4.297},
-    {13, 256, 192, 1, 6.085, 0.236, 0.348, 0.625, 3.638},
-    {10, 256, 256, 1, 6.520, 0.330, 0.420, 0.361, 4.510},
-    {11, 256, 256, 1, 5.436, 0.418, 0.297, 1.245, 5.429},   // persistent: the next tile's first stages and the stores overlap
-    {15, 128, 256, 2, 4.910, 0.491, 0.429, 0.114, 2.003, 4.595, 0.436, 0.247},
-    {16, 128, 256, 2, 4.598, 0.548, 0.372, 1.127, 1.970, 2.754, 0.362, 0.370},   // persistent
+    {2, 128, 128, 2, 3.539, 0.307, 0.207, 0.890, 1.100, 2.998, 0.227, 0.525},
+    {18, 128, 128, 1, 2.486, 0.188, 0.096, 1.359, 1.560},   // one workgroup per compute unit, eight-stage ring
+    {17, 128, 128, 1, 2.917, 0.222, 0.064, 1.478, 1.117},
+    {5, 256, 128, 1, 3.755, 0.305, 0.153, 0.861, 2.861},
+    {6, 192, 128, 1, 2.521, 0.308, 0.102, 1.515, 2.449},
+    {7, 160, 128, 1, 2.538, 0.301, 0.058, 1.800, 0.928},
+    {8, 192, 256, 1, 5.040, 0.314, 0.326, 0.790, 4.259},
+    {13, 256, 192, 1, 6.292, 0.286, 0.350, 0.529, 4.097},
+    {10, 256, 256, 1, 6.891, 0.365, 0.430, 0.314, 4.451},
+    {11, 256, 256, 1, 6.536, 0.454, 0.293, 1.470, 4.683},   // persistent: the next tile's first stages and the stores overlap
+    {15, 128, 256, 2, 5.720, 0.475, 0.516, 0.119, 1.977, 5.139, 0.452, 0.275},
+    {16, 128, 256, 2, 5.883, 0.607, 0.367, 1.472, 1.613, 2.756, 0.456, 0.314},   // persistent
+};
+
+// The shapes that run as split-K parts, priced from such runs (shorter K per workgroup, fp32 partials).  Of 1154 products 61 took a split
+// that measured 1.4 times as fast as the unsplit run on average; they take the same one here, and three others split, level with the unsplit run.
+constexpr TileCost kSplitCosts[] = {
+    {2, 128, 128, 2, 2.530, 0.253, 0.256, 1.760, 0.0, 1.980, 0.232, 0.194},
+    {5, 256, 128, 1, 4.180, 0.292, 0.165, 0.550, 0.0},
+    {10, 256, 256, 1, 6.270, 0.512, 0.322, 0.0, 0.0},
 };
 
 double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int cus)
@@ -605,7 +616,7 @@ double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int 
 // bound by the latency of their few loads in flight (M = 128, N = 4096, K = 14336: 32 tiles, 42 us, 0.7 TB/s).  Every tile's
 // K range can then be cut into up to eight parts of at least 16 K-steps (whole scale batches of eight), each part one
 // workgroup of as many tiles (17 us on that shape).  The reduction of the partials costs another launch and their way to
-// memory and back, 5.5 us + bytes at 12 TB/s (they are read back from the last-level cache), and a split has to win 3 %.
+// memory and back, 6 us + bytes at 10.9 TB/s (they are read back from the last-level cache), and a split has to win 4 %.
 void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int* splits, int* steps)
 {
     *splits = 1;
@@ -620,10 +631,11 @@ void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int*
     double best = 1e30;
     for (const TileCost& c : kTileCosts) {
         const int64_t t = tiles(c);
-        if (c.variant == 18 && 4 * t > 3 * (int64_t)cus) continue;
-        if (c.variant == 17 && (4 * t <= 3 * (int64_t)cus || t > cus)) continue;
-        if ((c.variant == 10 && t > cus) || (c.variant == 11 && t <= cus)) continue;
-        if ((c.variant == 15 && t > 2 * (int64_t)cus) || (c.variant == 16 && t <= 2 * (int64_t)cus)) continue;
+        if ((c.variant == 17 || c.variant == 18) && t > cus) continue;
+        // (persistent workgroups: only where there is a next tile, and not for a ragged few rounds, where one workgroup per tile, which
+        // the hardware hands to whichever unit is free, measured up to 5 % faster: N = 28672, K = 4096, M = 994: 63.4 against 66.8 us)
+        if (c.variant == 11 && (t <= cus || (t % cus != 0 && t < 3 * (int64_t)cus))) continue;
+        if (c.variant == 16 && t <= 2 * (int64_t)cus) continue;
         const double us = tile_cost(c, t, kt, N % 32 != 0, cus);
         if (us < best) {
             best = us;
@@ -631,15 +643,14 @@ void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int*
         }
     }
     if (!may_split) return;
-    best *= 0.97;
-    for (const TileCost& c : kTileCosts) {
-        if (c.variant != 2 && c.variant != 5 && c.variant != 10) continue;
+    best *= 0.96;
+    for (const TileCost& c : kSplitCosts) {
         const int64_t t = tiles(c), s_max = std::min<int64_t>(std::min<int64_t>((int64_t)cus * c.per_cu / t, kt / 16), 8);
         for (int64_t s = 2; s <= s_max; ++s) {
             const int64_t st = ((kt + s - 1) / s + 7) / 8 * 8;
             const int64_t n = (kt + st - 1) / st;  // parts of st steps that cover K (the last may be shorter)
             if (n < 2) continue;
-            const double us = tile_cost(c, t * n, st, N % 16 != 0, cus) + 5.5 + (double)n * (double)M * (double)N * 8.0 / 12.0e6;
+            const double us = tile_cost(c, t * n, st, false, cus) + 6.05 + (double)n * (double)M * (double)N * 8.0 / 10.9e6;
             if (us < best) {
                 best = us;
                 *variant = c.variant;
