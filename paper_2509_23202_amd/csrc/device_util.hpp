@@ -149,6 +149,31 @@ __device__ __forceinline__ Split3 split3(const float (&x)[8])
     return s;
 }
 
+// ---------------------------------------------------------------- waits
+typedef __attribute__((address_space(3))) void lds_void;
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);  // expcnt / lgkmcnt: no wait
+}
+
+// Barrier without the memory fence of __syncthreads(): a fence would make the compiler drain every outstanding
+// load (vmcnt(0)) and with it the whole prefetch ring.  The data hazards are handled explicitly instead: the
+// wait_vmcnt above it covers this wave's direct-to-LDS copies, the barrier publishes them to the other waves.
+__device__ __forceinline__ void block_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+__device__ __forceinline__ void wait_lgkmcnt0()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0); vmcnt / expcnt: no wait
+}
+
 // ---------------------------------------------------------------- misc
 __device__ __forceinline__ float fabs_max(float a, float b) { return fmaxf(a, fabsf(b)); }
 

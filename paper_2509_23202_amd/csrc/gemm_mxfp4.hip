@@ -40,29 +40,6 @@ struct GemmArgs {
     int split_steps;  // split-K launches: K-steps per split (a multiple of 8); blockIdx.y is the split, out the fp32 partials
 };
 
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);  // expcnt / lgkmcnt: no wait
-}
-
-// Barrier without the memory fence of __syncthreads(): a fence would make the compiler drain every outstanding
-// load (vmcnt(0)) and with it the whole prefetch ring.  The data hazards are handled explicitly instead: the
-// wait_vmcnt above it covers this wave's direct-to-LDS copies, the barrier publishes them to the other waves.
-__device__ __forceinline__ void block_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-__device__ __forceinline__ void wait_lgkmcnt0()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0); vmcnt / expcnt: no wait
-}
-
-typedef __attribute__((address_space(3))) void lds_void;
 typedef const __attribute__((address_space(1))) void global_void;
 
 template <int OPSEL>

@@ -48,22 +48,6 @@ struct Nv16Args {
     int split_steps;  // split-K launches: K-steps of 64 per split (a multiple of 8); blockIdx.y is the split, out the fp32 partials
 };
 
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-}
-
-__device__ __forceinline__ void block_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-typedef __attribute__((address_space(3))) void lds_void;
-
 // ---------------------------------------------------------------------------------------------------------------
 // Pre-pass: NVFP4 activations (GEMM layout) -> exact fp16 values code * s_G in the operand order above.  One wave per
 // fragment (16 rows x 128 K): 1 KB of codes and 128 scale bytes in, two K-steps of 2 KB out.

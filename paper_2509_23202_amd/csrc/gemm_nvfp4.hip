@@ -39,21 +39,6 @@ struct NvGemmArgs {
     int tn0, tn_count;  // this launch covers the tile columns tn0 .. tn0 + tn_count - 1 (tn_count = 0: all of them)
 };
 
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-}
-
-__device__ __forceinline__ void block_barrier()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-typedef __attribute__((address_space(3))) void lds_void;
 typedef const __attribute__((address_space(1))) void global_void;
 
 template <int BM, int BN, int WM, int WN, int STAGES, bool OUT_F32>

@@ -1,17 +1,20 @@
 // Hessian of a layer from calibration rows (arXiv 2509.23202, Section 4 "Standard GPTQ": the second-order information of
 // ||X What - X W||^2 is X^T X; Section 4.1 "Ingredient 3": of the ROTATED inputs X H_b).
 //
-// The rows are rotated FIRST and every rotated value is kept to 24 bits, so that an entry's error is relative to
-// sqrt(h_ii h_jj) of its own two channels.  (Rotating the finished X^T X is three times as fast, but where channels of a
-// block have something in common most rotated channels are small differences of large sums: with an offset of 100 under
-// unit noise the entries were off by 1 % of that scale, and diagonal entries could come out negative.)  Two launches:
-//   hessian_rotate_kernel   X -> the rotated rows in fp32, in the workspace, eight rows of a column side by side
-//   hessian_split_kernel    X'^T X' on the bf16 MFMA, both factors split into three bf16 parts: the six products above
-//                           2^-24 of the whole
-// 8192 rows at K = 4096: 0.87 ms (4.15 on the fp32 MFMA over both triangles; 0.27 for rotating X^T X).  Largest error over
-// sqrt(h_ii h_jj), T = 8192, b = 128, fp32 MFMA -> now: normal rows with loud channels 5.4e-6 -> 1.1e-6, offset 30
-// 3.5e-5 -> 7e-7, offset 100 3.3e-6 -> 5e-7, one factor per block and 0.2 % of noise 4.8e-6 -> 7e-7; a single row
-// 6e-8 -> 1e-7 (mean 2.5e-8 -> 2.6e-8).
+// The rows are rotated FIRST and every rotated value is kept to 23 or 24 bits, so that an entry's error is relative to
+// sqrt(h_ii h_jj) of its own two channels.  (Rotating the finished X^T X is faster, but where channels of a block have
+// something in common most rotated channels are small differences of large sums: with an offset of 100 under unit noise
+// the entries were off by 1 % of that scale, and diagonal entries could come out negative.)
+//   many rows  hessian_pack_kernel   X -> the rotated rows as two fp16 parts, scaled by block, in the workspace as the MFMA takes them
+//              hessian_tile_kernel   X'^T X' on the fp16 MFMA: the three products above 2^-23 of the whole
+//              hessian_part_kernel   the same for the tiles beyond whole rounds of the chip
+//   few rows   hessian_rotate_kernel X -> the rotated rows in fp32, in the workspace, eight rows of a column side by side
+//              hessian_split_kernel  X'^T X' on the bf16 MFMA, both factors split into three bf16 parts: the six products above
+//                                    2^-24 of the whole
+// 8192 rows at K = 4096: 0.44 ms (0.86 with six bf16 products, 4.15 on the fp32 MFMA over both triangles).  Largest error over
+// sqrt(h_ii h_jj), T = 8192, b = 128, fp32 MFMA -> bf16 -> fp16: normal rows with loud channels 5.4e-6 -> 1.1e-6 -> 2.1e-7, offset 30
+// 3.5e-5 -> 7e-7 -> 1.2e-7, offset 100 3.3e-6 -> 5e-7 -> 1.4e-7, one factor per block and 0.2 % of noise 4.8e-6 -> 7e-7 -> 1.4e-7 (the last
+// step for adding up four sums of 32 rows before they meet the large one).
 // Without rotation (b == 1) the values are bf16 and their products exact in fp32: hessian_kernel, straight from X.
 // The matrix is symmetric: only tiles on and below the diagonal are computed, each is stored twice.
 #include "device_util.hpp"
@@ -33,7 +36,10 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 struct HessArgs {
     const uint16_t* x;  // [T, K] bf16
     float* H;           // [K, K]
-    float* xr;          // b > 1: the rotated rows, packed (packed_at)
+    float* xr;          // b > 1, few rows: the rotated rows, packed (packed_at)
+    char* planes;       // b > 1, many rows: the stages of 32 rotated rows (see there), one behind the other ...
+    float* scales;      // ... and the scales of their blocks, [group of stages][K / 16]
+    int stages;         // of them (the rows behind are rotated by every workgroup for itself)
     float* part;        // b == 1: partial tiles of the split tail
     int64_t T;
     int K, b, accumulate;
@@ -41,7 +47,7 @@ struct HessArgs {
     int full;           // tiles 0 .. full - 1 take all of T in one workgroup ...
     int parts;          // ... each of the others is shared by this many
     int chunk;          // rows of X per part (multiple of kRows)
-    float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b
+    float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b (many rows: what is left of the blocks' scales and 1 / b)
 };
 
 // p-th tile of the lower triangle (row >= col), counted super-row by super-row
@@ -251,32 +257,24 @@ __global__ __launch_bounds__(256, 2) void hessian_tail_kernel(HessArgs a)
     finish_tile(a, ti, tj, acc, S);
 }
 
-// ---------------------------------------------------------------- b > 1: rotated rows
+// ---------------------------------------------------------------- b > 1, few rows
 
 // Where element (t, column) of the rotated rows lies: eight rows of a column side by side (what a lane of the bf16 MFMA takes
 // of the contraction), columns behind each other; a last group of fewer rows is packed, so that T K floats hold it all.
 __device__ __forceinline__ int64_t packed_at(const HessArgs& a, int64_t group, int col, int rows) { return group * 8 * a.K + (int64_t)col * rows; }
 
-// Eight rows by 512 columns per workgroup.  A thread rotates sixteen neighbouring columns of a row in registers -- butterflies, the
-// levels above sixteen across lanes, fp32 sums of up to 128 bf16 values -- and the power of two nearest below sqrt(b) is
-// divided out, exactly; what is left of 1 / b (a half at b = 32 and 128) is multiplied onto the finished sums.
-constexpr int kRotCols = 512;
-__global__ __launch_bounds__(256) void hessian_rotate_kernel(HessArgs a)
+// Sixteen neighbouring columns of row t per thread, rotated in registers -- butterflies, the levels above sixteen across lanes, fp32
+// sums of up to 128 bf16 values.  Columns go with the lanes; rows and columns that do not exist are zero.
+__device__ __forceinline__ void rotate_row(const HessArgs& a, int64_t t, int c, float (&v)[16])
 {
-    __shared__ __attribute__((aligned(16))) float S[kRotCols * 8 + kRotCols / 16 * 8];  // [column][row]; eight floats more every sixteen columns (banks)
-    const int tid = threadIdx.x, r = tid >> 5, piece = tid & 31;
-    const int c0 = blockIdx.y * kRotCols, cols = min(kRotCols, a.K - c0);
-    const int64_t group = blockIdx.x;
-    const int rows = (int)min((int64_t)8, a.T - group * 8);
     const int levels = a.b == 16 ? 0 : (a.b == 32 ? 1 : a.b == 64 ? 2 : 3);
     uint4 lo = make_uint4(0u, 0u, 0u, 0u), hi = lo;
-    if (r < rows && piece * 16 < cols) {  // (K is a multiple of b: lanes that exchange values are in or out of the row together)
-        const uint4* src = reinterpret_cast<const uint4*>(a.x + (group * 8 + r) * a.K + c0 + piece * 16);
+    if (t < a.T && c < a.K) {  // (K is a multiple of b: lanes that exchange values are in or out of the row together)
+        const uint4* src = reinterpret_cast<const uint4*>(a.x + t * a.K + c);
         lo = src[0];
         hi = src[1];
     }
     const uint32_t raw[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    float v[16];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         v[2 * i] = __uint_as_float(raw[i] << 16);
@@ -292,13 +290,28 @@ __global__ __launch_bounds__(256) void hessian_rotate_kernel(HessArgs a)
                 v[i + d] = x - y;
             }
     for (int l = 0; l < levels; ++l) {
-        const bool upper = (tid >> l) & 1;
+        const bool upper = (threadIdx.x >> l) & 1;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const float o = __shfl_xor(v[i], 1 << l);
             v[i] = upper ? o - v[i] : v[i] + o;
         }
     }
+}
+
+// Eight rows by 512 columns per workgroup.  A thread rotates sixteen neighbouring columns of a row in registers -- butterflies, the
+// levels above sixteen across lanes, fp32 sums of up to 128 bf16 values -- and the power of two nearest below sqrt(b) is
+// divided out, exactly; what is left of 1 / b (a half at b = 32 and 128) is multiplied onto the finished sums.
+constexpr int kRotCols = 512;
+__global__ __launch_bounds__(256) void hessian_rotate_kernel(HessArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float S[kRotCols * 8 + kRotCols / 16 * 8];  // [column][row]; eight floats more every sixteen columns (banks)
+    const int tid = threadIdx.x, r = tid >> 5, piece = tid & 31;
+    const int c0 = blockIdx.y * kRotCols, cols = min(kRotCols, a.K - c0);
+    const int64_t group = blockIdx.x;
+    const int rows = (int)min((int64_t)8, a.T - group * 8);
+    float v[16];
+    rotate_row(a, r < rows ? group * 8 + r : a.T, piece * 16 < cols ? c0 + piece * 16 : a.K, v);
 #pragma unroll
     for (int i = 0; i < 16; ++i) S[(piece * 16 + i) * 8 + piece * 8 + r] = v[i] * a.in_scale;
     __syncthreads();
@@ -492,6 +505,345 @@ __global__ __launch_bounds__(256, 2) void hessian_split_kernel(HessArgs a)
     }
 }
 
+// ---------------------------------------------------------------- b > 1, many rows
+
+// The rotated rows X' are kept as the MFMA takes them.  A stage is 32 rows; its columns lie in blocks of sixteen, in which lane
+// (c, q) holds column c of rows 8 q .. 8 q + 7: the high halves of the 64 lanes, then the low ones.  A value y is
+// (h + l) / 2^(14 - e), e the exponent of the largest |y| of the block over a GROUP of four stages, h the nearest fp16 of y's
+// share and l that of what is left: y itself or, where the remainder's 13th bit is set, y but for 2^-23 of it, down to 2^-17
+// of the block's largest value (below, l has a fixed last place: 2^-39 of that value).  Sums are kept 2^14 times as large: up to 2^113.
+constexpr int kBlockBytes = 2048;   // sixteen columns of a stage
+constexpr int kGroup = 4;           // stages that share their scales
+
+// The scale of a thread's block from the largest value of every thread: its exponent e, biased, 14 at least (2^(14 - e) and
+// 2^(e - 7) are normal numbers then, also where e says infinity).
+__device__ __forceinline__ uint32_t block_exponent(float top, float (*red)[8])
+{
+    const int tid = threadIdx.x, piece = tid & 7;
+#pragma unroll
+    for (int s = 8; s < 64; s <<= 1) top = fmaxf(top, __shfl_xor(top, s));
+    if ((tid & 63) < 8) red[tid >> 6][piece] = top;
+    __syncthreads();
+    top = fmaxf(fmaxf(red[0][piece], red[1][piece]), fmaxf(red[2][piece], red[3][piece]));
+    return max(__float_as_uint(top) >> 23, 14u);
+}
+__device__ __forceinline__ float block_scale(uint32_t e) { return __uint_as_float((e - 7u) << 23); }
+
+// a thread's sixteen values into the stage at dst, its blocks `pitch` bytes apart
+__device__ __forceinline__ void put_row(const float (&v)[16], uint32_t e, char* dst, int pitch)
+{
+    const int r = threadIdx.x >> 3, piece = threadIdx.x & 7;
+    const float up = __uint_as_float((268u - e) << 23);
+    _Float16* out = reinterpret_cast<_Float16*>(dst + piece * pitch) + (r >> 3) * 128 + (r & 7);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const float y = v[i] * up;
+        const _Float16 h = (_Float16)y;
+        out[i * 8] = h;
+        out[i * 8 + 512] = (_Float16)(y - (float)h);
+    }
+}
+
+// the stages that the workspace holds; a workgroup writes a group of them, 128 columns wide.  Bound: HBM, 2 bytes a value read
+// and 4 written.
+__global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
+{
+    constexpr int kPad = kBlockBytes + 16;   // (a row's eight pieces write to different banks)
+    __shared__ __attribute__((aligned(16))) char S[8 * kPad];
+    __shared__ float red[4][8];
+    const int tid = threadIdx.x, c0 = blockIdx.y * kT, blocks = min(kT, a.K - c0) / 16;
+    const int s0 = blockIdx.x * kGroup, count = min(kGroup, a.stages - s0);
+    float v[kGroup][16], top = 0.0f;
+#pragma unroll
+    for (int g = 0; g < kGroup; ++g) {
+        rotate_row(a, g < count ? (int64_t)(s0 + g) * 32 + (tid >> 3) : a.T, c0 + (tid & 7) * 16, v[g]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) top = fabs_max(top, v[g][i]);
+    }
+    const uint32_t e = block_exponent(top, red);
+    if (tid < blocks) a.scales[(int64_t)blockIdx.x * (a.K / 16) + c0 / 16 + tid] = block_scale(e);
+#pragma unroll
+    for (int g = 0; g < kGroup; ++g) {
+        if (g >= count) break;
+        put_row(v[g], e, S, kPad);
+        __syncthreads();
+        uint4* const dst = reinterpret_cast<uint4*>(a.planes + (int64_t)(s0 + g) * 128 * a.K + c0 * 128);
+        for (int i = tid; i < blocks * (kBlockBytes / 16); i += 256)
+            dst[i] = *reinterpret_cast<const uint4*>(S + (i >> 7) * kPad + (i & 127) * 16);
+        __syncthreads();
+    }
+}
+
+// the stage that begins with row t, of the 128 columns from c0, in LDS: for rows that the workspace has no room for
+__device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0, char* dst, float* scale, float (*red)[8])
+{
+    float v[16], top = 0.0f;
+    rotate_row(a, t + (threadIdx.x >> 3), c0 + (threadIdx.x & 7) * 16, v);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) top = fabs_max(top, v[i]);
+    const uint32_t e = block_exponent(top, red);
+    if (threadIdx.x < 8) scale[threadIdx.x] = block_scale(e);
+    put_row(v, e, dst, kBlockBytes);
+}
+
+// 16 x 16 sums in the MFMA's output order -- a lane holds columns col .. col + 3 of a row -- stored with their mirror image; of a
+// block on the diagonal the lower half counts (K is a multiple of 16)
+__device__ __forceinline__ void store_block(const HessArgs& a, int row, int col, bool cut, v4f s)
+{
+    if (row >= a.K || col >= a.K) return;
+    float* const own = a.H + (int64_t)row * a.K + col;
+    float* const mirror = a.H + (int64_t)col * a.K + row;
+    if (!cut) {
+        v4f* const d = reinterpret_cast<v4f*>(own);
+        *d = a.accumulate ? *d + s : s;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (cut && col + v <= row) own[v] = a.accumulate ? own[v] + s[v] : s[v];
+        float* const m = mirror + (int64_t)v * a.K;
+        if (!cut || col + v < row) *m = a.accumulate ? *m + s[v] : s[v];
+    }
+}
+
+// of the column's and the row's two parts: the products that count, small ones first (low times low is 2^-23 of the whole)
+__device__ constexpr int kParts[3][2] = {{1, 0}, {0, 1}, {0, 0}};
+
+// A tile of 128 x 128, a 64 x 64 quarter per wave, a stage at a time, copied into LDS as it lies in the workspace, the next one
+// meanwhile.  The three products of 32 rows are summed from zero in the MFMA (which cuts off what an addition leaves over), four
+// such sums in t, and those, with the scales of their blocks, in acc.  The column operand is the MFMA's A, so that a lane
+// owns four neighbouring columns of a row of H.  Two workgroups per compute unit, so that one's barrier and LDS reads run under the
+// other's MFMAs.  Bound at K = 4096, 512 tiles over 8192 rows, 375 us: without the copies into LDS 305, at the 1.6 PFLOP/s of a large
+// bf16 product 257.  (Operands of the next stage read into registers ahead of its barrier: 3 % slower.)
+constexpr int kTile = 4, kTileStage = 16 * kBlockBytes, kTileLds = 2 * (kTileStage + 1024) + 128;   // 16-wide blocks per wave side; stages and their scales, red
+__global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
+{
+    constexpr int NT = kTile, STAGE = kTileStage;
+    // two stages; per stage and wave the scales of 8 row blocks and 8 column blocks (and filling); block_exponent's maxima
+    extern __shared__ __attribute__((aligned(1024))) char St[];
+    float* const Sc = reinterpret_cast<float*>(St + 2 * STAGE);
+    float(*const red)[8] = reinterpret_cast<float(*)[8]>(St + 2 * (STAGE + 1024));
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of the tiles
+    const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
+    int ti, tj;
+    tile_of(xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3), a.nt, ti, tj);
+    const bool diag = ti == tj;
+    const int r0 = ti * kT, c0 = tj * kT;
+    const int wr = (wave >> 1) * NT, wc = (wave & 1) * NT;   // first block of rows / columns of the wave's quarter
+
+    // Blocks past the end are the last one again: they only feed outputs that are not stored.  Past the last stage the copies
+    // repeat it into a slot that nobody reads any more.
+    const int kb = a.K / 16, stages = a.stages;
+    const uint32_t scale_at = 4u * (uint32_t)min(((lane & 8) ? c0 : r0) / 16 + (lane & 7), kb - 1);
+    auto issue = [&](int s) {
+        const int from = min(s, stages - 1), slot = s & 1;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(a.planes + (int64_t)from * 128 * a.K, 0, 128 * a.K, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(a.scales + (int64_t)(from / kGroup) * kb, 0, 4 * kb, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int c = wave * 8 + i;                      // 1 KB: half a block
+            const int block = (c < 16 ? r0 : c0) / 16 + (c & 15) / 2;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(St + slot * STAGE + c * 1024), 16, lane * 16, min(block, kb - 1) * kBlockBytes + (c & 1) * 1024, 0, 0);
+        }
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_void*)(Sc + (slot * 4 + wave) * 64), 4, scale_at, 0, 0, 0);
+    };
+    v4f acc[NT][NT], t[NT][NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    // rows, cols: the wave's first block of either operand
+    auto multiply = [&](const char* rows, const char* cols) {
+        auto block = [&](const char* s, int i, int part) { return *(reinterpret_cast<const v8h*>(s + i * kBlockBytes + part * 1024) + lane); };
+        v8h u[2][NT], next[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) next[k] = block(rows, 0, k);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) u[k][j] = block(cols, j, k);
+        v4f sum[2][NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const v8h e[2] = {next[0], next[1]};
+            if (i + 1 < NT) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) next[k] = block(rows, i + 1, k);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // (the sums of the row block before are added up between the products of this one)
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    v4f& d = sum[i & 1][j];
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_f16(u[kParts[s][0]][j], e[kParts[s][1]], s ? d : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    if (i && s == 0) t[i - 1][j] += sum[(i - 1) & 1][j];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) t[NT - 1][j] += sum[(NT - 1) & 1][j];
+    };
+    auto scale_sums = [&](const float* rows, const float* cols) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const float f = rows[i] * cols[j];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][j][v] = fmaf(t[i][j][v], f, acc[i][j][v]);
+                t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            }
+    };
+    if (stages > 0) {
+        issue(0);
+        for (int s = 0; s < stages; ++s) {
+            wait_vmcnt<0>();
+            wait_lgkmcnt0();
+            block_barrier();   // stage s has landed, stage s - 1 has been read
+            issue(s + 1);
+            const char* base = St + (s & 1) * STAGE;
+            multiply(base + wr * kBlockBytes, base + (8 + wc) * kBlockBytes);
+            if ((s + 1) % kGroup == 0 || s + 1 == stages) {
+                const float* sc = Sc + ((s & 1) * 4 + wave) * 64;
+                scale_sums(sc + wr, sc + 8 + wc);
+            }
+        }
+        wait_vmcnt<0>();
+    }
+    for (int64_t row = (int64_t)stages * 32; row < a.T; row += 32) {
+        __syncthreads();
+        build_stage(a, row, r0, St, Sc, red);
+        __syncthreads();
+        build_stage(a, row, c0, St + 8 * kBlockBytes, Sc + 8, red);
+        __syncthreads();
+        multiply(St + wr * kBlockBytes, St + (8 + wc) * kBlockBytes);
+        scale_sums(Sc + wr, Sc + 8 + wc);
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            if (!diag || wr + i >= wc + j)
+                store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, acc[i][j] * a.out_scale);
+}
+
+// A tile of 32 x 32, for what is left beyond whole rounds of the tiles above: each of the four waves takes a quarter of the groups for
+// itself, straight from memory to registers a group ahead, no barrier; then their sums are added.
+__global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
+{
+    constexpr int NT = 2, SUB = kT / 32;
+    __shared__ __attribute__((aligned(16))) char St[16 * kBlockBytes];   // the stages rotated on the spot, then the waves' sums
+    __shared__ float Sc[16], red[4][8];
+    static_assert(sizeof(St) >= 4 * NT * NT * 64 * sizeof(v4f), "the sums fit");
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
+    const int p = xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3);
+    int ti, tj;
+    tile_of(a.full + p / (SUB * SUB), a.nt, ti, tj);
+    ti = SUB * ti + p / SUB % SUB;
+    tj = SUB * tj + p % SUB;
+    if (tj > ti || ti * 32 >= a.K) return;
+    const int r0 = ti * 32, c0 = tj * 32, kb = a.K / 16;
+    const int groups = (a.stages + kGroup - 1) / kGroup, share = (groups + 3) / 4;
+    const int g_begin = wave * share, g_end = min(groups, g_begin + share);
+
+    v4f acc[NT][NT], t[NT][NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    v8h rows[kGroup][2][NT], cols[kGroup][2][NT];   // (blocks past the end: the last one again, for outputs that are not stored)
+    auto fetch = [&](int s, v8h (&r)[2][NT], v8h (&c)[2][NT]) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(a.planes + (int64_t)min(s, a.stages - 1) * 128 * a.K, 0, 128 * a.K, 0x00020000);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                r[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(r0 / 16 + i, kb - 1) * kBlockBytes + k * 1024, 0));
+                c[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(c0 / 16 + i, kb - 1) * kBlockBytes + k * 1024, 0));
+            }
+    };
+    auto multiply = [&](const v8h (&r)[2][NT], const v8h (&c)[2][NT]) {
+        v4f sum[NT][NT];
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(c[kParts[s][0]][j], r[kParts[s][1]][i], s ? sum[i][j] : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) t[i][j] += sum[i][j];
+    };
+    auto scale_sums = [&](const float (&r)[NT], const float (&c)[NT]) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const float f = r[i] * c[j];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][j][v] = fmaf(t[i][j][v], f, acc[i][j][v]);
+                t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            }
+    };
+    if (g_begin < g_end) {
+#pragma unroll
+        for (int d = 0; d < kGroup; ++d) fetch(g_begin * kGroup + d, rows[d], cols[d]);
+        for (int g = g_begin; g < g_end; ++g) {
+            float fr[NT], fc[NT];
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                fr[i] = a.scales[(int64_t)g * kb + min(r0 / 16 + i, kb - 1)];
+                fc[i] = a.scales[(int64_t)g * kb + min(c0 / 16 + i, kb - 1)];
+            }
+#pragma unroll
+            for (int d = 0; d < kGroup; ++d) {
+                if (g * kGroup + d < a.stages) multiply(rows[d], cols[d]);
+                fetch((g + 1) * kGroup + d, rows[d], cols[d]);
+            }
+            scale_sums(fr, fc);
+        }
+    }
+    for (int64_t row = (int64_t)a.stages * 32; row < a.T; row += 32) {
+        __syncthreads();
+        build_stage(a, row, r0 & ~(kT - 1), St, Sc, red);
+        __syncthreads();
+        build_stage(a, row, c0 & ~(kT - 1), St + 8 * kBlockBytes, Sc + 8, red);
+        __syncthreads();
+        if (wave != (int)((row - (int64_t)a.stages * 32) / 32 & 3)) continue;
+        const int br = (r0 & (kT - 1)) / 16, bc = 8 + (c0 & (kT - 1)) / 16;
+        float fr[NT], fc[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            fr[i] = Sc[br + i];
+            fc[i] = Sc[bc + i];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                rows[0][k][i] = *(reinterpret_cast<const v8h*>(St + (br + i) * kBlockBytes + k * 1024) + lane);
+                cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (bc + i) * kBlockBytes + k * 1024) + lane);
+            }
+        }
+        multiply(rows[0], cols[0]);
+        scale_sums(fr, fc);
+    }
+    v4f* const sums = reinterpret_cast<v4f*>(St);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) sums[(wave * NT * NT + i * NT + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    const int i = wave / NT, j = wave % NT;   // one 16 x 16 block per wave
+    v4f s = sums[wave * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) s += sums[(w * NT * NT + wave) * 64 + lane];
+    if (ti != tj || i >= j) store_block(a, r0 + i * 16 + l16, c0 + j * 16 + 4 * q, ti == tj && i == j, s * a.out_scale);
+}
+
 }  // namespace
 
 hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float* H, bool accumulate, void* workspace, hipStream_t st)
@@ -509,6 +861,30 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
     // two workgroups per compute unit work at a time; the tiles beyond whole rounds of those would run on a mostly idle chip for a
     // whole tile's time (K = 4096: 528 tiles for 512 slots)
     const int tiles = a.nt * (a.nt + 1) / 2, slots = 2 * compute_units(), rem = tiles % slots;
+    // Two 22-bit halves on the fp16 MFMA from 1408 rows, or from 768 if there are enough tiles to fill the chip: fewer products, but
+    // one launch more and 32 rows or more rotated on the spot.  The other way against this one, us: T = 768, K = 2048 / 3328 / 4096
+    // 49 / 94 / 113 against 58 / 71 / 90; T = 1024, K = 1024 / 2048 / 4096 30 / 60 / 139 against 36 / 64 / 101; T = 1500, K = 1024 / 2048
+    // 42 / 85 against 41 / 80.  Below 768 rows its error is the larger one (T = 512 up to 1.06, 256 up to 1.26 times).
+    if (b > 1 && (T >= 1408 || (T >= 768 && tiles > slots / 3))) {
+        // (a stage takes 128 K bytes and K / 4 for its scales; what the 4 T K bytes do not hold is rotated on the spot)
+        a.stages = (int)(T * 16 / 513);
+        a.planes = static_cast<char*>(workspace);
+        a.scales = reinterpret_cast<float*>(a.planes + (int64_t)a.stages * 128 * K);
+        a.out_scale = 0x1p-14f / (float)b;
+        hipLaunchKernelGGL(hessian_pack_kernel, dim3((unsigned)((a.stages + kGroup - 1) / kGroup), (unsigned)a.nt), dim3(256), 0, st, a);
+        // parts of 32 x 32 where the tiles beyond whole rounds are few.  8192 rows, those left whole / in parts, us: K = 4096 (16 left)
+        // 592 / 436, 1024 (36) 251 / 90, 1664 (91) 250 / 178, 2048 (136) 252 / 229, 2304 (171) 257 / 283, 3328 (351) 345 / 601
+        const int small = rem > slots * 9 / 32 ? 0 : rem;
+        a.full = tiles - small;
+        if (a.full) {
+            static LdsAttrOnce once;
+            const hipError_t e = once.ensure(reinterpret_cast<const void*>(hessian_tile_kernel), kTileLds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(hessian_tile_kernel, dim3((unsigned)a.full), dim3(256), kTileLds, st, a);
+        }
+        if (small) hipLaunchKernelGGL(hessian_part_kernel, dim3((unsigned)(16 * small)), dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
     if (b > 1) {
         a.in_scale = b >= 64 ? 0.125f : 0.25f;
         a.out_scale = 1.0f / ((float)b * a.in_scale * a.in_scale);

@@ -373,6 +373,29 @@ def test_hessian_of_rows_with_a_common_component_in_a_block(fp4, oracle, kind, T
         assert np.array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("T,K,b", [(1408, 144, 16), (1409, 1744, 16), (1540, 256, 128), (800, 2416, 16), (1475, 4112, 16)])
+def test_hessian_of_many_rows_at_the_edges_of_stages_and_groups(fp4, oracle, T, K, b):
+    """Rows kept as two scaled fp16 halves: row counts around whole stages of 32 and groups of four, and the rows behind them that
+    are rotated on the spot (33 to 63 of them); tiles of 32, of 128, and both; rows whose sizes differ by up to 2^40, so that the scales of
+    neighbouring groups do.  Bound relative to sqrt(h_ii h_jj) >= sum |x_i x_j|: both halves 2^-23 of either value, sums of 32 rows
+    cut off at 2^-23, four of those added, then T / 128 of the groups' sums, each rounded to 2^-24; and 2 x 4 roundings of the rotated
+    values on either side of the oracle's, of partial sums not larger than four times the value in the root mean square."""
+    import torch
+    x = np.random.default_rng(T).standard_normal((T, K)) * 2.0 ** np.random.default_rng(K).integers(-20, 21, (T, 1))
+    xb = inputs.f32_to_bf16_bits(x.astype(np.float32))
+    X = oracle.rotate(xb, b).astype(np.float64)
+    want = X.T @ X
+    say(f"gptq hessian T={T} K={K} b={b}")
+    H = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(xb), b)
+    H2 = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(xb), b, H.clone())
+    torch.cuda.synchronize()
+    scale = np.sqrt(np.outer(np.diag(want), np.diag(want)))
+    for got, times in ((np_(H).astype(np.float64), 1), (np_(H2).astype(np.float64), 2)):
+        say(f"   largest error over sqrt(h_ii h_jj): {(np.abs(got - times * want) / scale).max():.2e}")
+        assert np.all(np.abs(got - times * want) <= times * (42 + T / 128) * 2.0 ** -24 * scale)
+        assert np.array_equal(got, got.T)
+
+
 def test_calibration_rows_to_codes_entirely_on_the_gpu(fp4, oracle, gptq):
     import torch
     N, K, T, b = 64, 512, 1536, 32
