@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libfp4mr.so: argument marshalling only.
+"""Thin binding of libfp4mr.so: argument marshalling only (ctypes; the calls of every token in compiled code, csrc/calls.cpp).
 
 PyTorch supplies device memory (``torch.empty(..., device="cuda")``) and the current HIP stream; every step of
 the path runs inside the library's HIP kernels.  There is no CPU fallback: importing this module raises if the
@@ -74,6 +74,16 @@ lib.fp4_set_option.argtypes = [_i32, _i32]
 lib.fp4_set_option.restype = _i32
 
 
+# The compiled form of the plain calls.  It answers None to everything else, and the Python below takes the call; without it (a
+# torch that it was not built against) Python takes them all.
+try:
+    from . import _calls
+    _calls.bind(*(ctypes.cast(f, _p).value for f in (lib.fp4_rotate_quantize, lib.fp4_quantize_weights, lib.fp4_rotate_quantize_dense, lib.fp4_gemm,
+                                                     lib.fp4_fused_linear, lib.fp4_w4a16_linear, lib.fp4_workspace_bytes, lib.fp4_packed_bytes)))
+except ImportError:
+    _calls = None
+
+
 class Fp4mrError(RuntimeError):
     def __init__(self, status: int):
         self.status = status
@@ -122,6 +132,10 @@ def workspace_bytes(op: int, M: int, N: int, K: int, fmt: int, flags: int = 0) -
 
 
 def _quantize(fn, op, x, had_block, fmt, flags, tensor_scale, codes, scales, workspace, rot=None):
+    if _calls is not None and tensor_scale is None and codes is None and scales is None and workspace is None:
+        out = _calls.quantize(x, had_block, fmt, flags, 2 if rot is not None else 1 if op == OP_QUANTIZE_WEIGHTS else 0, rot)
+        if out is not None:
+            return out
     assert x.is_cuda and x.dim() == 2 and x.is_contiguous()
     rows, K = x.shape
     if x.dtype == torch.float32:
@@ -250,6 +264,10 @@ def fp4_gptq_quantize_weights(w, had_block: int, fmt: int, hinv_u, perm=None, *,
 def fp4_gemm(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M: int, N: int, K: int, fmt: int, *,
              flags: int = 0, out=None, workspace=None):
     """out[M,N] = Ahat @ What^T (bf16, or fp32 with OUT_F32).  Operand layouts per A_LAYOUT_GEMM / W_LAYOUT_GEMM."""
+    if _calls is not None and out is None and workspace is None:
+        out = _calls.gemm(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, fmt, flags)
+        if out is not None:
+            return out
     empty = a_codes.new_empty if type(a_codes) is _Tensor else _plain_empty(a_codes)
     if out is None:
         out = empty((M, N), dtype=torch.float32 if flags & OUT_F32 else torch.bfloat16)
@@ -264,6 +282,10 @@ def fp4_gemm(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scal
 
 def fp4_fused_linear(x, had_block: int, w_codes, w_scales, N: int, fmt: int = MXFP4, *, flags: int = 0, out=None):
     """out[M,N] = Q(X H_b) @ Q(W H_b)^T in one launch for M <= 4 tokens (MXFP4, W in GEMM layout)."""
+    if _calls is not None and out is None:
+        out = _calls.linear(x, had_block, w_codes, w_scales, N, fmt, flags, 0)
+        if out is not None:
+            return out
     assert x.is_cuda and x.dim() == 2 and x.is_contiguous() and x.dtype == torch.bfloat16
     M, K = x.shape
     if out is None:
@@ -276,6 +298,10 @@ def fp4_fused_linear(x, had_block: int, w_codes, w_scales, N: int, fmt: int = MX
 
 def fp4_w4a16_linear(x, had_block: int, w_codes, w_scales, N: int, fmt: int = MXFP4, *, flags: int = 0, out=None):
     """out[M,N] = bf16(X H_b) @ Q(W H_b)^T: weight-only variant of fp4_fused_linear (M <= 16, MXFP4, W in GEMM layout)."""
+    if _calls is not None and out is None:
+        out = _calls.linear(x, had_block, w_codes, w_scales, N, fmt, flags, 1)
+        if out is not None:
+            return out
     assert x.is_cuda and x.dim() == 2 and x.is_contiguous() and x.dtype == torch.bfloat16
     M, K = x.shape
     if out is None:

@@ -1,4 +1,5 @@
-"""Builds libfp4mr.so (the C-ABI library of HIP kernels) in-tree for gfx950 with hipcc.
+"""Builds libfp4mr.so (the C-ABI library of HIP kernels) in-tree for gfx950 with hipcc, and _calls.so (the binding's compiled
+calls, host code only) with g++ against the installed torch.
 
     python -m paper_2509_23202_amd.build
 
@@ -10,6 +11,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -17,6 +19,7 @@ HERE = Path(__file__).resolve().parent
 CSRC = HERE / "csrc"
 BUILD = HERE / "_build"
 LIB = HERE / "libfp4mr.so"
+CALLS = HERE / "_calls.so"
 SOURCES = ["api.hip", "rotate_quantize.hip", "gemm_mxfp4.hip", "gemm_nvfp4.hip", "gemm_nv16.hip", "gemm_skinny.hip", "gemm_fused_decode.hip", "repack.hip", "gptq.hip", "gptq_prepare.hip", "gptq_hessian.hip", "probes.hip", "dequantize.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -48,10 +51,29 @@ def _compile(src: str) -> Path:
     return obj
 
 
+def _build_calls() -> None:
+    import torch
+    t = Path(torch.__file__).resolve().parent
+    if not (t / "include/c10/hip/HIPStream.h").exists():   # (not a ROCm build: the binding has nothing to call there)
+        CALLS.unlink(missing_ok=True)
+        return
+    tmp = CALLS.with_suffix(".so.tmp%d" % os.getpid())
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", str(HERE.parent / "include"),
+           "-isystem", str(t / "include"), "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           str(CSRC / "calls.cpp"), "-o", str(tmp), "-L", str(t / "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for calls.cpp:\n" + r.stderr)
+    os.replace(tmp, CALLS)
+
+
 def build(verbose: bool = True) -> Path:
     BUILD.mkdir(exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES), os.cpu_count() or 1)) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1, os.cpu_count() or 1)) as ex:
+        calls = ex.submit(_build_calls)
         objs = list(ex.map(_compile, SOURCES))
+        calls.result()
     tmp = LIB.with_suffix(".so.tmp%d" % os.getpid())
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]
     r = subprocess.run(cmd, capture_output=True, text=True)
