@@ -238,6 +238,9 @@ __global__ __launch_bounds__(kThreads) void rq_mfma_kernel(RqArgs a)
     constexpr int T = BP / 16;           // output tiles
     constexpr int NO = BP / 4;           // outputs per lane
     constexpr int NST = FR * (128 / BP); // supertiles per item
+    // 64-wide operand in GEMM order: a lane holds both halves of a block of 128 (K-offsets 0 and 64 of one row), whose last
+    // butterfly level is an addition and a subtraction in registers
+    constexpr bool PAIRED = LAYOUT == 1 && BP == 64 && NST == 2;
     using GQ = GroupQuant<G, NO, 16, HW>;
 
     extern __shared__ __attribute__((aligned(16))) unsigned char rq_dyn_lds[];  // dense rotations: kDenseLdsBytes<BP>
@@ -307,17 +310,33 @@ __global__ __launch_bounds__(kThreads) void rq_mfma_kernel(RqArgs a)
                 }
             }
         }
-#pragma unroll
-        for (int u = 0; u < NST; ++u) {
-            v4f acc[T];
+        v4f accs[PAIRED ? NST : 1][T];
+        auto rotate = [&](v4f (&acc)[T], const v4i (&in)[S]) {
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int s = 0; s < S; ++s)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hop[t][s], __builtin_bit_cast(v8bf, xin[u][s]), acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hop[t][s], __builtin_bit_cast(v8bf, in[s]), acc[t], 0, 0, 0);
             }
-            if constexpr (LAYOUT == 0) kronecker_levels<T>(acc, g, kron);  // the launcher sends wider blocks here only in canonical order
+        };
+        if constexpr (PAIRED) {
+            rotate(accs[0], xin[0]);
+            rotate(accs[1], xin[1]);
+            if (kron) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const v4f h0 = accs[0][t], h1 = accs[1][t];
+                    accs[0][t] = h0 + h1;
+                    accs[1][t] = h0 - h1;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < NST; ++u) {
+            v4f(&acc)[T] = accs[PAIRED ? u : 0];
+            if constexpr (!PAIRED) rotate(acc, xin[u]);
+            if constexpr (LAYOUT == 0) kronecker_levels<T>(acc, g, kron);
             if constexpr (PASS == 1) {
 #pragma unroll
                 for (int t = 0; t < T; ++t)
@@ -808,11 +827,16 @@ hipError_t dispatch_block(const RqArgs& a, bool in_f32, int grid_cap, hipStream_
         if (in_f32) return launch_direct<float, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
         return launch_direct<uint16_t, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
     }
+    // Few tokens in GEMM order take the 64-wide operand for every Hadamard block: half as many lanes share a group as on the 32-wide
+    // one, and a lane's two halves of a block of 128 meet in registers.  K = 4096, M = 16 / 201, us: b = 32 on the 32-wide operand
+    // 3.19 / 3.35, now 3.07 / 3.14; b = 128 on the 128-wide one, which takes longer to build than to use, 4.30 / 4.41, now 3.10 / 3.21.
+    if constexpr (LAYOUT == 1 && PASS == 0) {
+        if (!a.rot && !frag_kernel_eligible(a)) return launch_mfma<64, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
+    }
     if (a.b <= 32) return launch_mfma<32, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
     // Hadamard blocks of 64 and 128 run on the 32-wide kernels plus butterfly levels across lanes wherever the
     // vectors of an MFMA group are consecutive along K: canonical order, and the big-call GEMM-order kernel.
-    const bool k_consecutive = LAYOUT == 0 || frag_kernel_eligible(a);
-    if (!a.rot && k_consecutive) return launch_mfma<32, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
+    if (!a.rot) return launch_mfma<32, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
     if (a.b == 64) return launch_mfma<64, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
     return launch_mfma<128, G, LAYOUT, PASS, HW, POL>(a, grid_cap, st, blocks_out);
 }
