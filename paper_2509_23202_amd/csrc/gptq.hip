@@ -13,6 +13,7 @@
 // column positions.
 #include "device_util.hpp"
 #include "internal.hpp"
+#include "pair16.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -30,7 +31,12 @@ struct GptqArgs {
     int* iperm;             // [K] scratch
     float* wp;              // [N,K] scratch: working weights, visiting order
     uint8_t* q;             // [N,K] scratch: one code per byte, visiting order
-    float* err;             // [N,kOuter] scratch: the errors of the current outer block
+    // scratch, the operands of an outer block's update as scaled pairs of halves (pair16.hpp), 16 stages along the contraction:
+    char* e_pairs;          // errors, [stage][16 rows]
+    float* e_scales;        // [kOuter / kB][rows]: of a row's errors of 64 columns
+    char* u_pairs;          // rows of U, [stage][16 columns]
+    float* u_scales;        // [kOuter / kB][K]: of a column's entries in 64 rows
+    int Np;                 // N rounded up to 16
     const uint8_t* scales;  // [N,K/G] canonical
     const float* s_T;       // NVFP4 tensor scale (device), else null
     const float* table;     // 256 scale values indexed by the scale byte (fitted scale range), else null
@@ -47,27 +53,21 @@ __device__ __forceinline__ int visit_col(const GptqArgs& a, int j)
     return min(max(c, 0), a.K - 1);
 }
 
-__global__ void gptq_iperm_fill_kernel(GptqArgs a)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < a.K) a.iperm[j] = j;
-}
-
-__global__ void gptq_iperm_kernel(GptqArgs a)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < a.K) a.iperm[visit_col(a, j)] = j;
-}
-
 // wp[n, j] = (W H_b)[n, perm[j]]: the rotated weight of the column visited j-th.  One workgroup per row.  A thread rotates sixteen
 // neighbouring columns in registers -- butterflies, the levels above sixteen across lanes (fp32 sums of b bf16 values, exact while
 // the values' exponents spread over no more than 16 - log2(b) bits: 9 at b = 128, 12 at 16; beyond, every level rounds, log2(b)
 // roundings where a sequential sum has b), then one multiplication by 1/sqrt(b) carried in two floats -- and the
 // row is read back from LDS in visiting order for whole-line stores.  With a sum over the block per column, from LDS, [6144, 4096]
-// took 91 us at b = 16 and 486 at b = 128; now 39 at either.
+// took 91 us at b = 16 and 486 at b = 128; now 39 at either.  The first workgroup inverts the order as well (an entry that is no
+// column's position, where the order is not a permutation, names a column all the same).
 __global__ __launch_bounds__(256) void gptq_rotate_gather_kernel(GptqArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float rowbuf[];  // K floats
+    if (blockIdx.x == 0) {
+        for (int j = threadIdx.x; j < a.K; j += 256) a.iperm[j] = j;
+        __syncthreads();
+        for (int j = threadIdx.x; j < a.K; j += 256) a.iperm[visit_col(a, j)] = j;
+    }
     const int n = blockIdx.x, levels = a.b <= 16 ? 0 : (a.b == 32 ? 1 : a.b == 64 ? 2 : 3);
     const uint4* src = reinterpret_cast<const uint4*>(a.w + (int64_t)n * a.K);
     // (K is a multiple of 64 and of b, so the lanes that exchange values are in or out of the row together)
@@ -137,6 +137,52 @@ __device__ __forceinline__ float decode_scale(uint32_t byte, float s_T, float fa
 // diagonal).
 typedef float v2f_t __attribute__((ext_vector_type(2)));
 
+constexpr int kStages = kOuter / 32;
+// 16-wide block `block` of a stage of an operand of `blocks` blocks
+__device__ __forceinline__ int64_t pairs_at(int stage, int blocks, int block) { return ((int64_t)stage * blocks + block) * kPairBytes; }
+
+// the largest |v| that is finite (an infinite error or NaN must not take its neighbours' scale)
+__device__ __forceinline__ float largest_finite(float a, float v)
+{
+    const float f = fabsf(v);
+    return f < INFINITY ? fmaxf(a, f) : a;
+}
+
+// Rows o .. o + 511 of U, columns 16 cb .. 16 cb + 15, for the update behind the outer block; eight waves, 64 rows each.
+__device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    const float* src = a.U + (int64_t)(o + 64 * wave + 8 * q) * a.K + cb * 16 + l16;
+    float v[2][8], top = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[s][i] = src[(int64_t)(32 * s + i) * a.K];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) top = largest_finite(top, v[s][i]);
+    top = fmaxf(top, __shfl_xor(top, 16));
+    top = fmaxf(top, __shfl_xor(top, 32));
+    const uint32_t e = pair_exponent(top);
+    const float up = pair_up(e);
+    if (q == 0) a.u_scales[wave * a.K + cb * 16 + l16] = pair_scale(e);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        v8h h, l;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            _Float16 hi, lo;
+            pair_split(v[s][i], up, hi, lo);
+            h[i] = hi;
+            l[i] = lo;
+        }
+        v8h* dst = reinterpret_cast<v8h*>(a.u_pairs + pairs_at(2 * wave + s, a.K / 16, cb)) + lane;
+        dst[0] = h;
+        dst[64] = l;
+    }
+}
+
 constexpr int kWStride = kOuter + 4;   // floats per row of working weights in LDS: rows start four banks apart
 constexpr int kEStride = kB + 4;
 
@@ -194,9 +240,18 @@ __device__ __forceinline__ void sweep_part(float (&w)[4], float (&kept)[4], uint
     if constexpr (P + 1 < 16) sweep_part<P + 1, KEEP>(w, kept, packed, next, Us, Ru, Sc, row, part);
 }
 
-// The errors also go to err[N, kOuter] for the update of everything behind the outer block.
+// Barrier of the waves that share the working weights: LDS only (the sweep's stores to memory, and what the others have requested
+// from there, need not have arrived: 500 cycles a time).
+__device__ __forceinline__ void lds_barrier()
+{
+    wait_lgkmcnt0();
+    block_barrier();
+}
+
+// The errors also go to memory, as operands of the update of everything behind the outer block; workgroups behind the first `rows16`
+// prepare the other operand meanwhile.
 template <int FMT>
-__global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, int oe)
+__global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, int oe, int rows16)
 {
     __shared__ __attribute__((aligned(16))) float W[16 * kWStride];      // working weights of the outer block
     __shared__ __attribute__((aligned(16))) float Us[kB * kB];           // the block's triangle of U, zero on and below the diagonal
@@ -204,6 +259,10 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
     __shared__ __attribute__((aligned(16))) float Es[16 * kEStride];     // the block's errors
     __shared__ __attribute__((aligned(16))) uint8_t Sb[kOuter * 16];     // [column][row]: scale bytes of the outer block
     __shared__ __attribute__((aligned(16))) float Rd[kOuter];            // 1 / U[j,j]
+    if ((int)blockIdx.x >= rows16) {
+        pack_u(a, o, oe / 16 + (int)blockIdx.x - rows16);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4;
@@ -231,8 +290,9 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
     // Two barriers per block, the same for the sweeping and the pushing waves: behind the sweep (its errors are in LDS), and
     // behind the push onto the next block (its weights, triangle and scales are).
     if (wave < 4) {
-        __syncthreads();
-        __syncthreads();
+        __builtin_amdgcn_s_setprio(3);   // (the chain; the other four work beside it)
+        lds_barrier();
+        lds_barrier();
         const int row = wave * 4 + q, part = l16, n = n0 + row;
         for (int b = 0; b < blocks; ++b) {
             const float4 w4 = *reinterpret_cast<const float4*>(&W[row * kWStride + b * kB + part * 4]);
@@ -254,12 +314,35 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
             }
             const float4 e4 = make_float4(e[0], e[1], e[2], e[3]);
             *reinterpret_cast<float4*>(&Es[row * kEStride + part * 4]) = e4;
-            if (n < a.N) {
-                *reinterpret_cast<float4*>(a.err + (int64_t)n * kOuter + b * kB + part * 4) = e4;
-                *reinterpret_cast<uint32_t*>(a.q + (int64_t)n * a.K + o + b * kB + part * 4) = codes;
+            lds_barrier();
+            if (n < a.N) *reinterpret_cast<uint32_t*>(a.q + (int64_t)n * a.K + o + b * kB + part * 4) = codes;
+            if (oe < a.K) {   // (rows past the end too: what they hold is not stored)
+                float top = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) top = largest_finite(top, e[i]);
+                // the sixteen lanes of the row: rotations by 8, 4, 2, 1
+                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x128, 0xf, 0xf, true)));
+                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x124, 0xf, 0xf, true)));
+                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x122, 0xf, 0xf, true)));
+                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x121, 0xf, 0xf, true)));
+                const uint32_t ex = pair_exponent(top);
+                const float up = pair_up(ex);
+                typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+                v4h h, l;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    _Float16 hi, lo;
+                    pair_split(e[i], up, hi, lo);
+                    h[i] = hi;
+                    l[i] = lo;
+                }
+                // columns 4 part .. 4 part + 3 of 64: stage part / 8, there half of lane (row, (part % 8) / 2)
+                char* dst = a.e_pairs + pairs_at(2 * b + (part >> 3), a.Np / 16, blockIdx.x) + (((part & 7) >> 1) * 16 + row) * 16 + (part & 1) * 8;
+                *reinterpret_cast<v4h*>(dst) = h;
+                *reinterpret_cast<v4h*>(dst + 1024) = l;
+                if (part == 0) a.e_scales[b * a.Np + n] = pair_scale(ex);
             }
-            __syncthreads();
-            __syncthreads();
+            lds_barrier();
         }
         return;
     }
@@ -284,12 +367,9 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
             scn[it] = v2f_t{sv, sv > 0.0f ? 1.0f / sv : 0.0f};
         }
     };
-    auto stash = [&] {
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            *reinterpret_cast<float4*>(&Us[(it * 16 + (pt >> 4)) * kB + (pt & 15) * 4]) = tri[it];
-            Sc[it * 256 + pt] = scn[it];
-        }
+    auto stash = [&](int it) {   // a quarter
+        *reinterpret_cast<float4*>(&Us[(it * 16 + (pt >> 4)) * kB + (pt & 15) * 4]) = tri[it];
+        Sc[it * 256 + pt] = scn[it];
     };
     // A operand of a push onto 16 columns: rows 4 ks + q of block b.  (Through a buffer resource: one lane offset for all
     // loads, the rest scalar; sixteen 64-bit addresses would not leave the registers for two factors in flight.)
@@ -308,10 +388,11 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
         *dst = *dst - sum;
     };
     fetch_tri(0);
-    __syncthreads();
+    lds_barrier();
     decode_scales(0);
-    stash();
-    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < 4; ++it) stash(it);
+    lds_barrier();
     for (int b = 0; b < blocks; ++b) {
         float un[16];
         if (b + 1 < blocks) {
@@ -333,109 +414,91 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
             }
             decode_scales(b + 1);
         }
-        __syncthreads();
+        lds_barrier();
         if (b + 1 < blocks) {
-            stash();
 #pragma unroll
             for (int ks = 0; ks < 16; ++ks) ea[ks] = Es[l16 * kEStride + ks * 4 + q];
-            push(un, (b + 1) * kB + pw * 16);
+            // the push onto the next block, its triangle and scales written to LDS under the products
+            v4f* dst = reinterpret_cast<v4f*>(&W[l16 * kWStride + (b + 1) * kB + pw * 16 + 4 * q]);
+            const v4f old = *dst;
+            v4f sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) {
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(un[ks], ea[ks], sum, 0, 0, 0);
+                if (ks % 4 == 0) stash(ks / 4);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            *dst = old - sum;
         }
-        __syncthreads();
+        lds_barrier();
     }
 }
 
-// wp[n, c] -= sum_{j < kOuter} err[n, j] * U[u0 + j, c] for the columns c_begin <= c < c_end (visiting order): a dense fp32
-// contraction, [N x 512] . [512 x columns].  The fp32 MFMA (157 TFLOP/s) bounded it, 82 of them; here both factors are split
-// into three bf16 and the six products above 2^-24 of the whole run on the bf16 MFMA, 6 / 16 of the time.  They are exact in
-// binary32; per 32 terms they are summed smallest first from zero and added to the accumulator once, 16 roundings at its
-// size where the fp32 MFMA had 128: codes that differ from a sweep in 64 bits 7e-4 -> 6e-5 (MXFP4, K = 4096; NVFP4 level),
-// [6144, 4096] behind its first outer block 308 -> 157 us.
-// 128 x 128 output tile per workgroup, a 64 x 64 quarter per wave; 32 terms at a time are split and written to LDS in the
-// MFMA's operand order (lane (r, q) of a 16-wide block: element r, terms 8 q .. 8 q + 7), the next 32 fetched meanwhile.  U is
-// the MFMA's A operand, so that a lane owns four neighbouring columns of a row.
-__global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int u0, int c_begin, int c_end)
+// wp[n, c] -= sum_{j < kOuter} e[n, j] * U[o + j, c] for the columns c_begin <= c < K (visiting order): a dense fp32
+// contraction, [N x 512] . [512 x columns], of the pairs of halves that the outer kernel left.  A row's errors have scales of
+// their own (rows do not interact), and so have a column's entries of U; 64 terms are added to the accumulator at a time.
+// 128 x 128 output tile per workgroup, a 64 x 64 quarter per wave, a stage of 32 terms copied into LDS while the one before is
+// multiplied; two workgroups per compute unit.  [6144, 4096] behind its first outer block 92 us (157 with six bf16 products of
+// operands that every workgroup split for itself, 308 on the fp32 MFMA), of which wp is 24 at the rate of a large copy; codes that differ from
+// a sweep in 64 bits, 32 layers of K = 2048 and 4096: 9616 of 50 million (9830 with the bf16 products).
+constexpr int kUpdateStage = 16 * kPairBytes, kUpdateLds = 2 * (kUpdateStage + 1024);   // 8 row blocks, then 8 column blocks; their scales
+__global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_begin)
 {
-    constexpr int T = 128, KC = 32, NT = 4;
-    __shared__ v8bf Et[3][T / 16][64], Ut[3][T / 16][64];   // [part][block of 16 rows / columns][lane]
-    const int c0 = c_begin + blockIdx.x * T;
-    const int n0 = blockIdx.y * T;
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
-    const int wr = (wave >> 1) * 4, wc = (wave & 1) * 4;   // first block of rows / columns of the wave's quarter
-    // this thread stages lane `lane` of the blocks wave and wave + 4 of either operand (past the edges: the last row and
-    // column again, which only feed outputs that are not stored)
-    const float* er[2];
-    const float* uc[2];
+    constexpr int T = 128, NT = 4;
+    extern __shared__ __attribute__((aligned(1024))) char St[];
+    float* const Sc = reinterpret_cast<float*>(St + 2 * kUpdateStage);   // for two groups of 64 terms: of 128 rows, of 128 columns
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int wr = (wave >> 1) * NT, wc = (wave & 1) * NT;   // first block of rows / columns of the wave's quarter
+    // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of tiles, which share rows
+    const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7, p = xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3);
+    const int tiles = (a.K - c_begin + T - 1) / T;
+    const int n0 = p / tiles * T, c0 = c_begin + p % tiles * T;
+    const int row_blocks = a.Np / 16, col_blocks = a.K / 16;
+    // Blocks past the end are the last one again: they only feed outputs that are not stored.
+    const uint32_t scale_at = 4u * (uint32_t)(wave < 2 ? min(n0 + wave * 64 + lane, a.Np - 1) : min(c0 + (wave - 2) * 64 + lane, a.K - 1));
+    auto issue = [&](int s) {
+        const int slot = s & 1;
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(a.e_pairs + pairs_at(s, row_blocks, n0 / 16), 0, min(row_blocks - n0 / 16, 8) * kPairBytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t cols = __builtin_amdgcn_make_buffer_rsrc(a.u_pairs + pairs_at(s, col_blocks, c0 / 16), 0, min(col_blocks - c0 / 16, 8) * kPairBytes, 0x00020000);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        er[h] = a.err + (int64_t)min(n0 + (wave + 4 * h) * 16 + l16, a.N - 1) * kOuter + 8 * q;
-        uc[h] = a.U + (int64_t)(u0 + 8 * q) * a.K + min(c0 + (wave + 4 * h) * 16 + l16, a.K - 1);
-    }
-    float re[2][8], ru[2][8];
-    auto fetch = [&](int r0) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const float4 lo = *reinterpret_cast<const float4*>(er[h] + r0), hi = *reinterpret_cast<const float4*>(er[h] + r0 + 4);
-            re[h][0] = lo.x, re[h][1] = lo.y, re[h][2] = lo.z, re[h][3] = lo.w;
-            re[h][4] = hi.x, re[h][5] = hi.y, re[h][6] = hi.z, re[h][7] = hi.w;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ru[h][i] = uc[h][(int64_t)(r0 + i) * a.K];
+        for (int i = 0; i < 8; ++i) {
+            const int c = (wave & 1) * 8 + i;   // 1 KB: half a block; two waves for either operand
+            char* const dst = St + slot * kUpdateStage + wave * 8192 + i * 1024;
+            if (wave < 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_void*)dst, 16, lane * 16, min(c >> 1, row_blocks - 1 - n0 / 16) * kPairBytes + (c & 1) * 1024, 0, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(cols, (lds_void*)dst, 16, lane * 16, min(c >> 1, col_blocks - 1 - c0 / 16) * kPairBytes + (c & 1) * 1024, 0, 0);
+        }
+        if (s % 2 == 0) {
+            const __amdgpu_buffer_rsrc_t rs = wave < 2 ? __builtin_amdgcn_make_buffer_rsrc(a.e_scales + (int64_t)(s / 2) * a.Np, 0, 4 * a.Np, 0x00020000)
+                                                       : __builtin_amdgcn_make_buffer_rsrc(a.u_scales + (int64_t)(s / 2) * a.K, 0, 4 * a.K, 0x00020000);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(Sc + (s / 2 & 1) * 256 + wave * 64), 4, scale_at, 0, 0, 0);
         }
     };
-    v4f acc[NT][NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    fetch(0);
-    for (int r0 = 0; r0 < kOuter; r0 += KC) {
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const Split3 e = split3(re[h]), u = split3(ru[h]);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                Et[p][wave + 4 * h][lane] = e.part[p];
-                Ut[p][wave + 4 * h][lane] = u.part[p];
-            }
-        }
-        __syncthreads();
-        if (r0 + KC < kOuter) fetch(r0 + KC);
-        v8bf u[3][NT];
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) u[p][j] = Ut[p][wc + j][lane];
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            v8bf e[3];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) e[p] = Et[p][wr + i][lane];
-            v4f sum[NT];
-#pragma unroll
-            for (int j = 0; j < NT; ++j) sum[j] = v4f{0.f, 0.f, 0.f, 0.f};
-            // (part of U, part of the error): 2^-16, 2^-8, 1 of the product
-            constexpr int order[6][2] = {{2, 0}, {1, 1}, {0, 2}, {1, 0}, {0, 1}, {0, 0}};
-#pragma unroll
-            for (int t = 0; t < 6; ++t)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    sum[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u[order[t][0]][j], e[order[t][1]], sum[j], 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j] += sum[j];
+    PairSums<NT> sums;
+    sums.clear();
+    issue(0);
+    for (int s = 0; s < kStages; ++s) {
+        wait_vmcnt<0>();
+        wait_lgkmcnt0();
+        block_barrier();   // stage s has landed, stage s - 1 has been read
+        if (s + 1 < kStages) issue(s + 1);
+        const char* base = St + (s & 1) * kUpdateStage;
+        sums.multiply(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
+        if (s & 1) {
+            const float* sc = Sc + (s / 2 & 1) * 256;
+            sums.scale([&](int i) { return sc[(wr + i) * 16 + l16]; }, [&](int j) { return *reinterpret_cast<const v4f*>(sc + 128 + (wc + j) * 16 + 4 * q); });
         }
     }
-    // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 tile (c_end is a multiple of 64)
+    // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 tile (K is a multiple of 64)
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-        const int n = n0 + (wr + i) * 16 + l16;
-        if (n >= a.N) continue;
-        float* row = a.wp + (int64_t)n * a.K + c0 + wc * 16 + 4 * q;
+        const int row = n0 + (wr + i) * 16 + l16;
+        if (row >= a.N) continue;
+        float* dst = a.wp + (int64_t)row * a.K + c0 + wc * 16 + 4 * q;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            if (c0 + (wc + j) * 16 >= c_end) continue;
-            v4f* dst = reinterpret_cast<v4f*>(row + 16 * j);
-            *dst = *dst - acc[i][j];
+            if (c0 + (wc + j) * 16 >= a.K) continue;
+            v4f* d = reinterpret_cast<v4f*>(dst + 16 * j);
+            *d = *d - sums.acc[i][j] * kPairResult;
         }
     }
 }
@@ -461,13 +524,16 @@ __global__ __launch_bounds__(256) void gptq_pack_kernel(GptqArgs a)
     }
 }
 
+constexpr size_t kPairsPerIndex = kOuter * 4 + kOuter / kB * 4;   // bytes of a row's (column's) pairs and scales
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 }  // namespace
 
 size_t gptq_workspace_bytes(int64_t N, int64_t K)
 {
-    return align256((size_t)N * K * 4) + align256((size_t)N * K) + align256((size_t)N * kOuter * 4) + align256((size_t)K * 4);
+    // working weights, codes, the pairs and scales of an outer block's errors and of its rows of U, the inverse order
+    const size_t np = (size_t)(N + 15) / 16 * 16, k = (size_t)K;
+    return align256((size_t)N * k * 4) + align256((size_t)N * k) + (np + k) * kPairsPerIndex + align256(k * 4);
 }
 
 hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt, const float* U, const int* perm,
@@ -482,8 +548,15 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     ws += align256((size_t)N * K * 4);
     a.q = reinterpret_cast<uint8_t*>(ws);
     ws += align256((size_t)N * K);
-    a.err = reinterpret_cast<float*>(ws);
-    ws += align256((size_t)N * kOuter * 4);
+    a.Np = (int)((N + 15) / 16 * 16);
+    a.e_pairs = ws;
+    ws += (size_t)a.Np * kOuter * 4;
+    a.u_pairs = ws;
+    ws += (size_t)K * kOuter * 4;
+    a.e_scales = reinterpret_cast<float*>(ws);
+    ws += (size_t)a.Np * (kOuter / kB) * 4;
+    a.u_scales = reinterpret_cast<float*>(ws);
+    ws += (size_t)K * (kOuter / kB) * 4;
     a.iperm = reinterpret_cast<int*>(ws);
     a.scales = static_cast<const uint8_t*>(scales);
     a.s_T = s_T;
@@ -499,9 +572,6 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     a.factor = factor;
     if (K % kB != 0 || N <= 0 || K > 24576) return hipErrorInvalidValue;  // (a row is staged in LDS)
 
-    const unsigned kblocks = (unsigned)((K + 255) / 256);
-    hipLaunchKernelGGL(gptq_iperm_fill_kernel, dim3(kblocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(gptq_iperm_kernel, dim3(kblocks), dim3(256), 0, st, a);
     const size_t row_lds = (size_t)K * 4;
     static LdsAttrOnce raised;
     if (row_lds > 48 * 1024) {
@@ -510,18 +580,20 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     }
     hipLaunchKernelGGL(gptq_rotate_gather_kernel, dim3((unsigned)N), dim3(256), row_lds, st, a);
     const unsigned row128 = (unsigned)((N + 127) / 128), row16 = (unsigned)((N + 15) / 16);
-    auto update = [&](int u0, int c_begin, int c_end) {
-        const unsigned tiles = (unsigned)((c_end - c_begin + 127) / 128);
-        hipLaunchKernelGGL(gptq_update_kernel, dim3(tiles, row128), dim3(256), 0, st, a, u0, c_begin, c_end);
-    };
+    static LdsAttrOnce update_once;
+    if (K > kOuter) {
+        const hipError_t le = update_once.ensure(reinterpret_cast<const void*>(gptq_update_kernel), kUpdateLds);
+        if (le != hipSuccess) return le;
+    }
     for (int o = 0; o < (int)K; o += kOuter) {
         const int oe = std::min(o + kOuter, (int)K);
         // the outer block itself: every workgroup takes 16 rows through the block's columns, four waves sweeping 64 of them at a
-        // time, four pushing their errors onto the rest of the outer block ...
-        if (fmt == 0) hipLaunchKernelGGL(gptq_outer_kernel<0>, dim3(row16), dim3(512), 0, st, a, o, oe);
-        else hipLaunchKernelGGL(gptq_outer_kernel<1>, dim3(row16), dim3(512), 0, st, a, o, oe);
+        // time, four pushing their errors onto the rest of the outer block, while others prepare the block's rows of U ...
+        const unsigned pack = (unsigned)((K - oe) / 16);
+        if (fmt == 0) hipLaunchKernelGGL(gptq_outer_kernel<0>, dim3(row16 + pack), dim3(512), 0, st, a, o, oe, (int)row16);
+        else hipLaunchKernelGGL(gptq_outer_kernel<1>, dim3(row16 + pack), dim3(512), 0, st, a, o, oe, (int)row16);
         // ... everything behind the outer block sees all of its errors in one pass
-        if (oe < (int)K) update(o, oe, (int)K);
+        if (oe < (int)K) hipLaunchKernelGGL(gptq_update_kernel, dim3(row128 * (unsigned)((K - oe + 127) / 128)), dim3(256), kUpdateLds, st, a, oe);
     }
     hipLaunchKernelGGL(gptq_pack_kernel, dim3((unsigned)N), dim3(256), (size_t)K, st, a);
     return hipGetLastError();

@@ -19,6 +19,7 @@
 // The matrix is symmetric: only tiles on and below the diagonal are computed, each is stored twice.
 #include "device_util.hpp"
 #include "internal.hpp"
+#include "pair16.hpp"
 
 #include <algorithm>
 
@@ -507,16 +508,11 @@ __global__ __launch_bounds__(256, 2) void hessian_split_kernel(HessArgs a)
 
 // ---------------------------------------------------------------- b > 1, many rows
 
-// The rotated rows X' are kept as the MFMA takes them.  A stage is 32 rows; its columns lie in blocks of sixteen, in which lane
-// (c, q) holds column c of rows 8 q .. 8 q + 7: the high halves of the 64 lanes, then the low ones.  A value y is
-// (h + l) / 2^(14 - e), e the exponent of the largest |y| of the block over a GROUP of four stages, h the nearest fp16 of y's
-// share and l that of what is left: y itself or, where the remainder's 13th bit is set, y but for 2^-23 of it, down to 2^-17
-// of the block's largest value (below, l has a fixed last place: 2^-39 of that value).  Sums are kept 2^14 times as large: up to 2^113.
-constexpr int kBlockBytes = 2048;   // sixteen columns of a stage
+// The rotated rows X' are kept as scaled pairs of halves (pair16.hpp), a scale for every block of sixteen columns and GROUP of four
+// stages.
 constexpr int kGroup = 4;           // stages that share their scales
 
-// The scale of a thread's block from the largest value of every thread: its exponent e, biased, 14 at least (2^(14 - e) and
-// 2^(e - 7) are normal numbers then, also where e says infinity).
+// the exponent of a thread's block from the largest value of every thread
 __device__ __forceinline__ uint32_t block_exponent(float top, float (*red)[8])
 {
     const int tid = threadIdx.x, piece = tid & 7;
@@ -524,31 +520,24 @@ __device__ __forceinline__ uint32_t block_exponent(float top, float (*red)[8])
     for (int s = 8; s < 64; s <<= 1) top = fmaxf(top, __shfl_xor(top, s));
     if ((tid & 63) < 8) red[tid >> 6][piece] = top;
     __syncthreads();
-    top = fmaxf(fmaxf(red[0][piece], red[1][piece]), fmaxf(red[2][piece], red[3][piece]));
-    return max(__float_as_uint(top) >> 23, 14u);
+    return pair_exponent(fmaxf(fmaxf(red[0][piece], red[1][piece]), fmaxf(red[2][piece], red[3][piece])));
 }
-__device__ __forceinline__ float block_scale(uint32_t e) { return __uint_as_float((e - 7u) << 23); }
 
 // a thread's sixteen values into the stage at dst, its blocks `pitch` bytes apart
 __device__ __forceinline__ void put_row(const float (&v)[16], uint32_t e, char* dst, int pitch)
 {
     const int r = threadIdx.x >> 3, piece = threadIdx.x & 7;
-    const float up = __uint_as_float((268u - e) << 23);
+    const float up = pair_up(e);
     _Float16* out = reinterpret_cast<_Float16*>(dst + piece * pitch) + (r >> 3) * 128 + (r & 7);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const float y = v[i] * up;
-        const _Float16 h = (_Float16)y;
-        out[i * 8] = h;
-        out[i * 8 + 512] = (_Float16)(y - (float)h);
-    }
+    for (int i = 0; i < 16; ++i) pair_split(v[i], up, out[i * 8], out[i * 8 + 512]);
 }
 
 // the stages that the workspace holds; a workgroup writes a group of them, 128 columns wide.  Bound: HBM, 2 bytes a value read
 // and 4 written.
 __global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
 {
-    constexpr int kPad = kBlockBytes + 16;   // (a row's eight pieces write to different banks)
+    constexpr int kPad = kPairBytes + 16;   // (a row's eight pieces write to different banks)
     __shared__ __attribute__((aligned(16))) char S[8 * kPad];
     __shared__ float red[4][8];
     const int tid = threadIdx.x, c0 = blockIdx.y * kT, blocks = min(kT, a.K - c0) / 16;
@@ -561,14 +550,14 @@ __global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
         for (int i = 0; i < 16; ++i) top = fabs_max(top, v[g][i]);
     }
     const uint32_t e = block_exponent(top, red);
-    if (tid < blocks) a.scales[(int64_t)blockIdx.x * (a.K / 16) + c0 / 16 + tid] = block_scale(e);
+    if (tid < blocks) a.scales[(int64_t)blockIdx.x * (a.K / 16) + c0 / 16 + tid] = pair_scale(e);
 #pragma unroll
     for (int g = 0; g < kGroup; ++g) {
         if (g >= count) break;
         put_row(v[g], e, S, kPad);
         __syncthreads();
         uint4* const dst = reinterpret_cast<uint4*>(a.planes + (int64_t)(s0 + g) * 128 * a.K + c0 * 128);
-        for (int i = tid; i < blocks * (kBlockBytes / 16); i += 256)
+        for (int i = tid; i < blocks * (kPairBytes / 16); i += 256)
             dst[i] = *reinterpret_cast<const uint4*>(S + (i >> 7) * kPad + (i & 127) * 16);
         __syncthreads();
     }
@@ -582,8 +571,8 @@ __device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0
 #pragma unroll
     for (int i = 0; i < 16; ++i) top = fabs_max(top, v[i]);
     const uint32_t e = block_exponent(top, red);
-    if (threadIdx.x < 8) scale[threadIdx.x] = block_scale(e);
-    put_row(v, e, dst, kBlockBytes);
+    if (threadIdx.x < 8) scale[threadIdx.x] = pair_scale(e);
+    put_row(v, e, dst, kPairBytes);
 }
 
 // 16 x 16 sums in the MFMA's output order -- a lane holds columns col .. col + 3 of a row -- stored with their mirror image; of a
@@ -605,16 +594,11 @@ __device__ __forceinline__ void store_block(const HessArgs& a, int row, int col,
     }
 }
 
-// of the column's and the row's two parts: the products that count, small ones first (low times low is 2^-23 of the whole)
-__device__ constexpr int kParts[3][2] = {{1, 0}, {0, 1}, {0, 0}};
-
 // A tile of 128 x 128, a 64 x 64 quarter per wave, a stage at a time, copied into LDS as it lies in the workspace, the next one
-// meanwhile.  The three products of 32 rows are summed from zero in the MFMA (which cuts off what an addition leaves over), four
-// such sums in t, and those, with the scales of their blocks, in acc.  The column operand is the MFMA's A, so that a lane
-// owns four neighbouring columns of a row of H.  Two workgroups per compute unit, so that one's barrier and LDS reads run under the
+// meanwhile.  Two workgroups per compute unit, so that one's barrier and LDS reads run under the
 // other's MFMAs.  Bound at K = 4096, 512 tiles over 8192 rows, 375 us: without the copies into LDS 305, at the 1.6 PFLOP/s of a large
 // bf16 product 257.  (Operands of the next stage read into registers ahead of its barrier: 3 % slower.)
-constexpr int kTile = 4, kTileStage = 16 * kBlockBytes, kTileLds = 2 * (kTileStage + 1024) + 128;   // 16-wide blocks per wave side; stages and their scales, red
+constexpr int kTile = 4, kTileStage = 16 * kPairBytes, kTileLds = 2 * (kTileStage + 1024) + 128;   // 16-wide blocks per wave side; stages and their scales, red
 __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
 {
     constexpr int NT = kTile, STAGE = kTileStage;
@@ -643,59 +627,13 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
         for (int i = 0; i < 8; ++i) {
             const int c = wave * 8 + i;                      // 1 KB: half a block
             const int block = (c < 16 ? r0 : c0) / 16 + (c & 15) / 2;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(St + slot * STAGE + c * 1024), 16, lane * 16, min(block, kb - 1) * kBlockBytes + (c & 1) * 1024, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(St + slot * STAGE + c * 1024), 16, lane * 16, min(block, kb - 1) * kPairBytes + (c & 1) * 1024, 0, 0);
         }
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_void*)(Sc + (slot * 4 + wave) * 64), 4, scale_at, 0, 0, 0);
     };
-    v4f acc[NT][NT], t[NT][NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    // rows, cols: the wave's first block of either operand
-    auto multiply = [&](const char* rows, const char* cols) {
-        auto block = [&](const char* s, int i, int part) { return *(reinterpret_cast<const v8h*>(s + i * kBlockBytes + part * 1024) + lane); };
-        v8h u[2][NT], next[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) next[k] = block(rows, 0, k);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) u[k][j] = block(cols, j, k);
-        v4f sum[2][NT];
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const v8h e[2] = {next[0], next[1]};
-            if (i + 1 < NT) {
-#pragma unroll
-                for (int k = 0; k < 2; ++k) next[k] = block(rows, i + 1, k);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            // (the sums of the row block before are added up between the products of this one)
-#pragma unroll
-            for (int s = 0; s < 3; ++s)
-#pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    v4f& d = sum[i & 1][j];
-                    d = __builtin_amdgcn_mfma_f32_16x16x32_f16(u[kParts[s][0]][j], e[kParts[s][1]], s ? d : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    if (i && s == 0) t[i - 1][j] += sum[(i - 1) & 1][j];
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-        }
-#pragma unroll
-        for (int j = 0; j < NT; ++j) t[NT - 1][j] += sum[(NT - 1) & 1][j];
-    };
-    auto scale_sums = [&](const float* rows, const float* cols) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const float f = rows[i] * cols[j];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][j][v] = fmaf(t[i][j][v], f, acc[i][j][v]);
-                t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-            }
-    };
+    PairSums<NT> sums;
+    sums.clear();
+    auto scale_sums = [&](const float* rows, const float* cols) { sums.scale([&](int i) { return rows[i]; }, [&](int j) { return cols[j]; }); };
     if (stages > 0) {
         issue(0);
         for (int s = 0; s < stages; ++s) {
@@ -704,7 +642,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
             block_barrier();   // stage s has landed, stage s - 1 has been read
             issue(s + 1);
             const char* base = St + (s & 1) * STAGE;
-            multiply(base + wr * kBlockBytes, base + (8 + wc) * kBlockBytes);
+            sums.multiply(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
             if ((s + 1) % kGroup == 0 || s + 1 == stages) {
                 const float* sc = Sc + ((s & 1) * 4 + wave) * 64;
                 scale_sums(sc + wr, sc + 8 + wc);
@@ -716,9 +654,9 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
         __syncthreads();
         build_stage(a, row, r0, St, Sc, red);
         __syncthreads();
-        build_stage(a, row, c0, St + 8 * kBlockBytes, Sc + 8, red);
+        build_stage(a, row, c0, St + 8 * kPairBytes, Sc + 8, red);
         __syncthreads();
-        multiply(St + wr * kBlockBytes, St + (8 + wc) * kBlockBytes);
+        sums.multiply(St + wr * kPairBytes, St + (8 + wc) * kPairBytes);
         scale_sums(Sc + wr, Sc + 8 + wc);
     }
 #pragma unroll
@@ -726,7 +664,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
             if (!diag || wr + i >= wc + j)
-                store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, acc[i][j] * a.out_scale);
+                store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, sums.acc[i][j] * a.out_scale);
 }
 
 // A tile of 32 x 32, for what is left beyond whole rounds of the tiles above: each of the four waves takes a quarter of the groups for
@@ -734,7 +672,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
 __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
 {
     constexpr int NT = 2, SUB = kT / 32;
-    __shared__ __attribute__((aligned(16))) char St[16 * kBlockBytes];   // the stages rotated on the spot, then the waves' sums
+    __shared__ __attribute__((aligned(16))) char St[16 * kPairBytes];   // the stages rotated on the spot, then the waves' sums
     __shared__ float Sc[16], red[4][8];
     static_assert(sizeof(St) >= 4 * NT * NT * 64 * sizeof(v4f), "the sums fit");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
@@ -761,8 +699,8 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                r[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(r0 / 16 + i, kb - 1) * kBlockBytes + k * 1024, 0));
-                c[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(c0 / 16 + i, kb - 1) * kBlockBytes + k * 1024, 0));
+                r[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(r0 / 16 + i, kb - 1) * kPairBytes + k * 1024, 0));
+                c[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(c0 / 16 + i, kb - 1) * kPairBytes + k * 1024, 0));
             }
     };
     auto multiply = [&](const v8h (&r)[2][NT], const v8h (&c)[2][NT]) {
@@ -773,7 +711,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
             for (int i = 0; i < NT; ++i)
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
-                    sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(c[kParts[s][0]][j], r[kParts[s][1]][i], s ? sum[i][j] : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(c[kPairParts[s][0]][j], r[kPairParts[s][1]][i], s ? sum[i][j] : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -812,7 +750,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
         __syncthreads();
         build_stage(a, row, r0 & ~(kT - 1), St, Sc, red);
         __syncthreads();
-        build_stage(a, row, c0 & ~(kT - 1), St + 8 * kBlockBytes, Sc + 8, red);
+        build_stage(a, row, c0 & ~(kT - 1), St + 8 * kPairBytes, Sc + 8, red);
         __syncthreads();
         if (wave != (int)((row - (int64_t)a.stages * 32) / 32 & 3)) continue;
         const int br = (r0 & (kT - 1)) / 16, bc = 8 + (c0 & (kT - 1)) / 16;
@@ -823,8 +761,8 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
             fc[i] = Sc[bc + i];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                rows[0][k][i] = *(reinterpret_cast<const v8h*>(St + (br + i) * kBlockBytes + k * 1024) + lane);
-                cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (bc + i) * kBlockBytes + k * 1024) + lane);
+                rows[0][k][i] = *(reinterpret_cast<const v8h*>(St + (br + i) * kPairBytes + k * 1024) + lane);
+                cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (bc + i) * kPairBytes + k * 1024) + lane);
             }
         }
         multiply(rows[0], cols[0]);
@@ -870,7 +808,7 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
         a.stages = (int)(T * 16 / 513);
         a.planes = static_cast<char*>(workspace);
         a.scales = reinterpret_cast<float*>(a.planes + (int64_t)a.stages * 128 * K);
-        a.out_scale = 0x1p-14f / (float)b;
+        a.out_scale = kPairResult / (float)b;
         hipLaunchKernelGGL(hessian_pack_kernel, dim3((unsigned)((a.stages + kGroup - 1) / kGroup), (unsigned)a.nt), dim3(256), 0, st, a);
         // parts of 32 x 32 where the tiles beyond whole rounds are few.  8192 rows, those left whole / in parts, us: K = 4096 (16 left)
         // 592 / 436, 1024 (36) 251 / 90, 1664 (91) 250 / 178, 2048 (136) 252 / 229, 2304 (171) 257 / 283, 3328 (351) 345 / 601

@@ -1,0 +1,103 @@
+// Products of binary32 matrices on the fp16 MFMA: a value is a scaled pair of halves, a product three MFMAs.  Shared by the Hessian
+// product and the GPTQ sweep's update.
+#pragma once
+
+#include "device_util.hpp"
+
+namespace fp4mr {
+
+// An operand lies in stages of 32 along the contraction; the other index goes in blocks of sixteen, in which lane (c, q) holds
+// element c at 8 q .. 8 q + 7 of the contraction: the high halves of the 64 lanes, then the low ones.
+constexpr int kPairBytes = 2048;
+
+// A value y is (h + l) / 2^(14 - e), e an exponent that some neighbourhood shares and in which |y| < 2^(e + 1): h the nearest fp16
+// of y's share, l that of what is left -- y itself or, where the remainder's 13th bit is set, y but for 2^-23 of it, down to
+// 2^(e - 17) (below, l has a fixed last place: 2^(e - 39)).  Sums of products carry 2^14 more than the scales of both sides take out, so
+// that scales and sums stay normal numbers as long as results are between 2^-112 and 2^113.
+// Exponents are biased, 14 at least: 2^(14 - e) and 2^(e - 7) are normal numbers then, also where e says infinity.
+__device__ __forceinline__ uint32_t pair_exponent(float largest) { return max(__float_as_uint(largest) >> 23, 14u); }
+__device__ __forceinline__ float pair_up(uint32_t e) { return __uint_as_float((268u - e) << 23); }
+__device__ __forceinline__ float pair_scale(uint32_t e) { return __uint_as_float((e - 7u) << 23); }
+constexpr float kPairResult = 0x1p-14f;
+
+__device__ __forceinline__ void pair_split(float y, float up, _Float16& h, _Float16& l)
+{
+    const float s = y * up;
+    h = (_Float16)s;
+    l = (_Float16)(s - (float)h);
+}
+
+// of the column's and the row's two parts: the products that count, small ones first (low times low is 2^-23 of the whole)
+__device__ constexpr int kPairParts[3][2] = {{1, 0}, {0, 1}, {0, 0}};
+
+// A wave's 16 NT x 16 NT sums.  The three products of 32 terms are summed from zero in the MFMA (which cuts off what an addition
+// leaves over), a few such sums in t, and those, with their scales, in acc.  The column operand is the MFMA's A, so that a
+// lane owns four neighbouring columns of a row.
+template <int NT>
+struct PairSums {
+    v4f acc[NT][NT], t[NT][NT];
+
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+
+    // one stage; rows, cols: the wave's first block of either operand in LDS
+    __device__ __forceinline__ void multiply(const char* rows, const char* cols)
+    {
+        const int lane = threadIdx.x & 63;
+        auto block = [&](const char* s, int i, int part) { return *(reinterpret_cast<const v8h*>(s + i * kPairBytes + part * 1024) + lane); };
+        v8h u[2][NT], next[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) next[k] = block(rows, 0, k);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) u[k][j] = block(cols, j, k);
+        v4f sum[2][NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const v8h e[2] = {next[0], next[1]};
+            if (i + 1 < NT) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) next[k] = block(rows, i + 1, k);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // (the sums of the row block before are added up between the products of this one)
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    v4f& d = sum[i & 1][j];
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_f16(u[kPairParts[s][0]][j], e[kPairParts[s][1]], s ? d : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    if (i && s == 0) t[i - 1][j] += sum[(i - 1) & 1][j];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) t[NT - 1][j] += sum[(NT - 1) & 1][j];
+    }
+
+    // t, times the scales of row block i and column block j, onto acc
+    template <typename Row, typename Col>
+    __device__ __forceinline__ void scale(Row row, Col col)
+    {
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const auto f = row(i) * col(j);   // (one factor, or one for each of the four columns)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if constexpr (sizeof(f) == sizeof(float)) acc[i][j][v] = fmaf(t[i][j][v], f, acc[i][j][v]);
+                    else acc[i][j][v] = fmaf(t[i][j][v], f[v], acc[i][j][v]);
+                }
+                t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            }
+    }
+};
+
+}  // namespace fp4mr
