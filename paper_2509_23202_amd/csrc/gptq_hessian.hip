@@ -667,14 +667,16 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
                 store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, sums.acc[i][j] * a.out_scale);
 }
 
-// A tile of 32 x 32, for what is left beyond whole rounds of the tiles above: each of the four waves takes a quarter of the groups for
-// itself, straight from memory to registers a group ahead, no barrier; then their sums are added.
+// A tile of 16 NT x 16 NT, for what is left beyond whole rounds of the tiles above: each of the four waves takes a quarter of the
+// groups for itself, straight from memory to registers, no barrier; then their sums are added.  32 x 32: a group ahead.  64 x 64, half the
+// bytes per product: a register is refilled behind its last use, and two workgroups per compute unit cover for each other.
+template <int NT>
 __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
 {
-    constexpr int NT = 2, SUB = kT / 32;
+    constexpr int SIDE = 16 * NT, SUB = kT / SIDE;
     __shared__ __attribute__((aligned(16))) char St[16 * kPairBytes];   // the stages rotated on the spot, then the waves' sums
     __shared__ float Sc[16], red[4][8];
-    static_assert(sizeof(St) >= 4 * NT * NT * 64 * sizeof(v4f), "the sums fit");
+    static_assert(sizeof(St) >= 4 * 2 * NT * 64 * sizeof(v4f), "two rows of blocks of the sums fit");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
     const int p = xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3);
@@ -682,68 +684,79 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
     tile_of(a.full + p / (SUB * SUB), a.nt, ti, tj);
     ti = SUB * ti + p / SUB % SUB;
     tj = SUB * tj + p % SUB;
-    if (tj > ti || ti * 32 >= a.K) return;
-    const int r0 = ti * 32, c0 = tj * 32, kb = a.K / 16;
+    if (tj > ti || ti * SIDE >= a.K) return;
+    const int r0 = ti * SIDE, c0 = tj * SIDE, kb = a.K / 16;
     const int groups = (a.stages + kGroup - 1) / kGroup, share = (groups + 3) / 4;
     const int g_begin = wave * share, g_end = min(groups, g_begin + share);
 
-    v4f acc[NT][NT], t[NT][NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    v8h rows[kGroup][2][NT], cols[kGroup][2][NT];   // (blocks past the end: the last one again, for outputs that are not stored)
-    auto fetch = [&](int s, v8h (&r)[2][NT], v8h (&c)[2][NT]) {
+    // (the same for all lanes, written by the launch before: scalar loads)
+    const auto scales = reinterpret_cast<const __attribute__((address_space(4))) float*>(reinterpret_cast<uintptr_t>(a.scales));
+    PairSums<NT> sums;
+    sums.clear();
+    constexpr int AHEAD = NT == 2 ? kGroup : 1;
+    v8h rows[AHEAD][2][NT], cols[AHEAD][2][NT];   // (blocks past the end: the last one again, for outputs that are not stored)
+    auto fetch = [&](int s, int k, int block) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(a.planes + (int64_t)min(s, a.stages - 1) * 128 * a.K, 0, 128 * a.K, 0x00020000);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int i = 0; i < NT; ++i) {
-                r[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(r0 / 16 + i, kb - 1) * kPairBytes + k * 1024, 0));
-                c[k][i] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(c0 / 16 + i, kb - 1) * kPairBytes + k * 1024, 0));
-            }
+        return __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, min(block, kb - 1) * kPairBytes + k * 1024, 0));
     };
-    auto multiply = [&](const v8h (&r)[2][NT], const v8h (&c)[2][NT]) {
-        v4f sum[NT][NT];
+    auto fetch_row = [&](int s, int d, int k, int i) { rows[d][k][i] = fetch(s, k, r0 / 16 + i); };
+    auto fetch_col = [&](int s, int d, int k, int j) { cols[d][k][j] = fetch(s, k, c0 / 16 + j); };
+    // one stage, from registers d; next >= 0: that stage takes their place
+    auto multiply = [&](int d, int next) {
+        v4f sum[2][NT];
 #pragma unroll
-        for (int s = 0; s < 3; ++s)
+        for (int i = 0; i < NT; ++i) {
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+            for (int s = 0; s < 3; ++s)
 #pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(c[kPairParts[s][0]][j], r[kPairParts[s][1]][i], s ? sum[i][j] : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                for (int j = 0; j < NT; ++j) {
+                    v4f& x = sum[i & 1][j];
+                    x = __builtin_amdgcn_mfma_f32_16x16x32_f16(cols[d][kPairParts[s][0]][j], rows[d][kPairParts[s][1]][i], s ? x : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    if (i && s == 0) sums.t[i - 1][j] += sum[(i - 1) & 1][j];
+                    if (i + 1 == NT && s != 1 && next >= 0) fetch_col(next, d, kPairParts[s][0], j);
+                }
+            if (next >= 0) {
 #pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) t[i][j] += sum[i][j];
-    };
-    auto scale_sums = [&](const float (&r)[NT], const float (&c)[NT]) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const float f = r[i] * c[j];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][j][v] = fmaf(t[i][j][v], f, acc[i][j][v]);
-                t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+                for (int k = 0; k < 2; ++k) fetch_row(next, d, k, i);
             }
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) sums.t[NT - 1][j] += sum[(NT - 1) & 1][j];
     };
     if (g_begin < g_end) {
 #pragma unroll
-        for (int d = 0; d < kGroup; ++d) fetch(g_begin * kGroup + d, rows[d], cols[d]);
+        for (int d = 0; d < AHEAD; ++d)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int i = 0; i < NT; ++i) {
+                    fetch_row(g_begin * kGroup + d, d, k, i);
+                    fetch_col(g_begin * kGroup + d, d, k, i);
+                }
         for (int g = g_begin; g < g_end; ++g) {
             float fr[NT], fc[NT];
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                fr[i] = a.scales[(int64_t)g * kb + min(r0 / 16 + i, kb - 1)];
-                fc[i] = a.scales[(int64_t)g * kb + min(c0 / 16 + i, kb - 1)];
+                fr[i] = scales[(int64_t)g * kb + min(r0 / 16 + i, kb - 1)];
+                fc[i] = scales[(int64_t)g * kb + min(c0 / 16 + i, kb - 1)];
             }
+            if constexpr (AHEAD == kGroup) {
 #pragma unroll
-            for (int d = 0; d < kGroup; ++d) {
-                if (g * kGroup + d < a.stages) multiply(rows[d], cols[d]);
-                fetch((g + 1) * kGroup + d, rows[d], cols[d]);
+                for (int d = 0; d < kGroup; ++d) {
+                    if (g * kGroup + d < a.stages) multiply(d, -1);
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+#pragma unroll
+                        for (int i = 0; i < NT; ++i) {
+                            fetch_row((g + 1) * kGroup + d, d, k, i);
+                            fetch_col((g + 1) * kGroup + d, d, k, i);
+                        }
+                }
+            } else {
+                const int end = min(kGroup, a.stages - g * kGroup);
+                for (int d = 0; d < end; ++d) multiply(0, g * kGroup + d + 1);
             }
-            scale_sums(fr, fc);
+            sums.scale([&](int i) { return fr[i]; }, [&](int j) { return fc[j]; });
         }
     }
     for (int64_t row = (int64_t)a.stages * 32; row < a.T; row += 32) {
@@ -754,32 +767,33 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
         __syncthreads();
         if (wave != (int)((row - (int64_t)a.stages * 32) / 32 & 3)) continue;
         const int br = (r0 & (kT - 1)) / 16, bc = 8 + (c0 & (kT - 1)) / 16;
-        float fr[NT], fc[NT];
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            fr[i] = Sc[br + i];
-            fc[i] = Sc[bc + i];
+        for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 rows[0][k][i] = *(reinterpret_cast<const v8h*>(St + (br + i) * kPairBytes + k * 1024) + lane);
                 cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (bc + i) * kPairBytes + k * 1024) + lane);
             }
-        }
-        multiply(rows[0], cols[0]);
-        scale_sums(fr, fc);
+        multiply(0, -1);
+        sums.scale([&](int i) { return Sc[br + i]; }, [&](int j) { return Sc[bc + j]; });
     }
-    v4f* const sums = reinterpret_cast<v4f*>(St);
-    __syncthreads();
+    v4f* const all = reinterpret_cast<v4f*>(St);   // [wave][two rows of blocks][lane]
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int half = 0; half < NT; half += 2) {
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < NT; ++j) sums[(wave * NT * NT + i * NT + j) * 64 + lane] = acc[i][j];
-    __syncthreads();
-    const int i = wave / NT, j = wave % NT;   // one 16 x 16 block per wave
-    v4f s = sums[wave * 64 + lane];
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int w = 1; w < 4; ++w) s += sums[(w * NT * NT + wave) * 64 + lane];
-    if (ti != tj || i >= j) store_block(a, r0 + i * 16 + l16, c0 + j * 16 + 4 * q, ti == tj && i == j, s * a.out_scale);
+            for (int j = 0; j < NT; ++j) all[(wave * 2 * NT + i * NT + j) * 64 + lane] = sums.acc[half + i][j];
+        __syncthreads();
+        for (int block = wave; block < 2 * NT; block += 4) {
+            const int i = half + block / NT, j = block % NT;
+            v4f s = all[block * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) s += all[(w * 2 * NT + block) * 64 + lane];
+            if (ti != tj || i >= j) store_block(a, r0 + i * 16 + l16, c0 + j * 16 + 4 * q, ti == tj && i == j, s * a.out_scale);
+        }
+    }
 }
 
 }  // namespace
@@ -799,20 +813,22 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
     // two workgroups per compute unit work at a time; the tiles beyond whole rounds of those would run on a mostly idle chip for a
     // whole tile's time (K = 4096: 528 tiles for 512 slots)
     const int tiles = a.nt * (a.nt + 1) / 2, slots = 2 * compute_units(), rem = tiles % slots;
-    // Two 22-bit halves on the fp16 MFMA from 1408 rows, or from 768 if there are enough tiles to fill the chip: fewer products, but
-    // one launch more and 32 rows or more rotated on the spot.  The other way against this one, us: T = 768, K = 2048 / 3328 / 4096
-    // 49 / 94 / 113 against 58 / 71 / 90; T = 1024, K = 1024 / 2048 / 4096 30 / 60 / 139 against 36 / 64 / 101; T = 1500, K = 1024 / 2048
-    // 42 / 85 against 41 / 80.  Below 768 rows its error is the larger one (T = 512 up to 1.06, 256 up to 1.26 times).
-    if (b > 1 && (T >= 1408 || (T >= 768 && tiles > slots / 3))) {
+    // Two 22-bit halves on the fp16 MFMA from 1408 rows, or from fewer if there are tiles enough: fewer products, but one launch more and
+    // 32 rows or more rotated on the spot.  The other way against this one, us: T = 768, K = 2048 / 3328 / 4096 49 / 94 / 113 against
+    // 56 / 71 / 90; T = 1024, K = 1280 / 1664 / 2304 36 / 52 / 62 against 35 / 40 / 64; T = 1200, K = 1024 / 1280 / 1664 37 / 44 / 63 against
+    // 38 / 40 / 45; T = 1500, K = 512 / 1024 28 / 42 against 23 / 40.  Below 768 rows its error is the larger one (T = 512 up to 1.06, 256 up
+    // to 1.26 times).
+    if (b > 1 && (T >= 1408 || (T >= 1100 && tiles > 50) || (T >= 768 && tiles > slots / 3))) {
         // (a stage takes 128 K bytes and K / 4 for its scales; what the 4 T K bytes do not hold is rotated on the spot)
         a.stages = (int)(T * 16 / 513);
         a.planes = static_cast<char*>(workspace);
         a.scales = reinterpret_cast<float*>(a.planes + (int64_t)a.stages * 128 * K);
         a.out_scale = kPairResult / (float)b;
         hipLaunchKernelGGL(hessian_pack_kernel, dim3((unsigned)((a.stages + kGroup - 1) / kGroup), (unsigned)a.nt), dim3(256), 0, st, a);
-        // parts of 32 x 32 where the tiles beyond whole rounds are few.  8192 rows, those left whole / in parts, us: K = 4096 (16 left)
-        // 592 / 436, 1024 (36) 251 / 90, 1664 (91) 250 / 178, 2048 (136) 252 / 229, 2304 (171) 257 / 283, 3328 (351) 345 / 601
-        const int small = rem > slots * 9 / 32 ? 0 : rem;
+        // The tiles beyond whole rounds, up to one per compute unit, in parts of 64 x 64, or of 32 x 32 if those leave most of the chip
+        // idle.  8192 rows, left whole / in 64 / in 32, us: K = 512 (10 left) 248 / 96 / 44, 768 (21) - / 94 / 66, 1024 (36) 243 / 93 / 93,
+        // 1664 (91) 251 / 127 / 179, 2048 (136) 253 / 202 / 234, 2560 (210) 259 / 250 / 356, 3072 (300) 328 / 332 / 490, 4096 (16) 590 / 483 / 443
+        const int small = rem > slots / 2 ? 0 : rem;
         a.full = tiles - small;
         if (a.full) {
             static LdsAttrOnce once;
@@ -820,7 +836,8 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(hessian_tile_kernel, dim3((unsigned)a.full), dim3(256), kTileLds, st, a);
         }
-        if (small) hipLaunchKernelGGL(hessian_part_kernel, dim3((unsigned)(16 * small)), dim3(256), 0, st, a);
+        if (small > slots / 16) hipLaunchKernelGGL(hessian_part_kernel<4>, dim3((unsigned)(4 * small)), dim3(256), 0, st, a);
+        else if (small) hipLaunchKernelGGL(hessian_part_kernel<2>, dim3((unsigned)(16 * small)), dim3(256), 0, st, a);
         return hipGetLastError();
     }
     if (b > 1) {

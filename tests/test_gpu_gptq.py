@@ -373,10 +373,10 @@ def test_hessian_of_rows_with_a_common_component_in_a_block(fp4, oracle, kind, T
         assert np.array_equal(got, got.T)
 
 
-@pytest.mark.parametrize("T,K,b", [(1408, 144, 16), (1409, 1744, 16), (1540, 256, 128), (800, 2416, 16), (1475, 4112, 16)])
+@pytest.mark.parametrize("T,K,b", [(1408, 144, 16), (1409, 1744, 16), (1540, 256, 128), (800, 2416, 16), (1475, 4112, 16), (1130, 1264, 16), (1700, 912, 16)])
 def test_hessian_of_many_rows_at_the_edges_of_stages_and_groups(fp4, oracle, T, K, b):
     """Rows kept as two scaled fp16 halves: row counts around whole stages of 32 and groups of four, and the rows behind them that
-    are rotated on the spot (33 to 63 of them); tiles of 32, of 128, and both; rows whose sizes differ by up to 2^40, so that the scales of
+    are rotated on the spot (33 to 63 of them); tiles of 32, of 64, of 128, and two of them; rows whose sizes differ by up to 2^40, so that the scales of
     neighbouring groups do.  Bound relative to sqrt(h_ii h_jj) >= sum |x_i x_j|: both halves 2^-23 of either value, sums of 32 rows
     cut off at 2^-23, four of those added, then T / 128 of the groups' sums, each rounded to 2^-24; and 2 x 4 roundings of the rotated
     values on either side of the oracle's, of partial sums not larger than four times the value in the root mean square."""
