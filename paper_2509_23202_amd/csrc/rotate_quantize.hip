@@ -40,6 +40,14 @@ constexpr int kAmaxPassBlocks = 1024;  // grid cap of the NVFP4 abs-max pass and
 // 1500: 0.4 - 0.9 us); at 4000 partials the sixty loads per lane cost more than the launch (M = 1000 12.4 -> 12.9, M = 2048
 // 17 -> 21).  Nothing between was timed.
 constexpr int kFoldedPartials = 1536;
+// NVFP4 tensors up to which every workgroup of the quantize pass finds the tensor's abs-max for itself, with kOwnThreads threads, instead
+// of an abs-max pass before it.  Bound by the launch; then by one compute unit taking in the whole tensor, 1.8 us per 65536 values
+// (twice that for b >= 64, whose butterflies cross lanes).  Separate pass -> own, GEMM order, us: b = 16, M = 1, K = 4096 5.8 -> 4.3,
+// M = 4, K = 4096 6.1 -> 4.7, M = 4, K = 14336 6.3 -> 5.9, M = 16, K = 4096 6.35 -> 6.2, beyond M = 24, K = 4096 6.4 -> 7.7; b = 128,
+// M = 1, K = 4096 6.2 -> 4.9, M = 16, K = 1024 6.5 -> 5.8, beyond M = 24, K = 1024 6.55 -> 6.6, M = 4, K = 8192 6.4 -> 7.2.  Canonical order
+// and the scale search gain as much.
+constexpr int64_t kOwnMaxElements = 1 << 16, kOwnMaxElementsWide = 1 << 14;   // (wide: b >= 64)
+constexpr int kOwnThreads = 1024;
 constexpr int kFitRounds = 3;          // alternations of the tensor-scale fit
 constexpr int kRangePassBlocks = 512;  // grid cap of the range pre-pass (two partials per wave: the same 4096 slots)
 
@@ -95,6 +103,7 @@ struct RqArgs {
     uint32_t* amax_bits;   // NVFP4 dynamic: bit pattern of max |y| over the tensor (workspace)
     uint32_t* amax_partial;  // NVFP4 dynamic: one partial maximum per wave of the abs-max pass (workspace); range pass: max and min per wave
     int n_partials;          // > 0: the quantize pass reduces that many partials itself (small calls: no finalize launch)
+    int own_max;             // every workgroup of the quantize pass finds the abs-max for itself (few tokens: no abs-max pass)
     double* fit_partial;     // tensor-scale fit: per wave of the fit pass, sum x v and sum v v (workspace)
     int64_t rows, K;
     int64_t n_items;
@@ -223,6 +232,55 @@ __device__ __forceinline__ void build_dense_operand(v8bf (&hop)[BP / 16][BP / 32
     }
 }
 
+// NVFP4 tensor scale from the whole tensor, by one workgroup: the abs-max pass's arithmetic (32-wide operand, butterfly levels
+// above), so that the maximum is the same to the last bit.  Two runs of 64 vectors are in flight per wave.
+__device__ __forceinline__ float own_tensor_scale(const RqArgs& a)
+{
+    constexpr int WAVES = kOwnThreads / kWave, RUN = 64, AHEAD = 2;
+    __shared__ float red[WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane & 15, q = lane >> 4;
+    v8bf hop[2][1];
+    build_hadamard_operand<32>(hop, g, q, a.b < 32 ? a.b : 32);
+    const int kron = a.b > 32 ? (a.b == 64 ? 1 : 2) : 0;
+    const uint16_t* __restrict__ x = static_cast<const uint16_t*>(a.x);
+    const int total = (int)(a.rows * a.K), runs = (total + 32 * RUN - 1) / (32 * RUN);   // (the last vector may be half a one)
+    float top = 0.0f;
+    for (int r0 = wave; r0 < runs; r0 += AHEAD * WAVES) {
+        v4i in[AHEAD][4];
+#pragma unroll
+        for (int d = 0; d < AHEAD; ++d)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int at = (((r0 + d * WAVES) * RUN + u * 16 + g) << 5) + 8 * q;
+                const v4i zero = {0, 0, 0, 0};
+                in[d][u] = at + 8 <= total ? *reinterpret_cast<const v4i*>(x + at) : zero;
+            }
+#pragma unroll
+        for (int d = 0; d < AHEAD; ++d)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                v4f acc[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hop[t][0], __builtin_bit_cast(v8bf, in[d][u]), v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                kronecker_levels<2>(acc, g, kron);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) top = fabs_max(top, acc[t][v]);
+            }
+    }
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) top = fmaxf(top, __shfl_xor(top, m));
+    if (lane == 0) red[wave] = top;
+    __syncthreads();
+    top = red[lane % WAVES];
+#pragma unroll
+    for (int m = 1; m < WAVES; m <<= 1) top = fmaxf(top, __shfl_xor(top, m));
+    return __fdiv_rn(__fmaf_rn(top, a.c_hi, top * a.c_lo), 2688.0f);   // (monotone: max|y| = y(max|h|))
+}
+
 // ------------------------------------------------------------------------------------------------------
 // MFMA rotation kernel.  BP = b' in {32,64,128}; G = 32 (MXFP4) or 16 (NVFP4); LAYOUT 0 canonical / 1 GEMM;
 // PASS 0 = quantize, 1 = tensor abs-max only (NVFP4 pre-pass), 2 = sums of the tensor-scale fit, 3 = largest and smallest
@@ -231,8 +289,11 @@ __device__ __forceinline__ void build_dense_operand(v8bf (&hop)[BP / 16][BP / 32
 // Work item = FR * (128/BP) supertiles = FR * 2048 elements.
 //   canonical: supertiles are consecutive runs of 16 vectors in flat (row-major) order;
 //   GEMM:      an item is FR fragments (16 rows x 128 K); supertile u covers K-offset u*BP of all 16 rows.
-template <int BP, int G, int LAYOUT, int PASS, bool HW, int FR, int POL>
-__global__ __launch_bounds__(kThreads) void rq_mfma_kernel(RqArgs a)
+//
+// OWN (NVFP4, few tokens, Hadamard): the workgroup has kOwnThreads threads, which first take the whole tensor's abs-max; its
+// first four waves then quantize an item each, as without.
+template <int BP, int G, int LAYOUT, int PASS, bool HW, int FR, int POL, bool OWN = false>
+__global__ __launch_bounds__(OWN ? kOwnThreads : kThreads) void rq_mfma_kernel(RqArgs a)
 {
     constexpr int S = BP / 32;           // K-steps of the contraction
     constexpr int T = BP / 16;           // output tiles
@@ -250,8 +311,13 @@ __global__ __launch_bounds__(kThreads) void rq_mfma_kernel(RqArgs a)
     const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerBlock;
 
+    float s_T = 0.0f;
+    if constexpr (OWN) {
+        s_T = own_tensor_scale(a);
+        if (threadIdx.x >= kThreads) return;
+    }
     v8bf hop[T][S];
-    if (a.rot) build_dense_operand<BP>(hop, g, q, a.b, a.rot, rq_dyn_lds);  // (uniform branch: every thread takes it)
+    if (!OWN && a.rot) build_dense_operand<BP>(hop, g, q, a.b, a.rot, rq_dyn_lds);  // (uniform branch: every thread takes it)
     else build_hadamard_operand<BP>(hop, g, q, a.b < BP ? a.b : BP);
     // Hadamard blocks wider than the operand: finished by butterfly levels across the lanes of a quad
     const int kron = (!a.rot && a.b > BP) ? (a.b == 2 * BP ? 1 : 2) : 0;
@@ -264,9 +330,8 @@ __global__ __launch_bounds__(kThreads) void rq_mfma_kernel(RqArgs a)
     const int64_t KS = (a.K + 511) >> 9;
     const uint16_t* __restrict__ x = static_cast<const uint16_t*>(a.x);
 
-    float s_T = 0.0f;
     if constexpr (G == 16 && PASS != 1) {
-        s_T = load_tensor_scale(a, (int)(threadIdx.x & 63));
+        if constexpr (!OWN) s_T = load_tensor_scale(a, (int)(threadIdx.x & 63));
         if (!a.static_scale && blockIdx.x == 0 && threadIdx.x == 0) *a.tensor_scale = s_T;
     }
     float hmax = 0.0f;
@@ -801,6 +866,12 @@ hipError_t launch_mfma(const RqArgs& a0, int grid_cap, hipStream_t st, int* bloc
     if (blocks > grid_cap) blocks = grid_cap;
     if (blocks < 1) blocks = 1;
     if (blocks_out) *blocks_out = (int)blocks;
+    if constexpr (PASS == 0 && G == 16 && BP == (LAYOUT ? 64 : 32)) {
+        if (a.own_max) {
+            hipLaunchKernelGGL((rq_mfma_kernel<BP, G, LAYOUT, PASS, HW, FR, POL, true>), dim3((unsigned)blocks), dim3(kOwnThreads), 0, st, a);
+            return hipGetLastError();
+        }
+    }
     const size_t lds = a.rot ? (size_t)kDenseLdsBytes<BP> : 0;  // staging of the transposed rotation matrix
     hipLaunchKernelGGL((rq_mfma_kernel<BP, G, LAYOUT, PASS, HW, FR, POL>), dim3((unsigned)blocks), dim3(kThreads), lds, st, a);
     return hipGetLastError();
@@ -883,7 +954,9 @@ hipError_t launch_rotate_quantize(const void* x, int64_t rows, int64_t K, int b,
     const int grid_cap = rot ? (b > 64 ? 256 * 2 : 256 * 8) : 1 << 20;
 
     hipError_t e;
-    if (fmt == 1 && !static_scale) {
+    if (fmt == 1 && !static_scale && policy <= 1 && !rot && b > 1 && rows <= (b <= 32 ? kOwnMaxElements : kOwnMaxElementsWide) / K) {
+        a.own_max = 1;
+    } else if (fmt == 1 && !static_scale) {
         // dynamic tensor scale: abs-max pass (one partial per wave) -> finalize -> quantize pass
         a.amax_partial = a.amax_bits + 64;
         const int pass_cap = kAmaxPassBlocks;

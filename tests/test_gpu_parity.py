@@ -157,6 +157,32 @@ def test_nvfp4_block16_tensor_ending_in_half_a_32_vector(fp4, oracle, M, K, stat
     assert np.array_equal(np_(s).reshape(M, -1), ref_s)
 
 
+@pytest.mark.parametrize("flags", [0, "gemm", "mse"])
+@pytest.mark.parametrize("M,K,b", [(1, 128, 128), (3, 48, 16), (7, 48, 16), (5, 1664, 64), (16, 4096, 16), (7, 2304, 64), (2, 32768, 32), (1, 16384, 128), (65, 1008, 16)])
+def test_nvfp4_tensor_scale_found_by_every_workgroup(fp4, oracle, M, K, b, flags):
+    """Small tensors take their abs-max in the quantize pass itself.  Against the separate pass, which the same rows take with
+    rows of zeros behind them (more than 65536 values): tensor scale, codes and scales the same bit for bit.  The largest value
+    comes last, where a tensor of an odd number of 16-blocks ends in half a vector; and a tensor of zeros."""
+    import torch
+    flags = {0: 0, "gemm": fp4.LAYOUT_GEMM, "mse": fp4.SCALE_MSE}[flags]
+    if flags & fp4.LAYOUT_GEMM and K % 128:
+        K = (K + 127) // 128 * 128
+        M = min(M, 65536 // K)
+    say(f"nvfp4 own tensor scale M={M} K={K} b={b} flags={flags}")
+    more = (65536 // K // 16 + 2) * 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * K + b)
+    x = torch.randn(M, K, device="cuda", generator=g)
+    x[-1, -1] = 300.0
+    for scale in (1.0, 0.0):
+        xs = (x * scale).bfloat16()
+        c, s, T = fp4.fp4_rotate_quantize(xs, b, NV, flags=flags)
+        rows = (M + 15) // 16 * 16 if flags & fp4.LAYOUT_GEMM else M
+        c2, s2, T2 = fp4.fp4_rotate_quantize(torch.cat([xs, xs.new_zeros(more, K)]), b, NV, flags=flags)
+        assert torch.equal(T, T2)
+        assert torch.equal(c[: rows * K // 2], c2[: rows * K // 2]) and torch.equal(s[: rows * K // 16], s2[: rows * K // 16])
+
+
 @pytest.mark.parametrize("fmt", [MX, NV])
 @pytest.mark.parametrize("b", [1, 16, 32, 64, 128])
 def test_gemm_layout_is_a_permutation_of_canonical(fp4, fmt, b):
