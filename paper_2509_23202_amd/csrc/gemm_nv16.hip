@@ -13,6 +13,8 @@
 //     re-converting them);
 //   * only W is converted inside the product, and a wave's tile is 128 rows of X by 64 (or 32) rows of W: four (two)
 //     half-fragment conversions per 64 (32) MFMAs.
+// A last row of tiles with at most 64 tokens multiplies four of the eight row-blocks (its copies stay as they are): 0.62 of a tile's time
+// (N = 28672, K = 4096, M = 192: 58 -> 48 us; N = 57344, K = 8192, M = 320 with the launch that suits it 282 -> 247).
 // Block tile 128 x 256 (or 128 x 128 for a remainder of the tile grid, or 128 x 512), four (eight) waves side by side along
 // N, K-step 64, three-stage LDS ring fed by direct-to-LDS loads, one barrier per K-step.  75 KB of LDS and 256 registers per
 // wave: two workgroups share a compute unit (or one of eight waves fills it).
@@ -30,6 +32,7 @@
 #include "nv_dequant.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace fp4mr {
 namespace {
@@ -43,6 +46,7 @@ struct Nv16Args {
     void* out;
     int64_t M, N, K;
     int tiles_m;
+    int half_row;  // 1: the last row of tiles holds at most 64 tokens, its tiles come last
     int n_first;   // first output column of this launch (a multiple of 256)
     int n_cols;    // number of output columns this launch covers (to the end of N when the tile grid is ragged)
     int split_steps;  // split-K launches: K-steps of 64 per split (a multiple of 8); blockIdx.y is the split, out the fp32 partials
@@ -93,7 +97,10 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int tm = blockIdx.x % g.tiles_m, tn = blockIdx.x / g.tiles_m;   // consecutive workgroups share a W column band
+    // consecutive workgroups share a W column band; the tiles of a last row of at most 64 tokens, which are shorter, come behind all others
+    const int whole = g.tiles_m - g.half_row, whole_tiles = (int)gridDim.x / g.tiles_m * whole;
+    const bool half = (int)blockIdx.x >= whole_tiles;
+    const int tm = half ? whole : (int)blockIdx.x % whole, tn = half ? (int)blockIdx.x - whole_tiles : (int)blockIdx.x / whole;
     const int64_t n_tile0 = (int64_t)g.n_first + (int64_t)tn * BN;
 
     const int KH_all = (int)(g.K >> 6), KC = (int)(g.K >> 7);   // K-steps of 64 / fragments of 128 per row-block in memory
@@ -228,47 +235,54 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     // lgkmcnt(0): nothing is pending where the loop is entered, so that the waits inside count its own reads only (with an
     // order of its own on the way in, the compiler waits for everything at the head of every step)
     __builtin_amdgcn_s_waitcnt(0xc07f);
-    for (int kh = 0; kh < KH; ++kh) {
-        const int kn = kh + STAGES - 1, kl = min(kn, KH - 1);
-        char* const fill = smem + (kn % STAGES) * STAGE_BYTES;
-        const char* const next = smem + ((kh + 1) % STAGES) * STAGE_BYTES;
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < TN; ++i) {
-            const bool last = i + 1 == TN;
-            if (last) {
-                // stage kh + 1 has landed (this wave's copies: vmcnt; everybody's: barrier); the barrier also says that every
-                // wave holds stage kh in registers, so that its slot may be refilled
-                wait_vmcnt<(STAGES - 2) * OPS>();
-                block_barrier();
-#pragma unroll
-                for (int v = 0; v < TN; ++v) wraw[v] = read_w(next, v);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            v2h s2 = {0, 0};
-            if (!last) s2 = scale2(wraw[i + 1]);
-            const v8h a0 = operand(wcur, 0), a1 = operand(wcur, 1);
-#pragma unroll
-            for (int t = 0; t < 2 * TM; ++t) {
-                const int j = t % TM, s = t / TM;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(s == 0 ? a0 : a1, xf[j][s], acc[i][j], 0, 0, 0);
-                if (!last) {
-                    if (t < 8) micro(wraw[i + 1], s2, wnext, t);
-                } else {
-                    read_x(next, j, s);
-                    if (t == 2 * TM - 9) s2 = scale2(wraw[0]);
-                    if (t >= 2 * TM - 8) micro(wraw[0], s2, wnext, t - (2 * TM - 8));
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // the refill of the slot everybody left at the barrier of the step before, in pieces behind the first column-tiles
-            if (i == 0) issue_x(kl, fill);
-            if (i == (TN == 2 ? 0 : 1)) issue_wc(kl, fill);
-            if (i == (TN == 2 ? 0 : 2)) issue_ws(kl, fill);
+    // RM: 16-row blocks that are multiplied, eight or -- the tile holds at most 64 tokens -- the first four
+    auto steps = [&](auto rm) {
+        constexpr int RM = decltype(rm)::value;
+        for (int kh = 0; kh < KH; ++kh) {
+            const int kn = kh + STAGES - 1, kl = min(kn, KH - 1);
+            char* const fill = smem + (kn % STAGES) * STAGE_BYTES;
+            const char* const next = smem + ((kh + 1) % STAGES) * STAGE_BYTES;
             __builtin_amdgcn_sched_barrier(0);
-            wcur = wnext;
+    #pragma unroll
+            for (int i = 0; i < TN; ++i) {
+                const bool last = i + 1 == TN;
+                if (last) {
+                    // stage kh + 1 has landed (this wave's copies: vmcnt; everybody's: barrier); the barrier also says that every
+                    // wave holds stage kh in registers, so that its slot may be refilled
+                    wait_vmcnt<(STAGES - 2) * OPS>();
+                    block_barrier();
+    #pragma unroll
+                    for (int v = 0; v < TN; ++v) wraw[v] = read_w(next, v);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                v2h s2 = {0, 0};
+                if (!last) s2 = scale2(wraw[i + 1]);
+                if (last && RM == 4) s2 = scale2(wraw[0]);
+                const v8h a0 = operand(wcur, 0), a1 = operand(wcur, 1);
+    #pragma unroll
+                for (int t = 0; t < 2 * RM; ++t) {
+                    const int j = t % RM, s = t / RM;
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(s == 0 ? a0 : a1, xf[j][s], acc[i][j], 0, 0, 0);
+                    if (!last) {
+                        if (t < 8) micro(wraw[i + 1], s2, wnext, t);
+                    } else {
+                        read_x(next, j, s);
+                        if (t == 2 * RM - 9) s2 = scale2(wraw[0]);
+                        if (t >= 2 * RM - 8) micro(wraw[0], s2, wnext, t - (2 * RM - 8));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                // the refill of the slot everybody left at the barrier of the step before, in pieces behind the first column-tiles
+                if (i == 0) issue_x(kl, fill);
+                if (i == (TN == 2 ? 0 : 1)) issue_wc(kl, fill);
+                if (i == (TN == 2 ? 0 : 2)) issue_ws(kl, fill);
+                __builtin_amdgcn_sched_barrier(0);
+                wcur = wnext;
+            }
         }
-    }
+    };
+    if (half) steps(std::integral_constant<int, 4>{});
+    else steps(std::integral_constant<int, TM>{});
     wait_vmcnt<0>();   // (the repeated copies of the last steps: nothing may be in flight into LDS when the workgroup ends)
 
     // A lane owns out[m][n .. n+3] with m = m0 + 16 j + lane % 16, n = n0 + 16 i + 4 (lane / 16).
@@ -382,12 +396,19 @@ int device_cus()
 }
 
 template <int NW, int TN, int STAGES>
-hipError_t launch_tiles(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1)
+hipError_t launch_tiles(const Nv16Args& g0, bool out_f32, hipStream_t st, int splits = 1)
 {
+    Nv16Args g = g0;
     constexpr int BN = NW * TN * 16;
     constexpr size_t lds = STAGES * (size_t)(8 * 2048 + (BN / 16) * 512 + NW * 256);
     if (g.n_cols <= 0) return hipSuccess;
     const int tiles_n = (g.n_cols + BN - 1) / BN;
+    if (g.half_row) {
+        // Half tiles go last where that evens out the launch's end or gives every compute unit one whole tile at most.  Else the launch takes
+        // the time of whole tiles, and all of them in turn leave an XCD its rows of X (K = 2048, N = 12288, M = 960: 58 us, halves last 61.5).
+        const int64_t all = (int64_t)g.tiles_m * tiles_n * splits, cus = device_cus();
+        g.half_row = all > 2 * cus || (all > cus && all - (int64_t)tiles_n * splits <= cus) ? 1 : 0;
+    }
     if (splits > 1) {
         static LdsAttrOnce raised_s;
         auto k = gemm_nv16_kernel<NW, TN, true, STAGES, true>;
@@ -423,8 +444,25 @@ hipError_t launch_tiles(const Nv16Args& g, bool out_f32, hipStream_t st, int spl
 hipError_t launch_wide(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1)
 {
     const int64_t rows = (int64_t)g.tiles_m * splits, cus = device_cus();
-    if (g.K >= 6656 && rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st, splits);
+    // (a compute unit that gets one whole tile and one of half the rows is done sooner as a pair: M = 192, N = 57344, K = 8192 163 -> 153 us)
+    const bool pairs = splits == 1 && g.half_row && (g.tiles_m - 1) * (int64_t)((g.n_cols + 255) / 256) <= cus;
+    if (!pairs && g.K >= 6656 && rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st, splits);
     return launch_tiles<4, 4, 3>(g, out_f32, st, splits);
+}
+
+// Estimated time of a launch, microseconds per K-step: `whole` tiles and behind them `half` ones (of at most 64 tokens), wide or narrow.
+// A tile's step takes `alone` on a compute unit of its own, `shared` beside another, 0.62 of that with half the rows.
+double nv16_tiles_cost(int64_t whole, int64_t half, bool narrow, int64_t cus)
+{
+    const double alone = narrow ? 0.58 : 0.93, shared = 1.47 * alone, part = 0.62;
+    const int64_t slots = 2 * cus, left = whole % slots;
+    const double t = (double)(whole / slots) * shared;
+    auto last = [&](int64_t n, double f) { return n == 0 ? 0.0 : f * (n <= cus ? alone : shared); };
+    if (left == 0) return t + (double)(half / slots) * part * shared + last(half % slots, part);
+    if (left + half <= cus) return t + alone;
+    if (left <= cus && left + half <= slots) return t + 0.5 * (alone + shared);
+    // halves run on the slots that whole tiles leave, and behind all of them what does not fit there
+    return t + shared + ((double)half * part > (double)(slots - left) ? part * alone : 0.0);
 }
 
 hipError_t launch_narrow(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1) { return launch_tiles<4, 2, 3>(g, out_f32, st, splits); }
@@ -471,6 +509,7 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     g.N = N;
     g.K = K;
     g.tiles_m = (int)((M + 127) / 128);
+    g.half_row = (M - 1) % 128 < 64 ? 1 : 0;
     const int cus = device_cus();
     if (partial) {
         // few tiles, long K: every tile's K range shared by several workgroups, partial results added by a second kernel
@@ -498,8 +537,13 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     if (full_cols > 0 && full_cols < cols_w) {
         const int64_t narrow = (rest_cols + 127) / 128 * g.tiles_m;
         // time in units of a wide tile: ceil-rounds of wide tiles, against whole rounds + narrow tiles at half a unit each
-        const double t_wide = (double)((tiles_w + slots - 1) / slots);
-        const double t_split = (double)(full_cols * g.tiles_m / slots) + 0.5 * (double)((narrow + slots - 1) / slots);
+        double t_wide = (double)((tiles_w + slots - 1) / slots);
+        double t_split = (double)(full_cols * g.tiles_m / slots) + 0.5 * (double)((narrow + slots - 1) / slots);
+        if (g.half_row) {
+            const int64_t whole = g.tiles_m - 1, cols_n = (rest_cols + 127) / 128, all_n = (N + 127) / 128;
+            t_wide = std::min(nv16_tiles_cost(whole * cols_w, cols_w, false, cus), nv16_tiles_cost(whole * all_n, all_n, true, cus));
+            t_split = nv16_tiles_cost(whole * full_cols, full_cols, false, cus) + nv16_tiles_cost(whole * cols_n, cols_n, true, cus) + 10.0 / (double)(K >> 6);
+        }
         if (t_split < t_wide) {
             g.n_first = 0;
             g.n_cols = (int)(full_cols * 256);
@@ -511,6 +555,14 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     }
     g.n_first = 0;
     g.n_cols = (int)N;
+    // With a last row of half tiles, which are handed out last and even out the end of the launch, one launch is the better one unless the
+    // narrow tiles of the second fill what the wide ones leave (K, N, M: whole rounds first -> one launch, us: 8192, 57344, 320
+    // 259 -> 247; 8192, 57344, 560 430 -> 416; 4096, 28672, 1080 224 -> 207; 28672, 8192, 1080 narrow 494, wide 466).
+    if (g.half_row) {
+        const int64_t cols_n = (N + 127) / 128, whole_rows = g.tiles_m - 1;
+        const bool narrow = nv16_tiles_cost(whole_rows * cols_n, cols_n, true, cus) < nv16_tiles_cost(whole_rows * cols_w, cols_w, false, cus);
+        return narrow ? launch_narrow(g, out_f32, st) : launch_wide(g, out_f32, st);
+    }
     // less than a round and a quarter of wide tiles (one per compute unit and a few doubled up, or compute units left
     // idle): 128 x 128 tiles spread the same work twice as finely (N = 10240, K = 8192 at M = 512: 136 -> 119 us;
     // N = 8192, K = 28672 at M = 512 without the split-K workspace: 412 -> 280 us)

@@ -274,6 +274,25 @@ def test_gemm_nvfp4_every_tile_variant(fp4, oracle, variant, out_f32, knobs):
     _gemm_case(fp4, oracle, NV, 272, 528, 1280, seed=30 + variant, out_f32=out_f32, layout_gemm=True)
 
 
+@pytest.mark.parametrize("M,N,K", [(129, 8200, 512), (192, 57344, 6656), (320, 28672, 1024), (577, 10248, 384), (1088, 8192, 512), (2100, 10240, 512), (449, 12288, 2048)])
+def test_gemm_nvfp4_last_row_of_tiles_with_at_most_64_tokens(fp4, M, N, K):
+    """Those tiles multiply half their rows, and the launch is chosen with them in mind.  Every output is one sum along K in the same
+    order whatever the tile, so the result equals that of the same rows with rows of zeros up to whole tiles, bit for bit."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N)
+    x = torch.randn(M, K, device="cuda", generator=g).bfloat16()
+    qw = fp4.fp4_quantize_weights(torch.randn(N, K, device="cuda", generator=g).bfloat16(), 16, NV, flags=fp4.LAYOUT_GEMM)
+    say(f"nvfp4 half tiles M={M} N={N} K={K}")
+    out = []
+    for rows in (M, (M + 127) // 128 * 128):
+        qx = fp4.fp4_rotate_quantize(torch.cat([x, x.new_zeros(rows - M, K)]), 16, NV, flags=fp4.LAYOUT_GEMM)
+        room = torch.empty(fp4.workspace_bytes(fp4.OP_GEMM, rows, N, K, NV, fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM), dtype=torch.uint8, device="cuda")
+        out.append(fp4.fp4_gemm(*qx, *qw, rows, N, K, NV, flags=fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM, workspace=room))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1][:M])
+
+
 @pytest.mark.parametrize("variant", [2, 5, 10, 13, 15, 17, 18])
 def test_gemm_mxfp4_tile_variants_bf16_output_through_the_staged_epilogue(fp4, oracle, variant, knobs):
     """bf16 output goes through the LDS transpose of the epilogue, whose chunk swizzle depends on the wave tile's width
