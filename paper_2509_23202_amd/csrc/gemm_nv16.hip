@@ -407,7 +407,8 @@ hipError_t launch_tiles(const Nv16Args& g0, bool out_f32, hipStream_t st, int sp
         // Half tiles go last where that evens out the launch's end or gives every compute unit one whole tile at most.  Else the launch takes
         // the time of whole tiles, and all of them in turn leave an XCD its rows of X (K = 2048, N = 12288, M = 960: 58 us, halves last 61.5).
         const int64_t all = (int64_t)g.tiles_m * tiles_n * splits, cus = device_cus();
-        g.half_row = all > 2 * cus || (all > cus && all - (int64_t)tiles_n * splits <= cus) ? 1 : 0;
+        // Split launches gain from K = 4096 on (M = 320: N = 8192, K = 28672 148 -> 142 us, N = 6144, K = 4096 37 -> 33); below, as often lose.
+        g.half_row = (splits > 1 && g.K >= 4096) || all > 2 * cus || (all > cus && all - (int64_t)tiles_n * splits <= cus) ? 1 : 0;
     }
     if (splits > 1) {
         static LdsAttrOnce raised_s;
