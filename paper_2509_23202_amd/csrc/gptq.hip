@@ -33,9 +33,9 @@ struct GptqArgs {
     uint8_t* q;             // [N,K] scratch: one code per byte, visiting order
     // scratch, the operands of an outer block's update as scaled pairs of halves (pair16.hpp), 16 stages along the contraction:
     char* e_pairs;          // errors, [stage][16 rows]
-    float* e_scales;        // [kOuter / kB][rows]: of a row's errors of 64 columns
+    int* e_scales;          // [kOuter / kB][rows]: their exponents: of a row's errors of 64 columns
     char* u_pairs;          // rows of U, [stage][16 columns]
-    float* u_scales;        // [kOuter / kB][K]: of a column's entries in 64 rows
+    int* u_scales;          // [kOuter / kB][K]: of a column's entries in 64 rows
     int Np;                 // N rounded up to 16
     const uint8_t* scales;  // [N,K/G] canonical
     const float* s_T;       // NVFP4 tensor scale (device), else null
@@ -166,7 +166,7 @@ __device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb)
     top = fmaxf(top, __shfl_xor(top, 32));
     const uint32_t e = pair_exponent(top);
     const float up = pair_up(e);
-    if (q == 0) a.u_scales[wave * a.K + cb * 16 + l16] = pair_scale(e);
+    if (q == 0) a.u_scales[wave * a.K + cb * 16 + l16] = (int)e;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         v8h h, l;
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
                 char* dst = a.e_pairs + pairs_at(2 * b + (part >> 3), a.Np / 16, blockIdx.x) + (((part & 7) >> 1) * 16 + row) * 16 + (part & 1) * 8;
                 *reinterpret_cast<v4h*>(dst) = h;
                 *reinterpret_cast<v4h*>(dst + 1024) = l;
-                if (part == 0) a.e_scales[b * a.Np + n] = pair_scale(ex);
+                if (part == 0) a.e_scales[b * a.Np + n] = (int)ex;
             }
             lds_barrier();
         }
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
 {
     constexpr int T = 128, NT = 4;
     extern __shared__ __attribute__((aligned(1024))) char St[];
-    float* const Sc = reinterpret_cast<float*>(St + 2 * kUpdateStage);   // for two groups of 64 terms: of 128 rows, of 128 columns
+    int* const Sc = reinterpret_cast<int*>(St + 2 * kUpdateStage);   // exponents for two groups of 64 terms: of 128 rows, of 128 columns
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int wr = (wave >> 1) * NT, wc = (wave & 1) * NT;   // first block of rows / columns of the wave's quarter
     // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of tiles, which share rows
@@ -484,8 +484,8 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
         const char* base = St + (s & 1) * kUpdateStage;
         sums.multiply(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
         if (s & 1) {
-            const float* sc = Sc + (s / 2 & 1) * 256;
-            sums.scale([&](int i) { return sc[(wr + i) * 16 + l16]; }, [&](int j) { return *reinterpret_cast<const v4f*>(sc + 128 + (wc + j) * 16 + 4 * q); });
+            const int* sc = Sc + (s / 2 & 1) * 256;
+            sums.scale([&](int i) { return sc[(wr + i) * 16 + l16] - kPairBias; }, [&](int j) { return *reinterpret_cast<const v4i*>(sc + 128 + (wc + j) * 16 + 4 * q); });
         }
     }
     // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 tile (K is a multiple of 64)
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
         for (int j = 0; j < NT; ++j) {
             if (c0 + (wc + j) * 16 >= a.K) continue;
             v4f* d = reinterpret_cast<v4f*>(dst + 16 * j);
-            *d = *d - sums.acc[i][j] * kPairResult;
+            *d = *d - sums.acc[i][j];
         }
     }
 }
@@ -553,9 +553,9 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     ws += (size_t)a.Np * kOuter * 4;
     a.u_pairs = ws;
     ws += (size_t)K * kOuter * 4;
-    a.e_scales = reinterpret_cast<float*>(ws);
+    a.e_scales = reinterpret_cast<int*>(ws);
     ws += (size_t)a.Np * (kOuter / kB) * 4;
-    a.u_scales = reinterpret_cast<float*>(ws);
+    a.u_scales = reinterpret_cast<int*>(ws);
     ws += (size_t)K * (kOuter / kB) * 4;
     a.iperm = reinterpret_cast<int*>(ws);
     a.scales = static_cast<const uint8_t*>(scales);

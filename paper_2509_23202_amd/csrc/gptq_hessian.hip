@@ -39,7 +39,7 @@ struct HessArgs {
     float* H;           // [K, K]
     float* xr;          // b > 1, few rows: the rotated rows, packed (packed_at)
     char* planes;       // b > 1, many rows: the stages of 32 rotated rows (see there), one behind the other ...
-    float* scales;      // ... and the scales of their blocks, [group of stages][K / 16]
+    int* scales;        // ... and the exponents of their blocks, [group of stages][K / 16]
     int stages;         // of them (the rows behind are rotated by every workgroup for itself)
     float* part;        // b == 1: partial tiles of the split tail
     int64_t T;
@@ -48,7 +48,8 @@ struct HessArgs {
     int full;           // tiles 0 .. full - 1 take all of T in one workgroup ...
     int parts;          // ... each of the others is shared by this many
     int chunk;          // rows of X per part (multiple of kRows)
-    float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b (many rows: what is left of the blocks' scales and 1 / b)
+    float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b (few rows)
+    int bias;           // b > 1, many rows: what a product's exponent is less than those of its two blocks, 1 / b included
 };
 
 // p-th tile of the lower triangle (row >= col), counted super-row by super-row
@@ -550,7 +551,7 @@ __global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
         for (int i = 0; i < 16; ++i) top = fabs_max(top, v[g][i]);
     }
     const uint32_t e = block_exponent(top, red);
-    if (tid < blocks) a.scales[(int64_t)blockIdx.x * (a.K / 16) + c0 / 16 + tid] = pair_scale(e);
+    if (tid < blocks) a.scales[(int64_t)blockIdx.x * (a.K / 16) + c0 / 16 + tid] = (int)e;
 #pragma unroll
     for (int g = 0; g < kGroup; ++g) {
         if (g >= count) break;
@@ -564,14 +565,14 @@ __global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
 }
 
 // the stage that begins with row t, of the 128 columns from c0, in LDS: for rows that the workspace has no room for
-__device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0, char* dst, float* scale, float (*red)[8])
+__device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0, char* dst, int* scale, float (*red)[8])
 {
     float v[16], top = 0.0f;
     rotate_row(a, t + (threadIdx.x >> 3), c0 + (threadIdx.x & 7) * 16, v);
 #pragma unroll
     for (int i = 0; i < 16; ++i) top = fabs_max(top, v[i]);
     const uint32_t e = block_exponent(top, red);
-    if (threadIdx.x < 8) scale[threadIdx.x] = pair_scale(e);
+    if (threadIdx.x < 8) scale[threadIdx.x] = (int)e;
     put_row(v, e, dst, kPairBytes);
 }
 
@@ -604,7 +605,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
     constexpr int NT = kTile, STAGE = kTileStage;
     // two stages; per stage and wave the scales of 8 row blocks and 8 column blocks (and filling); block_exponent's maxima
     extern __shared__ __attribute__((aligned(1024))) char St[];
-    float* const Sc = reinterpret_cast<float*>(St + 2 * STAGE);
+    int* const Sc = reinterpret_cast<int*>(St + 2 * STAGE);
     float(*const red)[8] = reinterpret_cast<float(*)[8]>(St + 2 * (STAGE + 1024));
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of the tiles
@@ -633,7 +634,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
     };
     PairSums<NT> sums;
     sums.clear();
-    auto scale_sums = [&](const float* rows, const float* cols) { sums.scale([&](int i) { return rows[i]; }, [&](int j) { return cols[j]; }); };
+    auto scale_sums = [&](const int* rows, const int* cols) { sums.scale([&](int i) { return rows[i] - a.bias; }, [&](int j) { return cols[j]; }); };
     if (stages > 0) {
         issue(0);
         for (int s = 0; s < stages; ++s) {
@@ -644,7 +645,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
             const char* base = St + (s & 1) * STAGE;
             sums.multiply(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
             if ((s + 1) % kGroup == 0 || s + 1 == stages) {
-                const float* sc = Sc + ((s & 1) * 4 + wave) * 64;
+                const int* sc = Sc + ((s & 1) * 4 + wave) * 64;
                 scale_sums(sc + wr, sc + 8 + wc);
             }
         }
@@ -664,7 +665,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
             if (!diag || wr + i >= wc + j)
-                store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, sums.acc[i][j] * a.out_scale);
+                store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, sums.acc[i][j]);
 }
 
 // A tile of 16 NT x 16 NT, for what is left beyond whole rounds of the tiles above: each of the four waves takes a quarter of the
@@ -675,7 +676,8 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
 {
     constexpr int SIDE = 16 * NT, SUB = kT / SIDE;
     __shared__ __attribute__((aligned(16))) char St[16 * kPairBytes];   // the stages rotated on the spot, then the waves' sums
-    __shared__ float Sc[16], red[4][8];
+    __shared__ int Sc[16];
+    __shared__ float red[4][8];
     static_assert(sizeof(St) >= 4 * 2 * NT * 64 * sizeof(v4f), "two rows of blocks of the sums fit");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
@@ -690,7 +692,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
     const int g_begin = wave * share, g_end = min(groups, g_begin + share);
 
     // (the same for all lanes, written by the launch before: scalar loads)
-    const auto scales = reinterpret_cast<const __attribute__((address_space(4))) float*>(reinterpret_cast<uintptr_t>(a.scales));
+    const auto scales = reinterpret_cast<const __attribute__((address_space(4))) int*>(reinterpret_cast<uintptr_t>(a.scales));
     PairSums<NT> sums;
     sums.clear();
     constexpr int AHEAD = NT == 2 ? kGroup : 1;
@@ -734,10 +736,10 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                     fetch_col(g_begin * kGroup + d, d, k, i);
                 }
         for (int g = g_begin; g < g_end; ++g) {
-            float fr[NT], fc[NT];
+            int fr[NT], fc[NT];
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                fr[i] = scales[(int64_t)g * kb + min(r0 / 16 + i, kb - 1)];
+                fr[i] = scales[(int64_t)g * kb + min(r0 / 16 + i, kb - 1)] - a.bias;
                 fc[i] = scales[(int64_t)g * kb + min(c0 / 16 + i, kb - 1)];
             }
             if constexpr (AHEAD == kGroup) {
@@ -775,7 +777,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                 cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (bc + i) * kPairBytes + k * 1024) + lane);
             }
         multiply(0, -1);
-        sums.scale([&](int i) { return Sc[br + i]; }, [&](int j) { return Sc[bc + j]; });
+        sums.scale([&](int i) { return Sc[br + i] - a.bias; }, [&](int j) { return Sc[bc + j]; });
     }
     v4f* const all = reinterpret_cast<v4f*>(St);   // [wave][two rows of blocks][lane]
 #pragma unroll
@@ -791,7 +793,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
             v4f s = all[block * 64 + lane];
 #pragma unroll
             for (int w = 1; w < 4; ++w) s += all[(w * 2 * NT + block) * 64 + lane];
-            if (ti != tj || i >= j) store_block(a, r0 + i * 16 + l16, c0 + j * 16 + 4 * q, ti == tj && i == j, s * a.out_scale);
+            if (ti != tj || i >= j) store_block(a, r0 + i * 16 + l16, c0 + j * 16 + 4 * q, ti == tj && i == j, s);
         }
     }
 }
@@ -822,8 +824,8 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
         // (a stage takes 128 K bytes and K / 4 for its scales; what the 4 T K bytes do not hold is rotated on the spot)
         a.stages = (int)(T * 16 / 513);
         a.planes = static_cast<char*>(workspace);
-        a.scales = reinterpret_cast<float*>(a.planes + (int64_t)a.stages * 128 * K);
-        a.out_scale = kPairResult / (float)b;
+        a.scales = reinterpret_cast<int*>(a.planes + (int64_t)a.stages * 128 * K);
+        a.bias = kPairBias + (b == 16 ? 4 : b == 32 ? 5 : b == 64 ? 6 : 7);
         hipLaunchKernelGGL(hessian_pack_kernel, dim3((unsigned)((a.stages + kGroup - 1) / kGroup), (unsigned)a.nt), dim3(256), 0, st, a);
         // The tiles beyond whole rounds, up to one per compute unit, in parts of 64 x 64, or of 32 x 32 if those leave most of the chip
         // idle.  8192 rows, left whole / in 64 / in 32, us: K = 512 (10 left) 248 / 96 / 44, 768 (21) - / 94 / 66, 1024 (36) 243 / 93 / 93,

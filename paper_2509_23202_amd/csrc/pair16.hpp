@@ -10,15 +10,14 @@ namespace fp4mr {
 // element c at 8 q .. 8 q + 7 of the contraction: the high halves of the 64 lanes, then the low ones.
 constexpr int kPairBytes = 2048;
 
-// A value y is (h + l) / 2^(14 - e), e an exponent that some neighbourhood shares and in which |y| < 2^(e + 1): h the nearest fp16
+// A value y is (h + l) 2^(e - 14), e an exponent that some neighbourhood shares and in which |y| < 2^(e + 1): h the nearest fp16
 // of y's share, l that of what is left -- y itself or, where the remainder's 13th bit is set, y but for 2^-23 of it, down to
-// 2^(e - 17) (below, l has a fixed last place: 2^(e - 39)).  Sums of products carry 2^14 more than the scales of both sides take out, so
-// that scales and sums stay normal numbers as long as results are between 2^-112 and 2^113.
-// Exponents are biased, 14 at least: 2^(14 - e) and 2^(e - 7) are normal numbers then, also where e says infinity.
+// 2^(e - 17) (below, l has a fixed last place: 2^(e - 39)).  Exponents are biased, 14 at least (2^(14 - e) is a normal number then,
+// also where e says infinity), and stay integers: sums of products take theirs up in one v_ldexp_f32, so that what binary32 can
+// hold comes out whatever the two sides' exponents are.
 __device__ __forceinline__ uint32_t pair_exponent(float largest) { return max(__float_as_uint(largest) >> 23, 14u); }
 __device__ __forceinline__ float pair_up(uint32_t e) { return __uint_as_float((268u - e) << 23); }
-__device__ __forceinline__ float pair_scale(uint32_t e) { return __uint_as_float((e - 7u) << 23); }
-constexpr float kPairResult = 0x1p-14f;
+constexpr int kPairBias = 2 * (127 + 14);   // the exponent of a product: both sides' together, less this
 
 __device__ __forceinline__ void pair_split(float y, float up, _Float16& h, _Float16& l)
 {
@@ -31,7 +30,7 @@ __device__ __forceinline__ void pair_split(float y, float up, _Float16& h, _Floa
 __device__ constexpr int kPairParts[3][2] = {{1, 0}, {0, 1}, {0, 0}};
 
 // A wave's 16 NT x 16 NT sums.  The three products of 32 terms are summed from zero in the MFMA (which cuts off what an addition
-// leaves over), a few such sums in t, and those, with their scales, in acc.  The column operand is the MFMA's A, so that a
+// leaves over), a few such sums in t, and those, with their exponents, in acc.  The column operand is the MFMA's A, so that a
 // lane owns four neighbouring columns of a row.
 template <int NT>
 struct PairSums {
@@ -81,7 +80,7 @@ struct PairSums {
         for (int j = 0; j < NT; ++j) t[NT - 1][j] += sum[(NT - 1) & 1][j];
     }
 
-    // t, times the scales of row block i and column block j, onto acc
+    // t onto acc, its exponent that of the row in row block i and of the four columns (or the block) in column block j together
     template <typename Row, typename Col>
     __device__ __forceinline__ void scale(Row row, Col col)
     {
@@ -89,11 +88,11 @@ struct PairSums {
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
-                const auto f = row(i) * col(j);   // (one factor, or one for each of the four columns)
+                const auto e = row(i) + col(j);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    if constexpr (sizeof(f) == sizeof(float)) acc[i][j][v] = fmaf(t[i][j][v], f, acc[i][j][v]);
-                    else acc[i][j][v] = fmaf(t[i][j][v], f[v], acc[i][j][v]);
+                    if constexpr (sizeof(e) == sizeof(int)) acc[i][j][v] += __builtin_amdgcn_ldexpf(t[i][j][v], e);
+                    else acc[i][j][v] += __builtin_amdgcn_ldexpf(t[i][j][v], e[v]);
                 }
                 t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
             }

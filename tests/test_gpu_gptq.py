@@ -396,6 +396,24 @@ def test_hessian_of_many_rows_at_the_edges_of_stages_and_groups(fp4, oracle, T, 
         assert np.array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("log2_size", [-56, 56])
+@pytest.mark.parametrize("T,K,b", [(1540, 256, 128), (1475, 4112, 16)])
+def test_hessian_of_many_very_small_and_large_rows(fp4, T, K, b, log2_size):
+    """Rows times 2^+-56: entries up to 2^123 and down to those of diagonals near 2^-102.  Every step is a power of two away from that of
+    the same rows without the factor, and nothing leaves the range of normal numbers (entries below 2^-126 aside: half of their last
+    place), so the entries are 2^+-112 times theirs."""
+    import torch
+    xb = inputs.f32_to_bf16_bits(np.random.default_rng(T).standard_normal((T, K)).astype(np.float32))
+    x = to_dev_bf16(xb)
+    say(f"gptq hessian T={T} K={K} b={b} times 2^{log2_size}")
+    H = fp4.fp4_gptq_accumulate_hessian(x, b)
+    big = fp4.fp4_gptq_accumulate_hessian((x * 2.0 ** log2_size).bfloat16(), b)
+    torch.cuda.synchronize()
+    H, big = np_(H).astype(np.float64), np_(big).astype(np.float64)
+    assert np.isfinite(big).all()
+    assert np.all(np.abs(big - np.ldexp(H, 2 * log2_size)) <= 2.0 ** -149)
+
+
 def test_calibration_rows_to_codes_entirely_on_the_gpu(fp4, oracle, gptq):
     import torch
     N, K, T, b = 64, 512, 1536, 32
@@ -421,19 +439,22 @@ def test_calibration_rows_to_codes_entirely_on_the_gpu(fp4, oracle, gptq):
     assert abs(e_got - e_ref) <= 1e-2 * e_ref and e_got < 0.8 * e_rtn
 
 
+@pytest.mark.parametrize("low,high", [(-20, 20), (-70, 120)])
 @pytest.mark.parametrize("N,K,b", [(40, 1088, 1), (17, 1600, 64)])
-def test_rows_of_any_size_do_not_disturb_each_other(fp4, oracle, gptq, N, K, b):
-    """Rows times powers of two up to 2^40 apart, one row zero: power-of-two scales follow, and the codes are the same -- every
+def test_rows_of_any_size_do_not_disturb_each_other(fp4, oracle, gptq, N, K, b, low, high):
+    """Rows times powers of two, up to 2^190 apart (running values and updates stay between 2^-126 and 2^127), one row zero: power-of-two
+    scales follow, and the codes are the same -- every
     step of the sweep is exact under such a factor, also the scaled pairs of halves that an outer block's errors leave in."""
     import torch
     rng = np.random.default_rng(N)
     w = rng.standard_normal((N, K)).astype(np.float32)
     w[N // 2] = 0.0
-    k = rng.integers(-20, 21, (N, 1))
+    k = rng.integers(low, high + 1, (N, 1))
+    k[0], k[-1] = low, high
     U = np.triu(rng.standard_normal((K, K)) * 0.02, 1) * 2.0 ** rng.integers(-16, 1, (1, K))   # (larger entries: the errors grow without bound)
     U[np.diag_indices(K)] = rng.uniform(0.5, 2.0, K)
     perm = rng.permutation(K).astype(np.int32)
-    say(f"gptq row scales N={N} K={K}")
+    say(f"gptq row scales N={N} K={K} 2^{low} .. 2^{high}")
     got = []
     for x in (w, np.ldexp(w, k).astype(np.float32)):
         c, s, _ = fp4.fp4_gptq_quantize_weights(to_dev_bf16(inputs.f32_to_bf16_bits(x)), b, MX, to_dev(U.astype(np.float32)), to_dev(perm))
