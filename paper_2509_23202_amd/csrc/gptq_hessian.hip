@@ -39,7 +39,7 @@ struct HessArgs {
     float* H;           // [K, K]
     float* xr;          // b > 1, few rows: the rotated rows, packed (packed_at)
     char* planes;       // b > 1, many rows: the stages of 32 rotated rows (see there), one behind the other ...
-    int* scales;        // ... and the exponents of their blocks, [group of stages][K / 16]
+    uint8_t* exps;      // ... and the exponents of their columns, [group of stages][K]
     int stages;         // of them (the rows behind are rotated by every workgroup for itself)
     float* part;        // b == 1: partial tiles of the split tail
     int64_t T;
@@ -49,7 +49,7 @@ struct HessArgs {
     int parts;          // ... each of the others is shared by this many
     int chunk;          // rows of X per part (multiple of kRows)
     float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b (few rows)
-    int bias;           // b > 1, many rows: what a product's exponent is less than those of its two blocks, 1 / b included
+    int bias;           // b > 1, many rows: what a product's exponent is less than those of its two columns, 1 / b included
 };
 
 // p-th tile of the lower triangle (row >= col), counted super-row by super-row
@@ -509,29 +509,53 @@ __global__ __launch_bounds__(256, 2) void hessian_split_kernel(HessArgs a)
 
 // ---------------------------------------------------------------- b > 1, many rows
 
-// The rotated rows X' are kept as scaled pairs of halves (pair16.hpp), a scale for every block of sixteen columns and GROUP of four
-// stages.
-constexpr int kGroup = 4;           // stages that share their scales
+// The rotated rows X' are kept as scaled pairs of halves (pair16.hpp), an exponent for every column and GROUP of four stages: what is
+// left out of a value is relative to the largest value of its own channel, however loud the channels beside it are.
+constexpr int kGroup = 4;           // stages that share their exponents
 
-// the exponent of a thread's block from the largest value of every thread
-__device__ __forceinline__ uint32_t block_exponent(float top, float (*red)[8])
+// The exponents, a byte each, of 128 columns from the largest values of every thread's sixteen.  The eight lanes of a wave that share
+// columns halve them among themselves step by step, then the four waves meet in LDS.
+__device__ __forceinline__ void column_exponents(const float (&top)[16], float (*red)[kT], uint8_t* exps)
 {
     const int tid = threadIdx.x, piece = tid & 7;
+    float m8[8], m4[4], m2[2];
+    const bool b3 = tid & 8, b4 = tid & 16, b5 = tid & 32;
 #pragma unroll
-    for (int s = 8; s < 64; s <<= 1) top = fmaxf(top, __shfl_xor(top, s));
-    if ((tid & 63) < 8) red[tid >> 6][piece] = top;
+    for (int i = 0; i < 8; ++i) m8[i] = fmaxf(b3 ? top[i + 8] : top[i], __shfl_xor(b3 ? top[i] : top[i + 8], 8));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m4[i] = fmaxf(b4 ? m8[i + 4] : m8[i], __shfl_xor(b4 ? m8[i] : m8[i + 4], 16));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) m2[i] = fmaxf(b5 ? m4[i + 2] : m4[i], __shfl_xor(b5 ? m4[i] : m4[i + 2], 32));
+    *reinterpret_cast<float2*>(&red[tid >> 6][piece * 16 + (b3 ? 8 : 0) + (b4 ? 4 : 0) + (b5 ? 2 : 0)]) = make_float2(m2[0], m2[1]);
     __syncthreads();
-    return pair_exponent(fmaxf(fmaxf(red[0][piece], red[1][piece]), fmaxf(red[2][piece], red[3][piece])));
+    if (tid < kT) exps[tid] = (uint8_t)pair_exponent(fmaxf(fmaxf(red[0][tid], red[1][tid]), fmaxf(red[2][tid], red[3][tid])));
+    __syncthreads();
+}
+
+// the factors of a thread's sixteen columns
+__device__ __forceinline__ void column_ups(const uint8_t* exps, float (&up)[16])
+{
+    const uint4 w = *reinterpret_cast<const uint4*>(exps + (threadIdx.x & 7) * 16);
+    const uint32_t e[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) up[i] = pair_up(e[i >> 2] >> 8 * (i & 3) & 255u);
+}
+
+// what a lane needs of the exponents of 128 rows and 128 columns at `exps`: of row l16 of a block, of columns 4 q .. 4 q + 3 of a block
+__device__ __forceinline__ int row_exponent(const uint8_t* exps, int block) { return exps[block * 16 + (threadIdx.x & 15)]; }
+__device__ __forceinline__ v4i four_exponents(uint32_t w) { return v4i{(int)(w & 255u), (int)(w >> 8 & 255u), (int)(w >> 16 & 255u), (int)(w >> 24)}; }
+__device__ __forceinline__ v4i col_exponents(const uint8_t* exps, int block)
+{
+    return four_exponents(*reinterpret_cast<const uint32_t*>(exps + block * 16 + 4 * (threadIdx.x >> 4 & 3)));
 }
 
 // a thread's sixteen values into the stage at dst, its blocks `pitch` bytes apart
-__device__ __forceinline__ void put_row(const float (&v)[16], uint32_t e, char* dst, int pitch)
+__device__ __forceinline__ void put_row(const float (&v)[16], const float (&up)[16], char* dst, int pitch)
 {
     const int r = threadIdx.x >> 3, piece = threadIdx.x & 7;
-    const float up = pair_up(e);
     _Float16* out = reinterpret_cast<_Float16*>(dst + piece * pitch) + (r >> 3) * 128 + (r & 7);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) pair_split(v[i], up, out[i * 8], out[i * 8 + 512]);
+    for (int i = 0; i < 16; ++i) pair_split(v[i], up[i], out[i * 8], out[i * 8 + 512]);
 }
 
 // the stages that the workspace holds; a workgroup writes a group of them, 128 columns wide.  Bound: HBM, 2 bytes a value read
@@ -540,22 +564,24 @@ __global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
 {
     constexpr int kPad = kPairBytes + 16;   // (a row's eight pieces write to different banks)
     __shared__ __attribute__((aligned(16))) char S[8 * kPad];
-    __shared__ float red[4][8];
+    __shared__ __attribute__((aligned(16))) float red[4][kT];
+    __shared__ __attribute__((aligned(16))) uint8_t exps[kT];
     const int tid = threadIdx.x, c0 = blockIdx.y * kT, blocks = min(kT, a.K - c0) / 16;
     const int s0 = blockIdx.x * kGroup, count = min(kGroup, a.stages - s0);
-    float v[kGroup][16], top = 0.0f;
+    float v[kGroup][16], top[16] = {}, up[16];
 #pragma unroll
     for (int g = 0; g < kGroup; ++g) {
         rotate_row(a, g < count ? (int64_t)(s0 + g) * 32 + (tid >> 3) : a.T, c0 + (tid & 7) * 16, v[g]);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) top = fabs_max(top, v[g][i]);
+        for (int i = 0; i < 16; ++i) top[i] = fabs_max(top[i], v[g][i]);
     }
-    const uint32_t e = block_exponent(top, red);
-    if (tid < blocks) a.scales[(int64_t)blockIdx.x * (a.K / 16) + c0 / 16 + tid] = (int)e;
+    column_exponents(top, red, exps);
+    column_ups(exps, up);
+    if (tid < blocks * 16) a.exps[(int64_t)blockIdx.x * a.K + c0 + tid] = exps[tid];
 #pragma unroll
     for (int g = 0; g < kGroup; ++g) {
         if (g >= count) break;
-        put_row(v[g], e, S, kPad);
+        put_row(v[g], up, S, kPad);
         __syncthreads();
         uint4* const dst = reinterpret_cast<uint4*>(a.planes + (int64_t)(s0 + g) * 128 * a.K + c0 * 128);
         for (int i = tid; i < blocks * (kPairBytes / 16); i += 256)
@@ -565,15 +591,15 @@ __global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
 }
 
 // the stage that begins with row t, of the 128 columns from c0, in LDS: for rows that the workspace has no room for
-__device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0, char* dst, int* scale, float (*red)[8])
+__device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0, char* dst, uint8_t* exps, float (*red)[kT])
 {
-    float v[16], top = 0.0f;
+    float v[16], top[16], up[16];
     rotate_row(a, t + (threadIdx.x >> 3), c0 + (threadIdx.x & 7) * 16, v);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) top = fabs_max(top, v[i]);
-    const uint32_t e = block_exponent(top, red);
-    if (threadIdx.x < 8) scale[threadIdx.x] = (int)e;
-    put_row(v, e, dst, kPairBytes);
+    for (int i = 0; i < 16; ++i) top[i] = fabsf(v[i]);
+    column_exponents(top, red, exps);
+    column_ups(exps, up);
+    put_row(v, up, dst, kPairBytes);
 }
 
 // 16 x 16 sums in the MFMA's output order -- a lane holds columns col .. col + 3 of a row -- stored with their mirror image; of a
@@ -599,14 +625,13 @@ __device__ __forceinline__ void store_block(const HessArgs& a, int row, int col,
 // meanwhile.  Two workgroups per compute unit, so that one's barrier and LDS reads run under the
 // other's MFMAs.  Bound at K = 4096, 512 tiles over 8192 rows, 375 us: without the copies into LDS 305, at the 1.6 PFLOP/s of a large
 // bf16 product 257.  (Operands of the next stage read into registers ahead of its barrier: 3 % slower.)
-constexpr int kTile = 4, kTileStage = 16 * kPairBytes, kTileLds = 2 * (kTileStage + 1024) + 128;   // 16-wide blocks per wave side; stages and their scales, red
+constexpr int kTile = 4, kTileStage = 16 * kPairBytes, kTileLds = 2 * (kTileStage + 1024);   // 16-wide blocks per wave side; stages and their exponents
 __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
 {
     constexpr int NT = kTile, STAGE = kTileStage;
-    // two stages; per stage and wave the scales of 8 row blocks and 8 column blocks (and filling); block_exponent's maxima
+    // two stages; per stage and wave the exponents of 128 rows and of 128 columns
     extern __shared__ __attribute__((aligned(1024))) char St[];
-    int* const Sc = reinterpret_cast<int*>(St + 2 * STAGE);
-    float(*const red)[8] = reinterpret_cast<float(*)[8]>(St + 2 * (STAGE + 1024));
+    uint8_t* const Sc = reinterpret_cast<uint8_t*>(St + 2 * STAGE);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of the tiles
     const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
@@ -619,22 +644,24 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
     // Blocks past the end are the last one again: they only feed outputs that are not stored.  Past the last stage the copies
     // repeat it into a slot that nobody reads any more.
     const int kb = a.K / 16, stages = a.stages;
-    const uint32_t scale_at = 4u * (uint32_t)min(((lane & 8) ? c0 : r0) / 16 + (lane & 7), kb - 1);
+    const uint32_t exps_at = (uint32_t)min((lane < 32 ? r0 : c0) + 4 * (lane & 31), a.K - 4);
     auto issue = [&](int s) {
         const int from = min(s, stages - 1), slot = s & 1;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(a.planes + (int64_t)from * 128 * a.K, 0, 128 * a.K, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(a.scales + (int64_t)(from / kGroup) * kb, 0, 4 * kb, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(a.exps + (int64_t)(from / kGroup) * a.K, 0, a.K, 0x00020000);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int c = wave * 8 + i;                      // 1 KB: half a block
             const int block = (c < 16 ? r0 : c0) / 16 + (c & 15) / 2;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(St + slot * STAGE + c * 1024), 16, lane * 16, min(block, kb - 1) * kPairBytes + (c & 1) * 1024, 0, 0);
         }
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_void*)(Sc + (slot * 4 + wave) * 64), 4, scale_at, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_void*)(Sc + (slot * 4 + wave) * 256), 4, exps_at, 0, 0, 0);
     };
     PairSums<NT> sums;
     sums.clear();
-    auto scale_sums = [&](const int* rows, const int* cols) { sums.scale([&](int i) { return rows[i] - a.bias; }, [&](int j) { return cols[j]; }); };
+    auto scale_sums = [&](const uint8_t* exps) {
+        sums.scale([&](int i) { return row_exponent(exps, wr + i) - a.bias; }, [&](int j) { return col_exponents(exps + kT, wc + j); });
+    };
     if (stages > 0) {
         issue(0);
         for (int s = 0; s < stages; ++s) {
@@ -645,20 +672,19 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
             const char* base = St + (s & 1) * STAGE;
             sums.multiply(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
             if ((s + 1) % kGroup == 0 || s + 1 == stages) {
-                const int* sc = Sc + ((s & 1) * 4 + wave) * 64;
-                scale_sums(sc + wr, sc + 8 + wc);
+                scale_sums(Sc + ((s & 1) * 4 + wave) * 256);
             }
         }
         wait_vmcnt<0>();
     }
+    float(*const red)[kT] = reinterpret_cast<float(*)[kT]>(St + STAGE);
     for (int64_t row = (int64_t)stages * 32; row < a.T; row += 32) {
         __syncthreads();
         build_stage(a, row, r0, St, Sc, red);
-        __syncthreads();
-        build_stage(a, row, c0, St + 8 * kPairBytes, Sc + 8, red);
+        build_stage(a, row, c0, St + 8 * kPairBytes, Sc + kT, red);
         __syncthreads();
         sums.multiply(St + wr * kPairBytes, St + (8 + wc) * kPairBytes);
-        scale_sums(Sc + wr, Sc + 8 + wc);
+        scale_sums(Sc);
     }
 #pragma unroll
     for (int i = 0; i < NT; ++i)
@@ -676,8 +702,8 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
 {
     constexpr int SIDE = 16 * NT, SUB = kT / SIDE;
     __shared__ __attribute__((aligned(16))) char St[16 * kPairBytes];   // the stages rotated on the spot, then the waves' sums
-    __shared__ int Sc[16];
-    __shared__ float red[4][8];
+    __shared__ __attribute__((aligned(16))) uint8_t Sc[2 * kT];
+    __shared__ __attribute__((aligned(16))) float red[4][kT];
     static_assert(sizeof(St) >= 4 * 2 * NT * 64 * sizeof(v4f), "two rows of blocks of the sums fit");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
@@ -691,8 +717,6 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
     const int groups = (a.stages + kGroup - 1) / kGroup, share = (groups + 3) / 4;
     const int g_begin = wave * share, g_end = min(groups, g_begin + share);
 
-    // (the same for all lanes, written by the launch before: scalar loads)
-    const auto scales = reinterpret_cast<const __attribute__((address_space(4))) int*>(reinterpret_cast<uintptr_t>(a.scales));
     PairSums<NT> sums;
     sums.clear();
     constexpr int AHEAD = NT == 2 ? kGroup : 1;
@@ -736,11 +760,13 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                     fetch_col(g_begin * kGroup + d, d, k, i);
                 }
         for (int g = g_begin; g < g_end; ++g) {
-            int fr[NT], fc[NT];
+            int fr[NT];
+            uint32_t fc[NT];
+            const uint8_t* const exps = a.exps + (int64_t)g * a.K;
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                fr[i] = scales[(int64_t)g * kb + min(r0 / 16 + i, kb - 1)] - a.bias;
-                fc[i] = scales[(int64_t)g * kb + min(c0 / 16 + i, kb - 1)];
+                fr[i] = exps[min(r0 / 16 + i, kb - 1) * 16 + l16];
+                fc[i] = *reinterpret_cast<const uint32_t*>(exps + min(c0 / 16 + i, kb - 1) * 16 + 4 * q);
             }
             if constexpr (AHEAD == kGroup) {
 #pragma unroll
@@ -758,26 +784,25 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                 const int end = min(kGroup, a.stages - g * kGroup);
                 for (int d = 0; d < end; ++d) multiply(0, g * kGroup + d + 1);
             }
-            sums.scale([&](int i) { return fr[i]; }, [&](int j) { return fc[j]; });
+            sums.scale([&](int i) { return fr[i] - a.bias; }, [&](int j) { return four_exponents(fc[j]); });
         }
     }
     for (int64_t row = (int64_t)a.stages * 32; row < a.T; row += 32) {
         __syncthreads();
         build_stage(a, row, r0 & ~(kT - 1), St, Sc, red);
-        __syncthreads();
-        build_stage(a, row, c0 & ~(kT - 1), St + 8 * kPairBytes, Sc + 8, red);
+        build_stage(a, row, c0 & ~(kT - 1), St + 8 * kPairBytes, Sc + kT, red);
         __syncthreads();
         if (wave != (int)((row - (int64_t)a.stages * 32) / 32 & 3)) continue;
-        const int br = (r0 & (kT - 1)) / 16, bc = 8 + (c0 & (kT - 1)) / 16;
+        const int br = (r0 & (kT - 1)) / 16, bc = (c0 & (kT - 1)) / 16;
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 rows[0][k][i] = *(reinterpret_cast<const v8h*>(St + (br + i) * kPairBytes + k * 1024) + lane);
-                cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (bc + i) * kPairBytes + k * 1024) + lane);
+                cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (8 + bc + i) * kPairBytes + k * 1024) + lane);
             }
         multiply(0, -1);
-        sums.scale([&](int i) { return Sc[br + i] - a.bias; }, [&](int j) { return Sc[bc + j]; });
+        sums.scale([&](int i) { return row_exponent(Sc, br + i) - a.bias; }, [&](int j) { return col_exponents(Sc + kT, bc + j); });
     }
     v4f* const all = reinterpret_cast<v4f*>(St);   // [wave][two rows of blocks][lane]
 #pragma unroll
@@ -821,10 +846,10 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
     // 38 / 40 / 45; T = 1500, K = 512 / 1024 28 / 42 against 23 / 40.  Below 768 rows its error is the larger one (T = 512 up to 1.06, 256 up
     // to 1.26 times).
     if (b > 1 && (T >= 1408 || (T >= 1100 && tiles > 50) || (T >= 768 && tiles > slots / 3))) {
-        // (a stage takes 128 K bytes and K / 4 for its scales; what the 4 T K bytes do not hold is rotated on the spot)
-        a.stages = (int)(T * 16 / 513);
+        // (a stage takes 128 K bytes, a group of four K for their exponents; what the 4 T K bytes do not hold is rotated on the spot)
+        a.stages = (int)((T * 16 - 3) / 513);
         a.planes = static_cast<char*>(workspace);
-        a.scales = reinterpret_cast<int*>(a.planes + (int64_t)a.stages * 128 * K);
+        a.exps = reinterpret_cast<uint8_t*>(a.planes + (int64_t)a.stages * 128 * K);
         a.bias = kPairBias + (b == 16 ? 4 : b == 32 ? 5 : b == 64 ? 6 : 7);
         hipLaunchKernelGGL(hessian_pack_kernel, dim3((unsigned)((a.stages + kGroup - 1) / kGroup), (unsigned)a.nt), dim3(256), 0, st, a);
         // The tiles beyond whole rounds, up to one per compute unit, in parts of 64 x 64, or of 32 x 32 if those leave most of the chip

@@ -80,7 +80,7 @@ struct PairSums {
         for (int j = 0; j < NT; ++j) t[NT - 1][j] += sum[(NT - 1) & 1][j];
     }
 
-    // t onto acc, its exponent that of the row in row block i and of the four columns (or the block) in column block j together
+    // t onto acc, its exponents those of the row in row block i and of the four columns in column block j together
     template <typename Row, typename Col>
     __device__ __forceinline__ void scale(Row row, Col col)
     {
@@ -88,12 +88,9 @@ struct PairSums {
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
-                const auto e = row(i) + col(j);
+                const v4i e = row(i) + col(j);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if constexpr (sizeof(e) == sizeof(int)) acc[i][j][v] += __builtin_amdgcn_ldexpf(t[i][j][v], e);
-                    else acc[i][j][v] += __builtin_amdgcn_ldexpf(t[i][j][v], e[v]);
-                }
+                for (int v = 0; v < 4; ++v) acc[i][j][v] += __builtin_amdgcn_ldexpf(t[i][j][v], e[v]);
                 t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
             }
     }

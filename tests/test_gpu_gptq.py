@@ -396,6 +396,28 @@ def test_hessian_of_many_rows_at_the_edges_of_stages_and_groups(fp4, oracle, T, 
         assert np.array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("log2_quiet", [8, 18, 30])
+@pytest.mark.parametrize("T,K,b", [(1408, 144, 16), (1700, 912, 16), (1540, 256, 128), (1475, 4112, 16)])
+def test_hessian_of_many_rows_with_quiet_channels_in_a_block(fp4, oracle, T, K, b, log2_quiet):
+    """Every 64th row is constant within a block, which the rotation turns into one loud channel and exact zeros; the others are noise of
+    2^-log2_quiet of that.  All other channels of the block are as quiet, and their entries as accurate on their own scale as any: the
+    bound of the test above."""
+    import torch
+    rng = np.random.default_rng(T + log2_quiet)
+    x = rng.standard_normal((T, K)) * 2.0 ** -log2_quiet
+    x[::64] = np.repeat(rng.uniform(1.0, 2.0, (x[::64].shape[0], K // b)), b, axis=1)
+    xb = inputs.f32_to_bf16_bits(x.astype(np.float32))
+    X = oracle.rotate(xb, b).astype(np.float64)
+    want = X.T @ X
+    say(f"gptq hessian quiet channels T={T} K={K} b={b} 2^-{log2_quiet}")
+    H = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(xb), b)
+    torch.cuda.synchronize()
+    got, scale = np_(H).astype(np.float64), np.sqrt(np.outer(np.diag(want), np.diag(want)))
+    say(f"   largest error over sqrt(h_ii h_jj): {(np.abs(got - want) / scale).max():.2e}")
+    assert np.all(np.abs(got - want) <= (42 + T / 128) * 2.0 ** -24 * scale)
+    assert np.array_equal(got, got.T)
+
+
 @pytest.mark.parametrize("log2_size", [-56, 56])
 @pytest.mark.parametrize("T,K,b", [(1540, 256, 128), (1475, 4112, 16)])
 def test_hessian_of_many_very_small_and_large_rows(fp4, T, K, b, log2_size):
