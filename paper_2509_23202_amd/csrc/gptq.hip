@@ -482,10 +482,12 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
         block_barrier();   // stage s has landed, stage s - 1 has been read
         if (s + 1 < kStages) issue(s + 1);
         const char* base = St + (s & 1) * kUpdateStage;
-        sums.multiply(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
         if (s & 1) {
+            sums.multiply<false>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
             const int* sc = Sc + (s / 2 & 1) * 256;
             sums.scale([&](int i) { return sc[(wr + i) * 16 + l16] - kPairBias; }, [&](int j) { return *reinterpret_cast<const v4i*>(sc + 128 + (wc + j) * 16 + 4 * q); });
+        } else {
+            sums.multiply<true>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
         }
     }
     // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 tile (K is a multiple of 64)

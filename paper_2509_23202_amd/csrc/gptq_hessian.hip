@@ -22,6 +22,7 @@
 #include "pair16.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace fp4mr {
 namespace {
@@ -670,7 +671,8 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
             block_barrier();   // stage s has landed, stage s - 1 has been read
             issue(s + 1);
             const char* base = St + (s & 1) * STAGE;
-            sums.multiply(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
+            if (s % kGroup == 0) sums.multiply<true>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
+            else sums.multiply<false>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
             if ((s + 1) % kGroup == 0 || s + 1 == stages) {
                 scale_sums(Sc + ((s & 1) * 4 + wave) * 256);
             }
@@ -683,7 +685,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
         build_stage(a, row, r0, St, Sc, red);
         build_stage(a, row, c0, St + 8 * kPairBytes, Sc + kT, red);
         __syncthreads();
-        sums.multiply(St + wr * kPairBytes, St + (8 + wc) * kPairBytes);
+        sums.multiply<true>(St + wr * kPairBytes, St + (8 + wc) * kPairBytes);
         scale_sums(Sc);
     }
 #pragma unroll
@@ -727,8 +729,11 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
     };
     auto fetch_row = [&](int s, int d, int k, int i) { rows[d][k][i] = fetch(s, k, r0 / 16 + i); };
     auto fetch_col = [&](int s, int d, int k, int j) { cols[d][k][j] = fetch(s, k, c0 / 16 + j); };
-    // one stage, from registers d; next >= 0: that stage takes their place
-    auto multiply = [&](int d, int next) {
+    // one stage, the first of its group or not, from registers d; next >= 0: that stage takes their place
+    constexpr std::true_type first;
+    constexpr std::false_type later;
+    auto multiply = [&](auto first, int d, int next) {
+        constexpr bool FIRST = decltype(first)::value;
         v4f sum[2][NT];
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
@@ -738,7 +743,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                 for (int j = 0; j < NT; ++j) {
                     v4f& x = sum[i & 1][j];
                     x = __builtin_amdgcn_mfma_f32_16x16x32_f16(cols[d][kPairParts[s][0]][j], rows[d][kPairParts[s][1]][i], s ? x : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    if (i && s == 0) sums.t[i - 1][j] += sum[(i - 1) & 1][j];
+                    if (i && s == 0) sums.template add<FIRST>(i - 1, j, sum[(i - 1) & 1][j]);
                     if (i + 1 == NT && s != 1 && next >= 0) fetch_col(next, d, kPairParts[s][0], j);
                 }
             if (next >= 0) {
@@ -747,7 +752,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
             }
         }
 #pragma unroll
-        for (int j = 0; j < NT; ++j) sums.t[NT - 1][j] += sum[(NT - 1) & 1][j];
+        for (int j = 0; j < NT; ++j) sums.template add<FIRST>(NT - 1, j, sum[(NT - 1) & 1][j]);
     };
     if (g_begin < g_end) {
 #pragma unroll
@@ -771,7 +776,8 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
             if constexpr (AHEAD == kGroup) {
 #pragma unroll
                 for (int d = 0; d < kGroup; ++d) {
-                    if (g * kGroup + d < a.stages) multiply(d, -1);
+                    if (d == 0) multiply(first, d, -1);
+                    else if (g * kGroup + d < a.stages) multiply(later, d, -1);
 #pragma unroll
                     for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -782,7 +788,8 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                 }
             } else {
                 const int end = min(kGroup, a.stages - g * kGroup);
-                for (int d = 0; d < end; ++d) multiply(0, g * kGroup + d + 1);
+                multiply(first, 0, g * kGroup + 1);
+                for (int d = 1; d < end; ++d) multiply(later, 0, g * kGroup + d + 1);
             }
             sums.scale([&](int i) { return fr[i] - a.bias; }, [&](int j) { return four_exponents(fc[j]); });
         }
@@ -801,7 +808,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                 rows[0][k][i] = *(reinterpret_cast<const v8h*>(St + (br + i) * kPairBytes + k * 1024) + lane);
                 cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (8 + bc + i) * kPairBytes + k * 1024) + lane);
             }
-        multiply(0, -1);
+        multiply(first, 0, -1);
         sums.scale([&](int i) { return row_exponent(Sc, br + i) - a.bias; }, [&](int j) { return col_exponents(Sc + kT, bc + j); });
     }
     v4f* const all = reinterpret_cast<v4f*>(St);   // [wave][two rows of blocks][lane]

@@ -41,10 +41,18 @@ struct PairSums {
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j] = t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
     }
 
-    // one stage; rows, cols: the wave's first block of either operand in LDS
+    template <bool FIRST>
+    __device__ __forceinline__ void add(int i, int j, v4f sum)
+    {
+        if constexpr (FIRST) t[i][j] = sum;
+        else t[i][j] += sum;
+    }
+
+    // one stage, the FIRST of those that are added up in t or another; rows, cols: the wave's first block of either operand in LDS
+    template <bool FIRST>
     __device__ __forceinline__ void multiply(const char* rows, const char* cols)
     {
         const int lane = threadIdx.x & 63;
@@ -72,12 +80,12 @@ struct PairSums {
                 for (int j = 0; j < NT; ++j) {
                     v4f& d = sum[i & 1][j];
                     d = __builtin_amdgcn_mfma_f32_16x16x32_f16(u[kPairParts[s][0]][j], e[kPairParts[s][1]], s ? d : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    if (i && s == 0) t[i - 1][j] += sum[(i - 1) & 1][j];
+                    if (i && s == 0) add<FIRST>(i - 1, j, sum[(i - 1) & 1][j]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
 #pragma unroll
-        for (int j = 0; j < NT; ++j) t[NT - 1][j] += sum[(NT - 1) & 1][j];
+        for (int j = 0; j < NT; ++j) add<FIRST>(NT - 1, j, sum[(NT - 1) & 1][j]);
     }
 
     // t onto acc, its exponents those of the row in row block i and of the four columns in column block j together
@@ -91,7 +99,6 @@ struct PairSums {
                 const v4i e = row(i) + col(j);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[i][j][v] += __builtin_amdgcn_ldexpf(t[i][j][v], e[v]);
-                t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
             }
     }
 };
