@@ -847,12 +847,12 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
     // two workgroups per compute unit work at a time; the tiles beyond whole rounds of those would run on a mostly idle chip for a
     // whole tile's time (K = 4096: 528 tiles for 512 slots)
     const int tiles = a.nt * (a.nt + 1) / 2, slots = 2 * compute_units(), rem = tiles % slots;
-    // Two 22-bit halves on the fp16 MFMA from 1408 rows, or from fewer if there are tiles enough: fewer products, but one launch more and
-    // 32 rows or more rotated on the spot.  The other way against this one, us: T = 768, K = 2048 / 3328 / 4096 49 / 94 / 113 against
-    // 56 / 71 / 90; T = 1024, K = 1280 / 1664 / 2304 36 / 52 / 62 against 35 / 40 / 64; T = 1200, K = 1024 / 1280 / 1664 37 / 44 / 63 against
-    // 38 / 40 / 45; T = 1500, K = 512 / 1024 28 / 42 against 23 / 40.  Below 768 rows its error is the larger one (T = 512 up to 1.06, 256 up
-    // to 1.26 times).
-    if (b > 1 && (T >= 1408 || (T >= 1100 && tiles > 50) || (T >= 768 && tiles > slots / 3))) {
+    // Pairs of halves on the fp16 MFMA from 1408 rows, or from 1100 if there are tiles enough: fewer products, but one launch more and
+    // 32 rows or more rotated on the spot.  The other way against this one, us: T = 1200, K = 1024 / 1280 / 1664 37 / 44 / 63 against
+    // 38 / 40 / 45; T = 1500, K = 512 / 1024 28 / 42 against 23 / 40.  Not below, where it would still be the faster one (T = 768 / 1024, K = 4096
+    // 113 / 139 against 90 / 101): of rows very different in size its error is the larger one there (rms over sqrt(h_ii h_jj), b = 16, rows of
+    // 2^-20 .. 2^20: T = 768 2.7e-8 against 3.0e-8, 1024 2.8e-8 against 2.9e-8, 1100 3.0e-8 against 2.8e-8), as those of few sums of 32 rows are.
+    if (b > 1 && (T >= 1408 || (T >= 1100 && tiles > 50))) {
         // (a stage takes 128 K bytes, a group of four K for their exponents; what the 4 T K bytes do not hold is rotated on the spot)
         a.stages = (int)((T * 16 - 3) / 513);
         a.planes = static_cast<char*>(workspace);

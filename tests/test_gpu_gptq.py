@@ -396,6 +396,27 @@ def test_hessian_of_many_rows_at_the_edges_of_stages_and_groups(fp4, oracle, T, 
         assert np.array_equal(got, got.T)
 
 
+@pytest.mark.parametrize("T,K", [(768, 2416), (1099, 2416), (1099, 4112)])
+def test_hessian_of_fewer_rows_keeps_24_bits_of_a_rotated_value(fp4, T, K):
+    """One row that is not zero, of integers whose rotated sums are exact and take up to 24 bits: below 1100 rows values are kept whole.
+    Bound: of three bf16 parts (2^-9 and 2^-17 of the value at most behind the first) the products left out are 2^-25 of the whole, and
+    the MFMA's result is cut off to 24 bits, 2^-23."""
+    import torch
+    rng = np.random.default_rng(T + K)
+    row = rng.integers(128, 256, K) * 2.0 ** rng.integers(0, 13, K) * rng.choice([-1.0, 1.0], K)
+    x = np.zeros((T, K), dtype=np.float32)
+    x[T // 2] = row
+    h = np.array([[(-1) ** bin(i & j).count("1") for j in range(16)] for i in range(16)])
+    y = (row.reshape(-1, 16) @ h).reshape(-1)
+    want = np.outer(y, y) / 16.0
+    say(f"gptq hessian one row of {T}, K={K}")
+    H = fp4.fp4_gptq_accumulate_hessian(to_dev_bf16(inputs.f32_to_bf16_bits(x)), 16)
+    torch.cuda.synchronize()
+    err = np.abs(np_(H).astype(np.float64) - want)
+    say(f"   largest relative error: {(err / np.maximum(np.abs(want), 1.0)).max():.2e}")
+    assert np.all(err <= 1.3 * 2.0 ** -23 * np.abs(want))
+
+
 @pytest.mark.parametrize("log2_quiet", [8, 18, 30])
 @pytest.mark.parametrize("T,K,b", [(1408, 144, 16), (1700, 912, 16), (1540, 256, 128), (1475, 4112, 16)])
 def test_hessian_of_many_rows_with_quiet_channels_in_a_block(fp4, oracle, T, K, b, log2_quiet):
