@@ -148,8 +148,18 @@ __device__ __forceinline__ float largest_finite(float a, float v)
     return f < INFINITY ? fmaxf(a, f) : a;
 }
 
-// Rows o .. o + 511 of U, columns 16 cb .. 16 cb + 15, for the update behind the outer block; eight waves, 64 rows each.
-__device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb)
+// The power of two next to U[j,j], from its reciprocal: column j's errors are multiplied by it where they become operands of the update,
+// row j of U by its inverse.  Errors are as large as the channel is loud, (w - q) / U[j,j], and channels that have nothing to do with the
+// loud ones among their 64 need all bits of theirs; the products of both factors then have the size of w - q.
+__device__ __forceinline__ float error_factor(float r)
+{
+    return __uint_as_float((254u - min(max(__float_as_uint(r) >> 23 & 255u, 1u), 253u)) << 23);
+}
+__device__ __forceinline__ float inverse_power(float p) { return __uint_as_float(0x7f000000u - __float_as_uint(p)); }
+
+// Rows o .. o + 511 of U, columns 16 cb .. 16 cb + 15, for the update behind the outer block; eight waves, 64 rows each.  Rp: the
+// rows' error factors.
+__device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb, const float* Rp)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
     const float* src = a.U + (int64_t)(o + 64 * wave + 8 * q) * a.K + cb * 16 + l16;
@@ -161,7 +171,10 @@ __device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb)
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) top = largest_finite(top, v[s][i]);
+        for (int i = 0; i < 8; ++i) {
+            v[s][i] *= inverse_power(Rp[64 * wave + 32 * s + 8 * q + i]);
+            top = largest_finite(top, v[s][i]);
+        }
     top = fmaxf(top, __shfl_xor(top, 16));
     top = fmaxf(top, __shfl_xor(top, 32));
     const uint32_t e = pair_exponent(top);
@@ -259,11 +272,17 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
     __shared__ __attribute__((aligned(16))) float Es[16 * kEStride];     // the block's errors
     __shared__ __attribute__((aligned(16))) uint8_t Sb[kOuter * 16];     // [column][row]: scale bytes of the outer block
     __shared__ __attribute__((aligned(16))) float Rd[kOuter];            // 1 / U[j,j]
+    __shared__ __attribute__((aligned(16))) float Rp[kOuter];            // error_factor
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid < oe - o) {
+        Rd[tid] = 1.0f / a.U[(int64_t)(o + tid) * a.K + o + tid];
+        Rp[tid] = error_factor(Rd[tid]);
+    }
     if ((int)blockIdx.x >= rows16) {
-        pack_u(a, o, oe / 16 + (int)blockIdx.x - rows16);
+        __syncthreads();
+        pack_u(a, o, oe / 16 + (int)blockIdx.x - rows16, Rp);
         return;
     }
-    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4;
     const int n0 = blockIdx.x * 16, width = oe - o, blocks = width / kB;
@@ -284,7 +303,6 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
 #pragma unroll
         for (int r = 0; r < 16; ++r) bytes[r >> 2] |= (uint32_t)a.scales[(int64_t)min(n0 + r, a.N - 1) * groups + group] << (8 * (r & 3));
         *reinterpret_cast<uint4*>(&Sb[tid * 16]) = make_uint4(bytes[0], bytes[1], bytes[2], bytes[3]);
-        Rd[tid] = 1.0f / Ug[(int64_t)(o + tid) * a.K + o + tid];
     }
 
     // Two barriers per block, the same for the sweeping and the pushing waves: behind the sweep (its errors are in LDS), and
@@ -318,8 +336,13 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
             if (n < a.N) *reinterpret_cast<uint32_t*>(a.q + (int64_t)n * a.K + o + b * kB + part * 4) = codes;
             if (oe < a.K) {   // (rows past the end too: what they hold is not stored)
                 float top = 0.0f;
+                const float4 f4 = *reinterpret_cast<const float4*>(&Rp[b * kB + part * 4]);
+                const float f[4] = {f4.x, f4.y, f4.z, f4.w};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) top = largest_finite(top, e[i]);
+                for (int i = 0; i < 4; ++i) {
+                    e[i] *= f[i];
+                    top = largest_finite(top, e[i]);
+                }
                 // the sixteen lanes of the row: rotations by 8, 4, 2, 1
                 top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x128, 0xf, 0xf, true)));
                 top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x124, 0xf, 0xf, true)));

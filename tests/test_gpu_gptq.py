@@ -532,6 +532,31 @@ def test_update_behind_an_outer_block_at_the_edges_of_its_tiles(fp4, oracle, gpt
     assert diff.mean() <= 1e-3
 
 
+@pytest.mark.parametrize("log2_loud", [12, 40, -40])
+def test_update_with_channels_of_two_kinds_that_have_nothing_in_common(fp4, oracle, gptq, log2_loud):
+    """H = D C D with channels of two kinds that C keeps apart, the one 2^log2_loud times as loud: the factor's columns are divided by D,
+    so the errors of the loud columns are that much larger than those of the quiet ones among them, on which alone the
+    other quiet columns depend.  Codes as in the test above, of either kind."""
+    import torch
+    N, K = 130, 1600
+    rng = np.random.default_rng(50 + log2_loud)
+    wb = inputs.f32_to_bf16_bits(rng.standard_normal((N, K)).astype(np.float32))
+    loud = rng.random(K) < 0.5
+    U = np.triu(rng.standard_normal((K, K)) * 0.02, 1) * (loud[:, None] == loud[None, :])
+    U[np.diag_indices(K)] = rng.uniform(0.5, 2.0, K)
+    U = (U * np.where(loud, 2.0 ** -log2_loud, 1.0)[None, :]).astype(np.float32)
+    perm = np.arange(K, dtype=np.int32)
+    y = oracle.rotate(wb, 1)
+    _, scales, _ = oracle.quantize(y, MX)
+    want, _ = gptq.sweep(y, scales, MX, None, U, perm)
+    say(f"gptq two kinds of channels 2^{log2_loud}")
+    c, s, _ = fp4.fp4_gptq_quantize_weights(to_dev_bf16(wb), 1, MX, to_dev(U), to_dev(perm))
+    torch.cuda.synchronize()
+    diff = unpack(np_(c).reshape(N, -1)) != unpack(want)
+    say(f"   codes differing from the oracle: loud {diff[:, loud].mean():.2e}, quiet {diff[:, ~loud].mean():.2e}")
+    assert diff[:, loud].mean() <= 1e-3 and diff[:, ~loud].mean() <= 1e-3
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("at", [40, 616, 1130])
 def test_sweep_keeps_the_codes_of_columns_visited_before_a_non_finite_weight(fp4, oracle, value, at):
