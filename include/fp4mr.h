@@ -293,7 +293,8 @@ fp4mr_status_t fp4_gptq_accumulate_hessian(const void* x, int64_t T, int64_t K, 
  *               Cholesky of the index-reversed matrix, the same row operations applied to an identity); no inverse of A is formed.
  *   hessian     [K,K] fp32 row-major, device, symmetric positive semi-definite: X'^T X' of the ROTATED calibration inputs
  *               (only read); K <= 24576; damp > 0 makes the dampened matrix positive definite
- *   workspace   fp4_workspace_bytes(FP4MR_OP_GPTQ_PREPARE, 0, 0, K, fmt ignored, 0) bytes (about 2.5 K^2 floats)
+ *   workspace   fp4_workspace_bytes(FP4MR_OP_GPTQ_PREPARE, 0, 0, K, fmt ignored, 0) bytes: the larger of 2.5 K^2 floats and
+ *               Kp^2 + 128 Kp + 128^2 + K + 64 floats, Kp being K rounded up to a multiple of 128 (either in whole 256 bytes)
  * A Hessian that is not positive definite after dampening yields NaNs in hinv_u_out (no fault).
  */
 fp4mr_status_t fp4_gptq_prepare(const float* hessian, int64_t K, float damp, int act_order, int32_t* perm_out, float* hinv_u_out,

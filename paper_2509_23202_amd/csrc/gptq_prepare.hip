@@ -40,8 +40,7 @@ constexpr int PW = 32;         // columns per workgroup of the panel kernel
 
 struct PrepArgs {
     float* M;        // [Kp, Kp], lower block triangle used
-    char* P;         // the panel, L_jk^T of the blocks j > k and X_j of the blocks j < k, as operands (operand_at)
-    char* DP[2];     // X_k = D likewise, of an even and an odd step
+    char* P;         // the panel, L_jk^T of the blocks j > k and X_j of the blocks j < k, as operands (operand_at); the block k is left out
     float* DT;       // the 36 tiles of D, lane (l16, q) of a tile with row l16, columns 4 q .. 4 q + 3
     int Kp;          // K rounded up to whole blocks; the padding is the identity
     int nt;          // Kp / NB
@@ -162,6 +161,9 @@ __device__ __forceinline__ v4f product(v4f a, v4f b)
 // contraction is strips w and 7 - w, of which lane (l16, q) holds rows 4 q .. 4 q + 3 of column l16 -- what an fp32 MFMA leaves there.
 // Three parts of eight bits each, one behind the other, 1 KB a part.
 __device__ __forceinline__ int64_t operand_at(int w, int blocks, int block) { return ((int64_t)w * blocks + block) * 3072; }
+// of the panel of step k: how many sixteens, and where those of NB-block j != k begin
+__device__ __forceinline__ int panel_blocks(const PrepArgs& a) { return (a.nt - 1) * NS; }
+__device__ __forceinline__ int panel_block(const PrepArgs& a, int j) { return (j < a.k ? j : j - 1) * NS; }
 __device__ __forceinline__ void put_operand(char* p, v4f low, v4f high)
 {
     const float x[8] = {low[0], low[1], low[2], low[3], high[0], high[1], high[2], high[3]};
@@ -271,7 +273,7 @@ __global__ __launch_bounds__(256) void panel_kernel(PrepArgs a)
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        put_operand(a.P + operand_at(wave, a.Kp / SB, c0[j] / SB), acc[0][j], acc[1][j]);
+        put_operand(a.P + operand_at(wave, panel_blocks(a), blk * NS + sub / SB + j), acc[0][j], acc[1][j]);
         if (left) {   // (rows k of the inverse are finished)
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(512, 4) void update_kernel(PrepArgs a)
             for (int v = 0; v < 4; ++v) x[e][v] = Md[(int64_t)(SB * i + 4 * q + v) * a.Kp + SB * j + l16];
         }
         invert_factor(d, x);
-        // D: four values of a row per lane, in M and, as tiles, for the panel; as an operand of the next update; zeros above
+        // D: four values of a row per lane, in M and, as tiles, for the panel; zeros above
 #pragma unroll
         for (int e = 0; e < 5; ++e) {
             const int t = wave + 8 * e;
@@ -502,13 +504,6 @@ __global__ __launch_bounds__(512, 4) void update_kernel(PrepArgs a)
             for (int v = 0; v < 4; ++v) row[v] = d.S[t * TF + tile_at(l16, 4 * q + v)];
             *reinterpret_cast<v4f*>(Md + (int64_t)(SB * i + l16) * a.Kp + SB * j + 4 * q) = row;
             *reinterpret_cast<v4f*>(a.DT + t * 256 + lane * 4) = row;
-        }
-#pragma unroll
-        for (int e = 0; e < NS / 2; ++e) {
-            const int w = wave & 3, j = (wave >> 2) + 2 * e;
-            const v4f zero = v4f{0.f, 0.f, 0.f, 0.f};
-            put_operand(a.DP[next & 1] + operand_at(w, NS, j), j <= w ? get_tile(d.S + tile_index(w, j) * TF) : zero,
-                        j <= NS - 1 - w ? get_tile(d.S + tile_index(NS - 1 - w, j) * TF) : zero);
         }
         for (int t = wave; t < TILES - NS; t += 8) {   // (the strict lower triangle, mirrored)
             const int i = tile_row(t), j = t - tile_index(i, 0);
@@ -523,7 +518,7 @@ __global__ __launch_bounds__(512, 4) void update_kernel(PrepArgs a)
     while ((int64_t)i * (i + 1) / 2 > n) --i;
     while ((int64_t)(i + 1) * (i + 2) / 2 <= n) ++i;
     const int j = (int)(n - (int64_t)i * (i + 1) / 2);
-    const int blocks = a.Kp / SB, wr = (wave >> 1) * 2, wc = (wave & 1) * 2;   // first 16-wide block of the piece
+    const int blocks = panel_blocks(a), wr = (wave >> 1) * 2, wc = (wave & 1) * 2;   // first 16-wide block of the piece
     // the column operand is the MFMA's A: a lane owns four neighbouring columns of a row
     float* const C = a.M + (int64_t)(i * NB + wr * SB + l16) * a.Kp + j * NB + (half * 4 + wc) * SB + 4 * q;
     v4f old[2][2], low[2][2], high[2][2];
@@ -535,19 +530,37 @@ __global__ __launch_bounds__(512, 4) void update_kernel(PrepArgs a)
             if (j != a.k) old[x][y] = *reinterpret_cast<const v4f*>(C + (int64_t)(SB * x) * a.Kp + SB * y);
         }
     const bool own = j == a.k;
-    char* const A = a.P + operand_at(0, blocks, i * NS);
-    char* const B = (own ? a.DP[a.k & 1] : a.P + operand_at(0, blocks, j * NS)) + half * 4 * 3072;
-    // the copies of a quarter, 1 KB each: 24 of rows, 12 of columns; a wave takes five, the last of some twice (the same data)
+    char* const A = a.P + operand_at(0, blocks, panel_block(a, i));
+    char* const B = a.P + operand_at(0, blocks, panel_block(a, j) + half * 4);   // (unused if own)
+    // the copies of a quarter, 1 KB each: 24 of rows, 12 of columns; a wave takes five, the last of some twice (the same data).
+    // X_k = D is not in the panel: it is split here, from M, by four waves.
     constexpr int OPS = 5;
     auto issue = [&](int w) {
         const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(A + operand_at(w, blocks, 0), 0, NS * 3072, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(B + operand_at(w, own ? NS : blocks, 0), 0, NS / 2 * 3072, 0x00020000);
         char* const base = smem + (w & 1) * kUpdateStage;
 #pragma unroll
-        for (int it = 0; it < OPS; ++it) {
+        for (int it = 0; it < 3; ++it) {
+            const int c = it * 8 + wave;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(base + c * 1024), 16, lane * 16, c * 1024, 0, 0);
+        }
+        if (own) {
+            if (wave < NS / 2) {
+                const float* D = a.M + (int64_t)(a.k * NB + 4 * q) * a.Kp + a.k * NB + (half * 4 + wave) * SB + l16;
+                v4f d[2];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    d[0][v] = D[(int64_t)(SB * w + v) * a.Kp];
+                    d[1][v] = D[(int64_t)(SB * (NS - 1 - w) + v) * a.Kp];
+                }
+                put_operand(base + (NS + wave) * 3072, d[0], d[1]);
+            }
+            return;
+        }
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(B + operand_at(w, blocks, 0), 0, NS / 2 * 3072, 0x00020000);
+#pragma unroll
+        for (int it = 3; it < OPS; ++it) {
             const int c = min(it * 8 + wave, 35);
-            if (it < 3) __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void*)(base + c * 1024), 16, lane * 16, c * 1024, 0, 0);
-            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(base + c * 1024), 16, lane * 16, (c - 24) * 1024, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void*)(base + c * 1024), 16, lane * 16, (c - 24) * 1024, 0, 0);
         }
     };
     auto multiply = [&](int w) {
@@ -576,8 +589,9 @@ __global__ __launch_bounds__(512, 4) void update_kernel(PrepArgs a)
     issue(1);
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        if (w < 3) wait_vmcnt<OPS>();
+        if (w < 3 && !own) wait_vmcnt<OPS>();
         else wait_vmcnt<0>();
+        wait_lgkmcnt0();
         block_barrier();   // quarter w has landed
         multiply(w);
         if (w < 2) {
@@ -592,7 +606,7 @@ __global__ __launch_bounds__(512, 4) void update_kernel(PrepArgs a)
         for (int y = 0; y < 2; ++y) *reinterpret_cast<v4f*>(C + (int64_t)(SB * x) * a.Kp + SB * y) = old[x][y] - (high[x][y] + low[x][y]);
 }
 
-constexpr size_t kPanelBytes = NB * 6, kDiagBytes = kPanelBytes * NB;
+constexpr size_t kPanelBytes = NB * 6;   // per column
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 inline int64_t padded(int64_t K) { return (K + NB - 1) / NB * NB; }
 
@@ -600,10 +614,11 @@ inline int64_t padded(int64_t K) { return (K + NB - 1) / NB * NB; }
 
 size_t gptq_prepare_workspace_bytes(int64_t K)
 {
-    // M; the panel; the diagonal block's inverse, twice as an operand and as tiles; the diagonal; the mean.  Never less than the 2.5 K^2 floats that callers of
-    // this entry point are told to expect.
+    // The 2.5 K^2 floats that callers of this entry point are told to expect, or what they are told for few columns: M, 128 rows of it, a block
+    // of it, the diagonal, the mean.  launch_gptq_prepare needs M, the panel (6 bytes for a value of 128 rows, all blocks but one), 36 KB
+    // of tiles, the diagonal and the mean, which is less at every K.
     const size_t Kp = (size_t)padded(K), k = (size_t)K;
-    return std::max(Kp * Kp * 4 + kPanelBytes * Kp + 2 * kDiagBytes + TILES * 1024 + align256(k * 4) + 256, align256(k * k * 10));
+    return std::max(Kp * Kp * 4 + NB * Kp * 4 + NB * NB * 4 + align256(k * 4) + 256, align256(k * k * 10));
 }
 
 hipError_t launch_gptq_prepare(const float* H, int64_t K64, float damp, bool use_order, int* perm, float* U, void* workspace,
@@ -619,10 +634,7 @@ hipError_t launch_gptq_prepare(const float* H, int64_t K64, float damp, bool use
     a.M = reinterpret_cast<float*>(ws);
     ws += (size_t)Kp * Kp * 4;
     a.P = ws;
-    ws += kPanelBytes * (size_t)Kp;
-    a.DP[0] = ws;
-    a.DP[1] = ws + kDiagBytes;
-    ws += 2 * kDiagBytes;
+    ws += kPanelBytes * (size_t)(Kp - NB);
     a.DT = reinterpret_cast<float*>(ws);
     ws += TILES * 1024;
     float* diag = reinterpret_cast<float*>(ws);

@@ -82,6 +82,15 @@ def test_sizes(lib):
     assert b.workspace_bytes(b.OP_GEMM, 128, 16384, 4096, b.NVFP4, lay) >= 128 * 4096 * 2      # the many-token kernel's fp16 X
 
 
+def test_gptq_workspaces_are_what_the_header_says():
+    """A caller may have the sizes from there (fp4_gptq_prepare's formula) as well as from fp4_workspace_bytes."""
+    from paper_2509_23202_amd import binding as b
+    up = lambda n: (n + 255) // 256 * 256
+    for K in (1, 16, 64, 128, 129, 200, 256, 272, 320, 384, 385, 512, 4096, 14336):
+        Kp = (K + 127) // 128 * 128
+        assert b.workspace_bytes(b.OP_GPTQ_PREPARE, 0, 0, K, b.MXFP4) == max(up(10 * K * K), 4 * Kp * Kp + 512 * Kp + 65536 + up(4 * K) + 256)
+
+
 def test_argument_validation_happens_before_any_launch(lib):
     from paper_2509_23202_amd import binding as b
     L = b.lib

@@ -227,6 +227,25 @@ def test_prepare_at_the_edges_of_its_blocks(fp4, gptq, K):
     assert np.abs(U.T @ U @ A - np.eye(K)).max() <= 2e-3
 
 
+@pytest.mark.parametrize("K", [1, 128, 129, 256, 272, 384, 400])
+def test_prepare_stays_inside_its_workspace(fp4, K):
+    """The size in the header, around whole blocks of 128: the same factor, and nothing behind it is written."""
+    import torch
+    say(f"gptq prepare workspace K={K}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    x = torch.randn(2 * K + 8, K, device="cuda", generator=g)
+    H = x.t().contiguous() @ x
+    H = ((H + H.t()) * 0.5).contiguous()
+    need = fp4.workspace_bytes(fp4.OP_GPTQ_PREPARE, 0, 0, K, MX)
+    room = torch.full((need + 65536,), 0xa5, dtype=torch.uint8, device="cuda")
+    perm, U = fp4.fp4_gptq_prepare(H, 1e-2, True)
+    perm2, U2 = fp4.fp4_gptq_prepare(H, 1e-2, True, workspace=room[:need])
+    torch.cuda.synchronize()
+    assert torch.equal(perm, perm2) and torch.equal(U, U2)
+    assert bool((room[need:] == 0xa5).all())
+
+
 @pytest.mark.parametrize("log2_scale", [-124, -60, 110])
 def test_prepare_of_very_small_and_large_hessians(fp4, gptq, log2_scale):
     """The factor scales with the Hessian, also where pivots are subnormal in binary32 (mean of the diagonal 2^-124; they still
