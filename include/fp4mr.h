@@ -254,7 +254,8 @@ fp4mr_status_t fp4_w4a16_linear(const void* x, int64_t M, int64_t K, int had_blo
  *                permutation; entries outside [0,K) are clamped (garbage codes, no fault)
  *   codes_out, scales_out   canonical layout, as fp4_quantize_weights writes them (scales_out equals its output bit for
  *                bit: the sweep changes codes only); tensor_scale as there (NVFP4)
- *   workspace    fp4_workspace_bytes(FP4MR_OP_GPTQ, N, 0, K, fmt, flags) bytes
+ *   workspace    fp4_workspace_bytes(FP4MR_OP_GPTQ, N, 0, K, fmt, flags) bytes.  2080 (N' + K) - 2048 N bytes less (N' is N rounded up to 16,
+ *                2048 N up to 256) are accepted too: the same codes, later, for want of room to prepare the products' operands once
  *   flags        FP4MR_SCALE_MSE, FP4MR_SCALE_MSE | FP4MR_SCALE_FIT_TENSOR (NVFP4), FP4MR_SCALE_ROUND43 or
  *                FP4MR_SCALE_FIT_RANGE (MXFP4; tensor_scale then receives the FP4MR_FIT_RANGE_FLOATS floats and the sweep
  *                takes each group's scale from its 256 scale values), all optional: how the fixed grid is found;

@@ -259,7 +259,7 @@ fp4mr_status_t fp4_gptq_quantize_weights(const void* w, int64_t N, int64_t K, in
     if (!hinv_u) return FP4MR_ERR_NULL;
     if (N > (1 << 24) || K <= 0 || K % 64 != 0 || K > 24576) return FP4MR_ERR_SHAPE;
     if (!aligned16(hinv_u) || (perm && !aligned16(perm))) return FP4MR_ERR_ALIGN;
-    const size_t need = fp4_workspace_bytes(FP4MR_OP_GPTQ, N, 0, K, fmt, flags);
+    const size_t need = N > 0 ? align256(quant_workspace(fmt, flags)) + gptq_workspace_least(N, K) : 0;
     if (!workspace || workspace_bytes < need || !aligned16(workspace)) return FP4MR_ERR_WORKSPACE;
     // 1. the grid: scales (and the NVFP4 tensor scale) of the rotated weights in their original order; the codes this
     //    writes are the round-to-nearest ones, replaced below
@@ -271,7 +271,7 @@ fp4mr_status_t fp4_gptq_quantize_weights(const void* w, int64_t N, int64_t K, in
                                            fmt == FP4MR_NVFP4 ? tensor_scale : nullptr,
                                            (flags & FP4MR_SCALE_FIT_RANGE) ? tensor_scale + 2 : nullptr,  // the scale values just published
                                            (flags & FP4MR_SCALE_ROUND43) ? 4.0f / 3.0f : 1.0f, codes_out,
-                                           static_cast<char*>(workspace) + qws, static_cast<hipStream_t>(stream));
+                                           static_cast<char*>(workspace) + qws, workspace_bytes - qws, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? FP4MR_OK : FP4MR_ERR_DEVICE;
 }
 

@@ -36,6 +36,7 @@ struct GptqArgs {
     int* e_scales;          // [kOuter / kB][rows]: their exponents: of a row's errors of 64 columns
     char* u_pairs;          // rows of U, [stage][16 columns]
     int* u_scales;          // [kOuter / kB][K]: of a column's entries in 64 rows
+    float* err;             // ... or, in a workspace without room for those, the errors as they are, [N, kOuter]; else null
     int Np;                 // N rounded up to 16
     const uint8_t* scales;  // [N,K/G] canonical
     const float* s_T;       // NVFP4 tensor scale (device), else null
@@ -157,29 +158,18 @@ __device__ __forceinline__ float error_factor(float r)
 }
 __device__ __forceinline__ float inverse_power(float p) { return __uint_as_float(0x7f000000u - __float_as_uint(p)); }
 
-// Rows o .. o + 511 of U, columns 16 cb .. 16 cb + 15, for the update behind the outer block; eight waves, 64 rows each.  Rp: the
-// rows' error factors.
-__device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb, const float* Rp)
+// A lane's values of sixteen rows or columns by two stages into both, `step` bytes apart; the lane's row's exponent.
+__device__ __forceinline__ uint32_t put_pairs(const float (&v)[2][8], char* dst, int64_t step)
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
-    const float* src = a.U + (int64_t)(o + 64 * wave + 8 * q) * a.K + cb * 16 + l16;
-    float v[2][8], top = 0.0f;
+    float top = 0.0f;
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[s][i] = src[(int64_t)(32 * s + i) * a.K];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            v[s][i] *= inverse_power(Rp[64 * wave + 32 * s + 8 * q + i]);
-            top = largest_finite(top, v[s][i]);
-        }
+        for (int i = 0; i < 8; ++i) top = largest_finite(top, v[s][i]);
     top = fmaxf(top, __shfl_xor(top, 16));
     top = fmaxf(top, __shfl_xor(top, 32));
     const uint32_t e = pair_exponent(top);
     const float up = pair_up(e);
-    if (q == 0) a.u_scales[wave * a.K + cb * 16 + l16] = (int)e;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         v8h h, l;
@@ -190,10 +180,36 @@ __device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb, const f
             h[i] = hi;
             l[i] = lo;
         }
-        v8h* dst = reinterpret_cast<v8h*>(a.u_pairs + pairs_at(2 * wave + s, a.K / 16, cb)) + lane;
-        dst[0] = h;
-        dst[64] = l;
+        v8h* d = reinterpret_cast<v8h*>(dst + s * step) + (threadIdx.x & 63);
+        d[0] = h;
+        d[64] = l;
     }
+    return e;
+}
+
+// a lane's share of 64 rows of U from row j0 of the outer block at o, in column col; Rp: the block's error factors
+__device__ __forceinline__ void factor_rows(const GptqArgs& a, int o, int j0, int col, const float* Rp, float (&v)[2][8])
+{
+    const int r = j0 + 8 * (threadIdx.x >> 4 & 3);
+    const float* src = a.U + (int64_t)(o + r) * a.K + col;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[s][i] = src[(int64_t)(32 * s + i) * a.K];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[s][i] *= inverse_power(Rp[r + 32 * s + i]);
+}
+
+// Rows o .. o + 511 of U, columns 16 cb .. 16 cb + 15, for the update behind the outer block; eight waves, 64 rows each.
+__device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb, const float* Rp)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15;
+    float v[2][8];
+    factor_rows(a, o, 64 * wave, cb * 16 + l16, Rp, v);
+    const uint32_t e = put_pairs(v, a.u_pairs + pairs_at(2 * wave, a.K / 16, cb), pairs_at(1, a.K / 16, 0));
+    if (lane < 16) a.u_scales[wave * a.K + cb * 16 + l16] = (int)e;
 }
 
 constexpr int kWStride = kOuter + 4;   // floats per row of working weights in LDS: rows start four banks apart
@@ -343,27 +359,31 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
                     e[i] *= f[i];
                     top = largest_finite(top, e[i]);
                 }
-                // the sixteen lanes of the row: rotations by 8, 4, 2, 1
-                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x128, 0xf, 0xf, true)));
-                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x124, 0xf, 0xf, true)));
-                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x122, 0xf, 0xf, true)));
-                top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x121, 0xf, 0xf, true)));
-                const uint32_t ex = pair_exponent(top);
-                const float up = pair_up(ex);
-                typedef _Float16 v4h __attribute__((ext_vector_type(4)));
-                v4h h, l;
+                if (a.err) {
+                    if (n < a.N) *reinterpret_cast<float4*>(a.err + (int64_t)n * kOuter + b * kB + part * 4) = make_float4(e[0], e[1], e[2], e[3]);
+                } else {
+                    // the sixteen lanes of the row: rotations by 8, 4, 2, 1
+                    top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x128, 0xf, 0xf, true)));
+                    top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x124, 0xf, 0xf, true)));
+                    top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x122, 0xf, 0xf, true)));
+                    top = fmaxf(top, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(top), 0x121, 0xf, 0xf, true)));
+                    const uint32_t ex = pair_exponent(top);
+                    const float up = pair_up(ex);
+                    typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+                    v4h h, l;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    _Float16 hi, lo;
-                    pair_split(e[i], up, hi, lo);
-                    h[i] = hi;
-                    l[i] = lo;
+                    for (int i = 0; i < 4; ++i) {
+                        _Float16 hi, lo;
+                        pair_split(e[i], up, hi, lo);
+                        h[i] = hi;
+                        l[i] = lo;
+                    }
+                    // columns 4 part .. 4 part + 3 of 64: stage part / 8, there half of lane (row, (part % 8) / 2)
+                    char* dst = a.e_pairs + pairs_at(2 * b + (part >> 3), a.Np / 16, blockIdx.x) + (((part & 7) >> 1) * 16 + row) * 16 + (part & 1) * 8;
+                    *reinterpret_cast<v4h*>(dst) = h;
+                    *reinterpret_cast<v4h*>(dst + 1024) = l;
+                    if (part == 0) a.e_scales[b * a.Np + n] = (int)ex;
                 }
-                // columns 4 part .. 4 part + 3 of 64: stage part / 8, there half of lane (row, (part % 8) / 2)
-                char* dst = a.e_pairs + pairs_at(2 * b + (part >> 3), a.Np / 16, blockIdx.x) + (((part & 7) >> 1) * 16 + row) * 16 + (part & 1) * 8;
-                *reinterpret_cast<v4h*>(dst) = h;
-                *reinterpret_cast<v4h*>(dst + 1024) = l;
-                if (part == 0) a.e_scales[b * a.Np + n] = (int)ex;
             }
             lds_barrier();
         }
@@ -464,7 +484,12 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
 // multiplied; two workgroups per compute unit.  [6144, 4096] behind its first outer block 92 us (157 with six bf16 products of
 // operands that every workgroup split for itself, 308 on the fp32 MFMA), of which wp is 24 at the rate of a large copy; codes that differ from
 // a sweep in 64 bits, 32 layers of K = 2048 and 4096: 9616 of 50 million (9830 with the bf16 products).
-constexpr int kUpdateStage = 16 * kPairBytes, kUpdateLds = 2 * (kUpdateStage + 1024);   // 8 row blocks, then 8 column blocks; their scales
+constexpr int kUpdateStage = 16 * kPairBytes;   // 8 row blocks, then 8 column blocks
+constexpr int kUpdateLds = 2 * (kUpdateStage + 1024), kUpdateLdsUnpacked = kUpdateLds + kOuter * 4;   // two stages and their exponents; error factors
+//
+// PACKED == false: the workspace has no room for the pairs, every workgroup makes its own, 64 terms at a time, from the errors and from U.
+// The results are the same bit for bit.
+template <bool PACKED>
 __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_begin)
 {
     constexpr int T = 128, NT = 4;
@@ -476,41 +501,70 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
     const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7, p = xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3);
     const int tiles = (a.K - c_begin + T - 1) / T;
     const int n0 = p / tiles * T, c0 = c_begin + p % tiles * T;
-    const int row_blocks = a.Np / 16, col_blocks = a.K / 16;
-    // Blocks past the end are the last one again: they only feed outputs that are not stored.
-    const uint32_t scale_at = 4u * (uint32_t)(wave < 2 ? min(n0 + wave * 64 + lane, a.Np - 1) : min(c0 + (wave - 2) * 64 + lane, a.K - 1));
-    auto issue = [&](int s) {
-        const int slot = s & 1;
-        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(a.e_pairs + pairs_at(s, row_blocks, n0 / 16), 0, min(row_blocks - n0 / 16, 8) * kPairBytes, 0x00020000);
-        const __amdgpu_buffer_rsrc_t cols = __builtin_amdgcn_make_buffer_rsrc(a.u_pairs + pairs_at(s, col_blocks, c0 / 16), 0, min(col_blocks - c0 / 16, 8) * kPairBytes, 0x00020000);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int c = (wave & 1) * 8 + i;   // 1 KB: half a block; two waves for either operand
-            char* const dst = St + slot * kUpdateStage + wave * 8192 + i * 1024;
-            if (wave < 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_void*)dst, 16, lane * 16, min(c >> 1, row_blocks - 1 - n0 / 16) * kPairBytes + (c & 1) * 1024, 0, 0);
-            else __builtin_amdgcn_raw_ptr_buffer_load_lds(cols, (lds_void*)dst, 16, lane * 16, min(c >> 1, col_blocks - 1 - c0 / 16) * kPairBytes + (c & 1) * 1024, 0, 0);
-        }
-        if (s % 2 == 0) {
-            const __amdgpu_buffer_rsrc_t rs = wave < 2 ? __builtin_amdgcn_make_buffer_rsrc(a.e_scales + (int64_t)(s / 2) * a.Np, 0, 4 * a.Np, 0x00020000)
-                                                       : __builtin_amdgcn_make_buffer_rsrc(a.u_scales + (int64_t)(s / 2) * a.K, 0, 4 * a.K, 0x00020000);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(Sc + (s / 2 & 1) * 256 + wave * 64), 4, scale_at, 0, 0, 0);
-        }
-    };
     PairSums<NT> sums;
     sums.clear();
-    issue(0);
-    for (int s = 0; s < kStages; ++s) {
-        wait_vmcnt<0>();
-        wait_lgkmcnt0();
-        block_barrier();   // stage s has landed, stage s - 1 has been read
-        if (s + 1 < kStages) issue(s + 1);
-        const char* base = St + (s & 1) * kUpdateStage;
-        if (s & 1) {
-            sums.multiply<false>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
-            const int* sc = Sc + (s / 2 & 1) * 256;
-            sums.scale([&](int i) { return sc[(wr + i) * 16 + l16] - kPairBias; }, [&](int j) { return *reinterpret_cast<const v4i*>(sc + 128 + (wc + j) * 16 + 4 * q); });
-        } else {
-            sums.multiply<true>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
+    auto scale_sums = [&](const int* sc) {
+        sums.scale([&](int i) { return sc[(wr + i) * 16 + l16] - kPairBias; }, [&](int j) { return *reinterpret_cast<const v4i*>(sc + 128 + (wc + j) * 16 + 4 * q); });
+    };
+    if constexpr (PACKED) {
+        const int row_blocks = a.Np / 16, col_blocks = a.K / 16;
+        // Blocks past the end are the last one again: they only feed outputs that are not stored.
+        const uint32_t scale_at = 4u * (uint32_t)(wave < 2 ? min(n0 + wave * 64 + lane, a.Np - 1) : min(c0 + (wave - 2) * 64 + lane, a.K - 1));
+        auto issue = [&](int s) {
+            const int slot = s & 1;
+            const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(a.e_pairs + pairs_at(s, row_blocks, n0 / 16), 0, min(row_blocks - n0 / 16, 8) * kPairBytes, 0x00020000);
+            const __amdgpu_buffer_rsrc_t cols = __builtin_amdgcn_make_buffer_rsrc(a.u_pairs + pairs_at(s, col_blocks, c0 / 16), 0, min(col_blocks - c0 / 16, 8) * kPairBytes, 0x00020000);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int c = (wave & 1) * 8 + i;   // 1 KB: half a block; two waves for either operand
+                char* const dst = St + slot * kUpdateStage + wave * 8192 + i * 1024;
+                if (wave < 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (lds_void*)dst, 16, lane * 16, min(c >> 1, row_blocks - 1 - n0 / 16) * kPairBytes + (c & 1) * 1024, 0, 0);
+                else __builtin_amdgcn_raw_ptr_buffer_load_lds(cols, (lds_void*)dst, 16, lane * 16, min(c >> 1, col_blocks - 1 - c0 / 16) * kPairBytes + (c & 1) * 1024, 0, 0);
+            }
+            if (s % 2 == 0) {
+                const __amdgpu_buffer_rsrc_t rs = wave < 2 ? __builtin_amdgcn_make_buffer_rsrc(a.e_scales + (int64_t)(s / 2) * a.Np, 0, 4 * a.Np, 0x00020000)
+                                                           : __builtin_amdgcn_make_buffer_rsrc(a.u_scales + (int64_t)(s / 2) * a.K, 0, 4 * a.K, 0x00020000);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(Sc + (s / 2 & 1) * 256 + wave * 64), 4, scale_at, 0, 0, 0);
+            }
+        };
+        issue(0);
+        for (int s = 0; s < kStages; ++s) {
+            wait_vmcnt<0>();
+            wait_lgkmcnt0();
+            block_barrier();   // stage s has landed, stage s - 1 has been read
+            if (s + 1 < kStages) issue(s + 1);
+            const char* base = St + (s & 1) * kUpdateStage;
+            if (s & 1) {
+                sums.multiply<false>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
+                scale_sums(Sc + (s / 2 & 1) * 256);
+            } else {
+                sums.multiply<true>(base + wr * kPairBytes, base + (8 + wc) * kPairBytes);
+            }
+        }
+    } else {
+        float* const Rp = reinterpret_cast<float*>(St + kUpdateLds);
+        const int o = c_begin - kOuter;
+        for (int j = tid; j < kOuter; j += 256) Rp[j] = error_factor(1.0f / a.U[(int64_t)(o + j) * a.K + o + j]);
+        for (int j0 = 0; j0 < kOuter; j0 += kB) {
+            __syncthreads();
+            for (int block = wave; block < 16; block += 4) {
+                float v[2][8];
+                if (block < 8) {
+                    const float* src = a.err + (int64_t)min(n0 + block * 16 + l16, a.N - 1) * kOuter + j0 + 8 * q;
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) v[s][i] = src[32 * s + i];
+                } else {
+                    factor_rows(a, o, j0, min(c0 + (block - 8) * 16 + l16, a.K - 1), Rp, v);
+                }
+                const uint32_t e = put_pairs(v, St + block * kPairBytes, kUpdateStage);
+                if (lane < 16) Sc[block * 16 + l16] = (int)e;
+            }
+            __syncthreads();
+            sums.multiply<true>(St + wr * kPairBytes, St + (8 + wc) * kPairBytes);
+            sums.multiply<false>(St + kUpdateStage + wr * kPairBytes, St + kUpdateStage + (8 + wc) * kPairBytes);
+            scale_sums(Sc);
         }
     }
     // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 tile (K is a multiple of 64)
@@ -549,20 +603,24 @@ __global__ __launch_bounds__(256) void gptq_pack_kernel(GptqArgs a)
     }
 }
 
-constexpr size_t kPairsPerIndex = kOuter * 4 + kOuter / kB * 4;   // bytes of a row's (column's) pairs and scales
+constexpr size_t kPairsPerIndex = kOuter * 4 + kOuter / kB * 4;   // bytes of a row's (column's) pairs and exponents
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
+
+// working weights, codes and the inverse order, beside the update's operands
+inline size_t weights_bytes(int64_t N, int64_t K) { return align256((size_t)N * K * 4) + align256((size_t)N * K) + align256((size_t)K * 4); }
 
 }  // namespace
 
 size_t gptq_workspace_bytes(int64_t N, int64_t K)
 {
-    // working weights, codes, the pairs and scales of an outer block's errors and of its rows of U, the inverse order
-    const size_t np = (size_t)(N + 15) / 16 * 16, k = (size_t)K;
-    return align256((size_t)N * k * 4) + align256((size_t)N * k) + (np + k) * kPairsPerIndex + align256(k * 4);
+    // the pairs and exponents of an outer block's errors and of its rows of U
+    return weights_bytes(N, K) + ((size_t)(N + 15) / 16 * 16 + (size_t)K) * kPairsPerIndex;
 }
 
+size_t gptq_workspace_least(int64_t N, int64_t K) { return weights_bytes(N, K) + align256((size_t)N * kOuter * 4); }   // the errors alone
+
 hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt, const float* U, const int* perm,
-                             const void* scales, const float* s_T, const float* table, float factor, void* codes, void* workspace, hipStream_t st)
+                             const void* scales, const float* s_T, const float* table, float factor, void* codes, void* workspace, size_t workspace_bytes, hipStream_t st)
 {
     GptqArgs a{};
     a.w = static_cast<const uint16_t*>(w);
@@ -573,16 +631,22 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     ws += align256((size_t)N * K * 4);
     a.q = reinterpret_cast<uint8_t*>(ws);
     ws += align256((size_t)N * K);
-    a.Np = (int)((N + 15) / 16 * 16);
-    a.e_pairs = ws;
-    ws += (size_t)a.Np * kOuter * 4;
-    a.u_pairs = ws;
-    ws += (size_t)K * kOuter * 4;
-    a.e_scales = reinterpret_cast<int*>(ws);
-    ws += (size_t)a.Np * (kOuter / kB) * 4;
-    a.u_scales = reinterpret_cast<int*>(ws);
-    ws += (size_t)K * (kOuter / kB) * 4;
     a.iperm = reinterpret_cast<int*>(ws);
+    ws += align256((size_t)K * 4);
+    a.Np = (int)((N + 15) / 16 * 16);
+    // Less room than fp4_workspace_bytes asks for: the update prepares its operands on the spot, with the same results (a sweep of [4096, 4096] 607 -> 783 us, of [1024, 4096] 445 -> 573).
+    const bool packed = workspace_bytes >= gptq_workspace_bytes(N, K);
+    if (packed) {
+        a.e_pairs = ws;
+        ws += (size_t)a.Np * kOuter * 4;
+        a.u_pairs = ws;
+        ws += (size_t)K * kOuter * 4;
+        a.e_scales = reinterpret_cast<int*>(ws);
+        ws += (size_t)a.Np * (kOuter / kB) * 4;
+        a.u_scales = reinterpret_cast<int*>(ws);
+    } else {
+        a.err = reinterpret_cast<float*>(ws);
+    }
     a.scales = static_cast<const uint8_t*>(scales);
     a.s_T = s_T;
     a.table = table;
@@ -605,20 +669,24 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
     }
     hipLaunchKernelGGL(gptq_rotate_gather_kernel, dim3((unsigned)N), dim3(256), row_lds, st, a);
     const unsigned row128 = (unsigned)((N + 127) / 128), row16 = (unsigned)((N + 15) / 16);
-    static LdsAttrOnce update_once;
+    static LdsAttrOnce update_once, unpacked_once;
     if (K > kOuter) {
-        const hipError_t le = update_once.ensure(reinterpret_cast<const void*>(gptq_update_kernel), kUpdateLds);
+        const hipError_t le = packed ? update_once.ensure(reinterpret_cast<const void*>(gptq_update_kernel<true>), kUpdateLds)
+                                     : unpacked_once.ensure(reinterpret_cast<const void*>(gptq_update_kernel<false>), kUpdateLdsUnpacked);
         if (le != hipSuccess) return le;
     }
     for (int o = 0; o < (int)K; o += kOuter) {
         const int oe = std::min(o + kOuter, (int)K);
         // the outer block itself: every workgroup takes 16 rows through the block's columns, four waves sweeping 64 of them at a
         // time, four pushing their errors onto the rest of the outer block, while others prepare the block's rows of U ...
-        const unsigned pack = (unsigned)((K - oe) / 16);
+        const unsigned pack = packed ? (unsigned)((K - oe) / 16) : 0u;
         if (fmt == 0) hipLaunchKernelGGL(gptq_outer_kernel<0>, dim3(row16 + pack), dim3(512), 0, st, a, o, oe, (int)row16);
         else hipLaunchKernelGGL(gptq_outer_kernel<1>, dim3(row16 + pack), dim3(512), 0, st, a, o, oe, (int)row16);
         // ... everything behind the outer block sees all of its errors in one pass
-        if (oe < (int)K) hipLaunchKernelGGL(gptq_update_kernel, dim3(row128 * (unsigned)((K - oe + 127) / 128)), dim3(256), kUpdateLds, st, a, oe);
+        if (oe == (int)K) break;
+        const dim3 tiles(row128 * (unsigned)((K - oe + 127) / 128));
+        if (packed) hipLaunchKernelGGL(gptq_update_kernel<true>, tiles, dim3(256), kUpdateLds, st, a, oe);
+        else hipLaunchKernelGGL(gptq_update_kernel<false>, tiles, dim3(256), kUpdateLdsUnpacked, st, a, oe);
     }
     hipLaunchKernelGGL(gptq_pack_kernel, dim3((unsigned)N), dim3(256), (size_t)K, st, a);
     return hipGetLastError();

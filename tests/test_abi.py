@@ -89,6 +89,14 @@ def test_gptq_workspaces_are_what_the_header_says():
     for K in (1, 16, 64, 128, 129, 200, 256, 272, 320, 384, 385, 512, 4096, 14336):
         Kp = (K + 127) // 128 * 128
         assert b.workspace_bytes(b.OP_GPTQ_PREPARE, 0, 0, K, b.MXFP4) == max(up(10 * K * K), 4 * Kp * Kp + 512 * Kp + 65536 + up(4 * K) + 256)
+    # the sweep: what it asks for, and the least it takes (one byte less is refused; nothing is launched here)
+    fake = 0x10000
+    call = lambda N, K, size, x: b.lib.fp4_gptq_quantize_weights(x, N, K, 32, b.MXFP4, fake, None, fake, fake, None, fake, size, 0, None)
+    for N, K in ((1, 576), (17, 1088), (128, 512), (4096, 4096)):
+        rows = (N + 15) // 16 * 16
+        least = up(4 * N * K) + up(N * K) + up(2048 * N) + up(4 * K)
+        assert b.workspace_bytes(b.OP_GPTQ, N, 0, K, b.MXFP4) == least + 2080 * (rows + K) - up(2048 * N)
+        assert call(N, K, least - 1, fake) == 6 and call(N, K, least, None) == 1   # (the workspace is looked at before w)
 
 
 def test_argument_validation_happens_before_any_launch(lib):

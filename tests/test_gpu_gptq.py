@@ -551,6 +551,28 @@ def test_update_behind_an_outer_block_at_the_edges_of_its_tiles(fp4, oracle, gpt
     assert diff.mean() <= 1e-3
 
 
+@pytest.mark.parametrize("fmt,b", [(MX, 1), (NV, 16)])
+@pytest.mark.parametrize("N,K", [(1, 576), (16, 512), (128, 640), (130, 1600), (40, 1088)])
+def test_sweep_in_the_least_workspace(fp4, fmt, b, N, K):
+    """Without room for the prepared operands of the update: the same codes, and nothing written behind the workspace."""
+    import torch
+    say(f"gptq least workspace N={N} K={K} fmt={fmt}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + K)
+    w = torch.randn(N, K, device="cuda", generator=g).bfloat16()
+    U = torch.triu(torch.randn(K, K, device="cuda", generator=g) * 0.02, 1) + torch.diag(0.5 + torch.rand(K, device="cuda", generator=g))
+    perm = torch.randperm(K, device="cuda", generator=g).int()
+    up = lambda n: (n + 255) // 256 * 256
+    full = fp4.workspace_bytes(fp4.OP_GPTQ, N, 0, K, fmt)
+    need = full - 2080 * ((N + 15) // 16 * 16 + K) + up(2048 * N)
+    room = torch.full((full + 65536,), 0xa5, dtype=torch.uint8, device="cuda")
+    want = fp4.fp4_gptq_quantize_weights(w, b, fmt, U, perm)
+    got = fp4.fp4_gptq_quantize_weights(w, b, fmt, U, perm, workspace=room[:need])
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(want, got) if x is not None)
+    assert bool((room[need:] == 0xa5).all())
+
+
 @pytest.mark.parametrize("log2_loud", [12, 40, -40])
 def test_update_with_channels_of_two_kinds_that_have_nothing_in_common(fp4, oracle, gptq, log2_loud):
     """H = D C D with channels of two kinds that C keeps apart, the one 2^log2_loud times as loud: the factor's columns are divided by D,
