@@ -1,5 +1,6 @@
 """Builds libfp4mr.so (the C-ABI library of HIP kernels) in-tree for gfx950 with hipcc, and _calls.so (the binding's compiled
-calls, host code only) with g++ against the installed torch.
+calls, host code only) with g++ against the installed torch.  The library needs neither torch nor g++ nor Python's headers; where one of
+them is missing, the binding goes without the compiled calls.
 
     python -m paper_2509_23202_amd.build
 
@@ -73,13 +74,15 @@ def build(verbose: bool = True) -> Path:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1, os.cpu_count() or 1)) as ex:
         calls = ex.submit(_build_calls)
         objs = list(ex.map(_compile, SOURCES))
-        calls.result()
     tmp = LIB.with_suffix(".so.tmp%d" % os.getpid())
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
     os.replace(tmp, LIB)
+    if calls.exception() is not None:
+        CALLS.unlink(missing_ok=True)   # (one of another library's entry points must not stay)
+        print(f"without {CALLS.name}, the binding's calls go through ctypes: {calls.exception()}", file=sys.stderr)
     if verbose:
         print(f"built {LIB} ({LIB.stat().st_size >> 10} KiB)")
     return LIB
