@@ -74,20 +74,20 @@ lib.fp4_set_option.argtypes = [_i32, _i32]
 lib.fp4_set_option.restype = _i32
 
 
+class Fp4mrError(RuntimeError):
+    def __init__(self, status: int):
+        self.status = status
+        super().__init__(f"fp4mr status {status}: {lib.fp4_status_string(status).decode()}")
+
+
 # The compiled form of the plain calls.  It answers None to everything else, and the Python below takes the call; without it (a
 # torch that it was not built against) Python takes them all.
 try:
     from . import _calls
     _calls.bind(*(ctypes.cast(f, _p).value for f in (lib.fp4_rotate_quantize, lib.fp4_quantize_weights, lib.fp4_rotate_quantize_dense, lib.fp4_gemm,
-                                                     lib.fp4_fused_linear, lib.fp4_w4a16_linear, lib.fp4_workspace_bytes, lib.fp4_packed_bytes)))
+                                                     lib.fp4_fused_linear, lib.fp4_w4a16_linear, lib.fp4_workspace_bytes, lib.fp4_packed_bytes)), Fp4mrError)
 except ImportError:
     _calls = None
-
-
-class Fp4mrError(RuntimeError):
-    def __init__(self, status: int):
-        self.status = status
-        super().__init__(f"fp4mr status {status}: {lib.fp4_status_string(status).decode()}")
 
 
 def _check(status: int) -> None:

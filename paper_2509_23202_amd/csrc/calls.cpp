@@ -3,8 +3,9 @@
 // marshalling in Python took as long as the launch itself (one token against one projection: 6.8 us a call, now 4.7; sixteen tokens through a layer, eight launches: 64, now 44).
 //
 // Every function returns None for what is not the plain case (a Tensor subclass, a caller's own output or workspace, anything
-// that Python code under a mode should see, an argument of another type, a call that the library refuses): the Python path behind it then
-// takes the call from the start, and raises what it always raised.
+// that Python code under a mode should see, an argument of another type) and for a call that the library refuses before it launches
+// anything: the Python path behind it then takes the call from the start, and raises what it always raised.  An error of the device
+// is raised here: the launch has reported it and forgotten it, so that a second try would succeed.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -32,6 +33,7 @@ struct Entry {
     decltype(&fp4_workspace_bytes) workspace_bytes;
     decltype(&fp4_packed_bytes) packed_bytes;
 } entry;
+PyObject* error;   // the binding's exception, called with a status
 
 // an argument that is a plain Python int in range
 bool integer(PyObject* o, int64_t& v)
@@ -65,6 +67,17 @@ void* stream() { return c10::hip::getCurrentHIPStream(c10::hip::current_device()
 
 bool plain() { return !at::impl::torch_function_mode_enabled(); }
 
+// what a call returns whose status is not FP4MR_OK
+PyObject* refused(fp4mr_status_t status)
+{
+    if (status != FP4MR_ERR_DEVICE) Py_RETURN_NONE;
+    if (PyObject* const e = PyObject_CallFunction(error, "i", (int)status)) {
+        PyErr_SetObject(reinterpret_cast<PyObject*>(Py_TYPE(e)), e);
+        Py_DECREF(e);
+    }
+    return nullptr;
+}
+
 // quantize(x, had_block, fmt, flags, kind, rot): kind 0 rotate_quantize, 1 quantize_weights, 2 rotate_quantize_dense
 PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n)
 {
@@ -92,7 +105,7 @@ PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n)
     if (kind == 2) status = entry.rotate_quantize_dense(px, rows, K, (int)b, pr, (fp4mr_fmt_t)fmt, pc, ps, ts, ws, need, (uint32_t)flags, st);
     else status = (kind == 1 ? entry.quantize_weights : entry.rotate_quantize)(px, rows, K, (int)b, (fp4mr_fmt_t)fmt, pc, ps, ts, ws, need, (uint32_t)flags, st);
     Py_END_ALLOW_THREADS;
-    if (status != FP4MR_OK) Py_RETURN_NONE;
+    if (status != FP4MR_OK) return refused(status);
     PyObject* const out = PyTuple_New(3);
     if (!out) return nullptr;
     PyTuple_SET_ITEM(out, 0, THPVariable_Wrap(codes));
@@ -128,7 +141,7 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n)
     Py_BEGIN_ALLOW_THREADS;
     status = entry.gemm(pac, pas, pat, pwc, pws, pwt, M, N, K, (fp4mr_fmt_t)fmt, po, pw, need, (uint32_t)flags, st);
     Py_END_ALLOW_THREADS;
-    if (status != FP4MR_OK) Py_RETURN_NONE;
+    if (status != FP4MR_OK) return refused(status);
     return THPVariable_Wrap(out);
     END_HANDLE_TH_ERRORS
 }
@@ -151,17 +164,17 @@ PyObject* linear(PyObject*, PyObject* const* args, Py_ssize_t n)
     Py_BEGIN_ALLOW_THREADS;
     status = (weight_only ? entry.w4a16_linear : entry.fused_linear)(px, M, K, (int)b, pwc, pws, N, (fp4mr_fmt_t)fmt, po, (uint32_t)flags | FP4MR_W_LAYOUT_GEMM, st);
     Py_END_ALLOW_THREADS;
-    if (status != FP4MR_OK) Py_RETURN_NONE;
+    if (status != FP4MR_OK) return refused(status);
     return THPVariable_Wrap(out);
     END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses of the eight entry points, in the order of Entry)
+// bind(addresses of the eight entry points, in the order of Entry, and the exception)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n)
 {
     constexpr Py_ssize_t count = sizeof(Entry) / sizeof(void*);
-    if (n != count) {
-        PyErr_SetString(PyExc_TypeError, "bind() takes eight addresses");
+    if (n != count + 1 || !PyCallable_Check(args[count])) {
+        PyErr_SetString(PyExc_TypeError, "bind() takes eight addresses and an exception");
         return nullptr;
     }
     void* p[count];
@@ -174,6 +187,8 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n)
     }
     static_assert(sizeof(p) == sizeof(entry), "one address per entry point");
     std::memcpy(&entry, p, sizeof(entry));
+    Py_INCREF(args[count]);
+    Py_XSETREF(error, args[count]);
     Py_RETURN_NONE;
 }
 

@@ -61,6 +61,63 @@ def test_other_calls_are_handed_on():
             refused()
 
 
+@pytest.mark.gpu
+def test_an_error_of_the_device_is_raised_at_once(monkeypatch):
+    """Entry points that report one without having touched the device: each is called once, and the calls raise."""
+    import ctypes
+    names = ["fp4_rotate_quantize", "fp4_quantize_weights", "fp4_rotate_quantize_dense", "fp4_gemm", "fp4_fused_linear", "fp4_w4a16_linear",
+             "fp4_workspace_bytes", "fp4_packed_bytes"]
+    functions = [getattr(fp4.lib, name) for name in names]
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    called, device = [], 7
+
+    def stub(name):
+        f = getattr(fp4.lib, name)
+        return ctypes.CFUNCTYPE(f.restype, *f.argtypes)(lambda *args: called.append(name) or device)
+
+    stubs = [stub(name) for name in names[:6]]
+    assert fp4.lib.fp4_status_string(device).decode().startswith("HIP runtime error")
+    x, w = operands(fp4.MXFP4, 2, 256, 1), operands(fp4.MXFP4, 32, 256, 2)
+    rot = torch.eye(64).bfloat16().cuda()
+    qx, qw = fp4.fp4_rotate_quantize(x, 32, fp4.MXFP4, flags=fp4.LAYOUT_GEMM), fp4.fp4_quantize_weights(w, 32, fp4.MXFP4, flags=fp4.LAYOUT_GEMM)
+    torch.cuda.synchronize()
+    calls = [lambda: fp4.fp4_rotate_quantize(x, 32, fp4.MXFP4), lambda: fp4.fp4_quantize_weights(w, 32, fp4.MXFP4),
+             lambda: fp4.fp4_rotate_quantize_dense(x, rot, fp4.MXFP4), lambda: fp4.fp4_gemm(*qx, *qw, 2, 32, 256, fp4.MXFP4, flags=G),
+             lambda: fp4.fp4_fused_linear(x, 32, qw[0], qw[1], 32), lambda: fp4.fp4_w4a16_linear(x, 32, qw[0], qw[1], 32)]
+    try:
+        fp4._calls.bind(*map(address, stubs + functions[6:]), fp4.Fp4mrError)
+        for call in calls:
+            with pytest.raises(fp4.Fp4mrError) as raised:
+                call()
+            assert raised.value.status == device
+    finally:
+        fp4._calls.bind(*map(address, functions), fp4.Fp4mrError)
+    assert called == names[:6]
+    assert fp4.fp4_fused_linear(x, 32, qw[0], qw[1], 32).shape == (2, 32)
+
+
+@pytest.mark.gpu
+def test_calls_under_a_function_mode_are_handed_on():
+    """A mode sees the tensor functions of the Python form, and the results are the same."""
+    class Mode(torch.overrides.TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.seen = set()
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.seen.add(getattr(func, "__name__", str(func)))
+            return func(*args, **(kwargs or {}))
+
+    x, w = operands(fp4.MXFP4, 2, 256, 1), operands(fp4.MXFP4, 32, 256, 2)
+    qw = fp4.fp4_quantize_weights(w, 32, fp4.MXFP4, flags=fp4.LAYOUT_GEMM)
+    for call in (lambda: fp4.fp4_rotate_quantize(x, 32, fp4.MXFP4), lambda: fp4.fp4_fused_linear(x, 32, qw[0], qw[1], 32)):
+        want = flat(call())
+        with Mode() as mode:
+            got = flat(call())
+        assert {"data_ptr", "new_empty"} <= mode.seen
+        assert all(torch.equal(s, t) for s, t in zip(got, want))
+
+
 def test_cpu_tensors_are_refused():
     x = torch.zeros(2, 256, dtype=torch.bfloat16)
     for call in (lambda: fp4.fp4_rotate_quantize(x, 32, fp4.MXFP4), lambda: fp4.fp4_fused_linear(x, 32, x, x, 32)):
