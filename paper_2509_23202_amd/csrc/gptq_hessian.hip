@@ -1,20 +1,21 @@
 // Hessian of a layer from calibration rows (arXiv 2509.23202, Section 4 "Standard GPTQ": the second-order information of
 // ||X What - X W||^2 is X^T X; Section 4.1 "Ingredient 3": of the ROTATED inputs X H_b).
 //
-// The rows are rotated FIRST and every rotated value is kept to 23 or 24 bits, so that an entry's error is relative to
+// The rows are rotated FIRST and every rotated value is kept to 24 bits (few rows) or 23, so that an entry's error is relative to
 // sqrt(h_ii h_jj) of its own two channels.  (Rotating the finished X^T X is faster, but where channels of a block have
 // something in common most rotated channels are small differences of large sums: with an offset of 100 under unit noise
 // the entries were off by 1 % of that scale, and diagonal entries could come out negative.)
-//   many rows  hessian_pack_kernel   X -> the rotated rows as two fp16 parts, scaled by block, in the workspace as the MFMA takes them
+//   many rows  hessian_pack_kernel   X -> the rotated rows as two fp16 parts, scaled by column, in the workspace as the MFMA takes them
 //              hessian_tile_kernel   X'^T X' on the fp16 MFMA: the three products above 2^-23 of the whole
 //              hessian_part_kernel   the same for the tiles beyond whole rounds of the chip
 //   few rows   hessian_rotate_kernel X -> the rotated rows in fp32, in the workspace, eight rows of a column side by side
 //              hessian_split_kernel  X'^T X' on the bf16 MFMA, both factors split into three bf16 parts: the six products above
 //                                    2^-24 of the whole
-// 8192 rows at K = 4096: 0.44 ms (0.86 with six bf16 products, 4.15 on the fp32 MFMA over both triangles).  Largest error over
-// sqrt(h_ii h_jj), T = 8192, b = 128, fp32 MFMA -> bf16 -> fp16: normal rows with loud channels 5.4e-6 -> 1.1e-6 -> 2.1e-7, offset 30
-// 3.5e-5 -> 7e-7 -> 1.2e-7, offset 100 3.3e-6 -> 5e-7 -> 1.4e-7, one factor per block and 0.2 % of noise 4.8e-6 -> 7e-7 -> 1.4e-7 (the last
-// step for adding up four sums of 32 rows before they meet the large one).
+// 8192 rows at K = 4096: 0.45 ms (0.86 with six bf16 products, 4.15 on the fp32 MFMA over both triangles).  Largest error over
+// sqrt(h_ii h_jj), T = 8192, b = 128, K = 1024 / 4096, bf16 -> fp16: normal rows with loud channels 9.3e-7 / 1.0e-6 -> 2.0e-7 / 5.6e-7, offset
+// 30 9.5e-7 / 8.9e-7 -> 1.2e-7 / 4.6e-7, offset 100 6.2e-7 / 7.6e-7 -> 1.0e-7 / 3.6e-7, a channel of every 64th row 3000 times as large
+// 9.2e-7 / 1.0e-6 -> 3.0e-7 / 5.2e-7 (for adding up four sums of 32 rows before they meet the large one).  Of one row alone, with nothing to
+// add up, 1.1e-7 -> 3.3e-7.
 // Without rotation (b == 1) the values are bf16 and their products exact in fp32: hessian_kernel, straight from X.
 // The matrix is symmetric: only tiles on and below the diagonal are computed, each is stored twice.
 #include "device_util.hpp"
@@ -544,10 +545,10 @@ __device__ __forceinline__ void column_ups(const uint8_t* exps, float (&up)[16])
 
 // what a lane needs of the exponents of 128 rows and 128 columns at `exps`: of row l16 of a block, of columns 4 q .. 4 q + 3 of a block
 __device__ __forceinline__ int row_exponent(const uint8_t* exps, int block) { return exps[block * 16 + (threadIdx.x & 15)]; }
-__device__ __forceinline__ v4i four_exponents(uint32_t w) { return v4i{(int)(w & 255u), (int)(w >> 8 & 255u), (int)(w >> 16 & 255u), (int)(w >> 24)}; }
 __device__ __forceinline__ v4i col_exponents(const uint8_t* exps, int block)
 {
-    return four_exponents(*reinterpret_cast<const uint32_t*>(exps + block * 16 + 4 * (threadIdx.x >> 4 & 3)));
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(exps + block * 16 + 4 * (threadIdx.x >> 4 & 3));
+    return v4i{(int)(w & 255u), (int)(w >> 8 & 255u), (int)(w >> 16 & 255u), (int)(w >> 24)};
 }
 
 // a thread's sixteen values into the stage at dst, its blocks `pitch` bytes apart
@@ -624,8 +625,8 @@ __device__ __forceinline__ void store_block(const HessArgs& a, int row, int col,
 
 // A tile of 128 x 128, a 64 x 64 quarter per wave, a stage at a time, copied into LDS as it lies in the workspace, the next one
 // meanwhile.  Two workgroups per compute unit, so that one's barrier and LDS reads run under the
-// other's MFMAs.  Bound at K = 4096, 512 tiles over 8192 rows, 375 us: without the copies into LDS 305, at the 1.6 PFLOP/s of a large
-// bf16 product 257.  (Operands of the next stage read into registers ahead of its barrier: 3 % slower.)
+// other's MFMAs.  Bound at K = 4096, 512 tiles over 8192 rows, some 390 us (375 with an exponent for sixteen columns, of
+// which without the copies into LDS 305): at the 1.6 PFLOP/s of a large bf16 product 257.  (Operands of the next stage read into registers ahead of its barrier: 3 % slower.)
 constexpr int kTile = 4, kTileStage = 16 * kPairBytes, kTileLds = 2 * (kTileStage + 1024);   // 16-wide blocks per wave side; stages and their exponents
 __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
 {
@@ -704,7 +705,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
 {
     constexpr int SIDE = 16 * NT, SUB = kT / SIDE;
     __shared__ __attribute__((aligned(16))) char St[16 * kPairBytes];   // the stages rotated on the spot, then the waves' sums
-    __shared__ __attribute__((aligned(16))) uint8_t Sc[2 * kT];
+    __shared__ __attribute__((aligned(16))) uint8_t Sc[2 * kT], Ex[4][2 * kT];   // exponents of rows and columns: of a stage rotated on the spot; a wave's group
     __shared__ __attribute__((aligned(16))) float red[4][kT];
     static_assert(sizeof(St) >= 4 * 2 * NT * 64 * sizeof(v4f), "two rows of blocks of the sums fit");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
@@ -718,6 +719,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
     const int r0 = ti * SIDE, c0 = tj * SIDE, kb = a.K / 16;
     const int groups = (a.stages + kGroup - 1) / kGroup, share = (groups + 3) / 4;
     const int g_begin = wave * share, g_end = min(groups, g_begin + share);
+    const uint32_t exps_at = (uint32_t)min((lane < 32 ? r0 : c0) + 4 * (lane & 31), a.K - 4);
 
     PairSums<NT> sums;
     sums.clear();
@@ -765,14 +767,10 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                     fetch_col(g_begin * kGroup + d, d, k, i);
                 }
         for (int g = g_begin; g < g_end; ++g) {
-            int fr[NT];
-            uint32_t fc[NT];
-            const uint8_t* const exps = a.exps + (int64_t)g * a.K;
-#pragma unroll
-            for (int i = 0; i < NT; ++i) {
-                fr[i] = exps[min(r0 / 16 + i, kb - 1) * 16 + l16];
-                fc[i] = *reinterpret_cast<const uint32_t*>(exps + min(c0 / 16 + i, kb - 1) * 16 + 4 * q);
-            }
+            // (into LDS: in registers from here to the group's end, or fetched there, they cost more)
+            wait_lgkmcnt0();
+            const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(a.exps + (int64_t)g * a.K, 0, a.K, 0x00020000);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)Ex[wave], 4, exps_at, 0, 0, 0);
             if constexpr (AHEAD == kGroup) {
 #pragma unroll
                 for (int d = 0; d < kGroup; ++d) {
@@ -788,10 +786,17 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                 }
             } else {
                 const int end = min(kGroup, a.stages - g * kGroup);
-                multiply(first, 0, g * kGroup + 1);
-                for (int d = 1; d < end; ++d) multiply(later, 0, g * kGroup + d + 1);
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) sums.t[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+                for (int d = 0; d < end; ++d) multiply(later, 0, g * kGroup + d + 1);
             }
-            sums.scale([&](int i) { return fr[i] - a.bias; }, [&](int j) { return four_exponents(fc[j]); });
+            // the exponents have landed: at least this many fetches were issued behind them, and none is moved over these lines
+            asm volatile("" ::: "memory");
+            wait_vmcnt<AHEAD * 4 * NT>();
+            asm volatile("" ::: "memory");
+            sums.scale([&](int i) { return row_exponent(Ex[wave], i) - a.bias; }, [&](int j) { return col_exponents(Ex[wave] + kT, j); });
         }
     }
     for (int64_t row = (int64_t)a.stages * 32; row < a.T; row += 32) {
@@ -848,10 +853,11 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
     // whole tile's time (K = 4096: 528 tiles for 512 slots)
     const int tiles = a.nt * (a.nt + 1) / 2, slots = 2 * compute_units(), rem = tiles % slots;
     // Pairs of halves on the fp16 MFMA from 1408 rows, or from 1100 if there are tiles enough: fewer products, but one launch more and
-    // 32 rows or more rotated on the spot.  The other way against this one, us: T = 1200, K = 1024 / 1280 / 1664 37 / 44 / 63 against
-    // 38 / 40 / 45; T = 1500, K = 512 / 1024 28 / 42 against 23 / 40.  Not below, where it would still be the faster one (T = 768 / 1024, K = 4096
-    // 113 / 139 against 90 / 101): of rows very different in size its error is the larger one there (rms over sqrt(h_ii h_jj), b = 16, rows of
-    // 2^-20 .. 2^20: T = 768 2.7e-8 against 3.0e-8, 1024 2.8e-8 against 2.9e-8, 1100 3.0e-8 against 2.8e-8), as those of few sums of 32 rows are.
+    // 32 rows or more rotated on the spot.  The other way against this one, us: T = 1200, K = 1024 / 1280 / 1664 37 / 44 / 62 against
+    // 37 / 39 / 44; T = 1408 and 1500, K = 512 25 and 28 against 21, K = 1024 39 and 43 against 38.  Not below, where it would still be the
+    // faster one (T = 768 / 1024, K = 4096 112 / 135 against 87 / 98): of rows very different in size its error is the larger one there (rms over
+    // sqrt(h_ii h_jj), b = 16, rows of 2^-20 .. 2^20: T = 768 2.7e-8 against 3.0e-8, 1024 2.8e-8 against 2.9e-8, 1100 3.0e-8 against 2.8e-8), as
+    // those of few sums of 32 rows are.
     if (b > 1 && (T >= 1408 || (T >= 1100 && tiles > 50))) {
         // (a stage takes 128 K bytes, a group of four K for their exponents; what the 4 T K bytes do not hold is rotated on the spot)
         a.stages = (int)((T * 16 - 3) / 513);
@@ -860,8 +866,8 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
         a.bias = kPairBias + (b == 16 ? 4 : b == 32 ? 5 : b == 64 ? 6 : 7);
         hipLaunchKernelGGL(hessian_pack_kernel, dim3((unsigned)((a.stages + kGroup - 1) / kGroup), (unsigned)a.nt), dim3(256), 0, st, a);
         // The tiles beyond whole rounds, up to one per compute unit, in parts of 64 x 64, or of 32 x 32 if those leave most of the chip
-        // idle.  8192 rows, left whole / in 64 / in 32, us: K = 512 (10 left) 248 / 96 / 44, 768 (21) - / 94 / 66, 1024 (36) 243 / 93 / 93,
-        // 1664 (91) 251 / 127 / 179, 2048 (136) 253 / 202 / 234, 2560 (210) 259 / 250 / 356, 3072 (300) 328 / 332 / 490, 4096 (16) 590 / 483 / 443
+        // idle.  8192 rows, left whole / in 64 / in 32, us: K = 512 (10 left) 257 / 103 / 46, 768 (21) 257 / 102 / 70, 1024 (36) 255 / 99 / 100,
+        // 1664 (91) 264 / 135 / 183, 2048 (136) 264 / 213 / 234, 2560 (210) 271 / 261 / 360, 3072 (300) 350 / 350 / 515, 4096 (16) 624 / 517 / 468
         const int small = rem > slots / 2 ? 0 : rem;
         a.full = tiles - small;
         if (a.full) {
