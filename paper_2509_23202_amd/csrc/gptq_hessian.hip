@@ -331,13 +331,32 @@ __global__ __launch_bounds__(256) void hessian_rotate_kernel(HessArgs a)
     }
 }
 
+// 16 x 16 sums in the MFMA's output order -- a lane holds columns col .. col + 3 of a row -- stored with their mirror image; of a
+// block on the diagonal the lower half counts (K is a multiple of 16)
+__device__ __forceinline__ void store_block(const HessArgs& a, int row, int col, bool cut, v4f s)
+{
+    if (row >= a.K || col >= a.K) return;
+    float* const own = a.H + (int64_t)row * a.K + col;
+    float* const mirror = a.H + (int64_t)col * a.K + row;
+    if (!cut) {
+        v4f* const d = reinterpret_cast<v4f*>(own);
+        *d = a.accumulate ? *d + s : s;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (cut && col + v <= row) own[v] = a.accumulate ? own[v] + s[v] : s[v];
+        float* const m = mirror + (int64_t)v * a.K;
+        if (!cut || col + v < row) *m = a.accumulate ? *m + s[v] : s[v];
+    }
+}
+
 // A tile of 2 W x 2 W, a W x W quarter per wave, 32 rows of X' at a time: split and written to LDS in the MFMA's operand order
 // (lane (r, q) of a 16-wide block: column r, rows 8 q .. 8 q + 7), the next 32 rows fetched meanwhile.  The products of 32 rows
 // are summed from zero, the largest apart from the five others (the MFMA cuts off what an addition leaves over, the vector
 // adder rounds), and added to the accumulator once.  The column operand is the MFMA's A, so that a lane
 // owns four neighbouring columns of a row of H.
 // Bound at W = 64: a wave issues 96 MFMAs (1536 cycles) and 370 vector instructions (1480, half of them the split) per stage, and
-// two workgroups per compute unit overlap the two in part: 512 tiles over 8192 rows 0.70 ms, 1.2 PFLOP/s.
+// two workgroups per compute unit overlap the two in part: 512 tiles over 1099 rows 127 us, 0.87 PFLOP/s.
 template <int W>
 __global__ __launch_bounds__(256, 2) void hessian_split_kernel(HessArgs a)
 {
@@ -482,31 +501,12 @@ __global__ __launch_bounds__(256, 2) void hessian_split_kernel(HessArgs a)
         multiply(0);
     }
     if (idle) return;
-    // a lane holds columns 4 q .. 4 q + 3 of row l16 of every 16 x 16 block; of the diagonal blocks the lower half counts, and is
-    // mirrored like all the rest (K is a multiple of 16)
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-        const int row = r0 + (wr + i) * 16 + l16;
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int col = c0 + (wc + j) * 16 + 4 * q;
-            if (row >= a.K || col >= a.K || (diag && wr + i < wc + j)) continue;
-            const bool cut = diag && wr + i == wc + j;
-            const v4f s = acc[i][j] * a.out_scale;
-            float* const own = a.H + (int64_t)row * a.K + col;
-            float* const mirror = a.H + (int64_t)col * a.K + row;
-            if (!cut) {
-                v4f* const d = reinterpret_cast<v4f*>(own);
-                *d = a.accumulate ? *d + s : s;
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if (cut && col + v <= row) own[v] = a.accumulate ? own[v] + s[v] : s[v];
-                float* const m = mirror + (int64_t)v * a.K;
-                if (!cut || col + v < row) *m = a.accumulate ? *m + s[v] : s[v];
-            }
-        }
-    }
+        for (int j = 0; j < NT; ++j)
+            if (!diag || wr + i >= wc + j)
+                store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, acc[i][j] * a.out_scale);
 }
 
 // ---------------------------------------------------------------- b > 1, many rows
@@ -602,25 +602,6 @@ __device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0
     column_exponents(top, red, exps);
     column_ups(exps, up);
     put_row(v, up, dst, kPairBytes);
-}
-
-// 16 x 16 sums in the MFMA's output order -- a lane holds columns col .. col + 3 of a row -- stored with their mirror image; of a
-// block on the diagonal the lower half counts (K is a multiple of 16)
-__device__ __forceinline__ void store_block(const HessArgs& a, int row, int col, bool cut, v4f s)
-{
-    if (row >= a.K || col >= a.K) return;
-    float* const own = a.H + (int64_t)row * a.K + col;
-    float* const mirror = a.H + (int64_t)col * a.K + row;
-    if (!cut) {
-        v4f* const d = reinterpret_cast<v4f*>(own);
-        *d = a.accumulate ? *d + s : s;
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        if (cut && col + v <= row) own[v] = a.accumulate ? own[v] + s[v] : s[v];
-        float* const m = mirror + (int64_t)v * a.K;
-        if (!cut || col + v < row) *m = a.accumulate ? *m + s[v] : s[v];
-    }
 }
 
 // A tile of 128 x 128, a 64 x 64 quarter per wave, a stage at a time, copied into LDS as it lies in the workspace, the next one
@@ -884,9 +865,10 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
         a.in_scale = b >= 64 ? 0.125f : 0.25f;
         a.out_scale = 1.0f / ((float)b * a.in_scale * a.in_scale);
         hipLaunchKernelGGL(hessian_rotate_kernel, dim3((unsigned)((T + 7) / 8), (unsigned)((K + kRotCols - 1) / kRotCols)), dim3(256), 0, st, a);
-        // in parts of 64 x 64, or of 32 x 32 where they are so few that those have compute units to themselves.  8192 rows, the tiles
-        // left whole / in 64 / in 32, us: K = 4096 (16 left) 1150 / 962 / 862, 1024 (36) 515 / 207 / 160, 1408 (66) 522 / 289 / 239,
-        // 1664 (91) 525 / 295 / 300, 2048 (136) 519 / 360 / 401, 2944 (276) 714 / 622 / 764, 3328 (351) 725 / 737 / 961
+        // in parts of 64 x 64, or of 32 x 32 where they are so few that those have compute units to themselves.  1000 rows, the tiles
+        // left whole / in 64 / in 32, us: K = 512 (10 left) 80 / 37 / 21, 1024 (36) 88 / 40 / 32, 1408 (66) 92 / 52 / 42, 1664 (91) 92 / 54 / 50,
+        // 2048 (136) 90 / 63 / 65, 2944 (276) 117 / 97 / 111, 3328 (351) 118 / 111 / 134, 3712 (435) 119 / 130 / 165, 4096 (16) 179 / 155 / 139;
+        // 256 rows: 1664 36 / 22 / 19, 2048 37 / 26 / 24, 3328 52 / 45 / 47
         const int parts = rem > slots * 5 / 8 ? 0 : rem > slots / 6 ? 32 : 16, small = parts ? rem : 0;
         a.full = tiles - small;
         if (a.full) hipLaunchKernelGGL(hessian_split_kernel<64>, dim3((unsigned)a.full), dim3(256), 0, st, a);
