@@ -35,7 +35,7 @@ struct GptqArgs {
     char* e_pairs;          // errors, [stage][16 rows]
     int* e_scales;          // [kOuter / kB][rows]: their exponents: of a row's errors of 64 columns
     char* u_pairs;          // rows of U, [stage][16 columns]
-    int* u_scales;          // [kOuter / kB][K]: of a column's entries in 64 rows
+    float* u_scales;        // [kOuter / kB][K]: of a column's entries in 64 rows, as factors
     float* err;             // ... or, in a workspace without room for those, the errors as they are, [N, kOuter]; else null
     int Np;                 // N rounded up to 16
     const uint8_t* scales;  // [N,K/G] canonical
@@ -209,7 +209,7 @@ __device__ __forceinline__ void pack_u(const GptqArgs& a, int o, int cb, const f
     float v[2][8];
     factor_rows(a, o, 64 * wave, cb * 16 + l16, Rp, v);
     const uint32_t e = put_pairs(v, a.u_pairs + pairs_at(2 * wave, a.K / 16, cb), pairs_at(1, a.K / 16, 0));
-    if (lane < 16) a.u_scales[wave * a.K + cb * 16 + l16] = (int)e;
+    if (lane < 16) a.u_scales[wave * a.K + cb * 16 + l16] = pair_column(e);
 }
 
 constexpr int kWStride = kOuter + 4;   // floats per row of working weights in LDS: rows start four banks apart
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(512, 4) void gptq_outer_kernel(GptqArgs a, int o, i
 // contraction, [N x 512] . [512 x columns], of the pairs of halves that the outer kernel left.  A row's errors have scales of
 // their own (rows do not interact), and so have a column's entries of U; 64 terms are added to the accumulator at a time.
 // 128 x 128 output tile per workgroup, a 64 x 64 quarter per wave, a stage of 32 terms copied into LDS while the one before is
-// multiplied; two workgroups per compute unit.  [6144, 4096] behind its first outer block 92 us (157 with six bf16 products of
+// multiplied; two workgroups per compute unit.  [6144, 4096] behind its first outer block 95 us (157 with six bf16 products of
 // operands that every workgroup split for itself, 308 on the fp32 MFMA), of which wp is 24 at the rate of a large copy; codes that differ from
 // a sweep in 64 bits, 32 layers of K = 2048 and 4096: 9616 of 50 million (9830 with the bf16 products).
 constexpr int kUpdateStage = 16 * kPairBytes;   // 8 row blocks, then 8 column blocks
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
 {
     constexpr int T = 128, NT = 4;
     extern __shared__ __attribute__((aligned(1024))) char St[];
-    int* const Sc = reinterpret_cast<int*>(St + 2 * kUpdateStage);   // exponents for two groups of 64 terms: of 128 rows, of 128 columns
+    int* const Sc = reinterpret_cast<int*>(St + 2 * kUpdateStage);   // for two groups of 64 terms: exponents of 128 rows, factors of 128 columns
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int wr = (wave >> 1) * NT, wc = (wave & 1) * NT;   // first block of rows / columns of the wave's quarter
     // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of tiles, which share rows
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
     PairSums<NT> sums;
     sums.clear();
     auto scale_sums = [&](const int* sc) {
-        sums.scale([&](int i) { return sc[(wr + i) * 16 + l16] - kPairBias; }, [&](int j) { return *reinterpret_cast<const v4i*>(sc + 128 + (wc + j) * 16 + 4 * q); });
+        sums.scale([&](int i) { return sc[(wr + i) * 16 + l16] - kPairRow; }, [&](int j) { return *reinterpret_cast<const v4f*>(sc + 128 + (wc + j) * 16 + 4 * q); });
     };
     if constexpr (PACKED) {
         const int row_blocks = a.Np / 16, col_blocks = a.K / 16;
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(256, 2) void gptq_update_kernel(GptqArgs a, int c_b
                     factor_rows(a, o, j0, min(c0 + (block - 8) * 16 + l16, a.K - 1), Rp, v);
                 }
                 const uint32_t e = put_pairs(v, St + block * kPairBytes, kUpdateStage);
-                if (lane < 16) Sc[block * 16 + l16] = (int)e;
+                if (lane < 16) Sc[block * 16 + l16] = block < 8 ? (int)e : __float_as_int(pair_column(e));
             }
             __syncthreads();
             sums.multiply<true>(St + wr * kPairBytes, St + (8 + wc) * kPairBytes);
@@ -643,7 +643,7 @@ hipError_t launch_gptq_sweep(const void* w, int64_t N, int64_t K, int b, int fmt
         ws += (size_t)K * kOuter * 4;
         a.e_scales = reinterpret_cast<int*>(ws);
         ws += (size_t)a.Np * (kOuter / kB) * 4;
-        a.u_scales = reinterpret_cast<int*>(ws);
+        a.u_scales = reinterpret_cast<float*>(ws);
     } else {
         a.err = reinterpret_cast<float*>(ws);
     }

@@ -51,7 +51,7 @@ struct HessArgs {
     int parts;          // ... each of the others is shared by this many
     int chunk;          // rows of X per part (multiple of kRows)
     float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b (few rows)
-    int bias;           // b > 1, many rows: what a product's exponent is less than those of its two columns, 1 / b included
+    int row_step;       // b > 1, many rows: kPairRow, and the exponent of b
 };
 
 // p-th tile of the lower triangle (row >= col), counted super-row by super-row
@@ -545,10 +545,10 @@ __device__ __forceinline__ void column_ups(const uint8_t* exps, float (&up)[16])
 
 // what a lane needs of the exponents of 128 rows and 128 columns at `exps`: of row l16 of a block, of columns 4 q .. 4 q + 3 of a block
 __device__ __forceinline__ int row_exponent(const uint8_t* exps, int block) { return exps[block * 16 + (threadIdx.x & 15)]; }
-__device__ __forceinline__ v4i col_exponents(const uint8_t* exps, int block)
+__device__ __forceinline__ v4f col_factors(const uint8_t* exps, int block)
 {
     const uint32_t w = *reinterpret_cast<const uint32_t*>(exps + block * 16 + 4 * (threadIdx.x >> 4 & 3));
-    return v4i{(int)(w & 255u), (int)(w >> 8 & 255u), (int)(w >> 16 & 255u), (int)(w >> 24)};
+    return v4f{pair_column(w & 255u), pair_column(w >> 8 & 255u), pair_column(w >> 16 & 255u), pair_column(w >> 24)};
 }
 
 // a thread's sixteen values into the stage at dst, its blocks `pitch` bytes apart
@@ -643,7 +643,7 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
     PairSums<NT> sums;
     sums.clear();
     auto scale_sums = [&](const uint8_t* exps) {
-        sums.scale([&](int i) { return row_exponent(exps, wr + i) - a.bias; }, [&](int j) { return col_exponents(exps + kT, wc + j); });
+        sums.scale([&](int i) { return row_exponent(exps, wr + i) - a.row_step; }, [&](int j) { return col_factors(exps + kT, wc + j); });
     };
     if (stages > 0) {
         issue(0);
@@ -777,7 +777,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
             asm volatile("" ::: "memory");
             wait_vmcnt<AHEAD * 4 * NT>();
             asm volatile("" ::: "memory");
-            sums.scale([&](int i) { return row_exponent(Ex[wave], i) - a.bias; }, [&](int j) { return col_exponents(Ex[wave] + kT, j); });
+            sums.scale([&](int i) { return row_exponent(Ex[wave], i) - a.row_step; }, [&](int j) { return col_factors(Ex[wave] + kT, j); });
         }
     }
     for (int64_t row = (int64_t)a.stages * 32; row < a.T; row += 32) {
@@ -795,7 +795,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
                 cols[0][k][i] = *(reinterpret_cast<const v8h*>(St + (8 + bc + i) * kPairBytes + k * 1024) + lane);
             }
         multiply(first, 0, -1);
-        sums.scale([&](int i) { return row_exponent(Sc, br + i) - a.bias; }, [&](int j) { return col_exponents(Sc + kT, bc + j); });
+        sums.scale([&](int i) { return row_exponent(Sc, br + i) - a.row_step; }, [&](int j) { return col_factors(Sc + kT, bc + j); });
     }
     v4f* const all = reinterpret_cast<v4f*>(St);   // [wave][two rows of blocks][lane]
 #pragma unroll
@@ -844,7 +844,7 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
         a.stages = (int)((T * 16 - 3) / 513);
         a.planes = static_cast<char*>(workspace);
         a.exps = reinterpret_cast<uint8_t*>(a.planes + (int64_t)a.stages * 128 * K);
-        a.bias = kPairBias + (b == 16 ? 4 : b == 32 ? 5 : b == 64 ? 6 : 7);
+        a.row_step = kPairRow + (b == 16 ? 4 : b == 32 ? 5 : b == 64 ? 6 : 7);
         hipLaunchKernelGGL(hessian_pack_kernel, dim3((unsigned)((a.stages + kGroup - 1) / kGroup), (unsigned)a.nt), dim3(256), 0, st, a);
         // The tiles beyond whole rounds, up to one per compute unit, in parts of 64 x 64, or of 32 x 32 if those leave most of the chip
         // idle.  8192 rows, left whole / in 64 / in 32, us: K = 512 (10 left) 257 / 103 / 46, 768 (21) 257 / 102 / 70, 1024 (36) 255 / 99 / 100,

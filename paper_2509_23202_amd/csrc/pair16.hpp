@@ -13,11 +13,13 @@ constexpr int kPairBytes = 2048;
 // A value y is (h + l) 2^(e - 14), e an exponent that some neighbourhood shares and in which |y| < 2^(e + 1): h the nearest fp16
 // of y's share, l that of what is left -- y itself or, where the remainder's 13th bit is set, y but for 2^-23 of it, down to
 // 2^(e - 17) (below, l has a fixed last place: 2^(e - 39)).  Exponents are biased, 14 at least (2^(14 - e) is a normal number then,
-// also where e says infinity), and stay integers: sums of products take theirs up in one v_ldexp_f32, so that what binary32 can
-// hold comes out whatever the two sides' exponents are.
+// also where e says infinity).  A sum of products takes up the row's as an integer, in v_ldexp_f32, and the column's as a factor, in the
+// fused multiply-add onto what is there: results may have any size of binary32, whatever the two sides' exponents are (the first step
+// overflows where a row's values reach 2^118 or more; what it loses below 2^-149 is 2^-38 of the largest product).
 __device__ __forceinline__ uint32_t pair_exponent(float largest) { return max(__float_as_uint(largest) >> 23, 14u); }
 __device__ __forceinline__ float pair_up(uint32_t e) { return __uint_as_float((268u - e) << 23); }
-constexpr int kPairBias = 2 * (127 + 14);   // the exponent of a product: both sides' together, less this
+constexpr int kPairRow = 127 + 27;   // the row's step: its exponent less this
+__device__ __forceinline__ float pair_column(uint32_t e) { return __uint_as_float((e - 1u) << 23); }   // the column's factor, for the other 2^-1 of 2^-28
 
 __device__ __forceinline__ void pair_split(float y, float up, _Float16& h, _Float16& l)
 {
@@ -88,7 +90,7 @@ struct PairSums {
         for (int j = 0; j < NT; ++j) add<FIRST>(NT - 1, j, sum[(NT - 1) & 1][j]);
     }
 
-    // t onto acc, its exponents those of the row in row block i and of the four columns in column block j together
+    // t onto acc; row: the step of the lane's row in row block i, col: the factors of the four columns in column block j
     template <typename Row, typename Col>
     __device__ __forceinline__ void scale(Row row, Col col)
     {
@@ -96,9 +98,10 @@ struct PairSums {
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
-                const v4i e = row(i) + col(j);
+                const int e = row(i);
+                const v4f f = col(j);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][j][v] += __builtin_amdgcn_ldexpf(t[i][j][v], e[v]);
+                for (int v = 0; v < 4; ++v) acc[i][j][v] = fmaf(__builtin_amdgcn_ldexpf(t[i][j][v], e), f[v], acc[i][j][v]);
             }
     }
 };
