@@ -54,7 +54,7 @@ typedef enum {
     FP4MR_ERR_HAD_BLOCK = 3,  /* had_block not in {1, 16, 32, 64, 128} */
     FP4MR_ERR_FMT = 4,        /* fmt is neither FP4MR_MXFP4 nor FP4MR_NVFP4, or unknown flag bits */
     FP4MR_ERR_ALIGN = 5,      /* a data pointer is not 16-byte aligned */
-    FP4MR_ERR_WORKSPACE = 6,  /* workspace is NULL or smaller than fp4_workspace_bytes() says */
+    FP4MR_ERR_WORKSPACE = 6,  /* workspace is NULL or smaller than the call takes (never more than fp4_workspace_bytes() says) */
     FP4MR_ERR_DEVICE = 7      /* the HIP runtime reported an error at launch */
 } fp4mr_status_t;
 
@@ -278,6 +278,8 @@ fp4mr_status_t fp4_gptq_quantize_weights(const void* w, int64_t N, int64_t K, in
  *   workspace  fp4_workspace_bytes(FP4MR_OP_GPTQ_HESSIAN, T, 0, K, fmt ignored, 0) = 4 T K bytes
  * The rows are rotated first and products and sums are as accurate as fp32's: the error of H[i][j] is relative to
  * sqrt(H[i][i] H[j][j]), also where channels of a block share a large component that the rotation takes out of most of them.
+ * Up to 1099 rows (1407 for K <= 1152) a rotated value has 24 bits; beyond, for had_block > 1, 23, and no place below 2^-39 of the largest
+ * value of its own channel within the 128 rows that it is summed up with.  Entries may have any size of binary32.
  * The result is symmetric bit for bit (added to a symmetric matrix).  Rows with non-finite values leave NaNs or infinities in
  * the rows and columns of H that belong to their blocks.
  */

@@ -14,7 +14,8 @@
 //   * only W is converted inside the product, and a wave's tile is 128 rows of X by 64 (or 32) rows of W: four (two)
 //     half-fragment conversions per 64 (32) MFMAs.
 // A last row of tiles with at most 64 tokens multiplies four of the eight row-blocks (its copies stay as they are): 0.62 of a tile's time
-// (N = 28672, K = 4096, M = 192: 58 -> 48 us; N = 57344, K = 8192, M = 320 with the launch that suits it 282 -> 247).
+// (N = 28672, K = 4096, M = 192: 58 -> 48 us; N = 57344, K = 8192, M = 320 with the launch that suits it 282 -> 247 with one W
+// again and again, 302 -> 265 on another card with three in turn).
 // Block tile 128 x 256 (or 128 x 128 for a remainder of the tile grid, or 128 x 512), four (eight) waves side by side along
 // N, K-step 64, three-stage LDS ring fed by direct-to-LDS loads, one barrier per K-step.  75 KB of LDS and 256 registers per
 // wave: two workgroups share a compute unit (or one of eight waves fills it).
