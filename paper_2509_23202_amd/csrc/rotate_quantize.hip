@@ -292,7 +292,9 @@ __device__ __forceinline__ float own_tensor_scale(const RqArgs& a)
 //
 // OWN (NVFP4, few tokens, Hadamard): the workgroup has kOwnThreads threads, which first take the whole tensor's abs-max; its
 // first four waves then quantize an item each, as without.
-template <int BP, int G, int LAYOUT, int PASS, bool HW, int FR, int POL, bool OWN = false>
+// APART (Hadamard blocks of up to 32 on the 64-wide operand): either half is summed apart and every lane takes that of its outputs.  Summed
+// together they come out the same, but for a value that is not finite: times the other half's zeros it would be NaN there as well.
+template <int BP, int G, int LAYOUT, int PASS, bool HW, int FR, int POL, bool OWN = false, bool APART = false>
 __global__ __launch_bounds__(OWN ? kOwnThreads : kThreads) void rq_mfma_kernel(RqArgs a)
 {
     constexpr int S = BP / 32;           // K-steps of the contraction
@@ -317,10 +319,10 @@ __global__ __launch_bounds__(OWN ? kOwnThreads : kThreads) void rq_mfma_kernel(R
         if (threadIdx.x >= kThreads) return;
     }
     v8bf hop[T][S];
-    if (!OWN && a.rot) build_dense_operand<BP>(hop, g, q, a.b, a.rot, rq_dyn_lds);  // (uniform branch: every thread takes it)
+    if (!OWN && !APART && a.rot) build_dense_operand<BP>(hop, g, q, a.b, a.rot, rq_dyn_lds);  // (uniform branch: every thread takes it)
     else build_hadamard_operand<BP>(hop, g, q, a.b < BP ? a.b : BP);
     // Hadamard blocks wider than the operand: finished by butterfly levels across the lanes of a quad
-    const int kron = (!a.rot && a.b > BP) ? (a.b == 2 * BP ? 1 : 2) : 0;
+    const int kron = (!APART && !a.rot && a.b > BP) ? (a.b == 2 * BP ? 1 : 2) : 0;
 
     // vectors in the tensor; the last one may be half a vector (16-element blocks and groups: rows * K = 16 * odd), its
     // missing half loads as zeros and is neither stored nor scaled
@@ -381,19 +383,24 @@ __global__ __launch_bounds__(OWN ? kOwnThreads : kThreads) void rq_mfma_kernel(R
             for (int t = 0; t < T; ++t) {
                 acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < S; ++s)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hop[t][s], __builtin_bit_cast(v8bf, in[s]), acc[t], 0, 0, 0);
+                for (int s = 0; s < S; ++s) {
+                    const v4f sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hop[t][s], __builtin_bit_cast(v8bf, in[s]), APART ? v4f{0.f, 0.f, 0.f, 0.f} : acc[t], 0, 0, 0);
+                    acc[t] = APART && q < 2 * s ? acc[t] : sum;
+                }
             }
         };
         if constexpr (PAIRED) {
             rotate(accs[0], xin[0]);
             rotate(accs[1], xin[1]);
             if (kron) {
+                float minus = -1.0f;   // (a multiply-add, as kronecker_levels has it: a subtraction would turn a NaN's sign)
+                asm("" : "+v"(minus));
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
                     const v4f h0 = accs[0][t], h1 = accs[1][t];
                     accs[0][t] = h0 + h1;
-                    accs[1][t] = h0 - h1;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) accs[1][t][v] = __fmaf_rn(h1[v], minus, h0[v]);
                 }
             }
         }
@@ -866,15 +873,22 @@ hipError_t launch_mfma(const RqArgs& a0, int grid_cap, hipStream_t st, int* bloc
     if (blocks > grid_cap) blocks = grid_cap;
     if (blocks < 1) blocks = 1;
     if (blocks_out) *blocks_out = (int)blocks;
-    if constexpr (PASS == 0 && G == 16 && BP == (LAYOUT ? 64 : 32)) {
-        if (a.own_max) {
-            hipLaunchKernelGGL((rq_mfma_kernel<BP, G, LAYOUT, PASS, HW, FR, POL, true>), dim3((unsigned)blocks), dim3(kOwnThreads), 0, st, a);
-            return hipGetLastError();
-        }
-    }
     const size_t lds = a.rot ? (size_t)kDenseLdsBytes<BP> : 0;  // staging of the transposed rotation matrix
-    hipLaunchKernelGGL((rq_mfma_kernel<BP, G, LAYOUT, PASS, HW, FR, POL>), dim3((unsigned)blocks), dim3(kThreads), lds, st, a);
-    return hipGetLastError();
+    auto launch = [&](auto apart) {
+        constexpr bool APART = decltype(apart)::value;
+        if constexpr (PASS == 0 && G == 16 && BP == (LAYOUT ? 64 : 32)) {
+            if (a.own_max) {
+                hipLaunchKernelGGL((rq_mfma_kernel<BP, G, LAYOUT, PASS, HW, FR, POL, true, APART>), dim3((unsigned)blocks), dim3(kOwnThreads), 0, st, a);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((rq_mfma_kernel<BP, G, LAYOUT, PASS, HW, FR, POL, false, APART>), dim3((unsigned)blocks), dim3(kThreads), lds, st, a);
+        return hipGetLastError();
+    };
+    if constexpr (PASS == 0 && LAYOUT == 1 && BP == 64) {
+        if (a.b <= 32) return launch(std::true_type{});   // (a caller's own matrix of that size takes the 32-wide operand)
+    }
+    return launch(std::false_type{});
 }
 
 template <typename TIN, int G, int LAYOUT, int PASS, bool HW, int POL>

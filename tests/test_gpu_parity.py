@@ -202,6 +202,40 @@ def test_gemm_layout_is_a_permutation_of_canonical(fp4, fmt, b):
         assert np_(T0)[0] == np_(T1)[0]
 
 
+@pytest.mark.parametrize("fmt", [MX, NV])
+@pytest.mark.parametrize("b", [16, 32, 64, 128])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_gemm_layout_is_a_permutation_of_canonical_around_non_finite_values(fp4, fmt, b, value):
+    """A value that is not finite spoils the same codes and scales in either order (its rotation block, blocks of 16 in pairs), and
+    those to the same bytes; MXFP4 rows without one, and blocks in no such pair, are as they are without it."""
+    import torch
+    M, K = 45, 1024 + 128
+    rng = np.random.default_rng(b)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    x2 = x.copy()
+    at = [(0, 5), (3, 70), (3, 200), (17, 255), (18, 256), (31, 640), (31, 700), (44, K - 1)]
+    for r, c in at:
+        x2[r, c] = value
+    say(f"gemm layout vs canonical fmt={fmt} b={b} with {value}")
+    got = []
+    for v in (x, x2):
+        xd = to_dev_bf16(inputs.f32_to_bf16_bits(v))
+        c0, s0, T0 = fp4.fp4_rotate_quantize(xd, b, fmt)
+        c1, s1, T1 = fp4.fp4_rotate_quantize(xd, b, fmt, flags=fp4.LAYOUT_GEMM)
+        torch.cuda.synchronize()
+        cc, ss = gemm_layout_to_canonical(np_(c1), np_(s1), M, K, fmt)
+        assert np.array_equal(cc, np_(c0).reshape(M, -1))
+        assert np.array_equal(ss, np_(s0).reshape(M, -1))
+        got.append((cc, ss))
+    if fmt == MX:
+        w = max(b, 32)
+        touched = np.zeros((M, K // w), dtype=bool)
+        for r, c in at:
+            touched[r, c // w] = True
+        same = (got[0][0].reshape(M, K // w, -1) == got[1][0].reshape(M, K // w, -1)).all(axis=2)
+        assert same[~touched].all()
+
+
 def test_quantize_weights_matches_rotate_quantize(fp4):
     import torch
     w = to_dev_bf16(inputs.RECIPES[1].w(96, 512))
