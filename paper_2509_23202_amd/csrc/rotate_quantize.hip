@@ -12,8 +12,8 @@
 //
 //   b' = operand width.  b = 16 uses b' = 32 with the block-diagonal matrix diag(H_16, H_16); Hadamard blocks of 64
 //   and 128 also use b' = 32 and finish with butterfly levels across lanes (kronecker_levels) wherever the 16 vectors
-//   of an MFMA group are consecutive along K; b' = 64 / 128 operands remain for caller-supplied dense rotations
-//   and for small GEMM-order calls.
+//   of an MFMA group are consecutive along K.  Small GEMM-order calls use b' = 64 (two halves of 32 apart for b <= 32, two of them
+//   and a last level for 128).  b' = 64 and 128 are also what caller-supplied dense rotations of that size take.
 //   lane (g = l%16, q = l/16) of a "supertile" owns outputs [q*b'/4, (q+1)*b'/4) of vector g.
 //
 // Throughput is bound by the bytes in flight per compute unit: kernels keep registers low (many resident waves), ask
