@@ -235,17 +235,22 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
     const bool wide_mx = fmt == FP4MR_MXFP4 && M > 32 && N >= 40960 && K > 4096;
     // Optional split-K room behind what the call needs (FP4MR_OP_GEMM_SPLIT_K): used when the caller passed that much
     void* partial = nullptr;
+    size_t partial_room = 0;
     const bool few = variant == 0 && !wide_mx && gemm_skinny_takes(M, N, K, (int)fmt);
     if (M > 64 && variant == 0 && !few) {
-        const size_t extra = fmt == FP4MR_MXFP4 ? gemm_mx_split_k_bytes(M, N, K) : nv16_split_k_bytes(M, N, K);
-        if (extra && workspace && aligned16(workspace) && workspace_bytes >= align256(need) + extra) partial = static_cast<char*>(workspace) + align256(need);
+        const bool mx = fmt == FP4MR_MXFP4;
+        const size_t extra = mx ? gemm_mx_split_k_bytes(M, N, K) : 1;   // (NVFP4: the product looks for itself what fits)
+        if (extra && workspace && aligned16(workspace) && workspace_bytes >= align256(need) + extra) {
+            partial = static_cast<char*>(workspace) + align256(need);
+            partial_room = workspace_bytes - align256(need);
+        }
     }
     if (few)
         e = launch_gemm_skinny(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, (int)fmt, out, out_f32, alpha, st);
     else if (fmt == FP4MR_MXFP4)
         e = launch_gemm_mxfp4(a_codes, a_scales, w_codes, w_scales, M, N, K, out, out_f32, variant, alpha, partial, st);
     else
-        e = launch_gemm_nvfp4(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, variant, ws, partial, st);
+        e = launch_gemm_nvfp4(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, variant, ws, partial, partial_room, st);
     return e == hipSuccess ? FP4MR_OK : FP4MR_ERR_DEVICE;
 }
 

@@ -13,7 +13,7 @@
 //     re-converting them);
 //   * only W is converted inside the product, and a wave's tile is 128 rows of X by 64 (or 32) rows of W: four (two)
 //     half-fragment conversions per 64 (32) MFMAs.
-// A last row of tiles with at most 64 tokens multiplies four of the eight row-blocks (its copies stay as they are): 0.62 of a tile's time
+// A last row of tiles with at most 64 tokens copies and multiplies four of the eight row-blocks: 0.62 of a tile's time
 // (N = 28672, K = 4096, M = 192: 58 -> 48 us; N = 57344, K = 8192, M = 320 with the launch that suits it 282 -> 247 with one W
 // again and again, 302 -> 265 on another card with three in turn).
 // Block tile 128 x 256 (or 128 x 128 for a remainder of the tile grid, or 128 x 512), four (eight) waves side by side along
@@ -50,7 +50,9 @@ struct Nv16Args {
     int half_row;  // 1: the last row of tiles holds at most 64 tokens, its tiles come last
     int n_first;   // first output column of this launch (a multiple of 256)
     int n_cols;    // number of output columns this launch covers (to the end of N when the tile grid is ragged)
-    int split_steps;  // split-K launches: K-steps of 64 per split (a multiple of 8); blockIdx.y is the split, out the fp32 partials
+    // split-K launches: parts along K of a whole tile and of one of the last row's, K-steps of 64 in a part (even), where the partials of either begin
+    int parts[2], steps[2];
+    float* partial[2];
 };
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -77,8 +79,10 @@ __global__ __launch_bounds__(256) void nv_x16_kernel(const uint8_t* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// SPLITK: the workgroup multiplies K-steps blockIdx.y * split_steps .. only and writes its fp32 partial tile, without the
-// tensor scales, to slice blockIdx.y of the output; nv16_reduce_kernel adds the slices in split order.
+// SPLITK: tiles in several parts along K.  The workgroup multiplies the K-steps of its part only and writes its fp32 partial tile, without the
+// tensor scales, to its slice of the partials; nv16_reduce_kernel adds the slices in the parts' order, four neighbouring values a thread.
+// (M = 320, layers of 8192 features with N = 10240, 8192, 57344 and K = 28672: 591 -> 553 us with parts that suit half tiles, half tiles' copies and that
+// reduction, quantizers included.)
 template <int NW, int TN, bool OUT_F32, int STAGES, bool SPLITK = false>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
 {
@@ -89,24 +93,30 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     constexpr int WS_SLOT = 256;           // scale bytes one full-wave copy writes: four row-blocks' worth per wave
     constexpr int X_BYTES = FX * 2048, WC_BYTES = FW * 512, WS_BYTES = NW * WS_SLOT;
     constexpr int STAGE_BYTES = X_BYTES + WC_BYTES + WS_BYTES;
-    constexpr int XPW = FX * 2 / NW, WPW = FW / NW;      // 1 KB X chunks and W half-fragments a wave copies per stage
+    constexpr int WPW = FW / NW;                          // W half-fragments a wave copies per stage
     constexpr int WCI = WPW / 2;                          // W code instructions per wave and stage
-    constexpr int OPS = XPW + WCI + 1;                    // vector-memory operations per wave and stage
-    static_assert(FX * 2 % NW == 0 && FW % NW == 0, "the copies are dealt evenly to the waves");
+    static_assert(FX % NW == 0 && FW % NW == 0, "the copies are dealt evenly to the waves");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // consecutive workgroups share a W column band; the tiles of a last row of at most 64 tokens, which are shorter, come behind all others
-    const int whole = g.tiles_m - g.half_row, whole_tiles = (int)gridDim.x / g.tiles_m * whole;
-    const bool half = (int)blockIdx.x >= whole_tiles;
-    const int tm = half ? whole : (int)blockIdx.x % whole, tn = half ? (int)blockIdx.x - whole_tiles : (int)blockIdx.x / whole;
+    const int whole = g.tiles_m - g.half_row, tiles_n = (g.n_cols + BN - 1) / BN, whole_tiles = tiles_n * whole;
+    const int all_whole = whole_tiles * (SPLITK ? g.parts[0] : 1);
+    const bool half = (int)blockIdx.x >= all_whole;
+    int id = half ? (int)blockIdx.x - all_whole : (int)blockIdx.x, part = 0;
+    if constexpr (SPLITK) {   // part by part
+        const int n = half ? tiles_n : whole_tiles;
+        part = id / n;
+        id -= part * n;
+    }
+    const int tm = half ? whole : id % whole, tn = half ? id : id / whole;
     const int64_t n_tile0 = (int64_t)g.n_first + (int64_t)tn * BN;
 
     const int KH_all = (int)(g.K >> 6), KC = (int)(g.K >> 7);   // K-steps of 64 / fragments of 128 per row-block in memory
-    const int kh0 = SPLITK ? (int)blockIdx.y * g.split_steps : 0;  // (even: a split starts on a fragment)
-    const int KH = SPLITK ? min(g.split_steps, KH_all - kh0) : KH_all;
+    const int kh0 = SPLITK ? part * g.steps[half] : 0;  // (even: a part starts on a fragment)
+    const int KH = SPLITK ? min(g.steps[half], KH_all - kh0) : KH_all;
     const int a_rbs = (int)((g.M + 15) / 16), w_rbs = (int)((g.N + 15) / 16);
     const int a_rb0 = min(tm * FX, a_rbs - 1), w_rb0 = min((int)(n_tile0 / 16), w_rbs - 1);
     const int a_rb_last = a_rbs - 1 - a_rb0, w_rb_last = w_rbs - 1 - w_rb0;
@@ -114,7 +124,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
         const uint32_t n = bytes > 0xffffffffll ? 0xffffffffu : (uint32_t)bytes;
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, (int)n, 0x00020000);
     };
-    const int64_t x0 = (int64_t)kh0 * 2048, c0 = (int64_t)(kh0 >> 1) * 1024, s0 = (int64_t)(kh0 >> 1) * 128;  // (0 unless SPLITK)
+    const int64_t x0 = (int64_t)kh0 * 2048, c0 = (int64_t)(kh0 >> 1) * 1024, s0 = (int64_t)(kh0 >> 1) * 128;
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(g.x16 + (int64_t)a_rb0 * KH_all * 2048 + x0, (int64_t)(a_rbs - a_rb0) * KH_all * 2048 - x0);
     const __amdgpu_buffer_rsrc_t rs_wc = make_rsrc(g.w_codes + (int64_t)w_rb0 * KC * 1024 + c0, (int64_t)(w_rbs - w_rb0) * KC * 1024 - c0);
     const __amdgpu_buffer_rsrc_t rs_ws = make_rsrc(g.w_scales + (int64_t)w_rb0 * KC * 128 + s0, (int64_t)(w_rbs - w_rb0) * KC * 128 - s0);
@@ -134,7 +144,8 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     const uint32_t wc_voff1 = (uint32_t)((lane & 31) * 16 + min(wave * WPW + 2 + (lane >> 5), w_rb_last) * wc_rb_bytes);   // (WCI = 2 only)
     // (a wave that owns two row-blocks only fills the rest of its 256-byte slot with the scales of the two behind them)
     const uint32_t ws_voff = (uint32_t)((lane & 15) * 4 + min(wave * WPW + (lane >> 4), w_rb_last) * ws_rb_bytes);
-    auto issue_x = [&](int kl, char* base) {
+    auto issue_x = [&](auto rm, int kl, char* base) {
+        constexpr int XPW = decltype(rm)::value * 2 / NW;   // 1 KB chunks a wave copies per stage
 #pragma unroll
         for (int i = 0; i < XPW; ++i) {
             const int c = wave * XPW + i;                 // chunk = (row-block, plane)
@@ -154,10 +165,10 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     };
     // stage k goes to ring slot k % STAGES; past the last stage the copies repeat it into a slot nobody reads any more, so
     // that every K-step issues the same operations (no branch, uniform vmcnt bookkeeping)
-    auto issue = [&](int k) {
+    auto issue = [&](auto rm, int k) {
         const int kl = min(k, KH - 1);
         char* base = smem + (k % STAGES) * STAGE_BYTES;
-        issue_x(kl, base);
+        issue_x(rm, kl, base);
         issue_wc(kl, base);
         issue_ws(kl, base);
     };
@@ -167,9 +178,6 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     for (int i = 0; i < TN; ++i)
 #pragma unroll
         for (int j = 0; j < TM; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-#pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue(s);
 
     // where lane (r, q) finds its 8 code bytes and its scale byte inside a W half-fragment
     const int r = lane & 15, q = lane >> 4;
@@ -222,23 +230,26 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     WRaw wraw[TN];
     WHalf wcur, wnext;
     auto read_x = [&](const char* base, int j, int s) { xf[j][s] = *(reinterpret_cast<const v8h*>(base + (j * 2 + s) * 1024) + lane); };
-    wait_vmcnt<(STAGES - 2) * OPS>();
-    block_barrier();
-#pragma unroll
-    for (int i = 0; i < TN; ++i) wraw[i] = read_w(smem, i);
-#pragma unroll
-    for (int t = 0; t < 2 * TM; ++t) read_x(smem, t % TM, t / TM);
-    {
-        const v2h s2 = scale2(wraw[0]);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) micro(wraw[0], s2, wcur, u);
-    }
-    // lgkmcnt(0): nothing is pending where the loop is entered, so that the waits inside count its own reads only (with an
-    // order of its own on the way in, the compiler waits for everything at the head of every step)
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    // RM: 16-row blocks that are multiplied, eight or -- the tile holds at most 64 tokens -- the first four
+    // RM: 16-row blocks that are copied and multiplied, eight or -- the tile holds at most 64 tokens -- the first four
     auto steps = [&](auto rm) {
         constexpr int RM = decltype(rm)::value;
+        constexpr int OPS = RM * 2 / NW + WCI + 1;   // vector-memory operations per wave and stage
+#pragma unroll
+        for (int s = 0; s < STAGES - 1; ++s) issue(rm, s);
+        wait_vmcnt<(STAGES - 2) * OPS>();
+        block_barrier();
+#pragma unroll
+        for (int i = 0; i < TN; ++i) wraw[i] = read_w(smem, i);
+#pragma unroll
+        for (int t = 0; t < 2 * RM; ++t) read_x(smem, t % RM, t / RM);
+        {
+            const v2h s2 = scale2(wraw[0]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) micro(wraw[0], s2, wcur, u);
+        }
+        // lgkmcnt(0): nothing is pending where the loop is entered, so that the waits inside count its own reads only (with an
+        // order of its own on the way in, the compiler waits for everything at the head of every step)
+        __builtin_amdgcn_s_waitcnt(0xc07f);
         for (int kh = 0; kh < KH; ++kh) {
             const int kn = kh + STAGES - 1, kl = min(kn, KH - 1);
             char* const fill = smem + (kn % STAGES) * STAGE_BYTES;
@@ -274,7 +285,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // the refill of the slot everybody left at the barrier of the step before, in pieces behind the first column-tiles
-                if (i == 0) issue_x(kl, fill);
+                if (i == 0) issue_x(rm, kl, fill);
                 if (i == (TN == 2 ? 0 : 1)) issue_wc(kl, fill);
                 if (i == (TN == 2 ? 0 : 2)) issue_ws(kl, fill);
                 __builtin_amdgcn_sched_barrier(0);
@@ -291,6 +302,9 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     const int64_t n_lim = (int64_t)g.n_first + g.n_cols;
     const int64_t n_end = n_lim < g.N ? n_lim : g.N;
     const int64_t m_base = (int64_t)tm * BM + (lane & 15);
+    // a part's slice: the rows of the whole tiles, or those of the last row of tiles
+    const int64_t rows0 = (int64_t)whole * BM, slice_rows = half ? g.M - rows0 : min(rows0, g.M);
+    float* const slice = SPLITK ? g.partial[half] + (part * slice_rows - (half ? rows0 : 0)) * g.N : nullptr;
     const int64_t n_base = n_tile0 + wave * WN + (lane >> 4) * 4;
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
@@ -304,7 +318,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] *= ts;
             if constexpr (OUT_F32) {
-                float* o = static_cast<float*>(g.out) + (SPLITK ? (int64_t)blockIdx.y * g.M * g.N : 0) + m * g.N + n;
+                float* o = (SPLITK ? slice : static_cast<float*>(g.out)) + m * g.N + n;
                 if (n + 3 < n_end && (g.N & 3) == 0) {
                     *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
                 } else {
@@ -326,19 +340,38 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_nv16_kernel(Nv16Args g)
     }
 }
 
-// out[i] = s_T(A) s_T(W) (partial[0][i] + partial[1][i] + ...), the splits added in their order, as bf16 or fp32
-template <bool OUT_F32>
-__global__ __launch_bounds__(256) void nv16_reduce_kernel(const float* __restrict__ partial, int splits, int64_t mn, const float* a_ts,
-                                                          const float* w_ts, void* out)
+// out[i] = s_T(A) s_T(W) (partial[0][i] + partial[1][i] + ...), the parts added in their order, as bf16 or fp32: the rows of the whole
+// tiles, then those of the last row of tiles, either with slices of its own.  VEC neighbouring elements per thread.
+struct Nv16Sums {
+    const float* partial[2];
+    int parts[2];
+    int64_t count[2];   // elements
+    const float *a_ts, *w_ts;
+    void* out;
+};
+template <bool OUT_F32, int VEC>
+__global__ __launch_bounds__(256) void nv16_reduce_kernel(Nv16Sums a)
 {
-    const float ts = (*a_ts) * (*w_ts);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < mn; i += (int64_t)gridDim.x * 256) {
-        float s = partial[i];
-        for (int p = 1; p < splits; ++p) s += partial[(int64_t)p * mn + i];
-        s *= ts;
-        if constexpr (OUT_F32) static_cast<float*>(out)[i] = s;
-        else static_cast<__bf16*>(out)[i] = (__bf16)s;
+    typedef float vf __attribute__((ext_vector_type(VEC)));
+    typedef __bf16 vb __attribute__((ext_vector_type(VEC)));
+    const int64_t at = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VEC;
+    const bool last = at >= a.count[0];
+    const int64_t count = a.count[last], i = last ? at - a.count[0] : at;
+    if (i >= count) return;
+    const float* p = a.partial[last] + i;
+    const int parts = a.parts[last];
+    vf s = *reinterpret_cast<const vf*>(p);
+    for (int k = 1; k < parts; k += 4) {
+        vf v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const vf*>(p + min(k + u, parts - 1) * count);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k + u < parts) s += v[u];
     }
+    s *= (*a.a_ts) * (*a.w_ts);
+    if constexpr (OUT_F32) *reinterpret_cast<vf*>(static_cast<float*>(a.out) + at) = s;
+    else *reinterpret_cast<vb*>(static_cast<__bf16*>(a.out) + at) = __builtin_convertvector(s, vb);
 }
 
 // Split-K plan (see the MXFP4 kernels' plan: few tiles and a long K leave the launch bound by the latency of a handful of
@@ -355,11 +388,15 @@ bool nv16_narrow_tiles(int64_t tiles_w, int cus)
     return 4 * tiles_w <= 5 * (int64_t)cus;
 }
 
-void plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, int* splits, int* steps, bool* narrow)
+struct SplitPlan {
+    int parts[2] = {1, 1}, steps[2] = {0, 0};   // of whole tiles, of those of a last row of at most 64 tokens
+    bool narrow = false, rows512 = false;       // tiles of 128 columns; of 512
+    bool half_row = false;
+};
+
+SplitPlan plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t room)
 {
-    *splits = 1;
-    *steps = 0;
-    *narrow = false;
+    SplitPlan plan;
     const int64_t tiles_m = (M + 127) / 128;
     const int64_t tiles_w = tiles_m * ((N + 255) / 256), tiles_n = tiles_m * ((N + 127) / 128);
     const int64_t slots = 2 * (int64_t)cus;
@@ -383,12 +420,38 @@ void plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, int* splits, in
             const double t = 10.0 + st * step * shared(n * tiles) + 3.0 + (double)n * (double)M * (double)N * 8.0 / 8.0e6;
             if (t < best) {
                 best = t;
-                *splits = (int)n;
-                *steps = st;
-                *narrow = nar != 0;
+                plan.parts[0] = plan.parts[1] = (int)n;
+                plan.steps[0] = plan.steps[1] = st;
+                plan.narrow = nar != 0;
             }
         }
     }
+    if (plan.parts[0] == 1) return plan;
+    // Split launches gain from K = 4096 on with half tiles last (M = 320: N = 8192, K = 28672 148 -> 142 us, N = 6144, K = 4096 37 -> 33); below, as often lose.
+    plan.half_row = (M - 1) % 128 < 64 && K >= 4096;
+    const int64_t cols = (N + 511) / 512, rows = tiles_m - 1;
+    plan.rows512 = !plan.narrow && K >= 6656 && tiles_w * plan.parts[0] > cus && tiles_m * cols * plan.parts[0] <= cus;   // (see launch_wide)
+    if (!plan.rows512 || !plan.half_row || rows == 0) return plan;
+    // One workgroup per compute unit, and a part of a half tile takes 0.62 of a whole one's time: with as many parts for either as
+    // suit each other, parts are shorter.  Microseconds: steps of the longer part times 1.38, and the partials as above.  M = 320, K = 8192,
+    // N = 8192 and K = 28672, N = 8192: six and four parts instead of four, five of both, 60.9 -> 55.2 us, 143.9 -> 131.2.
+    best = 0.0;
+    for (int64_t s = 2; s <= std::min<int64_t>(16, kh / 8) && (rows * s + 1) * cols <= cus; ++s) {
+        auto even = [&](int64_t n) { return (int)((kh + 2 * n - 1) / (2 * n) * 2); };
+        const int st = even(s);
+        int64_t h = std::min<int64_t>(cus / cols - rows * s, s);
+        while (h > 1 && 0.62 * even(h - 1) <= st) --h;
+        const int sh = even(h), n = (kh + st - 1) / st, nh = (kh + sh - 1) / sh;
+        const int64_t partials = ((int64_t)n * rows * 128 + (int64_t)nh * (M - rows * 128)) * N;
+        const double t = 1.38 * std::max<double>(st, 0.62 * sh) + (double)partials * 8.0 / 8.0e6;
+        if ((size_t)partials * 4 > room || (best > 0.0 && t >= best)) continue;
+        best = t;
+        plan.parts[0] = n;
+        plan.parts[1] = nh;
+        plan.steps[0] = st;
+        plan.steps[1] = sh;
+    }
+    return plan;
 }
 
 int device_cus()
@@ -396,42 +459,38 @@ int device_cus()
     return compute_units();
 }
 
+template <int NW, int TN, int STAGES, bool OUT_F32, bool SPLITK>
+hipError_t launch_kernel(const Nv16Args& g, unsigned workgroups, hipStream_t st)
+{
+    constexpr size_t lds = STAGES * (size_t)(8 * 2048 + NW * TN * 512 + NW * 256);
+    static LdsAttrOnce raised;
+    auto k = gemm_nv16_kernel<NW, TN, OUT_F32, STAGES, SPLITK>;
+    const hipError_t e = raised.ensure(reinterpret_cast<const void*>(k), (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k, dim3(workgroups), dim3(NW * 64), lds, st, g);
+    return hipGetLastError();
+}
+
+// (g.parts[0] == 0: tiles are not split)
 template <int NW, int TN, int STAGES>
-hipError_t launch_tiles(const Nv16Args& g0, bool out_f32, hipStream_t st, int splits = 1)
+hipError_t launch_tiles(const Nv16Args& g0, bool out_f32, hipStream_t st)
 {
     Nv16Args g = g0;
     constexpr int BN = NW * TN * 16;
-    constexpr size_t lds = STAGES * (size_t)(8 * 2048 + (BN / 16) * 512 + NW * 256);
     if (g.n_cols <= 0) return hipSuccess;
     const int tiles_n = (g.n_cols + BN - 1) / BN;
+    if (g.parts[0]) {
+        const int n = tiles_n * ((g.tiles_m - g.half_row) * g.parts[0] + g.half_row * g.parts[1]);
+        return launch_kernel<NW, TN, STAGES, true, true>(g, (unsigned)n, st);
+    }
     if (g.half_row) {
         // Half tiles go last where that evens out the launch's end or gives every compute unit one whole tile at most.  Else the launch takes
         // the time of whole tiles, and all of them in turn leave an XCD its rows of X (K = 2048, N = 12288, M = 960: 58 us, halves last 61.5).
-        const int64_t all = (int64_t)g.tiles_m * tiles_n * splits, cus = device_cus();
-        // Split launches gain from K = 4096 on (M = 320: N = 8192, K = 28672 148 -> 142 us, N = 6144, K = 4096 37 -> 33); below, as often lose.
-        g.half_row = (splits > 1 && g.K >= 4096) || all > 2 * cus || (all > cus && all - (int64_t)tiles_n * splits <= cus) ? 1 : 0;
+        const int64_t all = (int64_t)g.tiles_m * tiles_n, cus = device_cus();
+        g.half_row = all > 2 * cus || (all > cus && all - tiles_n <= cus) ? 1 : 0;
     }
-    if (splits > 1) {
-        static LdsAttrOnce raised_s;
-        auto k = gemm_nv16_kernel<NW, TN, true, STAGES, true>;
-        hipError_t es;
-        if ((es = raised_s.ensure(reinterpret_cast<const void*>(k), (int)lds)) != hipSuccess) return es;
-        hipLaunchKernelGGL(k, dim3((unsigned)(g.tiles_m * tiles_n), (unsigned)splits), dim3(NW * 64), lds, st, g);
-        return hipGetLastError();
-    }
-    const dim3 grid((unsigned)(g.tiles_m * tiles_n));
-    hipError_t e;
-    static LdsAttrOnce raised[2];
-    if (out_f32) {
-        auto k = gemm_nv16_kernel<NW, TN, true, STAGES>;
-        if ((e = raised[1].ensure(reinterpret_cast<const void*>(k), (int)lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k, grid, dim3(NW * 64), lds, st, g);
-    } else {
-        auto k = gemm_nv16_kernel<NW, TN, false, STAGES>;
-        if ((e = raised[0].ensure(reinterpret_cast<const void*>(k), (int)lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k, grid, dim3(NW * 64), lds, st, g);
-    }
-    return hipGetLastError();
+    const unsigned n = (unsigned)(g.tiles_m * tiles_n);
+    return out_f32 ? launch_kernel<NW, TN, STAGES, true, false>(g, n, st) : launch_kernel<NW, TN, STAGES, false, false>(g, n, st);
 }
 
 // Tile columns of 256 (or wider).  Two workgroups of 128 x 256 share a compute unit, and one's epilogue runs under the other's
@@ -443,13 +502,13 @@ hipError_t launch_tiles(const Nv16Args& g0, bool out_f32, hipStream_t st, int sp
 // 512 columns took 0.95 - 1.02 of the pairs' time (M = 419, N = 24064, K = 8576: 180 -> 171 us), on 47 below it 0.98 - 1.11
 // (M = 451, N = 25992, K = 1536: 54 against 60).
 // Three stages either way: a fourth for the 512 columns measured 1 % slower.
-hipError_t launch_wide(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1)
+hipError_t launch_wide(const Nv16Args& g, bool out_f32, hipStream_t st)
 {
-    const int64_t rows = (int64_t)g.tiles_m * splits, cus = device_cus();
+    const int64_t rows = g.tiles_m, cus = device_cus();
     // (a compute unit that gets one whole tile and one of half the rows is done sooner as a pair: M = 192, N = 57344, K = 8192 163 -> 153 us)
-    const bool pairs = splits == 1 && g.half_row && (g.tiles_m - 1) * (int64_t)((g.n_cols + 255) / 256) <= cus;
-    if (!pairs && g.K >= 6656 && rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st, splits);
-    return launch_tiles<4, 4, 3>(g, out_f32, st, splits);
+    const bool pairs = g.half_row && (g.tiles_m - 1) * (int64_t)((g.n_cols + 255) / 256) <= cus;
+    if (!pairs && g.K >= 6656 && rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st);
+    return launch_tiles<4, 4, 3>(g, out_f32, st);
 }
 
 // Estimated time of a launch, microseconds per K-step: `whole` tiles and behind them `half` ones (of at most 64 tokens), wide or narrow.
@@ -467,7 +526,39 @@ double nv16_tiles_cost(int64_t whole, int64_t half, bool narrow, int64_t cus)
     return t + shared + ((double)half * part > (double)(slots - left) ? part * alone : 0.0);
 }
 
-hipError_t launch_narrow(const Nv16Args& g, bool out_f32, hipStream_t st, int splits = 1) { return launch_tiles<4, 2, 3>(g, out_f32, st, splits); }
+hipError_t launch_narrow(const Nv16Args& g, bool out_f32, hipStream_t st) { return launch_tiles<4, 2, 3>(g, out_f32, st); }
+
+// the product in parts, and their sums
+hipError_t launch_parts(Nv16Args g, const SplitPlan& plan, bool out_f32, float* partial, hipStream_t st)
+{
+    g.n_first = 0;
+    g.n_cols = (int)g.N;
+    g.half_row = plan.half_row ? 1 : 0;
+    const int64_t rows0 = std::min<int64_t>((int64_t)(g.tiles_m - g.half_row) * 128, g.M);
+    Nv16Sums r{};
+    r.a_ts = g.a_ts;
+    r.w_ts = g.w_ts;
+    r.out = g.out;
+    for (int h = 0; h < 2; ++h) {
+        g.steps[h] = plan.steps[h];
+        r.parts[h] = g.parts[h] = plan.parts[h];
+        r.partial[h] = g.partial[h] = partial;
+        r.count[h] = (h ? g.M - rows0 : rows0) * g.N;
+        partial += r.parts[h] * r.count[h];
+    }
+    const hipError_t e = plan.rows512 ? launch_tiles<8, 4, 3>(g, out_f32, st) : plan.narrow ? launch_tiles<4, 2, 3>(g, out_f32, st) : launch_tiles<4, 4, 3>(g, out_f32, st);
+    if (e != hipSuccess) return e;
+    const bool vec = g.N % 4 == 0;
+    const dim3 grid((unsigned)((g.M * g.N / (vec ? 4 : 1) + 255) / 256));
+    if (out_f32) {
+        if (vec) hipLaunchKernelGGL((nv16_reduce_kernel<true, 4>), grid, dim3(256), 0, st, r);
+        else hipLaunchKernelGGL((nv16_reduce_kernel<true, 1>), grid, dim3(256), 0, st, r);
+    } else {
+        if (vec) hipLaunchKernelGGL((nv16_reduce_kernel<false, 4>), grid, dim3(256), 0, st, r);
+        else hipLaunchKernelGGL((nv16_reduce_kernel<false, 1>), grid, dim3(256), 0, st, r);
+    }
+    return hipGetLastError();
+}
 
 }  // namespace
 
@@ -476,18 +567,18 @@ size_t nv16_workspace_bytes(int64_t M, int64_t K)
     return (size_t)(round_up(M, 16) * K * 2);
 }
 
-// bytes of fp32 partials a split-K run of this product needs (0: the product is not split)
-size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K)
+// bytes of fp32 partials a split-K run of this product needs, where there is room for as many as it likes (0: the product is not split)
+static size_t partial_bytes(const SplitPlan& p, int64_t M, int64_t N)
 {
-    int splits, steps;
-    bool narrow;
-    plan_split_k_nv16(M, N, K, device_cus(), &splits, &steps, &narrow);
-    return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * 4 : 0;
+    const int64_t last = p.half_row ? (M - 1) % 128 + 1 : 0;
+    return p.parts[0] > 1 ? (size_t)(p.parts[0] * (M - last) + p.parts[1] * last) * (size_t)N * 4 : 0;
 }
+
+size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K) { return partial_bytes(plan_split_k_nv16(M, N, K, device_cus(), SIZE_MAX), M, N); }
 
 hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                             const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
-                            bool out_f32, void* workspace, void* partial, hipStream_t st)
+                            bool out_f32, void* workspace, void* partial, size_t partial_room, hipStream_t st)
 {
     // 1. activations -> fp16 in operand order (workspace)
     const int64_t n_frags = round_up(M, 16) / 16 * (K / 128);
@@ -515,21 +606,8 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     const int cus = device_cus();
     if (partial) {
         // few tiles, long K: every tile's K range shared by several workgroups, partial results added by a second kernel
-        int splits, steps;
-        bool narrow;
-        plan_split_k_nv16(M, N, K, cus, &splits, &steps, &narrow);
-        if (splits > 1) {
-            g.out = partial;
-            g.n_first = 0;
-            g.n_cols = (int)N;
-            g.split_steps = steps;
-            if ((e = narrow ? launch_narrow(g, true, st, splits) : launch_wide(g, true, st, splits)) != hipSuccess) return e;
-            const int64_t mn = M * N;
-            const unsigned rblocks = (unsigned)std::min<int64_t>((mn + 255) / 256, 256 * 16);
-            if (out_f32) hipLaunchKernelGGL(nv16_reduce_kernel<true>, dim3(rblocks), dim3(256), 0, st, static_cast<const float*>(partial), splits, mn, a_ts, w_ts, out);
-            else hipLaunchKernelGGL(nv16_reduce_kernel<false>, dim3(rblocks), dim3(256), 0, st, static_cast<const float*>(partial), splits, mn, a_ts, w_ts, out);
-            return hipGetLastError();
-        }
+        const SplitPlan plan = plan_split_k_nv16(M, N, K, cus, partial_room);
+        if (plan.parts[0] > 1 && partial_bytes(plan, M, N) <= partial_room) return launch_parts(g, plan, out_f32, static_cast<float*>(partial), st);
     }
     const int64_t slots = 2 * (int64_t)cus;
     const int64_t cols_w = (N + 255) / 256;                         // wide tile columns

@@ -61,15 +61,16 @@ size_t gemm_mx_split_k_bytes(int64_t M, int64_t N, int64_t K);
 // variant 0: the fp16-activation kernel below (needs its workspace); 1..3: the tile kernels that dequantize both operands
 hipError_t launch_gemm_nvfp4(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                              const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
-                             bool out_f32, int variant, void* workspace, void* partial, hipStream_t st);
+                             bool out_f32, int variant, void* workspace, void* partial, size_t partial_room, hipStream_t st);
 
 // NVFP4 product for many tokens: the activations are dequantized once to fp16 into `workspace`
 // (nv16_workspace_bytes(M, K) bytes, 256-byte aligned), then multiplied against W dequantized on the fly
 size_t nv16_workspace_bytes(int64_t M, int64_t K);
 hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                             const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
-                            bool out_f32, void* workspace, void* partial, hipStream_t st);
-// fp32 partials of a split-K run of that product (`partial`, may be null: then it is never split); 0 = not split
+                            bool out_f32, void* workspace, void* partial, size_t partial_room, hipStream_t st);
+// fp32 partials of a split-K run of that product (`partial`, of partial_room bytes: with fewer than this, in fewer parts or not split; null: never
+// split); 0 = not split
 size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K);
 
 // few-token weight-streaming GEMM, both formats, operands in GEMM layout: every shape up to 64 tokens, and the shapes

@@ -606,6 +606,27 @@ def test_gemm_nvfp4_split_k(fp4, oracle, M, N, K, out_f32):
         assert np.all(err <= tol), (name, float((err / (1e-3 * S + 1e-300)).max()))
 
 
+@pytest.mark.parametrize("M,N,K", [(320, 8190, 8192), (192, 4200, 28672), (400, 6200, 8192), (160, 16384, 8192)])
+def test_gemm_nvfp4_parts_that_suit_half_tiles(fp4, M, N, K):
+    """A last row of at most 64 tokens in fewer parts than the whole tiles above it: against the fp64 product of the decoded operands, and with
+    every workspace from the least to the full one (fewer parts, then none)."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    ops = [fp4.fp4_rotate_quantize(torch.randn(n, K, device="cuda", generator=g).to(torch.bfloat16), 16, NV) for n in (M, N)]
+    a, w = (fp4.fp4_dequantize(*q, n, K, NV, flags=fp4.OUT_F32).double() for q, n in zip(ops, (M, N)))
+    Y, S = a @ w.t(), a.abs() @ w.abs().t()
+    del a, w
+    base = fp4.workspace_bytes(fp4.OP_GEMM, M, N, K, NV, fp4.OUT_F32)
+    full = fp4.workspace_bytes(fp4.OP_GEMM_SPLIT_K, M, N, K, NV, fp4.OUT_F32)
+    extra = (full - base) // 4
+    assert extra % (M * N) != 0 and extra > 2 * M * N   # different numbers of parts
+    for nbytes in (full, full - 256, base + 3 * M * N * 4, base):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        out = fp4.fp4_gemm(*ops[0], *ops[1], M, N, K, NV, flags=fp4.OUT_F32, workspace=ws)
+        assert bool(((out.double() - Y).abs() <= 1e-3 * S).all()), nbytes
+
+
 def test_gemm_mxfp4_exact_on_small_integers(fp4, oracle):
     """With scale bytes chosen freely and on-grid codes, 4*a*w are small integers: the fp32 accumulator must be
     EXACT (any summation order), and distinct scales per K-group pin the scale-to-group wiring."""
