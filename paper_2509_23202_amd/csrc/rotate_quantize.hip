@@ -332,9 +332,11 @@ __global__ __launch_bounds__(OWN ? kOwnThreads : kThreads) void rq_mfma_kernel(R
     const int64_t KS = (a.K + 511) >> 9;
     const uint16_t* __restrict__ x = static_cast<const uint16_t*>(a.x);
 
+    __shared__ typename GQ::v2f_t steps[POL == 1 && G == 16 ? kNvSteps : 1];
     if constexpr (G == 16 && PASS != 1) {
         if constexpr (!OWN) s_T = load_tensor_scale(a, (int)(threadIdx.x & 63));
         if (!a.static_scale && blockIdx.x == 0 && threadIdx.x == 0) *a.tensor_scale = s_T;
+        if constexpr (POL == 1) nv_steps(steps, s_T);
     }
     float hmax = 0.0f;
     double fit_num = 0.0, fit_den = 0.0;
@@ -436,7 +438,7 @@ __global__ __launch_bounds__(OWN ? kOwnThreads : kThreads) void rq_mfma_kernel(R
             }
             uint32_t out[GQ::ND], sc[GQ::NG];
             if constexpr (POL == 3) GQ::mx_fit(y, fr.lmin, fr.inv, fr.table, out, sc);
-            else GQ::template run<POL>(y, s_T, out, sc);
+            else GQ::template run<POL>(y, s_T, steps, out, sc);
             if constexpr (PASS == 2) {
                 // (vectors past the end were loaded as zeros: they add nothing)
                 if constexpr (G == 16) fit_accumulate<NO, GQ::ND, GQ::NG, HW>(y, out, sc, fit_num, fit_den);
@@ -545,9 +547,11 @@ __global__ __launch_bounds__(kThreads) void rq_frag_kernel(RqArgs a)
     const int kron = a.b > BP ? (a.b == 2 * BP ? 1 : 2) : 0;
 
     float s_T = 0.0f;
+    __shared__ typename GQ::v2f_t steps[POL == 1 && G == 16 ? kNvSteps : 1];
     if constexpr (G == 16) {
         s_T = load_tensor_scale(a, (int)(threadIdx.x & 63));
         if (!a.static_scale && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) *a.tensor_scale = s_T;
+        if constexpr (POL == 1) nv_steps(steps, s_T);
     }
 
     FitRange fr{0.0f, 0.0f, nullptr};
@@ -579,7 +583,7 @@ __global__ __launch_bounds__(kThreads) void rq_frag_kernel(RqArgs a)
                 }
             uint32_t out[GQ::ND], sc[GQ::NG];
             if constexpr (POL == 3) GQ::mx_fit(y, fr.lmin, fr.inv, fr.table, out, sc);
-            else GQ::template run<POL>(y, s_T, out, sc);
+            else GQ::template run<POL>(y, s_T, steps, out, sc);
             const int rr = wib * RPW + u;  // row inside the row-block
             const int fr = kk * (BP / 8) + (e_grp >> 7), e0 = e_grp & 127;  // fragment of the item, offset inside it
             const int d = fr * 256 + ((((e0 >> 5) * 16 + rr) << 2) + ((e0 & 31) >> 3));
@@ -645,9 +649,11 @@ __global__ __launch_bounds__(kThreads) void q_direct_kernel(RqArgs a)
     const TIN* __restrict__ x = static_cast<const TIN*>(a.x);
 
     float s_T = 0.0f;
+    __shared__ typename GQ::v2f_t steps[POL == 1 && G == 16 ? kNvSteps : 1];
     if constexpr (G == 16 && PASS != 1) {
         s_T = load_tensor_scale(a, (int)(threadIdx.x & 63));
         if (!a.static_scale && blockIdx.x == 0 && threadIdx.x == 0) *a.tensor_scale = s_T;
+        if constexpr (POL == 1) nv_steps(steps, s_T);
     }
     float hmax = 0.0f;
     double fit_num = 0.0, fit_den = 0.0;
@@ -704,7 +710,7 @@ __global__ __launch_bounds__(kThreads) void q_direct_kernel(RqArgs a)
             }
             uint32_t out[1], sc[1];
             if constexpr (POL == 3) GQ::mx_fit(y, fr.lmin, fr.inv, fr.table, out, sc);
-            else GQ::template run<POL>(y, s_T, out, sc);
+            else GQ::template run<POL>(y, s_T, steps, out, sc);
             if constexpr (PASS == 2) {
                 if constexpr (G == 16) fit_accumulate<8, 1, 1, HW>(y, out, sc, fit_num, fit_den);
                 continue;
@@ -760,9 +766,16 @@ __global__ __launch_bounds__(256) void fit_finalize_kernel(const double* partial
 {
     __shared__ double red[2][256];
     double num = 0.0, den = 0.0;
-    for (int i = threadIdx.x; i < n_waves; i += 256) {
-        num += partial[2 * i];
-        den += partial[2 * i + 1];
+    for (int i = threadIdx.x; i < n_waves; i += 8 * 256) {   // (eight requests at a time: one by one their latency is the kernel's time)
+        double2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = reinterpret_cast<const double2*>(partial)[min(i + 256 * u, n_waves - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (i + 256 * u >= n_waves) break;
+            num += v[u].x;
+            den += v[u].y;
+        }
     }
     red[0][threadIdx.x] = num;
     red[1][threadIdx.x] = den;

@@ -5,6 +5,8 @@
 
 #include "device_util.hpp"
 
+#include <type_traits>
+
 namespace fp4mr {
 
 // ------------------------------------------------------------------------------------------------------
@@ -18,6 +20,13 @@ struct GroupQuant {
     static constexpr int VG = NO / NG;                 // values per lane per group
     static constexpr int ND = NO / 8;                  // dwords of codes per lane
 
+    __device__ static __forceinline__ float group_max(float v)
+    {
+        if constexpr (LG >= 2) v = fmaxf(v, __shfl_xor(v, XOR_LO));
+        if constexpr (LG >= 4) v = fmaxf(v, __shfl_xor(v, XOR_LO * 2));
+        return v;
+    }
+
     // MXFP4: returns scale bytes in sc[NG], codes in out[ND]
     __device__ static __forceinline__ void mx(const float (&y)[NO], uint32_t (&out)[ND], uint32_t (&sc)[NG])
     {
@@ -26,8 +35,7 @@ struct GroupQuant {
             float amax = 0.0f;
 #pragma unroll
             for (int i = 0; i < VG; ++i) amax = fabs_max(amax, y[gi * VG + i]);
-            if constexpr (LG >= 2) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO));
-            if constexpr (LG >= 4) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO * 2));
+            amax = group_max(amax);
             // OCP MX: shared exponent = floor(log2 amax) - 2 -> biased byte = exponent field - 2, clamped at 0
             const int ef = (int)((__float_as_uint(amax) >> 23) & 0xffu);
             const uint32_t byte = (uint32_t)max(ef - 2, 0);
@@ -51,8 +59,7 @@ struct GroupQuant {
             float amax = 0.0f;
 #pragma unroll
             for (int i = 0; i < VG; ++i) amax = fabs_max(amax, y[gi * VG + i]);
-            if constexpr (LG >= 2) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO));
-            if constexpr (LG >= 4) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO * 2));
+            amax = group_max(amax);
             uint32_t c = 0;
             if (s_T > 0.0f) c = e4m3_encode<HW>(__fdiv_rn(amax, six_sT));
             sc[gi] = c;
@@ -112,8 +119,7 @@ struct GroupQuant {
             float amax = 0.0f;
 #pragma unroll
             for (int i = 0; i < VG; ++i) amax = fabs_max(amax, y[gi * VG + i]);
-            if constexpr (LG >= 2) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO));
-            if constexpr (LG >= 4) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO * 2));
+            amax = group_max(amax);
             const int ef = (int)((__float_as_uint(amax) >> 23) & 0xffu);
             const int byte0 = max(ef - 2, 0);
             float best_err = 0.0f;
@@ -149,7 +155,10 @@ struct GroupQuant {
     // octave above it (the scale that puts the largest element on 4 instead of 6), so the window is c0 - 2 .. c0 + 7,
     // tried in the order c0, +1, -1, +2, -2, +3, +4, +5, +6, +7 (a brute force over every code finds the global minimiser
     // inside this window in all but about 1e-4 of the groups of heavy-tailed data; within +-1 in only half of them).
-    __device__ static __forceinline__ void nv_mse(const float (&y)[NO], float s_T, uint32_t (&out)[ND], uint32_t (&sc)[NG])
+    // Bound: the vector ALU, some 60 instructions for a candidate's eight values, eight of them conversions.  `steps` holds every code's step
+    // s_T s_G and its reciprocal (nv_steps); a division per candidate, and the test for a zero step in every one, took a sixth of the
+    // search.  (A group's two sums added with v_permlane16_swap instead of a shuffle through LDS: 5 % slower, LDS is idle here.)
+    __device__ static __forceinline__ void nv_mse(const float (&y)[NO], float s_T, const v2f_t* steps, uint32_t (&out)[ND], uint32_t (&sc)[NG])
     {
         const float six_sT = 6.0f * s_T;
 #pragma unroll
@@ -157,43 +166,53 @@ struct GroupQuant {
             float amax = 0.0f;
 #pragma unroll
             for (int i = 0; i < VG; ++i) amax = fabs_max(amax, y[gi * VG + i]);
-            if constexpr (LG >= 2) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO));
-            if constexpr (LG >= 4) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO * 2));
+            amax = group_max(amax);
             int c0 = 0;
             if (s_T > 0.0f) c0 = (int)e4m3_encode<true>(__fdiv_rn(amax, six_sT));
             float best_err = 0.0f;
             uint32_t best_c = 0, best[VG / 8];
-            // a rolled loop: ten copies of the body would not fit the instruction cache's share of a wave
-#pragma unroll 1
-            for (int k = 0; k < 10; ++k) {
+            auto candidate = [&](int k) {
                 const int off = k < 5 ? ((k & 1) ? (k + 1) >> 1 : -(k >> 1)) : k - 2;   // 0, +1, -1, +2, -2, +3 .. +7
-                const int c = min(max(c0 + off, 0), 0x7e);
-                const float d = s_T * e4m3_decode<true>((uint32_t)c);
-                const float r = (d == 0.0f) ? 0.0f : __fdiv_rn(1.0f, d);
-                float err = 0.0f;
-                uint32_t cand[VG / 8];
+                return min(max(c0 + off, 0), 0x7e);
+            };
+            // ZERO: some step of the wave's is 0 (a scale of 0, or one that underflows), where a group is left at zero
+            auto search = [&](auto zero) {
+                constexpr bool ZERO = decltype(zero)::value;
+                int next_c = candidate(0);
+                v2f_t next = steps[next_c];
+#pragma unroll 2   // (by candidates in flight: one 275, two 260, ten 259 us for [3000, 8192] with the fit's three rounds; ten are much code)
+                for (int k = 0; k < 10; ++k) {
+                    const int c = next_c;
+                    const float d = next[0], r = next[1];
+                    next_c = candidate(k + 1);
+                    next = steps[next_c];
+                    float err = 0.0f;
+                    uint32_t cand[VG / 8];
 #pragma unroll
-                for (int dd = 0; dd < VG / 8; ++dd) {
-                    // the error is measured in units of d: (y r - q)^2 d^2 = (y - q d)^2 up to the rounding of y r
-                    float t[8];
+                    for (int dd = 0; dd < VG / 8; ++dd) {
+                        // the error is measured in units of d: (y r - q)^2 d^2 = (y - q d)^2 up to the rounding of y r
+                        float t[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) t[i] = y[gi * VG + dd * 8 + i] * r;
-                    if (d == 0.0f) {
-                        cand[dd] = 0u;
+                        for (int i = 0; i < 8; ++i) t[i] = y[gi * VG + dd * 8 + i] * r;
+                        if (ZERO && d == 0.0f) {
+                            cand[dd] = 0u;
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) err = __fmaf_rn(y[gi * VG + dd * 8 + i], y[gi * VG + dd * 8 + i], err);
-                    } else {
-                        cand[dd] = try8(t, 1.0f, d, err);
+                            for (int i = 0; i < 8; ++i) err = __fmaf_rn(y[gi * VG + dd * 8 + i], y[gi * VG + dd * 8 + i], err);
+                        } else {
+                            cand[dd] = try8(t, 1.0f, d, err);
+                        }
+                    }
+                    err = group_sum(err);
+                    if (k == 0 || err < best_err) {
+                        best_err = err;
+                        best_c = (uint32_t)c;
+#pragma unroll
+                        for (int dd = 0; dd < VG / 8; ++dd) best[dd] = cand[dd];
                     }
                 }
-                err = group_sum(err);
-                if (k == 0 || err < best_err) {
-                    best_err = err;
-                    best_c = (uint32_t)c;
-#pragma unroll
-                    for (int dd = 0; dd < VG / 8; ++dd) best[dd] = cand[dd];
-                }
-            }
+            };
+            if (__any(steps[max(c0 - 2, 0)][0] == 0.0f)) search(std::true_type{});
+            else search(std::false_type{});
             sc[gi] = best_c;
 #pragma unroll
             for (int dd = 0; dd < VG / 8; ++dd) out[gi * (VG / 8) + dd] = best[dd];
@@ -226,8 +245,7 @@ struct GroupQuant {
             float amax = 0.0f;
 #pragma unroll
             for (int i = 0; i < VG; ++i) amax = fabs_max(amax, y[gi * VG + i]);
-            if constexpr (LG >= 2) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO));
-            if constexpr (LG >= 4) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO * 2));
+            amax = group_max(amax);
             const uint32_t ab = __float_as_uint(amax);
             const int ef = (int)((ab >> 23) & 0xffu);
             const int below = (ab & 0x7fffffu) < 0x7c3b7u ? 1 : 0;  // mantissa under 1.5 / sqrt 2
@@ -255,9 +273,7 @@ struct GroupQuant {
         float amax = 0.0f;
 #pragma unroll
         for (int i = 0; i < VG; ++i) amax = fabs_max(amax, y[gi * VG + i]);
-        if constexpr (LG >= 2) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO));
-        if constexpr (LG >= 4) amax = fmaxf(amax, __shfl_xor(amax, XOR_LO * 2));
-        return amax;
+        return group_max(amax);
     }
 
     __device__ static __forceinline__ void mx_fit(const float (&y)[NO], float lmin, float inv, const float* __restrict__ table,
@@ -282,9 +298,9 @@ struct GroupQuant {
         }
     }
 
-    // POL: 0 abs-max, 1 squared-error search, 2 rounded exponent with the 4/3 factor (MXFP4 only)
+    // POL: 0 abs-max, 1 squared-error search (NVFP4: with the workgroup's table), 2 rounded exponent with the 4/3 factor (MXFP4 only)
     template <int POL>
-    __device__ static __forceinline__ void run(const float (&y)[NO], float s_T, uint32_t (&out)[ND], uint32_t (&sc)[NG])
+    __device__ static __forceinline__ void run(const float (&y)[NO], float s_T, const v2f_t* steps, uint32_t (&out)[ND], uint32_t (&sc)[NG])
     {
         static_assert(POL >= 0 && POL <= 2 && (POL != 2 || G == 32), "scale policy");
         if constexpr (G == 32) {
@@ -292,11 +308,22 @@ struct GroupQuant {
             else if constexpr (POL == 2) mx43(y, out, sc);
             else mx(y, out, sc);
         } else {
-            if constexpr (POL == 1) nv_mse(y, s_T, out, sc); else nv(y, s_T, out, sc);
+            if constexpr (POL == 1) nv_mse(y, s_T, steps, out, sc); else nv(y, s_T, out, sc);
         }
     }
 };
 
+// steps[c] = s_T times E4M3 code c, and its reciprocal (0 where that is 0): 127 codes, by the first threads of the workgroup
+constexpr int kNvSteps = 128;
+typedef float v2f_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void nv_steps(v2f_t* steps, float s_T)
+{
+    for (int c = threadIdx.x; c < kNvSteps; c += blockDim.x) {
+        const float d = s_T * e4m3_decode<true>((uint32_t)c);
+        steps[c] = v2f_t{d, d == 0.0f ? 0.0f : __fdiv_rn(1.0f, d)};
+    }
+    __syncthreads();
+}
 
 // Hadamard operand of the rotation MFMA: A[i][k] = H[32s + k][c(t,i)] with c(t,i) = (i/4)*NO + 4t + i%4 (the column
 // permutation that leaves every lane with NO = BP/4 consecutive outputs); the lane holds i = g, k = 8q .. 8q+7.

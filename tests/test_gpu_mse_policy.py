@@ -84,6 +84,29 @@ def test_mse_policy_bit_exact_on_oracle_values(fp4, oracle, fmt):
     assert (ref_s != abs_s).mean() > 0.05
 
 
+@pytest.mark.parametrize("T", [None, 2.0 ** -20, 0.0])
+def test_mse_policy_around_zero_scales(fp4, oracle, T):
+    """Groups whose scale codes are 0, 1, 2 or more, side by side, and calls where all groups have larger ones: with and without a step
+    of zero among a wave's candidates."""
+    import torch
+    rng = np.random.default_rng(77)
+    M, K = 40, 1024
+    y = (rng.laplace(size=(M, K)) * (T or 1.0)).astype(np.float32)
+    y[8:24] *= np.repeat(2.0 ** -rng.integers(4, 22, (16, K // 16)), 16, axis=1).astype(np.float32)
+    y[24, ::2] = 0.0
+    y[25] = 0.0
+    ref_c, ref_s, ref_T = oracle.quantize(y, NV, tensor_scale=T, policy="mse")
+    given = None if T is None else torch.tensor([T], dtype=torch.float32, device="cuda")
+    c, s, _ = fp4.fp4_rotate_quantize(to_dev(y), 1, NV, flags=fp4.SCALE_MSE, tensor_scale=given)
+    c, s, s_T = np_(c).reshape(M, -1), np_(s).reshape(M, -1), ref_T if T is None else T
+    # (a group of which every candidate's codes are zeros ties all of them but for the rounding of sums of sixteen squares in binary32)
+    e_got, e_ref = (group_err(oracle, y, a, b, NV, s_T) for a, b in ((c, s), (ref_c, ref_s)))
+    assert np.all(np.abs(e_got - e_ref) <= 1e-5 * np.maximum(e_got, e_ref))
+    same = s == ref_s
+    assert np.array_equal(unpack(c)[np.repeat(same, 16, axis=1)], unpack(ref_c)[np.repeat(same, 16, axis=1)])
+    say(f"mse policy, zero scales, T={T}: {(~same).sum()} of {same.size} groups with another scale")
+
+
 @pytest.mark.parametrize("fmt", [MX, NV])
 @pytest.mark.parametrize("b", [16, 32, 128])
 def test_mse_policy_end_to_end_with_rotation(fp4, oracle, fmt, b):
