@@ -228,27 +228,20 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
     }
     const bool out_f32 = (flags & FP4MR_OUT_F32) != 0;
     const float alpha = scale43_factor(flags);
-    // Few tokens: the weight-streaming kernels, except MXFP4 with more than two 16-token blocks on a very wide layer with
-    // K > 4096, where the 64 x 256 tile kernel's time hardly grows with the token count and the streaming kernels' does
-    // (N = 57344, K = 14336, M = 48: 87 us against 113; K = 6144, M = 64: 39 against 45; below N = 40960 the streaming
-    // kernels win at every token count: N = 28672, K = 8192, M = 64: 27.7 us against 38.4).
-    const bool wide_mx = fmt == FP4MR_MXFP4 && M > 32 && N >= 40960 && K > 4096;
     // Optional split-K room behind what the call needs (FP4MR_OP_GEMM_SPLIT_K): used when the caller passed that much
     void* partial = nullptr;
     size_t partial_room = 0;
-    const bool few = variant == 0 && !wide_mx && gemm_skinny_takes(M, N, K, (int)fmt);
-    if (M > 64 && variant == 0 && !few) {
-        const bool mx = fmt == FP4MR_MXFP4;
-        const size_t extra = mx ? gemm_mx_split_k_bytes(M, N, K) : 1;   // (NVFP4: the product looks for itself what fits)
-        if (extra && workspace && aligned16(workspace) && workspace_bytes >= align256(need) + extra) {
-            partial = static_cast<char*>(workspace) + align256(need);
-            partial_room = workspace_bytes - align256(need);
-        }
+    if (M > 64 && variant == 0 && workspace && aligned16(workspace) && workspace_bytes > align256(need)) {
+        partial = static_cast<char*>(workspace) + align256(need);
+        partial_room = workspace_bytes - align256(need);
     }
+    MxPlan plan{variant, 1, 0};
+    if (fmt == FP4MR_MXFP4 && variant == 0) plan = plan_mx(M, N, K, partial_room);
+    const bool few = fmt == FP4MR_MXFP4 ? plan.variant == 0 : variant == 0 && gemm_nv_streams(M, N, K);
     if (few)
         e = launch_gemm_skinny(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, (int)fmt, out, out_f32, alpha, st);
     else if (fmt == FP4MR_MXFP4)
-        e = launch_gemm_mxfp4(a_codes, a_scales, w_codes, w_scales, M, N, K, out, out_f32, variant, alpha, partial, st);
+        e = launch_gemm_mxfp4(a_codes, a_scales, w_codes, w_scales, M, N, K, out, out_f32, plan, alpha, partial, st);
     else
         e = launch_gemm_nvfp4(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, variant, ws, partial, partial_room, st);
     return e == hipSuccess ? FP4MR_OK : FP4MR_ERR_DEVICE;
@@ -342,10 +335,10 @@ size_t fp4_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, fp4mr_fmt_t 
         if (!(flags & FP4MR_A_LAYOUT_GEMM)) n += repack_bytes(M, K, fmt);
         if (!(flags & FP4MR_W_LAYOUT_GEMM)) n += repack_bytes(N, K, fmt);
         // NVFP4 with more than 64 tokens: the activations are dequantized once to fp16 (2 bytes per element)
-        if (fmt == FP4MR_NVFP4 && M > 64 && !gemm_skinny_takes(M, N, K, (int)fmt)) n += align256(nv16_workspace_bytes(M, K));
+        if (fmt == FP4MR_NVFP4 && !gemm_nv_streams(M, N, K)) n += align256(nv16_workspace_bytes(M, K));
         // what fp4_gemm needs, plus -- optional -- the fp32 partials of a split-K run where the shape has one
-        if (op == FP4MR_OP_GEMM_SPLIT_K && M > 64 && !gemm_skinny_takes(M, N, K, (int)fmt)) {
-            const size_t extra = fmt == FP4MR_MXFP4 ? gemm_mx_split_k_bytes(M, N, K) : nv16_split_k_bytes(M, N, K);
+        if (op == FP4MR_OP_GEMM_SPLIT_K) {
+            const size_t extra = fmt == FP4MR_MXFP4 ? gemm_mx_split_k_bytes(M, N, K) : gemm_nv_streams(M, N, K) ? 0 : nv16_split_k_bytes(M, N, K);
             if (extra) n = align256(n) + extra;
         }
         return n;

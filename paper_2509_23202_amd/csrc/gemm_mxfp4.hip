@@ -14,7 +14,7 @@
 // operand (columns = m).  A lane then owns four consecutive n of one m, i.e. one 8-byte bf16x4 store.
 //
 // Block tile BM x BN, K-step 128, STAGES-deep LDS ring fed by direct-to-LDS loads (tracked with vmcnt), one
-// barrier per K-step.  Scales take the same route into a single LDS buffer: with four and more stages one 16-byte
+// barrier per K-step, or per two with eight stages.  Scales take the same route into a single LDS buffer: with four and more stages one 16-byte
 // copy per pair of row-blocks and 8 K-steps, with three stages one 4-byte copy per row-block and 4 K-steps.
 #include "device_util.hpp"
 #include "internal.hpp"
@@ -82,6 +82,11 @@ void gemm_mx_kernel(GemmArgs g)
     constexpr int LPW = (F + NW - 1) / NW;                  // fragment loads per wave per stage
     constexpr int TM = WM / 16, TN = WN / 16;               // MFMA tiles per wave
     constexpr int STAGE_BYTES = F * 1024;
+    // PAIR: one barrier, and one wait for LDS reads, per two K-steps, for a stage less on its way: what a step of a small tile
+    // takes beside its copies (20 ns a KB, the compute unit's load path) falls from 110 to 75 ns (128 x 128 tiles, N = 4096, M = 400:
+    // K = 4096 11.2 -> 10.5 us, 14336 27.8 -> 26.2; with six or seven stages the stages missing cost more than that).
+    constexpr bool PAIR = STAGES == 8 && !PERSIST;
+    constexpr int LEAD = PAIR ? STAGES - 2 : STAGES - 1;    // a step requests the stage that many steps behind its own
     static_assert(STAGES >= 3 && STAGES <= 8, "ring bookkeeping is written for 3 to 8 stages");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -162,8 +167,8 @@ void gemm_mx_kernel(GemmArgs g)
     // Software pipeline of the LDS reads: the X fragments of step kt+1 are read into the other half of xf[2][.]
     // while step kt computes, and the W fragments run through a 4-deep register ring two groups of TM MFMAs ahead
     // of their use -- so no MFMA waits on LDS latency, at a cost of 2*TM*4 + 16 fragment registers.
-    // W-fragment register ring; RD = how many MFMA groups ahead it is filled (three slots when TN is not a multiple of 4)
-    constexpr int RING = (TN % 4 != 0) ? 3 : ((RD <= 3) ? 4 : 8);
+    // W-fragment register ring; RD = how many MFMA groups ahead it is filled (three or two slots when TN is not a multiple of 4)
+    constexpr int RING = TN == 2 ? 2 : (TN % 4 != 0) ? 3 : 4;
     v4i xf[2][TM], wring[RING];
     static_assert(TN % RING == 0 && RD < RING && RD <= TN, "the W-fragment ring index must be static");
     // every wave issues exactly LPW fragment loads per stage and NS scale loads per batch so that the vmcnt
@@ -227,23 +232,26 @@ void gemm_mx_kernel(GemmArgs g)
         wring[i % RING] = *(reinterpret_cast<const v4i*>(smem + (kt % STAGES) * STAGE_BYTES + (FX + wn * TN + i) * 1024) + lane);
     };
 
-    // prologue of a tile: scales of super-step 0 and STAGES-1 stages on their way into ring slots 0 .. STAGES-2
+    // prologue of a tile: scales of super-step 0 and LEAD stages on their way into ring slots 0 .. LEAD-1
     auto issue_prologue = [&]() {
         issue_scales(0);
 #pragma unroll
-        for (int s = 0; s < STAGES - 1; ++s) {
+        for (int s = 0; s < LEAD; ++s) {
 #pragma unroll
             for (int i = 0; i < LPW; ++i) issue_frag_one(min(s, KT - 1), smem + s * STAGE_BYTES, i);
         }
     };
     issue_prologue();
-    wait_vmcnt<(STAGES - 2) * LPW>();
+    wait_vmcnt<(LEAD - 1) * LPW>();
 
     // One K-step.  J = kt % 8 (SC8) or kt % 4: J & 3 selects the scale byte (op_sel), J & 1 the X register half.
     //   top:    stage kt+1 must have landed (this wave's copies: vmcnt; everybody's: barrier).  The same barrier
     //           says that every wave is done reading stage kt-1, whose LDS buffer is refilled with stage kt+STAGES-1.
     //   vmcnt:  allowed in flight = the STAGES-3 stages after kt+1, plus one scale batch when it was issued after
     //           stage kt+1's loads (batches go out at J == 0, ahead of that step's fragment loads).
+    // PAIR: an even step waits for the stages kt+1 and kt+2 of itself and of the odd step behind it, which has no wait of its own; the
+    // barrier says that stages kt-2 and kt-1 have been read, whose slots the two steps refill with stages kt+STAGES-2 and
+    // kt+STAGES-1; STAGES-5 stages may be in flight.  A scale batch (requested in step 8b) has landed for step 8b+6.
     constexpr int NST = TM * (16 * (WN / 8) / 64);  // store instructions a wave issues for one interior output tile
     static_assert((STAGES - 2) * LPW + NST < 64 && (STAGES - 3) * LPW + NS + NST < 64, "vmcnt is a 6-bit counter");
     bool pend = false;  // persistent workgroups: the previous tile's stores may be outstanding at the top of this tile
@@ -256,28 +264,31 @@ void gemm_mx_kernel(GemmArgs g)
         constexpr int P = J & 1;
         constexpr int JB = (SC8 && SD == 1) ? 4 : 0;  // the step of a period that requests the next scale batch
         constexpr int PER = SC8 ? 8 : 4;                // steps per scale batch
-        // the batch was requested 1 .. STAGES - 3 steps ago, i.e. behind the loads of the stage this step waits for
-        constexpr bool batch_after = ((J - JB - 1 + PER) % PER) <= STAGES - 4;
-        constexpr int ALLOWED = (STAGES - 3) * LPW + (batch_after ? NS : 0);
+        // the batch was requested 1 .. FLYING steps ago, i.e. behind the loads of the stage this step waits for
+        constexpr int FLYING = PAIR ? STAGES - 5 : STAGES - 3;
+        constexpr bool batch_after = ((J - JB - 1 + PER) % PER) <= FLYING - 1;
+        constexpr int ALLOWED = FLYING * LPW + (batch_after ? NS : 0);
         if constexpr (PERSIST && J <= STAGES - 3) {
             // first steps of a follow-on tile, as long as the stage they wait for (kt + 1) is one of the STAGES - 1 that
             // were prefetched: the previous tile's NST output stores were issued after those and may still be in flight
             // (vector memory operations complete in issue order, so the stages in front of the stores can be waited for
             // without waiting for the stores)
             if (pend && kt <= STAGES - 3) wait_vmcnt<ALLOWED + NST>(); else wait_vmcnt<ALLOWED>();
-        } else {
+        } else if constexpr (!PAIR || J % 2 == 0) {
             wait_vmcnt<ALLOWED>();
         }
-        wait_lgkmcnt0();
-        block_barrier();
-        // The global -> LDS loads of stage kt+STAGES-1 (and, at J == 0, of the next scale batch) are spread over the
+        if constexpr (!PAIR || J % 2 == 0) {
+            wait_lgkmcnt0();
+            block_barrier();
+        }
+        // The global -> LDS loads of stage kt+LEAD (and, at J == 0, of the next scale batch) are spread over the
         // groups of MFMAs: a wave issues in order, and a burst of vector-memory instructions at the top of the step
         // would hold its MFMAs back while the CU's single address unit works through all four waves' bursts.
         // Past the last stage the loads re-copy stage KT-1 into a ring slot nobody reads any more: the step body stays
         // free of branches (which would let the compiler pull the MFMAs away from the loads they are meant to cover)
         // and the vmcnt bookkeeping needs no special case for the tail.
-        const int kt_load = min(kt + STAGES - 1, KT - 1);
-        char* const load_base = smem + ((kt + STAGES - 1) % STAGES) * STAGE_BYTES;
+        const int kt_load = min(kt + LEAD, KT - 1);
+        char* const load_base = smem + ((kt + LEAD) % STAGES) * STAGE_BYTES;
         constexpr int DPG = (LPW + TN - 1) / TN;  // loads per group
 #pragma unroll
         for (int i = 0; i < TN; ++i) {
@@ -458,23 +469,39 @@ void gemm_mx_kernel(GemmArgs g)
 }
 
 
-// out[i] = alpha * (partial[0][i] + partial[1][i] + ...), the splits added in their order (deterministic), as bf16 or fp32
-template <bool OUT_F32>
+// out[i] = alpha * (partial[0][i] + partial[1][i] + ...), the splits added in their order (deterministic), as bf16 or fp32; V
+// neighbouring values per thread (four where mn and `partial` allow it), all splits' loads on their way together
+template <bool OUT_F32, int V>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int64_t mn, float alpha, void* out)
 {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < mn; i += (int64_t)gridDim.x * 256) {
-        float s = partial[i];
-        for (int p = 1; p < splits; ++p) s += partial[(int64_t)p * mn + i];
-        s *= alpha;
-        if constexpr (OUT_F32) static_cast<float*>(out)[i] = s;
-        else static_cast<__bf16*>(out)[i] = (__bf16)s;
-    }
+    constexpr int kMost = 8;   // splits (plan_mx)
+    typedef float vec __attribute__((ext_vector_type(V)));
+    typedef __bf16 vecb __attribute__((ext_vector_type(V)));
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
+    if (i >= mn) return;
+    vec x[kMost];
+#pragma unroll
+    for (int p = 0; p < kMost; ++p)
+        if (p < splits) x[p] = *reinterpret_cast<const vec*>(partial + (int64_t)p * mn + i);
+    vec s = x[0];
+#pragma unroll
+    for (int p = 1; p < kMost; ++p)
+        if (p < splits) s += x[p];
+    s *= alpha;
+    if constexpr (OUT_F32) *reinterpret_cast<vec*>(static_cast<float*>(out) + i) = s;
+    else *reinterpret_cast<vecb*>(static_cast<__bf16*>(out) + i) = __builtin_convertvector(s, vecb);
 }
 
-// the tile shapes that have a split-K instantiation (the ones the cost model picks for shapes with few tiles)
-template <int BM, int BN, int WM, int RD, bool PERSIST, int STAGES>
-constexpr bool kHasSplitK = !PERSIST && STAGES == 4 && ((BM == 128 && BN == 128) || (BM == 256 && BN == 128 && WM == 64) ||
-                                         (BM == 256 && BN == 256 && WM == 64 && RD == 3));
+template <int V>
+void launch_splitk_reduce(const float* partial, int splits, int64_t mn, float alpha, void* out, bool out_f32, hipStream_t st)
+{
+    const dim3 grid((unsigned)((mn + 256 * V - 1) / (256 * V)));
+    if (out_f32) hipLaunchKernelGGL((splitk_reduce_kernel<true, V>), grid, dim3(256), 0, st, partial, splits, mn, alpha, out);
+    else hipLaunchKernelGGL((splitk_reduce_kernel<false, V>), grid, dim3(256), 0, st, partial, splits, mn, alpha, out);
+}
+
+// the tile shapes that have a split-K instantiation
+constexpr bool tile_splits(int bm, int bn) { return bm <= 96 && bn <= 128; }
 
 // splits > 1: every tile is computed by `splits` workgroups, split y taking K-steps y * split_steps .. and writing its
 // fp32 partial tile to slice y of `partial`; the caller then runs splitk_reduce_kernel
@@ -485,7 +512,7 @@ hipError_t launch_variant(const GemmArgs& g0, bool out_f32, hipStream_t st, int 
     g.tiles_m = (int)((g.M + BM - 1) / BM);
     g.tiles_n = (int)((g.N + BN - 1) / BN);
     if (splits > 1) {
-        if constexpr (kHasSplitK<BM, BN, WM, RD, PERSIST, STAGES>) {
+        if constexpr (tile_splits(BM, BN)) {
             constexpr int threads_s = (BM / WM) * (BN / WN) * 64;
             constexpr size_t lds_s = (size_t)STAGES * (BM + BN) / 16 * 1024 +
                                      (STAGES >= 4 ? (size_t)((BM / 16 + 1) / 2 + (BN / 16 + 1) / 2) * 1024 * (STAGES >= 6 ? 2 : 1) : (size_t)(BM + BN) / 16 * 256);
@@ -499,9 +526,8 @@ hipError_t launch_variant(const GemmArgs& g0, bool out_f32, hipStream_t st, int 
             hipLaunchKernelGGL(k, dim3((unsigned)(g.tiles_m * g.tiles_n), (unsigned)splits), dim3(threads_s), lds_s, st, g);
             if ((es = hipGetLastError()) != hipSuccess) return es;
             const int64_t mn = g.M * g.N;
-            const unsigned rblocks = (unsigned)std::min<int64_t>((mn + 255) / 256, 256 * 16);
-            if (out_f32) hipLaunchKernelGGL(splitk_reduce_kernel<true>, dim3(rblocks), dim3(256), 0, st, partial, splits, mn, g0.alpha, g0.out);
-            else hipLaunchKernelGGL(splitk_reduce_kernel<false>, dim3(rblocks), dim3(256), 0, st, partial, splits, mn, g0.alpha, g0.out);
+            if (mn % 4 == 0) launch_splitk_reduce<4>(partial, splits, mn, g0.alpha, g0.out, out_f32, st);   // (both buffers begin at multiples of 16 bytes)
+            else launch_splitk_reduce<1>(partial, splits, mn, g0.alpha, g0.out, out_f32, st);
             return hipGetLastError();
         } else {
             return hipErrorInvalidValue;
@@ -554,6 +580,11 @@ struct TileCost {
 // reads under the other's products, against four of 128 x 64 M = 1111, N = 4096, K = 14336: 45.5 -> 41.0 us.  128 x 256 with two
 // workgroups per compute unit overlaps one's start-up and stores with the other's main loop: where a tile is not much longer
 // than those (M = 2166, N = 10968, K = 1024: 26.5 us, the best of the others 30.0; M = 1104, N = 26544, K = 1536: 38.4 against 42.5).
+// Where 128 x 128 tiles leave compute units without one, what a step takes is hardly its products: 75 ns, and 20 a KB of copies.  Tiles
+// of 64 or 96 rows and 64 or 128 columns put more units to work on fewer bytes each.  The last four rows are fitted to 9996 products with
+// cold weights (M = 65 ... 4096, N = 512 ... 28672, K = 1024 ... 28672), on the scale of the others.  Against the plan without them and with the streaming kernels
+// up to a fixed size: 0.92 of the time on average over 3352 products of up to 4096 tokens, 100 slower by 3 % and two by 10 (N = K = 2048, M = 201:
+// 6.8 -> 5.0 us; N = 1024, K = 2816: 7.8 -> 5.5; N = 6144, K = 4096: 11.1 -> 9.6; N = K = 8192: 21.8 -> 17.9).
 constexpr TileCost kTileCosts[] = {
     {2, 128, 128, 2, 3.539, 0.307, 0.207, 0.890, 1.100, 2.998, 0.227, 0.525},
     {18, 128, 128, 1, 2.486, 0.188, 0.096, 1.359, 1.560},   // one workgroup per compute unit, eight-stage ring
@@ -567,14 +598,10 @@ constexpr TileCost kTileCosts[] = {
     {11, 256, 256, 1, 6.536, 0.454, 0.293, 1.470, 4.683},   // persistent: the next tile's first stages and the stores overlap
     {15, 128, 256, 2, 5.720, 0.475, 0.516, 0.119, 1.977, 5.139, 0.452, 0.275},
     {16, 128, 256, 2, 5.883, 0.607, 0.367, 1.472, 1.613, 2.756, 0.456, 0.314},   // persistent
-};
-
-// The shapes that run as split-K parts, priced from such runs (shorter K per workgroup, fp32 partials).  Of 1154 products 61 took a split
-// that measured 1.4 times as fast as the unsplit run on average; they take the same one here, and three others split, level with the unsplit run.
-constexpr TileCost kSplitCosts[] = {
-    {2, 128, 128, 2, 2.530, 0.253, 0.256, 1.760, 0.0, 1.980, 0.232, 0.194},
-    {5, 256, 128, 1, 4.180, 0.292, 0.165, 0.550, 0.0},
-    {10, 256, 256, 1, 6.270, 0.512, 0.322, 0.0, 0.0},
+    {1, 64, 64, 2, 1.381, 0.131, 0.117, 2.946, 0.000, 0.145, 0.132, 0.208},     // these four with an eight-stage ring
+    {4, 64, 128, 1, 0.637, 0.164, 0.043, 3.028, 0.538},
+    {9, 96, 128, 1, 1.678, 0.183, 0.052, 2.475, 0.498},
+    {12, 96, 64, 1, 2.216, 0.149, 0.028, 1.506, 0.000},
 };
 
 double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int cus)
@@ -587,26 +614,33 @@ double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int 
     return t;
 }
 
-// Tile configuration by shape (the numbers of launch_gemm_mxfp4's switch): the cheapest by the table above, with more than 64
-// tokens and a partials buffer also as a split-K run.  With few tiles and a long K -- 65 to a few hundred tokens against
-// a narrow layer, the batched-decoding regime -- a handful of compute units each stream a long K range alone and the launch is
-// bound by the latency of their few loads in flight (M = 128, N = 4096, K = 14336: 32 tiles, 42 us, 0.7 TB/s).  Every tile's
-// K range can then be cut into up to eight parts of at least 16 K-steps (whole scale batches of eight), each part one
-// workgroup of as many tiles (17 us on that shape).  The reduction of the partials costs another launch and their way to
-// memory and back, 6 us + bytes at 10.9 TB/s (they are read back from the last-level cache), and a split has to win 4 %.
-void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int* splits, int* steps)
+}  // namespace
+
+// The cheapest way of a product: the tiles of the table above (variant: a number of launch_gemm_mxfp4's switch), with more than 64 tokens and
+// room for partials also as a split-K run, or the streaming kernels (variant 0), which have a price of their own (gemm_stream_us).
+// With few tiles and a long K -- batched decoding against a narrow layer -- a handful of compute units each stream a long K range alone.
+// Every tile's K range can then be cut into up to eight parts of at least 16 K-steps (whole scale batches of eight), each part one
+// workgroup of as many tiles.  Priced as as many tiles of as many steps, which share their start, and 3.9 us + bytes at 4 TB/s for the
+// partials and their sum's launch; a split has to win 4 %.  Of 2208 products with K from 4096 to 28672, parts of up to 96 rows
+// were the best way in 749, 1.26 times as fast as the best unsplit one on average; parts of 128 and more rows in nine.
+MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room)
 {
-    *splits = 1;
-    *steps = 0;
-    if (M <= 64) {
-        *variant = M <= 16 ? 4 : 3;
-        return;
-    }
+    MxPlan p{0, 1, 0};
+    if (M <= 16) return p;
+    // (more than 32 tokens on a very wide layer: 64 x 256 tiles, whose time hardly grows with the token count; N = 57344, K = 14336, M = 48:
+    // 87 us, streamed 113; K = 6144, M = 64: 39 and 45)
+    if (M > 32 && M <= 64 && N >= 40960 && K > 4096) return MxPlan{3, 1, 0};
+    const double stream = gemm_stream_us(M, N, K);
+    if (stream == 0.0) return p;
     const int cus = compute_units();
     const int64_t kt = K >> 7;
     auto tiles = [&](const TileCost& c) { return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
-    double best = 1e30;
+    // Up to 64 tokens both prices are rough where they are close (and the tiles were not timed beyond N = 32768): tiles have to win a
+    // fifth.  Of 7463 products of 20 to 64 tokens 0.96 of the streaming kernels' time on average; K = 1024, N > 8192 0.8.
+    if (M <= 64 && N > 32768) return p;
+    double best = M <= 64 ? stream / 1.2 : stream;
     for (const TileCost& c : kTileCosts) {
+        if (M <= 64 && c.bm != 64) continue;
         const int64_t t = tiles(c);
         if ((c.variant == 17 || c.variant == 18) && t > cus) continue;
         // (persistent workgroups: only where there is a next tile, and not for a ragged few rounds, where one workgroup per tile, which
@@ -616,42 +650,39 @@ void plan_mx(int64_t M, int64_t N, int64_t K, bool may_split, int* variant, int*
         const double us = tile_cost(c, t, kt, N % 32 != 0, cus);
         if (us < best) {
             best = us;
-            *variant = c.variant;
+            p.variant = c.variant;
         }
     }
-    if (!may_split) return;
+    if (M <= 64 || kt < 32) return p;
     best *= 0.96;
-    for (const TileCost& c : kSplitCosts) {
+    for (const TileCost& c : kTileCosts) {
+        if (!tile_splits(c.bm, c.bn)) continue;
         const int64_t t = tiles(c), s_max = std::min<int64_t>(std::min<int64_t>((int64_t)cus * c.per_cu / t, kt / 16), 8);
         for (int64_t s = 2; s <= s_max; ++s) {
             const int64_t st = ((kt + s - 1) / s + 7) / 8 * 8;
             const int64_t n = (kt + st - 1) / st;  // parts of st steps that cover K (the last may be shorter)
-            if (n < 2) continue;
-            const double us = tile_cost(c, t * n, st, false, cus) + 6.05 + (double)n * (double)M * (double)N * 8.0 / 10.9e6;
+            const double bytes = (double)n * (double)M * (double)N * 4.0;
+            if (n < 2 || bytes > (double)room) continue;
+            const double us = 0.871 * tile_cost(c, t * n, st, false, cus) + 3.94 + 2.0 * bytes / 8.03e6;
             if (us < best) {
                 best = us;
-                *variant = c.variant;
-                *splits = (int)n;
-                *steps = (int)st;
+                p = MxPlan{c.variant, (int)n, (int)st};
             }
         }
     }
+    return p;
 }
-
-}  // namespace
 
 // bytes of fp32 partials a split-K run of this product needs (0: the product is not split)
 size_t gemm_mx_split_k_bytes(int64_t M, int64_t N, int64_t K)
 {
-    int variant, splits, steps;
-    plan_mx(M, N, K, true, &variant, &splits, &steps);
-    return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * 4 : 0;
+    const MxPlan p = plan_mx(M, N, K, SIZE_MAX);
+    return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * 4 : 0;
 }
 
-// variant: 0 = pick by shape; 1.. = force a tile configuration (used by the benchmark's sweep)
-// partial: room for gemm_mx_split_k_bytes(M, N, K) bytes, or null (then the product is never split)
+// plan: of plan_mx, with a tile configuration, or any such (variant 1 ..) in one part; partial: room for a split run's partials
 hipError_t launch_gemm_mxfp4(const void* a_codes, const void* a_scales, const void* w_codes, const void* w_scales,
-                             int64_t M, int64_t N, int64_t K, void* out, bool out_f32, int variant, float alpha, void* partial,
+                             int64_t M, int64_t N, int64_t K, void* out, bool out_f32, const MxPlan& plan, float alpha, void* partial,
                              hipStream_t st)
 {
     GemmArgs g{};
@@ -664,22 +695,21 @@ hipError_t launch_gemm_mxfp4(const void* a_codes, const void* a_scales, const vo
     g.M = M;
     g.N = N;
     g.K = K;
-    int splits = 1, split_steps = 0;
-    if (variant == 0) plan_mx(M, N, K, partial != nullptr, &variant, &splits, &split_steps);
+    const int splits = plan.splits, split_steps = plan.steps;
     float* const pp = static_cast<float*>(partial);
-    switch (variant) {
-        case 1: return launch_variant<256, 256, 128, 128, 4>(g, out_f32, st);
-        case 2: return launch_variant<128, 128, 64, 64, 4>(g, out_f32, st, splits, split_steps, pp);
+    switch (plan.variant) {
+        case 1: return launch_variant<64, 64, 32, 32, 8, 1>(g, out_f32, st, splits, split_steps, pp);
+        case 2: return launch_variant<128, 128, 64, 64, 4>(g, out_f32, st);
         case 3: return launch_variant<64, 256, 64, 64, 4>(g, out_f32, st);
-        case 4: return launch_variant<16, 256, 16, 64, 4>(g, out_f32, st);
-        case 5: return launch_variant<256, 128, 64, 64, 4>(g, out_f32, st, splits, split_steps, pp);
+        case 4: return launch_variant<64, 128, 32, 64, 8>(g, out_f32, st, splits, split_steps, pp);
+        case 5: return launch_variant<256, 128, 64, 64, 4>(g, out_f32, st);
         case 6: return launch_variant<192, 128, 48, 64, 4>(g, out_f32, st);
         case 7: return launch_variant<160, 128, 80, 64, 4>(g, out_f32, st);
         case 8: return launch_variant<192, 256, 96, 64, 4>(g, out_f32, st);
-        case 9: return launch_variant<256, 256, 128, 128, 4, 6>(g, out_f32, st);
-        case 10: return launch_variant<256, 256, 64, 128, 4, 3>(g, out_f32, st, splits, split_steps, pp);
+        case 9: return launch_variant<96, 128, 48, 64, 8>(g, out_f32, st, splits, split_steps, pp);
+        case 10: return launch_variant<256, 256, 64, 128, 4, 3>(g, out_f32, st);
         case 11: return launch_variant<256, 256, 64, 128, 4, 3, true>(g, out_f32, st);
-        case 12: return launch_variant<256, 128, 128, 64, 4, 2, true>(g, out_f32, st);
+        case 12: return launch_variant<96, 64, 48, 32, 8, 1>(g, out_f32, st, splits, split_steps, pp);
         case 13: return launch_variant<256, 192, 64, 96, 4, 2>(g, out_f32, st);
         case 14: return launch_variant<256, 192, 64, 96, 4, 2, true>(g, out_f32, st);
         case 15: return launch_variant<128, 256, 64, 128, 3, 3>(g, out_f32, st);

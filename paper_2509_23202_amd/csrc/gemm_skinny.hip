@@ -1,4 +1,4 @@
-// W4A4 GEMM for few tokens (M <= 64, and up to 128 on narrow MXFP4 layers): the weight-streaming regime (arXiv 2509.23202, appendix on inference regimes:
+// W4A4 GEMM for few tokens (M <= 64, and up to 512 on narrow layers): the weight-streaming regime (arXiv 2509.23202, appendix on inference regimes:
 // at small batch the layer is memory-bound).  out[m,n] = sum_k Ahat[m,k] * What[n,k], both formats.
 //
 // The weights are read exactly once, straight from global memory into registers: a workgroup owns one 16-column
@@ -794,40 +794,46 @@ hipError_t launch_fmt(const SkinnyArgs& g, bool out_f32, hipStream_t st)
 
 }  // namespace
 
-// More than 64 tokens: MXFP4 with K <= 8192 as several sets of persistent workgroups (up to four resident token blocks
-// each), on layers narrow enough that the tile kernels' cost per launch (12-14 us at K = 4096, 15-25 at K = 8192, whatever
-// the token count) exceeds what the persistent kernel spends per row-block and set.  Measured, cold weights, tiles -> sets:
-// M = 96 (two sets), K = 4096: N = 4096 12.6 -> 6.4 us, 8192 12.9 -> 8.6, 14336 14.3 -> 12.2, 28672 17.9 -> 20.4 (not taken);
-// K = 8192: N = 4096 16.0 -> 9.3, 8192 17.8 -> 12.6, 14336 25.1 -> 18.9; K = 2048: N = 4096 8.1 -> 6.0, 8192 9.4 -> 8.7,
-// 14336 10.1 -> 12.6 (not taken); K = 1024: level or slower (not taken).  M = 256 (four sets), K = 4096: N = 4096 13.6 -> 9.3,
-// 6144 14.2 -> 11.2, 8192 14.5 -> 13.3, 14336 16.8 -> 20.9 (not taken); K = 8192: N = 4096 23.8 -> 12.7, 8192 24.5 -> 19.7.
-// M = 512 (eight sets): N = 4096 13.8 -> 12.8 (K = 4096), 24.0 -> 18.5 (K = 8192); N = 6144 15.1 -> 17.4 (not taken).
-// So: sets x N up to 28672 (N = 16384, K = 6144, M = 128: 17.9 -> 21.3, not taken).  K = 14336 (sets of two blocks): level with the split-K tiles at N = 4096, slower beyond (not taken).
-bool gemm_skinny_takes(int64_t M, int64_t N, int64_t K, int fmt)
+// What the MXFP4 streaming kernels take with more than 16 tokens, in microseconds: the activations' way into registers, then row-blocks
+// per workgroup times (a fixed part, the products, the loads in batches of four fragments).  Up to 64 tokens in one set of workgroups
+// where they fit, else, up to 512 tokens, in several sets (K <= 16384, with more than 64 tokens 8192; they pay on layers narrow enough that
+// each set has few row-blocks).  Fitted to 6751 and 4552 products with cold weights (N = 512 ... 57344, K = 1024 ... 14336), median error 2.5 %.
+// 0: not priced, up to 64 tokens they take it; infinity: they do not take it.
+double gemm_stream_us(int64_t M, int64_t N, int64_t K)
+{
+    const double none = __builtin_inf();
+    if (M > 512) return none;
+    const int per = (int)(((K >> 7) + kSkinnyWaves - 1) / kSkinnyWaves), nbk = (per + 3) / 4, mt = (int)((M + 15) / 16);  // fragments of K per wave
+    const int64_t n_rb = (N + 15) / 16;
+    const int cus = compute_units();
+    if (per == 1) return mt > 4 ? none : 2.90 + 0.256 * mt + (double)n_rb / cus * (0.611 + 0.106 * mt);   // (one-shot)
+    if (mt <= 4 && nbk <= stream_max_batches(mt)) {
+        const double rounds = (double)((n_rb + cus - 1) / cus);
+        return 2.34 + (0.0219 * per + 0.277 * nbk) * mt + rounds * (0.0381 + 0.0544 * per + 0.0789 * mt + 0.308 * nbk) + 0.146 * per * (double)n_rb / cus;
+    }
+    const int most = nbk <= stream_max_batches(4) ? 4 : nbk <= stream_max_batches(2) ? 2 : 0;
+    if (most == 0 || (mt > 4 && most < 4)) return mt <= 4 ? 0.0 : none;   // (more than 64 tokens with K > 8192: not timed)
+    const int parts = (mt + most - 1) / most, m = (mt + parts - 1) / parts, walkers = std::max(cus / parts / 8 * 8, 8);
+    const double rounds = (double)((n_rb + walkers - 1) / walkers);
+    return 2.80 + (0.0498 * per + 0.117 * nbk) * m + rounds * (0.180 + 0.0045 * per + 0.0317 * m + 0.524 * nbk) + 0.0480 * per * (double)n_rb / walkers;
+}
+
+// NVFP4: every product of up to 64 tokens, and of 65 to 256 one set of fp16-resident persistent workgroups per 16-token block where the layer is small
+// enough that dequantizing W once per set costs less than the many-token kernel's launch (which multiplies whole
+// 128-token tiles on a few compute units).  Measured, cold weights, tiles -> sets: N = K = 4096, M = 80 / 128 / 256:
+// 20.7 / 26.1 / 25.3 -> 10.3 / 12.5 / 21.6 us; N = K = 2048: 13.8 / 15.4 / 18.8 -> 4.8 / 5.7 / 8.5; N = 12288, K = 4096,
+// M = 80 / 128: 28.4 / 32.3 -> 21.2 / 30.3; N = 10240, K = 8192, M = 96 / 128: 38.2 / 41.6 -> 36.8 / 44.7 (128: not taken).
+// (257 to 512 tokens -- up to 32 sets -- on the smallest layers only: N = K = 2048, M = 512: 25 -> 15 us)
+bool gemm_nv_streams(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 64) return true;
     const int64_t per = ((K >> 7) + kSkinnyWaves - 1) / kSkinnyWaves;  // fragments of K per wave
-    // NVFP4, 65 to 256 tokens: one set of fp16-resident persistent workgroups per 16-token block where the layer is small
-    // enough that dequantizing W once per set costs less than the many-token kernel's launch (which multiplies whole
-    // 128-token tiles on a few compute units).  Measured, cold weights, tiles -> sets: N = K = 4096, M = 80 / 128 / 256:
-    // 20.7 / 26.1 / 25.3 -> 10.3 / 12.5 / 21.6 us; N = K = 2048: 13.8 / 15.4 / 18.8 -> 4.8 / 5.7 / 8.5; N = 12288, K = 4096,
-    // M = 80 / 128: 28.4 / 32.3 -> 21.2 / 30.3; N = 10240, K = 8192, M = 96 / 128: 38.2 / 41.6 -> 36.8 / 44.7 (128: not taken).
-    // (257 to 512 tokens -- up to 32 sets -- on the smallest layers only: N = K = 2048, M = 512: 25 -> 15 us)
-    if (fmt == 1) {
-        if (per > 8 || N > 12288) return false;
-        const int64_t work = (M + 15) / 16 * N * K;
-        // (one fragment per wave, K <= 1024: a set's row-block is mostly its barrier and reduction -- N = 8192, K = 1024:
-        // M = 80 / 128: 16 -> 9.0 / 11.9 us, M = 192: 17 -> 19.9, not taken)
-        if (per == 1) return M <= 256 && work <= (int64_t)1 << 26;
-        return M <= 512 && work <= (int64_t)1 << (M <= 256 ? 29 : 28);
-    }
-    if (fmt != 0 || M > 512) return false;
-    // (up to four sets at K <= 4096: N = 4096, M = 384 / 512 measured 11.5 / 11.7 us on tiles against 12.3 / 13.5; with a longer
-    // K the tiles cost more and up to eight sets pay: N = 4096, K = 8192, M = 512: 24.0 -> 18.5)
-    const int64_t sets = (M + 63) / 64;
-    if (per >= 4 && per <= 8) return sets * N <= 28672 && (per > 4 || sets <= 4);
-    if (per == 2 || per == 3) return M <= 128 && N <= 8192;
-    return false;
+    if (per > 8 || N > 12288) return false;
+    const int64_t work = (M + 15) / 16 * N * K;
+    // (one fragment per wave, K <= 1024: a set's row-block is mostly its barrier and reduction -- N = 8192, K = 1024:
+    // M = 80 / 128: 16 -> 9.0 / 11.9 us, M = 192: 17 -> 19.9, not taken)
+    if (per == 1) return M <= 256 && work <= (int64_t)1 << 26;
+    return M <= 512 && work <= (int64_t)1 << (M <= 256 ? 29 : 28);
 }
 
 hipError_t launch_gemm_skinny(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,

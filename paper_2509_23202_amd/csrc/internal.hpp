@@ -50,11 +50,20 @@ hipError_t launch_rotate_quantize(const void* x, int64_t rows, int64_t K, int b,
 hipError_t launch_repack_to_gemm(const void* codes, const void* scales, int64_t rows, int64_t K, int fmt,
                                  void* codes_gemm, void* scales_gemm, hipStream_t st);
 
+// variant: a tile configuration of the MXFP4 GEMM, or 0 for the few-token kernels; splits > 1: parts of `steps` K-steps each
+struct MxPlan {
+    int variant, splits, steps;
+};
+
 // both operands in GEMM layout; alpha multiplies the result (1, or powers of 4/3 for operands quantized with the
 // rounded-exponent rule whose scale bytes leave that tensor-level factor out)
 hipError_t launch_gemm_mxfp4(const void* a_codes, const void* a_scales, const void* w_codes, const void* w_scales,
-                             int64_t M, int64_t N, int64_t K, void* out, bool out_f32, int variant, float alpha, void* partial,
+                             int64_t M, int64_t N, int64_t K, void* out, bool out_f32, const MxPlan& plan, float alpha, void* partial,
                              hipStream_t st);
+// how an MXFP4 product runs best with `room` bytes for partials
+MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room);
+// what the few-token kernels take for it, in microseconds; 0: they take it, whatever that is; infinity: they do not take it
+double gemm_stream_us(int64_t M, int64_t N, int64_t K);
 // fp32 partials of a split-K run (few tiles, long K: every tile's K range shared by several workgroups); 0 = not split
 size_t gemm_mx_split_k_bytes(int64_t M, int64_t N, int64_t K);
 
@@ -73,9 +82,9 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
 // split); 0 = not split
 size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K);
 
-// few-token weight-streaming GEMM, both formats, operands in GEMM layout: every shape up to 64 tokens, and the shapes
-// gemm_skinny_takes() accepts above that
-bool gemm_skinny_takes(int64_t M, int64_t N, int64_t K, int fmt);
+// few-token weight-streaming GEMM, both formats, operands in GEMM layout: every shape up to 64 tokens, and above that those that
+// gemm_nv_streams accepts (NVFP4) and gemm_stream_us prices (MXFP4)
+bool gemm_nv_streams(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_skinny(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                               const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, int fmt, void* out,
                               bool out_f32, float alpha, hipStream_t st);

@@ -393,6 +393,21 @@ def test_gemm_mxfp4_eight_stage_ring_with_two_scale_buffers(fp4, oracle, K, vari
         assert np.all(err <= tol), float((err / (1e-3 * S + 1e-300)).max())
 
 
+@pytest.mark.parametrize("variant", [1, 4, 9, 12])
+@pytest.mark.parametrize("K", [128, 256, 896, 1024, 1152, 2176])
+def test_gemm_mxfp4_tiles_of_64_and_96_rows(fp4, oracle, K, variant, knobs):
+    """The eight-stage ring under 64 x 64, 64 x 128, 96 x 128 and 96 x 64 tiles, one barrier per two K-steps: K / 128 = 1, 2, 7, 8, 9,
+    17; six copies of a stage or five dealt to four waves; ragged last tile row and column (272 and 400)."""
+    test_gemm_mxfp4_eight_stage_ring_with_two_scale_buffers(fp4, oracle, K, variant, knobs)
+
+
+@pytest.mark.parametrize("variant", [1, 4, 9, 12])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (65, 72, 384), (97, 136, 640), (128, 130, 1152)])
+def test_gemm_mxfp4_tiles_of_64_and_96_rows_at_their_edges(fp4, oracle, variant, M, N, K, knobs):
+    knobs(variant=variant)
+    _gemm_case(fp4, oracle, MX, M, N, K, seed=190 + variant + M, out_f32=False, layout_gemm=True)
+
+
 @pytest.mark.parametrize("grid", [1, 2, 4])
 @pytest.mark.parametrize("out_f32", [False, True])
 def test_gemm_mxfp4_persistent_workgroups_walk_several_tiles(fp4, oracle, grid, out_f32, knobs):
@@ -574,6 +589,30 @@ def test_gemm_mxfp4_split_k(fp4, oracle, M, N, K, out_f32):
         torch.cuda.synchronize()
         err = np.abs(np_(out.float()).astype(np.float64) - Y)
         assert np.all(err <= tol), (name, float((err / (1e-3 * S + 1e-300)).max()))
+
+
+@pytest.mark.parametrize("M,N,K", [(65, 264, 8320), (80, 130, 16512), (97, 1032, 8320), (201, 2056, 10240)])
+def test_gemm_mxfp4_split_room_that_does_not_fit_the_best_plan(fp4, oracle, M, N, K):
+    """The parts of a split-K run follow the room for their sums: all of it, two parts of it, a byte less (130 columns: sums that are added
+    one by one)."""
+    import torch
+    rng = np.random.default_rng(M + N + K)
+    ya, yw = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    ac, asc, _ = oracle.quantize(ya, MX)
+    wc, wsc, _ = oracle.quantize(yw, MX)
+    Y, S = oracle.matmul(oracle.dequantize(ac, asc, MX), oracle.dequantize(wc, wsc, MX))
+    qa = fp4.fp4_rotate_quantize(to_dev(ya), 1, MX, flags=fp4.LAYOUT_GEMM | fp4.INPUT_F32)
+    qw = fp4.fp4_quantize_weights(to_dev(yw), 1, MX, flags=fp4.LAYOUT_GEMM | fp4.INPUT_F32)
+    gfl = fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM
+    full = fp4.workspace_bytes(fp4.OP_GEMM_SPLIT_K, M, N, K, MX, gfl)
+    say(f"gemm split-K room M={M} N={N} K={K}: {full // (M * N * 4)} splits")
+    assert full >= 2 * M * N * 4
+    for room in (full, 2 * M * N * 4, 2 * M * N * 4 - 1):
+        ws = torch.empty(room, dtype=torch.uint8, device="cuda")
+        out = fp4.fp4_gemm(qa[0], qa[1], None, qw[0], qw[1], None, M, N, K, MX, flags=gfl | fp4.OUT_F32, workspace=ws)
+        torch.cuda.synchronize()
+        err = np.abs(np_(out).astype(np.float64) - Y)
+        assert np.all(err <= 1e-3 * S), (room, float((err / (1e-3 * S + 1e-300)).max()))
 
 
 @pytest.mark.parametrize("M,N,K,out_f32", [(65, 400, 8320, True), (128, 1024, 14336, False), (200, 1000, 10368, False), (300, 528, 16512, True),
