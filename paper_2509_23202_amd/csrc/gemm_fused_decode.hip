@@ -283,12 +283,18 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_w4a16_decode_kernel(Fus
 // grid.  The kernel above rotates the activations again in every workgroup (M = 4, N = 28672, K = 4096: 1792 times, 18.5 us),
 // and its W loads wait for that; here they are rotated once per workgroup into LDS (M K bf16, in the order in which a
 // fragment's MFMAs read them: [fragment][MFMA j][K-block][token], neighbouring lanes 16 bytes apart), under the first W
-// loads, and from then on two batches of four W fragments per wave are in flight while a third is multiplied.  A batch that
+// loads, and from then on NBUF - 1 batches of four W fragments per wave are in flight while one is multiplied.  A batch that
 // does not exist is requested with zero size, so that every request is unconditional (the compiler's waits count on it).
+// Bound: start-up, then HBM.  A request of eight waves costs the compute unit's address path some 0.2 us, also one of zero size, and every copy of a
+// step is code to fetch, cold in each launch: so a batch asks for its scales twice instead of four times, and NBUF is as small as the
+// loads allow: 1 where a workgroup has a single batch (nothing else is requested), 2 else (3 where it says so below).  Against three buffers
+// everywhere, us, M = 4, weight-only: N = K = 1024 3.7 -> 3.1, 4096 5.1 -> 4.2, N = 6144, K = 4096 6.6 -> 5.6, N = 28672 13.4 -> 12.7, N = 4096,
+// K = 14336 11.9 -> 10.7.  (Four or five buffers: 6 and 10 % slower than three.  A last step without a request: a third copy of the
+// step, N = 6144 5.7 -> 6.0.)
 // Same K split, same order of additions: bit-identical.
 // QUANT: the quantizing product; a fragment in LDS is then 4 M entries [K-block][token] of sixteen code bytes and behind them
 // 4 M dwords with the scale byte.
-template <bool QUANT, bool OUT_F32>
+template <bool QUANT, bool OUT_F32, int NBUF>
 __global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(FusedArgs a)
 {
     using GQ = GroupQuant<32, 8, 16, true>;
@@ -312,7 +318,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(Fused
     };
     struct Batch {
         v4i wf[U];
-        uint32_t sw[U];
+        uint32_t sw[2];   // a dword holds the scale bytes of four fragments: of those up to a multiple of four, of those behind it
     };
     int rb_ahead = (int)blockIdx.x, batch_ahead = 0;   // the next batch to be requested
     auto request = [&](Batch& b) {
@@ -325,8 +331,10 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(Fused
         for (int u = 0; u < U; ++u) {
             const int kc = max(min(kc0 + u, k_end - 1), 0);   // (the tail repeats the last fragment; its products are skipped)
             b.wf[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs_w, lane * 16, kc * 1024, 2));   // streamed once
-            b.sw[u] = __builtin_amdgcn_raw_buffer_load_b32(rs_s, lane * 4, (kc >> 2) * 256, 0);
         }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            b.sw[h] = __builtin_amdgcn_raw_buffer_load_b32(rs_s, lane * 4, (max(min(kc0 + h * (U - 1), k_end - 1), 0) >> 2) * 256, 0);
         if (++batch_ahead == nb) {
             batch_ahead = 0;
             rb_ahead += G;
@@ -386,9 +394,9 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(Fused
     v4i x0[TOK], x1[TOK];
     load_x(x0, 0);
     if (items > 1) load_x(x1, 1);
-    Batch buf[3];
+    Batch buf[NBUF];
     request(buf[0]);
-    request(buf[1]);
+    if constexpr (NBUF == 3) request(buf[1]);
     if (items > 0) rotate(x0, 0);
     for (int item = 1; item < items; item += 2) {
         if (item + 1 < items) load_x(x0, item + 1);
@@ -403,24 +411,26 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(Fused
     const int x_pos = q * a.M + min(g, a.M - 1);
     v4f acc = {0.f, 0.f, 0.f, 0.f};
     int rb = (int)blockIdx.x, batch = 0, it = 0;
-    // one batch: request the batch two ahead, multiply the current one, and behind a row-block's last batch add the eight
-    // waves' partial sums in wave order and store; true = that was the last row-block
+    // one batch: request the one NBUF - 1 behind it, multiply this one, and behind a row-block's last batch add the eight waves' partial sums in
+    // wave order and store; true = that was the last row-block
     auto step = [&](const Batch& cur, Batch& nxt) -> bool {
-        request(nxt);
+        if constexpr (NBUF > 1) request(nxt);
+        const int kc0 = k_begin + batch * U;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int kc = k_begin + batch * U + u;
+            const int kc = kc0 + u;
             if (kc < k_end) {
                 const char* const xf = xs + (kc - k_begin) * frag_bytes;
+                const uint32_t sw = ((kc0 & 3) + u < 4 ? cur.sw[0] : cur.sw[1]) >> (8 * (kc & 3));
                 if constexpr (QUANT) {
                     const v4i x = *reinterpret_cast<const v4i*>(xf + x_pos * 16);
                     const uint32_t sx = *reinterpret_cast<const uint32_t*>(xf + a.M * 64 + x_pos * 4);
                     const v8i a8 = {cur.wf[u][0], cur.wf[u][1], cur.wf[u][2], cur.wf[u][3], 0, 0, 0, 0};
                     const v8i b8 = {x[0], x[1], x[2], x[3], 0, 0, 0, 0};
-                    acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, b8, acc, 4, 4, 0, (int)(cur.sw[u] >> (8 * (kc & 3))), 0, (int)sx);
+                    acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, b8, acc, 4, 4, 0, (int)sw, 0, (int)sx);
                     continue;
                 }
-                const float wscale = __uint_as_float(((cur.sw[u] >> (8 * (kc & 3))) & 0xffu) << 23);   // E8M0 byte as a binary32's exponent
+                const float wscale = __uint_as_float((sw & 0xffu) << 23);   // E8M0 byte as a binary32's exponent
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const v8bf w8 = decode8_bf16((uint32_t)cur.wf[u][j], wscale);
@@ -429,7 +439,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(Fused
                 }
             }
         }
-        if (++batch < nb) return false;
+        if (NBUF > 1 && ++batch < nb) return false;
         batch = 0;
         *reinterpret_cast<v4f*>(&partial[it][wave][lane * 4]) = acc;
         acc = v4f{0.f, 0.f, 0.f, 0.f};
@@ -449,12 +459,12 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_few_stream_kernel(Fused
         }
         it ^= 1;
         rb += G;
-        return rb >= n_rb;
+        return NBUF == 1 || rb >= n_rb;
     };
     for (;;) {
-        if (step(buf[0], buf[2])) break;
-        if (step(buf[1], buf[0])) break;
-        if (step(buf[2], buf[1])) break;
+        if (step(buf[0], buf[NBUF - 1])) break;
+        if constexpr (NBUF > 1) { if (step(buf[1], buf[0])) break; }
+        if constexpr (NBUF > 2) { if (step(buf[2], buf[1])) break; }
     }
 }
 
@@ -465,15 +475,30 @@ size_t few_stream_lds(int64_t M, int64_t K, bool quant)
     return 2 * kFusedWaves * 256 * sizeof(float) + (size_t)(kFusedWaves * per * M * (quant ? 80 : 256));
 }
 
+template <bool QUANT, bool OUT_F32, int NBUF>
+hipError_t launch_few_stream_as(const FusedArgs& a, int grid, hipStream_t st)
+{
+    const size_t lds = few_stream_lds(a.M, a.K, QUANT);
+    if (lds > 48 * 1024) {   // (what every kernel may have; asking for the device costs the smallest calls 0.1 us of their 4.5)
+        static LdsAttrOnce raised;
+        const hipError_t e = raised.ensure(reinterpret_cast<const void*>(gemm_few_stream_kernel<QUANT, OUT_F32, NBUF>), kLdsBytes);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((gemm_few_stream_kernel<QUANT, OUT_F32, NBUF>), dim3((unsigned)grid), dim3(kFusedWaves * 64), lds, st, a);
+    return hipGetLastError();
+}
+
 template <bool QUANT, bool OUT_F32>
 hipError_t launch_few_stream(const FusedArgs& a, hipStream_t st)
 {
-    static LdsAttrOnce raised;
-    const hipError_t e = raised.ensure(reinterpret_cast<const void*>(gemm_few_stream_kernel<QUANT, OUT_F32>), kLdsBytes);
-    if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)std::min((a.N + 15) / 16, compute_units());
-    hipLaunchKernelGGL((gemm_few_stream_kernel<QUANT, OUT_F32>), dim3(grid), dim3(kFusedWaves * 64), few_stream_lds(a.M, a.K, QUANT), st, a);
-    return hipGetLastError();
+    const int n_rb = (a.N + 15) / 16;
+    if (n_rb <= 256 && a.K <= 4096) return launch_few_stream_as<QUANT, OUT_F32, 1>(a, n_rb, st);   // (a compute unit each)
+    const int grid = std::min(n_rb, compute_units());
+    if constexpr (QUANT) {
+        // (two batches per row-block: the first row-block whole on its way under the rotation, N = K = 8192, M = 4 9.5 -> 8.9 us)
+        if (a.K > 4096 && a.K <= 8192) return launch_few_stream_as<QUANT, OUT_F32, 3>(a, grid, st);
+    }
+    return launch_few_stream_as<QUANT, OUT_F32, 2>(a, grid, st);
 }
 
 }  // namespace
@@ -496,15 +521,13 @@ hipError_t launch_fused_decode(const void* x, int64_t M, int64_t K, int b, const
     a.alpha = alpha;
     const dim3 grid((unsigned)((N + 15) / 16)), block(kFusedWaves * 64);
     // Persistent workgroups wherever their LDS holds the activations (weight-only: M K <= 73728).  Cold weights, one-shot ->
-    // persistent, us, M = 1 / 4 / 16: N = 6144, K = 4096 6.3 / 6.3 / 18.0 -> 6.1 / 6.4 / 9.6; N = 28672 16.2 / 18.2 / 60.5 ->
-    // 13.2 / 13.1 / 16.7; N = 4096, K = 14336 10.9 / 13.9 -> 9.4 / 11.3; N = K = 1024 level, 8.0 -> 6.7.
-    // The quantizing product, M = 1 / 4: N = 28672, K = 4096 13.0 / 16.2 -> 12.0 / 12.1; N = K = 8192 8.7 / 9.6 -> 8.4 / 9.1;
-    // N = 4096, K = 14336 9.3 / 12.2 -> 9.0 / 11.8; with less than two row-blocks per workgroup and a short K there is nothing
-    // to stream ahead and the one-shot kernel starts faster (N = 6144, K = 4096 5.3 / 5.7 against 5.5 / 6.2; N = K = 1024 2.7 / 3.5
-    // against 3.2 / 4.1).
+    // persistent, us, M = 1 / 4 / 16: N = 6144, K = 4096 6.3 / 6.3 / 18.0 -> 5.7 / 5.7 / 9.0; N = 28672 16.2 / 18.2 / 60.5 ->
+    // 13.2 / 12.7 / 16.0; N = 4096, K = 14336 10.9 / 13.9 -> 9.4 / 10.7.
+    // The quantizing product, M = 1 / 4: N = K = 1024 3.1 / 3.9 -> 2.6 / 3.5, 4096 4.2 / 5.0 -> 3.8 / 3.9, N = 6144, K = 4096 5.4 / 5.9 -> 4.8 / 5.0,
+    // N = 28672 13.0 / 16.2 -> 11.4 / 11.7, N = K = 8192 8.7 / 9.6 -> 8.1 / 8.9, N = 4096, K = 14336 9.3 / 12.2 -> 8.9 / 11.2.
     const bool fits = few_stream_lds(M, K, !weight_only) <= (size_t)kLdsBytes;
     if (weight_only && fits) return out_f32 ? launch_few_stream<false, true>(a, st) : launch_few_stream<false, false>(a, st);
-    if (!weight_only && fits && ((N + 15) / 16 >= 2 * (int64_t)compute_units() || K > 8192))
+    if (!weight_only && fits)
         return out_f32 ? launch_few_stream<true, true>(a, st) : launch_few_stream<true, false>(a, st);
     if (weight_only) {
         if (M <= 4) {

@@ -185,3 +185,11 @@ def test_w4a16_persistent_against_oracle(fp4, oracle, M, N, K, b):
     """Several row-blocks per workgroup; M K = 73728, which fills the LDS of a compute unit, and one token more, which takes the
     one-shot kernel."""
     _w4a16_case(fp4, oracle, M, N, K, b, False, salt=M + N + b + 1)
+
+
+@pytest.mark.parametrize("M,N,K,b", [(4, 4096, 4096, 64), (3, 4104, 4096, 32), (2, 4104, 4224, 16), (4, 72, 8192, 128), (1, 4200, 8320, 32)])
+def test_few_tokens_either_side_of_a_buffer_less(fp4, oracle, M, N, K, b):
+    """256 row-blocks and one more, K = 4096 and 8192 and one fragment more: one batch of fragments in a workgroup, two buffers, three."""
+    if b <= 32:
+        test_fused_equals_two_launch_path(fp4, M, N, K, b, False)
+    _w4a16_case(fp4, oracle, M, N, K, b, False, salt=M + N + b + 2)
