@@ -321,7 +321,8 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_skinny_nt_kernel(Skinn
 // its X fragments -- of MT 16-token blocks -- are loaded once and stay in registers: a batch is W only, a W fragment meets
 // all MT blocks, and nothing of X is read again for the rest of the launch (the one-shot kernels fetch MT X fragments from
 // L2 per W fragment).  !XRES (MT = 1, any K): the X fragments travel with W in the batches, two buffers.
-template <int FMT, bool OUT_F32, int U, bool XRES, int MT = 1, int NB = 1>
+// ONE: the workgroup has a single batch, nothing is requested behind it.
+template <int FMT, bool OUT_F32, int U, bool XRES, int MT = 1, int NB = 1, bool ONE = false>
 __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyArgs g)
 {
     static_assert(MT == 1 || XRES, "several token blocks only with the X fragments resident");
@@ -365,9 +366,12 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
         else return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, lane_sc, rb_off + kc * 128, 0);
     };
 
+    // (MXFP4: a dword holds the scale bytes of four fragments; of a batch, those up to a multiple of four and those behind it)
+    constexpr int SW = FMT == 0 ? 2 : U;
+    static_assert(FMT == 1 || U == 4, "two scale dwords per batch");
     struct Batch {
         v4i wf[U], xf[XRES ? 1 : U];
-        uint32_t sw[U], sx[XRES ? 1 : U];
+        uint32_t sw[SW], sx[XRES ? 1 : U];
     };
     // Every batch is requested UNCONDITIONALLY: a batch that does not exist (past the last row-block, or of a wave without a
     // share of K) is requested through buffer resources of zero size, whose loads return zeros without touching memory.
@@ -383,18 +387,22 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
         for (int u = 0; u < U; ++u) {
             const int kc = max(min(kc0 + u, k_end - 1), 0);  // the tail repeats the last fragment; its product is skipped
             b.wf[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs_w, lane16, kc * 1024, 2));  // streamed once
-            b.sw[u] = load_scale(rs_ws, kc);
+            if constexpr (FMT == 1) b.sw[u] = load_scale(rs_ws, kc);
             if constexpr (!XRES) {
                 b.xf[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(valid ? rs_x : rs_none, lane16, kc * 1024, 0));
                 b.sx[u] = load_scale(valid ? rs_xs : rs_none, kc);
             }
+        }
+        if constexpr (FMT == 0) {
+            b.sw[0] = load_scale(rs_ws, max(min(kc0, k_end - 1), 0));
+            b.sw[1] = load_scale(rs_ws, max(min(kc0 + U - 1, k_end - 1), 0));
         }
     };
     constexpr int XF = XRES ? NB * U : 1;  // resident X fragments per token block: the wave's whole share of K
     // MXFP4: codes and scale dwords as loaded.  NVFP4: DEQUANTIZED once, as fp16 -- the per-fragment dequantization of X,
     // half of the vector arithmetic that bounds the one-shot NVFP4 kernels, is then paid once per workgroup
     v4i xres[FMT == 0 ? MT : 1][FMT == 0 ? XF : 1];
-    uint32_t sxres[FMT == 0 ? MT : 1][FMT == 0 ? XF : 1];
+    uint32_t sxres[FMT == 0 ? MT : 1][FMT == 0 ? NB + 1 : 1];   // of the blocks of four fragments from k_begin on
     NvFrag16 xres16[FMT == 1 ? XF : 1];
     const bool mine = nb > 0;  // this wave has a share of K
     if constexpr (XRES) {
@@ -406,13 +414,13 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
                 const bool has = k_begin + j < k_end;  // (fragments past the wave's share: zero-size loads, never multiplied)
                 const int kc = has ? k_begin + j : 0;
                 const v4i xf = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(has ? rs_x : rs_none, lane16, mrb * KC * 1024 + kc * 1024, 0));
-                const uint32_t sx = load_scale(has ? rs_xs : rs_none, kc, mrb * sc_per_rb * SCB);
-                if constexpr (FMT == 0) {
-                    xres[t][j] = xf;
-                    sxres[t][j] = sx;
-                } else {
-                    xres16[j] = nv_dequant_frag(xf, sx);
-                }
+                if constexpr (FMT == 0) xres[t][j] = xf;
+                else xres16[j] = nv_dequant_frag(xf, load_scale(has ? rs_xs : rs_none, kc, mrb * sc_per_rb * SCB));
+            }
+            if constexpr (FMT == 0) {
+#pragma unroll
+                for (int i = 0; i < NB + 1; ++i)
+                    sxres[t][i] = load_scale(mine ? rs_xs : rs_none, mine ? min((k_begin & ~3) + 4 * i, k_end - 1) : 0, mrb * sc_per_rb * SCB);
             }
         }
     }
@@ -423,15 +431,18 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
         for (int u = 0; u < U; ++u) {
             if (kc0 + u < k_end) {
                 if constexpr (FMT == 0) {
-                    const int kc = kc0 + u;
+                    const int kc = kc0 + u, shift = 8 * (kc & 3);
+                    const bool behind = (kc0 & 3) + u >= 4;
+                    const uint32_t sw = (behind ? b.sw[1] : b.sw[0]) >> shift;
                     const v8i a8 = {b.wf[u][0], b.wf[u][1], b.wf[u][2], b.wf[u][3], 0, 0, 0, 0};
 #pragma unroll
                     for (int t = 0; t < MT; ++t) {
                         const v4i xf = XRES ? xres[t][XRES && FMT == 0 ? X0 + u : 0] : b.xf[XRES ? 0 : u];
-                        const uint32_t sx = XRES ? sxres[t][XRES && FMT == 0 ? X0 + u : 0] : b.sx[XRES ? 0 : u];
+                        uint32_t sx;
+                        if constexpr (XRES) sx = behind ? sxres[t][X0 / 4 + 1] : sxres[t][X0 / 4];
+                        else sx = b.sx[u];
                         const v8i b8 = {xf[0], xf[1], xf[2], xf[3], 0, 0, 0, 0};
-                        acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, b8, acc[t], 4, 4, 0, (int)(b.sw[u] >> (8 * (kc & 3))), 0,
-                                                                                (int)(sx >> (8 * (kc & 3))));
+                        acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, b8, acc[t], 4, 4, 0, (int)sw, 0, (int)(sx >> shift));
                     }
                 } else {
                     const NvFrag16 w16 = nv_dequant_frag(b.wf[u], b.sw[u]);
@@ -488,8 +499,13 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
         // wave whose share of K is shorter requests its missing batches with zero size).  The batches of all the walker's
         // row-blocks form one sequence, NBUF - 1 of them in flight ahead of the one being multiplied, through NBUF
         // buffers in rotation; the loop body is NB * NBUF steps with every index a constant, left by `break` so that no
-        // control flow merges back into it.
-        constexpr int NBUF = MT * NB >= 7 ? 2 : 3;
+        // control flow merges back into it.  A request costs the compute unit's address path 0.2 us, also one of zero size, and every
+        // step is code that a launch fetches cold: MXFP4 has the fewest buffers that the loads allow (against three where the registers
+        // had room, and four scale dwords a batch, us, M = 16 / 32: N = 6144, K = 4096 5.5 / 6.3 -> 5.0 / 5.6, N = 8192, K = 2048 4.9 / 5.5
+        // -> 4.3 / 4.9, N = 28672, K = 4096 12.5 / 14.0 -> 12.1 / 14.0; N = K = 2048, one batch, 3.4 / 4.1 -> 3.1 / 3.6).  Two batches per
+        // row-block keep three (N = 10240, K = 5120, M = 16: 8.1 us, with two 8.7), and so does NVFP4 (N = 57344, K = 8192: 43.8, 46.5).
+        constexpr int NBUF = ONE ? 1 : FMT == 1 || (NB == 2 && MT <= 2) ? 3 : 2;
+        static_assert(!ONE || NB == 1, "one batch");
         constexpr int P = NB * NBUF;
         static_assert(P <= 12, "the loop body below spells out twelve steps");
         Batch buf[NBUF];
@@ -504,7 +520,7 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
         // current row-block, and behind a row-block's last batch reduce and store; true = that was the last row-block
         auto step = [&](auto qc) -> bool {
             constexpr int q = decltype(qc)::value, batch = q % NB, ahead = batch + NBUF - 1;
-            request(buf[(q + NBUF - 1) % NBUF], rb + (ahead / NB) * G, ahead % NB);
+            if constexpr (!ONE) request(buf[(q + NBUF - 1) % NBUF], rb + (ahead / NB) * G, ahead % NB);
             consume(buf[q % NBUF], k_begin + batch * U, acc, std::integral_constant<int, batch * U>{});
             if constexpr (batch == NB - 1) {
                 reduce_store(acc, rb, it);
@@ -512,7 +528,7 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
                 for (int t = 0; t < MT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
                 ++it;
                 rb += G;
-                return rb >= n_rb;
+                return ONE || rb >= n_rb;
             }
             return false;
         };
@@ -596,6 +612,13 @@ hipError_t launch_stream_resident(SkinnyArgs g, bool out_f32, int parts, hipStre
 {
     g.parts = parts;
     const dim3 grid(stream_grid(g.N, parts)), block(kSkinnyWaves * 64);
+    if constexpr (NB == 1) {
+        if ((int64_t)grid.x * 16 >= (int64_t)std::max(parts, 1) * g.N) {   // one batch per workgroup
+            if (out_f32) hipLaunchKernelGGL((gemm_stream_kernel<0, true, 4, true, MT, 1, true>), grid, block, 0, st, g);
+            else hipLaunchKernelGGL((gemm_stream_kernel<0, false, 4, true, MT, 1, true>), grid, block, 0, st, g);
+            return hipGetLastError();
+        }
+    }
     if (out_f32) hipLaunchKernelGGL((gemm_stream_kernel<0, true, 4, true, MT, NB>), grid, block, 0, st, g);
     else hipLaunchKernelGGL((gemm_stream_kernel<0, false, 4, true, MT, NB>), grid, block, 0, st, g);
     return hipGetLastError();
@@ -754,13 +777,10 @@ hipError_t launch_fmt(const SkinnyArgs& g, bool out_f32, hipStream_t st)
     switch (mt) {
         case 1:
             if constexpr (FMT == 0) {
-                // The persistent kernels win by keeping loads in flight across batches and row-blocks, which needs several
-                // batches per row-block or more row-blocks than workgroups: a layer of at most one row-block per compute unit
-                // and one batch (N <= 4096, K <= 4096) is launch-bound and 0.1-0.4 us faster with the one-shot kernel's
-                // occupancy.  (NVFP4 stays with the one-shot kernels: its in-register dequantization needs the registers of
+                // (K <= 1024, one fragment per wave, is launch-bound: N = 8192, K = 1024, 3.7 us with the one-shot kernel against 4.6.
+                // NVFP4 stays with the one-shot kernels where X does not fit: its in-register dequantization needs the registers of
                 // the second batch buffer -- 68 us against 54 on N = 57344, K = 8192.)
-                // ... and so is any layer with K <= 1024 (one fragment per wave: N = 8192, K = 1024, 3.7 us against 4.6)
-                const bool one_shot = per <= 1 || (per <= 4 && (g.N + 15) / 16 <= stream_walkers());
+                const bool one_shot = per <= 1;
                 hipError_t e = hipSuccess;
                 if (!one_shot) {
                     if (try_stream_resident<1>(g, out_f32, per, 1, st, &e)) return e;
@@ -797,7 +817,7 @@ hipError_t launch_fmt(const SkinnyArgs& g, bool out_f32, hipStream_t st)
 // What the MXFP4 streaming kernels take with more than 16 tokens, in microseconds: the activations' way into registers, then row-blocks
 // per workgroup times (a fixed part, the products, the loads in batches of four fragments).  Up to 64 tokens in one set of workgroups
 // where they fit, else, up to 512 tokens, in several sets (K <= 16384, with more than 64 tokens 8192; they pay on layers narrow enough that
-// each set has few row-blocks).  Fitted to 6751 and 4552 products with cold weights (N = 512 ... 57344, K = 1024 ... 14336), median error 2.5 %.
+// each set has few row-blocks).  Fitted to 6751 and 4552 products with cold weights (N = 512 ... 57344, K = 1024 ... 14336), median error 2.5 %, on the tile table's scale.
 // 0: not priced, up to 64 tokens they take it; infinity: they do not take it.
 double gemm_stream_us(int64_t M, int64_t N, int64_t K)
 {
@@ -806,10 +826,10 @@ double gemm_stream_us(int64_t M, int64_t N, int64_t K)
     const int per = (int)(((K >> 7) + kSkinnyWaves - 1) / kSkinnyWaves), nbk = (per + 3) / 4, mt = (int)((M + 15) / 16);  // fragments of K per wave
     const int64_t n_rb = (N + 15) / 16;
     const int cus = compute_units();
-    if (per == 1) return mt > 4 ? none : 2.90 + 0.256 * mt + (double)n_rb / cus * (0.611 + 0.106 * mt);   // (one-shot)
+    if (per == 1) return mt > 4 ? none : 2.90 + 0.256 * mt + (double)n_rb / cus * (0.611 + 0.106 * mt);
     if (mt <= 4 && nbk <= stream_max_batches(mt)) {
         const double rounds = (double)((n_rb + cus - 1) / cus);
-        return 2.34 + (0.0219 * per + 0.277 * nbk) * mt + rounds * (0.0381 + 0.0544 * per + 0.0789 * mt + 0.308 * nbk) + 0.146 * per * (double)n_rb / cus;
+        return 2.25 + (0.0210 * per + 0.266 * nbk) * mt + rounds * (0.0366 + 0.0522 * per + 0.0757 * mt + 0.296 * nbk) + 0.140 * per * (double)n_rb / cus;
     }
     const int most = nbk <= stream_max_batches(4) ? 4 : nbk <= stream_max_batches(2) ? 2 : 0;
     if (most == 0 || (mt > 4 && most < 4)) return mt <= 4 ? 0.0 : none;   // (more than 64 tokens with K > 8192: not timed)

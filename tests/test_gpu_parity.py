@@ -408,6 +408,33 @@ def test_gemm_mxfp4_tiles_of_64_and_96_rows_at_their_edges(fp4, oracle, variant,
     _gemm_case(fp4, oracle, MX, M, N, K, seed=190 + variant + M, out_f32=False, layout_gemm=True)
 
 
+@pytest.mark.parametrize("M", [5, 40, 70])
+@pytest.mark.parametrize("N,K", [(40, 384), (4096, 512), (4104, 512), (72, 1408), (40, 5120), (4104, 5248), (40, 7296), (24, 12416)])
+def test_gemm_mxfp4_streamed_shares_that_begin_inside_a_scale_block(fp4, oracle, M, N, K):
+    """A wave's share of K begins at any fragment of the four that a scale dword serves; scales that differ per row-block and
+    fragment; 256 row-blocks and one more (a single batch per workgroup, or two)."""
+    import torch
+    rng = np.random.default_rng(M + N + K)
+
+    def operand(rows):
+        v = rng.standard_normal((rows, K))
+        v *= 2.0 ** ((np.arange(rows)[:, None] // 16 * 5) % 11 - 5)
+        v *= 2.0 ** ((np.arange(K)[None, :] // 128 * 3) % 7 - 3)
+        return v.astype(np.float32)
+
+    ya, yw = operand(M), operand(N)
+    ac, asc, _ = oracle.quantize(ya, MX)
+    wc, wsc, _ = oracle.quantize(yw, MX)
+    Y, S = oracle.matmul(oracle.dequantize(ac, asc, MX), oracle.dequantize(wc, wsc, MX))
+    say(f"gemm streamed M={M} N={N} K={K}")
+    qa = fp4.fp4_rotate_quantize(to_dev(ya), 1, MX, flags=fp4.LAYOUT_GEMM | fp4.INPUT_F32)
+    qw = fp4.fp4_quantize_weights(to_dev(yw), 1, MX, flags=fp4.LAYOUT_GEMM | fp4.INPUT_F32)
+    out = fp4.fp4_gemm(qa[0], qa[1], None, qw[0], qw[1], None, M, N, K, MX, flags=fp4.OUT_F32 | fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM)
+    torch.cuda.synchronize()
+    err = np.abs(np_(out).astype(np.float64) - Y)
+    assert np.all(err <= 1e-3 * S), float((err / (1e-3 * S + 1e-300)).max())
+
+
 @pytest.mark.parametrize("grid", [1, 2, 4])
 @pytest.mark.parametrize("out_f32", [False, True])
 def test_gemm_mxfp4_persistent_workgroups_walk_several_tiles(fp4, oracle, grid, out_f32, knobs):
