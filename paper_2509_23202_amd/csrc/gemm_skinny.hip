@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_skinny_kernel(SkinnyAr
 template <int FMT, int NT, int MT, bool OUT_F32, bool PF = false>
 __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_skinny_nt_kernel(SkinnyArgs g)
 {
-    constexpr int U = MT == 1 ? 4 : 2;  // K positions in flight per wave (NT W fragments and MT X fragments each)
+    constexpr int U = MT == 1 ? 4 : NT == 4 ? 1 : 2;  // K positions in flight per wave (NT W fragments and MT X fragments each)
     __shared__ float partial[kSkinnyWaves][NT * MT][256];
 
     const int lane = threadIdx.x & 63;
@@ -711,6 +711,21 @@ template <int FMT, int MT>
 bool try_two_row_blocks(const SkinnyArgs& g, bool out_f32, hipStream_t st, hipError_t* err)
 {
     const int n_rb = (g.N + 15) / 16, wgs = (n_rb + 1) / 2;
+    // NVFP4 with three or four token blocks: four row-blocks, half the X share again, where their workgroups, one to a compute unit, are
+    // nearly whole rounds of the chip.  Two -> four, us, M = 40 / 64: N = 16384, K = 8192 (a round) 24.2 / 29.3 -> 20.4 / 23.7; 0.875 of
+    // two, four and one: N = 28672, K = 4096 25.3 / 31.1 -> 23.3 / 26.6, N = 57344, K = 8192 76.4 / 95.8 -> 73.4 / 82.2, N = 14336, K = 4096 14.7 / 17.5 ->
+    // 12.8 / 14.8; 0.83 of three, N = 40960, K = 5120 37.8 / 48.7 -> 38.2 / 43.4; 0.75 of two, N = 24576, K = 4096 21.3 / 25.8 -> 22.2 / 25.9.
+    // (Two token blocks: 0.9 - 1.25 of the time.  With the loads of the next position ahead the registers of the second set cost more.)
+    if constexpr (FMT == 1 && MT >= 3) {
+        const int wgs4 = (n_rb + 3) / 4, rounds = (wgs4 + stream_cus() - 1) / stream_cus();
+        if (20 * wgs4 >= (MT == 3 ? 17 : 16) * rounds * stream_cus()) {
+            const dim3 grid4((unsigned)wgs4), block4(kSkinnyWaves * 64);
+            if (out_f32) hipLaunchKernelGGL((gemm_skinny_nt_kernel<FMT, 4, MT, true>), grid4, block4, 0, st, g);
+            else hipLaunchKernelGGL((gemm_skinny_nt_kernel<FMT, 4, MT, false>), grid4, block4, 0, st, g);
+            *err = hipGetLastError();
+            return true;
+        }
+    }
     if (5 * wgs < 3 * stream_cus()) return false;
     const dim3 grid((unsigned)wgs), block(kSkinnyWaves * 64);
     // at most one workgroup per compute unit and several batches of K per wave: the instantiation that prefetches
