@@ -614,6 +614,11 @@ double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int 
     return t;
 }
 
+// (the least of K: two parts of sixteen K-steps)
+bool may_split(int64_t M, int64_t K) { return M > 64 && K >= 32 * 128; }
+
+}  // namespace
+
 // The cheapest way of a product: the tiles of the table above (variant: a number of launch_gemm_mxfp4's switch), with more than 64 tokens and
 // room for partials also as a split-K run, or the streaming kernels (variant 0), which have a price of their own (gemm_stream_us).
 // With few tiles and a long K -- batched decoding against a narrow layer -- a handful of compute units each stream a long K range alone.
@@ -621,7 +626,7 @@ double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int 
 // workgroup of as many tiles.  Priced as as many tiles of as many steps, which share their start, and 3.9 us + bytes at 4 TB/s for the
 // partials and their sum's launch; a split has to win 4 %.  Of 2208 products with K from 4096 to 28672, parts of up to 96 rows
 // were the best way in 749, 1.26 times as fast as the best unsplit one on average; parts of 128 and more rows in nine.
-MxPlan find_plan(int64_t M, int64_t N, int64_t K, size_t room)
+MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room)
 {
     MxPlan p{0, 1, 0};
     if (M <= 16) return p;
@@ -651,7 +656,7 @@ MxPlan find_plan(int64_t M, int64_t N, int64_t K, size_t room)
             p.variant = c.variant;
         }
     }
-    if (M <= 64 || kt < 32) return p;
+    if (!may_split(M, K)) return p;
     best *= 0.96;
     for (const TileCost& c : kTileCosts) {
         if (!tile_splits(c.bm, c.bn)) continue;
@@ -671,27 +676,10 @@ MxPlan find_plan(int64_t M, int64_t N, int64_t K, size_t room)
     return p;
 }
 
-}  // namespace
-
-// A call asks twice, for the room and with it, and a program for the same few products over and over: each thread keeps the last plans
-// (0.4 us to find one, where the smallest launches take 4 to 5).
-MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room)
-{
-    struct Known {
-        int64_t M, N, K;
-        size_t room;
-        MxPlan plan;
-    };
-    static thread_local Known known[32] = {};
-    if (M <= 64 || K < 32 * 128) room = 0;   // (never split)
-    Known& e = known[(M * 5 + (N >> 3) * 3 + (K >> 7)) & 31];
-    if (e.M != M || e.N != N || e.K != K || e.room != room) e = Known{M, N, K, room, find_plan(M, N, K, room)};
-    return e.plan;
-}
-
 // bytes of fp32 partials a split-K run of this product needs (0: the product is not split)
 size_t gemm_mx_split_k_bytes(int64_t M, int64_t N, int64_t K)
 {
+    if (!may_split(M, K)) return 0;
     const MxPlan p = plan_mx(M, N, K, SIZE_MAX);
     return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * 4 : 0;
 }

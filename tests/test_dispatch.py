@@ -1,0 +1,118 @@
+"""Which kernels a call launches, with which grid and into which bytes of its workspace, as the library's host code decides it: no
+GPU runs.  A process of its own loads a stand-in for the few HIP entry points that the library calls, in front of the real ones: it
+reports the compute units that a test gives each device and writes down every launch."""
+import json
+import shutil
+import subprocess
+import sys
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parent.parent
+LIB = ROOT / "paper_2509_23202_amd" / "libfp4mr.so"
+MX, NV = 0, 1
+OP_GEMM, OP_SPLIT = 2, 6
+
+HIP = r"""
+#include <stdio.h>
+#include <string.h>
+typedef struct { unsigned x, y, z; } dim3;
+static const void* fn[8192]; static const char* fn_name[8192]; static int fns;
+static int device, units[64], n; static char text[1 << 22]; static int at;
+static dim3 g, b; static size_t lds; static void* st; static void* module;
+void fake_device(int d, int cus) { device = d; units[d] = cus; }
+const char* fake_launches(void) { text[at] = 0; at = n = 0; return text; }
+void** __hipRegisterFatBinary(const void* d) { (void)d; return &module; }
+void __hipUnregisterFatBinary(void** m) { (void)m; }
+void __hipRegisterVar(void** m, void* v, char* a, char* name, int e, size_t s, int c, int gl) {}
+void __hipRegisterFunction(void** m, const void* f, char* d, const char* name, unsigned t, void* ti, void* bi, void* bd, void* gd, int* ws)
+{ if (fns < 8192) { fn[fns] = f; fn_name[fns++] = name; } }
+int __hipPushCallConfiguration(dim3 gg, dim3 bb, size_t l, void* s) { g = gg; b = bb; lds = l; st = s; return 0; }
+int __hipPopCallConfiguration(dim3* gg, dim3* bb, size_t* l, void** s) { *gg = g; *bb = b; *l = lds; *s = st; return 0; }
+int hipGetDevice(int* d) { *d = device; return 0; }
+int hipDeviceGetAttribute(int* v, int a, int d) { *v = units[d]; return 0; }
+int hipFuncSetAttribute(const void* f, int a, int v) { return 0; }
+int hipGetLastError(void) { return 0; }
+int hipGetSymbolAddress(void** p, const void* s) { *p = (void*)s; return 0; }
+int hipLaunchKernel(const void* f, dim3 gg, dim3 bb, void** args, size_t l, void* s)
+{
+    const char* name = "?";
+    for (int i = 0; i < fns; ++i) if (fn[i] == f) name = fn_name[i];
+    long long v[6] = {0};
+    if (strstr(name, "splitk_reduce_kernel")) {        /* partial, parts, elements */
+        v[0] = *(long long*)args[0]; v[1] = *(int*)args[1]; v[2] = *(long long*)args[2];
+    } else if (strstr(name, "nv16_reduce_kernel")) {   /* Nv16Sums: partial[2], parts[2], count[2] */
+        const char* a = args[0]; int parts[2];
+        memcpy(v, a, 8); memcpy(v + 3, a + 8, 8); memcpy(parts, a + 16, 8); memcpy(v + 2, a + 24, 8); memcpy(v + 5, a + 32, 8);
+        v[1] = parts[0]; v[4] = parts[1];
+    }
+    at += snprintf(text + at, sizeof text - at - 1, "%s %u %u %zu %lld %lld %lld %lld %lld %lld\n", name, gg.x, gg.y, l, v[0], v[1], v[2], v[3], v[4], v[5]);
+    return 0;
+}
+"""
+
+HOST = r"""
+import ctypes, json, sys
+hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+hip.fake_launches.restype = ctypes.c_char_p
+lib.fp4_workspace_bytes.restype = ctypes.c_size_t
+P, I, Z = ctypes.c_void_p, ctypes.c_int64, ctypes.c_size_t
+lib.fp4_workspace_bytes.argtypes = [ctypes.c_int, I, I, I, ctypes.c_int, ctypes.c_uint32]
+lib.fp4_gemm.argtypes = [P] * 6 + [I] * 3 + [ctypes.c_int, P, P, Z, ctypes.c_uint32, P]
+lib.fp4_fused_linear.argtypes = lib.fp4_w4a16_linear.argtypes = [P, I, I, ctypes.c_int, P, P, I, ctypes.c_int, P, ctypes.c_uint32, P]
+BUF, WS, LAYOUTS = 1 << 40, 1 << 41, 24    # addresses that nothing reads; A_LAYOUT_GEMM | W_LAYOUT_GEMM
+def launches():
+    out = []
+    for l in hip.fake_launches().decode().split("\n")[:-1]:
+        f = l.split(" ")
+        out.append({"kernel": f[0], "grid": [int(f[1]), int(f[2])], "sums": [[int(v) for v in f[4:7]], [int(v) for v in f[7:10]]]})
+    return out
+for req in json.load(sys.stdin):
+    what, a = req[0], req[1:]
+    if what == "device": hip.fake_device(*a); r = None
+    elif what == "bytes": r = lib.fp4_workspace_bytes(a[0], a[1], a[2], a[3], a[4], LAYOUTS)
+    elif what == "gemm":
+        M, N, K, fmt, room = a
+        s = lib.fp4_gemm(BUF, BUF, BUF, BUF, BUF, BUF, M, N, K, fmt, BUF, WS, room, LAYOUTS, None)
+        r = launches()
+        assert s == 0, s
+        for l in r: l["ends"] = max(p + n * c * 4 for p, n, c in l.pop("sums")) - WS
+    else:
+        M, N, K = a
+        s = getattr(lib, what)(BUF, M, K, 32, BUF, BUF, N, 0, BUF, 16, None)
+        r = launches()
+        assert s == 0, s
+    print(json.dumps(r))
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler")
+    if not LIB.exists():
+        from paper_2509_23202_amd import build
+        build.build(verbose=False)
+    d = tmp_path_factory.mktemp("dispatch")
+    (d / "hip.c").write_text(HIP)
+    subprocess.run([cc, "-shared", "-fPIC", "-w", "-o", str(d / "hip.so"), str(d / "hip.c")], check=True)
+
+    def ask(*requests):
+        r = subprocess.run([sys.executable, "-c", HOST, str(d / "hip.so"), str(LIB)], input=json.dumps(requests), capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return [json.loads(l) for l in r.stdout.splitlines()]
+
+    return ask
+
+
+@pytest.mark.parametrize("fmt", [MX, NV])
+def test_a_plan_is_made_for_the_device_that_is_current(host, fmt):
+    """A thread that goes on to a device with fewer compute units plans for that one, as a thread that starts there."""
+    big, small = ["device", 0, 256], ["device", 1, 64]
+    for ask in (["bytes", OP_SPLIT, 201, 4096, 14336, fmt], ["gemm", 201, 4096, 14336, fmt, 1 << 30], ["gemm", 48, 4096, 8192, fmt, 1 << 30]):
+        alone = host(small, ask)[-1]
+        assert host(big, ask, small, ask)[-1] == alone
+        assert host(big, ask)[-1] != alone
