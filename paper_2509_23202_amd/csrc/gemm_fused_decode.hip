@@ -491,9 +491,8 @@ hipError_t launch_few_stream_as(const FusedArgs& a, int grid, hipStream_t st)
 template <bool QUANT, bool OUT_F32>
 hipError_t launch_few_stream(const FusedArgs& a, hipStream_t st)
 {
-    const int n_rb = (a.N + 15) / 16;
-    if (n_rb <= 256 && a.K <= 4096) return launch_few_stream_as<QUANT, OUT_F32, 1>(a, n_rb, st);   // (a compute unit each)
-    const int grid = std::min(n_rb, compute_units());
+    const int n_rb = (a.N + 15) / 16, grid = std::min(n_rb, compute_units());
+    if (n_rb == grid && a.K <= 4096) return launch_few_stream_as<QUANT, OUT_F32, 1>(a, grid, st);   // (a compute unit each, with one batch)
     if constexpr (QUANT) {
         // (two batches per row-block: the first row-block whole on its way under the rotation, N = K = 8192, M = 4 9.5 -> 8.9 us)
         if (a.K > 4096 && a.K <= 8192) return launch_few_stream_as<QUANT, OUT_F32, 3>(a, grid, st);

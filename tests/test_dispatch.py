@@ -116,3 +116,13 @@ def test_a_plan_is_made_for_the_device_that_is_current(host, fmt):
         alone = host(small, ask)[-1]
         assert host(big, ask, small, ask)[-1] == alone
         assert host(big, ask)[-1] != alone
+
+
+@pytest.mark.parametrize("call", ["fp4_fused_linear", "fp4_w4a16_linear"])
+@pytest.mark.parametrize("cus", [32, 255, 256, 304])
+def test_few_token_linears_start_one_workgroup_per_compute_unit(host, call, cus):
+    """Row-blocks of one more and of as many as there are compute units, K of one batch of fragments and of two."""
+    for N in (16 * cus, 16 * cus + 8, 4096, 4104):
+        for K in (4096, 4224):
+            (launch,) = host(["device", 0, cus], [call, 4, N, K])[1]
+            assert launch["grid"][0] == min((N + 15) // 16, cus), (N, K)
