@@ -201,7 +201,7 @@ fp4mr_status_t fp4_quantize_weights(const void* w, int64_t N, int64_t K, int had
  *                Optional: with at least fp4_workspace_bytes(FP4MR_OP_GEMM_SPLIT_K, ...) bytes (the same plus room for
  *                fp32 partial results; equal to the former where the shape has nothing to gain) a product with few
  *                output tiles and a long K -- 65 to a few hundred tokens against a narrow layer -- is split along K
- *                over otherwise idle compute units (with less room, in fewer parts) and the partial results are added in a fixed order (deterministic;
+ *                over otherwise idle compute units (with less room, in fewer parts where those still gain) and the partial results are added in a fixed order (deterministic;
  *                the fp32 sums are grouped per split, so the result can differ from the unsplit one in its last bits).
  */
 fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* a_tensor_scale,

@@ -228,7 +228,7 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
     }
     const bool out_f32 = (flags & FP4MR_OUT_F32) != 0;
     const float alpha = scale43_factor(flags);
-    // Optional split-K room behind what the call needs (FP4MR_OP_GEMM_SPLIT_K): used when the caller passed that much
+    // Optional split-K room behind what the call needs (FP4MR_OP_GEMM_SPLIT_K asks for that of the best plan; with less, the best one that fits)
     void* partial = nullptr;
     size_t partial_room = 0;
     if (M > 64 && variant == 0 && workspace && aligned16(workspace) && workspace_bytes > align256(need)) {

@@ -394,7 +394,15 @@ struct SplitPlan {
     bool half_row = false;
 };
 
-SplitPlan plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t room)
+// bytes of the partials (0: not split)
+size_t partial_bytes(const SplitPlan& p, int64_t M, int64_t N)
+{
+    const int64_t last = p.half_row ? (M - 1) % 128 + 1 : 0;
+    return p.parts[0] > 1 ? (size_t)(p.parts[0] * (M - last) + p.parts[1] * last) * (size_t)N * 4 : 0;
+}
+
+// `most`: bytes that as many parts for all tiles may take, `room`: that parts of different numbers may
+SplitPlan search_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t most, size_t room)
 {
     SplitPlan plan;
     const int64_t tiles_m = (M + 127) / 128;
@@ -416,7 +424,7 @@ SplitPlan plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t roo
         for (int64_t s = 2; s <= s_max; ++s) {
             const int st = (int)(((kh + s - 1) / s + 7) / 8 * 8);
             const int64_t n = (kh + st - 1) / st;
-            if (n < 2) continue;
+            if (n < 2 || (double)n * (double)M * (double)N * 4.0 > (double)most) continue;
             const double t = 10.0 + st * step * shared(n * tiles) + 3.0 + (double)n * (double)M * (double)N * 8.0 / 8.0e6;
             if (t < best) {
                 best = t;
@@ -452,6 +460,13 @@ SplitPlan plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t roo
         plan.steps[1] = sh;
     }
     return plan;
+}
+
+// the plan with all the room it likes, and only where its partials do not fit `room` that of the parts which do
+SplitPlan plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t room)
+{
+    const SplitPlan plan = search_split_k_nv16(M, N, K, cus, SIZE_MAX, room);
+    return partial_bytes(plan, M, N) <= room ? plan : search_split_k_nv16(M, N, K, cus, room, room);
 }
 
 int device_cus()
@@ -568,12 +583,6 @@ size_t nv16_workspace_bytes(int64_t M, int64_t K)
 }
 
 // bytes of fp32 partials a split-K run of this product needs, where there is room for as many as it likes (0: the product is not split)
-static size_t partial_bytes(const SplitPlan& p, int64_t M, int64_t N)
-{
-    const int64_t last = p.half_row ? (M - 1) % 128 + 1 : 0;
-    return p.parts[0] > 1 ? (size_t)(p.parts[0] * (M - last) + p.parts[1] * last) * (size_t)N * 4 : 0;
-}
-
 size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K) { return partial_bytes(plan_split_k_nv16(M, N, K, device_cus(), SIZE_MAX), M, N); }
 
 hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
@@ -607,7 +616,7 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     if (partial) {
         // few tiles, long K: every tile's K range shared by several workgroups, partial results added by a second kernel
         const SplitPlan plan = plan_split_k_nv16(M, N, K, cus, partial_room);
-        if (plan.parts[0] > 1 && partial_bytes(plan, M, N) <= partial_room) return launch_parts(g, plan, out_f32, static_cast<float*>(partial), st);
+        if (plan.parts[0] > 1) return launch_parts(g, plan, out_f32, static_cast<float*>(partial), st);
     }
     const int64_t slots = 2 * (int64_t)cus;
     const int64_t cols_w = (N + 255) / 256;                         // wide tile columns

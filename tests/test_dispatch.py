@@ -126,3 +126,21 @@ def test_few_token_linears_start_one_workgroup_per_compute_unit(host, call, cus)
         for K in (4096, 4224):
             (launch,) = host(["device", 0, cus], [call, 4, N, K])[1]
             assert launch["grid"][0] == min((N + 15) // 16, cus), (N, K)
+
+
+@pytest.mark.parametrize("fmt,M,N,K", [(MX, 97, 2056, 14336), (MX, 201, 4096, 14336), (NV, 128, 8192, 28672), (NV, 300, 4096, 4096), (NV, 256, 8192, 28672),
+                                       (NV, 320, 8192, 8192), (NV, 129, 4104, 12288)])
+def test_split_runs_have_the_parts_that_their_workspace_holds(host, fmt, M, N, K):
+    """Room for every number of parts up to the best one: a run in at most as many, whose partial sums end inside the workspace; more room
+    than the best run needs changes nothing."""
+    base, full = host(["device", 0, 256], ["bytes", OP_GEMM, M, N, K, fmt], ["bytes", OP_SPLIT, M, N, K, fmt])[1:]
+    base = (base + 255) // 256 * 256
+    part = M * N * 4
+    assert full >= base + 2 * part
+    best, more = host(["device", 0, 256], ["gemm", M, N, K, fmt, full], ["gemm", M, N, K, fmt, full + 7 * part])[1:]
+    assert best == more and best[-1]["ends"] == full
+    for n in range(1, (full - base) // part + 1):
+        for room in (base + n * part, base + (n + 1) * part - 1):
+            run = host(["device", 0, 256], ["gemm", M, N, K, fmt, room])[1]
+            assert ("reduce" in run[-1]["kernel"]) == (n >= 2), room
+            assert max(l["ends"] for l in run) <= room

@@ -618,9 +618,9 @@ def test_gemm_mxfp4_split_k(fp4, oracle, M, N, K, out_f32):
         assert np.all(err <= tol), (name, float((err / (1e-3 * S + 1e-300)).max()))
 
 
-@pytest.mark.parametrize("M,N,K", [(65, 264, 8320), (80, 130, 16512), (97, 1032, 8320), (201, 2056, 10240)])
+@pytest.mark.parametrize("M,N,K", [(65, 264, 8320), (80, 130, 16512), (97, 130, 16512), (97, 1032, 8320), (201, 2056, 10240)])
 def test_gemm_mxfp4_split_room_that_does_not_fit_the_best_plan(fp4, oracle, M, N, K):
-    """The parts of a split-K run follow the room for their sums: all of it, two parts of it, a byte less (130 columns: sums that are added
+    """The parts of a split-K run follow the room for their sums: all of it, two parts of it, a byte less (97 rows of 130 columns: sums that are added
     one by one)."""
     import torch
     rng = np.random.default_rng(M + N + K)
@@ -698,6 +698,29 @@ def test_gemm_nvfp4_parts_that_suit_half_tiles(fp4, M, N, K):
         ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
         out = fp4.fp4_gemm(*ops[0], *ops[1], M, N, K, NV, flags=fp4.OUT_F32, workspace=ws)
         assert bool(((out.double() - Y).abs() <= 1e-3 * S).all()), nbytes
+
+
+@pytest.mark.parametrize("fmt,M,N,K", [(MX, 97, 130, 16512), (MX, 201, 1032, 14336), (NV, 128, 2056, 10240), (NV, 192, 4200, 28672), (NV, 300, 528, 16512)])
+def test_gemm_split_runs_write_nothing_behind_their_workspace(fp4, fmt, M, N, K):
+    """Room for the best number of parts, for fewer, for one: the result against the fp64 product of the decoded operands, and the bytes behind the
+    workspace, which belong to the same allocation, as they were."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    gfl = fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM
+    ops = [fp4.fp4_rotate_quantize(torch.randn(n, K, device="cuda", generator=g).to(torch.bfloat16), 16, fmt, flags=fp4.LAYOUT_GEMM) for n in (M, N)]
+    a, w = (fp4.fp4_dequantize(*q, n, K, fmt, flags=fp4.OUT_F32 | fp4.LAYOUT_GEMM).double() for q, n in zip(ops, (M, N)))
+    Y, S = a @ w.t(), a.abs() @ w.abs().t()
+    base, full = (fp4.workspace_bytes(op, M, N, K, fmt, gfl) for op in (fp4.OP_GEMM, fp4.OP_GEMM_SPLIT_K))
+    base, part = (base + 255) // 256 * 256, M * N * 4
+    say(f"split-K room fmt={fmt} M={M} N={N} K={K}: {(full - base) / part} parts")
+    assert full >= base + 2 * part
+    for room in (full, full - 256, base + 2 * part, base + 2 * part - 16):
+        buf = torch.full((full + 2 * part,), 0xa5, dtype=torch.uint8, device="cuda")
+        out = fp4.fp4_gemm(*ops[0], *ops[1], M, N, K, fmt, flags=gfl | fp4.OUT_F32, workspace=buf[:room])
+        assert bool(((out.double() - Y).abs() <= 1e-3 * S).all()), room
+        assert bool((buf[room:] == 0xa5).all()), room
+        assert bool((buf[base:room] != 0xa5).any()) == (room >= base + 2 * part), room
 
 
 def test_gemm_mxfp4_exact_on_small_integers(fp4, oracle):
