@@ -9,11 +9,11 @@
 // No split-K workspace, no atomics, one launch.
 //
 // Three kernels share that scheme.  gemm_skinny_kernel launches one workgroup per row-block; its loads drain before the
-// reduction, so each workgroup pays one memory latency with nothing in flight.  gemm_stream_kernel (MXFP4) keeps one
+// reduction, so each workgroup pays one memory latency with nothing in flight.  gemm_stream_kernel keeps one
 // workgroup per compute unit resident, walks the row-blocks with a stride, holds the activations in registers for the
-// whole launch and two or three register batches of W per wave in rotation, so the loads of the next batches are in flight
+// whole launch (NVFP4: dequantized) and one to three register batches of W per wave in rotation, so the loads of the next batches are in flight
 // while the current one is multiplied and its row-block's partial sums meet in LDS.  gemm_skinny_nt_kernel (NVFP4; MXFP4
-// where the activations do not fit the registers) gives a workgroup two row-blocks so that each X fragment serves two W
+// where the activations do not fit the registers) gives a workgroup two row-blocks, or four, so that each X fragment serves as many W
 // fragments.  All add the eight partials in wave order: bit-identical results.
 #include "device_util.hpp"
 #include "internal.hpp"
@@ -321,8 +321,8 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_skinny_nt_kernel(Skinn
 // its X fragments -- of MT 16-token blocks -- are loaded once and stay in registers: a batch is W only, a W fragment meets
 // all MT blocks, and nothing of X is read again for the rest of the launch (the one-shot kernels fetch MT X fragments from
 // L2 per W fragment).  !XRES (MT = 1, any K): the X fragments travel with W in the batches, two buffers.
-// ONE: the workgroup has a single batch, nothing is requested behind it.
-template <int FMT, bool OUT_F32, int U, bool XRES, int MT = 1, int NB = 1, bool ONE = false>
+// NBUF (XRES): register buffers of a batch each, NBUF - 1 batches on their way while one is multiplied; 1: the workgroup has a single batch.
+template <int FMT, bool OUT_F32, int U, bool XRES, int MT = 1, int NB = 1, int NBUF = 2>
 __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyArgs g)
 {
     static_assert(MT == 1 || XRES, "several token blocks only with the X fragments resident");
@@ -499,13 +499,8 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
         // wave whose share of K is shorter requests its missing batches with zero size).  The batches of all the walker's
         // row-blocks form one sequence, NBUF - 1 of them in flight ahead of the one being multiplied, through NBUF
         // buffers in rotation; the loop body is NB * NBUF steps with every index a constant, left by `break` so that no
-        // control flow merges back into it.  A request costs the compute unit's address path 0.2 us, also one of zero size, and every
-        // step is code that a launch fetches cold: MXFP4 has the fewest buffers that the loads allow (against three where the registers
-        // had room, and four scale dwords a batch, us, M = 16 / 32: N = 6144, K = 4096 5.5 / 6.3 -> 5.0 / 5.6, N = 8192, K = 2048 4.9 / 5.5
-        // -> 4.3 / 4.9, N = 28672, K = 4096 12.5 / 14.0 -> 12.1 / 14.0; N = K = 2048, one batch, 3.4 / 4.1 -> 3.1 / 3.6).  Two batches per
-        // row-block keep three (N = 10240, K = 5120, M = 16: 8.1 us, with two 8.7), and so does NVFP4 (N = 57344, K = 8192: 43.8, 46.5).
-        constexpr int NBUF = ONE ? 1 : FMT == 1 || (NB == 2 && MT <= 2) ? 3 : 2;
-        static_assert(!ONE || NB == 1, "one batch");
+        // control flow merges back into it.
+        static_assert(NBUF > 1 || NB == 1, "one batch");
         constexpr int P = NB * NBUF;
         static_assert(P <= 12, "the loop body below spells out twelve steps");
         Batch buf[NBUF];
@@ -520,7 +515,7 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
         // current row-block, and behind a row-block's last batch reduce and store; true = that was the last row-block
         auto step = [&](auto qc) -> bool {
             constexpr int q = decltype(qc)::value, batch = q % NB, ahead = batch + NBUF - 1;
-            if constexpr (!ONE) request(buf[(q + NBUF - 1) % NBUF], rb + (ahead / NB) * G, ahead % NB);
+            if constexpr (NBUF > 1) request(buf[(q + NBUF - 1) % NBUF], rb + (ahead / NB) * G, ahead % NB);
             consume(buf[q % NBUF], k_begin + batch * U, acc, std::integral_constant<int, batch * U>{});
             if constexpr (batch == NB - 1) {
                 reduce_store(acc, rb, it);
@@ -528,7 +523,7 @@ __global__ __launch_bounds__(kSkinnyWaves * 64) void gemm_stream_kernel(SkinnyAr
                 for (int t = 0; t < MT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
                 ++it;
                 rb += G;
-                return ONE || rb >= n_rb;
+                return NBUF == 1 || rb >= n_rb;
             }
             return false;
         };
@@ -607,21 +602,37 @@ unsigned stream_grid(int N, int parts)
 // MXFP4 with the activations resident in registers: MT 16-token blocks, a wave's share of K in NB batches of four fragments
 // (K <= 4096 NB).  parts > 1: that many sets of workgroups, each with its own MT token blocks; W passes through every
 // XCD's L2 once and is read from there once per set.
+template <int MT, int NB, int NBUF>
+hipError_t launch_stream_buffers(const SkinnyArgs& g, bool out_f32, unsigned grid, hipStream_t st)
+{
+    const dim3 block(kSkinnyWaves * 64);
+    if (out_f32) hipLaunchKernelGGL((gemm_stream_kernel<0, true, 4, true, MT, NB, NBUF>), dim3(grid), block, 0, st, g);
+    else hipLaunchKernelGGL((gemm_stream_kernel<0, false, 4, true, MT, NB, NBUF>), dim3(grid), block, 0, st, g);
+    return hipGetLastError();
+}
+
+// How many buffers.  A request costs the compute unit's address path 0.2 us, also one of zero size, and every step is code that a launch
+// fetches cold, so as few as the loads allow: one where a workgroup has a single batch, two else (against three, and four scale dwords a
+// batch, us, M = 16 / 32: N = 6144, K = 4096 5.5 / 6.3 -> 5.0 / 5.6, N = 8192, K = 2048 4.9 / 5.5 -> 4.3 / 4.9, N = 28672, K = 4096 12.5 / 14.0 ->
+// 12.1 / 14.0; N = K = 2048, one batch, 3.4 / 4.1 -> 3.1 / 3.6).  Two batches per row-block keep three (N = 10240, K = 5120, M = 16: 8.1 us, with
+// two 8.7).  On long walks what is in flight counts for more than the start.  Batches of a short K are mostly empty, so that two hold too little:
+// three from five row-blocks per workgroup on up to K = 1536 (medians over 13902 products of 1 to 64 tokens, three buffers' time over two's: K = 1280
+// 0.96 at five, 0.87 beyond twelve; K = 1536 0.98 and 0.91; at three 1.02 and 1.03), from nine on up to K = 2560 (K = 1792 0.95, 2304 0.93, 2560 0.97, 3072
+// 1.01); and from three on with three or four batches and one token block (0.97 - 0.99; with fewer 1.02 - 1.05).  Several sets walk shorter ways: two.
 template <int MT, int NB>
 hipError_t launch_stream_resident(SkinnyArgs g, bool out_f32, int parts, hipStream_t st)
 {
     g.parts = parts;
-    const dim3 grid(stream_grid(g.N, parts)), block(kSkinnyWaves * 64);
+    const unsigned grid = stream_grid(g.N, parts);
+    const int n_rb = (g.N + 15) / 16, walkers = (int)grid / std::max(parts, 1), KC = g.K >> 7;
     if constexpr (NB == 1) {
-        if ((int64_t)grid.x * 16 >= (int64_t)std::max(parts, 1) * g.N) {   // one batch per workgroup
-            if (out_f32) hipLaunchKernelGGL((gemm_stream_kernel<0, true, 4, true, MT, 1, true>), grid, block, 0, st, g);
-            else hipLaunchKernelGGL((gemm_stream_kernel<0, false, 4, true, MT, 1, true>), grid, block, 0, st, g);
-            return hipGetLastError();
-        }
+        if (n_rb <= walkers) return launch_stream_buffers<MT, NB, 1>(g, out_f32, grid, st);
+        if (parts <= 1 && (n_rb > 8 * walkers ? KC <= 20 : n_rb > 4 * walkers && KC <= 12)) return launch_stream_buffers<MT, NB, 3>(g, out_f32, grid, st);
     }
-    if (out_f32) hipLaunchKernelGGL((gemm_stream_kernel<0, true, 4, true, MT, NB>), grid, block, 0, st, g);
-    else hipLaunchKernelGGL((gemm_stream_kernel<0, false, 4, true, MT, NB>), grid, block, 0, st, g);
-    return hipGetLastError();
+    if constexpr (NB >= 3 && MT == 1) {
+        if (parts <= 1 && n_rb > 2 * walkers) return launch_stream_buffers<MT, NB, 3>(g, out_f32, grid, st);
+    }
+    return launch_stream_buffers<MT, NB, NB == 2 && MT <= 2 ? 3 : 2>(g, out_f32, grid, st);
 }
 
 // NVFP4, up to 16 tokens, K <= 8192: the activations resident as fp16 (a wave's share of K in NB batches of two fragments)
@@ -630,8 +641,8 @@ hipError_t launch_stream_resident_nv(SkinnyArgs g, bool out_f32, int parts, hipS
 {
     g.parts = parts;
     const dim3 grid(stream_grid(g.N, parts)), block(kSkinnyWaves * 64);
-    if (out_f32) hipLaunchKernelGGL((gemm_stream_kernel<1, true, 2, true, 1, NB>), grid, block, 0, st, g);
-    else hipLaunchKernelGGL((gemm_stream_kernel<1, false, 2, true, 1, NB>), grid, block, 0, st, g);
+    if (out_f32) hipLaunchKernelGGL((gemm_stream_kernel<1, true, 2, true, 1, NB, 3>), grid, block, 0, st, g);
+    else hipLaunchKernelGGL((gemm_stream_kernel<1, false, 2, true, 1, NB, 3>), grid, block, 0, st, g);
     return hipGetLastError();
 }
 
@@ -645,8 +656,8 @@ hipError_t launch_stream_nv(const SkinnyArgs& g, bool out_f32, int per, int part
     }
 }
 
-// largest number of batches per row-block for which MT token blocks of X fit the registers (MT * NB * 20 for X: up to
-// 235 in all, no spills; three blocks with three batches would spill)
+// largest number of batches per row-block for which MT token blocks of X fit the registers (16 registers a batch
+// and block for the codes, one for the scale bytes of four fragments; no spills; three blocks with three batches would spill)
 constexpr int stream_max_batches(int mt)
 {
     return mt <= 2 ? 4 : 2;
@@ -792,10 +803,14 @@ hipError_t launch_fmt(const SkinnyArgs& g, bool out_f32, hipStream_t st)
     switch (mt) {
         case 1:
             if constexpr (FMT == 0) {
-                // (K <= 1024, one fragment per wave, is launch-bound: N = 8192, K = 1024, 3.7 us with the one-shot kernel against 4.6.
+                // (K <= 1024, one fragment per wave, is launch-bound: N = 8192, K = 1024, 3.7 us with the one-shot kernel against 4.6.  So is a
+                // share of two fragments that only some of the waves have: one-shot's time over the persistent kernel's, K = 1152 and 1280
+                // 0.92 up to N = 2048, 0.94 - 0.98 up to 16384 (beyond that three buffers are level or faster); 1408 and 1536 0.95 - 0.98 up to
+                // 2048, 1.01 at 4096; 1664 to 2048 0.97 - 1.04 up to 2048, not taken.
                 // NVFP4 stays with the one-shot kernels where X does not fit: its in-register dequantization needs the registers of
                 // the second batch buffer -- 68 us against 54 on N = 57344, K = 8192.)
-                const bool one_shot = per <= 1;
+                const int n_rb = (g.N + 15) / 16, kc = g.K >> 7, w = stream_walkers();
+                const bool one_shot = per <= 1 || (kc <= 12 && n_rb <= (kc <= 10 ? 4 * w : w / 2));
                 hipError_t e = hipSuccess;
                 if (!one_shot) {
                     if (try_stream_resident<1>(g, out_f32, per, 1, st, &e)) return e;

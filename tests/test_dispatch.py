@@ -144,3 +144,15 @@ def test_split_runs_have_the_parts_that_their_workspace_holds(host, fmt, M, N, K
             run = host(["device", 0, 256], ["gemm", M, N, K, fmt, room])[1]
             assert ("reduce" in run[-1]["kernel"]) == (n >= 2), room
             assert max(l["ends"] for l in run) <= room
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [(1, 512, 1152, "gemm_skinny_kernel"), (16, 2048, 1536, "gemm_skinny_kernel"), (7, 1024, 2048, "Li1ELi1ELi1E"),
+                                          (5, 16384, 1280, "gemm_skinny_kernel"), (16, 4096, 1536, "Li1ELi1ELi1E"), (16, 2048, 2048, "Li1ELi1ELi1E"),
+                                          (8, 6144, 2048, "Li1ELi1ELi2E"), (8, 40960, 1152, "Li1ELi1ELi3E"), (55, 42752, 2560, "Li4ELi1ELi3E"),
+                                          (20, 57344, 3072, "Li2ELi1ELi2E"), (12, 24576, 1536, "Li1ELi1ELi3E"), (1, 28672, 4096, "Li1ELi1ELi2E"),
+                                          (16, 4096, 14336, "Li1ELi4ELi2E"), (16, 14336, 14336, "Li1ELi4ELi3E"), (2, 10240, 5120, "Li1ELi2ELi3E"),
+                                          (20, 14336, 14336, "Li2ELi4ELi2E")])
+def test_mxfp4_few_tokens_take_the_buffers_that_suit_their_walk(host, M, N, K, kernel):
+    """One-shot kernel, or token blocks, batches per row-block and buffers of the persistent one."""
+    (launch,) = host(["device", 0, 256], ["gemm", M, N, K, MX, 0])[1]
+    assert kernel in launch["kernel"], launch

@@ -535,6 +535,18 @@ def test_gemm_mxfp4_persistent_kernel_with_several_batches_of_resident_activatio
     _gemm_case(fp4, oracle, MX, M, N, K, seed=700 + M + K, out_f32=out_f32, layout_gemm=True)
 
 
+@pytest.mark.parametrize("M,N,K", [(5, 296, 1152), (16, 296, 2560), (40, 296, 1408), (60, 280, 2176), (20, 168, 1536), (64, 168, 1280), (9, 104, 8320),
+                                   (16, 88, 12416), (1, 88, 16384)])
+def test_gemm_mxfp4_streamed_through_a_third_buffer(fp4, oracle, M, N, K, knobs):
+    """Long walks (two workgroups, N / 16 row-blocks): more than eight row-blocks each and K up to 2560, more than four and K up to 1536, more
+    than two and three or four batches; numbers of row-blocks that leave the three buffers at each turn of their rotation; ragged N."""
+    for grid in (1, 2):
+        knobs(grid=grid)
+        _gemm_case(fp4, oracle, MX, M, N, K, seed=820 + M + K, out_f32=grid == 1, layout_gemm=True)
+    knobs(grid=0)
+    _gemm_case(fp4, oracle, MX, M, N, K, seed=820 + M + K, out_f32=False, layout_gemm=True)   # (up to 16 tokens and K = 1152: the one-shot kernel)
+
+
 @pytest.mark.parametrize("grid,M,N,K,out_f32", [(0, 65, 400, 4096, False), (0, 128, 1000, 4096, True), (16, 96, 2056, 2048, False),
                                                 (16, 100, 1160, 1152, True), (1, 81, 520, 3072, False), (0, 113, 6144, 4096, False),
                                                 (16, 128, 4104, 1536, True), (0, 72, 12288, 3200, False), (0, 96, 272, 8192, False),
