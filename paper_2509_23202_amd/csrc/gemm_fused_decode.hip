@@ -287,7 +287,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) void gemm_w4a16_decode_kernel(Fus
 // does not exist is requested with zero size, so that every request is unconditional (the compiler's waits count on it).
 // Bound: start-up, then HBM.  A request of eight waves costs the compute unit's address path some 0.2 us, also one of zero size, and every copy of a
 // step is code to fetch, cold in each launch: so a batch asks for its scales twice instead of four times, and NBUF is as small as the
-// loads allow: 1 where a workgroup has a single batch (nothing else is requested), 2 else (3 where it says so below).  Against three buffers
+// loads allow: 1 where a workgroup has a single batch (nothing else is requested), 2 else (3 where launch_few_stream says so).  Against three buffers
 // everywhere, us, M = 4, weight-only: N = K = 1024 3.7 -> 3.1, 4096 5.1 -> 4.2, N = 6144, K = 4096 6.6 -> 5.6, N = 28672 13.4 -> 12.7, N = 4096,
 // K = 14336 11.9 -> 10.7.  (Four or five buffers: 6 and 10 % slower than three.  A last step without a request: a third copy of the
 // step, N = 6144 5.7 -> 6.0.)
@@ -494,8 +494,10 @@ hipError_t launch_few_stream(const FusedArgs& a, hipStream_t st)
     const int n_rb = (a.N + 15) / 16, grid = std::min(n_rb, compute_units());
     if (n_rb == grid && a.K <= 4096) return launch_few_stream_as<QUANT, OUT_F32, 1>(a, grid, st);   // (a compute unit each, with one batch)
     if constexpr (QUANT) {
-        // (two batches per row-block: the first row-block whole on its way under the rotation, N = K = 8192, M = 4 9.5 -> 8.9 us)
-        if (a.K > 4096 && a.K <= 8192) return launch_few_stream_as<QUANT, OUT_F32, 3>(a, grid, st);
+        // (two batches per row-block, both nearly full, on a long walk.  Medians over 12909 products of K = 4224 to 8192, two buffers' time over
+        // three's: one or two row-blocks per workgroup 0.90 - 0.97 (N = 4400 to 4800, K about 6144, M = 1 / 4: 6.8 / 8.4 us with three, 6.3 / 8.0 with two), more 0.95 -
+        // 1.00 up to K = 7168, beyond that 0.97 - 1.00 with one token and 1.01 - 1.03 with more)
+        if (a.K > 7168 && a.K <= 8192 && a.M > 1 && n_rb > 2 * grid) return launch_few_stream_as<QUANT, OUT_F32, 3>(a, grid, st);
     }
     return launch_few_stream_as<QUANT, OUT_F32, 2>(a, grid, st);
 }
