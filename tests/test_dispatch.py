@@ -146,6 +146,12 @@ def test_split_runs_have_the_parts_that_their_workspace_holds(host, fmt, M, N, K
             assert max(l["ends"] for l in run) <= room
 
 
+@pytest.mark.parametrize("M,K", [(1, 235520), (2, 117760), (3, 77824), (4, 58368)])
+def test_fused_linear_takes_the_one_shot_kernel_where_lds_does_not_hold_the_codes(host, M, K):
+    held, over = (host(["device", 0, 256], ["fp4_fused_linear", M, 24, k])[1] for k in (K, K + 128))
+    assert "gemm_few_stream_kernel" in held[0]["kernel"] and "gemm_fused_decode_kernel" in over[0]["kernel"]
+
+
 @pytest.mark.parametrize("M,N,K,kernel", [(1, 512, 1152, "gemm_skinny_kernel"), (16, 2048, 1536, "gemm_skinny_kernel"), (7, 1024, 2048, "Li1ELi1ELi1E"),
                                           (5, 16384, 1280, "gemm_skinny_kernel"), (16, 4096, 1536, "Li1ELi1ELi1E"), (16, 2048, 2048, "Li1ELi1ELi1E"),
                                           (8, 6144, 2048, "Li1ELi1ELi2E"), (8, 40960, 1152, "Li1ELi1ELi3E"), (55, 42752, 2560, "Li4ELi1ELi3E"),

@@ -175,8 +175,8 @@ def test_w4a16_full_size_decode_layers(fp4, oracle):
 
 @pytest.mark.parametrize("M,N,K,b", [(1, 8200, 512, 32), (3, 8216, 128 * 9, 64), (4, 12296, 4096, 128), (2, 40, 128 * 67, 16), (4, 8600, 128, 32)])
 def test_fused_persistent_equals_two_launch_path(fp4, M, N, K, b):
-    """Sizes that take the persistent workgroups (two or more row-blocks each, or K > 8192): a ragged last row-block, a share of
-    K that ends inside a batch of fragments, waves with no share, one batch and several per row-block."""
+    """Several row-blocks per persistent workgroup, and K > 8192: a ragged last row-block, a share of K that ends inside a batch of
+    fragments, waves with no share, one batch and several per row-block."""
     test_fused_equals_two_launch_path(fp4, M, N, K, b, False)
 
 
@@ -193,3 +193,25 @@ def test_few_tokens_either_side_of_a_buffer_less(fp4, oracle, M, N, K, b):
     if b <= 32:
         test_fused_equals_two_launch_path(fp4, M, N, K, b, False)
     _w4a16_case(fp4, oracle, M, N, K, b, False, salt=M + N + b + 2)
+
+
+# K at which a compute unit's LDS still holds the codes and scale bytes of M tokens, and one fragment more, which the one-shot kernel takes
+@pytest.mark.parametrize("M,N,K,b", [(4, 24, 58368, 32), (4, 24, 58496, 32), (4, 264, 58496, 16), (3, 40, 78080, 64), (4, 24, 60032, 128),
+                                     (1, 24, 235520, 32), (1, 24, 235648, 32), (2, 40, 117888, 64)])
+def test_fused_either_side_of_what_lds_holds(fp4, M, N, K, b):
+    """The one-shot quantizing kernel and the largest K of the persistent one: ragged N, shares of K that end inside a chunk of four
+    fragments, waves with a shorter share.  Against the fp64 product of the codes that the stand-alone quantizer makes of the same inputs, to the
+    bare accumulation bound, and for blocks of up to 32 bit for bit against the two calls."""
+    import torch
+    r = inputs.RECIPES[2]
+    x, w = to_dev_bf16(r.x(M, K, salt=M + N)), to_dev_bf16(r.w(N, K, salt=M + N))
+    qw = fp4.fp4_quantize_weights(w, b, MX, flags=fp4.LAYOUT_GEMM)
+    say(f"fused, one-shot and persistent M={M} N={N} K={K} b={b}")
+    got = fp4.fp4_fused_linear(x, b, qw[0], qw[1], N, MX, flags=fp4.OUT_F32)
+    qa = fp4.fp4_rotate_quantize(x, b, MX)
+    a = fp4.fp4_dequantize(qa[0], qa[1], None, M, K, MX, flags=fp4.OUT_F32).double()
+    wd = fp4.fp4_dequantize(qw[0], qw[1], None, N, K, MX, flags=fp4.OUT_F32 | fp4.LAYOUT_GEMM).double()
+    Y, S = a @ wd.t(), a.abs() @ wd.abs().t()
+    assert bool(((got.double() - Y).abs() <= 1e-3 * S).all())
+    if b <= 32:
+        test_fused_equals_two_launch_path(fp4, M, N, K, b, True)
