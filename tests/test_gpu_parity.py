@@ -445,7 +445,7 @@ def test_gemm_mxfp4_persistent_workgroups_walk_several_tiles(fp4, oracle, grid, 
     _gemm_case(fp4, oracle, MX, 272, 528, 1280, seed=40 + grid, out_f32=out_f32, layout_gemm=True)
 
 
-@pytest.mark.parametrize("variant", [11, 12, 14, 16])
+@pytest.mark.parametrize("variant", [11, 14, 16])
 @pytest.mark.parametrize("K", [128, 256, 384, 1024, 1152, 3072])
 @pytest.mark.parametrize("grid", [1, 2])
 def test_gemm_mxfp4_persistent_interior_tiles_overlap_their_stores(fp4, oracle, grid, K, variant, knobs):
@@ -456,7 +456,17 @@ def test_gemm_mxfp4_persistent_interior_tiles_overlap_their_stores(fp4, oracle, 
     _gemm_case(fp4, oracle, MX, 512, 768, K, seed=60 + grid + K, out_f32=False, layout_gemm=True)
 
 
-@pytest.mark.parametrize("variant", [11, 12, 14, 16])
+@pytest.mark.parametrize("variant", [1, 4, 9, 12])
+@pytest.mark.parametrize("M,N,K,out_f32", [(512, 768, 128, False), (512, 768, 384, False), (512, 768, 3072, False), (528, 784, 3072, False), (528, 784, 3072, True)])
+def test_gemm_mxfp4_small_tiles_whatever_the_grid_cap(fp4, oracle, M, N, K, out_f32, variant, knobs):
+    """Tiles of 64 and 96 rows are one workgroup each, which the cap on persistent workgroups leaves alone: whole and ragged tile grids, bf16
+    (staged) and fp32 (direct) epilogues."""
+    knobs(variant=variant)
+    knobs(grid=2)
+    _gemm_case(fp4, oracle, MX, M, N, K, seed=97 + K + variant, out_f32=out_f32, layout_gemm=True)
+
+
+@pytest.mark.parametrize("variant", [11, 14, 16])
 @pytest.mark.parametrize("grid", [1, 3])
 @pytest.mark.parametrize("out_f32", [False, True])
 def test_gemm_mxfp4_persistent_variants_across_ragged_tiles(fp4, oracle, grid, out_f32, variant, knobs):
@@ -552,10 +562,11 @@ def test_gemm_mxfp4_streamed_through_a_third_buffer(fp4, oracle, M, N, K, knobs)
                                                 (16, 128, 4104, 1536, True), (0, 72, 12288, 3200, False), (0, 96, 272, 8192, False),
                                                 (16, 128, 400, 6144, True), (0, 70, 144, 5120, False), (16, 81, 528, 8192, True),
                                                 (0, 200, 1000, 4096, False), (24, 256, 528, 8192, True), (0, 300, 272, 5120, False),
-                                                (32, 512, 400, 4096, False), (0, 130, 8192, 4096, False)])
+                                                (32, 512, 400, 4096, False), (0, 130, 8192, 4096, False),
+                                                (16, 65, 264, 1152, True), (32, 200, 520, 1536, False), (16, 96, 2056, 2048, True)])
 def test_gemm_mxfp4_65_to_512_tokens_on_sets_of_persistent_workgroups(fp4, oracle, grid, M, N, K, out_f32, knobs):
-    """65 to 512 tokens on a narrow MXFP4 layer with 1024 < K <= 8192 (sets x N <= 32768): the persistent weight-streaming
-    kernel runs as two to eight sets of workgroups, each with three or four 16-token blocks of X in registers (the last
+    """65 to 512 tokens on a narrow MXFP4 layer with 1024 < K <= 8192, where their price says so (the widest of these run as small tiles): the persistent
+    weight-streaming kernel runs as two to eight sets of workgroups, each with three or four 16-token blocks of X in registers (the last
     set's last blocks can lie past the end of M and are then neither loaded nor stored); a grid cap makes 8 walkers per
     set take many row-blocks each; ragged N, waves without a K share (K / 128 = 9, 12), fp32 and bf16 output."""
     knobs(grid=grid)
