@@ -82,9 +82,8 @@ void gemm_mx_kernel(GemmArgs g)
     constexpr int LPW = (F + NW - 1) / NW;                  // fragment loads per wave per stage
     constexpr int TM = WM / 16, TN = WN / 16;               // MFMA tiles per wave
     constexpr int STAGE_BYTES = F * 1024;
-    // PAIR: one barrier, and one wait for LDS reads, per two K-steps, for a stage less on its way: what a step of a small tile
-    // takes beside its copies (20 ns a KB, the compute unit's load path) falls from 110 to 75 ns (128 x 128 tiles, N = 4096, M = 400:
-    // K = 4096 11.2 -> 10.5 us, 14336 27.8 -> 26.2; with six or seven stages the stages missing cost more than that).
+    // PAIR: one barrier, and one wait for LDS reads, per two K-steps, for a stage less on its way (128 x 128 tiles, N = 4096, M = 400:
+    // K = 4096 11.2 -> 10.5 us, 14336 27.8 -> 26.2, of which 11 ns a step; with six or seven stages the stages missing cost more than that).
     constexpr bool PAIR = STAGES == 8 && !PERSIST;
     constexpr int LEAD = PAIR ? STAGES - 2 : STAGES - 1;    // a step requests the stage that many steps behind its own
     static_assert(STAGES >= 3 && STAGES <= 8, "ring bookkeeping is written for 3 to 8 stages");
@@ -500,8 +499,8 @@ void launch_splitk_reduce(const float* partial, int splits, int64_t mn, float al
     else hipLaunchKernelGGL((splitk_reduce_kernel<false, V>), grid, dim3(256), 0, st, partial, splits, mn, alpha, out);
 }
 
-// the tile shapes that have a split-K instantiation
-constexpr bool tile_splits(int bm, int bn) { return bm <= 96 && bn <= 128; }
+// the tile shapes that have a split-K instantiation: the small ones, and 128 x 128 with four stages
+constexpr bool tile_splits(int bm, int bn, int stages) { return (bm <= 96 && bn <= 128) || (bm == 128 && bn == 128 && stages == 4); }
 
 // splits > 1: every tile is computed by `splits` workgroups, split y taking K-steps y * split_steps .. and writing its
 // fp32 partial tile to slice y of `partial`; the caller then runs splitk_reduce_kernel
@@ -512,7 +511,7 @@ hipError_t launch_variant(const GemmArgs& g0, bool out_f32, hipStream_t st, int 
     g.tiles_m = (int)((g.M + BM - 1) / BM);
     g.tiles_n = (int)((g.N + BN - 1) / BN);
     if (splits > 1) {
-        if constexpr (tile_splits(BM, BN)) {
+        if constexpr (tile_splits(BM, BN, STAGES)) {
             constexpr int threads_s = (BM / WM) * (BN / WN) * 64;
             constexpr size_t lds_s = (size_t)STAGES * (BM + BN) / 16 * 1024 +
                                      (STAGES >= 4 ? (size_t)((BM / 16 + 1) / 2 + (BN / 16 + 1) / 2) * 1024 * (STAGES >= 6 ? 2 : 1) : (size_t)(BM + BN) / 16 * 256);
@@ -580,15 +579,19 @@ struct TileCost {
 // reads under the other's products, against four of 128 x 64 M = 1111, N = 4096, K = 14336: 45.5 -> 41.0 us.  128 x 256 with two
 // workgroups per compute unit overlaps one's start-up and stores with the other's main loop: where a tile is not much longer
 // than those (M = 2166, N = 10968, K = 1024: 26.5 us, the best of the others 30.0; M = 1104, N = 26544, K = 1536: 38.4 against 42.5).
-// Where 128 x 128 tiles leave compute units without one, what a step takes is hardly its products: 75 ns, and 20 a KB of copies.  Tiles
-// of 64 or 96 rows and 64 or 128 columns put more units to work on fewer bytes each.  The last four rows are fitted to 9996 products with
-// cold weights (M = 65 ... 4096, N = 512 ... 28672, K = 1024 ... 28672), on the scale of the others.  Against the plan without them and with the streaming kernels
-// up to a fixed size: 0.92 of the time on average over 3352 products of up to 4096 tokens, 100 slower by 3 % and two by 10 (N = K = 2048, M = 201:
-// 6.8 -> 5.0 us; N = 1024, K = 2816: 7.8 -> 5.5; N = 6144, K = 4096: 11.1 -> 9.6; N = K = 8192: 21.8 -> 17.9).
+// Where 128 x 128 tiles leave compute units without one, what a step takes is its copies: 128 tiles in two rows, one to a compute unit, 30 ns
+// and 10 a KB where W comes from the last-level cache, 16 a KB where it comes from HBM (64 x 64 / 64 x 128 / 128 x 128, 8 / 12 / 16 KB a step:
+// 112 / 133 / 197 and 152 / 223 / 285 ns).  Tiles
+// of 64 or 96 rows and 64 or 128 columns put more units to work on fewer bytes each (N = K = 2048, M = 201: 6.8 -> 5.0 us; N = 1024, K = 2816:
+// 7.8 -> 5.5; N = 6144, K = 4096: 11.1 -> 9.6; N = K = 8192: 21.8 -> 17.9).  Their four rows were fitted to 9996 products with cold weights (M = 65
+// ... 4096, N = 512 ... 28672, K = 1024 ... 28672), on the scale of the others, and once more, with those of the eight-stage 128 x 128 tiles, the
+// parts and the streaming kernels' prices, to 32735 on three cards (M = 17 ... 900, N = 512 ... 32768, K = 1024 ... 28672), for the choice to lose least
+// and for few products to lose by the change.  What was taken lost 1.1 % on the best way on average and more than 5 % on 3006 products; now 0.65 % and
+// 1503 (0.7 % on the 8100 left out of the fit).  2923 products go another way, at 0.95 of their time on average, 41 of them more than 5 % slower.
 constexpr TileCost kTileCosts[] = {
     {2, 128, 128, 2, 3.539, 0.307, 0.207, 0.890, 1.100, 2.998, 0.227, 0.525},
-    {18, 128, 128, 1, 2.486, 0.188, 0.096, 1.359, 1.560},   // one workgroup per compute unit, eight-stage ring
-    {17, 128, 128, 1, 2.917, 0.222, 0.064, 1.478, 1.117},
+    {18, 128, 128, 1, 2.990, 0.193, 0.099, 1.057, 1.501},   // one workgroup per compute unit, eight-stage ring
+    {17, 128, 128, 1, 2.916, 0.230, 0.068, 1.215, 0.609},
     {5, 256, 128, 1, 3.755, 0.305, 0.153, 0.861, 2.861},
     {6, 192, 128, 1, 2.521, 0.308, 0.102, 1.515, 2.449},
     {7, 160, 128, 1, 2.538, 0.301, 0.058, 1.800, 0.928},
@@ -598,11 +601,13 @@ constexpr TileCost kTileCosts[] = {
     {11, 256, 256, 1, 6.536, 0.454, 0.293, 1.470, 4.683},   // persistent: the next tile's first stages and the stores overlap
     {15, 128, 256, 2, 5.720, 0.475, 0.516, 0.119, 1.977, 5.139, 0.452, 0.275},
     {16, 128, 256, 2, 5.883, 0.607, 0.367, 1.472, 1.613, 2.756, 0.456, 0.314},   // persistent
-    {1, 64, 64, 2, 1.381, 0.131, 0.117, 2.946, 0.000, 0.145, 0.132, 0.208},     // these four with an eight-stage ring
-    {4, 64, 128, 1, 0.637, 0.164, 0.043, 3.028, 0.538},
-    {9, 96, 128, 1, 1.678, 0.183, 0.052, 2.475, 0.498},
-    {12, 96, 64, 1, 2.216, 0.149, 0.028, 1.506, 0.000},
+    {1, 64, 64, 2, 1.320, 0.134, 0.101, 2.941, 0.000, 0.147, 0.132, 0.162},     // these four with an eight-stage ring
+    {4, 64, 128, 1, 0.640, 0.164, 0.045, 3.000, 0.509},
+    {9, 96, 128, 1, 1.679, 0.182, 0.064, 2.467, 0.408},
+    {12, 96, 64, 1, 2.334, 0.153, 0.006, 1.770, 0.000},
 };
+// 128 x 128 tiles in parts, priced from such runs
+constexpr TileCost kSplit128 = {2, 128, 128, 2, 3.260, 0.317, 0.268, 0.809, 0.000, 1.638, 0.246, 0.260};
 
 double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int cus)
 {
@@ -623,9 +628,11 @@ bool may_split(int64_t M, int64_t K) { return M > 64 && K >= 32 * 128; }
 // room for partials also as a split-K run, or the streaming kernels (variant 0), which have a price of their own (gemm_stream_us).
 // With few tiles and a long K -- batched decoding against a narrow layer -- a handful of compute units each stream a long K range alone.
 // Every tile's K range can then be cut into up to eight parts of at least 16 K-steps (whole scale batches of eight), each part one
-// workgroup of as many tiles.  Priced as as many tiles of as many steps, which share their start, and 3.9 us + bytes at 4 TB/s for the
-// partials and their sum's launch; a split has to win 4 %.  Of 2208 products with K from 4096 to 28672, parts of up to 96 rows
-// were the best way in 749, 1.26 times as fast as the best unsplit one on average; parts of 128 and more rows in nine.
+// workgroup of as many tiles.  Priced as as many tiles of as many steps, which share their start, and 3.8 us + bytes at 4.3 TB/s (written and
+// read) for the partials and their sum's launch; a split has to win 4 %.  Of 2208 products with K from 4096 to 28672, parts of up to 96 rows
+// were the best way in 749, 1.26 times as fast as the best unsplit one on average.  Parts of 128 x 128, two workgroups to a compute unit, are where more
+// than half the units have a small tile and none could have a second part of one (M = 119, N = 8320, K = 24576: 39.6 us in three parts, unsplit
+// 64 x 128 52.2): 44 of 32735 products, at 0.905 of their time on average.
 MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room)
 {
     MxPlan p{0, 1, 0};
@@ -658,21 +665,23 @@ MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room)
     }
     if (!may_split(M, K)) return p;
     best *= 0.96;
-    for (const TileCost& c : kTileCosts) {
-        if (!tile_splits(c.bm, c.bn)) continue;
+    auto parts = [&](const TileCost& c, double share, double launch, double us_per_mb) {
         const int64_t t = tiles(c), s_max = std::min<int64_t>(std::min<int64_t>((int64_t)cus * c.per_cu / t, kt / 16), 8);
         for (int64_t s = 2; s <= s_max; ++s) {
             const int64_t st = ((kt + s - 1) / s + 7) / 8 * 8;
             const int64_t n = (kt + st - 1) / st;  // parts of st steps that cover K (the last may be shorter)
             const double bytes = (double)n * (double)M * (double)N * 4.0;
             if (n < 2 || bytes > (double)room) continue;
-            const double us = 0.871 * tile_cost(c, t * n, st, false, cus) + 3.94 + 2.0 * bytes / 8.03e6;
+            const double us = share * tile_cost(c, t * n, st, false, cus) + launch + us_per_mb * bytes * 1e-6;
             if (us < best) {
                 best = us;
                 p = MxPlan{c.variant, (int)n, (int)st};
             }
         }
-    }
+    };
+    for (const TileCost& c : kTileCosts)
+        if (c.bm <= 96 && c.bn <= 128) parts(c, 0.811, 3.83, 0.467);
+    parts(kSplit128, 1.0, 8.04, 0.200);
     return p;
 }
 
@@ -703,7 +712,7 @@ hipError_t launch_gemm_mxfp4(const void* a_codes, const void* a_scales, const vo
     float* const pp = static_cast<float*>(partial);
     switch (plan.variant) {
         case 1: return launch_variant<64, 64, 32, 32, 8, 1>(g, out_f32, st, splits, split_steps, pp);
-        case 2: return launch_variant<128, 128, 64, 64, 4>(g, out_f32, st);
+        case 2: return launch_variant<128, 128, 64, 64, 4>(g, out_f32, st, splits, split_steps, pp);
         case 3: return launch_variant<64, 256, 64, 64, 4>(g, out_f32, st);
         case 4: return launch_variant<64, 128, 32, 64, 8>(g, out_f32, st, splits, split_steps, pp);
         case 5: return launch_variant<256, 128, 64, 64, 4>(g, out_f32, st);

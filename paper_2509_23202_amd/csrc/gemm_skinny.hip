@@ -847,7 +847,7 @@ hipError_t launch_fmt(const SkinnyArgs& g, bool out_f32, hipStream_t st)
 // What the MXFP4 streaming kernels take with more than 16 tokens, in microseconds: the activations' way into registers, then row-blocks
 // per workgroup times (a fixed part, the products, the loads in batches of four fragments).  Up to 64 tokens in one set of workgroups
 // where they fit, else, up to 512 tokens, in several sets (K <= 16384, with more than 64 tokens 8192; they pay on layers narrow enough that
-// each set has few row-blocks).  Fitted to 6751 and 4552 products with cold weights (N = 512 ... 57344, K = 1024 ... 14336), median error 2.5 %, on the tile table's scale.
+// each set has few row-blocks).  Fitted to 6751 and 4552 products with cold weights (N = 512 ... 57344, K = 1024 ... 14336), median error 2.5 %, on the tile table's scale, and with it once more (see there).
 // 0: not priced, up to 64 tokens they take it; infinity: they do not take it.
 double gemm_stream_us(int64_t M, int64_t N, int64_t K)
 {
@@ -859,13 +859,13 @@ double gemm_stream_us(int64_t M, int64_t N, int64_t K)
     if (per == 1) return mt > 4 ? none : 2.90 + 0.256 * mt + (double)n_rb / cus * (0.611 + 0.106 * mt);
     if (mt <= 4 && nbk <= stream_max_batches(mt)) {
         const double rounds = (double)((n_rb + cus - 1) / cus);
-        return 2.25 + (0.0210 * per + 0.266 * nbk) * mt + rounds * (0.0366 + 0.0522 * per + 0.0757 * mt + 0.296 * nbk) + 0.140 * per * (double)n_rb / cus;
+        return 2.35 + (0.0208 * per + 0.360 * nbk) * mt + rounds * (0.0753 + 0.0391 * per + 0.0917 * mt + 0.271 * nbk) + 0.123 * per * (double)n_rb / cus;
     }
     const int most = nbk <= stream_max_batches(4) ? 4 : nbk <= stream_max_batches(2) ? 2 : 0;
     if (most == 0 || (mt > 4 && most < 4)) return mt <= 4 ? 0.0 : none;   // (more than 64 tokens with K > 8192: not timed)
     const int parts = (mt + most - 1) / most, m = (mt + parts - 1) / parts, walkers = std::max(cus / parts / 8 * 8, 8);
     const double rounds = (double)((n_rb + walkers - 1) / walkers);
-    return 2.80 + (0.0498 * per + 0.117 * nbk) * m + rounds * (0.180 + 0.0045 * per + 0.0317 * m + 0.524 * nbk) + 0.0480 * per * (double)n_rb / walkers;
+    return 2.66 + (0.0401 * per + 0.1556 * nbk) * m + rounds * (0.203 + 0.0056 * per + 0.0264 * m + 0.508 * nbk) + 0.0460 * per * (double)n_rb / walkers;
 }
 
 // NVFP4: every product of up to 64 tokens, and of 65 to 256 one set of fp16-resident persistent workgroups per 16-token block where the layer is small
