@@ -494,10 +494,11 @@ hipError_t launch_few_stream(const FusedArgs& a, hipStream_t st)
     const int n_rb = (a.N + 15) / 16, grid = std::min(n_rb, compute_units());
     if (n_rb == grid && a.K <= 4096) return launch_few_stream_as<QUANT, OUT_F32, 1>(a, grid, st);   // (a compute unit each, with one batch)
     if constexpr (QUANT) {
-        // (two batches per row-block, both nearly full, on a long walk.  Medians over 12909 products of K = 4224 to 8192, two buffers' time over
-        // three's: one or two row-blocks per workgroup 0.90 - 0.97 (N = 4400 to 4800, K about 6144, M = 1 / 4: 6.8 / 8.4 us with three, 6.3 / 8.0 with two), more 0.95 -
-        // 1.00 up to K = 7168, beyond that 0.97 - 1.00 with one token and 1.01 - 1.03 with more)
-        if (a.K > 7168 && a.K <= 8192 && a.M > 1 && n_rb > 2 * grid) return launch_few_stream_as<QUANT, OUT_F32, 3>(a, grid, st);
+        // (two batches per row-block, both nearly full, and two row-blocks for nearly every workgroup, or more.  Medians over 12909 products of K =
+        // 4224 to 8192, two buffers' time over three's: up to 1.75 row-blocks per workgroup on average 0.90 - 0.99 (N = 4400 to 4800, K about 6144, M = 1 /
+        // 4: 6.8 / 8.4 us with three, 6.3 / 8.0 with two), from there to two 1.00 up to K = 7168, beyond that 1.01 - 1.02 (N = K = 8192, M = 4: 9.4 us with
+        // two, 8.9 with three); more 0.95 - 1.00 up to K = 7168, beyond that 0.97 - 1.00 with one token and 1.01 - 1.03 with more)
+        if (a.K > 7168 && a.K <= 8192 && 4 * n_rb > 7 * grid && (a.M > 1 || n_rb <= 2 * grid)) return launch_few_stream_as<QUANT, OUT_F32, 3>(a, grid, st);
     }
     return launch_few_stream_as<QUANT, OUT_F32, 2>(a, grid, st);
 }

@@ -164,7 +164,7 @@ def test_mxfp4_few_tokens_take_the_buffers_that_suit_their_walk(host, M, N, K, k
     assert kernel in launch["kernel"], launch
 
 
-@pytest.mark.parametrize("M,N,K,buffers", [(4, 4096, 4096, 1), (1, 4104, 4096, 2), (3, 768, 4224, 2), (4, 2048, 6144, 2), (2, 8192, 8192, 2), (1, 28672, 8192, 2),
+@pytest.mark.parametrize("M,N,K,buffers", [(4, 4096, 4096, 1), (1, 4104, 4096, 2), (3, 768, 4224, 2), (4, 2048, 6144, 2), (2, 7168, 8192, 2), (2, 7176, 8192, 3), (4, 8192, 8192, 3), (1, 8192, 8192, 3), (1, 28672, 8192, 2),
                                            (4, 57344, 7168, 2), (2, 8200, 8192, 3), (4, 28672, 7296, 3), (4, 57344, 8320, 2)])
 def test_fused_linear_takes_the_buffers_that_suit_its_walk(host, M, N, K, buffers):
     (launch,) = host(["device", 0, 256], ["fp4_fused_linear", M, N, K])[1]
