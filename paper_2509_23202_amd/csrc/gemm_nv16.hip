@@ -436,7 +436,10 @@ SplitPlan search_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t m
     }
     if (plan.parts[0] == 1) return plan;
     // Split launches gain from K = 4096 on with half tiles last (M = 320: N = 8192, K = 28672 148 -> 142 us, N = 6144, K = 4096 37 -> 33); below, as often lose.
-    plan.half_row = (M - 1) % 128 < 64 && K >= 4096;
+    // But where the whole tiles' parts are a round of compute units or less and all are more, no unit should have two whole ones (N = 18432, K = 3840, three
+    // parts, M = 129 / 161: 51.9 / 53.2 us in turn, halves last 43.8 / 46.5).
+    const int64_t row_wgs = (plan.narrow ? (N + 127) / 128 : (N + 255) / 256) * plan.parts[0], all = tiles_m * row_wgs;
+    plan.half_row = (M - 1) % 128 < 64 && (K >= 4096 || (all > cus && all - row_wgs <= cus));
     const int64_t cols = (N + 511) / 512, rows = tiles_m - 1;
     plan.rows512 = !plan.narrow && K >= 6656 && tiles_w * plan.parts[0] > cus && tiles_m * cols * plan.parts[0] <= cus;   // (see launch_wide)
     if (!plan.rows512 || !plan.half_row || rows == 0) return plan;

@@ -78,7 +78,7 @@ for req in json.load(sys.stdin):
         s = lib.fp4_gemm(BUF, BUF, BUF, BUF, BUF, BUF, M, N, K, fmt, BUF, WS, room, LAYOUTS, None)
         r = launches()
         assert s == 0, s
-        for l in r: l["ends"] = max(p + n * c * 4 for p, n, c in l.pop("sums")) - WS
+        for l in r: l["ends"] = max(p + n * c * 4 for p, n, c in l["sums"]) - WS
     else:
         M, N, K = a
         s = getattr(lib, what)(BUF, M, K, 32, BUF, BUF, N, 0, BUF, 16, None)
@@ -175,3 +175,12 @@ def test_fused_linear_takes_the_buffers_that_suit_its_walk(host, M, N, K, buffer
 def test_mxfp4_tiles_and_parts_of_long_and_narrow_layers(host, M, N, K, tile, parts):
     runs = host(["device", 0, 256], ["gemm", M, N, K, MX, 1 << 30])[1]
     assert f"gemm_mx_kernelILi{tile[0]}ELi{tile[1]}E" in runs[0]["kernel"] and runs[0]["grid"][1] == parts and len(runs) == (2 if parts > 1 else 1), runs
+
+
+@pytest.mark.parametrize("M,N,K,last", [(134, 18560, 3840, 6), (161, 18432, 3840, 33), (642, 1368, 2048, 2), (129, 12352, 3968, 1), (320, 8192, 8192, 64), (520, 1368, 2048, 0), (520, 1368, 3072, 0)])
+def test_nvfp4_parts_with_their_half_tiles_last(host, M, N, K, last):
+    """Split runs hand out the tiles of a last row of at most 64 tokens last, as half tiles: from K = 4096 on, and below it where all whole
+    tiles' parts are a workgroup for every compute unit or less, and the half ones' come on top."""
+    full = host(["bytes", OP_SPLIT, M, N, K, NV])[0]
+    runs = host(["device", 0, 256], ["gemm", M, N, K, NV, full])[1]
+    assert "nv16_reduce" in runs[-1]["kernel"] and runs[-1]["sums"][1][2] == last * N

@@ -702,6 +702,19 @@ def test_gemm_nvfp4_split_k(fp4, oracle, M, N, K, out_f32):
         assert np.all(err <= tol), (name, float((err / (1e-3 * S + 1e-300)).max()))
 
 
+@pytest.mark.parametrize("M,N,K", [(134, 18560, 3840), (129, 12358, 3968), (642, 1368, 2048)])
+def test_gemm_nvfp4_parts_of_a_short_k_with_half_tiles_last(fp4, M, N, K):
+    """K below 4096: a few tokens in a last row of tiles whose parts come on top of a round of the chip, against the fp64 product of the decoded operands."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    ops = [fp4.fp4_rotate_quantize(torch.randn(n, K, device="cuda", generator=g).to(torch.bfloat16), 16, NV) for n in (M, N)]
+    a, w = (fp4.fp4_dequantize(*q, n, K, NV, flags=fp4.OUT_F32).double() for q, n in zip(ops, (M, N)))
+    Y, S = a @ w.t(), a.abs() @ w.abs().t()
+    out = fp4.fp4_gemm(*ops[0], *ops[1], M, N, K, NV, flags=fp4.OUT_F32)
+    assert bool(((out.double() - Y).abs() <= 1e-3 * S).all())
+
+
 @pytest.mark.parametrize("M,N,K", [(320, 8190, 8192), (192, 4200, 28672), (400, 6200, 8192), (160, 16384, 8192)])
 def test_gemm_nvfp4_parts_that_suit_half_tiles(fp4, M, N, K):
     """A last row of at most 64 tokens in fewer parts than the whole tiles above it: against the fp64 product of the decoded operands, and with
