@@ -499,8 +499,8 @@ void launch_splitk_reduce(const float* partial, int splits, int64_t mn, float al
     else hipLaunchKernelGGL((splitk_reduce_kernel<false, V>), grid, dim3(256), 0, st, partial, splits, mn, alpha, out);
 }
 
-// the tile shapes that have a split-K instantiation: the small ones, and 128 x 128 with four stages
-constexpr bool tile_splits(int bm, int bn, int stages) { return (bm <= 96 && bn <= 128) || (bm == 128 && bn == 128 && stages == 4); }
+// the tile shapes that have a split-K instantiation: the small ones, and with four stages 128 x 128, 256 x 128 and 256 x 256
+constexpr bool tile_splits(int bm, int bn, int stages) { return (bm <= 96 && bn <= 128) || (stages == 4 && ((bm == 128 && bn == 128) || (bm == 256 && bn != 192))); }
 
 // splits > 1: every tile is computed by `splits` workgroups, split y taking K-steps y * split_steps .. and writing its
 // fp32 partial tile to slice y of `partial`; the caller then runs splitk_reduce_kernel
@@ -606,8 +606,12 @@ constexpr TileCost kTileCosts[] = {
     {9, 96, 128, 1, 1.679, 0.182, 0.064, 2.467, 0.408},
     {12, 96, 64, 1, 2.334, 0.153, 0.006, 1.770, 0.000},
 };
-// 128 x 128 tiles in parts, priced from such runs
-constexpr TileCost kSplit128 = {2, 128, 128, 2, 3.260, 0.317, 0.268, 0.809, 0.000, 1.638, 0.246, 0.260};
+// larger tiles in parts, priced from such runs
+constexpr TileCost kSplitCosts[] = {
+    {2, 128, 128, 2, 2.862, 0.331, 0.261, 0.302, 0.000, 1.141, 0.250, 0.277},
+    {5, 256, 128, 1, 8.639, 0.122, 0.338, 0.000, 0.000},
+    {10, 256, 256, 1, 7.046, 0.499, 0.323, 0.000, 0.000},
+};
 
 double tile_cost(const TileCost& c, int64_t tiles, int64_t kt, bool ragged, int cus)
 {
@@ -630,9 +634,9 @@ bool may_split(int64_t M, int64_t K) { return M > 64 && K >= 32 * 128; }
 // Every tile's K range can then be cut into up to eight parts of at least 16 K-steps (whole scale batches of eight), each part one
 // workgroup of as many tiles.  Priced as as many tiles of as many steps, which share their start, and 3.8 us + bytes at 4.3 TB/s (written and
 // read) for the partials and their sum's launch; a split has to win 4 %.  Of 2208 products with K from 4096 to 28672, parts of up to 96 rows
-// were the best way in 749, 1.26 times as fast as the best unsplit one on average.  Parts of 128 x 128, two workgroups to a compute unit, are where more
-// than half the units have a small tile and none could have a second part of one (M = 119, N = 8320, K = 24576: 39.6 us in three parts, unsplit
-// 64 x 128 52.2): 44 of 32735 products, at 0.905 of their time on average.
+// were the best way in 749, 1.26 times as fast as the best unsplit one on average.  Parts of larger tiles are where more than half the units have a small
+// tile and none could have a second part of one, K >= 16384 mostly (three parts of 128 x 128, M = 119, N = 8320, K = 24576: 39.6 us, unsplit 64 x 128 52.2; four of
+// 256 x 128, M = 230, N = 6248, K = 26752: 41.7, 49.0; three of 256 x 256, M = 220, N = 17152, K = 28416: 90, unsplit 256 x 128 104).
 MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room)
 {
     MxPlan p{0, 1, 0};
@@ -681,7 +685,7 @@ MxPlan plan_mx(int64_t M, int64_t N, int64_t K, size_t room)
     };
     for (const TileCost& c : kTileCosts)
         if (c.bm <= 96 && c.bn <= 128) parts(c, 0.811, 3.83, 0.467);
-    parts(kSplit128, 1.0, 8.04, 0.200);
+    for (const TileCost& c : kSplitCosts) parts(c, 1.0, 8.55, 0.205);
     return p;
 }
 
@@ -715,12 +719,12 @@ hipError_t launch_gemm_mxfp4(const void* a_codes, const void* a_scales, const vo
         case 2: return launch_variant<128, 128, 64, 64, 4>(g, out_f32, st, splits, split_steps, pp);
         case 3: return launch_variant<64, 256, 64, 64, 4>(g, out_f32, st);
         case 4: return launch_variant<64, 128, 32, 64, 8>(g, out_f32, st, splits, split_steps, pp);
-        case 5: return launch_variant<256, 128, 64, 64, 4>(g, out_f32, st);
+        case 5: return launch_variant<256, 128, 64, 64, 4>(g, out_f32, st, splits, split_steps, pp);
         case 6: return launch_variant<192, 128, 48, 64, 4>(g, out_f32, st);
         case 7: return launch_variant<160, 128, 80, 64, 4>(g, out_f32, st);
         case 8: return launch_variant<192, 256, 96, 64, 4>(g, out_f32, st);
         case 9: return launch_variant<96, 128, 48, 64, 8>(g, out_f32, st, splits, split_steps, pp);
-        case 10: return launch_variant<256, 256, 64, 128, 4, 3>(g, out_f32, st);
+        case 10: return launch_variant<256, 256, 64, 128, 4, 3>(g, out_f32, st, splits, split_steps, pp);
         case 11: return launch_variant<256, 256, 64, 128, 4, 3, true>(g, out_f32, st);
         case 12: return launch_variant<96, 64, 48, 32, 8, 1>(g, out_f32, st, splits, split_steps, pp);
         case 13: return launch_variant<256, 192, 64, 96, 4, 2>(g, out_f32, st);

@@ -171,7 +171,8 @@ def test_fused_linear_takes_the_buffers_that_suit_its_walk(host, M, N, K, buffer
     assert f"gemm_few_stream_kernelILb1ELb0ELi{buffers}E" in launch["kernel"], launch
 
 
-@pytest.mark.parametrize("M,N,K,tile,parts", [(119, 8320, 24576, (128, 128), 3), (108, 8570, 27136, (128, 128), 3), (201, 4096, 14336, (64, 128), 2), (201, 6144, 4096, (64, 128), 1)])
+@pytest.mark.parametrize("M,N,K,tile,parts", [(119, 8320, 24576, (128, 128), 3), (108, 8570, 27136, (128, 128), 3), (230, 6248, 26752, (256, 128), 4),
+                                               (201, 8190, 28672, (256, 128), 4), (220, 17152, 28416, (256, 256), 3), (201, 4096, 14336, (64, 128), 2), (201, 6144, 4096, (64, 128), 1)])
 def test_mxfp4_tiles_and_parts_of_long_and_narrow_layers(host, M, N, K, tile, parts):
     runs = host(["device", 0, 256], ["gemm", M, N, K, MX, 1 << 30])[1]
     assert f"gemm_mx_kernelILi{tile[0]}ELi{tile[1]}E" in runs[0]["kernel"] and runs[0]["grid"][1] == parts and len(runs) == (2 if parts > 1 else 1), runs

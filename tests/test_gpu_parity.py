@@ -736,8 +736,8 @@ def test_gemm_nvfp4_parts_that_suit_half_tiles(fp4, M, N, K):
         assert bool(((out.double() - Y).abs() <= 1e-3 * S).all()), nbytes
 
 
-@pytest.mark.parametrize("M,N,K", [(119, 8320, 24576), (108, 8570, 27136)])
-def test_gemm_mxfp4_128x128_tiles_in_parts(fp4, M, N, K):
+@pytest.mark.parametrize("M,N,K", [(119, 8320, 24576), (108, 8570, 27136), (230, 6248, 26752), (201, 8190, 28672), (220, 17152, 28416)])
+def test_gemm_mxfp4_larger_tiles_in_parts(fp4, M, N, K):
     """A layer with a small tile for more than half of the compute units and K enough for parts of larger ones: whole and ragged tile columns, parts
     of different lengths; against the fp64 product of the decoded operands."""
     import torch
@@ -746,7 +746,7 @@ def test_gemm_mxfp4_128x128_tiles_in_parts(fp4, M, N, K):
     ops = [fp4.fp4_rotate_quantize(torch.randn(n, K, device="cuda", generator=g).to(torch.bfloat16), 32, MX, flags=fp4.LAYOUT_GEMM) for n in (M, N)]
     a, w = (fp4.fp4_dequantize(*q, n, K, MX, flags=fp4.OUT_F32 | fp4.LAYOUT_GEMM).double() for q, n in zip(ops, (M, N)))
     Y, S = a @ w.t(), a.abs() @ w.abs().t()
-    say(f"gemm 128x128 parts M={M} N={N} K={K}")
+    say(f"gemm parts of larger tiles M={M} N={N} K={K}")
     for flags in (0, fp4.OUT_F32):
         out = fp4.fp4_gemm(*ops[0], *ops[1], M, N, K, MX, flags=flags | fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM)
         assert bool(((out.double() - Y).abs() <= 1e-3 * S + (0 if flags else 1) * Y.abs() * 2.0 ** -8).all())
