@@ -726,10 +726,12 @@ bool try_two_row_blocks(const SkinnyArgs& g, bool out_f32, hipStream_t st, hipEr
     // nearly whole rounds of the chip.  Two -> four, us, M = 40 / 64: N = 16384, K = 8192 (a round) 24.2 / 29.3 -> 20.4 / 23.7; 0.875 of
     // two, four and one: N = 28672, K = 4096 25.3 / 31.1 -> 23.3 / 26.6, N = 57344, K = 8192 76.4 / 95.8 -> 73.4 / 82.2, N = 14336, K = 4096 14.7 / 17.5 ->
     // 12.8 / 14.8; 0.83 of three, N = 40960, K = 5120 37.8 / 48.7 -> 38.2 / 43.4 on one card, 40.0 / 46.1 on another, a layer with N = 40192, K = 6016, M = 61 2 % slower; 0.75 of two, N = 24576, K = 4096 21.3 / 25.8 -> 22.2 / 25.9.
+    // Of 192 products from 0.85 of whole rounds on, 0.84 of the time with one round, 0.90 with more; slower were only K <= 2048 below 0.875 of several rounds (N =
+    // 56400, K = 1024, M = 57 20.8 -> 22.3; N = 28456, K = 1280, M = 41 12.7 -> 13.4), so those need 0.9.
     // (Two token blocks: 0.9 - 1.25 of the time.  With the loads of the next position ahead the registers of the second set cost more.)
     if constexpr (FMT == 1 && MT >= 3) {
         const int wgs4 = (n_rb + 3) / 4, rounds = (wgs4 + stream_cus() - 1) / stream_cus();
-        if (20 * wgs4 >= 17 * rounds * stream_cus()) {
+        if (20 * wgs4 >= (g.K <= 2048 && rounds > 1 ? 18 : 17) * rounds * stream_cus()) {
             const dim3 grid4((unsigned)wgs4), block4(kSkinnyWaves * 64);
             if (out_f32) hipLaunchKernelGGL((gemm_skinny_nt_kernel<FMT, 4, MT, true>), grid4, block4, 0, st, g);
             else hipLaunchKernelGGL((gemm_skinny_nt_kernel<FMT, 4, MT, false>), grid4, block4, 0, st, g);

@@ -185,3 +185,9 @@ def test_nvfp4_parts_with_their_half_tiles_last(host, M, N, K, last):
     full = host(["bytes", OP_SPLIT, M, N, K, NV])[0]
     runs = host(["device", 0, 256], ["gemm", M, N, K, NV, full])[1]
     assert "nv16_reduce" in runs[-1]["kernel"] and runs[-1]["sums"][1][2] == last * N
+
+
+@pytest.mark.parametrize("M,N,K,blocks", [(57, 56400, 1024, 2), (41, 28456, 1280, 2), (57, 59008, 1024, 4), (41, 28456, 2176, 4), (33, 14344, 128, 4), (64, 13824, 8320, 2), (32, 16384, 8320, 2)])
+def test_nvfp4_33_to_64_tokens_row_blocks_per_workgroup(host, M, N, K, blocks):
+    (launch,) = host(["device", 0, 256], ["gemm", M, N, K, NV, 0])[1]
+    assert f"gemm_skinny_nt_kernelILi1ELi{blocks}E" in launch["kernel"], launch
