@@ -77,7 +77,8 @@ enum {
 
 /* operation selector for fp4_workspace_bytes */
 enum { FP4MR_OP_ROTATE_QUANTIZE = 0, FP4MR_OP_QUANTIZE_WEIGHTS = 1, FP4MR_OP_GEMM = 2, FP4MR_OP_GPTQ = 3, FP4MR_OP_GPTQ_PREPARE = 4, FP4MR_OP_GPTQ_HESSIAN = 5,
-       FP4MR_OP_GEMM_SPLIT_K = 6 /* fp4_gemm with room for split-K partials: see fp4_gemm's workspace */ };
+       FP4MR_OP_GEMM_SPLIT_K = 6 /* fp4_gemm with room for split-K partials: see fp4_gemm's workspace */,
+       FP4MR_OP_GEMM_FASTEST = 7 /* whichever of the two sizes makes fp4_gemm the faster */ };
 
 /*
  * Online rotation + quantization of activations: codes, scales = Q(X H_b)   (Section 4.2 item 1: rotation
@@ -203,6 +204,9 @@ fp4mr_status_t fp4_quantize_weights(const void* w, int64_t N, int64_t K, int had
  *                output tiles and a long K -- 65 to a few hundred tokens against a narrow layer -- is split along K
  *                over otherwise idle compute units (with less room, in fewer parts where those still gain) and the partial results are added in a fixed order (deterministic;
  *                the fp32 sums are grouped per split, so the result can differ from the unsplit one in its last bits).
+ *                NVFP4: a call with room for partials runs in parts wherever there is a plan for it.  With FP4MR_OP_GEMM's bytes most products of more than 32 tokens
+ *                go to a kernel that needs no parts, often the faster way; FP4MR_OP_GEMM_FASTEST asks for the one size or the other accordingly (MXFP4: always
+ *                for FP4MR_OP_GEMM_SPLIT_K's).
  */
 fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* a_tensor_scale,
                         const void* w_codes, const void* w_scales, const float* w_tensor_scale,

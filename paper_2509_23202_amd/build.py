@@ -21,7 +21,7 @@ CSRC = HERE / "csrc"
 BUILD = HERE / "_build"
 LIB = HERE / "libfp4mr.so"
 CALLS = HERE / "_calls.so"
-SOURCES = ["api.hip", "rotate_quantize.hip", "gemm_mxfp4.hip", "gemm_nvfp4.hip", "gemm_nv16.hip", "gemm_skinny.hip", "gemm_fused_decode.hip", "repack.hip", "gptq.hip", "gptq_prepare.hip", "gptq_hessian.hip", "probes.hip", "dequantize.hip"]
+SOURCES = ["api.hip", "rotate_quantize.hip", "gemm_mxfp4.hip", "gemm_nvfp4.hip", "gemm_nv16.hip", "gemm_nv_codes.hip", "gemm_skinny.hip", "gemm_fused_decode.hip", "repack.hip", "gptq.hip", "gptq_prepare.hip", "gptq_hessian.hip", "probes.hip", "dequantize.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed-fp32 instruction selection is switched off for all device code (a device-only target feature; the host
@@ -37,7 +37,8 @@ EXTRA_FLAGS = {"rotate_quantize.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "gemm_fused_decode.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                # (dequantized fragments come out of the vector ALU: as MFMA operands they should stay in vector registers)
                "gemm_nvfp4.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-               "gemm_nv16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+               "gemm_nv16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "gemm_nv_codes.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> Path:

@@ -237,8 +237,13 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
     }
     MxPlan plan{variant, 1, 0};
     if (fmt == FP4MR_MXFP4 && variant == 0) plan = plan_mx(M, N, K, partial_room);
+    // (a caller who gives NVFP4 room for parts gets a product in parts where the plan has any)
+    int tile = -1;
+    if (fmt == FP4MR_NVFP4 && variant == 0 && !(partial && !gemm_nv_streams(M, N, K) && nv16_splits(M, N, K, partial_room))) tile = plan_nv_codes(M, N, K, 0);
     const bool few = fmt == FP4MR_MXFP4 ? plan.variant == 0 : variant == 0 && gemm_nv_streams(M, N, K);
-    if (few)
+    if (tile >= 0)
+        e = launch_gemm_nv_codes(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, tile, st);
+    else if (few)
         e = launch_gemm_skinny(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, (int)fmt, out, out_f32, alpha, st);
     else if (fmt == FP4MR_MXFP4)
         e = launch_gemm_mxfp4(a_codes, a_scales, w_codes, w_scales, M, N, K, out, out_f32, plan, alpha, partial, st);
@@ -329,7 +334,7 @@ size_t fp4_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, fp4mr_fmt_t 
     if (op == FP4MR_OP_GPTQ_HESSIAN) return (M > 0 && K > 0) ? align256((size_t)M * K * 4) : 0;
     if (op == FP4MR_OP_GPTQ_PREPARE) return K > 0 ? gptq_prepare_workspace_bytes(K) : 0;
     if (op == FP4MR_OP_GPTQ) return (M > 0 && K > 0) ? align256(quant_workspace(fmt, flags)) + gptq_workspace_bytes(M, K) : 0;
-    if (op == FP4MR_OP_GEMM || op == FP4MR_OP_GEMM_SPLIT_K) {
+    if (op == FP4MR_OP_GEMM || op == FP4MR_OP_GEMM_SPLIT_K || op == FP4MR_OP_GEMM_FASTEST) {
         if (M <= 0 || N <= 0 || K <= 0 || K % 128 != 0) return 0;
         size_t n = 0;
         if (!(flags & FP4MR_A_LAYOUT_GEMM)) n += repack_bytes(M, K, fmt);
@@ -337,7 +342,8 @@ size_t fp4_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, fp4mr_fmt_t 
         // NVFP4 with more than 64 tokens: the activations are dequantized once to fp16 (2 bytes per element)
         if (fmt == FP4MR_NVFP4 && !gemm_nv_streams(M, N, K)) n += align256(nv16_workspace_bytes(M, K));
         // what fp4_gemm needs, plus -- optional -- the fp32 partials of a split-K run where the shape has one
-        if (op == FP4MR_OP_GEMM_SPLIT_K) {
+        // (FP4MR_OP_GEMM_FASTEST: only where it is estimated to be the faster way)
+        if (op == FP4MR_OP_GEMM_SPLIT_K || (op == FP4MR_OP_GEMM_FASTEST && !(fmt == FP4MR_NVFP4 && plan_nv_codes(M, N, K, 0) >= 0 && plan_nv_codes(M, N, K, SIZE_MAX) >= 0))) {
             const size_t extra = fmt == FP4MR_MXFP4 ? gemm_mx_split_k_bytes(M, N, K) : gemm_nv_streams(M, N, K) ? 0 : nv16_split_k_bytes(M, N, K);
             if (extra) n = align256(n) + extra;
         }

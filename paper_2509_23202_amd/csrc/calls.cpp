@@ -132,7 +132,7 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n)
         Py_RETURN_NONE;
     const at::Tensor out = empty({M, N}, flags & FP4MR_OUT_F32 ? at::kFloat : at::kBFloat16, *ac);
     at::Tensor workspace;
-    const size_t need = entry.workspace_bytes(FP4MR_OP_GEMM_SPLIT_K, M, N, K, (fp4mr_fmt_t)fmt, (uint32_t)flags);
+    const size_t need = entry.workspace_bytes(FP4MR_OP_GEMM_FASTEST, M, N, K, (fp4mr_fmt_t)fmt, (uint32_t)flags);
     if (need) workspace = empty({(int64_t)need}, at::kByte, *ac);
     void *const pac = pointer(ac), *const pas = pointer(as), *const pwc = pointer(wc), *const pws = pointer(ws), *const po = out.data_ptr();
     float *const pat = static_cast<float*>(pointer(at_)), *const pwt = static_cast<float*>(pointer(wt));

@@ -491,24 +491,38 @@ hipError_t launch_kernel(const Nv16Args& g, unsigned workgroups, hipStream_t st)
 
 // (g.parts[0] == 0: tiles are not split)
 template <int NW, int TN, int STAGES>
-hipError_t launch_tiles(const Nv16Args& g0, bool out_f32, hipStream_t st)
+hipError_t launch_tiles(const Nv16Args& g, bool out_f32, hipStream_t st)
 {
-    Nv16Args g = g0;
     constexpr int BN = NW * TN * 16;
-    if (g.n_cols <= 0) return hipSuccess;
     const int tiles_n = (g.n_cols + BN - 1) / BN;
     if (g.parts[0]) {
         const int n = tiles_n * ((g.tiles_m - g.half_row) * g.parts[0] + g.half_row * g.parts[1]);
         return launch_kernel<NW, TN, STAGES, true, true>(g, (unsigned)n, st);
     }
-    if (g.half_row) {
-        // Half tiles go last where that evens out the launch's end or gives every compute unit one whole tile at most.  Else the launch takes
-        // the time of whole tiles, and all of them in turn leave an XCD its rows of X (K = 2048, N = 12288, M = 960: 58 us, halves last 61.5).
-        const int64_t all = (int64_t)g.tiles_m * tiles_n, cus = device_cus();
-        g.half_row = all > 2 * cus || (all > cus && all - tiles_n <= cus) ? 1 : 0;
-    }
     const unsigned n = (unsigned)(g.tiles_m * tiles_n);
     return out_f32 ? launch_kernel<NW, TN, STAGES, true, false>(g, n, st) : launch_kernel<NW, TN, STAGES, false, false>(g, n, st);
+}
+
+hipError_t launch_width(int width, const Nv16Args& g, bool out_f32, hipStream_t st)
+{
+    return width == 512 ? launch_tiles<8, 4, 3>(g, out_f32, st) : width == 128 ? launch_tiles<4, 2, 3>(g, out_f32, st) : launch_tiles<4, 4, 3>(g, out_f32, st);
+}
+
+// one launch of the product: columns n_first .. n_first + n_cols - 1 in tiles of `width`, the last row's half tiles behind all others or not
+struct Nv16Launch {
+    int width, n_first, n_cols, half_row;
+};
+
+Nv16Launch of_width(int width, int64_t first, int64_t cols, int64_t tiles_m, bool half_row, int64_t cus)
+{
+    Nv16Launch l{width, (int)first, (int)cols, 0};
+    if (half_row) {
+        // Half tiles go last where that evens out the launch's end or gives every compute unit one whole tile at most.  Else the launch takes
+        // the time of whole tiles, and all of them in turn leave an XCD its rows of X (K = 2048, N = 12288, M = 960: 58 us, halves last 61.5).
+        const int64_t tiles_n = (cols + width - 1) / width, all = tiles_m * tiles_n;
+        l.half_row = all > 2 * cus || (all > cus && all - tiles_n <= cus) ? 1 : 0;
+    }
+    return l;
 }
 
 // Tile columns of 256 (or wider).  Two workgroups of 128 x 256 share a compute unit, and one's epilogue runs under the other's
@@ -520,13 +534,12 @@ hipError_t launch_tiles(const Nv16Args& g0, bool out_f32, hipStream_t st)
 // 512 columns took 0.95 - 1.02 of the pairs' time (M = 419, N = 24064, K = 8576: 180 -> 171 us), on 47 below it 0.98 - 1.11
 // (M = 451, N = 25992, K = 1536: 54 against 60).
 // Three stages either way: a fourth for the 512 columns measured 1 % slower.
-hipError_t launch_wide(const Nv16Args& g, bool out_f32, hipStream_t st)
+Nv16Launch wide(int64_t first, int64_t cols, int64_t tiles_m, bool half_row, int64_t K, int64_t cus)
 {
-    const int64_t rows = g.tiles_m, cus = device_cus();
     // (a compute unit that gets one whole tile and one of half the rows is done sooner as a pair: M = 192, N = 57344, K = 8192 163 -> 153 us)
-    const bool pairs = g.half_row && (g.tiles_m - 1) * (int64_t)((g.n_cols + 255) / 256) <= cus;
-    if (!pairs && g.K >= 6656 && rows * ((g.n_cols + 255) / 256) > cus && rows * ((g.n_cols + 511) / 512) <= cus) return launch_tiles<8, 4, 3>(g, out_f32, st);
-    return launch_tiles<4, 4, 3>(g, out_f32, st);
+    const bool pairs = half_row && (tiles_m - 1) * ((cols + 255) / 256) <= cus;
+    const bool rows512 = !pairs && K >= 6656 && tiles_m * ((cols + 255) / 256) > cus && tiles_m * ((cols + 511) / 512) <= cus;
+    return of_width(rows512 ? 512 : 256, first, cols, tiles_m, half_row, cus);
 }
 
 // Estimated time of a launch, microseconds per K-step: `whole` tiles and behind them `half` ones (of at most 64 tokens), wide or narrow.
@@ -544,7 +557,46 @@ double nv16_tiles_cost(int64_t whole, int64_t half, bool narrow, int64_t cus)
     return t + shared + ((double)half * part > (double)(slots - left) ? part * alone : 0.0);
 }
 
-hipError_t launch_narrow(const Nv16Args& g, bool out_f32, hipStream_t st) { return launch_tiles<4, 2, 3>(g, out_f32, st); }
+// The product in one piece along K: one launch or two.  Two workgroups per compute unit: a round of the chip is 2 * CUs tiles.  The tile columns that
+// fill whole rounds run as 128 x 256 tiles; what is left over runs as 128 x 128 tiles in a second launch when that fits it
+// into fewer rounds-worth of time (N = 10240 at M = 4096: 1280 wide tiles are two and a half rounds; 1024 of them
+// plus 512 narrow ones are two and a half rounds' worth of work in two and a half rounds' time).
+int plan_whole(int64_t M, int64_t N, int64_t K, int cus, Nv16Launch (&l)[2])
+{
+    const int64_t tiles_m = (M + 127) / 128;
+    const bool half_row = (M - 1) % 128 < 64;
+    const int64_t slots = 2 * (int64_t)cus;
+    const int64_t cols_w = (N + 255) / 256;                         // wide tile columns
+    const int64_t tiles_w = cols_w * tiles_m;
+    const int64_t full_cols = tiles_w / slots * slots / tiles_m;    // wide tile columns inside whole rounds
+    const int64_t rest_cols = N - full_cols * 256;                  // output columns left over
+    if (full_cols > 0 && full_cols < cols_w) {
+        const int64_t narrow = (rest_cols + 127) / 128 * tiles_m;
+        // time in units of a wide tile: ceil-rounds of wide tiles, against whole rounds + narrow tiles at half a unit each
+        double t_wide = (double)((tiles_w + slots - 1) / slots);
+        double t_split = (double)(full_cols * tiles_m / slots) + 0.5 * (double)((narrow + slots - 1) / slots);
+        if (half_row) {
+            const int64_t whole = tiles_m - 1, cols_n = (rest_cols + 127) / 128, all_n = (N + 127) / 128;
+            t_wide = std::min(nv16_tiles_cost(whole * cols_w, cols_w, false, cus), nv16_tiles_cost(whole * all_n, all_n, true, cus));
+            t_split = nv16_tiles_cost(whole * full_cols, full_cols, false, cus) + nv16_tiles_cost(whole * cols_n, cols_n, true, cus) + 10.0 / (double)(K >> 6);
+        }
+        if (t_split < t_wide) {
+            l[0] = wide(0, full_cols * 256, tiles_m, half_row, K, cus);
+            l[1] = of_width(128, full_cols * 256, rest_cols, tiles_m, half_row, cus);
+            return 2;
+        }
+    }
+    // With a last row of half tiles, which are handed out last and even out the end of the launch, one launch is the better one unless the
+    // narrow tiles of the second fill what the wide ones leave (K, N, M: whole rounds first -> one launch, us: 8192, 57344, 320
+    // 259 -> 247; 8192, 57344, 560 430 -> 416; 4096, 28672, 1080 224 -> 207; 28672, 8192, 1080 narrow 494, wide 466).
+    // Less than a round and a quarter of wide tiles (one per compute unit and a few doubled up, or compute units left
+    // idle): 128 x 128 tiles spread the same work twice as finely (N = 10240, K = 8192 at M = 512: 136 -> 119 us;
+    // N = 8192, K = 28672 at M = 512 without the split-K workspace: 412 -> 280 us).
+    const int64_t cols_n = (N + 127) / 128, whole = tiles_m - 1;
+    const bool narrow = half_row ? nv16_tiles_cost(whole * cols_n, cols_n, true, cus) < nv16_tiles_cost(whole * cols_w, cols_w, false, cus) : nv16_narrow_tiles(tiles_w, cus);
+    l[0] = narrow ? of_width(128, 0, N, tiles_m, half_row, cus) : wide(0, N, tiles_m, half_row, K, cus);
+    return 1;
+}
 
 // the product in parts, and their sums
 hipError_t launch_parts(Nv16Args g, const SplitPlan& plan, bool out_f32, float* partial, hipStream_t st)
@@ -564,7 +616,7 @@ hipError_t launch_parts(Nv16Args g, const SplitPlan& plan, bool out_f32, float* 
         r.count[h] = (h ? g.M - rows0 : rows0) * g.N;
         partial += r.parts[h] * r.count[h];
     }
-    const hipError_t e = plan.rows512 ? launch_tiles<8, 4, 3>(g, out_f32, st) : plan.narrow ? launch_tiles<4, 2, 3>(g, out_f32, st) : launch_tiles<4, 4, 3>(g, out_f32, st);
+    const hipError_t e = launch_width(plan.rows512 ? 512 : plan.narrow ? 128 : 256, g, out_f32, st);
     if (e != hipSuccess) return e;
     const bool vec = g.N % 4 == 0;
     const dim3 grid((unsigned)((g.M * g.N / (vec ? 4 : 1) + 255) / 256));
@@ -588,6 +640,34 @@ size_t nv16_workspace_bytes(int64_t M, int64_t K)
 // bytes of fp32 partials a split-K run of this product needs, where there is room for as many as it likes (0: the product is not split)
 size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K) { return partial_bytes(plan_split_k_nv16(M, N, K, device_cus(), SIZE_MAX), M, N); }
 
+bool nv16_splits(int64_t M, int64_t N, int64_t K, size_t partial_room) { return plan_split_k_nv16(M, N, K, device_cus(), partial_room).parts[0] > 1; }
+
+// Price of the whole call: the fp16 copy of X, the launches of the plan (a half tile counts as 0.62 of a whole one), the sum of the parts.  Fitted to 2263 products with
+// cold weights (M = 65 ... 4096, N = 512 ... 57344, K = 1024 ... 28672), median error 4 %.
+double nv16_us(int64_t M, int64_t N, int64_t K, size_t partial_room)
+{
+    constexpr TileRounds narrow = {2, 9.621, 0.8373, 6.093, 0.3200, 0.1981, 9.981, 0.5480, 0.3470}, wide = {2, 25.06, 1.3711, 8.275, 0.1857, 0.9045, 18.40, 0.9649, 0.5646},
+                         rows512 = {1, 4.879, 1.6131, 15.98, 0.7689, 0.6808};
+    const int cus = device_cus();
+    const int64_t tiles_m = (M + 127) / 128;
+    double us = 4.160 + 0.614e-6 * (double)M * (double)K;
+    auto add = [&](int width, int64_t cols, int64_t half_row, int64_t parts, int64_t half_parts, int64_t steps) {
+        const double tiles_n = (double)((cols + width - 1) / width);
+        us += tile_rounds_us(width == 512 ? rows512 : width == 256 ? wide : narrow, tiles_n * ((double)((tiles_m - half_row) * parts) + 0.62 * (double)(half_row * half_parts)), (double)steps, cus);
+    };
+    SplitPlan p;
+    if (partial_room) p = plan_split_k_nv16(M, N, K, cus, partial_room);
+    if (p.parts[0] > 1) {
+        us += 3.683;
+        add(p.rows512 ? 512 : p.narrow ? 128 : 256, N, p.half_row, p.parts[0], p.parts[1], p.steps[0]);
+        return us;
+    }
+    Nv16Launch l[2];
+    const int n = plan_whole(M, N, K, cus, l);
+    for (int i = 0; i < n; ++i) add(l[i].width, l[i].n_cols, l[i].half_row, 1, 1, K >> 6);
+    return n > 1 ? us + 10.59 : us;
+}
+
 hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                             const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
                             bool out_f32, void* workspace, void* partial, size_t partial_room, hipStream_t st)
@@ -599,10 +679,7 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
 
-    // 2. the product.  Two workgroups per compute unit: a round of the chip is 2 * CUs tiles.  The tile columns that fill
-    // whole rounds run as 128 x 256 tiles; what is left over runs as 128 x 128 tiles in a second launch when that fits it
-    // into fewer rounds-worth of time (N = 10240 at M = 4096: 1280 wide tiles are two and a half rounds; 1024 of them
-    // plus 512 narrow ones are two and a half rounds' worth of work in two and a half rounds' time).
+    // 2. the product
     Nv16Args g{};
     g.x16 = static_cast<const uint8_t*>(workspace);
     g.w_codes = static_cast<const uint8_t*>(w_codes);
@@ -614,52 +691,21 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     g.N = N;
     g.K = K;
     g.tiles_m = (int)((M + 127) / 128);
-    g.half_row = (M - 1) % 128 < 64 ? 1 : 0;
     const int cus = device_cus();
     if (partial) {
         // few tiles, long K: every tile's K range shared by several workgroups, partial results added by a second kernel
         const SplitPlan plan = plan_split_k_nv16(M, N, K, cus, partial_room);
         if (plan.parts[0] > 1) return launch_parts(g, plan, out_f32, static_cast<float*>(partial), st);
     }
-    const int64_t slots = 2 * (int64_t)cus;
-    const int64_t cols_w = (N + 255) / 256;                         // wide tile columns
-    const int64_t tiles_w = cols_w * g.tiles_m;
-    const int64_t full_cols = tiles_w / slots * slots / g.tiles_m;  // wide tile columns inside whole rounds
-    const int64_t rest_cols = N - full_cols * 256;                  // output columns left over
-    if (full_cols > 0 && full_cols < cols_w) {
-        const int64_t narrow = (rest_cols + 127) / 128 * g.tiles_m;
-        // time in units of a wide tile: ceil-rounds of wide tiles, against whole rounds + narrow tiles at half a unit each
-        double t_wide = (double)((tiles_w + slots - 1) / slots);
-        double t_split = (double)(full_cols * g.tiles_m / slots) + 0.5 * (double)((narrow + slots - 1) / slots);
-        if (g.half_row) {
-            const int64_t whole = g.tiles_m - 1, cols_n = (rest_cols + 127) / 128, all_n = (N + 127) / 128;
-            t_wide = std::min(nv16_tiles_cost(whole * cols_w, cols_w, false, cus), nv16_tiles_cost(whole * all_n, all_n, true, cus));
-            t_split = nv16_tiles_cost(whole * full_cols, full_cols, false, cus) + nv16_tiles_cost(whole * cols_n, cols_n, true, cus) + 10.0 / (double)(K >> 6);
-        }
-        if (t_split < t_wide) {
-            g.n_first = 0;
-            g.n_cols = (int)(full_cols * 256);
-            if ((e = launch_wide(g, out_f32, st)) != hipSuccess) return e;
-            g.n_first = (int)(full_cols * 256);
-            g.n_cols = (int)rest_cols;
-            return launch_narrow(g, out_f32, st);
-        }
+    Nv16Launch l[2];
+    const int n = plan_whole(M, N, K, cus, l);
+    for (int i = 0; i < n; ++i) {
+        g.n_first = l[i].n_first;
+        g.n_cols = l[i].n_cols;
+        g.half_row = l[i].half_row;
+        if ((e = launch_width(l[i].width, g, out_f32, st)) != hipSuccess) return e;
     }
-    g.n_first = 0;
-    g.n_cols = (int)N;
-    // With a last row of half tiles, which are handed out last and even out the end of the launch, one launch is the better one unless the
-    // narrow tiles of the second fill what the wide ones leave (K, N, M: whole rounds first -> one launch, us: 8192, 57344, 320
-    // 259 -> 247; 8192, 57344, 560 430 -> 416; 4096, 28672, 1080 224 -> 207; 28672, 8192, 1080 narrow 494, wide 466).
-    if (g.half_row) {
-        const int64_t cols_n = (N + 127) / 128, whole_rows = g.tiles_m - 1;
-        const bool narrow = nv16_tiles_cost(whole_rows * cols_n, cols_n, true, cus) < nv16_tiles_cost(whole_rows * cols_w, cols_w, false, cus);
-        return narrow ? launch_narrow(g, out_f32, st) : launch_wide(g, out_f32, st);
-    }
-    // less than a round and a quarter of wide tiles (one per compute unit and a few doubled up, or compute units left
-    // idle): 128 x 128 tiles spread the same work twice as finely (N = 10240, K = 8192 at M = 512: 136 -> 119 us;
-    // N = 8192, K = 28672 at M = 512 without the split-K workspace: 412 -> 280 us)
-    if (nv16_narrow_tiles(tiles_w, cus)) return launch_narrow(g, out_f32, st);
-    return launch_wide(g, out_f32, st);
+    return hipSuccess;
 }
 
 }  // namespace fp4mr

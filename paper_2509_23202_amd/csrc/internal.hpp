@@ -82,9 +82,38 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
 // split); 0 = not split
 size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K);
 
+// what that takes with partial_room bytes for partials, in microseconds
+double nv16_us(int64_t M, int64_t N, int64_t K, size_t partial_room);
+// whether it runs split with that room
+bool nv16_splits(int64_t M, int64_t N, int64_t K, size_t partial_room);
+
+// What the workgroups of a launch take, microseconds, `steps` of K each: `per_cu` to a compute unit in whole rounds, each (fixed + steps x step), and a last
+// round that is not whole: on units of their own (alone + steps x (alone_step + alone_busy x the share of the units)), or some of them two to a unit.
+struct TileRounds {
+    int per_cu;
+    double fixed, step, alone, alone_step, alone_busy, pair, pair_step, pair_busy;
+};
+inline double tile_rounds_us(const TileRounds& c, double workgroups, double steps, int cus)
+{
+    const double slots = (double)cus * c.per_cu, full = (double)(int64_t)(workgroups / slots), rest = workgroups - full * slots;
+    const double t = full * (c.fixed + steps * c.step);
+    if (rest <= 0.0) return t;
+    if (rest <= cus) return t + c.alone + steps * (c.alone_step + c.alone_busy * rest / cus);
+    return t + c.pair + steps * (c.pair_step + c.pair_busy * (rest - cus) / cus);
+}
+
+// NVFP4 product of 33 tokens and more, both operands dequantized inside it, in one launch without a workspace.  plan: the tile that suits it, or -1 where the few-token
+// kernels or the one above with that room for partials are the better choice.
+int plan_nv_codes(int64_t M, int64_t N, int64_t K, size_t room);
+hipError_t launch_gemm_nv_codes(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes, const void* w_scales, const float* w_ts,
+                                int64_t M, int64_t N, int64_t K, void* out, bool out_f32, int tile, hipStream_t st);
+
 // few-token weight-streaming GEMM, both formats, operands in GEMM layout: every shape up to 64 tokens, and above that those that
 // gemm_nv_streams accepts (NVFP4) and gemm_stream_us prices (MXFP4)
 bool gemm_nv_streams(int64_t M, int64_t N, int64_t K);
+// what they take for an NVFP4 product of more than 16 tokens, in microseconds, where a set of workgroups per 16 tokens does it; 0: they take it, whatever
+// that is; infinity: they do not take it
+double gemm_nv_stream_us(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_skinny(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                               const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, int fmt, void* out,
                               bool out_f32, float alpha, hipStream_t st);

@@ -68,7 +68,7 @@ def main():
                 x = torch.randn(M, K, device="cuda").to(torch.bfloat16)
                 qa = fp4.fp4_rotate_quantize(x, b, fmt, flags=GL)
                 out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
-                ws = torch.empty(max(fp4.workspace_bytes(fp4.OP_GEMM_SPLIT_K, M, N, K, fmt, gfl), 16), dtype=torch.uint8, device="cuda")
+                ws = torch.empty(max(fp4.workspace_bytes(fp4.OP_GEMM_FASTEST, M, N, K, fmt, gfl), 16), dtype=torch.uint8, device="cuda")
                 n = max(12, nc) if M < 1024 else max(6, min(nc, 8))
                 t = graph_us(lambda i: fp4.fp4_gemm(qa[0], qa[1], qa[2], copies[i % nc][0], copies[i % nc][1], qw[2], M, N, K, fmt,
                                                     flags=gfl, out=out, workspace=ws), n)

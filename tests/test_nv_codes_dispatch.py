@@ -1,0 +1,52 @@
+"""Which NVFP4 products go to the kernel that dequantizes both operands in its waves, with which tile, and what a caller's workspace has to do
+with it, as the library's host code decides it (the stand-in for HIP of test_dispatch; no GPU runs)."""
+import pytest
+
+from tests.test_dispatch import NV, MX, OP_GEMM, OP_SPLIT, host  # noqa: F401  (host: the fixture)
+
+OP_FASTEST = 7
+# tile (token blocks, column blocks, waves on the same tokens, groups that share K): shapes that it is the cheapest for
+SHAPES = {
+    (2, 2, 1, 8): [(350, 76, 128), (273, 71, 256), (424, 60, 384), (302, 68, 640), (514, 95, 1664)],
+    (2, 4, 1, 8): [(489, 572, 640), (345, 758, 768), (545, 485, 1664), (518, 557, 2944)],
+    (4, 4, 1, 8): [(100, 6261, 1920), (49, 9436, 1664), (52, 8387, 2944)],
+    (3, 4, 1, 4): [(65, 3326, 256), (65, 3152, 128), (594, 432, 1408), (65, 5571, 768), (133, 3658, 2944)],
+    (4, 4, 1, 4): [(99, 5764, 128), (107, 5469, 256), (103, 5496, 384), (49, 8631, 1152)],
+    (5, 4, 1, 4): [(66, 8720, 128), (129, 6126, 256), (66, 8772, 384), (71, 8270, 1152)],
+    (6, 4, 1, 4): [(81, 8568, 128), (278, 4907, 256), (86, 8752, 384), (274, 4237, 1152)],
+    (7, 4, 2, 2): [(132, 11144, 128), (217, 8394, 256), (525, 5452, 384), (295, 8998, 1152)],
+    (8, 4, 2, 2): [(585, 5384, 128), (342, 8250, 256), (456, 7036, 384), (576, 5573, 1152)],
+}
+
+
+def kernel(tile):
+    return "gemm_nv_codes_kernelI" + "".join(f"Li{v}E" for v in tile)
+
+
+@pytest.mark.parametrize("tile", list(SHAPES))
+def test_tiles_of_products_in_one_launch(host, tile):
+    for M, N, K in SHAPES[tile]:
+        need = host(["bytes", OP_GEMM, M, N, K, NV])[0]
+        (launch,) = host(["device", 0, 256], ["gemm", M, N, K, NV, need])[1]
+        assert kernel(tile) in launch["kernel"], (M, N, K, launch)
+        columns = 16 * tile[1] * tile[2]
+        assert launch["grid"][0] == -(-M // (16 * tile[0])) * -(-N // columns)
+
+
+@pytest.mark.parametrize("M,N,K", [(192, 4096, 4096), (320, 8192, 8192), (600, 520, 2048), (320, 8192, 28672), (128, 28672, 4096), (33, 57344, 8192), (640, 2048, 2048), (2048, 57344, 8192), (16, 8192, 8192)])
+def test_the_fastest_size_is_one_of_the_two_and_room_for_parts_means_parts(host, M, N, K):
+    need, split, fastest = host(["device", 0, 256], *(["bytes", op, M, N, K, NV] for op in (OP_GEMM, OP_SPLIT, OP_FASTEST)))[1:]
+    assert fastest in (need, split)
+    runs = host(["device", 0, 256], ["gemm", M, N, K, NV, split])[1]
+    if split > need:
+        assert "nv16_reduce" in runs[-1]["kernel"]
+    if fastest < split:   # the kernel that the size is for
+        assert "gemm_nv_codes" in host(["device", 0, 256], ["gemm", M, N, K, NV, fastest])[1][0]["kernel"]
+    if M <= 32:
+        assert not any("gemm_nv_codes" in r["kernel"] for r in runs)
+
+
+@pytest.mark.parametrize("M,N,K", [(201, 4096, 14336), (128, 4096, 28672), (64, 4096, 4096)])
+def test_mxfp4_is_always_fastest_with_room_for_parts(host, M, N, K):
+    split, fastest = host(["device", 0, 256], *(["bytes", op, M, N, K, MX] for op in (OP_SPLIT, OP_FASTEST)))[1:]
+    assert fastest == split
