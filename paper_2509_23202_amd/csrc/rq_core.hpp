@@ -84,8 +84,9 @@ struct GroupQuant {
     // lane of a group takes the same decision.  Hardware converts only (encode and decode).
     typedef float v2f_t __attribute__((ext_vector_type(2)));
 
-    // codes of 8 values at scale `sc` (E8M0 in the exponent field) and the squared error they leave
-    __device__ static __forceinline__ uint32_t try8(const float (&t)[8], float sc, float mul, float& err)
+    // codes of the 8 values t at scale `sc` (E8M0 in the exponent field), and the squared error that they leave in
+    // y = t mul: one fma for y - q mul (its product exact) and one for the square
+    __device__ static __forceinline__ uint32_t try8(const float (&t)[8], const float* y, float sc, float mul, float& err)
     {
         uint32_t p = 0;
         p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, t[0], t[1], sc, 0);
@@ -99,8 +100,8 @@ struct GroupQuant {
         const float q[8] = {q0[0], q0[1], q1[0], q1[1], q2[0], q2[1], q3[0], q3[1]};
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const float d = t[i] - q[i];
-            err = __fmaf_rn(d * mul, d * mul, err);
+            const float d = __fmaf_rn(-q[i], mul, y[i]);
+            err = __fmaf_rn(d, d, err);
         }
         return p;
     }
@@ -135,7 +136,7 @@ struct GroupQuant {
                     float t[8];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) t[i] = y[gi * VG + d * 8 + i];
-                    cand[d] = try8(t, scf, 1.0f, err);
+                    cand[d] = try8(t, t, scf, 1.0f, err);
                 }
                 err = group_sum(err);
                 if (k == 0 || err < best_err) {
@@ -155,7 +156,9 @@ struct GroupQuant {
     // octave above it (the scale that puts the largest element on 4 instead of 6), so the window is c0 - 2 .. c0 + 7,
     // tried in the order c0, +1, -1, +2, -2, +3, +4, +5, +6, +7 (a brute force over every code finds the global minimiser
     // inside this window in all but about 1e-4 of the groups of heavy-tailed data; within +-1 in only half of them).
-    // Bound: the vector ALU, some 60 instructions for a candidate's eight values, eight of them conversions.  `steps` holds every code's step
+    // Bound: the vector ALU, some 45 instructions for a candidate's eight values, eight of them conversions.  (The error as
+    // ((y r - q) d)^2 takes two multiplications and a subtraction where y - q d is one fma: [8191, 8192] with the search 183 -> 173 us,
+    // with the fitted tensor scale 611 -> 563, and it is the closer one: q d has no rounding of its own.)  `steps` holds every code's step
     // s_T s_G and its reciprocal (nv_steps); a division per candidate, and the test for a zero step in every one, took a sixth of the
     // search.  (A group's two sums added with v_permlane16_swap instead of a shuffle through LDS: 5 % slower, LDS is idle here.)
     __device__ static __forceinline__ void nv_mse(const float (&y)[NO], float s_T, const v2f_t* steps, uint32_t (&out)[ND], uint32_t (&sc)[NG])
@@ -190,7 +193,6 @@ struct GroupQuant {
                     uint32_t cand[VG / 8];
 #pragma unroll
                     for (int dd = 0; dd < VG / 8; ++dd) {
-                        // the error is measured in units of d: (y r - q)^2 d^2 = (y - q d)^2 up to the rounding of y r
                         float t[8];
 #pragma unroll
                         for (int i = 0; i < 8; ++i) t[i] = y[gi * VG + dd * 8 + i] * r;
@@ -199,7 +201,7 @@ struct GroupQuant {
 #pragma unroll
                             for (int i = 0; i < 8; ++i) err = __fmaf_rn(y[gi * VG + dd * 8 + i], y[gi * VG + dd * 8 + i], err);
                         } else {
-                            cand[dd] = try8(t, 1.0f, d, err);
+                            cand[dd] = try8(t, &y[gi * VG + dd * 8], 1.0f, d, err);
                         }
                     }
                     err = group_sum(err);
