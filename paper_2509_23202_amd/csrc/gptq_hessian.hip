@@ -6,7 +6,7 @@
 // something in common most rotated channels are small differences of large sums: with an offset of 100 under unit noise
 // the entries were off by 1 % of that scale, and diagonal entries could come out negative.)
 //   many rows  hessian_pack_kernel   X -> the rotated rows as two fp16 parts, scaled by column, in the workspace as the MFMA takes them
-//              hessian_tile_kernel   X'^T X' on the fp16 MFMA: the three products above 2^-23 of the whole
+//              hessian_pair_kernel   X'^T X' on the fp16 MFMA: the three products above 2^-23 of the whole
 //              hessian_part_kernel   the same for the tiles beyond whole rounds of the chip
 //   few rows   hessian_rotate_kernel X -> the rotated rows in fp32, in the workspace, eight rows of a column side by side
 //              hessian_split_kernel  X'^T X' on the bf16 MFMA, both factors split into three bf16 parts: the six products above
@@ -47,7 +47,8 @@ struct HessArgs {
     int64_t T;
     int K, b, accumulate;
     int nt;             // tiles per side
-    int full;           // tiles 0 .. full - 1 take all of T in one workgroup ...
+    int full;           // tiles (pairs: b > 1, many rows) 0 .. full - 1 take all of T in one workgroup ...
+    bool pairs;
     int parts;          // ... each of the others is shared by this many
     int chunk;          // rows of X per part (multiple of kRows)
     float in_scale, out_scale;  // powers of two: in_scale^2 * out_scale = 1 / b (few rows)
@@ -519,7 +520,7 @@ constexpr int kGroup = 4;           // stages that share their exponents
 // columns halve them among themselves step by step, then the four waves meet in LDS.
 __device__ __forceinline__ void column_exponents(const float (&top)[16], float (*red)[kT], uint8_t* exps)
 {
-    const int tid = threadIdx.x, piece = tid & 7;
+    const int tid = threadIdx.x & 255, piece = tid & 7;
     float m8[8], m4[4], m2[2];
     const bool b3 = tid & 8, b4 = tid & 16, b5 = tid & 32;
 #pragma unroll
@@ -543,18 +544,24 @@ __device__ __forceinline__ void column_ups(const uint8_t* exps, float (&up)[16])
     for (int i = 0; i < 16; ++i) up[i] = pair_up(e[i >> 2] >> 8 * (i & 3) & 255u);
 }
 
+// pair_column of four exponents (14 at least: none borrows)
+__device__ __forceinline__ v4f four_column_factors(uint32_t exps)
+{
+    const uint32_t w = exps - 0x01010101u;
+    return v4f{__uint_as_float((w & 255u) << 23), __uint_as_float((w >> 8 & 255u) << 23), __uint_as_float((w >> 16 & 255u) << 23), __uint_as_float((w >> 24) << 23)};
+}
+
 // what a lane needs of the exponents of 128 rows and 128 columns at `exps`: of row l16 of a block, of columns 4 q .. 4 q + 3 of a block
 __device__ __forceinline__ int row_exponent(const uint8_t* exps, int block) { return exps[block * 16 + (threadIdx.x & 15)]; }
 __device__ __forceinline__ v4f col_factors(const uint8_t* exps, int block)
 {
-    const uint32_t w = *reinterpret_cast<const uint32_t*>(exps + block * 16 + 4 * (threadIdx.x >> 4 & 3));
-    return v4f{pair_column(w & 255u), pair_column(w >> 8 & 255u), pair_column(w >> 16 & 255u), pair_column(w >> 24)};
+    return four_column_factors(*reinterpret_cast<const uint32_t*>(exps + block * 16 + 4 * (threadIdx.x >> 4 & 3)));
 }
 
 // a thread's sixteen values into the stage at dst, its blocks `pitch` bytes apart
 __device__ __forceinline__ void put_row(const float (&v)[16], const float (&up)[16], char* dst, int pitch)
 {
-    const int r = threadIdx.x >> 3, piece = threadIdx.x & 7;
+    const int r = threadIdx.x >> 3 & 31, piece = threadIdx.x & 7;
     _Float16* out = reinterpret_cast<_Float16*>(dst + piece * pitch) + (r >> 3) * 128 + (r & 7);
 #pragma unroll
     for (int i = 0; i < 16; ++i) pair_split(v[i], up[i], out[i * 8], out[i * 8 + 512]);
@@ -596,7 +603,7 @@ __global__ __launch_bounds__(256) void hessian_pack_kernel(HessArgs a)
 __device__ __forceinline__ void build_stage(const HessArgs& a, int64_t t, int c0, char* dst, uint8_t* exps, float (*red)[kT])
 {
     float v[16], top[16], up[16];
-    rotate_row(a, t + (threadIdx.x >> 3), c0 + (threadIdx.x & 7) * 16, v);
+    rotate_row(a, t + (threadIdx.x >> 3 & 31), c0 + (threadIdx.x & 7) * 16, v);
 #pragma unroll
     for (int i = 0; i < 16; ++i) top[i] = fabsf(v[i]);
     column_exponents(top, red, exps);
@@ -678,6 +685,149 @@ __global__ __launch_bounds__(256, 2) void hessian_tile_kernel(HessArgs a)
                 store_block(a, r0 + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, sums.acc[i][j]);
 }
 
+// Row and column of the p-th pair of tiles (2 row, col) and (2 row + 1, col), col <= 2 row.  Four rows of pairs, then the next four, column by column:
+// what runs on an XCD at a time shares its operands through one L2.
+__device__ __forceinline__ void pair_of(int p, int rows, int& row, int& col)
+{
+    int R = 0;
+    while (16 * (R + 1) * (R + 1) <= p) ++R;   // (at most rows / 4 scalar trips: 4 R rows hold (4 R)^2 pairs)
+    p -= 16 * R * R;
+    int h = min(4, rows - 4 * R);
+    row = 4 * R;
+    col = 8 * R + 1;
+    if (p < h * col) {
+        col = p / h;
+        row += p % h;
+        return;
+    }
+    p -= h * col;
+    for (;;) {   // two columns each that one row less reaches
+        --h;
+        ++row;
+        if (p < 2 * h) break;
+        p -= 2 * h;
+        col += 2;
+    }
+    col += p / h;
+    row += p % h;
+}
+
+// Two tiles of 128 x 128, one below the other, a stage at a time, copied into LDS as it lies in the workspace: four waves multiply the upper
+// one, in quarters of 64 x 64, four the lower one, in turn (pair_alternate).  48 KB are copied for what takes the tiles by themselves 64, and the
+// matrix cores work 1540 of some 2250 cycles a stage, there 1540 of 2900.  Bound: the phases of a group's first stage (its exponents and steps are
+// 150 vector instructions, which share a SIMD's issue with the other wave's MFMAs: 1400 cycles, the others 900) and the clock, 1.85 GHz
+// under this load.  The products 8192 rows, K = 4096: 390 -> 310 us.
+constexpr int kPairStage = 24 * kPairBytes;   // 16-wide blocks per wave side; a stage: 16 blocks of rows, 8 of columns
+constexpr int kPairLds = 3 * kPairStage + 4 * 8 * 256;   // three stages, the exponents of four
+__global__ __launch_bounds__(512, 2) void hessian_pair_kernel(HessArgs a)
+{
+    constexpr int NT = kTile, STAGE = kPairStage;
+    extern __shared__ __attribute__((aligned(1024))) char St[];
+    uint8_t* const Sc = reinterpret_cast<uint8_t*>(St + 3 * STAGE);   // [stage % 4][wave]: of its four's 128 rows, of 128 columns
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), four = wave >> 2;
+    // workgroups are handed to the XCDs in turn: XCD x takes a contiguous run of the pairs
+    const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
+    int ti, tj;
+    pair_of(xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3), a.nt / 2, ti, tj);
+    const bool diag = 2 * ti + four == tj;
+    const int r0 = ti * 2 * kT, c0 = tj * kT;
+    const int wr = (wave >> 1 & 1) * NT, wc = (wave & 1) * NT;   // first block of rows / columns of the wave's quarter
+
+    // Blocks past the end are the last one again: they only feed outputs that are not stored.  Stages past the end are zero.
+    const int kb = a.K / 16, stages = a.stages;
+    const uint32_t exps_at = (uint32_t)min((lane < 32 ? r0 + four * kT : c0) + 4 * (lane & 31), a.K - 4);
+    auto exps_of = [&](int n) { return Sc + ((n & 3) * 8 + wave) * 256; };
+    auto issue = [&](int n, auto between) {
+        const int from = min(n, stages - 1);
+        const uint32_t at = n < stages ? (uint32_t)lane * 16u : 0xfffff000u;
+        char* const slot = St + n % 3 * STAGE;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(a.planes + (int64_t)from * 128 * a.K, 0, 128 * a.K, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(a.exps + (int64_t)(from / kGroup) * a.K, 0, a.K, 0x00020000);
+        each<6>([&](auto i) {
+            const int c = wave * 6 + i;   // 1 KB: half a block
+            const int block = c < 32 ? r0 / 16 + c / 2 : c0 / 16 + c / 2 - 16;
+            copy_to_lds(rs, slot + c * 1024, at, min(block, kb - 1) * kPairBytes + (c & 1) * 1024);
+            between(i);
+        });
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_void*)exps_of(n), 4, exps_at, 0, 0, 0);
+    };
+    PairChain<NT> sums;
+    sums.clear();
+    PairOperands<NT> held;
+    // a group's exponents: of a lane's four rows, of its sixteen columns
+    uint32_t row_exps[NT], col_exps[NT];
+    auto read_exps = [&](const uint8_t* from) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            row_exps[i] = from[(wr + i) * 16 + l16];
+            col_exps[i] = *reinterpret_cast<const uint32_t*>(from + kT + (wc + i) * 16 + 4 * q);
+        }
+    };
+    auto row = [&](int i) { return (int)row_exps[i] - a.row_step; };
+    auto col = [&](int j) { return four_column_factors(col_exps[j]); };
+    if (stages > 0) {
+        const int groups = (stages + kGroup - 1) / kGroup;
+        pair_alternate<7, kGroup>(four, groups, issue,
+            [&](auto part) { sums.template begin<part.value>(row, col); },
+            [&](int n, auto i) {
+                if (i.value == 0) read_exps(exps_of(max(n - 1, 0)));
+                const char* base = St + n % 3 * STAGE;
+                held.fetch(base + (four * 8 + wr) * kPairBytes, base + (16 + wc) * kPairBytes);
+            },
+            [&](auto i) { sums.template multiply<i.value == 0, (i.value > 1)>(held); });
+        read_exps(exps_of(groups * kGroup - 1));
+        sums.end(row, col);
+    }
+    // rows that the workspace has no room for, 32 at a time: either four its rows, and both the columns
+    float(*const red)[kT] = reinterpret_cast<float(*)[kT]>(St + STAGE + four * 4 * kT * 4);
+    uint8_t* const ex = Sc + four * 2 * kT;
+    for (int64_t row0 = (int64_t)stages * 32; row0 < a.T; row0 += 32) {
+        __syncthreads();
+        build_stage(a, row0, r0 + four * kT, St + four * 8 * kPairBytes, ex, red);
+        build_stage(a, row0, c0, St + 16 * kPairBytes, ex + kT, red);
+        __syncthreads();
+        held.fetch(St + (four * 8 + wr) * kPairBytes, St + (16 + wc) * kPairBytes);
+        read_exps(ex);
+        sums.restart();
+        each<sums.kBegin>([&](auto part) { sums.template begin<part.value>(row, col); });
+        sums.template multiply<true, false>(held);
+        sums.end(row, col);
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            if (!diag || wr + i >= wc + j)
+                store_block(a, r0 + four * kT + (wr + i) * 16 + l16, c0 + (wc + j) * 16 + 4 * q, diag && wr + i == wc + j, sums.acc[i][j]);
+}
+
+// The p-th of the tiles that are left: those from `full` on or, of pairs, every other one of the diagonal, the last row if it has no partner,
+// and the pairs from `full` on.
+__device__ __forceinline__ void left_tile(const HessArgs& a, int p, int& ti, int& tj)
+{
+    if (!a.pairs) {
+        tile_of(a.full + p, a.nt, ti, tj);
+        return;
+    }
+    const int rows = a.nt / 2;
+    if (p < rows) {
+        ti = tj = 2 * p + 1;
+        return;
+    }
+    p -= rows;
+    if (a.nt & 1) {
+        if (p < a.nt) {
+            ti = a.nt - 1;
+            tj = p;
+            return;
+        }
+        p -= a.nt;
+    }
+    pair_of(a.full + p / 2, rows, ti, tj);
+    ti = 2 * ti + (p & 1);
+}
+
 // A tile of 16 NT x 16 NT, for what is left beyond whole rounds of the tiles above: each of the four waves takes a quarter of the
 // groups for itself, straight from memory to registers, no barrier; then their sums are added.  32 x 32: a group ahead.  64 x 64, half the
 // bytes per product: a register is refilled behind its last use, and two workgroups per compute unit cover for each other.
@@ -693,7 +843,7 @@ __global__ __launch_bounds__(256, 2) void hessian_part_kernel(HessArgs a)
     const int n = (int)gridDim.x, per = n >> 3, more = n & 7, xcd = blockIdx.x & 7;
     const int p = xcd * per + min(xcd, more) + ((int)blockIdx.x >> 3);
     int ti, tj;
-    tile_of(a.full + p / (SUB * SUB), a.nt, ti, tj);
+    left_tile(a, p / (SUB * SUB), ti, tj);
     ti = SUB * ti + p / SUB % SUB;
     tj = SUB * tj + p % SUB;
     if (tj > ti || ti * SIDE >= a.K) return;
@@ -849,11 +999,23 @@ hipError_t launch_gptq_hessian(const void* x, int64_t T, int64_t K, int b, float
         // The tiles beyond whole rounds, up to one per compute unit, in parts of 64 x 64, or of 32 x 32 if those leave most of the chip
         // idle.  8192 rows, left whole / in 64 / in 32, us: K = 512 (10 left) 257 / 103 / 46, 768 (21) 257 / 102 / 70, 1024 (36) 255 / 99 / 100,
         // 1664 (91) 264 / 135 / 183, 2048 (136) 264 / 213 / 234, 2560 (210) 271 / 261 / 360, 3072 (300) 350 / 350 / 515, 4096 (16) 624 / 517 / 468
-        const int small = rem > slots / 2 ? 0 : rem;
-        a.full = tiles - small;
-        if (a.full) {
-            static LdsAttrOnce once;
-            const hipError_t e = once.ensure(reinterpret_cast<const void*>(hessian_tile_kernel), kTileLds);
+        //
+        // Pairs of tiles, one to a compute unit, where they fill it: from 2048 rows if nearly all units have one in every round, from 4096 if three
+        // of four have.  Tiles / pairs, us: 1408 rows, K = 4096 104 / 104, 5120 (400 pairs for 256 units) 156 / 168, 8192 (1024) 328 / 331; 2048
+        // rows, 4096 132 / 129, 5120 209 / 211, 8192 449 / 435; 4096 rows, 2944 (121) 176 / 203, 3584 (196) 190 / 188, 4096 228 / 210, 5120
+        // 378 / 366, 8192 828 / 762; 8192 rows, 2944 326 / 357, 3584 356 / 335, 4096 424 / 386, 5120 719 / 664, 8192 1643 / 1481.
+        const int units = slots / 2, rows = a.nt / 2, all = rows * rows, over = all % units;
+        const int pairs = all > units && over <= units / 2 ? all - over : all, rounds = (pairs + units - 1) / units;
+        a.pairs = (T >= 4096 && 4 * (int64_t)pairs >= 3 * (int64_t)rounds * units) || (T >= 2048 && 20 * (int64_t)pairs >= 19 * (int64_t)rounds * units);
+        a.full = a.pairs ? pairs : rem > slots / 2 ? tiles : tiles - rem;
+        const int small = tiles - (a.pairs ? 2 : 1) * a.full;
+        static LdsAttrOnce pair_once, tile_once;
+        if (a.pairs) {
+            const hipError_t e = pair_once.ensure(reinterpret_cast<const void*>(hessian_pair_kernel), kPairLds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(hessian_pair_kernel, dim3((unsigned)a.full), dim3(512), kPairLds, st, a);
+        } else if (a.full) {
+            const hipError_t e = tile_once.ensure(reinterpret_cast<const void*>(hessian_tile_kernel), kTileLds);
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(hessian_tile_kernel, dim3((unsigned)a.full), dim3(256), kTileLds, st, a);
         }

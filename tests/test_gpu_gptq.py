@@ -350,6 +350,33 @@ def test_hessian_tiles_and_split_rows(fp4, oracle, T, K, b):
         assert np.array_equal(got, got.T)
 
 
+# (pairs of tiles are taken where they fill the chip: 256 compute units)
+@pytest.mark.parametrize("T,K,b", [(2048, 4096, 16), (2050, 4224, 128), (2081, 4096, 64), (2113, 4080, 16), (4130, 3600, 16), (4200, 3456, 128), (4096, 5120, 32), (2100, 6144, 64)])
+def test_hessian_in_pairs_of_tiles(fp4, T, K, b):
+    """Full and partial rounds of pairs, an odd number of tile rows, a last tile that is not whole, every remainder of stages by a group
+    of four, rows behind the last whole stage; fresh and accumulated, against the fp64 product of rows rotated in fp64.
+    Bound: as above."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(T + K)
+    x = torch.randn(T, K, device="cuda", generator=g)
+    x[:, torch.randperm(K, device="cuda", generator=g)[:K // 200]] *= 50.0
+    x = x.bfloat16()
+    h = torch.ones(1, 1, dtype=torch.float64, device="cuda")
+    while h.shape[0] < b:
+        h = torch.cat([torch.cat([h, h], 1), torch.cat([h, -h], 1)], 0)
+    rotated = ((x.double().view(-1, b) @ h) / b ** 0.5).view(T, K)
+    want = rotated.t() @ rotated
+    say(f"gptq hessian in pairs T={T} K={K} b={b}")
+    H = fp4.fp4_gptq_accumulate_hessian(x, b)
+    H2 = fp4.fp4_gptq_accumulate_hessian(x, b, H.clone())
+    d = want.diagonal().sqrt()
+    for got, times in ((H, 1), (H2, 2)):
+        worst = ((got.double() - times * want).abs() / (d[:, None] * d[None, :])).max().item()
+        say(f"   largest difference {worst:.2e}")
+        assert worst <= 2e-5 * times * (T / 700) ** 0.5
+        assert torch.equal(got, got.t())
+
+
 def common_mode_rows(kind, T, K, b, salt):
     """Calibration rows whose channels have something in common inside a rotation block, as bf16 bits: the rotation moves it
     into a few channels and the others keep what little is left."""
