@@ -337,9 +337,11 @@ double codes_us(int64_t M, int64_t N, int64_t K, int cus, int* tile)
 // and 11 % in one of ten.  Of 2263 products timed that were the kernel for many tokens' it takes 82 %; all of them together take 0.762 of the time (0.755 if every one went the faster way), 3 are
 // more than 3 % slower, the worst 7 %; with 0.95 0.759, 13 and 12 %.  Of the few-token kernels' 713 with 33 to 512 tokens and N <= 12288, 0.83.
 // Up to 32 tokens there is nothing to gain: 194 products, 0.999 if every one went the faster way.  33 to 64 tokens where those kernels have no price (N > 12288, K > 8192, K <= 1024) stay with them.
+// Beyond M N K = 1.5e11 (200 us) both are bound by the same port and the estimates are off by more than what is between them: of 802 products there, M = 900 ... 4096, 0.99 of the time with this kernel,
+// 59 more than 3 % slower (17 % the worst; N = 10240, K = 8192, M = 2048: 333 us against 322); of 593 from 1e11 to 1.5e11 0.945, 27; of 1252 from 5e10 on 0.90, 25.
 int plan_nv_codes(int64_t M, int64_t N, int64_t K, size_t room)
 {
-    if (M <= 32) return -1;
+    if (M <= 32 || (double)M * (double)N * (double)K > 1.5e11) return -1;
     const double few = gemm_nv_stream_us(M, N, K);
     if (few == 0.0) return -1;
     int tile = -1;

@@ -50,3 +50,10 @@ def test_the_fastest_size_is_one_of_the_two_and_room_for_parts_means_parts(host,
 def test_mxfp4_is_always_fastest_with_room_for_parts(host, M, N, K):
     split, fastest = host(["device", 0, 256], *(["bytes", op, M, N, K, MX] for op in (OP_SPLIT, OP_FASTEST)))[1:]
     assert fastest == split
+
+
+@pytest.mark.parametrize("M,N,K,taken", [(1788, 10240, 8192, True), (1789, 10240, 8192, False), (2048, 10240, 8192, False)])
+def test_the_largest_products_stay_with_the_kernel_for_many_tokens(host, M, N, K, taken):
+    fastest = host(["device", 0, 256], ["bytes", OP_FASTEST, M, N, K, NV])[1]
+    runs = host(["device", 0, 256], ["gemm", M, N, K, NV, fastest])[1]
+    assert any("gemm_nv_codes" in r["kernel"] for r in runs) == taken
