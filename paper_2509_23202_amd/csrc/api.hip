@@ -207,6 +207,8 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
     const int variant = options().gemm_variant;
     if (variant < 0 || variant > (fmt == FP4MR_MXFP4 ? kMaxGemmVariantMx : kMaxGemmVariantNv)) return FP4MR_ERR_FMT;
 
+    const bool no_codes = fmt == FP4MR_NVFP4 && variant == kVariantNvNoCodes, chosen = variant == 0 || no_codes;
+
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
     hipError_t e;
@@ -231,7 +233,7 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
     // Optional split-K room behind what the call needs (FP4MR_OP_GEMM_SPLIT_K asks for that of the best plan; with less, the best one that fits)
     void* partial = nullptr;
     size_t partial_room = 0;
-    if (M > 64 && variant == 0 && workspace && aligned16(workspace) && workspace_bytes > align256(need)) {
+    if (M > 64 && chosen && workspace && aligned16(workspace) && workspace_bytes > align256(need)) {
         partial = static_cast<char*>(workspace) + align256(need);
         partial_room = workspace_bytes - align256(need);
     }
@@ -240,7 +242,7 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
     // (a caller who gives NVFP4 room for parts gets a product in parts where the plan has any)
     int tile = -1;
     if (fmt == FP4MR_NVFP4 && variant == 0 && !(partial && !gemm_nv_streams(M, N, K) && nv16_splits(M, N, K, partial_room))) tile = plan_nv_codes(M, N, K, 0);
-    const bool few = fmt == FP4MR_MXFP4 ? plan.variant == 0 : variant == 0 && gemm_nv_streams(M, N, K);
+    const bool few = fmt == FP4MR_MXFP4 ? plan.variant == 0 : chosen && gemm_nv_streams(M, N, K);
     if (tile >= 0)
         e = launch_gemm_nv_codes(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, tile, st);
     else if (few)
@@ -343,7 +345,7 @@ size_t fp4_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, fp4mr_fmt_t 
         if (fmt == FP4MR_NVFP4 && !gemm_nv_streams(M, N, K)) n += align256(nv16_workspace_bytes(M, K));
         // what fp4_gemm needs, plus -- optional -- the fp32 partials of a split-K run where the shape has one
         // (FP4MR_OP_GEMM_FASTEST: only where it is estimated to be the faster way)
-        if (op == FP4MR_OP_GEMM_SPLIT_K || (op == FP4MR_OP_GEMM_FASTEST && !(fmt == FP4MR_NVFP4 && plan_nv_codes(M, N, K, 0) >= 0 && plan_nv_codes(M, N, K, SIZE_MAX) >= 0))) {
+        if (op == FP4MR_OP_GEMM_SPLIT_K || (op == FP4MR_OP_GEMM_FASTEST && !(fmt == FP4MR_NVFP4 && options().gemm_variant != kVariantNvNoCodes && plan_nv_codes(M, N, K, 0) >= 0 && plan_nv_codes(M, N, K, SIZE_MAX) >= 0))) {
             const size_t extra = fmt == FP4MR_MXFP4 ? gemm_mx_split_k_bytes(M, N, K) : gemm_nv_streams(M, N, K) ? 0 : nv16_split_k_bytes(M, N, K);
             if (extra) n = align256(n) + extra;
         }

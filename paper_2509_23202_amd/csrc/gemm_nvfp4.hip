@@ -225,7 +225,7 @@ hipError_t launch_gemm_nvfp4(const void* a_codes, const void* a_scales, const fl
 {
     // By default many-token products go to the kernel that takes its activations as fp16 (gemm_nv16.hip); the tile
     // kernels of this file, which dequantize both operands inside the product, remain as forced configurations.
-    if (variant == 0) return launch_gemm_nv16(a_codes, a_scales, a_ts, w_codes, w_scales, w_ts, M, N, K, out, out_f32, workspace, partial, partial_room, st);
+    if (variant == 0 || variant == kVariantNvNoCodes) return launch_gemm_nv16(a_codes, a_scales, a_ts, w_codes, w_scales, w_ts, M, N, K, out, out_f32, workspace, partial, partial_room, st);
     NvGemmArgs g{};
     g.a_codes = static_cast<const uint8_t*>(a_codes);
     g.a_scales = static_cast<const uint8_t*>(a_scales);

@@ -38,7 +38,9 @@ int compute_units();
 
 // largest valid forced tile configuration per format (fp4_gemm rejects anything else before it launches)
 constexpr int kMaxGemmVariantMx = 18;
-constexpr int kMaxGemmVariantNv = 3;
+constexpr int kMaxGemmVariantNv = 4;
+// NVFP4: chosen as by itself, but without the kernel that dequantizes both operands in its waves
+constexpr int kVariantNvNoCodes = 4;
 
 // policy: group scales by 0 abs-max, 1 squared-error search, 2 rounded exponent with the 4/3 factor (MXFP4 only).
 // rot: null for the normalised Hadamard of size b, else a bf16 [b, b] row-major matrix (y = x . rot per block)
@@ -67,7 +69,7 @@ double gemm_stream_us(int64_t M, int64_t N, int64_t K);
 // fp32 partials of a split-K run (few tiles, long K: every tile's K range shared by several workgroups); 0 = not split
 size_t gemm_mx_split_k_bytes(int64_t M, int64_t N, int64_t K);
 
-// variant 0: the fp16-activation kernel below (needs its workspace); 1..3: the tile kernels that dequantize both operands
+// variant 0, 4: the fp16-activation kernel below (needs its workspace); 1..3: the tile kernels that dequantize both operands
 hipError_t launch_gemm_nvfp4(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                              const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
                              bool out_f32, int variant, void* workspace, void* partial, size_t partial_room, hipStream_t st);

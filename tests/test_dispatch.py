@@ -13,6 +13,20 @@ ROOT = Path(__file__).resolve().parent.parent
 LIB = ROOT / "paper_2509_23202_amd" / "libfp4mr.so"
 MX, NV = 0, 1
 OP_GEMM, OP_SPLIT = 2, 6
+NO_CODES = 4   # GEMM variant of NVFP4: picked by size, but not the kernel that dequantizes both operands in its waves
+
+# Products of the kernel for many tokens that the tests on the device name: the tile widths of their launches with the least workspace.
+NV16_HALF_ROWS = {(129, 12296, 512): [128], (192, 57344, 6656): [256], (320, 28672, 1024): [256], (577, 10248, 384): [128], (1088, 8192, 512): [256], (2100, 10240, 512): [256],
+                  (449, 12288, 2048): [128], (1161, 14977, 2048): [256, 128]}
+NV16_TWO_LAUNCHES = {(2048, 10240, 512): [256, 128], (1137, 14664, 512): [256, 128], (2378, 14324, 384): [256, 128], (2053, 10248, 512): [256], (4000, 10200, 512): [256]}
+NV16_NARROW = {(1024, 10240, 512): [128], (1000, 10200, 512): [128], (512, 8192, 512): [128]}
+NV16_ONE_ROUND = {(2048, 8192, 128): [256], (2041, 7945, 256): [256], (300, 28680, 384): [256]}
+NV16_512_COLUMNS = {(2048, 8192, 6656): [512], (2041, 7945, 6784): [512], (300, 28680, 6656): [256]}
+# and of those in parts along K, with all the room for them
+NV16_PARTS = {(65, 400, 8320): 128, (128, 1024, 14336): 128, (200, 1000, 10368): 128, (300, 528, 16512): 128, (520, 1040, 4096): 128, (600, 520, 2048): 128}
+NV16_PARTS_SHORT_K = {(134, 18560, 3840): 256, (129, 12358, 3968): 256, (642, 1368, 2048): 128}
+NV16_PARTS_HALF_ROWS = {(320, 8190, 8192): 512, (192, 4200, 28672): 512, (400, 6200, 8192): 512, (160, 16384, 8192): 512, (320, 8200, 8192): 512}
+NV16_PARTS_ROOM = {(128, 2056, 10240): 128, (192, 4200, 28672): 512, (300, 528, 16512): 128, (256, 528, 8320): 128}
 
 HIP = r"""
 #include <stdio.h>
@@ -73,6 +87,7 @@ def launches():
 for req in json.load(sys.stdin):
     what, a = req[0], req[1:]
     if what == "device": hip.fake_device(*a); r = None
+    elif what == "variant": r = lib.fp4_set_option(0, *a)
     elif what == "bytes": r = lib.fp4_workspace_bytes(a[0], a[1], a[2], a[3], a[4], LAYOUTS)
     elif what == "gemm":
         M, N, K, fmt, room = a
@@ -109,6 +124,28 @@ def host(tmp_path_factory):
     return ask
 
 
+def nv16_width(kernel):
+    return {"Li4ELi2E": 128, "Li4ELi4E": 256, "Li8ELi4E": 512}[kernel.split("gemm_nv16_kernelI")[1][:8]]
+
+
+@pytest.mark.parametrize("shapes", [NV16_HALF_ROWS, NV16_TWO_LAUNCHES, NV16_NARROW, NV16_ONE_ROUND, NV16_512_COLUMNS], ids=["half_rows", "two_launches", "narrow", "one_round", "512_columns"])
+def test_nvfp4_products_for_many_tokens_run_in_the_tiles_that_their_tests_name(host, shapes):
+    for (M, N, K), widths in shapes.items():
+        need = host(["bytes", OP_GEMM, M, N, K, NV])[0]
+        x16, *runs = host(["device", 0, 256], ["variant", NO_CODES], ["gemm", M, N, K, NV, need])[2]
+        assert "nv_x16" in x16["kernel"] and [nv16_width(r["kernel"]) for r in runs] == widths, (M, N, K)
+
+
+@pytest.mark.parametrize("shapes", [NV16_PARTS, NV16_PARTS_SHORT_K, NV16_PARTS_HALF_ROWS, NV16_PARTS_ROOM], ids=["parts", "short_k", "half_rows", "room"])
+def test_nvfp4_products_in_parts_run_in_the_tiles_that_their_tests_name(host, shapes):
+    """With the size that promises the fastest call too, which is the one for parts where the other kernel is out of the question."""
+    for (M, N, K), width in shapes.items():
+        full, fastest = host(["device", 0, 256], ["variant", NO_CODES], ["bytes", OP_SPLIT, M, N, K, NV], ["bytes", 7, M, N, K, NV])[2:]
+        assert full == fastest
+        x16, tiles, sums = host(["device", 0, 256], ["variant", NO_CODES], ["gemm", M, N, K, NV, full])[2]
+        assert "nv_x16" in x16["kernel"] and nv16_width(tiles["kernel"]) == width and "nv16_reduce" in sums["kernel"], (M, N, K)
+
+
 @pytest.mark.parametrize("fmt", [MX, NV])
 def test_a_plan_is_made_for_the_device_that_is_current(host, fmt):
     """A thread that goes on to a device with fewer compute units plans for that one, as a thread that starts there."""
@@ -134,15 +171,16 @@ def test_few_token_linears_start_one_workgroup_per_compute_unit(host, call, cus)
 def test_split_runs_have_the_parts_that_their_workspace_holds(host, fmt, M, N, K):
     """Room for every number of parts up to the best one: a run in at most as many, whose partial sums end inside the workspace; more room
     than the best run needs changes nothing."""
-    base, full = host(["device", 0, 256], ["bytes", OP_GEMM, M, N, K, fmt], ["bytes", OP_SPLIT, M, N, K, fmt])[1:]
+    start = ["device", 0, 256], ["variant", NO_CODES if fmt == NV else 0]
+    base, full = host(*start, ["bytes", OP_GEMM, M, N, K, fmt], ["bytes", OP_SPLIT, M, N, K, fmt])[2:]
     base = (base + 255) // 256 * 256
     part = M * N * 4
     assert full >= base + 2 * part
-    best, more = host(["device", 0, 256], ["gemm", M, N, K, fmt, full], ["gemm", M, N, K, fmt, full + 7 * part])[1:]
+    best, more = host(*start, ["gemm", M, N, K, fmt, full], ["gemm", M, N, K, fmt, full + 7 * part])[2:]
     assert best == more and best[-1]["ends"] == full
     for n in range(1, (full - base) // part + 1):
         for room in (base + n * part, base + (n + 1) * part - 1):
-            run = host(["device", 0, 256], ["gemm", M, N, K, fmt, room])[1]
+            run = host(*start, ["gemm", M, N, K, fmt, room])[2]
             assert ("reduce" in run[-1]["kernel"]) == (n >= 2), room
             assert max(l["ends"] for l in run) <= room
 
@@ -184,7 +222,7 @@ def test_nvfp4_parts_with_their_half_tiles_last(host, M, N, K, last):
     """Split runs hand out the tiles of a last row of at most 64 tokens last, as half tiles: from K = 4096 on, and below it where all whole
     tiles' parts are a workgroup for every compute unit or less, and the half ones' come on top."""
     full = host(["bytes", OP_SPLIT, M, N, K, NV])[0]
-    runs = host(["device", 0, 256], ["gemm", M, N, K, NV, full])[1]
+    runs = host(["device", 0, 256], ["variant", NO_CODES], ["gemm", M, N, K, NV, full])[2]
     assert "nv16_reduce" in runs[-1]["kernel"] and runs[-1]["sums"][1][2] == last * N
 
 

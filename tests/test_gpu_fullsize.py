@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 from paper_2509_23202_amd import inputs
+from tests.test_dispatch import NO_CODES, NV16_NARROW, NV16_ONE_ROUND, NV16_TWO_LAUNCHES, NV16_512_COLUMNS
 from tests.gpu_util import MX, NV, compare_codes, gemm_layout_to_canonical, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
@@ -219,36 +220,39 @@ def test_short_k_layers_take_the_two_workgroups_per_unit_tiles(fp4, oracle, M, N
     check_layer(fp4, oracle, inputs.RECIPES[3], M, 1024, N, MX, 32, n_m=48, n_n=64, salt=M)
 
 
-@pytest.mark.parametrize("M,N", [(2048, 10240), (2053, 10248), (4000, 10200)])
-def test_nvfp4_two_launch_split_of_the_tile_grid(fp4, oracle, M, N):
-    """More 256 x 256 tiles than one round of compute units and a partial round left over: the shape rule runs the tile
-    columns that fill whole rounds as 256 x 256 tiles and the remaining columns as 128 x 128 tiles in a second launch
-    (ragged last tile row and column in the second and third case).  Columns either side of every multiple of 256
-    that can be the seam between the two launches are sampled on purpose."""
+@pytest.mark.parametrize("M,N,K", NV16_TWO_LAUNCHES)
+def test_nvfp4_two_launch_split_of_the_tile_grid(fp4, oracle, M, N, K, knobs):
+    """More 128 x 256 tiles than one round of the chip and a partial round left over: the shape rule runs the tile
+    columns that fill whole rounds as 128 x 256 tiles and the remaining columns as 128 x 128 tiles in a second launch
+    (ragged last tile row and column in the second and third case; the last two are better off in one launch).  Columns either side
+    of every multiple of 256 that can be the seam between the two launches are sampled on purpose."""
+    knobs(variant=NO_CODES)
     seams = [c * 256 + d for c in range(1, (N + 255) // 256) for d in (-1, 0)]
-    check_layer(fp4, oracle, inputs.RECIPES[4], M, 512, N, NV, 16, n_m=48, n_n=96, salt=M, extra_n=seams)
+    check_layer(fp4, oracle, inputs.RECIPES[4], M, K, N, NV, 16, n_m=48, n_n=96, salt=M, extra_n=seams)
 
 
-@pytest.mark.parametrize("M,N", [(1024, 10240), (1000, 10200), (512, 8192)])
-def test_nvfp4_narrow_tiles_when_wide_ones_are_about_one_round(fp4, oracle, M, N):
+@pytest.mark.parametrize("M,N,K", NV16_NARROW)
+def test_nvfp4_narrow_tiles_when_wide_ones_are_about_one_round(fp4, oracle, M, N, K, knobs):
     """Between one 128 x 256 tile per compute unit and a round and a quarter of them the whole product runs as
     128 x 128 tiles (640, 640 with ragged edges, and 256 of them here); columns either side of every multiple of 128
     near the middle and the end of N are sampled on purpose."""
+    knobs(variant=NO_CODES)
     seams = [c * 128 + d for c in (1, 2, N // 256, N // 128 - 1, (N - 1) // 128) for d in (-1, 0) if 0 <= c * 128 + d < N]
-    check_layer(fp4, oracle, inputs.RECIPES[4], M, 512, N, NV, 16, n_m=48, n_n=96, salt=M + 5, extra_n=seams)
+    check_layer(fp4, oracle, inputs.RECIPES[4], M, K, N, NV, 16, n_m=48, n_n=96, salt=M + 5, extra_n=seams)
 
 
-@pytest.mark.parametrize("M,N,K", [(2048, 8192, 128), (2041, 7945, 256), (300, 28680, 384), (320, 8200, 8192)])
-def test_nvfp4_eight_wave_tiles_in_a_single_round(fp4, oracle, M, N, K):
+@pytest.mark.parametrize("M,N,K", [*NV16_ONE_ROUND, (320, 8200, 8192)])
+def test_nvfp4_eight_wave_tiles_in_a_single_round(fp4, oracle, M, N, K, knobs):
     """More 128 x 256 tiles than compute units in no more than one round: short K (pairs of 128 x 256 tiles), with two K-steps
     (fewer than the ring has stages) and a ragged last tile row and column, and (the last case) 128 x 512 tiles of eight waves
     shared out along K.  Columns either side of the multiples of 512 near the start, the middle and the end of N are sampled on
     purpose."""
+    knobs(variant=NO_CODES)
     seams = [c * 512 + d for c in (1, N // 1024, N // 512) for d in (-1, 0)] + [N - 1]
     check_layer(fp4, oracle, inputs.RECIPES[4], M, K, N, NV, 16, n_m=48, n_n=96, salt=M + N, extra_n=seams)
 
 
-@pytest.mark.parametrize("M,N,K", [(2048, 8192, 6656), (2041, 7945, 6784), (300, 28680, 6656)])
-def test_nvfp4_eight_wave_tiles_unsplit(fp4, oracle, M, N, K):
+@pytest.mark.parametrize("M,N,K", NV16_512_COLUMNS)
+def test_nvfp4_eight_wave_tiles_unsplit(fp4, oracle, M, N, K, knobs):
     """The same grids from the K on at which 128 x 512 tiles are taken, each workgroup over the whole of K."""
-    test_nvfp4_eight_wave_tiles_in_a_single_round(fp4, oracle, M, N, K)
+    test_nvfp4_eight_wave_tiles_in_a_single_round(fp4, oracle, M, N, K, knobs)

@@ -5,6 +5,7 @@ import sys
 
 import pytest
 
+from tests.test_dispatch import NO_CODES
 from tests.gpu_util import MX, NV
 
 pytestmark = pytest.mark.gpu
@@ -26,12 +27,14 @@ def fp4():
 @pytest.mark.parametrize("fmt,M,N,K", [(MX, 16, 1040, 4096), (MX, 128, 528, 4096), (MX, 128, 272, 14336), (MX, 300, 784, 1024),
                                        (MX, 1024, 1040, 512), (NV, 16, 528, 8192), (NV, 40, 1040, 1152), (NV, 16, 272, 14336),
                                        (NV, 256, 528, 8320)])
-def test_graph_replays_equal_the_eager_calls(fp4, fmt, M, N, K):
+def test_graph_replays_equal_the_eager_calls(fp4, fmt, M, N, K, knobs):
     """Persistent few-token kernels (one set, several sets, fp16-resident NVFP4), the tile kernels with and without the
     split-K workspace, the NVFP4 many-token kernel with its fp16 pre-pass and split, and the NVFP4 quantizer's two passes
     (tensor scale through the workspace): three different activation tensors, two rounds of replays, eager work and
     synchronisation between the replays, every output compared bit for bit."""
     import torch
+    if fmt == NV:
+        knobs(variant=NO_CODES)
     b = 32 if fmt == MX else 16
     GL = fp4.LAYOUT_GEMM
     gfl = fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM

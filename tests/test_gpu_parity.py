@@ -13,6 +13,7 @@ import numpy as np
 import pytest
 
 from paper_2509_23202_amd import inputs
+from tests.test_dispatch import NO_CODES, NV16_HALF_ROWS, NV16_PARTS_HALF_ROWS, NV16_PARTS_SHORT_K
 from tests.gpu_util import MX, NV, compare_codes, gemm_layout_to_canonical, to_dev, to_dev_bf16, unpack
 
 pytestmark = pytest.mark.gpu
@@ -308,11 +309,12 @@ def test_gemm_nvfp4_every_tile_variant(fp4, oracle, variant, out_f32, knobs):
     _gemm_case(fp4, oracle, NV, 272, 528, 1280, seed=30 + variant, out_f32=out_f32, layout_gemm=True)
 
 
-@pytest.mark.parametrize("M,N,K", [(129, 8200, 512), (192, 57344, 6656), (320, 28672, 1024), (577, 10248, 384), (1088, 8192, 512), (2100, 10240, 512), (449, 12288, 2048)])
-def test_gemm_nvfp4_last_row_of_tiles_with_at_most_64_tokens(fp4, M, N, K):
+@pytest.mark.parametrize("M,N,K", NV16_HALF_ROWS)
+def test_gemm_nvfp4_last_row_of_tiles_with_at_most_64_tokens(fp4, M, N, K, knobs):
     """Those tiles multiply half their rows, and the launch is chosen with them in mind.  Every output is one sum along K in the same
-    order whatever the tile, so the result equals that of the same rows with rows of zeros up to whole tiles, bit for bit."""
+    order whatever the tile, so the result equals that of the same rows with rows of zeros up to whole tiles, bit for bit; bf16 and fp32."""
     import torch
+    knobs(variant=NO_CODES)
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N)
     x = torch.randn(M, K, device="cuda", generator=g).bfloat16()
@@ -321,10 +323,12 @@ def test_gemm_nvfp4_last_row_of_tiles_with_at_most_64_tokens(fp4, M, N, K):
     out = []
     for rows in (M, (M + 127) // 128 * 128):
         qx = fp4.fp4_rotate_quantize(torch.cat([x, x.new_zeros(rows - M, K)]), 16, NV, flags=fp4.LAYOUT_GEMM)
-        room = torch.empty(fp4.workspace_bytes(fp4.OP_GEMM, rows, N, K, NV, fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM), dtype=torch.uint8, device="cuda")
-        out.append(fp4.fp4_gemm(*qx, *qw, rows, N, K, NV, flags=fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM, workspace=room))
+        for flags in (fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM, fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM | fp4.OUT_F32):
+            room = torch.empty(fp4.workspace_bytes(fp4.OP_GEMM, rows, N, K, NV, flags), dtype=torch.uint8, device="cuda")
+            out.append(fp4.fp4_gemm(*qx, *qw, rows, N, K, NV, flags=flags, workspace=room))
     torch.cuda.synchronize()
-    assert torch.equal(out[0], out[1][:M])
+    assert torch.equal(out[0], out[2][:M]) and torch.equal(out[1], out[3][:M])
+    assert torch.equal(out[0], out[1].bfloat16())
 
 
 @pytest.mark.parametrize("variant", [2, 5, 10, 13, 15, 17, 18])
@@ -674,11 +678,12 @@ def test_gemm_nvfp4_four_row_blocks_per_workgroup(fp4, oracle, M, N, K, out_f32)
 
 @pytest.mark.parametrize("M,N,K,out_f32", [(65, 400, 8320, True), (128, 1024, 14336, False), (200, 1000, 10368, False), (300, 528, 16512, True),
                                            (520, 1040, 4096, False), (600, 520, 2048, True)])
-def test_gemm_nvfp4_split_k(fp4, oracle, M, N, K, out_f32):
+def test_gemm_nvfp4_split_k(fp4, oracle, M, N, K, out_f32, knobs):
     """The NVFP4 many-token kernel with its K range shared by several workgroups (optional workspace): ragged M and N,
     K / 64 = 32, 64, 130, 162, 224, 258 (a last split of two K-steps of 64, i.e. one fragment; ragged last splits; short K in
     parts of eight steps on 128 x 128 tiles), both output types; the same call with the minimum workspace runs unsplit and must meet the same bound."""
     import torch
+    knobs(variant=NO_CODES)
     r = inputs.RECIPES[4]
     xb, wb = r.x(M, K, salt=M + K), r.w(N, K, salt=M + K)
     ya, yw = oracle.rotate(xb, 16), oracle.rotate(wb, 16)
@@ -702,10 +707,11 @@ def test_gemm_nvfp4_split_k(fp4, oracle, M, N, K, out_f32):
         assert np.all(err <= tol), (name, float((err / (1e-3 * S + 1e-300)).max()))
 
 
-@pytest.mark.parametrize("M,N,K", [(134, 18560, 3840), (129, 12358, 3968), (642, 1368, 2048)])
-def test_gemm_nvfp4_parts_of_a_short_k_with_half_tiles_last(fp4, M, N, K):
+@pytest.mark.parametrize("M,N,K", NV16_PARTS_SHORT_K)
+def test_gemm_nvfp4_parts_of_a_short_k_with_half_tiles_last(fp4, M, N, K, knobs):
     """K below 4096: a few tokens in a last row of tiles whose parts come on top of a round of the chip, against the fp64 product of the decoded operands."""
     import torch
+    knobs(variant=NO_CODES)
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + K)
     ops = [fp4.fp4_rotate_quantize(torch.randn(n, K, device="cuda", generator=g).to(torch.bfloat16), 16, NV) for n in (M, N)]
@@ -715,11 +721,12 @@ def test_gemm_nvfp4_parts_of_a_short_k_with_half_tiles_last(fp4, M, N, K):
     assert bool(((out.double() - Y).abs() <= 1e-3 * S).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(320, 8190, 8192), (192, 4200, 28672), (400, 6200, 8192), (160, 16384, 8192)])
-def test_gemm_nvfp4_parts_that_suit_half_tiles(fp4, M, N, K):
+@pytest.mark.parametrize("M,N,K", list(NV16_PARTS_HALF_ROWS)[:4])
+def test_gemm_nvfp4_parts_that_suit_half_tiles(fp4, M, N, K, knobs):
     """A last row of at most 64 tokens in fewer parts than the whole tiles above it: against the fp64 product of the decoded operands, and with
     every workspace from the least to the full one (fewer parts, then none)."""
     import torch
+    knobs(variant=NO_CODES)
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + K)
     ops = [fp4.fp4_rotate_quantize(torch.randn(n, K, device="cuda", generator=g).to(torch.bfloat16), 16, NV) for n in (M, N)]
@@ -753,10 +760,11 @@ def test_gemm_mxfp4_larger_tiles_in_parts(fp4, M, N, K):
 
 
 @pytest.mark.parametrize("fmt,M,N,K", [(MX, 97, 130, 16512), (MX, 201, 1032, 14336), (NV, 128, 2056, 10240), (NV, 192, 4200, 28672), (NV, 300, 528, 16512)])
-def test_gemm_split_runs_write_nothing_behind_their_workspace(fp4, fmt, M, N, K):
+def test_gemm_split_runs_write_nothing_behind_their_workspace(fp4, fmt, M, N, K, knobs):
     """Room for the best number of parts, for fewer, for one: the result against the fp64 product of the decoded operands, and the bytes behind the
     workspace, which belong to the same allocation, as they were."""
     import torch
+    knobs(variant=NO_CODES if fmt == NV else 0)
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + K)
     gfl = fp4.A_LAYOUT_GEMM | fp4.W_LAYOUT_GEMM
