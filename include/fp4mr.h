@@ -78,7 +78,7 @@ enum {
 /* operation selector for fp4_workspace_bytes */
 enum { FP4MR_OP_ROTATE_QUANTIZE = 0, FP4MR_OP_QUANTIZE_WEIGHTS = 1, FP4MR_OP_GEMM = 2, FP4MR_OP_GPTQ = 3, FP4MR_OP_GPTQ_PREPARE = 4, FP4MR_OP_GPTQ_HESSIAN = 5,
        FP4MR_OP_GEMM_SPLIT_K = 6 /* fp4_gemm with room for split-K partials: see fp4_gemm's workspace */,
-       FP4MR_OP_GEMM_FASTEST = 7 /* whichever of the two sizes makes fp4_gemm the faster */ };
+       FP4MR_OP_GEMM_FASTEST = 7 /* the least size with which fp4_gemm is fastest: one of the two */ };
 
 /*
  * Online rotation + quantization of activations: codes, scales = Q(X H_b)   (Section 4.2 item 1: rotation
@@ -196,17 +196,17 @@ fp4mr_status_t fp4_quantize_weights(const void* w, int64_t N, int64_t K, int had
  *   flags        layouts, FP4MR_OUT_F32, and for MXFP4 FP4MR_A_SCALE43 / FP4MR_W_SCALE43 (FP4MR_ERR_FMT with NVFP4)
  *   workspace    fp4_workspace_bytes(FP4MR_OP_GEMM, M, N, K, fmt, flags) bytes: room for operands handed over in
  *                row-major layout (they are re-tiled first), and, for NVFP4 with M > 64 on the shapes that the
- *                many-token kernel takes, 2 bytes per element of the activation operand (its exact fp16 values
- *                code * s_G are written once, so that the product kernel converts only W).  May be NULL when that size
+ *                few-token kernels do not take, 2 bytes per element of the activation operand (one of two kernels writes its exact fp16
+ *                values code * s_G there once, so that the product converts only W).  May be NULL when that size
  *                is 0 (MXFP4 with both operands in GEMM layout).
  *                Optional: with at least fp4_workspace_bytes(FP4MR_OP_GEMM_SPLIT_K, ...) bytes (the same plus room for
  *                fp32 partial results; equal to the former where the shape has nothing to gain) a product with few
  *                output tiles and a long K -- 65 to a few hundred tokens against a narrow layer -- is split along K
  *                over otherwise idle compute units (with less room, in fewer parts where those still gain) and the partial results are added in a fixed order (deterministic;
  *                the fp32 sums are grouped per split, so the result can differ from the unsplit one in its last bits).
- *                NVFP4: a call with room for partials runs in parts wherever there is a plan for it.  With FP4MR_OP_GEMM's bytes most products of more than 32 tokens
- *                go to a kernel that needs no parts, often the faster way; FP4MR_OP_GEMM_FASTEST asks for the one size or the other accordingly (MXFP4: always
- *                for FP4MR_OP_GEMM_SPLIT_K's).
+ *                NVFP4: most products of more than 32 tokens go to a kernel that needs no parts where it is estimated to be the faster, whatever room there is: more
+ *                room never leads to a slower way.  FP4MR_OP_GEMM_FASTEST is FP4MR_OP_GEMM_SPLIT_K's size where the product would then run in parts and
+ *                FP4MR_OP_GEMM's where it would not (MXFP4: always the former).
  */
 fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* a_tensor_scale,
                         const void* w_codes, const void* w_scales, const float* w_tensor_scale,

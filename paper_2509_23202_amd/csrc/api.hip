@@ -237,20 +237,28 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
         partial = static_cast<char*>(workspace) + align256(need);
         partial_room = workspace_bytes - align256(need);
     }
-    MxPlan plan{variant, 1, 0};
-    if (fmt == FP4MR_MXFP4 && variant == 0) plan = plan_mx(M, N, K, partial_room);
-    // (a caller who gives NVFP4 room for parts gets a product in parts where the plan has any)
-    int tile = -1;
-    if (fmt == FP4MR_NVFP4 && variant == 0 && !(partial && !gemm_nv_streams(M, N, K) && nv16_splits(M, N, K, partial_room))) tile = plan_nv_codes(M, N, K, 0);
-    const bool few = fmt == FP4MR_MXFP4 ? plan.variant == 0 : chosen && gemm_nv_streams(M, N, K);
-    if (tile >= 0)
-        e = launch_gemm_nv_codes(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, tile, st);
-    else if (few)
-        e = launch_gemm_skinny(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, (int)fmt, out, out_f32, alpha, st);
-    else if (fmt == FP4MR_MXFP4)
-        e = launch_gemm_mxfp4(a_codes, a_scales, w_codes, w_scales, M, N, K, out, out_f32, plan, alpha, partial, st);
-    else
-        e = launch_gemm_nvfp4(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, variant, ws, partial, partial_room, st);
+    if (fmt == FP4MR_MXFP4) {
+        const MxPlan plan = variant == 0 ? plan_mx(M, N, K, partial_room) : MxPlan{variant, 1, 0};
+        if (plan.variant == 0)
+            e = launch_gemm_skinny(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, (int)fmt, out, out_f32, alpha, st);
+        else
+            e = launch_gemm_mxfp4(a_codes, a_scales, w_codes, w_scales, M, N, K, out, out_f32, plan, alpha, partial, st);
+    } else if (!chosen) {
+        e = launch_gemm_nvfp4(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, variant, st);
+    } else {
+        // the few-token kernels or the one for many tokens, as that would run with this room, or the one without parts if it is the faster: more room
+        // never leads to a slower call
+        const bool few = gemm_nv_streams(M, N, K);
+        Nv16Plan many;
+        if (!few) many = plan_nv16(M, N, K, partial_room);
+        const int tile = no_codes || M <= 32 ? -1 : plan_nv_codes(M, N, K, few ? gemm_nv_stream_us(M, N, K) : many.us);
+        if (tile >= 0)
+            e = launch_gemm_nv_codes(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, tile, st);
+        else if (few)
+            e = launch_gemm_skinny(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, (int)fmt, out, out_f32, alpha, st);
+        else
+            e = launch_gemm_nv16(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, many, ws, partial, st);
+    }
     return e == hipSuccess ? FP4MR_OK : FP4MR_ERR_DEVICE;
 }
 
@@ -341,14 +349,22 @@ size_t fp4_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, fp4mr_fmt_t 
         size_t n = 0;
         if (!(flags & FP4MR_A_LAYOUT_GEMM)) n += repack_bytes(M, K, fmt);
         if (!(flags & FP4MR_W_LAYOUT_GEMM)) n += repack_bytes(N, K, fmt);
-        // NVFP4 with more than 64 tokens: the activations are dequantized once to fp16 (2 bytes per element)
-        if (fmt == FP4MR_NVFP4 && !gemm_nv_streams(M, N, K)) n += align256(nv16_workspace_bytes(M, K));
+        const bool many = fmt == FP4MR_NVFP4 && !gemm_nv_streams(M, N, K);
+        // the kernel for many tokens dequantizes the activations once to fp16, 2 bytes per element.  Asked for on behalf of products of the kernel that dequantizes
+        // them in its waves too: with one size for all a caller's workspace for some number of tokens does for fewer
+        if (many) n += align256(nv16_workspace_bytes(M, K));
         // what fp4_gemm needs, plus -- optional -- the fp32 partials of a split-K run where the shape has one
-        // (FP4MR_OP_GEMM_FASTEST: only where it is estimated to be the faster way)
-        if (op == FP4MR_OP_GEMM_SPLIT_K || (op == FP4MR_OP_GEMM_FASTEST && !(fmt == FP4MR_NVFP4 && options().gemm_variant != kVariantNvNoCodes && plan_nv_codes(M, N, K, 0) >= 0 && plan_nv_codes(M, N, K, SIZE_MAX) >= 0))) {
-            const size_t extra = fmt == FP4MR_MXFP4 ? gemm_mx_split_k_bytes(M, N, K) : gemm_nv_streams(M, N, K) ? 0 : nv16_split_k_bytes(M, N, K);
-            if (extra) n = align256(n) + extra;
+        // (FP4MR_OP_GEMM_FASTEST: only where that run is what fp4_gemm would then choose)
+        if (op == FP4MR_OP_GEMM) return n;
+        size_t extra = 0;
+        if (fmt == FP4MR_MXFP4) {
+            extra = gemm_mx_split_k_bytes(M, N, K);
+        } else if (many) {
+            const Nv16Plan plan = plan_nv16(M, N, K, SIZE_MAX);
+            const bool codes = options().gemm_variant != kVariantNvNoCodes && plan_nv_codes(M, N, K, plan.us) >= 0;
+            if (op == FP4MR_OP_GEMM_SPLIT_K || !codes) extra = plan.partial_bytes;
         }
+        if (extra) n = align256(n) + extra;
         return n;
     }
     return 0;

@@ -388,23 +388,17 @@ bool nv16_narrow_tiles(int64_t tiles_w, int cus)
     return 4 * tiles_w <= 5 * (int64_t)cus;
 }
 
-struct SplitPlan {
-    int parts[2] = {1, 1}, steps[2] = {0, 0};   // of whole tiles, of those of a last row of at most 64 tokens
-    bool narrow = false, rows512 = false;       // tiles of 128 columns; of 512
-    bool half_row = false;
-};
-
 // bytes of the partials (0: not split)
-size_t partial_bytes(const SplitPlan& p, int64_t M, int64_t N)
+size_t partial_bytes(const Nv16Parts& p, int64_t M, int64_t N)
 {
     const int64_t last = p.half_row ? (M - 1) % 128 + 1 : 0;
     return p.parts[0] > 1 ? (size_t)(p.parts[0] * (M - last) + p.parts[1] * last) * (size_t)N * 4 : 0;
 }
 
 // `most`: bytes that as many parts for all tiles may take, `room`: that parts of different numbers may
-SplitPlan search_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t most, size_t room)
+Nv16Parts search_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t most, size_t room)
 {
-    SplitPlan plan;
+    Nv16Parts plan;
     const int64_t tiles_m = (M + 127) / 128;
     const int64_t tiles_w = tiles_m * ((N + 255) / 256), tiles_n = tiles_m * ((N + 127) / 128);
     const int64_t slots = 2 * (int64_t)cus;
@@ -466,15 +460,10 @@ SplitPlan search_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t m
 }
 
 // the plan with all the room it likes, and only where its partials do not fit `room` that of the parts which do
-SplitPlan plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t room)
+Nv16Parts plan_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t room)
 {
-    const SplitPlan plan = search_split_k_nv16(M, N, K, cus, SIZE_MAX, room);
+    const Nv16Parts plan = search_split_k_nv16(M, N, K, cus, SIZE_MAX, room);
     return partial_bytes(plan, M, N) <= room ? plan : search_split_k_nv16(M, N, K, cus, room, room);
-}
-
-int device_cus()
-{
-    return compute_units();
 }
 
 template <int NW, int TN, int STAGES, bool OUT_F32, bool SPLITK>
@@ -507,11 +496,6 @@ hipError_t launch_width(int width, const Nv16Args& g, bool out_f32, hipStream_t 
 {
     return width == 512 ? launch_tiles<8, 4, 3>(g, out_f32, st) : width == 128 ? launch_tiles<4, 2, 3>(g, out_f32, st) : launch_tiles<4, 4, 3>(g, out_f32, st);
 }
-
-// one launch of the product: columns n_first .. n_first + n_cols - 1 in tiles of `width`, the last row's half tiles behind all others or not
-struct Nv16Launch {
-    int width, n_first, n_cols, half_row;
-};
 
 Nv16Launch of_width(int width, int64_t first, int64_t cols, int64_t tiles_m, bool half_row, int64_t cus)
 {
@@ -599,7 +583,7 @@ int plan_whole(int64_t M, int64_t N, int64_t K, int cus, Nv16Launch (&l)[2])
 }
 
 // the product in parts, and their sums
-hipError_t launch_parts(Nv16Args g, const SplitPlan& plan, bool out_f32, float* partial, hipStream_t st)
+hipError_t launch_parts(Nv16Args g, const Nv16Parts& plan, bool out_f32, float* partial, hipStream_t st)
 {
     g.n_first = 0;
     g.n_cols = (int)g.N;
@@ -616,7 +600,7 @@ hipError_t launch_parts(Nv16Args g, const SplitPlan& plan, bool out_f32, float* 
         r.count[h] = (h ? g.M - rows0 : rows0) * g.N;
         partial += r.parts[h] * r.count[h];
     }
-    const hipError_t e = launch_width(plan.rows512 ? 512 : plan.narrow ? 128 : 256, g, out_f32, st);
+    const hipError_t e = launch_width(plan.width(), g, out_f32, st);
     if (e != hipSuccess) return e;
     const bool vec = g.N % 4 == 0;
     const dim3 grid((unsigned)((g.M * g.N / (vec ? 4 : 1) + 255) / 256));
@@ -637,40 +621,43 @@ size_t nv16_workspace_bytes(int64_t M, int64_t K)
     return (size_t)(round_up(M, 16) * K * 2);
 }
 
-// bytes of fp32 partials a split-K run of this product needs, where there is room for as many as it likes (0: the product is not split)
-size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K) { return partial_bytes(plan_split_k_nv16(M, N, K, device_cus(), SIZE_MAX), M, N); }
-
-bool nv16_splits(int64_t M, int64_t N, int64_t K, size_t partial_room) { return plan_split_k_nv16(M, N, K, device_cus(), partial_room).parts[0] > 1; }
-
 // Price of the whole call: the fp16 copy of X, the launches of the plan (a half tile counts as 0.62 of a whole one), the sum of the parts.  Fitted to 2263 products with
 // cold weights (M = 65 ... 4096, N = 512 ... 57344, K = 1024 ... 28672), median error 4 %.
-double nv16_us(int64_t M, int64_t N, int64_t K, size_t partial_room)
+static double nv16_us(int64_t M, int64_t N, int64_t K, int cus, const Nv16Plan& plan)
 {
     constexpr TileRounds narrow = {2, 9.621, 0.8373, 6.093, 0.3200, 0.1981, 9.981, 0.5480, 0.3470}, wide = {2, 25.06, 1.3711, 8.275, 0.1857, 0.9045, 18.40, 0.9649, 0.5646},
                          rows512 = {1, 4.879, 1.6131, 15.98, 0.7689, 0.6808};
-    const int cus = device_cus();
     const int64_t tiles_m = (M + 127) / 128;
     double us = 4.160 + 0.614e-6 * (double)M * (double)K;
     auto add = [&](int width, int64_t cols, int64_t half_row, int64_t parts, int64_t half_parts, int64_t steps) {
         const double tiles_n = (double)((cols + width - 1) / width);
         us += tile_rounds_us(width == 512 ? rows512 : width == 256 ? wide : narrow, tiles_n * ((double)((tiles_m - half_row) * parts) + 0.62 * (double)(half_row * half_parts)), (double)steps, cus);
     };
-    SplitPlan p;
-    if (partial_room) p = plan_split_k_nv16(M, N, K, cus, partial_room);
+    const Nv16Parts& p = plan.split;
     if (p.parts[0] > 1) {
         us += 3.683;
-        add(p.rows512 ? 512 : p.narrow ? 128 : 256, N, p.half_row, p.parts[0], p.parts[1], p.steps[0]);
+        add(p.width(), N, p.half_row, p.parts[0], p.parts[1], p.steps[0]);
         return us;
     }
-    Nv16Launch l[2];
-    const int n = plan_whole(M, N, K, cus, l);
-    for (int i = 0; i < n; ++i) add(l[i].width, l[i].n_cols, l[i].half_row, 1, 1, K >> 6);
-    return n > 1 ? us + 10.59 : us;
+    for (int i = 0; i < plan.launches; ++i) add(plan.launch[i].width, plan.launch[i].n_cols, plan.launch[i].half_row, 1, 1, K >> 6);
+    return plan.launches > 1 ? us + 10.59 : us;
+}
+
+Nv16Plan plan_nv16(int64_t M, int64_t N, int64_t K, size_t partial_room)
+{
+    const int cus = compute_units();
+    Nv16Plan p;
+    // few tiles, long K: every tile's K range shared by several workgroups, partial results added by a second kernel
+    if (partial_room) p.split = plan_split_k_nv16(M, N, K, cus, partial_room);
+    p.partial_bytes = partial_bytes(p.split, M, N);
+    if (!p.partial_bytes) p.launches = plan_whole(M, N, K, cus, p.launch);
+    p.us = nv16_us(M, N, K, cus, p);
+    return p;
 }
 
 hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                             const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
-                            bool out_f32, void* workspace, void* partial, size_t partial_room, hipStream_t st)
+                            bool out_f32, const Nv16Plan& plan, void* workspace, void* partial, hipStream_t st)
 {
     // 1. activations -> fp16 in operand order (workspace)
     const int64_t n_frags = round_up(M, 16) / 16 * (K / 128);
@@ -691,19 +678,12 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
     g.N = N;
     g.K = K;
     g.tiles_m = (int)((M + 127) / 128);
-    const int cus = device_cus();
-    if (partial) {
-        // few tiles, long K: every tile's K range shared by several workgroups, partial results added by a second kernel
-        const SplitPlan plan = plan_split_k_nv16(M, N, K, cus, partial_room);
-        if (plan.parts[0] > 1) return launch_parts(g, plan, out_f32, static_cast<float*>(partial), st);
-    }
-    Nv16Launch l[2];
-    const int n = plan_whole(M, N, K, cus, l);
-    for (int i = 0; i < n; ++i) {
-        g.n_first = l[i].n_first;
-        g.n_cols = l[i].n_cols;
-        g.half_row = l[i].half_row;
-        if ((e = launch_width(l[i].width, g, out_f32, st)) != hipSuccess) return e;
+    if (plan.partial_bytes) return launch_parts(g, plan.split, out_f32, static_cast<float*>(partial), st);
+    for (int i = 0; i < plan.launches; ++i) {
+        g.n_first = plan.launch[i].n_first;
+        g.n_cols = plan.launch[i].n_cols;
+        g.half_row = plan.launch[i].half_row;
+        if ((e = launch_width(plan.launch[i].width, g, out_f32, st)) != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -339,14 +339,11 @@ double codes_us(int64_t M, int64_t N, int64_t K, int cus, int* tile)
 // Up to 32 tokens there is nothing to gain: 194 products, 0.999 if every one went the faster way.  33 to 64 tokens where those kernels have no price (N > 12288, K > 8192, K <= 1024) stay with them.
 // Beyond M N K = 1.5e11 (200 us) both are bound by the same port and the estimates are off by more than what is between them: of 802 products there, M = 900 ... 4096, 0.99 of the time with this kernel,
 // 59 more than 3 % slower (17 % the worst; N = 10240, K = 8192, M = 2048: 333 us against 322); of 593 from 1e11 to 1.5e11 0.945, 27; of 1252 from 5e10 on 0.90, 25.
-int plan_nv_codes(int64_t M, int64_t N, int64_t K, size_t room)
+int plan_nv_codes(int64_t M, int64_t N, int64_t K, double other)
 {
-    if (M <= 32 || (double)M * (double)N * (double)K > 1.5e11) return -1;
-    const double few = gemm_nv_stream_us(M, N, K);
-    if (few == 0.0) return -1;
+    if (M <= 32 || (double)M * (double)N * (double)K > 1.5e11 || other == 0.0) return -1;
     int tile = -1;
-    const double us = codes_us(M, N, K, compute_units(), &tile);
-    return us < 0.92 * (few < __builtin_inf() ? few : nv16_us(M, N, K, room)) ? tile : -1;
+    return codes_us(M, N, K, compute_units(), &tile) < 0.92 * other ? tile : -1;
 }
 
 hipError_t launch_gemm_nv_codes(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes, const void* w_scales, const float* w_ts,

@@ -892,7 +892,6 @@ bool gemm_nv_streams(int64_t M, int64_t N, int64_t K)
 // fragments), and a share that grows with the sets, which all dequantize W.  Fitted to 907 products with cold weights (M = 17 ... 512), median error 2 %.
 double gemm_nv_stream_us(int64_t M, int64_t N, int64_t K)
 {
-    if (!gemm_nv_streams(M, N, K)) return __builtin_inf();
     const int per = (int)(((K >> 7) + kSkinnyWaves - 1) / kSkinnyWaves), mt = (int)((M + 15) / 16), cus = compute_units();
     if (M <= 64 && (per < 2 || per > 8 || N > 12288)) return 0.0;   // (other kernels: not priced)
     const double n_rb = (double)((N + 15) / 16), walkers = std::max(cus / mt / 8 * 8, 8), batches = (per + 1) / 2;

@@ -69,25 +69,38 @@ double gemm_stream_us(int64_t M, int64_t N, int64_t K);
 // fp32 partials of a split-K run (few tiles, long K: every tile's K range shared by several workgroups); 0 = not split
 size_t gemm_mx_split_k_bytes(int64_t M, int64_t N, int64_t K);
 
-// variant 0, 4: the fp16-activation kernel below (needs its workspace); 1..3: the tile kernels that dequantize both operands
+// variants 1..3: the tile kernels that dequantize both operands
 hipError_t launch_gemm_nvfp4(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                              const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
-                             bool out_f32, int variant, void* workspace, void* partial, size_t partial_room, hipStream_t st);
+                             bool out_f32, int variant, hipStream_t st);
+
+// A many-token NVFP4 product in parts along K (1: not in parts): numbers and K-steps of 64 of the parts of whole tiles, and of those of a last row of at most 64 tokens.
+struct Nv16Parts {
+    int parts[2] = {1, 1}, steps[2] = {0, 0};
+    bool narrow = false, rows512 = false;       // tiles of 128 columns; of 512
+    bool half_row = false;
+    int width() const { return rows512 ? 512 : narrow ? 128 : 256; }
+};
+// one launch of it in one piece: columns n_first .. n_first + n_cols - 1 in tiles of `width`, the last row's half tiles behind all others or not
+struct Nv16Launch {
+    int width, n_first, n_cols, half_row;
+};
+struct Nv16Plan {
+    Nv16Parts split;
+    size_t partial_bytes = 0;   // 0: not in parts, but in these launches
+    int launches = 0;
+    Nv16Launch launch[2] = {};
+    double us = 0.0;            // what it is estimated to take
+};
 
 // NVFP4 product for many tokens: the activations are dequantized once to fp16 into `workspace`
-// (nv16_workspace_bytes(M, K) bytes, 256-byte aligned), then multiplied against W dequantized on the fly
+// (nv16_workspace_bytes(M, K) bytes, 256-byte aligned), then multiplied against W dequantized on the fly.  plan: with that room for fp32 partials (with little, in
+// fewer parts or not split).
 size_t nv16_workspace_bytes(int64_t M, int64_t K);
+Nv16Plan plan_nv16(int64_t M, int64_t N, int64_t K, size_t partial_room);
 hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                             const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
-                            bool out_f32, void* workspace, void* partial, size_t partial_room, hipStream_t st);
-// fp32 partials of a split-K run of that product (`partial`, of partial_room bytes: with fewer than this, in fewer parts or not split; null: never
-// split); 0 = not split
-size_t nv16_split_k_bytes(int64_t M, int64_t N, int64_t K);
-
-// what that takes with partial_room bytes for partials, in microseconds
-double nv16_us(int64_t M, int64_t N, int64_t K, size_t partial_room);
-// whether it runs split with that room
-bool nv16_splits(int64_t M, int64_t N, int64_t K, size_t partial_room);
+                            bool out_f32, const Nv16Plan& plan, void* workspace, void* partial, hipStream_t st);
 
 // What the workgroups of a launch take, microseconds, `steps` of K each: `per_cu` to a compute unit in whole rounds, each (fixed + steps x step), and a last
 // round that is not whole: on units of their own (alone + steps x (alone_step + alone_busy x the share of the units)), or some of them two to a unit.
@@ -104,17 +117,17 @@ inline double tile_rounds_us(const TileRounds& c, double workgroups, double step
     return t + c.pair + steps * (c.pair_step + c.pair_busy * (rest - cus) / cus);
 }
 
-// NVFP4 product of 33 tokens and more, both operands dequantized inside it, in one launch without a workspace.  plan: the tile that suits it, or -1 where the few-token
-// kernels or the one above with that room for partials are the better choice.
-int plan_nv_codes(int64_t M, int64_t N, int64_t K, size_t room);
+// NVFP4 product of 33 tokens and more, both operands dequantized inside it, in one launch without a workspace.  plan: the tile that suits it, or -1 where what
+// takes `other` microseconds otherwise is the better choice.
+int plan_nv_codes(int64_t M, int64_t N, int64_t K, double other);
 hipError_t launch_gemm_nv_codes(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes, const void* w_scales, const float* w_ts,
                                 int64_t M, int64_t N, int64_t K, void* out, bool out_f32, int tile, hipStream_t st);
 
 // few-token weight-streaming GEMM, both formats, operands in GEMM layout: every shape up to 64 tokens, and above that those that
 // gemm_nv_streams accepts (NVFP4) and gemm_stream_us prices (MXFP4)
 bool gemm_nv_streams(int64_t M, int64_t N, int64_t K);
-// what they take for an NVFP4 product of more than 16 tokens, in microseconds, where a set of workgroups per 16 tokens does it; 0: they take it, whatever
-// that is; infinity: they do not take it
+// what they take for an NVFP4 product of more than 16 tokens, in microseconds, where a set of workgroups per 16 tokens does it (gemm_nv_streams); 0: they take
+// it, whatever that is
 double gemm_nv_stream_us(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_skinny(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes,
                               const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, int fmt, void* out,

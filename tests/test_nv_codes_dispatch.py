@@ -33,17 +33,19 @@ def test_tiles_of_products_in_one_launch(host, tile):
         assert launch["grid"][0] == -(-M // (16 * tile[0])) * -(-N // columns)
 
 
-@pytest.mark.parametrize("M,N,K", [(192, 4096, 4096), (320, 8192, 8192), (600, 520, 2048), (320, 8192, 28672), (128, 28672, 4096), (33, 57344, 8192), (640, 2048, 2048), (2048, 57344, 8192), (16, 8192, 8192)])
-def test_the_fastest_size_is_one_of_the_two_and_room_for_parts_means_parts(host, M, N, K):
+@pytest.mark.parametrize("M,N,K,codes", [(192, 4096, 4096, True), (320, 8192, 8192, True), (128, 4096, 4096, True), (600, 520, 2048, True), (320, 8192, 28672, False), (300, 10240, 8192, False),
+                                         (128, 28672, 4096, True), (33, 57344, 8192, False), (640, 2048, 2048, True), (2048, 57344, 8192, False), (16, 8192, 8192, False)])
+def test_more_room_never_leads_to_the_slower_kernel(host, M, N, K, codes):
+    """The kernel follows the prices, not the bytes that are left over: with the size for parts and with far more, what is chosen with the size that
+    promises the fastest call; that size is one of the two, and the larger only where the product runs in parts."""
     need, split, fastest = host(["device", 0, 256], *(["bytes", op, M, N, K, NV] for op in (OP_GEMM, OP_SPLIT, OP_FASTEST)))[1:]
-    assert fastest in (need, split)
-    runs = host(["device", 0, 256], ["gemm", M, N, K, NV, split])[1]
-    if split > need:
-        assert "nv16_reduce" in runs[-1]["kernel"]
-    if fastest < split:   # the kernel that the size is for
-        assert "gemm_nv_codes" in host(["device", 0, 256], ["gemm", M, N, K, NV, fastest])[1][0]["kernel"]
-    if M <= 32:
-        assert not any("gemm_nv_codes" in r["kernel"] for r in runs)
+    runs = host(["device", 0, 256], *(["gemm", M, N, K, NV, room] for room in (need, fastest, split, split + (1 << 30))))[1:]
+    names = [[r["kernel"] for r in run] for run in runs]
+    assert names[1] == names[2] == names[3]
+    assert all(("gemm_nv_codes" in n[0]) == codes for n in names[1:])
+    assert fastest == (split if "nv16_reduce" in names[2][-1] else need)
+    if split > need and not codes:
+        assert "nv16_reduce" in names[2][-1] and "nv16_reduce" not in names[0][-1]
 
 
 @pytest.mark.parametrize("M,N,K", [(201, 4096, 14336), (128, 4096, 28672), (64, 4096, 4096)])
