@@ -40,6 +40,34 @@ def test_products_are_exact(fp4, tile):
             assert torch.equal(out, Y.to(out.dtype)), (M, N, K, flags)
 
 
+@pytest.mark.parametrize("tile", list(SHAPES))
+def test_every_scale_and_other_tensor_scales(fp4, tile):
+    """Every finite E4M3 scale of either operand, zero and subnormal ones too, and tensor scales that are not 1.  A row of X has one group that is not zero, so that an output is a single
+    s_x s_w times a sum of sixteen code products -- multiples of 1/4 up to 576, and 8 bits of scales: exact in fp32 -- times the rounded product of the tensor scales."""
+    import torch
+    M, N, K = SHAPES[tile][-1]
+    G = K // 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(sum(tile) + 100)
+    at, wt = torch.full((1,), 0.0371, device="cuda"), torch.full((1,), 2.3e-3, device="cuda")
+    one = torch.ones(1, device="cuda")
+    for first in range(0, 127, M):
+        print(f"[case] nvfp4 codes scales tile={tile} M={M} N={N} K={K} from {first}", flush=True)
+        rows = torch.arange(M, device="cuda")
+        asc = torch.zeros(M, G, dtype=torch.uint8, device="cuda")
+        asc[rows, (first + 5 * rows) % G] = ((first + rows) % 127).to(torch.uint8)
+        ac = torch.randint(0, 256, (M, K // 2), device="cuda", dtype=torch.uint8, generator=g)
+        wsc = torch.randint(0, 127, (N, G), device="cuda", dtype=torch.uint8, generator=g)
+        wc = torch.randint(0, 256, (N, K // 2), device="cuda", dtype=torch.uint8, generator=g)
+        assert len(wsc.unique()) == 127
+        a, w = (fp4.fp4_dequantize(c.view(-1), s.view(-1), one, r, K, fp4.NVFP4, flags=fp4.OUT_F32).double() for c, s, r in ((ac, asc, M), (wc, wsc, N)))
+        Y = (a @ w.t()).float() * (at * wt)
+        for flags in (fp4.OUT_F32, 0):
+            room = torch.empty(fp4.workspace_bytes(fp4.OP_GEMM, M, N, K, fp4.NVFP4, flags), dtype=torch.uint8, device="cuda")
+            out = fp4.fp4_gemm(ac.view(-1), asc.view(-1), at, wc.view(-1), wsc.view(-1), wt, M, N, K, fp4.NVFP4, flags=flags, workspace=room)
+            assert torch.equal(out, Y.to(out.dtype)), (M, N, K, flags)
+
+
 def test_replays_of_a_graph(fp4):
     """Captured, and replayed with work of its own in between: every replay is the eager result."""
     import torch
