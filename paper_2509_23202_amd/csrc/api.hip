@@ -251,7 +251,7 @@ fp4mr_status_t fp4_gemm(const void* a_codes, const void* a_scales, const float* 
         const bool few = gemm_nv_streams(M, N, K);
         Nv16Plan many;
         if (!few) many = plan_nv16(M, N, K, partial_room);
-        const int tile = no_codes || M <= 32 ? -1 : plan_nv_codes(M, N, K, few ? gemm_nv_stream_us(M, N, K) : many.us);
+        const int tile = no_codes || M <= 32 ? -1 : plan_nv_codes(M, N, K, few ? gemm_nv_stream_us(M, N, K) : many.us, few);
         if (tile >= 0)
             e = launch_gemm_nv_codes(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale, M, N, K, out, out_f32, tile, st);
         else if (few)
@@ -361,7 +361,7 @@ size_t fp4_workspace_bytes(int op, int64_t M, int64_t N, int64_t K, fp4mr_fmt_t 
             extra = gemm_mx_split_k_bytes(M, N, K);
         } else if (many) {
             const Nv16Plan plan = plan_nv16(M, N, K, SIZE_MAX);
-            const bool codes = options().gemm_variant != kVariantNvNoCodes && plan_nv_codes(M, N, K, plan.us) >= 0;
+            const bool codes = options().gemm_variant != kVariantNvNoCodes && plan_nv_codes(M, N, K, plan.us, false) >= 0;
             if (op == FP4MR_OP_GEMM_SPLIT_K || !codes) extra = plan.partial_bytes;
         }
         if (extra) n = align256(n) + extra;

@@ -435,7 +435,7 @@ Nv16Parts search_split_k_nv16(int64_t M, int64_t N, int64_t K, int cus, size_t m
     const int64_t row_wgs = (plan.narrow ? (N + 127) / 128 : (N + 255) / 256) * plan.parts[0], all = tiles_m * row_wgs;
     plan.half_row = (M - 1) % 128 < 64 && (K >= 4096 || (all > cus && all - row_wgs <= cus));
     const int64_t cols = (N + 511) / 512, rows = tiles_m - 1;
-    plan.rows512 = !plan.narrow && K >= 6656 && tiles_w * plan.parts[0] > cus && tiles_m * cols * plan.parts[0] <= cus;   // (see launch_wide)
+    plan.rows512 = !plan.narrow && K >= 6656 && tiles_w * plan.parts[0] > cus && tiles_m * cols * plan.parts[0] <= cus;   // (see wide())
     if (!plan.rows512 || !plan.half_row || rows == 0) return plan;
     // One workgroup per compute unit, and a part of a half tile takes 0.62 of a whole one's time: with as many parts for either as
     // suit each other, parts are shorter.  Microseconds: steps of the longer part times 1.38, and the partials as above.  M = 320, K = 8192,
@@ -621,26 +621,31 @@ size_t nv16_workspace_bytes(int64_t M, int64_t K)
     return (size_t)(round_up(M, 16) * K * 2);
 }
 
-// Price of the whole call: the fp16 copy of X, the launches of the plan (a half tile counts as 0.62 of a whole one), the sum of the parts.  Fitted to 2263 products with
-// cold weights (M = 65 ... 4096, N = 512 ... 57344, K = 1024 ... 28672), median error 4 %.
+// Price of the whole call: the fp16 copy of X, the launches of the plan, the sum of the parts, the output.  A half tile counts as 0.7 of a whole one; where a unit has one whole tile at most and some a half
+// one besides, the launch takes a way of 0.3 from whole tiles alone to as many whole ones; parts count half as the longest of them and half as their mean.  Fitted to 3902 products on two cards (M = 33 ... 4096, N = 256 ... 57344, K = 256 ... 28672, half of them
+// multiples of 256), where they run in parts with room for them and without: median error 3 %, one in ten off by more than 10 %.
 static double nv16_us(int64_t M, int64_t N, int64_t K, int cus, const Nv16Plan& plan)
 {
-    constexpr TileRounds narrow = {2, 9.621, 0.8373, 6.093, 0.3200, 0.1981, 9.981, 0.5480, 0.3470}, wide = {2, 25.06, 1.3711, 8.275, 0.1857, 0.9045, 18.40, 0.9649, 0.5646},
-                         rows512 = {1, 4.879, 1.6131, 15.98, 0.7689, 0.6808};
+    constexpr TileRounds narrow = {2, 5.7906, 0.6708, 0.0000, 0.4982, 0.0202, 1.9628, 0.6652, 0.1387}, wide = {2, 10.5536, 1.2001, 2.3438, 0.3651, 0.5578, 6.5882, 1.0898, 0.2570},
+                         rows512 = {1, 4.023, 1.3912, 4.023, 0.8982, 0.4930};   // (one round at most)
     const int64_t tiles_m = (M + 127) / 128;
-    double us = 4.160 + 0.614e-6 * (double)M * (double)K;
-    auto add = [&](int width, int64_t cols, int64_t half_row, int64_t parts, int64_t half_parts, int64_t steps) {
-        const double tiles_n = (double)((cols + width - 1) / width);
-        us += tile_rounds_us(width == 512 ? rows512 : width == 256 ? wide : narrow, tiles_n * ((double)((tiles_m - half_row) * parts) + 0.62 * (double)(half_row * half_parts)), (double)steps, cus);
+    double us = 6.579 + 0.3803e-6 * (double)M * (double)K + 0.8693e-6 * (double)M * (double)N;
+    auto add = [&](int width, int64_t cols, int64_t half_row, int64_t parts, int64_t half_parts, double steps) {
+        const TileRounds& c = width == 512 ? rows512 : width == 256 ? wide : narrow;
+        const double tiles_n = (double)((cols + width - 1) / width), whole = tiles_n * (double)((tiles_m - half_row) * parts), half = tiles_n * (double)(half_row * half_parts);
+        if (c.per_cu == 2 && whole <= cus && whole + half > cus && whole + half <= 2 * cus)
+            us += 0.7 * tile_rounds_us(c, cus, steps, cus) + 0.3 * tile_rounds_us(c, whole + half, steps, cus);
+        else
+            us += tile_rounds_us(c, whole + 0.7 * half, steps, cus);
     };
     const Nv16Parts& p = plan.split;
     if (p.parts[0] > 1) {
-        us += 3.683;
-        add(p.width(), N, p.half_row, p.parts[0], p.parts[1], p.steps[0]);
+        us += 6.429 + 0.1332e-6 * (double)plan.partial_bytes;
+        add(p.width(), N, p.half_row, p.parts[0], p.parts[1], 0.5 * (p.steps[0] + (double)(K >> 6) / p.parts[0]));
         return us;
     }
-    for (int i = 0; i < plan.launches; ++i) add(plan.launch[i].width, plan.launch[i].n_cols, plan.launch[i].half_row, 1, 1, K >> 6);
-    return plan.launches > 1 ? us + 10.59 : us;
+    for (int i = 0; i < plan.launches; ++i) add(plan.launch[i].width, plan.launch[i].n_cols, plan.launch[i].half_row, 1, 1, (double)(K >> 6));
+    return plan.launches > 1 ? us + 7.763 : us;
 }
 
 Nv16Plan plan_nv16(int64_t M, int64_t N, int64_t K, size_t partial_room)

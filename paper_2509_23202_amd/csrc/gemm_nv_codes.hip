@@ -295,24 +295,24 @@ hipError_t launch_codes(const NvCodesArgs& g, hipStream_t st)
     return hipGetLastError();
 }
 
-// What a launch of one of the tiles takes, microseconds: `once`, and tile_rounds_us of its workgroups with a group's steps of 64.  Fitted to launches of every tile on 3520 products with cold
-// weights (M = 17 ... 4096, N = 512 ... 57344, K = 1024 ... 28672; median error 2 %): the tile that this takes is on average 0.1 % slower
-// than the best of the nine, those together 0.8 % than fifteen.
+// What a launch of one of the tiles takes, microseconds: `once`, and tile_rounds_us of its workgroups, their steps (of 64) two thirds those of the
+// longest share of K and one third the mean's.  Fitted to 25 000 launches of 5053 products on two cards (M = 33 ... 4096, N = 256 ... 57344, K = 256 ... 28672, half of them multiples of 256, whose
+// launches are whole rounds more often than others), five of the tiles each: the median error is 2 %, one in ten is off by more than 5 to 8 %.
 struct CodesTile {
     int tm, tn, nwn, kw;
     double once;
     TileRounds rounds;
 };
 constexpr CodesTile kCodesTiles[] = {
-    {2, 2, 1, 8, 1.547, {1, 2.167, 0.501, 1.968, 0.429, 0.106}},
-    {2, 4, 1, 8, 2.149, {1, 2.742, 0.710, 1.932, 0.602, 0.145}},
-    {4, 4, 1, 8, 1.735, {1, 2.804, 1.066, 2.768, 0.797, 0.210}},
-    {3, 4, 1, 4, 3.081, {2, 2.181, 0.823, 0.631, 0.467, 0.054, 1.808, 0.774, 0.101}},
-    {4, 4, 1, 4, 3.937, {2, 2.214, 0.964, 0.000, 0.519, 0.073, 1.287, 0.858, 0.148}},
-    {5, 4, 1, 4, 4.285, {2, 2.398, 1.158, 0.000, 0.615, 0.070, 1.546, 1.017, 0.188}},
-    {6, 4, 1, 4, 4.615, {2, 2.515, 1.322, 0.000, 0.683, 0.087, 1.592, 1.174, 0.202}},
-    {7, 4, 2, 2, 5.628, {2, 4.186, 1.383, 0.193, 0.833, 0.077, 2.752, 1.294, 0.201}},
-    {8, 4, 2, 2, 6.320, {2, 4.302, 1.562, 0.000, 0.893, 0.081, 2.344, 1.465, 0.222}},
+    {2, 2, 1, 8, 0.000, {1, 2.212, 0.472, 3.913, 0.457, 0.075}},
+    {2, 4, 1, 8, 0.000, {1, 3.231, 0.658, 4.261, 0.625, 0.135}},
+    {4, 4, 1, 8, 0.000, {1, 3.426, 1.020, 4.766, 0.827, 0.217}},
+    {3, 4, 1, 4, 3.866, {2, 2.879, 0.783, 0.000, 0.469, 0.073, 1.288, 0.768, 0.128}},
+    {4, 4, 1, 4, 4.086, {2, 3.070, 0.907, 0.000, 0.507, 0.131, 1.458, 0.875, 0.140}},
+    {5, 4, 1, 4, 4.522, {2, 3.326, 1.097, 0.000, 0.589, 0.130, 1.663, 1.038, 0.166}},
+    {6, 4, 1, 4, 4.925, {2, 3.672, 1.251, 0.000, 0.632, 0.179, 1.711, 1.193, 0.191}},
+    {7, 4, 2, 2, 6.108, {2, 4.706, 1.440, 0.000, 0.742, 0.216, 2.543, 1.339, 0.206}},
+    {8, 4, 2, 2, 6.761, {2, 4.906, 1.625, 0.000, 0.795, 0.225, 2.328, 1.496, 0.305}},
 };
 
 // the cheapest of them and its price
@@ -322,7 +322,8 @@ double codes_us(int64_t M, int64_t N, int64_t K, int cus, int* tile)
     for (int i = 0; i < (int)(sizeof(kCodesTiles) / sizeof(kCodesTiles[0])); ++i) {
         const CodesTile& c = kCodesTiles[i];
         const double wgs = (double)((M + 16 * c.tm - 1) / (16 * c.tm)) * (double)((N + 16 * c.tn * c.nwn - 1) / (16 * c.tn * c.nwn));
-        const double us = c.once + tile_rounds_us(c.rounds, wgs, (double)(((K >> 7) + c.kw - 1) / c.kw * 2), cus);
+        const double shares = (double)(K >> 7) / c.kw, steps = (4.0 * (double)(((K >> 7) + c.kw - 1) / c.kw) + 2.0 * shares) / 3.0;
+        const double us = c.once + tile_rounds_us(c.rounds, wgs, steps, cus);
         if (us < best) {
             best = us;
             *tile = i;
@@ -333,17 +334,17 @@ double codes_us(int64_t M, int64_t N, int64_t K, int cus, int* tile)
 
 }  // namespace
 
-// Which NVFP4 products this kernel takes: those of more than 32 tokens that it is estimated to do in 0.92 of what the others take, for an estimate of theirs is off by 2 - 4 % mostly
-// and 11 % in one of ten.  Of 2263 products timed that were the kernel for many tokens' it takes 82 %; all of them together take 0.762 of the time (0.755 if every one went the faster way), 3 are
-// more than 3 % slower, the worst 7 %; with 0.95 0.759, 13 and 12 %.  Of the few-token kernels' 713 with 33 to 512 tokens and N <= 12288, 0.83.
+// Which NVFP4 products this kernel takes: those of more than 32 tokens that it is estimated to do in 0.98 of what the kernel for many tokens takes, in 0.92 of what the few-token kernels do (a few
+// microseconds, of which two more are quickly lost), or in 0.90 where there are more than 5e7 outputs, whose stores put the estimates off by 8 % (with 0.97 there 4 products more were slower, 20 % the worst).
+// Of 5053 products timed both ways (as above, M N K up to 4e11) it takes 3718; all of them together take 0.796 of the time that the others alone do (0.793 if every one went the faster way), and 12 are more
+// than 3 % slower for it, 6 % the worst.  (With last rounds that are whole priced like those in front of them, 0.92 for all, and never beyond M N K = 1.5e11: 0.800 and 59, 15 % the worst.  M = 1024, N = 8192,
+// K = 8192 and 14336 118 and 205 us, with this kernel 126 and 221; M = 512, N = 16384, K = 8192 120 and 130; M = 192, N = 57344, K = 5120 107 and 118.)
 // Up to 32 tokens there is nothing to gain: 194 products, 0.999 if every one went the faster way.  33 to 64 tokens where those kernels have no price (N > 12288, K > 8192, K <= 1024) stay with them.
-// Beyond M N K = 1.5e11 (200 us) both are bound by the same port and the estimates are off by more than what is between them: of 802 products there, M = 900 ... 4096, 0.99 of the time with this kernel,
-// 59 more than 3 % slower (17 % the worst; N = 10240, K = 8192, M = 2048: 333 us against 322); of 593 from 1e11 to 1.5e11 0.945, 27; of 1252 from 5e10 on 0.90, 25.
-int plan_nv_codes(int64_t M, int64_t N, int64_t K, double other)
+int plan_nv_codes(int64_t M, int64_t N, int64_t K, double other, bool few)
 {
-    if (M <= 32 || (double)M * (double)N * (double)K > 1.5e11 || other == 0.0) return -1;
+    if (M <= 32 || other == 0.0) return -1;
     int tile = -1;
-    return codes_us(M, N, K, compute_units(), &tile) < 0.92 * other ? tile : -1;
+    return codes_us(M, N, K, compute_units(), &tile) < (M * N > 50000000 ? 0.90 : few ? 0.92 : 0.98) * other ? tile : -1;
 }
 
 hipError_t launch_gemm_nv_codes(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes, const void* w_scales, const float* w_ts,

@@ -102,24 +102,28 @@ hipError_t launch_gemm_nv16(const void* a_codes, const void* a_scales, const flo
                             const void* w_scales, const float* w_ts, int64_t M, int64_t N, int64_t K, void* out,
                             bool out_f32, const Nv16Plan& plan, void* workspace, void* partial, hipStream_t st);
 
-// What the workgroups of a launch take, microseconds, `steps` of K each: `per_cu` to a compute unit in whole rounds, each (fixed + steps x step), and a last
-// round that is not whole: on units of their own (alone + steps x (alone_step + alone_busy x the share of the units)), or some of them two to a unit.
+// What the workgroups of a launch take, microseconds, `steps` of K each: `per_cu` to a compute unit in rounds, each (fixed + steps x step), and a last round, whole or
+// not: on units of their own (alone + steps x (alone_step + alone_busy x the share of the units)), or some of them two to a unit.
 struct TileRounds {
     int per_cu;
     double fixed, step, alone, alone_step, alone_busy, pair, pair_step, pair_busy;
 };
 inline double tile_rounds_us(const TileRounds& c, double workgroups, double steps, int cus)
 {
-    const double slots = (double)cus * c.per_cu, full = (double)(int64_t)(workgroups / slots), rest = workgroups - full * slots;
+    const double slots = (double)cus * c.per_cu;
+    double full = (double)(int64_t)(workgroups / slots), rest = workgroups - full * slots;
+    if (rest <= 0.0 && full > 0.0) {   // (a last round that is whole is no faster for it: priced as one of many, 512 workgroups were 15 % too cheap)
+        full -= 1.0;
+        rest = slots;
+    }
     const double t = full * (c.fixed + steps * c.step);
-    if (rest <= 0.0) return t;
     if (rest <= cus) return t + c.alone + steps * (c.alone_step + c.alone_busy * rest / cus);
     return t + c.pair + steps * (c.pair_step + c.pair_busy * (rest - cus) / cus);
 }
 
 // NVFP4 product of 33 tokens and more, both operands dequantized inside it, in one launch without a workspace.  plan: the tile that suits it, or -1 where what
-// takes `other` microseconds otherwise is the better choice.
-int plan_nv_codes(int64_t M, int64_t N, int64_t K, double other);
+// takes `other` microseconds otherwise, on the few-token kernels or the one for many tokens, is the better choice.
+int plan_nv_codes(int64_t M, int64_t N, int64_t K, double other, bool few);
 hipError_t launch_gemm_nv_codes(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes, const void* w_scales, const float* w_ts,
                                 int64_t M, int64_t N, int64_t K, void* out, bool out_f32, int tile, hipStream_t st);
 

@@ -10,7 +10,7 @@ SHAPES = {
     (2, 2, 1, 8): [(350, 76, 128), (273, 71, 256), (424, 60, 384), (302, 68, 640), (514, 95, 1664)],
     (2, 4, 1, 8): [(489, 572, 640), (345, 758, 768), (545, 485, 1664), (518, 557, 2944)],
     (4, 4, 1, 8): [(100, 6261, 1920), (49, 9436, 1664), (52, 8387, 2944)],
-    (3, 4, 1, 4): [(65, 3326, 256), (65, 3152, 128), (594, 432, 1408), (65, 5571, 768), (133, 3658, 2944)],
+    (3, 4, 1, 4): [(65, 3326, 256), (65, 3152, 128), (133, 3658, 1408), (65, 5571, 768), (133, 3658, 2944)],
     (4, 4, 1, 4): [(99, 5764, 128), (107, 5469, 256), (103, 5496, 384), (49, 8631, 1152)],
     (5, 4, 1, 4): [(66, 8720, 128), (129, 6126, 256), (66, 8772, 384), (71, 8270, 1152)],
     (6, 4, 1, 4): [(81, 8568, 128), (278, 4907, 256), (86, 8752, 384), (274, 4237, 1152)],
@@ -33,7 +33,7 @@ def test_tiles_of_products_in_one_launch(host, tile):
         assert launch["grid"][0] == -(-M // (16 * tile[0])) * -(-N // columns)
 
 
-@pytest.mark.parametrize("M,N,K,codes", [(192, 4096, 4096, True), (320, 8192, 8192, True), (128, 4096, 4096, True), (600, 520, 2048, True), (320, 8192, 28672, False), (300, 10240, 8192, False),
+@pytest.mark.parametrize("M,N,K,codes", [(192, 4096, 4096, True), (320, 8192, 8192, True), (128, 4096, 4096, True), (600, 520, 2048, True), (320, 8192, 28672, False), (300, 10240, 14336, False),
                                          (128, 28672, 4096, True), (33, 57344, 8192, False), (640, 2048, 2048, True), (2048, 57344, 8192, False), (16, 8192, 8192, False)])
 def test_more_room_never_leads_to_the_slower_kernel(host, M, N, K, codes):
     """The kernel follows the prices, not the bytes that are left over: with the size for parts and with far more, what is chosen with the size that
@@ -54,8 +54,9 @@ def test_mxfp4_is_always_fastest_with_room_for_parts(host, M, N, K):
     assert fastest == split
 
 
-@pytest.mark.parametrize("M,N,K,taken", [(1788, 10240, 8192, True), (1789, 10240, 8192, False), (2048, 10240, 8192, False)])
-def test_the_largest_products_stay_with_the_kernel_for_many_tokens(host, M, N, K, taken):
+@pytest.mark.parametrize("M,N,K", [(1024, 8192, 8192), (1024, 8192, 14336), (512, 16384, 8192), (2048, 4096, 8192), (192, 57344, 4096), (192, 57344, 5120), (768, 10240, 14336), (2048, 10240, 8192)])
+def test_a_whole_last_round_is_priced_as_a_last_one(host, M, N, K):
+    """Launches that fill the last round, or nearly: 4 to 12 % slower on this kernel, which price it below the others where a round that is whole counts as one of many."""
     fastest = host(["device", 0, 256], ["bytes", OP_FASTEST, M, N, K, NV])[1]
     runs = host(["device", 0, 256], ["gemm", M, N, K, NV, fastest])[1]
-    assert any("gemm_nv_codes" in r["kernel"] for r in runs) == taken
+    assert not any("gemm_nv_codes" in r["kernel"] for r in runs)
