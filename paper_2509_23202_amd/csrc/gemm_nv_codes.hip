@@ -334,17 +334,17 @@ double codes_us(int64_t M, int64_t N, int64_t K, int cus, int* tile)
 
 }  // namespace
 
-// Which NVFP4 products this kernel takes: those of more than 32 tokens that it is estimated to do in 0.98 of what the kernel for many tokens takes, in 0.92 of what the few-token kernels do (a few
-// microseconds, of which two more are quickly lost), or in 0.90 where there are more than 5e7 outputs, whose stores put the estimates off by 8 % (with 0.97 there 4 products more were slower, 20 % the worst).
-// Of 5053 products timed both ways (as above, M N K up to 4e11) it takes 3718; all of them together take 0.796 of the time that the others alone do (0.793 if every one went the faster way), and 12 are more
-// than 3 % slower for it, 6 % the worst.  (With last rounds that are whole priced like those in front of them, 0.92 for all, and never beyond M N K = 1.5e11: 0.800 and 59, 15 % the worst.  M = 1024, N = 8192,
-// K = 8192 and 14336 118 and 205 us, with this kernel 126 and 221; M = 512, N = 16384, K = 8192 120 and 130; M = 192, N = 57344, K = 5120 107 and 118.)
+// Which NVFP4 products this kernel takes: those of more than 32 tokens that it is estimated to do in 0.98 of what the kernel for many tokens takes, in 0.95 of what the few-token kernels do (where it is estimated at
+// 0.92 to 0.95 of them it took 0.98 on average, at 0.95 to 0.97 0.995), or in 0.90 where there are more than 5e7 outputs, whose stores put the estimates off by 8 % (with 0.97 there 4 products more were
+// slower, 20 % the worst).  Of 5053 products timed both ways (as above, M N K up to 4e11) it takes 3737; all of them together take 0.796 of the time that the others alone do (0.793 if every one went the faster
+// way), and 16 are more than 3 % slower for it, 6 % the worst.  (With last rounds that are whole priced like those in front of them, 0.92 for all, and never beyond M N K = 1.5e11: 0.800 and 59, 15 % the worst.
+// M = 1024, N = 8192, K = 8192 and 14336 118 and 205 us, with this kernel 126 and 221; M = 512, N = 16384, K = 8192 120 and 130; M = 192, N = 57344, K = 5120 107 and 118.)
 // Up to 32 tokens there is nothing to gain: 194 products, 0.999 if every one went the faster way.  33 to 64 tokens where those kernels have no price (N > 12288, K > 8192, K <= 1024) stay with them.
 int plan_nv_codes(int64_t M, int64_t N, int64_t K, double other, bool few)
 {
     if (M <= 32 || other == 0.0) return -1;
     int tile = -1;
-    return codes_us(M, N, K, compute_units(), &tile) < (M * N > 50000000 ? 0.90 : few ? 0.92 : 0.98) * other ? tile : -1;
+    return codes_us(M, N, K, compute_units(), &tile) < (M * N > 50000000 ? 0.90 : few ? 0.95 : 0.98) * other ? tile : -1;
 }
 
 hipError_t launch_gemm_nv_codes(const void* a_codes, const void* a_scales, const float* a_ts, const void* w_codes, const void* w_scales, const float* w_ts,
