@@ -6,12 +6,13 @@
 // something in common most rotated channels are small differences of large sums: with an offset of 100 under unit noise
 // the entries were off by 1 % of that scale, and diagonal entries could come out negative.)
 //   many rows  hessian_pack_kernel   X -> the rotated rows as two fp16 parts, scaled by column, in the workspace as the MFMA takes them
-//              hessian_pair_kernel   X'^T X' on the fp16 MFMA: the three products above 2^-23 of the whole
+//              hessian_tile_kernel   X'^T X' on the fp16 MFMA, a tile to a workgroup: the three products above 2^-23 of the whole
+//              hessian_pair_kernel   the same, two tiles to a workgroup, from 2048 or 4096 rows on where they fill the chip (the rule stands at the launch)
 //              hessian_part_kernel   the same for the tiles beyond whole rounds of the chip
 //   few rows   hessian_rotate_kernel X -> the rotated rows in fp32, in the workspace, eight rows of a column side by side
 //              hessian_split_kernel  X'^T X' on the bf16 MFMA, both factors split into three bf16 parts: the six products above
 //                                    2^-24 of the whole
-// 8192 rows at K = 4096: 0.45 ms (0.86 with six bf16 products, 4.15 on the fp32 MFMA over both triangles).  Largest error over
+// 8192 rows at K = 4096: 0.39 - 0.42 ms (0.86 with six bf16 products, 4.15 on the fp32 MFMA over both triangles).  Largest error over
 // sqrt(h_ii h_jj), T = 8192, b = 128, K = 1024 / 4096, bf16 -> fp16: normal rows with loud channels 9.3e-7 / 1.0e-6 -> 2.0e-7 / 5.6e-7, offset
 // 30 9.5e-7 / 8.9e-7 -> 1.2e-7 / 4.6e-7, offset 100 6.2e-7 / 7.6e-7 -> 1.0e-7 / 3.6e-7, a channel of every 64th row 3000 times as large
 // 9.2e-7 / 1.0e-6 -> 3.0e-7 / 5.2e-7 (for adding up four sums of 32 rows before they meet the large one).  Of one row alone, with nothing to
